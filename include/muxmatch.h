@@ -140,7 +140,7 @@ typedef struct {
  * went without the kernels that use such waits (every solve starts with all of them again).  The
  * result is exact either way; a set bit says the solve was slower than it should have been. */
 #define MF_FALLBACK_TEAMS    1  /* several workgroups per chain of bids          */
-#define MF_FALLBACK_SEARCHES 2  /* shortest-augmenting-path searches             */
+#define MF_FALLBACK_SEARCHES 2  /* shortest-augmenting-path searches (and phases on short lists) */
 
 /*
  * Creates a context bound to HIP device `device` and to `hip_stream` (a
@@ -328,6 +328,13 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            steps; "path_grid" (0: one workgroup per compute unit), "path_width" (1024 epsilons),
  *            "path_frontier_rows" (1024), "path_pull" (0), "path_spin_limit" (2^22 polls a workgroup
  *            waits for the others before all give up; see mf_result.fallbacks)
+ *   lists    "core" (1; 0: never): the phases from the one on in which a list of every line's best entries
+ *            reaches "core_depth" (12) epsilons below the best run on such lists, in one launch;
+ *            "core_many" (4) / "core_few" (32): chain steps between two looks at the list of bidders,
+ *            "core_after" (128): chain steps after which the last bidders are searched for,
+ *            "core_width" (8192): label window of those searches, in epsilons, "core_refine" (16):
+ *            epsilon, in weight units, at or below which a complete phase is followed by an attempt
+ *            to prove its assignment optimal at once
  */
 int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
 

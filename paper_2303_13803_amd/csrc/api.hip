@@ -128,6 +128,13 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     ctx->path_grid = 0;
     ctx->path_after = 256;
     ctx->path_spin_limit = 1u << 22;
+    ctx->core = 1;
+    ctx->core_depth_eps = 12;
+    ctx->core_many = 4;
+    ctx->core_few = 32;
+    ctx->core_after = 128;
+    ctx->core_refine = 16;
+    ctx->core_width = 8192;
     {
         hipDeviceProp_t prop;
         ctx->n_cus = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.multiProcessorCount : 0;
@@ -175,8 +182,20 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(dev_alloc(&ctx->path_base, nm + 8));
     TRY(dev_alloc(&ctx->edge_count, nm));
     TRY(dev_alloc(&ctx->edge_start, nm + 1));
-    TRY(dev_alloc(&ctx->path_tree, nm));
-    TRY(dev_alloc(&ctx->path_parent, nm));
+    {
+        const size_t fewer = (size_t)(max_n < max_m ? max_n : max_m);
+        TRY(dev_alloc(&ctx->core_entries[0], fewer * MF_CORE_LIST));
+        TRY(dev_alloc(&ctx->core_entries[1], nm * MF_CORE_LIST));
+        for (int k = 0; k < 2; ++k) { TRY(dev_alloc(&ctx->core_bound[k], nm)); TRY(dev_alloc(&ctx->core_built[k], nm)); TRY(dev_alloc(&ctx->core_reach[k], nm)); }
+        TRY(dev_alloc(&ctx->core_depth, MF_CORE_PROBES));
+        TRY(hipHostMalloc((void **)&ctx->h_core_depth, sizeof(double) * MF_CORE_PROBES));
+        TRY(dev_alloc(&ctx->core_parent, nm));
+        TRY(dev_alloc(&ctx->core_weight, nm));
+        TRY(hipMalloc(&ctx->core_ctl, mf_core_ctl_bytes()));
+        TRY(hipHostMalloc(&ctx->h_core_ctl, mf_core_ctl_bytes()));
+    }
+    TRY(dev_alloc(&ctx->path_tree, nm + 64));
+    TRY(dev_alloc(&ctx->path_parent, nm + 64));
     TRY(dev_alloc(&ctx->path_jump, nm));
     TRY(dev_alloc(&ctx->path_stamp, nm));
     TRY(dev_alloc(&ctx->list[0], nm));
@@ -209,7 +228,8 @@ int mf_destroy(mf_ctx *ctx)
     (void)hipStreamSynchronize(ctx->stream);
     void *dev[] = {ctx->score_range, ctx->proj_on, ctx->proj_off, ctx->mem_on, ctx->mem_off, ctx->sm_on, ctx->sm_off, ctx->order_on, ctx->order_off, ctx->rank_off, ctx->rank_on, ctx->mem_on_sorted, ctx->mem_off_sorted, ctx->fit_len_on, ctx->fit_len_off, ctx->staged, ctx->type_segment, ctx->pairs_evaluated, ctx->feasible_pairs, ctx->largest_weight, ctx->wt, ctx->price,
                    ctx->profit, ctx->colword, ctx->roword, ctx->row2col, ctx->col2row, ctx->team_ctl, ctx->path_ctl, ctx->path_label, ctx->path_expanded, ctx->path_frontier[0], ctx->path_frontier[1], ctx->path_stamp, ctx->path_held, ctx->path_base, ctx->path_tree, ctx->path_parent, ctx->path_jump, ctx->edge_count, ctx->edge_start, ctx->list[0], ctx->list[1], ctx->colmark, ctx->stats,
-                   ctx->cert};
+                   ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
+                   ctx->core_depth, ctx->core_parent, ctx->core_weight, ctx->core_ctl, ctx->cert};
     for (void *p : dev) if (p) (void)hipFree(p);
     if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     for (int i = 0; i < 2; ++i) {
@@ -217,6 +237,8 @@ int mf_destroy(mf_ctx *ctx)
         if (ctx->ev_stats[i]) (void)hipEventDestroy(ctx->ev_stats[i]);
     }
     if (ctx->h_cert) (void)hipHostFree(ctx->h_cert);
+    if (ctx->h_core_depth) (void)hipHostFree(ctx->h_core_depth);
+    if (ctx->h_core_ctl) (void)hipHostFree(ctx->h_core_ctl);
     if (ctx->h_pairs_evaluated) (void)hipHostFree(ctx->h_pairs_evaluated);
     if (ctx->h_feasible_pairs) (void)hipHostFree(ctx->h_feasible_pairs);
     for (int i = 0; i < 10; ++i) if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
@@ -392,6 +414,13 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
     if (!strcmp(name, "path_pull")) { ctx->path_pull = value != 0; return MF_OK; }
     if (!strcmp(name, "path_frontier_rows")) { if (value < 8 || value > (1 << 20)) return MF_ERR_ARG; ctx->path_frontier_rows = (int)value; return MF_OK; }
     if (!strcmp(name, "path_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->path_width = (int)value; return MF_OK; }
+    if (!strcmp(name, "core")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->core = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_depth")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_depth_eps = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_many")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_many = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_width = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_few")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_few = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_after")) { if (value < 0) return MF_ERR_ARG; ctx->core_after = value; return MF_OK; }
+    if (!strcmp(name, "core_refine")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_refine = (int)value; return MF_OK; }
     if (!strcmp(name, "edge_lists_from")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->edge_lists_from = (int)value; return MF_OK; }
     if (!strcmp(name, "fit_prefix_below")) { if (value < 0 || value > 101) return MF_ERR_ARG; ctx->fit_prefix_below = (int)value; return MF_OK; }
     if (!strcmp(name, "fit_prefix")) { ctx->fit_prefix = value != 0; return MF_OK; }

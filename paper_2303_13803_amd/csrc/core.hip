@@ -1,0 +1,1367 @@
+// The matching on short lists (paper: Algorithm "Scheduling algorithm", GetMatching).
+//
+// Once the duals are known to within a few epsilons, a bidder chooses among a handful of lines: on
+// cluster-scale rounds a row has 2-200 columns within a hundred epsilons of its best one, out of
+// 20,000.  From that phase on every bidding line is kept as a list of its CORE_LIST best entries
+// and one number, the largest value K w - dual of any entry that is not on the list.  Duals only
+// rise while a side bids, so as long as the best listed value is at least that number the list
+// decides the bid exactly as the whole line would; a line whose list has sunk below it is read whole.
+//
+// With lists the work of a phase is small (8 x CORE_LIST bytes a bid instead of 80,000) and what
+// bounds it is the latency of dependent steps: bid -> evicted holder -> its bid, or one super-step
+// of a shortest-path search after another.  So all the remaining phases run in ONE launch, on the
+// workgroups of ONE die (XCD): what they share sits in that die's L2, where a load or an atomic
+// takes about 0.1 us and a barrier over its 32 compute units 1 us (measured; across the eight dies
+// 0.7 us and 4.4 us).  A chain step takes 1 us here instead of 4 us, a search super-step 2 us
+// instead of 10 us, and nothing goes back to the host between them.
+#include "scan.h"
+
+namespace {
+
+constexpr int CORE_THREADS = 512;
+constexpr int CORE_WAVES = CORE_THREADS / 64;
+constexpr int CORE_LIST = MF_CORE_LIST;
+static_assert(CORE_LIST == 128, "two entries per lane");
+constexpr int CORE_PUSH_BUFFER = 4096;
+constexpr int CORE_MAX_SOURCES = 64;
+constexpr int CORE_MAX_WORKGROUPS = 64;
+constexpr int CORE_SLICE = 1024;                    // entries of a whole line one wavefront takes at a time
+constexpr unsigned long long CORE_INF = ~0ull;
+constexpr unsigned CORE_IN_TREE = 0xffffffffu;
+constexpr int CORE_NO_LABEL = INT32_MIN;
+constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
+constexpr unsigned CORE_GAVE_UP = 0x80000000u;
+constexpr double CORE_FAR = 1.0e300;                  // no candidate
+constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose list holds all of its entries
+
+// ---------------------------------------------------------------- the lists
+
+// One workgroup per line: the CORE_LIST entries with the largest K w - dual.  What bounds it is
+// reading the line, once: a thread keeps its up to NV groups of four entries, and their values, in
+// registers (0.5 ms for 20,000 lines of 20,000 entries; reading the line three times took 1.25 ms).
+// The cut is found from a histogram of the distances to the line's best value in
+// eighths of a power of two: all entries of the bins that fit are taken, the next bin fills the
+// list up in an order that starts somewhere else in every line (tied bidders would otherwise all
+// hold the same few of many tied entries).  Only entries at least as good as the CORE_LIST + 1st of the
+// threads' own best values go into the histogram, a few hundred: one LDS atomic for every entry
+// would take longer than reading the line.
+// NV == 0: lines of any length, read three times.
+constexpr int LIST_BINS = 2048;
+
+__device__ __forceinline__ int distance_bin(double d)        // d >= 0; monotone
+{
+    return min((int)(__float_as_uint((float)d) >> 20), LIST_BINS - 1);
+}
+
+template <int NT, int NV>
+__global__ __launch_bounds__(NT) void core_list_kernel(
+    const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
+    const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *depth,
+    const double *__restrict__ own_dual, const int *__restrict__ partner)
+{
+    __shared__ unsigned hist[LIST_BINS];
+    __shared__ double s_red[NT / 64];
+    __shared__ int s_low, s_fill, s_cut, s_room, s_all, s_near;
+    const int b = blockIdx.x * stride;
+    if (b >= lines) return;
+    const int tid = threadIdx.x;
+    int2 *out = entries + (size_t)b * CORE_LIST;
+    // a column nobody holds and that has no price will not bid soon: an empty list that says so (should
+    // it bid before the lists are made again, it reads its whole line)
+    if (partner && partner[b] < 0 && !(own_dual[b] > 0.0)) {
+        for (int t = tid; t < CORE_LIST; t += NT) out[t] = make_int2(0, MF_INFEASIBLE);
+        if (tid == 0) { bound[b] = CORE_FAR; depth[blockIdx.x] = 0.0; }
+        return;
+    }
+    const int to = line_len ? min(line_len[b], len) : len;
+    const int32_t *line = A + (size_t)b * pitch;
+    const int groups = (to + 3) / 4;
+    const int turn = groups > 0 ? (int)(((unsigned)b * 2654435761u >> 8) % (unsigned)groups) : 0;
+    for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
+    constexpr int KEEP = NV > 0 ? NV : 1;
+    int4 kept_w[KEEP];
+    double kept_v[KEEP][4];
+    auto group_of = [&](int g0) { const int g = g0 + turn; return g >= groups ? g - groups : g; };
+    auto read = [&](int g, int4 &w4, double *v) {
+        w4 = *(const int4 *)(line + g * 4);                  // lines are padded to a multiple of four
+        const double2 p01 = *(const double2 *)(dual + g * 4);
+        const double2 p23 = *(const double2 *)(dual + g * 4 + 2);
+        const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+        const double p[4] = {p01.x, p01.y, p23.x, p23.y};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            v[e] = g * 4 + e < to && w[e] != MF_INFEASIBLE ? fma(Kd, (double)w[e], -p[e]) : NEG_HUGE;
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int q = 0; q < KEEP; ++q) {
+            const int g0 = tid + q * NT;
+            kept_w[q] = make_int4(MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kept_v[q][e] = NEG_HUGE;
+            if (g0 < groups) read(group_of(g0), kept_w[q], kept_v[q]);
+        }
+    }
+    auto for_each = [&](auto what) {                         // what(position, weight, value) for the feasible entries
+        if constexpr (NV > 0) {
+#pragma unroll
+            for (int q = 0; q < KEEP; ++q) {
+                const int g0 = tid + q * NT, g = group_of(g0);
+                const int32_t w[4] = {kept_w[q].x, kept_w[q].y, kept_w[q].z, kept_w[q].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (kept_v[q][e] > NEG_HUGE) what(g * 4 + e, w[e], kept_v[q][e]);
+            }
+        } else {
+            for (int g0 = tid; g0 < groups; g0 += NT) {
+                const int g = group_of(g0);
+                int4 w4;
+                double v[4];
+                read(g, w4, v);
+                const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (v[e] > NEG_HUGE) what(g * 4 + e, w[e], v[e]);
+            }
+        }
+    };
+    auto block_max = [&](double v) {
+        v = wave_max(v);
+        __syncthreads();
+        if ((tid & 63) == 0) s_red[tid >> 6] = v;
+        __syncthreads();
+        v = s_red[0];
+        for (int k = 1; k < NT / 64; ++k) v = fmax(v, s_red[k]);
+        return v;
+    };
+    // the first bin at which the histogram's running count exceeds CORE_LIST (LIST_BINS if none does)
+    // and the count before it (all, if none); first wavefront
+    constexpr int PER = LIST_BINS / 64;
+    auto find_cut = [&](int &bin, int &room) {
+        unsigned mine = 0;
+        for (int t = 0; t < PER; ++t) mine += hist[tid * PER + t];
+        unsigned run = mine;
+        for (int d = 1; d < 64; d <<= 1) { const unsigned o = __shfl_up(run, d); if (tid >= d) run += o; }
+        unsigned before = run - mine;
+        if (tid == 63 && run <= (unsigned)CORE_LIST) { bin = LIST_BINS; room = (int)run; }
+        if (before <= (unsigned)CORE_LIST && run > (unsigned)CORE_LIST) {
+            int t = 0;
+            while (before + hist[tid * PER + t] <= (unsigned)CORE_LIST) { before += hist[tid * PER + t]; ++t; }
+            bin = tid * PER + t;
+            room = (int)before;
+        }
+    };
+    double best = NEG_HUGE;
+    for_each([&](int, int32_t, double v) { best = fmax(best, v); });
+    const double own = best;
+    best = block_max(best);
+    if (own > NEG_HUGE) atomicAdd(&hist[distance_bin(best - own)], 1u);
+    __syncthreads();
+    if (tid < 64) find_cut(s_near, s_room);                  // the bin the CORE_LIST + 1st of the threads' best values is in
+    __syncthreads();
+    const int near = s_near;
+    for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
+    __syncthreads();
+    for_each([&](int, int32_t, double v) {
+        const int bin = distance_bin(best - v);
+        if (bin <= near) atomicAdd(&hist[bin], 1u);
+    });
+    __syncthreads();
+    if (tid < 64) {
+        find_cut(s_cut, s_room);
+        if (tid == 0) { s_low = 0; s_fill = 0; s_all = 1; }
+    }
+    __syncthreads();
+    const int cut = s_cut, low = s_room;
+    double outside = NEG_HUGE;
+    for_each([&](int j, int32_t w, double v) {
+        const int bin = distance_bin(best - v);
+        if (bin < cut) out[atomicAdd(&s_low, 1)] = make_int2(j, w);
+        else {
+            const int at = bin == cut ? low + atomicAdd(&s_fill, 1) : CORE_LIST;
+            if (at < CORE_LIST) out[at] = make_int2(j, w);
+            else { outside = fmax(outside, v); s_all = 0; }
+        }
+    });
+    outside = block_max(outside);
+    __syncthreads();
+    const int used = min(low + s_fill, CORE_LIST);
+    for (int t = used + tid; t < CORE_LIST; t += NT) out[t] = make_int2(0, MF_INFEASIBLE);
+    if (tid == 0) {
+        bound[b] = s_all ? CORE_UNBOUNDED : outside;
+        depth[blockIdx.x] = s_all ? 1.0e13 : best - outside;
+    }
+}
+
+__global__ void core_snapshot_kernel(const double *__restrict__ dual, int count, double *__restrict__ built)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < count) built[k] = dual[k];
+}
+
+// ---------------------------------------------------------------- the engine
+
+struct alignas(256) CoreCtl {
+    // who takes part: the workgroups of the die the first one to arrive runs on
+    int die;
+    unsigned joined, arrived;
+    // barriers each workgroup has reached (top bit: it gave up); one lane polls each
+    alignas(256) unsigned reached[CORE_MAX_WORKGROUPS];
+    // bidders handed on: epoch e reads cnt[e & 3], fills cnt[(e + 1) & 3] and clears cnt[(e + 2) & 3]
+    alignas(128) int cnt[4];
+    int whole_count[4];                                  // rows whose whole lines a refinement looks at next (same ring)
+    unsigned dense[4];                                   // whole lines read in an epoch (same ring)
+    alignas(128) unsigned long long slack[3];            // see slack_of: bits of a non-negative double, two means
+    int rev_count;
+    // searches
+    // (read together, a lane each: [0..2] lowest label left per slot, [3..5] path ends found, [6..8] frontier lengths, [9] sink, [10..12] lines to be read whole)
+    alignas(128) unsigned long long low[3];
+    unsigned long long sink_found[3], frontier[3], sink, whole_front[3];
+    alignas(128) unsigned long long src_profit[CORE_MAX_SOURCES], src_outside[CORE_MAX_SOURCES];
+    alignas(128) unsigned jump_pending[CORE_JUMP_PASSES + 1];
+    // refinement
+    alignas(128) unsigned failed[3];
+    // the phases
+    alignas(128) double eps[MF_CORE_PHASES];
+    int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];   // bidders that may be left over (second: while few have given up)
+    // what the launch reports
+    alignas(128) int reason, phase, stage, count, parity, phases_run;
+    unsigned long long bids, depth, steps, scans, whole_lines, rested;
+};
+static_assert(sizeof(CoreCtl) <= 8192, "the context allocates 8 KiB for this block");
+
+struct CoreSide {
+    const int32_t *A;                   // the bidding side's lines
+    long long pitch;
+    int lines, len;                     // how many, how long
+    const int *line_len;                // optional
+    unsigned long long *otherword;      // opposite (dual, holder) words
+    double *other_dual;                 // the same duals, brought up to date at the end of a side
+    const int2 *entries;
+    const double *bound, *built, *reach;    // built: the opposite duals when the lists were made; reach: from a line's best entry to its bound
+};
+
+struct CoreArgs {
+    CoreSide side[2];                   // 0: rows bid, 1: columns bid
+    double Kd;
+    int n_phases, first_phase, first_stage, first_count, first_parity;
+    int growth_rest;
+    unsigned long long rested_before;
+    int have_columns;                   // the lists of side 1 exist
+    int may_refine;
+    double stale_rise;
+    double stale;                       // epsilons a dual may have come down since the lists were made before they are made again
+    int refine_rounds;
+    double refine_lower;
+    double refine_below;                // epsilon at or below which a complete phase is followed by a refinement
+    int path_max;
+    long long path_after, tail_steps;
+    int steps_many, steps_few;
+    double path_width;
+    int frontier_high;
+    unsigned spin_limit;
+    int workgroups;
+    int dense_limit;
+    int frontier_room;
+    double bid_limit;
+    int *row2col, *col2row;
+    unsigned long long *rowword;        // == side[1].otherword
+    int *list0, *list1;
+    // searches and refinement
+    unsigned long long *label, *expanded, *frontier0, *frontier1;
+    unsigned *stamp;
+    int *held, *jump;
+    unsigned long long *parent;
+    double *remainder;                  // [columns] how far off the nearest unlisted entry of the holder's line is at least
+    int *whole0, *whole1;               // lines to be read whole (by step parity)
+    int32_t *held_weight;               // [max(rows, columns)] weight of each opposite line's pair with its holder
+};
+
+struct CoreShared {
+    unsigned long long list[CORE_PUSH_BUFFER];
+    double profit[CORE_MAX_SOURCES], remainder[CORE_MAX_SOURCES], outside[CORE_MAX_SOURCES];
+    int row[CORE_MAX_SOURCES], alive[CORE_MAX_SOURCES];
+    unsigned pushes, base;
+    unsigned long long sink, low;
+    int n_alive, ok, dense;
+    unsigned failed;
+};
+
+__device__ __forceinline__ unsigned die_number()
+{
+    return (unsigned)__builtin_amdgcn_s_getreg((31 << 11) | 20) & 0xfu;     // XCC_ID
+}
+
+__device__ __forceinline__ int load_fresh_i32(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_i32(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_u32(unsigned *p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_f64(double *p, double v) { store_through((unsigned long long *)p, (unsigned long long)__double_as_longlong(v)); }
+
+// Best and second-best value of a whole line against the current words (one wavefront).  Out of
+// line and with nothing but values passed: rare, and its registers would be the callers' otherwise.
+__device__ __noinline__ Top2 read_whole_line(const int32_t *line, int to, const unsigned long long *words, double Kd, int salt)
+{
+    const int lane = threadIdx.x & 63;
+    Top2 t{NEG_HUGE, NEG_HUGE, 0x7fffffff, 0};
+#pragma unroll 2
+    for (int j = lane * 4; j < to; j += 256) {
+        const int4 w4 = *(const int4 *)(line + j);
+        const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+        double v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double p = word_dual(load_fresh_u64(&words[min(j + e, to - 1)]));
+            v[e] = j + e < to ? fma(Kd, (double)w[e], -p) : NEG_HUGE;
+        }
+        top2_push4(t.b1, t.b2, t.idx, t.w, v[0], v[1], v[2], v[3], j, w4, salt);
+    }
+    t = wave_top2(t);
+    t.idx ^= salt;
+    return t;
+}
+
+// Everything a workgroup carries through the launch.
+struct Core {
+    const CoreArgs &a;
+    CoreCtl *ctl;
+    CoreShared &sh;
+    unsigned G, rank;
+    unsigned generation;
+    int tid, lane, wave;
+    unsigned bids, depth, steps, scans, whole, rests;          // this wavefront's counts
+
+    __device__ Core(const CoreArgs &args, CoreCtl *c, CoreShared &s)
+        : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), tid(threadIdx.x), lane(threadIdx.x & 63),
+          wave(threadIdx.x >> 6), bids(0), depth(0), steps(0), scans(0), whole(0), rests(0) {}
+
+    __device__ int gtid() const { return (int)rank * CORE_THREADS + tid; }
+    __device__ int gsize() const { return (int)G * CORE_THREADS; }
+    // (dealt out over the compute units first: a scan's gathers are bound by one unit's request rate)
+    __device__ int gwave() const { return wave * (int)G + (int)rank; }
+    __device__ int gwaves() const { return (int)G * CORE_WAVES; }
+
+    // Barrier over the participating workgroups: each stores the barrier's number in a slot of its
+    // own, and one wavefront polls all the slots, a lane each.  (A store and a load of L2 take 0.1 us
+    // each, a read-modify-write 0.27 us and the next one on the same address waits for it: counting
+    // arrivals took 1.0 us.)  Every wait is bounded; whoever's runs out says so in its slot and
+    // everybody leaves.
+    __device__ __forceinline__ bool barrier()
+    {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        ++generation;
+        if (G == 1u && a.spin_limit > 0u) return true;
+        if (tid < 64) {
+            if (lane == 0) store_u32(&ctl->reached[rank], generation);
+            unsigned spins = 0;
+            bool ok = true;
+            for (;;) {
+                const unsigned seen = lane < (int)G ? load_fresh_u32(&ctl->reached[lane]) : generation;
+                if (__any(seen & CORE_GAVE_UP)) { ok = false; break; }
+                if (__all(seen >= generation)) break;
+                if (++spins > a.spin_limit) { ok = false; break; }
+            }
+            if (lane == 0) {
+                if (!ok) store_u32(&ctl->reached[rank], CORE_GAVE_UP);
+                sh.ok = ok ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        return sh.ok != 0;
+    }
+
+    // The workgroups of one die find each other, at most `workgroups` of them; the others leave.
+    // Returns 0 (not one of them), 1, or -1 (a wait ran out).
+    __device__ __forceinline__ int join()
+    {
+        if (tid == 0) {
+            const int mine = (int)die_number();
+            const int was = atomicCAS(&ctl->die, -1, mine);
+            int number = was == -1 || was == mine ? (int)atomicAdd(&ctl->joined, 1u) : -1;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            atomicAdd(&ctl->arrived, 1u);
+            if (number >= a.workgroups) number = -1;
+            sh.n_alive = number;
+            sh.ok = number >= 0 ? 1 : 0;
+            if (number >= 0) {
+                unsigned spins = 0;
+                while (load_fresh_u32(&ctl->arrived) < gridDim.x)
+                    if (++spins > a.spin_limit) { sh.ok = -1; break; }
+                sh.base = min(load_fresh_u32(&ctl->joined), (unsigned)a.workgroups);
+                if (sh.ok < 0) store_u32(&ctl->reached[number], CORE_GAVE_UP);
+            }
+        }
+        __syncthreads();
+        const int ok = sh.ok;
+        if (ok == 1) { rank = (unsigned)sh.n_alive; G = sh.base; }
+        __syncthreads();
+        return ok;
+    }
+
+    // ---------------- bids ----------------
+
+    __device__ __forceinline__ Top2 whole_line(const CoreSide &s, int b)
+    {
+        return read_whole_line(s.A + (size_t)b * s.pitch, s.line_len ? min(s.line_len[b], s.len) : s.len, s.otherword, a.Kd, tie_salt(b));
+    }
+
+    // the same from the line's list; *outside: what no unlisted entry exceeds
+    __device__ __forceinline__ Top2 listed(const CoreSide &s, int b, double slack, double *outside)
+    {
+        const int2 *e = s.entries + (size_t)b * CORE_LIST;
+        const int2 e0 = e[lane], e1 = e[lane + 64];
+        *outside = s.bound[b] + slack;
+        const unsigned long long w0 = load_fresh_u64(&s.otherword[e0.x]), w1 = load_fresh_u64(&s.otherword[e1.x]);
+        const double v0 = fma(a.Kd, (double)e0.y, -word_dual(w0)), v1 = fma(a.Kd, (double)e1.y, -word_dual(w1));
+        const bool first = v0 >= v1;
+        const double hi = fmax(v0, v1), lo = fmin(v0, v1);
+        Top2 t;
+        t.b1 = wave_max(hi);
+        const unsigned long long hit = __ballot(hi == t.b1);
+        // among tied lanes the first at or after a lane that depends on the bidder
+        const unsigned turn = (unsigned)tie_salt(b) & 63u;
+        const unsigned long long turned = (hit >> turn) | (turn ? hit << (64u - turn) : 0ull);
+        const int src = (int)((((unsigned)__ffsll((long long)turned) - 1u) + turn) & 63u);
+        t.b2 = wave_max(lane == src ? lo : hi);
+        t.idx = __builtin_amdgcn_readlane(first ? e0.x : e1.x, src);
+        t.w = __builtin_amdgcn_readlane(first ? e0.y : e1.y, src);
+        return t;
+    }
+
+    // One bid of bidder b by this wavefront; returns who has to bid next because of it, or -1.
+    __device__ __forceinline__ int bid(const CoreSide &s, int b, double eps, double slack, bool count_rests)
+    {
+        double outside;
+        Top2 t = listed(s, b, slack, &outside);
+        ++bids;
+        if (t.b1 < outside) {                            // the list no longer decides
+            t = whole_line(s, b);
+            outside = NEG_HUGE;
+            ++whole;
+            if (lane == 0) atomicAdd(&sh.dense, 1);
+        }
+        if (t.b1 <= eps) {
+            if (count_rests) ++rests;
+            return -1;
+        }
+        int next = 0;
+        if (lane == 0) {
+            const double keep = fmax(fmax(t.b2, outside) - eps, 0.0);
+            const unsigned long long mine = pack_word(a.Kd * (double)t.w - keep, b + 1);
+            const unsigned long long old = atomicMax(&s.otherword[t.idx], mine);
+            next = old < mine ? word_id(old) : b;
+        }
+        return __builtin_amdgcn_readfirstlane(next);
+    }
+
+    // hands a bidder on to the next epoch (called by one lane)
+    __device__ __forceinline__ void push(int b, int *next, int *counter)
+    {
+        const unsigned slot = atomicAdd(&sh.pushes, 1u);
+        if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)b;
+        else store_i32(&next[atomicAdd(counter, 1)], b);
+    }
+    __device__ __forceinline__ void flush(int *next, int *counter)
+    {
+        __syncthreads();
+        const unsigned mine = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+        if (tid == 0) sh.base = mine ? (unsigned)atomicAdd(counter, (int)mine) : 0u;
+        __syncthreads();
+        for (unsigned t = tid; t < mine; t += CORE_THREADS) store_i32(&next[sh.base + t], (int)sh.list[t]);
+    }
+
+    // The most any opposite dual has come down since the side's lists were made (a list's bound holds
+    // for entries that were worth so much less then).  ok: false when a wait ran out.  *stale: the duals
+    // have risen, on average, by a good part of what the lists reach below their best entries, so
+    // that many of them are about to stop deciding bids.
+    __device__ __forceinline__ double slack_of(const CoreSide &s, bool &ok, bool *stale)
+    {
+        if (gtid() < 3) store_through(&ctl->slack[gtid()], 0ull);
+        ok = barrier();
+        if (!ok) return 0.0;
+        double most = 0.0, rise = 0.0, reach = 0.0;
+        for (int k = gtid(); k < s.len; k += gsize()) {
+            const double d = s.built[k] - word_dual(load_fresh_u64(&s.otherword[k]));
+            most = fmax(most, d);
+            rise -= d;
+        }
+        for (int i = gtid(); i < s.lines; i += gsize()) reach += s.reach[i];
+        most = wave_max(most);
+        for (int off = 32; off >= 1; off >>= 1) { rise += __shfl_xor(rise, off); reach += __shfl_xor(reach, off); }
+        if (lane == 0) {
+            if (most > 0.0) atomicMax(&ctl->slack[0], (unsigned long long)__double_as_longlong(most));
+            if (rise > 0.0) atomicAdd(&ctl->slack[1], (unsigned long long)(rise / s.len));
+            atomicAdd(&ctl->slack[2], (unsigned long long)(reach / s.lines));
+        }
+        ok = barrier();
+        const double up = (double)load_fresh_u64(&ctl->slack[1]), far = (double)load_fresh_u64(&ctl->slack[2]);
+        *stale = s.len > CORE_LIST && up > a.stale_rise * far;
+        return __longlong_as_double((long long)load_fresh_u64(&ctl->slack[0]));
+    }
+    // brings the plain copy of the opposite duals up to date
+    __device__ __forceinline__ void write_duals(const CoreSide &s)
+    {
+        for (int k = gtid(); k < s.len; k += gsize()) store_f64(&s.other_dual[k], word_dual(load_fresh_u64(&s.otherword[k])));
+    }
+    __device__ __forceinline__ void begin_lists(int parity, int count)
+    {
+        if (gtid() < 4) {
+            store_i32(&ctl->cnt[gtid()], gtid() == parity ? count : 0);
+            store_u32(&ctl->dense[gtid()], 0u);
+            store_i32(&ctl->whole_count[gtid()], 0);
+        }
+    }
+
+    __device__ __forceinline__ int search(const CoreSide &s, double eps, double slack, int count, const int *list, int *next, int *counter);
+    __device__ __forceinline__ int refine(double lower_by);
+    __device__ __forceinline__ int run();
+    __device__ __forceinline__ int leave(int reason, int phase, int stage, int count, int parity);
+};
+
+// Runs one side until at most stop_at bidders are left.  epoch: position in the rings of lists and
+// counters.  Returns 0 (done), or a reason to leave the launch.
+__device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, double slack, int stop_at, bool count_rests, unsigned &epoch,
+                        int &count, double &bid_budget)
+{
+    const CoreArgs &a = c.a;
+    CoreCtl *ctl = c.ctl;
+    long long few_steps = 0, stuck_steps = 0;
+    int fewest = count;
+    unsigned dense_lines = 0, looks = 0;
+    while (count > stop_at) {
+        const int *list = ((epoch & 1u) ? a.list1 : a.list0);
+        int *next = ((epoch & 1u) ? a.list0 : a.list1);
+        int *counter = &ctl->cnt[(epoch + 1u) & 3u];
+        if (c.gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); }
+        if (c.tid == 0) { c.sh.pushes = 0u; c.sh.dense = 0; }
+        __syncthreads();
+        // a side that only prepares prices does not follow its last chains for ever
+        if (stop_at > 0 && a.tail_steps > 0 && few_steps >= a.tail_steps) break;
+        const bool few = count <= a.path_max || (count <= CORE_MAX_SOURCES && few_steps >= 4 * a.path_after);
+        // (hundreds of bidders that outbid each other by an epsilon at a time, as on rank-one weights: a
+        // search for as many of them as it takes)
+        const bool stuck = stuck_steps >= 16 * a.path_after + 512;
+        if (a.path_max > 0 && ((few && few_steps >= a.path_after) || stuck)) {
+            const int rc = c.search(s, eps, slack, count, list, next, counter);
+            if (rc == MF_CORE_DENSE || rc == MF_CORE_RELIST) { ++epoch; count = load_fresh_i32(&ctl->cnt[epoch & 3u]); }
+            if (rc) return rc;
+            few_steps = stuck_steps = 0;
+        } else {
+            // with more bidders than wavefronts a chain is followed for a few steps only
+            const int most = count > c.gwaves() ? a.steps_many : a.steps_few;
+            bid_budget -= (double)count * most;
+            // (far more looks at the list than a side takes: finish it on whole lines)
+            if (bid_budget < 0.0 || ++looks > 100000u) return MF_CORE_LIMIT;
+            for (int item = c.gwave(); item < count; item += c.gwaves()) {
+                int b = load_fresh_i32(&list[item]);
+                int done = 0;
+                for (; b >= 0 && done < most; ++done) b = c.bid(s, b, eps, slack, count_rests);
+                if (b >= 0 && c.lane == 0) c.push(b, next, counter);
+                if (c.gwave() == 0) c.depth += (unsigned)done;
+            }
+            if (count <= CORE_MAX_SOURCES) few_steps += most;
+            stuck_steps += most;
+            c.flush(next, counter);
+            if (c.tid == 0 && c.sh.dense) atomicAdd(&ctl->dense[(epoch + 1u) & 3u], (unsigned)c.sh.dense);
+        }
+        if (!c.barrier()) return MF_CORE_ABORT;
+        ++epoch;
+        count = load_fresh_i32(&ctl->cnt[epoch & 3u]);
+        if (count <= fewest - fewest / 8) { fewest = count; stuck_steps = 0; }
+        dense_lines += load_fresh_u32(&ctl->dense[epoch & 3u]);
+        if (count > stop_at && dense_lines > (unsigned)a.dense_limit) return MF_CORE_RELIST;
+    }
+    return 0;
+}
+
+// Shortest augmenting paths for the bidders in list[0..count): see paths.hip for the method (one
+// label-correcting search with every unplaced bidder a root, the nearest end of a path served one
+// at a time).  Here a scanned line costs its list; what lies beyond the list is bounded below by
+// the length the list's bound gives, and only a line for which that is shorter than the nearest
+// path end known is read whole.
+__device__ __forceinline__ int Core::search(const CoreSide &s, double eps, double slack, int listed_count, const int *list, int *next, int *counter)
+{
+    const int count = min(listed_count, CORE_MAX_SOURCES);
+    for (int k = gtid(); k < s.len; k += gsize()) {
+        store_through(&a.label[k], CORE_INF);
+        store_through(&a.expanded[k], CORE_INF);
+        store_f64(&a.remainder[k], CORE_FAR);
+        store_u32(&a.stamp[k], 0u);
+        const int h = word_id(load_fresh_u64(&s.otherword[k]));
+        if (h >= 0) store_i32(&a.held_weight[k], s.A[(size_t)h * s.pitch + k]);
+    }
+    for (int item = gwave(); item < count; item += gwaves()) {
+        const int r = load_fresh_i32(&list[item]);
+        double outside;
+        const Top2 t = listed(s, r, slack, &outside);
+        const double best = t.b1 >= outside ? t.b1 : whole_line(s, r).b1;
+        if (lane == 0) {
+            store_through(&ctl->src_profit[item], (unsigned long long)__double_as_longlong(best - eps));
+            store_through(&ctl->src_outside[item], (unsigned long long)__double_as_longlong(outside));
+            store_i32(&a.held[r], -1 - item);
+        }
+    }
+    if (gtid() < 3) {
+        store_through(&ctl->low[gtid()], CORE_INF);
+        store_through(&ctl->sink_found[gtid()], CORE_INF);
+        store_through(&ctl->frontier[gtid()], 0ull);
+        store_through(&ctl->whole_front[gtid()], 0ull);
+    }
+    if (gtid() <= CORE_JUMP_PASSES) store_u32(&ctl->jump_pending[gtid()], 0u);
+    if (gtid() == 0) store_through(&ctl->sink, CORE_INF);
+    if (!barrier()) return MF_CORE_ABORT;
+    if (tid < count) {
+        sh.profit[tid] = __longlong_as_double((long long)load_fresh_u64(&ctl->src_profit[tid]));
+        sh.outside[tid] = __longlong_as_double((long long)load_fresh_u64(&ctl->src_outside[tid]));
+        sh.remainder[tid] = sh.profit[tid] + eps - sh.outside[tid];
+        sh.row[tid] = load_fresh_i32(&list[tid]);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int n = 0;
+        for (int j = 0; j < count; ++j)
+            if (sh.profit[j] > 0.0) sh.alive[n++] = j;      // a bidder whose best value is at most eps rests
+        sh.n_alive = n;
+    }
+    __syncthreads();
+    int n_alive = sh.n_alive;
+    auto resting_bidders = [&]() {
+        unsigned long long best = CORE_INF;
+        for (int e = 0; e < n_alive; ++e) {
+            const int j = sh.alive[e];
+            const unsigned long long w = ((unsigned long long)(long long)sh.profit[j] << 21) | (1ull << 20) | (unsigned long long)sh.row[j];
+            best = w < best ? w : best;
+        }
+        return best;
+    };
+    unsigned long long agreed_sink = resting_bidders();
+    double low = 0.0, width = 4.0 * eps;
+    unsigned step = 0, since_served = 0;
+    bool swept = false, from_bidders = true, sweep_next = false;
+    int status = 0;
+    unsigned long long my_steps = 0;
+    while (n_alive > 0) {
+        if (++since_served > 4u * (unsigned)s.len + 4096u) { status = MF_CORE_DENSE; break; }     // (the same in every workgroup)
+        ++step;
+        const unsigned c = step % 3u, p = (step + 1u) % 3u, z = (step + 2u) % 3u;
+        if (tid == 0) { sh.pushes = 0u; sh.sink = CORE_INF; sh.low = CORE_INF; sh.dense = 0; }
+        __syncthreads();
+        const unsigned long long words = load_fresh_u64(&ctl->low[min(lane, 12)]);
+        auto word_at = [&](unsigned q) {
+            return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(words & 0xffffffffull), (int)q) |
+                   ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(words >> 32), (int)q) << 32);
+        };
+        const int front = from_bidders ? 0 : (int)word_at(6u + c);
+        const int whole_front = from_bidders ? 0 : min((int)word_at(10u + c), s.len + CORE_MAX_SOURCES);
+        const bool sweeping = !from_bidders && (sweep_next || front + whole_front == 0);
+        const int nf = from_bidders ? n_alive : (sweeping ? 0 : min(front, a.frontier_room));
+        const int nw = sweeping ? 0 : whole_front;
+        {
+            const unsigned long long found = word_at(3u + c);
+            agreed_sink = found < agreed_sink ? found : agreed_sink;
+        }
+        if (!from_bidders && !sweep_next && swept && nf + nw == 0) {
+            const unsigned long long lo = word_at(c);
+            if (lo == CORE_INF || lo >= (agreed_sink >> 21)) {
+                // ---- every label below the nearest path end is final: serve its tree ----
+                // (Should a wait run out anywhere in here, the launch ends and the phase starts again
+                // from the prices it began with: nothing half-done survives.)
+                const unsigned long long sink = agreed_sink, d_star = sink >> 21;
+                const int sink_id = (int)(sink & 0xfffffull);
+                const bool gives_up = ((sink >> 20) & 1ull) != 0;
+                for (int k = gtid(); k < s.len; k += gsize()) {
+                    const unsigned long long lw = load_fresh_u64(&a.label[k]);
+                    int up = CORE_NO_LABEL;
+                    const int row = (int)(lw & MF_ID_MASK);
+                    if (lw != CORE_INF) up = load_fresh_i32(&a.held[row]);
+                    store_through(&a.parent[k], ((unsigned long long)(unsigned)row << 32) | (unsigned long long)(unsigned)up);
+                    store_i32(&a.jump[k], up);
+                }
+                if (!barrier()) return MF_CORE_ABORT;
+                int passes = 0;
+                bool lost = false;
+                for (;;) {
+                    bool short_of_it = false;
+                    for (int k = gtid(); k < s.len; k += gsize()) {
+                        int up = load_fresh_i32(&a.jump[k]);
+                        if (up < 0) continue;
+                        for (int hop = 0; hop < CORE_JUMP_HOPS && up >= 0; ++hop) up = load_fresh_i32(&a.jump[up]);
+                        store_i32(&a.jump[k], up);
+                        short_of_it |= up >= 0;
+                    }
+                    if (__syncthreads_or(short_of_it) && tid == 0) atomicOr(&ctl->jump_pending[passes], 1u);
+                    if (!barrier()) return MF_CORE_ABORT;
+                    if (load_fresh_u32(&ctl->jump_pending[passes]) == 0u) break;
+                    if (++passes >= CORE_JUMP_PASSES) { lost = true; break; }
+                }
+                int root = -1;
+                {
+                    int at = sink_id;
+                    if (gives_up) at = load_fresh_i32(&a.held[sink_id]);
+                    if (at >= 0) at = load_fresh_i32(&a.jump[at]);
+                    if (at < 0 && at != CORE_NO_LABEL) root = -1 - at;
+                }
+                if (lost || root < 0 || root >= count) { status = MF_CORE_DENSE; break; }
+                for (int k = gtid(); k < s.len; k += gsize()) {
+                    if (load_fresh_i32(&a.jump[k]) != -1 - root) continue;
+                    store_u32(&a.stamp[k], CORE_IN_TREE);
+                    const unsigned long long d_int = load_fresh_u64(&a.label[k]) >> MF_ID_BITS;
+                    if (d_int < d_star) {
+                        const unsigned long long cw = load_fresh_u64(&s.otherword[k]);
+                        store_through(&s.otherword[k], pack_word(word_dual(cw) + (double)(long long)(d_star - d_int), (int)(cw & MF_ID_MASK)));
+                    }
+                }
+                if (!barrier()) return MF_CORE_ABORT;
+                if (rank == 0) {
+                    if (tid == 0) {
+                        int k = sink_id;
+                        if (gives_up) {
+                            const int h = load_fresh_i32(&a.held[sink_id]);
+                            k = h < 0 ? -1 : h;
+                        }
+                        unsigned hops = 0;
+                        while (k >= 0 && hops <= (unsigned)s.lines) {
+                            const unsigned long long pr = load_fresh_u64(&a.parent[k]);
+                            const int i = (int)(pr >> 32);
+                            const unsigned long long word = load_fresh_u64(&s.otherword[k]);
+                            store_through(&s.otherword[k], pack_word(word_dual(word) + eps, i + 1));
+                            if (hops < (unsigned)CORE_PUSH_BUFFER) sh.list[hops] = ((unsigned long long)(unsigned)i << 32) | (unsigned long long)(unsigned)k;
+                            else store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                            ++hops;
+                            k = (int)(unsigned)(pr & 0xffffffffull);
+                        }
+                        sh.pushes = hops;
+                        for (int q = 0; q <= CORE_JUMP_PASSES; ++q) store_u32(&ctl->jump_pending[q], 0u);
+                        store_through(&ctl->sink, CORE_INF);
+                        for (int q = 0; q < 3; ++q) {
+                            store_through(&ctl->sink_found[q], CORE_INF); store_through(&ctl->low[q], CORE_INF);
+                            store_through(&ctl->frontier[q], 0ull); store_through(&ctl->whole_front[q], 0ull);
+                        }
+                    }
+                    __syncthreads();
+                    for (unsigned t = tid; t < min(sh.pushes, (unsigned)CORE_PUSH_BUFFER); t += CORE_THREADS) {
+                        const int k = (int)(unsigned)(sh.list[t] & 0xffffffffull), i = (int)(sh.list[t] >> 32);
+                        store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                    }
+                }
+                for (int k = gtid(); k < s.len; k += gsize()) {
+                    if (load_fresh_u32(&a.stamp[k]) == CORE_IN_TREE) {
+                        store_through(&a.label[k], CORE_INF);
+                        store_u32(&a.stamp[k], 0u);
+                    }
+                    store_through(&a.expanded[k], CORE_INF);
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    int n = 0;
+                    for (int e = 0; e < n_alive; ++e) if (sh.alive[e] != root) sh.alive[n++] = sh.alive[e];
+                    sh.n_alive = n;
+                    for (int e = 0; e < n; ++e) sh.remainder[sh.alive[e]] = sh.profit[sh.alive[e]] + eps - sh.outside[sh.alive[e]];
+                }
+                if (!barrier()) return MF_CORE_ABORT;
+                n_alive = sh.n_alive;
+                agreed_sink = resting_bidders();
+                since_served = 0;
+                --step;
+                from_bidders = true; sweep_next = false; swept = false;
+                continue;
+            }
+            low = (double)(long long)lo;
+        }
+        const double bound = (double)(long long)(min(agreed_sink, word_at(9)) >> 21);
+        if (nf > a.frontier_high) width = fmax(eps, width * 0.5);
+        else if (nf < a.frontier_high / 8) width = fmin(a.path_width * eps, width * 2.0);
+        const double limit = fmin(low + width, bound);
+        if (gtid() == 0) {
+            store_through(&ctl->frontier[z], 0ull);
+            store_through(&ctl->whole_front[z], 0ull);
+            store_through(&ctl->low[z], CORE_INF);
+            store_through(&ctl->sink_found[z], CORE_INF);
+        }
+        const unsigned long long *frontier = ((step & 1u) ? a.frontier1 : a.frontier0);
+        unsigned long long *next_frontier = ((step & 1u) ? a.frontier0 : a.frontier1);
+        auto reach = [&](int k, int holder) {
+            const unsigned long long entry = ((unsigned long long)(unsigned)holder << 32) | (unsigned long long)(unsigned)k;
+            const unsigned slot = atomicAdd(&sh.pushes, 1u);
+            if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = entry;
+            else {                                      // (no room: the pass over all columns finds the label)
+                const unsigned long long at = atomicAdd(&ctl->frontier[p], 1ull);
+                if (at < (unsigned long long)a.frontier_room) store_through(&next_frontier[at], entry);
+            }
+        };
+        auto ends_at = [&](unsigned long long word) { atomicMin(&ctl->sink, word); atomicMin(&ctl->sink_found[p], word); };
+        // One candidate: column k at weight w through row i.  `first` is what the compare-and-swap of
+        // its label saw (so that a wavefront has those of both its entries in flight at once).  A
+        // column lowered twice in a step is twice on the frontier: looking it up in a stamp would
+        // cost every first one another round trip.
+        auto candidate = [&](double base, int32_t w, unsigned long long word) {
+            const double cand = base - fma(a.Kd, (double)w, -word_dual(word));
+            return w != MF_INFEASIBLE && cand < bound ? cand : CORE_FAR;
+        };
+        auto label_of = [&](double cand, int i) { return ((unsigned long long)(long long)cand << MF_ID_BITS) | (unsigned long long)i; };
+        auto shorter = [&](unsigned long long mine, unsigned long long seen) { return (mine >> MF_ID_BITS) < (seen >> MF_ID_BITS); };
+        auto settle = [&](double cand, int k, unsigned long long word, unsigned long long mine, unsigned long long seen, unsigned long long was) {
+            while (was != seen) {                       // strictly shorter only: see lower_label in paths.hip
+                if (!shorter(mine, was)) return;
+                seen = was;
+                was = atomicCAS(&a.label[k], seen, mine);
+            }
+            if (cand < limit) {
+                const int holder = word_id(word);
+                if (holder < 0) ends_at(((unsigned long long)(long long)cand << 21) | (unsigned long long)k);
+                else reach(k, holder);
+            }
+        };
+        auto relax = [&](int i, double base, int k, int32_t w, unsigned long long word, unsigned long long seen) {
+            const double cand = candidate(base, w, word);
+            if (!(cand < CORE_FAR)) return;
+            const unsigned long long mine = label_of(cand, i);
+            if (shorter(mine, seen)) settle(cand, k, word, mine, seen, atomicCAS(&a.label[k], seen, mine));
+        };
+        int *whole_list = (step & 1u) ? a.whole1 : a.whole0, *next_whole = (step & 1u) ? a.whole0 : a.whole1;
+        if (nf + nw > 0) {
+            swept = false;
+            for (int it = gwave(); it < nf; it += gwaves()) {
+                int i, mine_col = -1;
+                if (from_bidders) i = sh.row[sh.alive[it]];
+                else {
+                    const unsigned long long entry = load_fresh_u64(&frontier[it]);
+                    mine_col = (int)(unsigned)(entry & 0xffffffffull);
+                    i = (int)(unsigned)(entry >> 32);
+                }
+                const int2 *e = s.entries + (size_t)i * CORE_LIST;
+                const int2 e0 = e[lane], e1 = e[lane + 64];
+                const double outside = s.bound[i] + slack;
+                unsigned long long lw = 0ull, held_word = 0ull, ex = CORE_INF;
+                int32_t w_held = 0;
+                if (!from_bidders) {
+                    lw = load_fresh_u64(&a.label[mine_col]);
+                    held_word = load_fresh_u64(&s.otherword[mine_col]);
+                    w_held = load_fresh_i32(&a.held_weight[mine_col]);
+                    ex = load_fresh_u64(&a.expanded[mine_col]);
+                }
+                const unsigned long long w0 = load_fresh_u64(&s.otherword[e0.x]), w1 = load_fresh_u64(&s.otherword[e1.x]);
+                const unsigned long long l0 = load_fresh_u64(&a.label[e0.x]), l1 = load_fresh_u64(&a.label[e1.x]);
+                double dist, profit;
+                if (from_bidders) { dist = 0.0; profit = sh.profit[sh.alive[it]]; }
+                else {
+                    if (lw == CORE_INF || (lw >> MF_ID_BITS) >= ex) continue;     // (scanned from that label already)
+                    dist = (double)(long long)(lw >> MF_ID_BITS);
+                    profit = fma(a.Kd, (double)w_held, -word_dual(held_word));
+                }
+                const double base = dist + profit + eps;
+                {
+                    const double c0 = candidate(base, e0.y, w0), c1 = candidate(base, e1.y, w1);
+                    const unsigned long long m0 = label_of(c0, i), m1 = label_of(c1, i);
+                    const bool try0 = c0 < CORE_FAR && shorter(m0, l0), try1 = c1 < CORE_FAR && shorter(m1, l1);
+                    unsigned long long was0 = 0ull, was1 = 0ull;
+                    if (try0) was0 = atomicCAS(&a.label[e0.x], l0, m0);
+                    if (try1) was1 = atomicCAS(&a.label[e1.x], l1, m1);
+                    if (try0) settle(c0, e0.x, w0, m0, l0, was0);
+                    if (try1) settle(c1, e1.x, w1, m1, l1, was1);
+                }
+                // (last: a load that is waited for after a store waits for the store as well)
+                if (!from_bidders && lane == 0) {
+                    store_through(&a.expanded[mine_col], lw >> MF_ID_BITS);
+                    // (what is not on the list is at least this far away: looked at when the window gets there)
+                    store_f64(&a.remainder[mine_col], base - outside);
+                    store_i32(&a.held[i], mine_col);
+                    if (dist + profit < bound)
+                        ends_at(((unsigned long long)(long long)(dist + profit) << 21) | (1ull << 20) | (unsigned long long)i);
+                }
+                ++scans;
+            }
+            // whole lines, in slices: a wavefront each
+            const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
+            for (int it = gwave(); it < nw * slices; it += gwaves()) {
+                const int e = it / slices, from = (it - e * slices) * CORE_SLICE;
+                const int entry = load_fresh_i32(&whole_list[e]);
+                int i;
+                double base;
+                if (entry < 0) {                                    // a bidder
+                    const int j = -1 - entry;
+                    i = sh.row[j];
+                    base = sh.profit[j] + eps;
+                } else {
+                    const unsigned long long lw = load_fresh_u64(&a.label[entry]), word = load_fresh_u64(&s.otherword[entry]);
+                    i = word_id(word);
+                    base = (double)(long long)(lw >> MF_ID_BITS) + fma(a.Kd, (double)load_fresh_i32(&a.held_weight[entry]), -word_dual(word)) + eps;
+                    if (lw == CORE_INF || i < 0) continue;          // (cannot be)
+                }
+                const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
+                const int32_t *line = s.A + (size_t)i * s.pitch;
+#pragma unroll 1
+                for (int j = from + lane; j < to; j += 64) {
+                    const int32_t w = line[j];
+                    const unsigned long long word = load_fresh_u64(&s.otherword[j]), label = load_fresh_u64(&a.label[j]);
+                    relax(i, base, j, w, word, label);
+                }
+                if (from == 0) ++whole;
+            }
+            sweep_next = from_bidders && step > 1u;
+            from_bidders = false;
+        } else {
+            swept = true;
+            sweep_next = false;
+            auto read_whole = [&](int entry) {
+                const unsigned long long at = atomicAdd(&ctl->whole_front[p], 1ull);
+                store_i32(&next_whole[at], entry);
+            };
+            for (int k = gtid(); k < s.len; k += gsize()) {
+                const unsigned long long lw = load_fresh_u64(&a.label[k]);
+                const unsigned long long ex = load_fresh_u64(&a.expanded[k]);
+                const double rem = load_fresh(&a.remainder[k]);
+                const unsigned long long d_int = lw >> MF_ID_BITS;
+                if (lw == CORE_INF) continue;
+                if (d_int < ex) {
+                    const double d = (double)(long long)d_int;
+                    if (!(d < bound)) continue;
+                    const int holder = word_id(load_fresh_u64(&s.otherword[k]));
+                    if (holder < 0) atomicMin(&sh.sink, (d_int << 21) | (unsigned long long)k);
+                    else if (d >= limit) atomicMin(&sh.low, d_int);
+                    else reach(k, holder);
+                } else if (rem < bound) {
+                    if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
+                    else { read_whole(k); store_f64(&a.remainder[k], CORE_FAR); }
+                }
+            }
+            if (rank == 0 && tid < n_alive) {
+                const int j = sh.alive[tid];
+                const double rem = sh.remainder[j];
+                if (rem < bound) {
+                    if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
+                    else { read_whole(-1 - j); sh.remainder[j] = CORE_FAR; }
+                }
+            }
+        }
+        __syncthreads();
+        const unsigned pushed = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+        if (tid == 0) {
+            sh.base = pushed ? (unsigned)atomicAdd(&ctl->frontier[p], (unsigned long long)pushed) : 0u;
+            if (sh.sink != CORE_INF) ends_at(sh.sink);
+            if (sh.low != CORE_INF) atomicMin(&ctl->low[p], sh.low);
+        }
+        __syncthreads();
+        for (unsigned t = tid; t < pushed; t += CORE_THREADS)
+            if (sh.base + t < (unsigned)a.frontier_room) store_through(&next_frontier[sh.base + t], sh.list[t]);
+        ++my_steps;
+        if (!barrier()) return MF_CORE_ABORT;
+    }
+    if (gtid() == 0) {
+        steps += (unsigned)my_steps;
+        for (int e = 0; e < n_alive; ++e) store_i32(&next[atomicAdd(counter, 1)], sh.row[sh.alive[e]]);
+        for (int rest = count; rest < listed_count; ++rest) store_i32(&next[atomicAdd(counter, 1)], load_fresh_i32(&list[rest]));
+    }
+    if (status) {
+        if (!barrier()) return MF_CORE_ABORT;
+    }
+    __syncthreads();
+    return status;
+}
+
+// A complete assignment that is optimal already only lacks exact prices.  Rows raise the prices of
+// the columns they would rather have until no row prefers anything to what it holds (a row without a
+// partner: until nothing is worth having), each raise setting off the row that holds the column;
+// this ends, without a free column ever getting a price, exactly when the assignment is optimal.  (All
+// prices are first lowered by some hundred epsilons: raising can then also arrive at prices a little
+// below those of the phase, which is what rows that would rather have a free column call for.)  The
+// phases at finer epsilons, which would re-assign everybody several times over only to arrive at the
+// same assignment, are then left out.  Returns 1 (prices proved exact), 0 (not optimal yet),
+// 2 (better lists are wanted; it goes on from the prices reached), or -1.
+__device__ __forceinline__ int Core::refine(double lower_by)
+{
+    const CoreSide &s = a.side[0];
+    for (int k = gtid(); k < s.len; k += gsize()) {
+        const int r = load_fresh_i32(&a.col2row[k]);
+        store_through(&s.otherword[k], pack_word(fmax(load_fresh(&s.other_dual[k]) - lower_by, 0.0), r + 1));
+        store_u32(&a.stamp[k], 0u);
+    }
+    for (int i = gtid(); i < s.lines; i += gsize()) {
+        store_i32(&a.list0[i], i);
+        const int col = load_fresh_i32(&a.row2col[i]);
+        store_i32(&a.held_weight[i], col >= 0 ? s.A[(size_t)i * s.pitch + col] : 0);
+    }
+    if (gtid() < 3) store_u32(&ctl->failed[gtid()], 0u);
+    begin_lists(0, 0);
+    bool ok;
+    bool risen;
+    const double slack = slack_of(s, ok, &risen);               // (its barriers also end the set-up above)
+    if (!ok) return -1;
+    int count = s.lines;
+    int done = -2;
+    unsigned epoch = 0, whole_lines = 0;
+    int whole_rows = 0;
+    for (unsigned round = 1;; ++round, ++epoch) {
+        const int *list = ((epoch & 1u) ? a.list1 : a.list0);
+        int *next = ((epoch & 1u) ? a.list0 : a.list1);
+        int *counter = &ctl->cnt[(epoch + 1u) & 3u];
+        if (gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); store_i32(&ctl->whole_count[(epoch + 2u) & 3u], 0); store_u32(&ctl->failed[(round + 1u) % 3u], 0u); }
+        if (tid == 0) { sh.pushes = 0u; sh.failed = 0u; sh.dense = 0; }
+        __syncthreads();
+        for (int item = gwave(); item < count; item += gwaves()) {
+            const int i = load_fresh_i32(&list[item]);
+            const int2 *e = s.entries + (size_t)i * CORE_LIST;
+            const int2 e0 = e[lane], e1 = e[lane + 64];
+            const int col = load_fresh_i32(&a.row2col[i]);
+            const int32_t w_held = load_fresh_i32(&a.held_weight[i]);
+            const double outside = s.bound[i] + slack;
+            const unsigned long long w0 = load_fresh_u64(&s.otherword[e0.x]), w1 = load_fresh_u64(&s.otherword[e1.x]);
+            const double profit = col >= 0 ? fma(a.Kd, (double)w_held, -word_dual(load_fresh_u64(&s.otherword[max(col, 0)]))) : 0.0;
+            bool failed = profit < 0.0;                 // it would rather rest
+            auto wants = [&](int32_t w, unsigned long long word, double &need) {
+                need = fma(a.Kd, (double)w, -profit);
+                return w != MF_INFEASIBLE && word_dual(word) < need;
+            };
+            if (!failed) {
+                double n0, n1;
+                const bool want0 = wants(e0.y, w0, n0), want1 = wants(e1.y, w1, n1);
+                failed |= (want0 && word_id(w0) < 0) || (want1 && word_id(w1) < 0);      // a free column would get a price
+                if (!failed) {
+                    const unsigned long long m0 = pack_word(n0, (int)(w0 & MF_ID_MASK)), m1 = pack_word(n1, (int)(w1 & MF_ID_MASK));
+                    unsigned long long was0 = CORE_INF, was1 = CORE_INF;
+                    if (want0) was0 = atomicMax(&s.otherword[e0.x], m0);
+                    if (want1) was1 = atomicMax(&s.otherword[e1.x], m1);
+                    const bool raised0 = was0 < m0, raised1 = was1 < m1;
+                    unsigned st0 = round, st1 = round;
+                    if (raised0) st0 = atomicExch(&a.stamp[e0.x], round);
+                    if (raised1) st1 = atomicExch(&a.stamp[e1.x], round);
+                    if (st0 != round) push(word_id(w0), next, counter);
+                    if (st1 != round) push(word_id(w1), next, counter);
+                }
+                if (lane == 0 && profit < outside) {    // the list does not show everything this row might want: all of it, next round
+                    const int at = atomicAdd(&ctl->whole_count[(epoch + 1u) & 3u], 1);
+                    if (at < s.len) store_i32(&((epoch & 1u) ? a.whole0 : a.whole1)[at], i);
+                    else failed = true;
+                    atomicAdd(&sh.dense, 1);
+                }
+            }
+            if (__any(failed)) { if (lane == 0) atomicOr(&sh.failed, 1u); break; }
+            ++scans;
+        }
+        const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
+        for (int it = gwave(); it < whole_rows * slices; it += gwaves()) {
+            const int i = load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[it / slices]), from = it % slices * CORE_SLICE;
+            const int col = load_fresh_i32(&a.row2col[i]);
+            const double profit = col >= 0 ? fma(a.Kd, (double)load_fresh_i32(&a.held_weight[i]), -word_dual(load_fresh_u64(&s.otherword[max(col, 0)]))) : 0.0;
+            const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
+            const int32_t *line = s.A + (size_t)i * s.pitch;
+#pragma unroll 1
+            for (int j = from + lane; j < to; j += 64) {
+                const int32_t w = line[j];
+                const unsigned long long word = load_fresh_u64(&s.otherword[j]);
+                const double need = fma(a.Kd, (double)w, -profit);
+                if (w == MF_INFEASIBLE || !(word_dual(word) < need)) continue;
+                if (word_id(word) < 0) { atomicOr(&sh.failed, 1u); break; }
+                const unsigned long long mine = pack_word(need, (int)(word & MF_ID_MASK));
+                if (atomicMax(&s.otherword[j], mine) < mine && atomicExch(&a.stamp[j], round) != round) push(word_id(word), next, counter);
+            }
+            if (from == 0) ++whole;
+        }
+        flush(next, counter);
+        if (tid == 0 && sh.failed) atomicOr(&ctl->failed[round % 3u], 1u);
+        if (tid == 0 && sh.dense) atomicAdd(&ctl->dense[(epoch + 1u) & 3u], (unsigned)sh.dense);
+        if (!barrier()) return -1;
+        if (load_fresh_u32(&ctl->failed[round % 3u]) != 0u) { done = 0; break; }
+        count = load_fresh_i32(&ctl->cnt[(epoch + 1u) & 3u]);
+        whole_rows = min(load_fresh_i32(&ctl->whole_count[(epoch + 1u) & 3u]), s.len);
+        if (count + whole_rows == 0) { done = 1; break; }
+        whole_lines += load_fresh_u32(&ctl->dense[(epoch + 1u) & 3u]);
+        if (whole_lines > (unsigned)a.dense_limit) { done = 2; break; }
+        if (round >= (unsigned)a.refine_rounds) { done = 0; break; }         // prices that go round and round: not optimal yet
+    }
+    if (gtid() == 0) steps += 1;
+    return done;
+}
+
+// Ends the launch with everything the host, or the next launch, needs in memory.
+__device__ __forceinline__ int Core::leave(int reason, int phase, int stage, int count, int parity)
+{
+    if (lane == 0) {
+        if (bids) atomicAdd(&ctl->bids, (unsigned long long)bids);
+        if (scans) atomicAdd(&ctl->scans, (unsigned long long)scans);
+        if (whole) atomicAdd(&ctl->whole_lines, (unsigned long long)whole);
+        if (rests) atomicAdd(&ctl->rested, (unsigned long long)rests);
+    }
+    // a wait that runs out here still counts: the reason stays "a wait ran out"
+    if (reason == MF_CORE_ABORT || !barrier()) return MF_CORE_ABORT;
+    if (gtid() == 0) {
+        ctl->reason = reason;
+        ctl->phase = phase;
+        ctl->stage = stage;
+        ctl->count = count;
+        ctl->parity = parity;
+        ctl->steps = steps;
+        ctl->depth = depth;
+    }
+    return reason;
+}
+
+__device__ __forceinline__ int Core::run()
+{
+    const CoreSide &fwd = a.side[0], &rev = a.side[1];
+    int ph = a.first_phase, stage = a.first_stage, count = a.first_count;
+    unsigned epoch = (unsigned)a.first_parity;
+    int left_rows = 0, left_cols = 0;
+    double bid_budget = a.bid_limit;
+    bool ok, fresh_lists = stage != MF_CORE_RESET;    // (the launch before this one asked for them)
+    if (stage == MF_CORE_FORWARD || stage == MF_CORE_REVERSE) {
+        begin_lists((int)epoch, count);
+        if (!barrier()) return MF_CORE_ABORT;
+    }
+    if (stage == MF_CORE_FORWARD_DONE) left_rows = count;
+    if (stage == MF_CORE_REVERSE_DONE) left_cols = count;
+    for (;;) {
+        const double eps = ctl->eps[ph];
+        const int stop = a.rested_before + load_fresh_u64(&ctl->rested) < (unsigned long long)a.growth_rest ? ctl->stop_grown[ph] : ctl->stop[ph];
+        if (stage == MF_CORE_RESET) {
+            if (gtid() == 0) store_i32(&ctl->phase, ph);
+            for (int k = gtid(); k < fwd.len; k += gsize()) {
+                store_through(&fwd.otherword[k], pack_word(load_fresh(&fwd.other_dual[k]), 0));
+                store_i32(&a.col2row[k], -1);
+            }
+            for (int i = gtid(); i < fwd.lines; i += gsize()) { store_i32(&a.row2col[i], -1); store_i32(&a.list0[i], i); }
+            begin_lists(0, fwd.lines);
+            count = fwd.lines;
+            epoch = 0;
+            stage = MF_CORE_FORWARD;                    // (slack_of's barriers end this)
+        }
+        if (stage == MF_CORE_FORWARD || stage == MF_CORE_REVERSE) {
+            const bool forward = stage == MF_CORE_FORWARD;
+            const CoreSide side = forward ? a.side[0] : a.side[1];
+            bool risen;
+            const double slack = slack_of(side, ok, &risen);
+            if (!ok) return MF_CORE_ABORT;
+            // duals that came down a long way make every list's bound useless: better lists first
+            if (((slack > a.stale * eps && side.len > CORE_LIST) || risen) && !fresh_lists) {
+                if (forward) write_duals(side);
+                return leave(MF_CORE_RELIST, ph, stage, count, (int)(epoch & 1u));
+            }
+            fresh_lists = false;
+            const int rc = run_bids(*this, side, eps, slack, stop, forward, epoch, count, bid_budget);
+            if (rc) {
+                if (rc != MF_CORE_ABORT) write_duals(side);
+                return leave(rc, ph, stage, count, (int)(epoch & 1u));
+            }
+            if (forward) { left_rows = count; stage = MF_CORE_FORWARD_DONE; }
+            else { left_cols = count; stage = MF_CORE_REVERSE_DONE; }
+        }
+        if (stage == MF_CORE_FORWARD_DONE) {
+            if (lane == 0 && rests) atomicAdd(&ctl->rested, (unsigned long long)rests);
+            rests = 0;
+            for (int i = gtid(); i < fwd.lines; i += gsize()) {
+                store_i32(&a.row2col[i], -1);
+                store_f64(&rev.other_dual[i], 0.0);
+                store_through(&a.rowword[i], 0ull);
+            }
+            begin_lists(0, 0);
+            if (tid == 0) sh.pushes = 0u;
+            if (!barrier()) return MF_CORE_ABORT;
+            for (int k = gtid(); k < fwd.len; k += gsize()) {
+                const unsigned long long word = load_fresh_u64(&fwd.otherword[k]);
+                const double p = word_dual(word);
+                const int r = word_id(word);
+                store_f64(&fwd.other_dual[k], p);
+                store_i32(&a.col2row[k], r);
+                if (r >= 0) {
+                    const double pi = fma(a.Kd, (double)fwd.A[(size_t)r * fwd.pitch + k], -p);
+                    store_i32(&a.row2col[r], k);
+                    store_f64(&rev.other_dual[r], pi);
+                    store_through(&a.rowword[r], pack_word(pi, k + 1));
+                } else if (p > 0.0) push(k, a.list0, &ctl->cnt[0]);      // an unassigned column that still carries a price must bid
+            }
+            flush(a.list0, &ctl->cnt[0]);
+            if (!barrier()) return MF_CORE_ABORT;
+            count = load_fresh_i32(&ctl->cnt[0]);
+            // (every row left over leaves a column unused, too)
+            const int most_unused = stop > 0 ? stop + left_rows : 0;
+            if (left_rows > 0 && count > most_unused) {
+                // rows that still wanted to bid get the profit that covers all of their pairs (see settle_unplaced_kernel)
+                bool risen;
+                const double slack = slack_of(fwd, ok, &risen);
+                if (!ok) return MF_CORE_ABORT;
+                for (int i = gwave(); i < fwd.lines; i += gwaves()) {
+                    if (load_fresh_i32(&a.row2col[i]) >= 0) continue;
+                    double outside;
+                    const Top2 t = listed(fwd, i, slack, &outside);
+                    const double pi = fmax(t.b1 < outside ? whole_line(fwd, i).b1 : t.b1, 0.0);
+                    if (lane == 0) {
+                        store_f64(&rev.other_dual[i], pi);
+                        store_through(&a.rowword[i], pack_word(pi, 0));
+                    }
+                }
+                if (!barrier()) return MF_CORE_ABORT;
+            }
+            epoch = 0;
+            left_cols = count;
+            if (count > most_unused) {
+                if (!a.have_columns) return leave(MF_CORE_COLUMNS, ph, MF_CORE_REVERSE, count, 0);
+                stage = MF_CORE_REVERSE;
+                continue;
+            }
+            stage = MF_CORE_PHASE_DONE;
+        }
+        if (stage == MF_CORE_REVERSE_DONE) {
+            for (int k = gtid(); k < fwd.len; k += gsize()) { store_i32(&a.col2row[k], -1); store_f64(&fwd.other_dual[k], 0.0); }
+            if (!barrier()) return MF_CORE_ABORT;
+            for (int i = gtid(); i < fwd.lines; i += gsize()) {
+                const unsigned long long word = load_fresh_u64(&a.rowword[i]);
+                const int k = word_id(word);
+                store_i32(&a.row2col[i], k);
+                store_f64(&rev.other_dual[i], word_dual(word));
+                if (k >= 0) {
+                    store_i32(&a.col2row[k], i);
+                    store_f64(&fwd.other_dual[k], fma(a.Kd, (double)fwd.A[(size_t)i * fwd.pitch + k], -word_dual(word)));
+                }
+            }
+            if (!barrier()) return MF_CORE_ABORT;
+        }
+        // (stage is now MF_CORE_PHASE_DONE, or the launch starts there)
+        if (ph + 1 >= a.n_phases) return leave(MF_CORE_DONE, ph, MF_CORE_PHASE_DONE, 0, 0);
+        if (left_rows == 0 && left_cols == 0 && eps <= a.refine_below && a.may_refine) {
+            const int exact = refine(fresh_lists ? 0.0 : a.refine_lower * eps);      // (after new lists it goes on from the prices reached)
+            fresh_lists = false;
+            if (exact < 0) return MF_CORE_ABORT;
+            if (exact == 2) {
+                write_duals(fwd);
+                return leave(MF_CORE_RELIST, ph, MF_CORE_PHASE_DONE, 0, 0);
+            }
+            if (exact > 0) {
+                write_duals(fwd);
+                return leave(MF_CORE_DONE, ph, MF_CORE_PHASE_DONE, 0, 0);
+            }
+        }
+        ++ph;
+        stage = MF_CORE_RESET;
+    }
+}
+
+__global__ __launch_bounds__(CORE_THREADS) void core_kernel(CoreArgs a, CoreCtl *ctl)
+{
+    __shared__ CoreShared sh;
+    Core core(a, ctl, sh);
+    const int joined = core.join();
+    if (joined != 1) return;                            // (not of that die, or a wait ran out: the reason stays as it was)
+    (void)core.run();
+}
+
+struct CorePhases { double eps[MF_CORE_PHASES]; int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES]; };
+
+__global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
+{
+    if (threadIdx.x < MF_CORE_PHASES) {
+        ctl->eps[threadIdx.x] = phases.eps[threadIdx.x];
+        ctl->stop[threadIdx.x] = phases.stop[threadIdx.x];
+        ctl->stop_grown[threadIdx.x] = phases.stop_grown[threadIdx.x];
+    }
+    if (threadIdx.x != 0) return;
+    ctl->die = -1;
+    ctl->joined = 0u; ctl->arrived = 0u;
+    for (int k = 0; k < CORE_MAX_WORKGROUPS; ++k) ctl->reached[k] = 0u;
+    ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
+    ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_lines = 0ull; ctl->rested = 0ull;
+}
+
+}  // namespace
+
+namespace {
+
+void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int which, double *depth, const double *own_dual, const int *partner)
+{
+    const dim3 grid((lines + stride - 1) / stride);
+#define MF_LIST(NT, NV)                                                                                                      \
+    hipLaunchKernelGGL((core_list_kernel<NT, NV>), grid, dim3(NT), 0, ctx->stream, s.A, s.pitch, s.len, s.line_len, lines,   \
+                       stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], depth, own_dual, partner)
+    // (the threads' best values stand for the line's best: there have to be well over CORE_LIST of them)
+    if (s.len <= 4096) MF_LIST(512, 2);
+    else if (s.len <= 8192) MF_LIST(512, 4);
+    else if (s.len <= 20480) MF_LIST(1024, 5);
+    else MF_LIST(1024, 0);
+#undef MF_LIST
+}
+
+}  // namespace
+
+// Lists of a side's lines for its opposite duals as they are; with `partner`, of those that may bid.
+int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner)
+{
+    if (s.len <= CORE_LIST) partner = nullptr;          // whole lines: they never have to be made again
+    launch_lists(ctx, s, lines, 1, which, ctx->core_reach[which], own_dual, partner);
+    hipLaunchKernelGGL(core_snapshot_kernel, dim3((s.len + 255) / 256), dim3(256), 0, ctx->stream, s.other_dual, s.len,
+                       ctx->core_built[which]);
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
+// How far below a line's best value its list would reach, for a sample of lines: *deep becomes the
+// share of them that reach at least `distance`.
+int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep)
+{
+    const int stride = (lines + MF_CORE_PROBES - 1) / MF_CORE_PROBES, probes = (lines + stride - 1) / stride;
+    launch_lists(ctx, s, lines, stride, 0, ctx->core_depth, nullptr, nullptr);
+    MF_HIP(hipGetLastError());
+    MF_HIP(hipMemcpyAsync(ctx->h_core_depth, ctx->core_depth, sizeof(double) * probes, hipMemcpyDeviceToHost, ctx->stream));
+    MF_HIP(hipStreamSynchronize(ctx->stream));
+    int n = 0;
+    for (int k = 0; k < probes; ++k) n += ctx->h_core_depth[k] >= distance;
+    *deep = (double)n / probes;
+    return MF_OK;
+}
+
+int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st)
+{
+    CoreArgs a{};
+    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
+    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
+    a.Kd = fwd.Kd;
+    CorePhases phases{};
+    for (int k = 0; k < plan.n_phases; ++k) { phases.eps[k] = (double)plan.eps[k]; phases.stop[k] = plan.stop[k]; phases.stop_grown[k] = plan.stop_grown[k]; }
+    a.n_phases = plan.n_phases;
+    a.first_phase = st->phase; a.first_stage = st->stage; a.first_count = st->count; a.first_parity = st->parity;
+    a.growth_rest = ctx->phase_growth_rest;
+    a.rested_before = plan.rested_before;
+    a.have_columns = plan.have_columns ? 1 : 0;
+    a.may_refine = plan.may_refine ? 1 : 0;
+    a.stale = plan.stale;
+    a.stale_rise = 0.35;
+    a.refine_below = plan.refine_below;
+    a.refine_rounds = 256;
+    a.refine_lower = 256.0;
+    a.path_max = ctx->path_max;
+    a.path_after = ctx->path_after < ctx->core_after ? ctx->path_after : ctx->core_after;
+    a.tail_steps = ctx->phase_tail_steps;
+    a.steps_many = ctx->core_many; a.steps_few = ctx->core_few;
+    a.path_width = (double)ctx->core_width;
+    a.frontier_high = ctx->path_frontier_rows;
+    a.spin_limit = ctx->path_spin_limit;
+    a.dense_limit = 128 + rn / 64;
+    {
+        // a small problem needs few wavefronts, and a barrier over few workgroups is short
+        const int want = (rm + 31) / 32;
+        a.workgroups = want < CORE_MAX_WORKGROUPS ? want : CORE_MAX_WORKGROUPS;
+    }
+    a.frontier_room = (int)((ctx->max_n > ctx->max_m ? ctx->max_n : ctx->max_m) * 16ll < (1ll << 30) ? (ctx->max_n > ctx->max_m ? ctx->max_n : ctx->max_m) * 16ll : (1ll << 30));
+    a.bid_limit = plan.bid_limit;
+    a.row2col = ctx->row2col; a.col2row = ctx->col2row; a.rowword = ctx->roword;
+    a.list0 = ctx->list[0]; a.list1 = ctx->list[1];
+    a.label = ctx->path_label; a.expanded = ctx->path_expanded;
+    a.frontier0 = ctx->path_frontier[0]; a.frontier1 = ctx->path_frontier[1];
+    a.stamp = ctx->path_stamp; a.held = ctx->path_held; a.jump = ctx->path_jump;
+    a.parent = ctx->core_parent; a.remainder = ctx->path_base; a.whole0 = ctx->path_tree; a.whole1 = ctx->path_parent; a.held_weight = ctx->core_weight;
+    CoreCtl *ctl = (CoreCtl *)ctx->core_ctl;
+    hipLaunchKernelGGL(core_begin_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl, st->phase, phases);
+    // one workgroup per compute unit of the device: those of one die stay
+    hipLaunchKernelGGL(core_kernel, dim3(ctx->n_cus), dim3(CORE_THREADS), 0, ctx->stream, a, ctl);
+    MF_HIP(hipGetLastError());
+    MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
+    MF_HIP(hipStreamSynchronize(ctx->stream));
+    const CoreCtl &h = *(const CoreCtl *)ctx->h_core_ctl;
+    st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
+    st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
+    st->rested += (long long)h.rested;
+    st->bytes += (long long)(h.bids + h.scans) * CORE_LIST * 8 + (long long)h.whole_lines * rm * 4;
+    st->whole += (long long)h.whole_lines;
+    return MF_OK;
+}
+
+size_t mf_core_ctl_bytes() { return sizeof(CoreCtl); }
+

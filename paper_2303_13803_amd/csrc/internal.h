@@ -25,6 +25,19 @@
 enum { T_PROJ = 0, T_PAIR, T_BID_BULK, T_BID_BULK_LAUNCHES, T_TRANSPOSE, T_DUALS, T_CERT, T_SOLVE,
        T_BID_BULK_BYTES, T_PAIR_EVALUATED, T_COUNT = 16 };
 
+// The matching on short lists (core.hip): entries per list, most phases of a solve, lines a probe
+// looks at, why a launch ended and at which stage of a phase it (or the next one) starts.
+#define MF_CORE_LIST 128
+#define MF_CORE_PHASES 64
+#define MF_CORE_PROBES 256
+enum { MF_CORE_DONE = 1,        // the matching is complete and its prices are good
+       MF_CORE_ABORT,           // a wait ran out: the phase starts again without this kernel
+       MF_CORE_RELIST,          // many lines had to be read whole: the lists are due again
+       MF_CORE_COLUMNS,         // columns have to bid and have no lists yet
+       MF_CORE_DENSE,           // a search gave up: this side is finished on whole lines
+       MF_CORE_LIMIT };         // the limit on bids may be reached: likewise
+enum { MF_CORE_RESET = 0, MF_CORE_FORWARD, MF_CORE_FORWARD_DONE, MF_CORE_REVERSE, MF_CORE_REVERSE_DONE, MF_CORE_PHASE_DONE };
+
 struct mf_device_stats {            // lives in device memory, cleared per solve
     unsigned long long rounds;      // bidding rounds
     unsigned long long bids;        // bids evaluated (one line scan each)
@@ -128,6 +141,18 @@ struct mf_ctx {
     bool path_off;                  // set after a wait of the search ran out, for the rest of the solve
     int n_cus;                      // compute units of the device
     int chain_grid;                 // workgroups of that kernel
+    // phases on short lists (core.hip)
+    int core;                       // 0: never
+    int core_depth_eps;             // how many epsilons the lists have to reach below a line's best value
+    int core_many, core_few;        // chain steps between two looks at the list, with more / fewer bidders than wavefronts
+    long long core_after;           // chain steps after which the last bidders are searched for
+    int core_refine;                // epsilon (weight units) at or below which a complete phase is followed by a refinement
+    int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
+    int core_width;                 // label window of a search on lists, in epsilons
+    double *core_bound[2], *core_built[2], *core_reach[2], *core_depth, *h_core_depth;
+    unsigned long long *core_parent;
+    int32_t *core_weight;
+    void *core_ctl, *h_core_ctl;
     int *list[2];
     int *colmark;                   // [max_m]
     mf_device_stats *stats;
@@ -193,6 +218,24 @@ inline size_t mf_edge_capacity(const mf_ctx *ctx)      // entries the lists may 
 }
 // paths.hip
 int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring);
+// core.hip
+struct mf_core_plan {
+    int n_phases;
+    long long eps[MF_CORE_PHASES];
+    int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];
+    double refine_below, bid_limit;
+    unsigned long long rested_before;
+    bool have_columns, may_refine;
+    double stale;
+};
+struct mf_core_state {
+    int reason, phase, stage, count, parity;
+    long long bids, depth, steps, scans, rested, bytes, whole;      // summed over launches
+};
+int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
+int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep);
+int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st);
+size_t mf_core_ctl_bytes();
 // certificate.hip
 int mf_extract_duals(mf_ctx *ctx, const int32_t *A, int64_t lda, int rn, int rm, double Kd, const int *line_len,
                      int n, bool flip, bool staged, int32_t *d_row2col, int64_t *d_u, int64_t *d_v);
