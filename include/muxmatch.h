@@ -334,7 +334,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            "core_after" (128): chain steps after which the last bidders are searched for,
  *            "core_width" (8192): label window of those searches, in epsilons, "core_refine" (16):
  *            epsilon, in weight units, at or below which a complete phase is followed by an attempt
- *            to prove its assignment optimal at once
+ *            to prove its assignment optimal at once, "core_wide" (8192; 0: never): rows from which on the
+ *            launches begin on all dies, going on on one with at most "core_narrow" (1024) bidders
  */
 int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
 

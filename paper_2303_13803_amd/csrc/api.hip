@@ -134,6 +134,8 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     ctx->core_few = 32;
     ctx->core_after = 128;
     ctx->core_refine = 16;
+    ctx->core_wide = 8192;
+    ctx->core_narrow = 1024;
     ctx->core_width = 8192;
     {
         hipDeviceProp_t prop;
@@ -418,6 +420,8 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
     if (!strcmp(name, "core_depth")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_depth_eps = (int)value; return MF_OK; }
     if (!strcmp(name, "core_many")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_many = (int)value; return MF_OK; }
     if (!strcmp(name, "core_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_width = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_wide")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_wide = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_narrow")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_narrow = (int)value; return MF_OK; }
     if (!strcmp(name, "core_few")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_few = (int)value; return MF_OK; }
     if (!strcmp(name, "core_after")) { if (value < 0) return MF_ERR_ARG; ctx->core_after = value; return MF_OK; }
     if (!strcmp(name, "core_refine")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_refine = (int)value; return MF_OK; }

@@ -765,6 +765,9 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
     plan.refine_below = (double)ctx->core_refine * fwd.Kd;
     st.phase = ph; st.stage = MF_CORE_RESET; st.count = 0; st.parity = 0;
     plan.may_refine = true;
+    // (launches over all dies pay from about 8000 rows on: see the top of core.hip)
+    plan.use_wide = ctx->core_wide > 0 && rn >= ctx->core_wide;
+    st.wide = plan.use_wide ? 1 : 0;
     plan.stale = 8.0;
     int rc = mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr);
     if (rc != MF_OK) return rc;
@@ -784,6 +787,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
             after = st.phase;
             return MF_OK;
         }
+        if (st.reason == MF_CORE_HANDOVER) { st.wide = !st.wide; continue; }
         const bool forward = st.stage != MF_CORE_REVERSE;
         if (st.phase != at_phase || st.stage != at_stage) { at_phase = st.phase; at_stage = st.stage; lists_made = 0; }
         if (st.reason == MF_CORE_COLUMNS || (st.reason == MF_CORE_RELIST && ++lists_made <= 4)) {
@@ -955,9 +959,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     };
     int phases = 0;
     mf_core_state core{};
-    // (near-square problems of ten thousands of lines spend as long in searches there as in those of the
-    // whole device: measured 60.3 against 57.4 ms for a 20,000 x 20,000 round)
-    bool core_ok = ctx->core && ctx->n_cus > 0 && !ctx->path_off && (rn < 16384 || rm >= rn + rn / 2);
+    bool core_ok = ctx->core && ctx->n_cus > 0 && !ctx->path_off;
     for (int ph = 0; ph < n_phases; ++ph) {
         // From the phase on in which a list of each row's best columns reaches far enough below the
         // best (core_depth epsilons), the rest of the solve runs on such lists.

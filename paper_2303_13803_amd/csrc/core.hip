@@ -14,6 +14,12 @@
 // takes about 0.1 us and a barrier over its 32 compute units 1 us (measured; across the eight dies
 // 0.7 us and 4.4 us).  A chain step takes 1 us here instead of 4 us, a search super-step 2 us
 // instead of 10 us, and nothing goes back to the host between them.
+//
+// While thousands of lines bid at once throughput counts instead: the proof and the first bids of a
+// phase of a large problem run in launches over all dies, which hand over to one die once at most
+// core_narrow lines bid and get it back for the next phase (two launches a phase more, about 50 us:
+// 20,000 x 40,000 36.3 -> 29.8 ms, 20,000 x 20,000 60 -> 57 ms; at 4096 rows and at 6001 it is a loss,
+// 9.0 -> 9.2 and 14.7 -> 16.5 ms, and the line is drawn at 8192).
 #include "scan.h"
 
 namespace {
@@ -24,7 +30,7 @@ constexpr int CORE_LIST = MF_CORE_LIST;
 static_assert(CORE_LIST == 128, "two entries per lane");
 constexpr int CORE_PUSH_BUFFER = 4096;
 constexpr int CORE_MAX_SOURCES = 64;
-constexpr int CORE_MAX_WORKGROUPS = 64;
+constexpr int CORE_MAX_WORKGROUPS = 1024;
 constexpr int CORE_SLICE = 1024;                    // entries of a whole line one wavefront takes at a time
 constexpr unsigned long long CORE_INF = ~0ull;
 constexpr unsigned CORE_IN_TREE = 0xffffffffu;
@@ -52,6 +58,9 @@ __device__ __forceinline__ int distance_bin(double d)        // d >= 0; monotone
 {
     return min((int)(__float_as_uint((float)d) >> 20), LIST_BINS - 1);
 }
+// where a bin is counted: lane l of the wavefront that sums them up has bins 32 l .. 32 l + 31, a row apart
+__device__ __forceinline__ int bin_slot(int bin) { return (bin & 31) * 64 + (bin >> 5); }
+static_assert(LIST_BINS == 64 * 32, "32 bins per lane");
 
 template <int NT, int NV>
 __global__ __launch_bounds__(NT) void core_list_kernel(
@@ -102,7 +111,8 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
             if (g0 < groups) read(group_of(g0), kept_w[q], kept_v[q]);
         }
     }
-    auto for_each = [&](auto what) {                         // what(position, weight, value) for the feasible entries
+    // what(position, weight, value) for the entries worth more than `above`
+    auto for_each = [&](double above, auto what) {
         if constexpr (NV > 0) {
 #pragma unroll
             for (int q = 0; q < KEEP; ++q) {
@@ -110,7 +120,7 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
                 const int32_t w[4] = {kept_w[q].x, kept_w[q].y, kept_w[q].z, kept_w[q].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (kept_v[q][e] > NEG_HUGE) what(g * 4 + e, w[e], kept_v[q][e]);
+                    if (kept_v[q][e] > above) what(g * 4 + e, w[e], kept_v[q][e]);
             }
         } else {
             for (int g0 = tid; g0 < groups; g0 += NT) {
@@ -121,7 +131,7 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
                 const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (v[e] > NEG_HUGE) what(g * 4 + e, w[e], v[e]);
+                    if (v[e] > above) what(g * 4 + e, w[e], v[e]);
             }
         }
     };
@@ -139,32 +149,34 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
     constexpr int PER = LIST_BINS / 64;
     auto find_cut = [&](int &bin, int &room) {
         unsigned mine = 0;
-        for (int t = 0; t < PER; ++t) mine += hist[tid * PER + t];
+        for (int t = 0; t < PER; ++t) mine += hist[t * 64 + tid];
         unsigned run = mine;
         for (int d = 1; d < 64; d <<= 1) { const unsigned o = __shfl_up(run, d); if (tid >= d) run += o; }
         unsigned before = run - mine;
         if (tid == 63 && run <= (unsigned)CORE_LIST) { bin = LIST_BINS; room = (int)run; }
         if (before <= (unsigned)CORE_LIST && run > (unsigned)CORE_LIST) {
             int t = 0;
-            while (before + hist[tid * PER + t] <= (unsigned)CORE_LIST) { before += hist[tid * PER + t]; ++t; }
+            while (before + hist[t * 64 + tid] <= (unsigned)CORE_LIST) { before += hist[t * 64 + tid]; ++t; }
             bin = tid * PER + t;
             room = (int)before;
         }
     };
     double best = NEG_HUGE;
-    for_each([&](int, int32_t, double v) { best = fmax(best, v); });
+    for_each(NEG_HUGE, [&](int, int32_t, double v) { best = fmax(best, v); });
     const double own = best;
     best = block_max(best);
-    if (own > NEG_HUGE) atomicAdd(&hist[distance_bin(best - own)], 1u);
+    if (own > NEG_HUGE) atomicAdd(&hist[bin_slot(distance_bin(best - own))], 1u);
     __syncthreads();
     if (tid < 64) find_cut(s_near, s_room);                  // the bin the CORE_LIST + 1st of the threads' best values is in
     __syncthreads();
     const int near = s_near;
     for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
     __syncthreads();
-    for_each([&](int, int32_t, double v) {
+    // (everything in the bins up to that one is worth more than this: one comparison an entry from here on)
+    const double above = near < LIST_BINS - 1 ? best - (double)__uint_as_float((unsigned)(near + 1) << 20) : NEG_HUGE;
+    for_each(above, [&](int, int32_t, double v) {
         const int bin = distance_bin(best - v);
-        if (bin <= near) atomicAdd(&hist[bin], 1u);
+        if (bin <= near) atomicAdd(&hist[bin_slot(bin)], 1u);
     });
     __syncthreads();
     if (tid < 64) {
@@ -173,8 +185,9 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
     }
     __syncthreads();
     const int cut = s_cut, low = s_room;
-    double outside = NEG_HUGE;
-    for_each([&](int j, int32_t w, double v) {
+    double outside = above;                                  // what is worth less is not on the list
+    if (tid == 0 && above > NEG_HUGE) s_all = 0;
+    for_each(above, [&](int j, int32_t w, double v) {
         const int bin = distance_bin(best - v);
         if (bin < cut) out[atomicAdd(&s_low, 1)] = make_int2(j, w);
         else {
@@ -228,7 +241,6 @@ struct alignas(256) CoreCtl {
     alignas(128) int reason, phase, stage, count, parity, phases_run;
     unsigned long long bids, depth, steps, scans, whole_lines, rested;
 };
-static_assert(sizeof(CoreCtl) <= 8192, "the context allocates 8 KiB for this block");
 
 struct CoreSide {
     const int32_t *A;                   // the bidding side's lines
@@ -251,7 +263,7 @@ struct CoreArgs {
     int may_refine;
     double stale_rise;
     double stale;                       // epsilons a dual may have come down since the lists were made before they are made again
-    int refine_rounds;
+    int refine_rounds, refined;         // refined: a launch before this one has begun the refinement it starts with
     double refine_lower;
     double refine_below;                // epsilon at or below which a complete phase is followed by a refinement
     int path_max;
@@ -261,6 +273,8 @@ struct CoreArgs {
     int frontier_high;
     unsigned spin_limit;
     int workgroups;
+    int wide, use_wide;                 // this launch spans all dies; such launches do the wide parts
+    int narrow_at;
     int dense_limit;
     int frontier_room;
     double bid_limit;
@@ -356,9 +370,14 @@ struct Core {
             unsigned spins = 0;
             bool ok = true;
             for (;;) {
-                const unsigned seen = lane < (int)G ? load_fresh_u32(&ctl->reached[lane]) : generation;
-                if (__any(seen & CORE_GAVE_UP)) { ok = false; break; }
-                if (__all(seen >= generation)) break;
+                unsigned least = generation, any = 0u;
+                for (unsigned g = lane; g < G; g += 64u) {
+                    const unsigned seen = load_fresh_u32(&ctl->reached[g]);
+                    least = min(least, seen);
+                    any |= seen;
+                }
+                if (__any(any & CORE_GAVE_UP)) { ok = false; break; }
+                if (__all(least >= generation)) break;
                 if (++spins > a.spin_limit) { ok = false; break; }
             }
             if (lane == 0) {
@@ -370,14 +389,15 @@ struct Core {
         return sh.ok != 0;
     }
 
-    // The workgroups of one die find each other, at most `workgroups` of them; the others leave.
+    // The workgroups of one die (with `wide`: of all dies) find each other, at most `workgroups` of
+    // them; the others leave.
     // Returns 0 (not one of them), 1, or -1 (a wait ran out).
     __device__ __forceinline__ int join()
     {
         if (tid == 0) {
             const int mine = (int)die_number();
             const int was = atomicCAS(&ctl->die, -1, mine);
-            int number = was == -1 || was == mine ? (int)atomicAdd(&ctl->joined, 1u) : -1;
+            int number = a.wide || was == -1 || was == mine ? (int)atomicAdd(&ctl->joined, 1u) : -1;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             atomicAdd(&ctl->arrived, 1u);
             if (number >= a.workgroups) number = -1;
@@ -535,6 +555,8 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
         if (c.gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); }
         if (c.tid == 0) { c.sh.pushes = 0u; c.sh.dense = 0; }
         __syncthreads();
+        // few enough for one die: its chain steps and barriers are shorter
+        if (a.wide && count <= a.narrow_at) return MF_CORE_HANDOVER;
         // a side that only prepares prices does not follow its last chains for ever
         if (stop_at > 0 && a.tail_steps > 0 && few_steps >= a.tail_steps) break;
         const bool few = count <= a.path_max || (count <= CORE_MAX_SOURCES && few_steps >= 4 * a.path_after);
@@ -990,7 +1012,7 @@ __device__ __forceinline__ int Core::refine(double lower_by)
     int count = s.lines;
     int done = -2;
     unsigned epoch = 0, whole_lines = 0;
-    int whole_rows = 0;
+    int whole_rows = 0, fewest = count;
     for (unsigned round = 1;; ++round, ++epoch) {
         const int *list = ((epoch & 1u) ? a.list1 : a.list0);
         int *next = ((epoch & 1u) ? a.list0 : a.list1);
@@ -1067,7 +1089,10 @@ __device__ __forceinline__ int Core::refine(double lower_by)
         if (count + whole_rows == 0) { done = 1; break; }
         whole_lines += load_fresh_u32(&ctl->dense[(epoch + 1u) & 3u]);
         if (whole_lines > (unsigned)a.dense_limit) { done = 2; break; }
-        if (round >= (unsigned)a.refine_rounds) { done = 0; break; }         // prices that go round and round: not optimal yet
+        // (on the way to a proof fewer and fewer rows are left; once more and more of them are, prices
+        // are going round and round)
+        fewest = min(fewest, count);
+        if (round >= (unsigned)a.refine_rounds || count > fewest + fewest / 4 + 64) { done = 0; break; }         // prices that go round and round: not optimal yet
     }
     if (gtid() == 0) steps += 1;
     return done;
@@ -1113,6 +1138,7 @@ __device__ __forceinline__ int Core::run()
     for (;;) {
         const double eps = ctl->eps[ph];
         const int stop = a.rested_before + load_fresh_u64(&ctl->rested) < (unsigned long long)a.growth_rest ? ctl->stop_grown[ph] : ctl->stop[ph];
+        if (stage == MF_CORE_RESET && a.use_wide && !a.wide) return leave(MF_CORE_HANDOVER, ph, stage, 0, 0);
         if (stage == MF_CORE_RESET) {
             if (gtid() == 0) store_i32(&ctl->phase, ph);
             for (int k = gtid(); k < fwd.len; k += gsize()) {
@@ -1218,7 +1244,8 @@ __device__ __forceinline__ int Core::run()
         // (stage is now MF_CORE_PHASE_DONE, or the launch starts there)
         if (ph + 1 >= a.n_phases) return leave(MF_CORE_DONE, ph, MF_CORE_PHASE_DONE, 0, 0);
         if (left_rows == 0 && left_cols == 0 && eps <= a.refine_below && a.may_refine) {
-            const int exact = refine(fresh_lists ? 0.0 : a.refine_lower * eps);      // (after new lists it goes on from the prices reached)
+            if (a.use_wide && !a.wide) return leave(MF_CORE_HANDOVER, ph, MF_CORE_PHASE_DONE, 0, 0);
+            const int exact = refine(a.refined ? 0.0 : a.refine_lower * eps);      // (after new lists it goes on from the prices reached)
             fresh_lists = false;
             if (exact < 0) return MF_CORE_ABORT;
             if (exact == 2) {
@@ -1248,6 +1275,7 @@ struct CorePhases { double eps[MF_CORE_PHASES]; int stop[MF_CORE_PHASES], stop_g
 
 __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
 {
+    for (int k = threadIdx.x; k < CORE_MAX_WORKGROUPS; k += blockDim.x) ctl->reached[k] = 0u;
     if (threadIdx.x < MF_CORE_PHASES) {
         ctl->eps[threadIdx.x] = phases.eps[threadIdx.x];
         ctl->stop[threadIdx.x] = phases.stop[threadIdx.x];
@@ -1256,7 +1284,6 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
     if (threadIdx.x != 0) return;
     ctl->die = -1;
     ctl->joined = 0u; ctl->arrived = 0u;
-    for (int k = 0; k < CORE_MAX_WORKGROUPS; ++k) ctl->reached[k] = 0u;
     ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
     ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_lines = 0ull; ctl->rested = 0ull;
 }
@@ -1333,11 +1360,12 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.path_width = (double)ctx->core_width;
     a.frontier_high = ctx->path_frontier_rows;
     a.spin_limit = ctx->path_spin_limit;
+    a.wide = st->wide; a.use_wide = plan.use_wide ? 1 : 0; a.narrow_at = ctx->core_narrow; a.refined = st->refined;
     a.dense_limit = 128 + rn / 64;
     {
         // a small problem needs few wavefronts, and a barrier over few workgroups is short
-        const int want = (rm + 31) / 32;
-        a.workgroups = want < CORE_MAX_WORKGROUPS ? want : CORE_MAX_WORKGROUPS;
+        const int want = (rm + 31) / 32, most = st->wide ? CORE_MAX_WORKGROUPS : 64;
+        a.workgroups = want < most ? want : most;
     }
     a.frontier_room = (int)((ctx->max_n > ctx->max_m ? ctx->max_n : ctx->max_m) * 16ll < (1ll << 30) ? (ctx->max_n > ctx->max_m ? ctx->max_n : ctx->max_m) * 16ll : (1ll << 30));
     a.bid_limit = plan.bid_limit;
@@ -1355,6 +1383,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
     const CoreCtl &h = *(const CoreCtl *)ctx->h_core_ctl;
+    st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
     st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;

@@ -35,7 +35,8 @@ enum { MF_CORE_DONE = 1,        // the matching is complete and its prices are g
        MF_CORE_RELIST,          // many lines had to be read whole: the lists are due again
        MF_CORE_COLUMNS,         // columns have to bid and have no lists yet
        MF_CORE_DENSE,           // a search gave up: this side is finished on whole lines
-       MF_CORE_LIMIT };         // the limit on bids may be reached: likewise
+       MF_CORE_LIMIT,           // the limit on bids may be reached: likewise
+       MF_CORE_HANDOVER };      // on from here on all dies, or on one
 enum { MF_CORE_RESET = 0, MF_CORE_FORWARD, MF_CORE_FORWARD_DONE, MF_CORE_REVERSE, MF_CORE_REVERSE_DONE, MF_CORE_PHASE_DONE };
 
 struct mf_device_stats {            // lives in device memory, cleared per solve
@@ -146,6 +147,7 @@ struct mf_ctx {
     int core_depth_eps;             // how many epsilons the lists have to reach below a line's best value
     int core_many, core_few;        // chain steps between two looks at the list, with more / fewer bidders than wavefronts
     long long core_after;           // chain steps after which the last bidders are searched for
+    int core_wide, core_narrow;     // lines from which the wide parts run on all dies; bidders at or below which one die takes over
     int core_refine;                // epsilon (weight units) at or below which a complete phase is followed by a refinement
     int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
     int core_width;                 // label window of a search on lists, in epsilons
@@ -225,11 +227,12 @@ struct mf_core_plan {
     int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];
     double refine_below, bid_limit;
     unsigned long long rested_before;
-    bool have_columns, may_refine;
+    bool have_columns, may_refine, use_wide;
     double stale;
 };
 struct mf_core_state {
     int reason, phase, stage, count, parity;
+    int wide, refined;
     long long bids, depth, steps, scans, rested, bytes, whole;      // summed over launches
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);

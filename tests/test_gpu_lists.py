@@ -2,7 +2,8 @@
 
 The lists hold 128 entries: lines of fewer, of exactly as many, of one more, and of a multiple of
 the wavefront and of a slice of a whole line plus one; ties beyond what a list holds (a line is then
-read whole); lists that are made once and again.  The optimum is the exact CPU solver's, the duals
+read whole); lists that are made once and again; phases that start on
+the whole device and go on on one die.  The optimum is the exact CPU solver's, the duals
 are re-checked on the host, and the solve with the lists off has to agree."""
 import numpy as np
 import pytest
@@ -19,7 +20,8 @@ INF = synth.INFEASIBLE
                                              (300, 131, 2 ** 20, 0.3), (257, 1025, 2 ** 24, 0.5), (512, 513, 255, 0.1),
                                              (640, 640, 3, 0.0), (200, 2051, 1, 0.0), (1000, 1000, 2 ** 24, 0.95),
                                              (100, 4097, 2 ** 24, 0.2), (64, 8193, 2 ** 20, 0.6), (30, 20483, 2 ** 24, 0.2)])
-@pytest.mark.parametrize("options", [{}, {"core_depth": 0}, {"core_depth": 0, "core_after": 0, "core_width": 1}, {"core_refine": 0}])
+@pytest.mark.parametrize("options", [{}, {"core_depth": 0}, {"core_depth": 0, "core_after": 0, "core_width": 1}, {"core_refine": 0},
+                                     {"core_depth": 0, "core_wide": 1, "core_narrow": 16}])
 def test_phases_on_lists_reach_the_optimum(orc, n, m, high, masked, options):
     import paper_2303_13803_amd as mm
     W = synth.uniform_matrix(71, n, m, high, masked)
