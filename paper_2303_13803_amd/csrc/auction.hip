@@ -795,6 +795,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
             rc = forward ? mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr)
                          : mf_core_lists(ctx, rev, rm, 1, ctx->price, ctx->col2row);
             if (rc != MF_OK) return rc;
+            st.columns_ready &= ~(forward ? 1u : 2u);
             if (!forward) plan.have_columns = true;
             continue;
         }

@@ -32,12 +32,16 @@ constexpr int CORE_PUSH_BUFFER = 4096;
 constexpr int CORE_MAX_SOURCES = 64;
 constexpr int CORE_MAX_WORKGROUPS = 1024;
 constexpr int CORE_SLICE = 1024;                    // entries of a whole line one wavefront takes at a time
+// Rounds a workgroup goes on by itself within a step of a search or a refinement, and rows it does so
+// with at most (four for each of its wavefronts).  4 to 16 rounds measure the same within 3 %.
+constexpr int CORE_OWN_ROUNDS = 10, CORE_OWN_MOST = 32;
 constexpr unsigned long long CORE_INF = ~0ull;
 constexpr unsigned CORE_IN_TREE = 0xffffffffu;
 constexpr int CORE_NO_LABEL = INT32_MIN;
 constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
 constexpr unsigned CORE_GAVE_UP = 0x80000000u;
 constexpr double CORE_FAR = 1.0e300;                  // no candidate
+constexpr double CORE_WHOLE = 2.0e300;                // in Core's remainder: the line has been read whole
 constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose list holds all of its entries
 
 // ---------------------------------------------------------------- the lists
@@ -225,12 +229,12 @@ struct alignas(256) CoreCtl {
     int whole_count[4];                                  // rows whose whole lines a refinement looks at next (same ring)
     unsigned dense[4];                                   // whole lines read in an epoch (same ring)
     alignas(128) unsigned long long slack[3];            // see slack_of: bits of a non-negative double, two means
-    int rev_count;
+    int rev_count, tree_count;
     // searches
     // (read together, a lane each: [0..2] lowest label left per slot, [3..5] path ends found, [6..8] frontier lengths, [9] sink, [10..12] lines to be read whole)
     alignas(128) unsigned long long low[3];
     unsigned long long sink_found[3], frontier[3], sink, whole_front[3];
-    alignas(128) unsigned long long src_profit[CORE_MAX_SOURCES], src_outside[CORE_MAX_SOURCES];
+    alignas(128) unsigned long long src_profit[CORE_MAX_SOURCES], src_outside[CORE_MAX_SOURCES], src_dropped[CORE_MAX_SOURCES];
     alignas(128) unsigned jump_pending[CORE_JUMP_PASSES + 1];
     // refinement
     alignas(128) unsigned failed[3];
@@ -238,7 +242,8 @@ struct alignas(256) CoreCtl {
     alignas(128) double eps[MF_CORE_PHASES];
     int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];   // bidders that may be left over (second: while few have given up)
     // what the launch reports
-    alignas(128) int reason, phase, stage, count, parity, phases_run;
+    alignas(128) int reason, phase, stage, count, parity;
+    unsigned columns_ready;
     unsigned long long bids, depth, steps, scans, whole_lines, rested;
 };
 
@@ -250,6 +255,8 @@ struct CoreSide {
     unsigned long long *otherword;      // opposite (dual, holder) words
     double *other_dual;                 // the same duals, brought up to date at the end of a side
     const int2 *entries;
+    int *t_start, *t_at;                // the lists by opposite line: where each one's entries start (and, while they are made, end)
+    int2 *t_entries;                    // (line, weight)
     const double *bound, *built, *reach;    // built: the opposite duals when the lists were made; reach: from a line's best entry to its bound
 };
 
@@ -261,9 +268,11 @@ struct CoreArgs {
     unsigned long long rested_before;
     int have_columns;                   // the lists of side 1 exist
     int may_refine;
+    unsigned columns_ready;
     double stale_rise;
     double stale;                       // epsilons a dual may have come down since the lists were made before they are made again
-    int refine_rounds, refined;         // refined: a launch before this one has begun the refinement it starts with
+    int refine_rounds, refine_patience; // rounds in all; rounds without a new least number of rows left
+    int refined;                     // refined: a launch before this one has begun the refinement it starts with
     double refine_lower;
     double refine_below;                // epsilon at or below which a complete phase is followed by a refinement
     int path_max;
@@ -278,7 +287,7 @@ struct CoreArgs {
     int dense_limit;
     int frontier_room;
     double bid_limit;
-    int *row2col, *col2row;
+    int *row2col, *col2row, *tree;
     unsigned long long *rowword;        // == side[1].otherword
     int *list0, *list1;
     // searches and refinement
@@ -286,6 +295,8 @@ struct CoreArgs {
     unsigned *stamp;
     int *held, *jump;
     unsigned long long *parent;
+    double *base;                       // [lines] of a line that has been scanned: length of its path + its profit + eps; else CORE_FAR
+    double *dropped;                    // [columns] the shortest candidate the holder's scan left out because it lay beyond every path end
     double *remainder;                  // [columns] how far off the nearest unlisted entry of the holder's line is at least
     int *whole0, *whole1;               // lines to be read whole (by step parity)
     int32_t *held_weight;               // [max(rows, columns)] weight of each opposite line's pair with its holder
@@ -340,12 +351,12 @@ struct Core {
     CoreCtl *ctl;
     CoreShared &sh;
     unsigned G, rank;
-    unsigned generation;
+    unsigned generation, columns_ready;     // columns_ready: the sides whose lists exist by column (bits)
     int tid, lane, wave;
     unsigned bids, depth, steps, scans, whole, rests;          // this wavefront's counts
 
     __device__ Core(const CoreArgs &args, CoreCtl *c, CoreShared &s)
-        : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), tid(threadIdx.x), lane(threadIdx.x & 63),
+        : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), columns_ready(args.columns_ready), tid(threadIdx.x), lane(threadIdx.x & 63),
           wave(threadIdx.x >> 6), bids(0), depth(0), steps(0), scans(0), whole(0), rests(0) {}
 
     __device__ int gtid() const { return (int)rank * CORE_THREADS + tid; }
@@ -490,6 +501,30 @@ struct Core {
         for (unsigned t = tid; t < mine; t += CORE_THREADS) store_i32(&next[sh.base + t], (int)sh.list[t]);
     }
 
+    // The same without a place in `next` for more than one of each: lines kept may be there twice.
+    __device__ __forceinline__ bool keep(int b)
+    {
+        const unsigned slot = atomicAdd(&sh.pushes, 1u);
+        if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)b;
+        return slot < (unsigned)CORE_PUSH_BUFFER;
+    }
+    __device__ __forceinline__ void hand_on(int *next, int *counter, unsigned from, unsigned mark)
+    {
+        __syncthreads();
+        const unsigned to = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+        for (unsigned t0 = from + wave * 64; t0 < to; t0 += CORE_THREADS) {
+            const unsigned t = t0 + lane;
+            const int b = t < to ? (int)sh.list[t] : 0;
+            const bool first = t < to && atomicExch(&a.stamp[b], mark) != mark;
+            const unsigned long long all = __ballot(first);
+            if (!all) continue;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(counter, __popcll(all));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (first) store_i32(&next[at + __popcll(all & ((1ull << lane) - 1ull))], b);
+        }
+    }
+
     // The most any opposite dual has come down since the side's lists were made (a list's bound holds
     // for entries that were worth so much less then).  ok: false when a wait ran out.  *stale: the duals
     // have risen, on average, by a good part of what the lists reach below their best entries, so
@@ -530,6 +565,53 @@ struct Core {
             store_u32(&ctl->dense[gtid()], 0u);
             store_i32(&ctl->whole_count[gtid()], 0);
         }
+    }
+
+    // The side's lists once more by opposite line (columns, in a search): made when a search first
+    // needs them and good as long as the lists are.
+    __device__ __forceinline__ bool by_column(const CoreSide &s)
+    {
+        const int total = s.lines * CORE_LIST;
+        for (int k = gtid(); k < s.len; k += gsize()) store_i32(&s.t_at[k], 0);
+        if (!barrier()) return false;
+#pragma unroll 4
+        for (int e = gtid(); e < total; e += gsize()) {
+            const int2 entry = s.entries[e];
+            if (entry.y != MF_INFEASIBLE) atomicAdd(&s.t_at[entry.x], 1);
+        }
+        if (!barrier()) return false;
+        if (rank == 0) {                                     // running sums: a stretch of columns per thread
+            const int per = (s.len + CORE_THREADS - 1) / CORE_THREADS, first = tid * per, last = min(first + per, s.len);
+            int mine = 0;
+            for (int k = first; k < last; ++k) mine += load_fresh_i32(&s.t_at[k]);
+            int *sums = (int *)sh.list;
+            __syncthreads();
+            sums[tid] = mine;
+            __syncthreads();
+            for (int d = 1; d < CORE_THREADS; d <<= 1) {
+                const int o = tid >= d ? sums[tid - d] : 0;
+                __syncthreads();
+                sums[tid] += o;
+                __syncthreads();
+            }
+            int run = sums[tid] - mine;
+            for (int k = first; k < last; ++k) {
+                const int n = load_fresh_i32(&s.t_at[k]);
+                store_i32(&s.t_start[k], run);
+                store_i32(&s.t_at[k], run);
+                run += n;
+            }
+        }
+        if (!barrier()) return false;
+#pragma unroll 4
+        for (int e = gtid(); e < total; e += gsize()) {
+            const int2 entry = s.entries[e];
+            if (entry.y != MF_INFEASIBLE) {
+                const int at = atomicAdd(&s.t_at[entry.x], 1);
+                store_through((unsigned long long *)&s.t_entries[at], (unsigned long long)(unsigned)(e / CORE_LIST) | ((unsigned long long)(unsigned)entry.y << 32));
+            }
+        }
+        return barrier();
     }
 
     __device__ __forceinline__ int search(const CoreSide &s, double eps, double slack, int count, const int *list, int *next, int *counter);
@@ -601,6 +683,14 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
 // at a time).  Here a scanned line costs its list; what lies beyond the list is bounded below by
 // the length the list's bound gives, and only a line for which that is shorter than the nearest
 // path end known is read whole.
+//
+// When a path is served only the columns of its root's tree change price, and only they lose their
+// labels: no label of another tree can become shorter, because a column of the tree is, at its raised
+// price, at least as far from any scanned row as the served path was long.  The tree's columns get
+// their new labels from the scanned rows whose lists they are on, through the lists kept by column, and
+// candidates a scan left out because they lay beyond the path end of the time are remembered by
+// the shortest one.  (Scanning every labelled row again after each path was 600,000 scans, not 50,000, for
+// a 20,000 x 20,000 matching.)
 __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, double slack, int listed_count, const int *list, int *next, int *counter)
 {
     const int count = min(listed_count, CORE_MAX_SOURCES);
@@ -608,10 +698,13 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         store_through(&a.label[k], CORE_INF);
         store_through(&a.expanded[k], CORE_INF);
         store_f64(&a.remainder[k], CORE_FAR);
+        store_f64(&a.dropped[k], CORE_FAR);
         store_u32(&a.stamp[k], 0u);
         const int h = word_id(load_fresh_u64(&s.otherword[k]));
         if (h >= 0) store_i32(&a.held_weight[k], s.A[(size_t)h * s.pitch + k]);
     }
+    for (int i = gtid(); i < s.lines; i += gsize()) store_f64(&a.base[i], CORE_FAR);
+    if (!barrier()) return MF_CORE_ABORT;
     for (int item = gwave(); item < count; item += gwaves()) {
         const int r = load_fresh_i32(&list[item]);
         double outside;
@@ -621,6 +714,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
             store_through(&ctl->src_profit[item], (unsigned long long)__double_as_longlong(best - eps));
             store_through(&ctl->src_outside[item], (unsigned long long)__double_as_longlong(outside));
             store_i32(&a.held[r], -1 - item);
+            if (best - eps > 0.0) store_f64(&a.base[r], best);
         }
     }
     if (gtid() < 3) {
@@ -647,6 +741,11 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
     }
     __syncthreads();
     int n_alive = sh.n_alive;
+    const unsigned side_bit = s.otherword == a.side[0].otherword ? 1u : 2u;
+    if (n_alive > 1 && !(columns_ready & side_bit)) {
+        if (!by_column(s)) return MF_CORE_ABORT;
+        columns_ready |= side_bit;
+    }
     auto resting_bidders = [&]() {
         unsigned long long best = CORE_INF;
         for (int e = 0; e < n_alive; ++e) {
@@ -724,15 +823,25 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                     if (at < 0 && at != CORE_NO_LABEL) root = -1 - at;
                 }
                 if (lost || root < 0 || root >= count) { status = MF_CORE_DENSE; break; }
+                if (tid == 0) sh.pushes = 0u;
+                if (gtid() == 0) { store_i32(&ctl->tree_count, 0); store_f64(&a.base[sh.row[root]], CORE_FAR); }
+                if (!barrier()) return MF_CORE_ABORT;
                 for (int k = gtid(); k < s.len; k += gsize()) {
                     if (load_fresh_i32(&a.jump[k]) != -1 - root) continue;
                     store_u32(&a.stamp[k], CORE_IN_TREE);
                     const unsigned long long d_int = load_fresh_u64(&a.label[k]) >> MF_ID_BITS;
+                    const unsigned long long cw = load_fresh_u64(&s.otherword[k]);
+                    if (word_id(cw) >= 0) store_f64(&a.base[word_id(cw)], CORE_FAR);        // its holder's scan no longer counts
+                    {
+                        const unsigned slot = atomicAdd(&sh.pushes, 1u);
+                        if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)k;
+                        else store_i32(&a.tree[atomicAdd(&ctl->tree_count, 1)], k);
+                    }
                     if (d_int < d_star) {
-                        const unsigned long long cw = load_fresh_u64(&s.otherword[k]);
                         store_through(&s.otherword[k], pack_word(word_dual(cw) + (double)(long long)(d_star - d_int), (int)(cw & MF_ID_MASK)));
                     }
                 }
+                flush(a.tree, &ctl->tree_count);
                 if (!barrier()) return MF_CORE_ABORT;
                 if (rank == 0) {
                     if (tid == 0) {
@@ -766,26 +875,73 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                         store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
                     }
                 }
+                // The tree's columns lose their labels.  What the others have reached stays as it is: a
+                // column of the tree, at its raised price, is at least as far from any of them as the
+                // path just served was long.
                 for (int k = gtid(); k < s.len; k += gsize()) {
                     if (load_fresh_u32(&a.stamp[k]) == CORE_IN_TREE) {
                         store_through(&a.label[k], CORE_INF);
                         store_u32(&a.stamp[k], 0u);
+                        store_through(&a.expanded[k], CORE_INF);
+                        store_f64(&a.remainder[k], CORE_FAR);
+                        store_f64(&a.dropped[k], CORE_FAR);
+                    } else if (load_fresh(&a.remainder[k]) > CORE_FAR) {
+                        // a line read whole may have labelled such columns: it is due again from there on
+                        const int i = word_id(load_fresh_u64(&s.otherword[k]));
+                        store_f64(&a.remainder[k], fmax(load_fresh(&a.base[i]) - (s.bound[i] + slack), (double)(long long)d_star));
                     }
-                    store_through(&a.expanded[k], CORE_INF);
                 }
                 __syncthreads();
                 if (tid == 0) {
                     int n = 0;
                     for (int e = 0; e < n_alive; ++e) if (sh.alive[e] != root) sh.alive[n++] = sh.alive[e];
                     sh.n_alive = n;
-                    for (int e = 0; e < n; ++e) sh.remainder[sh.alive[e]] = sh.profit[sh.alive[e]] + eps - sh.outside[sh.alive[e]];
+                    for (int e = 0; e < n; ++e) {
+                        const int j = sh.alive[e];
+                        if (sh.remainder[j] > CORE_FAR) sh.remainder[j] = fmax(sh.profit[j] + eps - sh.outside[j], (double)(long long)d_star);
+                    }
                 }
                 if (!barrier()) return MF_CORE_ABORT;
                 n_alive = sh.n_alive;
                 agreed_sink = resting_bidders();
                 since_served = 0;
                 --step;
-                from_bidders = true; sweep_next = false; swept = false;
+                if (n_alive > 0) {
+                    // new labels for the tree's columns: a wavefront per column, or stretch of one's entries,
+                    // looks at the scanned rows whose lists it is on
+                    const int n_tree = load_fresh_i32(&ctl->tree_count);
+                    constexpr int STRETCH = 512;
+                    for (int it = gwave(); it < n_tree; it += gwaves()) {
+                        const int k = load_fresh_i32(&a.tree[it]);
+                        const int from = load_fresh_i32(&s.t_start[k]), to = load_fresh_i32(&s.t_at[k]);
+                        const double price = word_dual(load_fresh_u64(&s.otherword[k]));
+                        for (int e0 = from; e0 < to; e0 += STRETCH) {
+                            double best = CORE_FAR;
+                            int who = 0;
+#pragma unroll
+                            for (int q = 0; q < STRETCH / 64; ++q) {
+                                const int e = e0 + q * 64 + lane;
+                                if (e < to) {
+                                    const unsigned long long entry = load_fresh_u64((const unsigned long long *)&s.t_entries[e]);
+                                    const int i = (int)(unsigned)(entry & 0xffffffffull);
+                                    const double cand = load_fresh(&a.base[i]) - fma(a.Kd, (double)(int)(entry >> 32), -price);
+                                    if (cand < best) { best = cand; who = i; }
+                                }
+                            }
+                            const double least = -wave_max(-best);
+                            if (least < CORE_FAR * 0.5) {
+                                const int i = wave_min(best == least ? who : 0x7fffffff);
+                                if (lane == 0) {
+                                    const unsigned long long mine = ((unsigned long long)(long long)least << MF_ID_BITS) | (unsigned long long)i;
+                                    if (mine < load_fresh_u64(&a.label[k])) store_through(&a.label[k], mine);
+                                }
+                                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                            }
+                        }
+                    }
+                    if (!barrier()) return MF_CORE_ABORT;
+                }
+                from_bidders = false; sweep_next = true; swept = false;
                 continue;
             }
             low = (double)(long long)lo;
@@ -841,13 +997,24 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
             if (shorter(mine, seen)) settle(cand, k, word, mine, seen, atomicCAS(&a.label[k], seen, mine));
         };
         int *whole_list = (step & 1u) ? a.whole1 : a.whole0, *next_whole = (step & 1u) ? a.whole0 : a.whole1;
+        unsigned taken = 0;                                         // of sh.list: scanned already
         if (nf + nw > 0) {
             swept = false;
-            for (int it = gwave(); it < nf; it += gwaves()) {
-                int i, mine_col = -1;
-                if (from_bidders) i = sh.row[sh.alive[it]];
-                else {
-                    const unsigned long long entry = load_fresh_u64(&frontier[it]);
+            // With few rows on the frontier a workgroup goes on with what its own scans reach for some
+            // rounds before the next step shares it out.  A path is some 70 rows long and each of
+            // them took a step of 4.5 us, 2.4 us of it to hand over to everybody else and wait for
+            // them; a round of its own takes 2 us (all searches of a 20,000 x 20,000 matching
+            // 11.8 -> 6.5 ms, 1024 x 1024 1.1 -> 0.7 ms).
+            int here = nf, first = gwave(), stride = gwaves();
+            unsigned start = 0;
+            for (int round = 0;; ++round) {
+            for (int it = first; it < here; it += stride) {
+                int i, mine_col;                                     // (a bidder: -1 - its number)
+                if (round == 0 && from_bidders) {
+                    mine_col = -1 - sh.alive[it];
+                    i = sh.row[-1 - mine_col];
+                } else {
+                    const unsigned long long entry = round ? sh.list[start + it] : load_fresh_u64(&frontier[it]);
                     mine_col = (int)(unsigned)(entry & 0xffffffffull);
                     i = (int)(unsigned)(entry >> 32);
                 }
@@ -856,7 +1023,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 const double outside = s.bound[i] + slack;
                 unsigned long long lw = 0ull, held_word = 0ull, ex = CORE_INF;
                 int32_t w_held = 0;
-                if (!from_bidders) {
+                if (mine_col >= 0) {
                     lw = load_fresh_u64(&a.label[mine_col]);
                     held_word = load_fresh_u64(&s.otherword[mine_col]);
                     w_held = load_fresh_i32(&a.held_weight[mine_col]);
@@ -865,17 +1032,21 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 const unsigned long long w0 = load_fresh_u64(&s.otherword[e0.x]), w1 = load_fresh_u64(&s.otherword[e1.x]);
                 const unsigned long long l0 = load_fresh_u64(&a.label[e0.x]), l1 = load_fresh_u64(&a.label[e1.x]);
                 double dist, profit;
-                if (from_bidders) { dist = 0.0; profit = sh.profit[sh.alive[it]]; }
+                if (mine_col < 0) { dist = 0.0; profit = sh.profit[-1 - mine_col]; }
                 else {
                     if (lw == CORE_INF || (lw >> MF_ID_BITS) >= ex) continue;     // (scanned from that label already)
                     dist = (double)(long long)(lw >> MF_ID_BITS);
                     profit = fma(a.Kd, (double)w_held, -word_dual(held_word));
                 }
                 const double base = dist + profit + eps;
+                double left_out;
                 {
                     const double c0 = candidate(base, e0.y, w0), c1 = candidate(base, e1.y, w1);
                     const unsigned long long m0 = label_of(c0, i), m1 = label_of(c1, i);
                     const bool try0 = c0 < CORE_FAR && shorter(m0, l0), try1 = c1 < CORE_FAR && shorter(m1, l1);
+                    // (what lies beyond the nearest path end is left out until that end is served)
+                    const double x0 = base - fma(a.Kd, (double)e0.y, -word_dual(w0)), x1 = base - fma(a.Kd, (double)e1.y, -word_dual(w1));
+                    left_out = fmin(e0.y != MF_INFEASIBLE && !(x0 < bound) ? x0 : CORE_FAR, e1.y != MF_INFEASIBLE && !(x1 < bound) ? x1 : CORE_FAR);
                     unsigned long long was0 = 0ull, was1 = 0ull;
                     if (try0) was0 = atomicCAS(&a.label[e0.x], l0, m0);
                     if (try1) was1 = atomicCAS(&a.label[e1.x], l1, m1);
@@ -883,7 +1054,11 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                     if (try1) settle(c1, e1.x, w1, m1, l1, was1);
                 }
                 // (last: a load that is waited for after a store waits for the store as well)
-                if (!from_bidders && lane == 0) {
+                left_out = -wave_max(-left_out);
+                if (mine_col < 0 && lane == 0) store_through(&ctl->src_dropped[-1 - mine_col], (unsigned long long)__double_as_longlong(left_out));
+                if (mine_col >= 0 && lane == 0) {
+                    store_f64(&a.base[i], base);
+                    store_f64(&a.dropped[mine_col], left_out);
                     store_through(&a.expanded[mine_col], lw >> MF_ID_BITS);
                     // (what is not on the list is at least this far away: looked at when the window gets there)
                     store_f64(&a.remainder[mine_col], base - outside);
@@ -892,6 +1067,16 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                         ends_at(((unsigned long long)(long long)(dist + profit) << 21) | (1ull << 20) | (unsigned long long)i);
                 }
                 ++scans;
+            }
+            if (round >= CORE_OWN_ROUNDS || 2 * nf > gwaves()) break;
+            __syncthreads();
+            const unsigned end = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+            __syncthreads();
+            start = taken;
+            here = (int)(end - taken);
+            if (here == 0 || here > CORE_OWN_MOST) break;
+            taken = end;
+            first = wave; stride = CORE_WAVES;
             }
             // whole lines, in slices: a wavefront each
             const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
@@ -920,7 +1105,6 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 if (from == 0) ++whole;
             }
-            sweep_next = from_bidders && step > 1u;
             from_bidders = false;
         } else {
             swept = true;
@@ -932,32 +1116,45 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
             for (int k = gtid(); k < s.len; k += gsize()) {
                 const unsigned long long lw = load_fresh_u64(&a.label[k]);
                 const unsigned long long ex = load_fresh_u64(&a.expanded[k]);
-                const double rem = load_fresh(&a.remainder[k]);
+                const double rem = load_fresh(&a.remainder[k]), drop = load_fresh(&a.dropped[k]);
+                const int holder = word_id(load_fresh_u64(&s.otherword[k]));
                 const unsigned long long d_int = lw >> MF_ID_BITS;
                 if (lw == CORE_INF) continue;
-                if (d_int < ex) {
+                if (d_int < ex) {                       // not scanned from this label yet
                     const double d = (double)(long long)d_int;
                     if (!(d < bound)) continue;
-                    const int holder = word_id(load_fresh_u64(&s.otherword[k]));
                     if (holder < 0) atomicMin(&sh.sink, (d_int << 21) | (unsigned long long)k);
                     else if (d >= limit) atomicMin(&sh.low, d_int);
                     else reach(k, holder);
-                } else if (rem < bound) {
+                    continue;
+                }
+                // (a path may end in the row that holds it; found before, but ends found before one was served are forgotten)
+                const double rests = load_fresh(&a.base[holder]) - eps;
+                if (rests < bound) atomicMin(&sh.sink, ((unsigned long long)(long long)rests << 21) | (1ull << 20) | (unsigned long long)holder);
+                if (drop < bound) {                     // candidates left out then may be of use now: scan it again
+                    if (drop >= limit) atomicMin(&sh.low, (unsigned long long)(long long)drop);
+                    else { store_through(&a.expanded[k], CORE_INF); reach(k, holder); }
+                }
+                if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
-                    else { read_whole(k); store_f64(&a.remainder[k], CORE_FAR); }
+                    else { read_whole(k); store_f64(&a.remainder[k], CORE_WHOLE); }
                 }
             }
             if (rank == 0 && tid < n_alive) {
                 const int j = sh.alive[tid];
-                const double rem = sh.remainder[j];
+                const double rem = sh.remainder[j], drop = __longlong_as_double((long long)load_fresh_u64(&ctl->src_dropped[j]));
+                if (drop < bound) {
+                    if (drop >= limit) atomicMin(&sh.low, (unsigned long long)(long long)drop);
+                    else reach(-1 - j, sh.row[j]);
+                }
                 if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
-                    else { read_whole(-1 - j); sh.remainder[j] = CORE_FAR; }
+                    else { read_whole(-1 - j); sh.remainder[j] = CORE_WHOLE; }
                 }
             }
         }
         __syncthreads();
-        const unsigned pushed = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+        const unsigned pushed = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER) - taken;
         if (tid == 0) {
             sh.base = pushed ? (unsigned)atomicAdd(&ctl->frontier[p], (unsigned long long)pushed) : 0u;
             if (sh.sink != CORE_INF) ends_at(sh.sink);
@@ -965,7 +1162,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         }
         __syncthreads();
         for (unsigned t = tid; t < pushed; t += CORE_THREADS)
-            if (sh.base + t < (unsigned)a.frontier_room) store_through(&next_frontier[sh.base + t], sh.list[t]);
+            if (sh.base + t < (unsigned)a.frontier_room) store_through(&next_frontier[sh.base + t], sh.list[taken + t]);
         ++my_steps;
         if (!barrier()) return MF_CORE_ABORT;
     }
@@ -1012,7 +1209,7 @@ __device__ __forceinline__ int Core::refine(double lower_by)
     int count = s.lines;
     int done = -2;
     unsigned epoch = 0, whole_lines = 0;
-    int whole_rows = 0, fewest = count;
+    int whole_rows = 0, fewest = count, unimproved = 0;
     for (unsigned round = 1;; ++round, ++epoch) {
         const int *list = ((epoch & 1u) ? a.list1 : a.list0);
         int *next = ((epoch & 1u) ? a.list0 : a.list1);
@@ -1020,8 +1217,14 @@ __device__ __forceinline__ int Core::refine(double lower_by)
         if (gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); store_i32(&ctl->whole_count[(epoch + 2u) & 3u], 0); store_u32(&ctl->failed[(round + 1u) % 3u], 0u); }
         if (tid == 0) { sh.pushes = 0u; sh.failed = 0u; sh.dense = 0; }
         __syncthreads();
-        for (int item = gwave(); item < count; item += gwaves()) {
-            const int i = load_fresh_i32(&list[item]);
+        // (few rows left: a workgroup looks at the rows it has set off itself for some rounds, as in a
+        // search: 7 -> 3 us for each row of the last chains)
+        const bool few = count <= gwaves();
+        int here = count, first = gwave(), stride = gwaves();
+        unsigned start = 0, taken = 0;
+        for (int own = 0;; ++own) {
+        for (int item = first; item < here; item += stride) {
+            const int i = own ? (int)(unsigned)sh.list[start + item] : load_fresh_i32(&list[item]);
             const int2 *e = s.entries + (size_t)i * CORE_LIST;
             const int2 e0 = e[lane], e1 = e[lane + 64];
             const int col = load_fresh_i32(&a.row2col[i]);
@@ -1045,10 +1248,15 @@ __device__ __forceinline__ int Core::refine(double lower_by)
                     if (want1) was1 = atomicMax(&s.otherword[e1.x], m1);
                     const bool raised0 = was0 < m0, raised1 = was1 < m1;
                     unsigned st0 = round, st1 = round;
-                    if (raised0) st0 = atomicExch(&a.stamp[e0.x], round);
-                    if (raised1) st1 = atomicExch(&a.stamp[e1.x], round);
-                    if (st0 != round) push(word_id(w0), next, counter);
-                    if (st1 != round) push(word_id(w1), next, counter);
+                    if (few) {                          // (a row set off twice: sorted out when they are handed on)
+                        if (raised0 && !keep(word_id(w0))) failed = true;
+                        if (raised1 && !keep(word_id(w1))) failed = true;
+                    } else {
+                        if (raised0) st0 = atomicExch(&a.stamp[e0.x], round);
+                        if (raised1) st1 = atomicExch(&a.stamp[e1.x], round);
+                        if (st0 != round) push(word_id(w0), next, counter);
+                        if (st1 != round) push(word_id(w1), next, counter);
+                    }
                 }
                 if (lane == 0 && profit < outside) {    // the list does not show everything this row might want: all of it, next round
                     const int at = atomicAdd(&ctl->whole_count[(epoch + 1u) & 3u], 1);
@@ -1059,6 +1267,17 @@ __device__ __forceinline__ int Core::refine(double lower_by)
             }
             if (__any(failed)) { if (lane == 0) atomicOr(&sh.failed, 1u); break; }
             ++scans;
+        }
+        if (own >= CORE_OWN_ROUNDS || !few) break;
+        __syncthreads();
+        const unsigned end = min(sh.pushes, (unsigned)CORE_PUSH_BUFFER);
+        const bool failed = sh.failed != 0u;
+        __syncthreads();
+        here = (int)(end - taken);
+        if (failed || here == 0 || here > CORE_OWN_MOST) break;
+        start = taken;
+        taken = end;
+        first = wave; stride = CORE_WAVES;
         }
         const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
         for (int it = gwave(); it < whole_rows * slices; it += gwaves()) {
@@ -1075,11 +1294,14 @@ __device__ __forceinline__ int Core::refine(double lower_by)
                 if (w == MF_INFEASIBLE || !(word_dual(word) < need)) continue;
                 if (word_id(word) < 0) { atomicOr(&sh.failed, 1u); break; }
                 const unsigned long long mine = pack_word(need, (int)(word & MF_ID_MASK));
-                if (atomicMax(&s.otherword[j], mine) < mine && atomicExch(&a.stamp[j], round) != round) push(word_id(word), next, counter);
+                if (!(atomicMax(&s.otherword[j], mine) < mine)) continue;
+                if (few) { if (!keep(word_id(word))) atomicOr(&sh.failed, 1u); }
+                else if (atomicExch(&a.stamp[j], round) != round) push(word_id(word), next, counter);
             }
             if (from == 0) ++whole;
         }
-        flush(next, counter);
+        if (few) hand_on(next, counter, taken, round);
+        else flush(next, counter);
         if (tid == 0 && sh.failed) atomicOr(&ctl->failed[round % 3u], 1u);
         if (tid == 0 && sh.dense) atomicAdd(&ctl->dense[(epoch + 1u) & 3u], (unsigned)sh.dense);
         if (!barrier()) return -1;
@@ -1091,8 +1313,9 @@ __device__ __forceinline__ int Core::refine(double lower_by)
         if (whole_lines > (unsigned)a.dense_limit) { done = 2; break; }
         // (on the way to a proof fewer and fewer rows are left; once more and more of them are, prices
         // are going round and round)
-        fewest = min(fewest, count);
-        if (round >= (unsigned)a.refine_rounds || count > fewest + fewest / 4 + 64) { done = 0; break; }         // prices that go round and round: not optimal yet
+        unimproved += few ? CORE_OWN_ROUNDS + 1 : 1;
+        if (count < fewest) { fewest = count; unimproved = 0; }
+        if (round >= (unsigned)a.refine_rounds || unimproved > a.refine_patience || count > fewest + fewest / 4 + 64) { done = 0; break; }
     }
     if (gtid() == 0) steps += 1;
     return done;
@@ -1116,6 +1339,7 @@ __device__ __forceinline__ int Core::leave(int reason, int phase, int stage, int
         ctl->count = count;
         ctl->parity = parity;
         ctl->steps = steps;
+        ctl->columns_ready = columns_ready;
         ctl->depth = depth;
     }
     return reason;
@@ -1285,6 +1509,7 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
     ctl->die = -1;
     ctl->joined = 0u; ctl->arrived = 0u;
     ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
+    ctl->columns_ready = 0u;
     ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_lines = 0ull; ctl->rested = 0ull;
 }
 
@@ -1337,8 +1562,8 @@ int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, do
 int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st)
 {
     CoreArgs a{};
-    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
-    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
+    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
+    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
     a.Kd = fwd.Kd;
     CorePhases phases{};
     for (int k = 0; k < plan.n_phases; ++k) { phases.eps[k] = (double)plan.eps[k]; phases.stop[k] = plan.stop[k]; phases.stop_grown[k] = plan.stop_grown[k]; }
@@ -1352,14 +1577,17 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.stale_rise = 0.35;
     a.refine_below = plan.refine_below;
     a.refine_rounds = 256;
+    a.refine_patience = 40;
     a.refine_lower = 256.0;
     a.path_max = ctx->path_max;
     a.path_after = ctx->path_after < ctx->core_after ? ctx->path_after : ctx->core_after;
     a.tail_steps = ctx->phase_tail_steps;
     a.steps_many = ctx->core_many; a.steps_few = ctx->core_few;
     a.path_width = (double)ctx->core_width;
-    a.frontier_high = ctx->path_frontier_rows;
+        a.frontier_high = ctx->path_frontier_rows;
     a.spin_limit = ctx->path_spin_limit;
+    a.columns_ready = st->columns_ready;
+    a.base = ctx->core_base; a.dropped = ctx->core_dropped; a.tree = ctx->core_tree;
     a.wide = st->wide; a.use_wide = plan.use_wide ? 1 : 0; a.narrow_at = ctx->core_narrow; a.refined = st->refined;
     a.dense_limit = 128 + rn / 64;
     {
@@ -1383,6 +1611,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
     const CoreCtl &h = *(const CoreCtl *)ctx->h_core_ctl;
+    st->columns_ready = h.columns_ready;
     st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
     st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;

@@ -152,6 +152,9 @@ struct mf_ctx {
     int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
     int core_width;                 // label window of a search on lists, in epsilons
     double *core_bound[2], *core_built[2], *core_reach[2], *core_depth, *h_core_depth;
+    int *core_t_start[2], *core_t_at[2], *core_tree;    // the lists by opposite line (searches)
+    int2 *core_t_entries[2];
+    double *core_base, *core_dropped;
     unsigned long long *core_parent;
     int32_t *core_weight;
     void *core_ctl, *h_core_ctl;
@@ -233,6 +236,7 @@ struct mf_core_plan {
 struct mf_core_state {
     int reason, phase, stage, count, parity;
     int wide, refined;
+    unsigned columns_ready;             // the sides whose lists also exist by opposite line (bits)
     long long bids, depth, steps, scans, rested, bytes, whole;      // summed over launches
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
