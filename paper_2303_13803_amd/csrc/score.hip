@@ -21,18 +21,131 @@ union Half8Words { half8 v; unsigned int u[4]; uint4 q; };
 
 namespace {
 
-__global__ void project_kernel(const float *__restrict__ X, int rows, int F,
-                               const float *__restrict__ W1, int col_off,
-                               const float *__restrict__ bias, int H, float *__restrict__ P)
+// Both layer-1 projections, P_on = W1[:, :F] x + b1 and P_off = W1[:, F:] x, and the largest
+// magnitude of everything the fp16 pieces are scaled by (range[0..4], as bit patterns of non-negative
+// floats, which order like unsigned integers; zero on entry).
+//
+// A workgroup takes PROJECT_ROWS workloads of one side and 64 hidden units: lane k of every wavefront is
+// hidden unit k of the slab, and a wavefront does PROJECT_ROWS / 4 rows, so that one LDS read of a weight
+// (a row of 64, no conflicts) serves them all and a feature is a broadcast.  Weights and features are
+// staged PROJECT_FEATURES at a time; the sum runs over the features in order, starting from the bias.  A
+// thread per output, reading its weights 2F floats apart from its neighbour's, took 311 us each for
+// 20,000 workloads x 128 units where storing them takes 2, and the ranges another 40 us of reading it
+// all back.  The last PROJECT_EXTRA workgroups look at W2 and the SM term.
+constexpr int PROJECT_ROWS = 32, PROJECT_FEATURES = 32, PROJECT_EXTRA = 4;
+
+struct ProjectArgs {
+    const float *X[2];                                     // features: online, offline
+    int rows[2];
+    float *P[2];
+    const float *W1, *b1;
+    int F, H;
+    const float *range_of[3];                              // W2, W1sm, sm_off (the latter two may be null)
+    int range_count[3];
+    unsigned *range;                                       // null: not wanted
+};
+
+__device__ __forceinline__ void note_range(float mx, unsigned *slot, float *wave_mx)
 {
-    long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (long)rows * H) return;
-    int r = (int)(idx / H), k = (int)(idx % H);
-    const float *x = X + (size_t)r * F;
-    const float *w = W1 + (size_t)k * 2 * F + col_off;
-    float s = bias ? bias[k] : 0.0f;
-    for (int t = 0; t < F; ++t) s = fmaf(x[t], w[t], s);
-    P[idx] = s;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    if ((threadIdx.x & 63) == 0) wave_mx[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        mx = fmaxf(fmaxf(wave_mx[0], wave_mx[1]), fmaxf(wave_mx[2], wave_mx[3]));
+        // the maximum only grows, so an outdated (smaller) cached value at worst costs a redundant atomic
+        if (mx > 0.0f && __float_as_uint(mx) > *slot) atomicMax(slot, __float_as_uint(mx));
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
+{
+    __shared__ float w_lds[PROJECT_FEATURES][64];
+    __shared__ float x_lds[PROJECT_ROWS][PROJECT_FEATURES];
+    __shared__ float wave_mx[4];
+    const int tiles_on = (a.rows[0] + PROJECT_ROWS - 1) / PROJECT_ROWS, tiles_off = (a.rows[1] + PROJECT_ROWS - 1) / PROJECT_ROWS;
+    int tile = blockIdx.x;
+    if (tile >= tiles_on + tiles_off) {
+        if (!a.range || blockIdx.y > 0) return;
+        tile -= tiles_on + tiles_off;
+        for (int q = 0; q < 3; ++q) {
+            if (!a.range_of[q]) continue;
+            float mx = 0.0f;
+            for (int i = tile * 256 + threadIdx.x; i < a.range_count[q]; i += PROJECT_EXTRA * 256) mx = fmaxf(mx, fabsf(a.range_of[q][i]));
+            note_range(mx, &a.range[2 + q], wave_mx);
+        }
+        return;
+    }
+    const int side = tile >= tiles_on;
+    if (side) tile -= tiles_on;
+    const int k0 = blockIdx.y * 64, lane = threadIdx.x & 63, group = threadIdx.x >> 6;
+    constexpr int MINE = PROJECT_ROWS / 4;
+    const int row0 = tile * PROJECT_ROWS, rows = min(PROJECT_ROWS, a.rows[side] - row0);
+    const float *X = a.X[side] + (size_t)row0 * a.F, *W = a.W1 + (size_t)k0 * 2 * a.F + (side ? a.F : 0);
+    float sum[MINE];
+#pragma unroll
+    for (int r = 0; r < MINE; ++r) sum[r] = side == 0 ? a.b1[k0 + lane] : 0.0f;
+    for (int t0 = 0; t0 < a.F; t0 += PROJECT_FEATURES) {
+        const int depth = min(PROJECT_FEATURES, a.F - t0);
+        __syncthreads();
+        for (int e = threadIdx.x; e < 64 * PROJECT_FEATURES; e += 256) {
+            const int k = e / PROJECT_FEATURES, t = e % PROJECT_FEATURES;
+            if (t < depth) w_lds[t][k] = W[(size_t)k * 2 * a.F + t0 + t];
+        }
+        for (int e = threadIdx.x; e < PROJECT_ROWS * PROJECT_FEATURES; e += 256) {
+            const int r = e / PROJECT_FEATURES, t = e % PROJECT_FEATURES;
+            if (t < depth) x_lds[r][t] = r < rows ? X[(size_t)r * a.F + t0 + t] : 0.0f;
+        }
+        __syncthreads();
+        for (int t = 0; t < depth; ++t) {
+            const float w = w_lds[t][lane];
+#pragma unroll
+            for (int r = 0; r < MINE; ++r) sum[r] = fmaf(x_lds[group * MINE + r][t], w, sum[r]);
+        }
+    }
+    float mx = 0.0f;
+#pragma unroll
+    for (int r = 0; r < MINE; ++r) {
+        const int row = group * MINE + r;
+        if (row < rows) {
+            a.P[side][(size_t)(row0 + row) * a.H + k0 + lane] = sum[r];
+            mx = fmaxf(mx, fabsf(sum[r]));
+        }
+    }
+    if (a.range) note_range(mx, &a.range[side], wave_mx);
+}
+
+// What is prepared per workload before anything is ordered: its memory fraction and SM share, its rank
+// (zero), and the words later kernels of the call count or take maxima in.
+struct SetupArgs {
+    const float *X[2];                                     // online, offline
+    int rows[2];
+    int F, mem_feature, sm_feature[2];                     // sm_feature < 0: none
+    float *mem[2], *sm[2];
+    int32_t *rank[2], *order[2];                           // null: this side is not ordered
+    const int32_t *group;                                  // of the online side: order by group first (optional)
+    float *sorted[2];                                      // null: not wanted
+    int32_t *fit_len[2];
+    float mem_limit;
+    int slice[2];
+    unsigned long long *pairs_evaluated, *feasible_pairs;
+    int *largest;
+    unsigned *range;
+};
+
+__global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
+{
+    const int side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
+    if (side == 0 && r < 8) {
+        a.range[r] = 0u;
+        if (r == 0) { *a.pairs_evaluated = 0ull; if (a.feasible_pairs) *a.feasible_pairs = 0ull; if (a.largest) *a.largest = 0; }
+    }
+    if (r >= a.rows[side]) return;
+    const float *x = a.X[side] + (size_t)r * a.F;
+    a.mem[side][r] = x[a.mem_feature];
+    if (a.sm_feature[side] >= 0) a.sm[side][r] = x[a.sm_feature[side]];
+    if (a.rank[side]) a.rank[side][r] = 0;
 }
 
 // order[k] = the workload with the k-th smallest key (ties by index).  Keys are
@@ -53,12 +166,9 @@ constexpr int RANK_THREADS = 256, RANK_TILE = 2048;
 // keys still fill the device; rank[] starts at zero.  With GROUPED the order is
 // by group first (group[i] in [0, 2^15)) and by key within a group.
 template <bool GROUPED>
-__global__ __launch_bounds__(RANK_THREADS) void rank_count_kernel(const float *__restrict__ key,
-                                                                  const int32_t *__restrict__ group, int count,
-                                                                  int slice, int32_t *__restrict__ rank)
+__device__ __forceinline__ void count_ranks(const float *__restrict__ key, const int32_t *__restrict__ group, int count,
+                                            int slice, int32_t *__restrict__ rank, unsigned *tile, int *gtile)
 {
-    __shared__ __align__(16) unsigned tile[RANK_TILE];
-    __shared__ __align__(16) int gtile[GROUPED ? RANK_TILE : 4];
     const int i = blockIdx.x * RANK_THREADS + threadIdx.x;
     const unsigned mine = i < count ? ordered_bits(key[i]) : 0u;
     const int gmine = (GROUPED && i < count) ? group[i] : 0;
@@ -94,10 +204,24 @@ __global__ __launch_bounds__(RANK_THREADS) void rank_count_kernel(const float *_
     if (i < count && before) atomicAdd(&rank[i], before);
 }
 
-__global__ void order_from_rank_kernel(const int32_t *__restrict__ rank, int count, int32_t *__restrict__ order)
+// Both sides of the matrix (blockIdx.z).
+__global__ __launch_bounds__(RANK_THREADS) void rank_count_kernel(SetupArgs a)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) order[rank[i]] = i;
+    __shared__ __align__(16) unsigned tile[RANK_TILE];
+    __shared__ __align__(16) int gtile[RANK_TILE];
+    const int side = blockIdx.z, count = a.rows[side];
+    if (!a.rank[side] || (int)blockIdx.x * RANK_THREADS >= count || (int)blockIdx.y * a.slice[side] >= count) return;
+    if (side == 0 && a.group) count_ranks<true>(a.mem[0], a.group, count, a.slice[0], a.rank[0], tile, gtile);
+    else count_ranks<false>(a.mem[side], nullptr, count, a.slice[side], a.rank[side], tile, gtile);
+}
+
+__global__ __launch_bounds__(256) void order_kernel(SetupArgs a)
+{
+    const int side = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+    if (!a.rank[side] || i >= a.rows[side]) return;
+    const int at = a.rank[side][i];
+    a.order[side][at] = i;
+    if (a.sorted[side]) a.sorted[side][at] = a.mem[side][i];
 }
 
 // The staged matrix: rows and columns of the weight matrix in order of memory fraction.  Before
@@ -123,37 +247,32 @@ __global__ __launch_bounds__(256) void stage_marks_kernel(const float *__restric
     }
 }
 
-// *total += sum of len[0..count): how many pairs can share at all.
-__global__ void sum_lengths_kernel(const int32_t *__restrict__ len, int count, unsigned long long *total)
-{
-    unsigned long long t = 0;
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < count; k += gridDim.x * blockDim.x) t += (unsigned)len[k];
-    for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
-    if ((threadIdx.x & 63) == 0 && t) atomicAdd(total, t);
-}
-
-__global__ void gather_by_order_kernel(const float *__restrict__ value, const int32_t *__restrict__ order, int count,
-                                       float *__restrict__ out)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) out[k] = value[order[k]];
-}
-
 // In memory order the pairs that can share form, in every row, a prefix of the columns (and in
 // every column a prefix of the rows): len[k] = how many entries of `other` (ascending) fit next
 // to mine[k].  A binary search on the same float32 rule the marks were written with.
-__global__ void fit_prefix_kernel(const float *__restrict__ mine, int count, const float *__restrict__ other,
-                                  int other_count, float mem_limit, int32_t *__restrict__ len)
+// (columns with rows ordered by group first: count of all rows.)  Also how many pairs can share at all.
+__global__ __launch_bounds__(256) void fit_prefix_kernel(SetupArgs a)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= count) return;
-    const float a = mine[k];
-    int lo = 0, hi = other_count;                          // first position that does not fit
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a + other[mid] > mem_limit) hi = mid; else lo = mid + 1;
+    const int side = blockIdx.y, k = blockIdx.x * 256 + threadIdx.x;
+    int len = 0;
+    if (k < a.rows[side]) {
+        if (side == 1 && a.group) len = a.rows[0];
+        else {
+            const float mine = a.sorted[side][k];
+            const float *other = a.sorted[1 - side];
+            int lo = 0, hi = a.rows[1 - side];             // first position that does not fit
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (mine + other[mid] > a.mem_limit) hi = mid; else lo = mid + 1;
+            }
+            len = lo;
+        }
+        a.fit_len[side][k] = len;
     }
-    len[k] = lo;
+    if (side) return;
+    unsigned long long t = (unsigned)len;
+    for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+    if ((threadIdx.x & 63) == 0 && t) atomicAdd(a.feasible_pairs, t);
 }
 
 // The placement kernels see every weight once more: they note the largest on the way (the
@@ -243,42 +362,11 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
     }
 }
 
-__global__ void clear_counter_kernel(unsigned long long *c) { *c = 0ull; }
-
 __global__ void fill_flag_kernel(int *flag) { *flag = 0; }
 
-__global__ void fill_value_kernel(int32_t *p, int count, int value)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = value;
-}
-
-__global__ void fill_zero_kernel(int32_t *p, int count)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0;
-}
-
-// Largest magnitudes of up to five arrays (blockIdx.y picks one), as bit patterns of non-negative
-// floats, which order like unsigned integers: slots[y] = max |a_y[i]|.  The slots start at zero.
 __global__ void range_clear_kernel(unsigned *slots)
 {
     if (threadIdx.x < 8) slots[threadIdx.x] = 0u;
-}
-
-struct RangeArrays { const float *a[5]; long long count[5]; };
-
-__global__ __launch_bounds__(256) void range_kernel(RangeArrays arrays, unsigned *slots)
-{
-    const float *a = arrays.a[blockIdx.y];
-    if (!a) return;
-    const long long count = arrays.count[blockIdx.y];
-    float mx = 0.0f;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long long)gridDim.x * 256)
-        mx = fmaxf(mx, fabsf(a[i]));
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if ((threadIdx.x & 63) == 0 && mx > 0.0f) atomicMax(&slots[blockIdx.y], __float_as_uint(mx));
 }
 
 constexpr int PAIR_THREADS = 512;   // 8 wavefronts: two per SIMD share one LDS copy of W2
@@ -712,46 +800,37 @@ int launch_pair(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, 
 #undef MF_PAIR_CASE
 }
 
-// What the fp16 pieces of the scorer's hidden layer are scaled by depends on the largest
-// projections and weights: found here, after the projections, before the pair kernel.
-void launch_score_range(mf_ctx *ctx, const mf_predictor *p, int n, int m)
+// Layer 1 of everybody, and what the fp16 pieces of the hidden layer are scaled by (slots zero on entry).
+void launch_projections(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int n, const float *d_off, int m)
 {
-    if (!ctx->score_split) return;
-    RangeArrays arrays{};
-    arrays.a[0] = ctx->proj_on;  arrays.count[0] = (long long)n * p->H;
-    arrays.a[1] = ctx->proj_off; arrays.count[1] = (long long)m * p->H;
-    arrays.a[2] = p->d_W2;       arrays.count[2] = (long long)p->H * p->H;
-    arrays.a[3] = p->d_W1sm;     arrays.count[3] = p->H;
-    arrays.a[4] = p->d_W1sm ? ctx->sm_off : nullptr; arrays.count[4] = m;
-    hipLaunchKernelGGL(range_clear_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->score_range);
-    hipLaunchKernelGGL(range_kernel, dim3(64, 5), dim3(256), 0, ctx->stream, arrays, ctx->score_range);
+    ProjectArgs a{};
+    a.X[0] = d_on; a.X[1] = d_off;
+    a.rows[0] = n; a.rows[1] = m;
+    a.P[0] = ctx->proj_on; a.P[1] = ctx->proj_off;
+    a.W1 = p->d_W1; a.b1 = p->d_b1;
+    a.F = p->F; a.H = p->H;
+    a.range_of[0] = p->d_W2; a.range_count[0] = p->H * p->H;
+    a.range_of[1] = p->d_W1sm; a.range_count[1] = p->H;
+    a.range_of[2] = p->d_W1sm ? ctx->sm_off : nullptr; a.range_count[2] = m;
+    a.range = ctx->score_split ? ctx->score_range : nullptr;
+    const int tiles = (n + PROJECT_ROWS - 1) / PROJECT_ROWS + (m + PROJECT_ROWS - 1) / PROJECT_ROWS;
+    hipLaunchKernelGGL(project_kernel, dim3(tiles + PROJECT_EXTRA, p->H / 64), dim3(256), 0, ctx->stream, a);
 }
 
-// order[k] = the workload with the k-th smallest (group, key); rank[i] = its position k
-void order_by_memory(mf_ctx *ctx, const float *key, const int32_t *group, int count, int32_t *order,
-                     int32_t *rank)
+SetupArgs setup_args(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int n, const float *d_off, int m)
 {
-    const int blocks = (count + RANK_THREADS - 1) / RANK_THREADS;
-    int split = 2048 / blocks;
-    split = split < 1 ? 1 : (split > 64 ? 64 : split);
-    const int slice = ((count + split - 1) / split + 3) & ~3;
-    const dim3 grid(blocks, (count + slice - 1) / slice);
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(RANK_THREADS), 0, ctx->stream, rank, count);
-    if (group)
-        hipLaunchKernelGGL(rank_count_kernel<true>, grid, dim3(RANK_THREADS), 0, ctx->stream, key, group, count,
-                           slice, rank);
-    else
-        hipLaunchKernelGGL(rank_count_kernel<false>, grid, dim3(RANK_THREADS), 0, ctx->stream, key, group, count,
-                           slice, rank);
-    hipLaunchKernelGGL(order_from_rank_kernel, dim3(blocks), dim3(RANK_THREADS), 0, ctx->stream, rank,
-                       count, order);
-}
-
-__global__ void gather_feature_kernel(const float *__restrict__ X, int rows, int F, int feature,
-                                      float *__restrict__ out)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < rows) out[r] = X[(size_t)r * F + feature];
+    SetupArgs a{};
+    a.X[0] = d_on; a.X[1] = d_off;
+    a.rows[0] = n; a.rows[1] = m;
+    a.F = p->F; a.mem_feature = p->mem_feature;
+    a.sm_feature[0] = p->d_W1sm ? p->sm_on_feature : -1;
+    a.sm_feature[1] = p->d_W1sm ? p->sm_off_feature : -1;
+    a.mem[0] = ctx->mem_on; a.mem[1] = ctx->mem_off;
+    a.sm[0] = ctx->sm_on; a.sm[1] = ctx->sm_off;
+    a.mem_limit = p->mem_limit;
+    a.pairs_evaluated = ctx->pairs_evaluated;
+    a.range = ctx->score_range;
+    return a;
 }
 
 // segment[t] = number of workloads whose type is below t (t = 0..n_types); *bad is raised for
@@ -786,7 +865,6 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
                     float *d_sigma)
 {
     const mf_predictor *p0 = &preds[0];
-    const int F = p0->F;
     const bool typed = d_type != nullptr;
     int32_t type_first[MF_MAX_TYPES + 1] = {0};
     if (typed) {
@@ -803,48 +881,49 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
         if (bad) return MF_ERR_ARG;
     }
     MF_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
-    hipLaunchKernelGGL(gather_feature_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_on, n, F,
-                       p0->mem_feature, ctx->mem_on);
-    hipLaunchKernelGGL(gather_feature_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, d_off, m, F,
-                       p0->mem_feature, ctx->mem_off);
-    if (p0->d_W1sm) {
-        hipLaunchKernelGGL(gather_feature_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_on, n, F,
-                           p0->sm_on_feature, ctx->sm_on);
-        hipLaunchKernelGGL(gather_feature_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, d_off, m, F,
-                           p0->sm_off_feature, ctx->sm_off);
-    }
     // Pairs whose memory fractions do not fit get no score, so unless the caller wants every
     // score, walk rows and columns in memory order: the pairs that cannot fit then form one
     // corner of the tile grid and the kernel leaves them out.  Results land at the same places.
     const bool by_memory = ctx->fit_order && !d_sigma;
-    hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->pairs_evaluated);
-    hipLaunchKernelGGL(fill_flag_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->largest_weight);
+    // (each of these is a few microseconds of work: as eight launches, not twenty-two, the set-up of a
+    // 64 x 64 round takes 31 us, not 310)
+    SetupArgs a = setup_args(ctx, p0, d_on, n, d_off, m);
+    a.largest = ctx->largest_weight;
     ctx->largest_weight_known = false;
-    if (by_memory || typed) order_by_memory(ctx, ctx->mem_on, d_type, n, ctx->order_on, ctx->rank_on);
+    a.group = d_type;
+    if (by_memory || typed) { a.rank[0] = ctx->rank_on; a.order[0] = ctx->order_on; }
+    if (by_memory) {
+        a.rank[1] = ctx->rank_off; a.order[1] = ctx->order_off;
+        a.sorted[0] = ctx->mem_on_sorted; a.sorted[1] = ctx->mem_off_sorted;
+        a.fit_len[0] = ctx->fit_len_on; a.fit_len[1] = ctx->fit_len_off;
+        a.feasible_pairs = ctx->feasible_pairs;
+    }
+    const int most = n > m ? n : m, blocks = (most + 255) / 256;
+    hipLaunchKernelGGL(setup_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
+    if (by_memory || typed) {
+        int slices = 0;
+        for (int side = 0; side < 2; ++side) {
+            const int count = a.rows[side];
+            int split = 2048 / ((count + RANK_THREADS - 1) / RANK_THREADS);
+            split = split < 1 ? 1 : (split > 64 ? 64 : split);
+            a.slice[side] = ((count + split - 1) / split + 3) & ~3;
+            const int mine = (count + a.slice[side] - 1) / a.slice[side];
+            if (a.rank[side] && mine > slices) slices = mine;
+        }
+        hipLaunchKernelGGL(rank_count_kernel, dim3((most + RANK_THREADS - 1) / RANK_THREADS, slices, 2), dim3(RANK_THREADS), 0,
+                           ctx->stream, a);
+        hipLaunchKernelGGL(order_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
+    }
     const int64_t lds = ((int64_t)m + 3) & ~3ll;
     ctx->staged_n = ctx->staged_m = 0;
     if (by_memory) {
-        order_by_memory(ctx, ctx->mem_off, nullptr, m, ctx->order_off, ctx->rank_off);
-        hipLaunchKernelGGL(gather_by_order_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, ctx->mem_on,
-                           ctx->order_on, n, ctx->mem_on_sorted);
-        hipLaunchKernelGGL(gather_by_order_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->mem_off,
-                           ctx->order_off, m, ctx->mem_off_sorted);
         const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
         // feasibility is a prefix of every staged row (columns are in memory order) and, when the
         // rows are in memory order too - one predictor - of every staged column; with several
         // predictors the rows are ordered by type first and columns are read whole
-        hipLaunchKernelGGL(fit_prefix_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, ctx->mem_on_sorted,
-                           n, ctx->mem_off_sorted, m, p0->mem_limit, ctx->fit_len_on);
+        hipLaunchKernelGGL(fit_prefix_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
         hipLaunchKernelGGL(stage_marks_kernel, dim3(n, chunks), dim3(256), 0, ctx->stream, ctx->mem_on_sorted,
                            ctx->mem_off_sorted, n, m, p0->mem_limit, ctx->staged, lds, ctx->fit_len_on);
-        if (!typed)
-            hipLaunchKernelGGL(fit_prefix_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->mem_off_sorted,
-                               m, ctx->mem_on_sorted, n, p0->mem_limit, ctx->fit_len_off);
-        else
-            hipLaunchKernelGGL(fill_value_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->fit_len_off, m, n);
-        hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->feasible_pairs);
-        hipLaunchKernelGGL(sum_lengths_kernel, dim3(64), dim3(256), 0, ctx->stream, ctx->fit_len_on, n,
-                           ctx->feasible_pairs);
         ctx->staged_n = n;
         ctx->staged_m = m;
     }
@@ -857,13 +936,8 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     for (int t = 0; t < n_types; ++t) {
         const mf_predictor *p = &preds[t];
         const int H = p->H;
-        long tot = (long)n * H;
-        hipLaunchKernelGGL(project_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream,
-                           d_on, n, F, p->d_W1, 0, p->d_b1, H, ctx->proj_on);
-        tot = (long)m * H;
-        hipLaunchKernelGGL(project_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream,
-                           d_off, m, F, p->d_W1, F, (const float *)nullptr, H, ctx->proj_off);
-        launch_score_range(ctx, p, n, m);
+        if (t > 0) hipLaunchKernelGGL(range_clear_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->score_range);
+        launch_projections(ctx, p, d_on, n, d_off, m);
         MF_HIP(hipGetLastError());
         if (t == 0) MF_HIP(hipEventRecord(ctx->ev[1], ctx->stream));      // later types' projections count as scoring
         const int32_t *segment = typed ? ctx->type_segment + t : nullptr;
@@ -916,7 +990,7 @@ int mf_launch_rescore(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int
                       int m, int32_t *d_W, int64_t ldw, const int32_t *d_rows, int n_rows,
                       const int32_t *d_cols, int n_cols)
 {
-    const int H = p->H, F = p->F;
+    const int H = p->H;
     ctx->staged_n = ctx->staged_m = 0;       // the staged copy no longer matches the matrix
     ctx->largest_weight_known = false;
     // the lists index device arrays: refuse anything out of range before a kernel trusts it
@@ -933,25 +1007,10 @@ int mf_launch_rescore(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int
     MF_HIP(hipStreamSynchronize(ctx->stream));
     if (bad) return MF_ERR_ARG;
     MF_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
-    long tot = (long)n * H;
-    hipLaunchKernelGGL(project_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream,
-                       d_on, n, F, p->d_W1, 0, p->d_b1, H, ctx->proj_on);
-    tot = (long)m * H;
-    hipLaunchKernelGGL(project_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, ctx->stream,
-                       d_off, m, F, p->d_W1, F, (const float *)nullptr, H, ctx->proj_off);
-    hipLaunchKernelGGL(gather_feature_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_on, n, F,
-                       p->mem_feature, ctx->mem_on);
-    hipLaunchKernelGGL(gather_feature_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, d_off, m, F,
-                       p->mem_feature, ctx->mem_off);
-    if (p->d_W1sm) {
-        hipLaunchKernelGGL(gather_feature_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_on, n, F,
-                           p->sm_on_feature, ctx->sm_on);
-        hipLaunchKernelGGL(gather_feature_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, d_off, m, F,
-                           p->sm_off_feature, ctx->sm_off);
-    }
-    launch_score_range(ctx, p, n, m);       // over everybody, as a full scoring pass would find it
+    const SetupArgs a = setup_args(ctx, p, d_on, n, d_off, m);
+    hipLaunchKernelGGL(setup_kernel, dim3(((n > m ? n : m) + 255) / 256, 2), dim3(256), 0, ctx->stream, a);
+    launch_projections(ctx, p, d_on, n, d_off, m);          // of everybody, and so the range, as in a full scoring pass
     MF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->pairs_evaluated);
     ctx->pairs_total = (double)n_rows * (double)m + (double)n * (double)n_cols;
     MF_HIP(hipEventRecord(ctx->ev[1], ctx->stream));
     int rc = MF_OK;
