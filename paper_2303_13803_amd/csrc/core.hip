@@ -36,7 +36,7 @@ constexpr int CORE_SLICE = 1024;                    // entries of a whole line o
 // with at most (four for each of its wavefronts).  4 to 16 rounds measure the same within 3 %.
 constexpr int CORE_OWN_ROUNDS = 10, CORE_OWN_MOST = 32;
 constexpr unsigned long long CORE_INF = ~0ull;
-constexpr unsigned CORE_IN_TREE = 0xffffffffu;
+constexpr unsigned CORE_IN_TREE = 0xffffffffu, CORE_READ = 1u;     // of a column, in a search: in the tree being served; its holder's line has been read whole
 constexpr int CORE_NO_LABEL = INT32_MIN;
 constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
 constexpr unsigned CORE_GAVE_UP = 0x80000000u;
@@ -47,8 +47,11 @@ constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose lis
 // ---------------------------------------------------------------- the lists
 
 // One workgroup per line: the CORE_LIST entries with the largest K w - dual.  What bounds it is
-// reading the line, once: a thread keeps its up to NV groups of four entries, and their values, in
-// registers (0.5 ms for 20,000 lines of 20,000 entries; reading the line three times took 1.25 ms).
+// reading the line, once, and a dozen barriers: a thread keeps the values of its up to NV groups of
+// four entries in registers, as floats relative to a good entry (the few listed entries' weights are
+// read again), so that two workgroups of 1024 threads fit a compute unit and one reads while the other
+// waits (20,000 lines of 20,000 entries: 1.18 ms with weights and doubles kept, 0.93 ms; reading the line
+// three times took 1.25 ms).  The bound allows for the rounding.
 // The cut is found from a histogram of the distances to the line's best value in
 // eighths of a power of two: all entries of the bins that fit are taken, the next bin fills the
 // list up in an order that starts somewhere else in every line (tied bidders would otherwise all
@@ -57,17 +60,18 @@ constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose lis
 // would take longer than reading the line.
 // NV == 0: lines of any length, read three times.
 constexpr int LIST_BINS = 2048;
+constexpr float LIST_NONE = -3.0e38f;                // an entry that cannot be chosen
 
-__device__ __forceinline__ int distance_bin(double d)        // d >= 0; monotone
+__device__ __forceinline__ int distance_bin(float d)         // d >= 0; monotone
 {
-    return min((int)(__float_as_uint((float)d) >> 20), LIST_BINS - 1);
+    return min((int)(__float_as_uint(d) >> 20), LIST_BINS - 1);
 }
 // where a bin is counted: lane l of the wavefront that sums them up has bins 32 l .. 32 l + 31, a row apart
 __device__ __forceinline__ int bin_slot(int bin) { return (bin & 31) * 64 + (bin >> 5); }
 static_assert(LIST_BINS == 64 * 32, "32 bins per lane");
 
 template <int NT, int NV>
-__global__ __launch_bounds__(NT) void core_list_kernel(
+__global__ __launch_bounds__(NT, NV > 0 ? 8 : 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
     const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *depth,
     const double *__restrict__ own_dual, const int *__restrict__ partner)
@@ -92,52 +96,18 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
     const int turn = groups > 0 ? (int)(((unsigned)b * 2654435761u >> 8) % (unsigned)groups) : 0;
     for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
     constexpr int KEEP = NV > 0 ? NV : 1;
-    int4 kept_w[KEEP];
-    double kept_v[KEEP][4];
+    float kept_v[KEEP][4];
     auto group_of = [&](int g0) { const int g = g0 + turn; return g >= groups ? g - groups : g; };
-    auto read = [&](int g, int4 &w4, double *v) {
-        w4 = *(const int4 *)(line + g * 4);                  // lines are padded to a multiple of four
+    double ref = 0.0;
+    auto read = [&](int g, float *v) {
+        const int4 w4 = *(const int4 *)(line + g * 4);                  // lines are padded to a multiple of four
         const double2 p01 = *(const double2 *)(dual + g * 4);
         const double2 p23 = *(const double2 *)(dual + g * 4 + 2);
         const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
         const double p[4] = {p01.x, p01.y, p23.x, p23.y};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            v[e] = g * 4 + e < to && w[e] != MF_INFEASIBLE ? fma(Kd, (double)w[e], -p[e]) : NEG_HUGE;
-    };
-    if constexpr (NV > 0) {
-#pragma unroll
-        for (int q = 0; q < KEEP; ++q) {
-            const int g0 = tid + q * NT;
-            kept_w[q] = make_int4(MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) kept_v[q][e] = NEG_HUGE;
-            if (g0 < groups) read(group_of(g0), kept_w[q], kept_v[q]);
-        }
-    }
-    // what(position, weight, value) for the entries worth more than `above`
-    auto for_each = [&](double above, auto what) {
-        if constexpr (NV > 0) {
-#pragma unroll
-            for (int q = 0; q < KEEP; ++q) {
-                const int g0 = tid + q * NT, g = group_of(g0);
-                const int32_t w[4] = {kept_w[q].x, kept_w[q].y, kept_w[q].z, kept_w[q].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (kept_v[q][e] > above) what(g * 4 + e, w[e], kept_v[q][e]);
-            }
-        } else {
-            for (int g0 = tid; g0 < groups; g0 += NT) {
-                const int g = group_of(g0);
-                int4 w4;
-                double v[4];
-                read(g, w4, v);
-                const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (v[e] > above) what(g * 4 + e, w[e], v[e]);
-            }
-        }
+            v[e] = g * 4 + e < to && w[e] != MF_INFEASIBLE ? (float)(fma(Kd, (double)w[e], -p[e]) - ref) : LIST_NONE;
     };
     auto block_max = [&](double v) {
         v = wave_max(v);
@@ -147,6 +117,51 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
         v = s_red[0];
         for (int k = 1; k < NT / 64; ++k) v = fmax(v, s_red[k]);
         return v;
+    };
+    {
+        // values are kept as floats relative to the best of a first stretch of the line
+        double first = NEG_HUGE;
+        if (tid < groups) {
+            const int g = group_of(tid);
+            const int4 w4 = *(const int4 *)(line + g * 4);
+            const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (g * 4 + e < to && w[e] != MF_INFEASIBLE) first = fmax(first, fma(Kd, (double)w[e], -dual[g * 4 + e]));
+        }
+        first = block_max(first);
+        if (first > NEG_HUGE) ref = first;
+    }
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int q = 0; q < KEEP; ++q) {
+            const int g0 = tid + q * NT;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) kept_v[q][e] = LIST_NONE;
+            if (g0 < groups) read(group_of(g0), kept_v[q]);
+            if (q % 2) __builtin_amdgcn_sched_barrier(0);       // two groups' loads in flight: more would not fit beside what is kept
+        }
+    }
+    // what(position, value) for the entries worth more than `above`
+    auto for_each = [&](float above, auto what) {
+        if constexpr (NV > 0) {
+#pragma unroll
+            for (int q = 0; q < KEEP; ++q) {
+                const int g0 = tid + q * NT, g = group_of(g0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (kept_v[q][e] > above) what(g * 4 + e, kept_v[q][e]);
+            }
+        } else {
+            for (int g0 = tid; g0 < groups; g0 += NT) {
+                const int g = group_of(g0);
+                float v[4];
+                read(g, v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (v[e] > above) what(g * 4 + e, v[e]);
+            }
+        }
     };
     // the first bin at which the histogram's running count exceeds CORE_LIST (LIST_BINS if none does)
     // and the count before it (all, if none); first wavefront
@@ -165,11 +180,11 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
             room = (int)before;
         }
     };
-    double best = NEG_HUGE;
-    for_each(NEG_HUGE, [&](int, int32_t, double v) { best = fmax(best, v); });
-    const double own = best;
-    best = block_max(best);
-    if (own > NEG_HUGE) atomicAdd(&hist[bin_slot(distance_bin(best - own))], 1u);
+    float best = LIST_NONE;
+    for_each(LIST_NONE, [&](int, float v) { best = fmaxf(best, v); });
+    const float own = best;
+    best = (float)block_max((double)best);
+    if (own > LIST_NONE) atomicAdd(&hist[bin_slot(distance_bin(best - own))], 1u);
     __syncthreads();
     if (tid < 64) find_cut(s_near, s_room);                  // the bin the CORE_LIST + 1st of the threads' best values is in
     __syncthreads();
@@ -177,8 +192,8 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
     for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
     __syncthreads();
     // (everything in the bins up to that one is worth more than this: one comparison an entry from here on)
-    const double above = near < LIST_BINS - 1 ? best - (double)__uint_as_float((unsigned)(near + 1) << 20) : NEG_HUGE;
-    for_each(above, [&](int, int32_t, double v) {
+    const float above = near < LIST_BINS - 1 ? fmaxf(best - __uint_as_float((unsigned)(near + 1) << 20), LIST_NONE) : LIST_NONE;
+    for_each(above, [&](int, float v) {
         const int bin = distance_bin(best - v);
         if (bin <= near) atomicAdd(&hist[bin_slot(bin)], 1u);
     });
@@ -189,24 +204,25 @@ __global__ __launch_bounds__(NT) void core_list_kernel(
     }
     __syncthreads();
     const int cut = s_cut, low = s_room;
-    double outside = above;                                  // what is worth less is not on the list
-    if (tid == 0 && above > NEG_HUGE) s_all = 0;
-    for_each(above, [&](int j, int32_t w, double v) {
+    float outside = above;                                   // what is worth less is not on the list
+    if (tid == 0 && above > LIST_NONE) s_all = 0;
+    for_each(above, [&](int j, float v) {
         const int bin = distance_bin(best - v);
-        if (bin < cut) out[atomicAdd(&s_low, 1)] = make_int2(j, w);
+        if (bin < cut) out[atomicAdd(&s_low, 1)] = make_int2(j, line[j]);
         else {
             const int at = bin == cut ? low + atomicAdd(&s_fill, 1) : CORE_LIST;
-            if (at < CORE_LIST) out[at] = make_int2(j, w);
-            else { outside = fmax(outside, v); s_all = 0; }
+            if (at < CORE_LIST) out[at] = make_int2(j, line[j]);
+            else { outside = fmaxf(outside, v); s_all = 0; }
         }
     });
-    outside = block_max(outside);
+    // (no smaller than any unlisted value was before it was rounded)
+    const double past = block_max((double)outside + fabs((double)outside) * 0x1p-23);
     __syncthreads();
     const int used = min(low + s_fill, CORE_LIST);
     for (int t = used + tid; t < CORE_LIST; t += NT) out[t] = make_int2(0, MF_INFEASIBLE);
     if (tid == 0) {
-        bound[b] = s_all ? CORE_UNBOUNDED : outside;
-        depth[blockIdx.x] = s_all ? 1.0e13 : best - outside;
+        bound[b] = s_all ? CORE_UNBOUNDED : ref + past;
+        depth[blockIdx.x] = s_all ? 1.0e13 : (double)best - past;
     }
 }
 
@@ -229,12 +245,12 @@ struct alignas(256) CoreCtl {
     int whole_count[4];                                  // rows whose whole lines a refinement looks at next (same ring)
     unsigned dense[4];                                   // whole lines read in an epoch (same ring)
     alignas(128) unsigned long long slack[3];            // see slack_of: bits of a non-negative double, two means
-    int rev_count, tree_count;
+    int rev_count, tree_count, read_count;
     // searches
     // (read together, a lane each: [0..2] lowest label left per slot, [3..5] path ends found, [6..8] frontier lengths, [9] sink, [10..12] lines to be read whole)
     alignas(128) unsigned long long low[3];
     unsigned long long sink_found[3], frontier[3], sink, whole_front[3];
-    alignas(128) unsigned long long src_profit[CORE_MAX_SOURCES], src_outside[CORE_MAX_SOURCES], src_dropped[CORE_MAX_SOURCES];
+    alignas(128) unsigned long long src_profit[CORE_MAX_SOURCES], src_outside[CORE_MAX_SOURCES], src_dropped[CORE_MAX_SOURCES], src_left[CORE_MAX_SOURCES];
     alignas(128) unsigned jump_pending[CORE_JUMP_PASSES + 1];
     // refinement
     alignas(128) unsigned failed[3];
@@ -251,6 +267,7 @@ struct CoreSide {
     const int32_t *A;                   // the bidding side's lines
     long long pitch;
     int lines, len;                     // how many, how long
+    long long read_limit;               // lines one search may read whole
     const int *line_len;                // optional
     unsigned long long *otherword;      // opposite (dual, holder) words
     double *other_dual;                 // the same duals, brought up to date at the end of a side
@@ -434,6 +451,16 @@ struct Core {
     __device__ __forceinline__ Top2 whole_line(const CoreSide &s, int b)
     {
         return read_whole_line(s.A + (size_t)b * s.pitch, s.line_len ? min(s.line_len[b], s.len) : s.len, s.otherword, a.Kd, tie_salt(b));
+    }
+
+    // a slice of a line, all of it in flight (lines are padded to a multiple of four)
+    __device__ __forceinline__ void load_slice(const int32_t *line, int from, int to, int4 *ahead)
+    {
+#pragma unroll
+        for (int q = 0; q < CORE_SLICE / 256; ++q) {
+            const int j = from + q * 256 + lane * 4;
+            ahead[q] = j < to ? *(const int4 *)(line + j) : make_int4(MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE, MF_INFEASIBLE);
+        }
     }
 
     // the same from the line's list; *outside: what no unlisted entry exceeds
@@ -713,6 +740,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         if (lane == 0) {
             store_through(&ctl->src_profit[item], (unsigned long long)__double_as_longlong(best - eps));
             store_through(&ctl->src_outside[item], (unsigned long long)__double_as_longlong(outside));
+            store_through(&ctl->src_left[item], (unsigned long long)__double_as_longlong(CORE_WHOLE));
             store_i32(&a.held[r], -1 - item);
             if (best - eps > 0.0) store_f64(&a.base[r], best);
         }
@@ -760,6 +788,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
     unsigned step = 0, since_served = 0;
     bool swept = false, from_bidders = true, sweep_next = false;
     int status = 0;
+    long long lines_read = 0;                                // whole lines; the same in every workgroup
     unsigned long long my_steps = 0;
     while (n_alive > 0) {
         if (++since_served > 4u * (unsigned)s.len + 4096u) { status = MF_CORE_DENSE; break; }     // (the same in every workgroup)
@@ -777,6 +806,10 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         const bool sweeping = !from_bidders && (sweep_next || front + whole_front == 0);
         const int nf = from_bidders ? n_alive : (sweeping ? 0 : min(front, a.frontier_room));
         const int nw = sweeping ? 0 : whole_front;
+        lines_read += nw;
+        // Paths so long that the lists do not show what they are made of are better searched for on whole
+        // lines by the whole device: a 20,000 x 20,000 round of that kind took 390 ms here, 120 ms so.
+        if (lines_read > s.read_limit) { status = MF_CORE_DENSE; break; }
         {
             const unsigned long long found = word_at(3u + c);
             agreed_sink = found < agreed_sink ? found : agreed_sink;
@@ -824,7 +857,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 if (lost || root < 0 || root >= count) { status = MF_CORE_DENSE; break; }
                 if (tid == 0) sh.pushes = 0u;
-                if (gtid() == 0) { store_i32(&ctl->tree_count, 0); store_f64(&a.base[sh.row[root]], CORE_FAR); }
+                if (gtid() == 0) { store_i32(&ctl->tree_count, 0); store_i32(&ctl->read_count, 0); store_f64(&a.base[sh.row[root]], CORE_FAR); }
                 if (!barrier()) return MF_CORE_ABORT;
                 for (int k = gtid(); k < s.len; k += gsize()) {
                     if (load_fresh_i32(&a.jump[k]) != -1 - root) continue;
@@ -878,28 +911,31 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 // The tree's columns lose their labels.  What the others have reached stays as it is: a
                 // column of the tree, at its raised price, is at least as far from any of them as the
                 // path just served was long.
+                __syncthreads();
+                if (tid == 0) sh.pushes = 0u;
+                __syncthreads();
+                auto was_read = [&](int i) {
+                    const unsigned slot = atomicAdd(&sh.pushes, 1u);
+                    if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)i;
+                    else store_i32(&a.whole0[atomicAdd(&ctl->read_count, 1)], i);
+                };
                 for (int k = gtid(); k < s.len; k += gsize()) {
-                    if (load_fresh_u32(&a.stamp[k]) == CORE_IN_TREE) {
+                    const unsigned state = load_fresh_u32(&a.stamp[k]);
+                    if (state == CORE_IN_TREE) {
                         store_through(&a.label[k], CORE_INF);
                         store_u32(&a.stamp[k], 0u);
                         store_through(&a.expanded[k], CORE_INF);
                         store_f64(&a.remainder[k], CORE_FAR);
                         store_f64(&a.dropped[k], CORE_FAR);
-                    } else if (load_fresh(&a.remainder[k]) > CORE_FAR) {
-                        // a line read whole may have labelled such columns: it is due again from there on
-                        const int i = word_id(load_fresh_u64(&s.otherword[k]));
-                        store_f64(&a.remainder[k], fmax(load_fresh(&a.base[i]) - (s.bound[i] + slack), (double)(long long)d_star));
-                    }
+                    } else if (state == CORE_READ) was_read(word_id(load_fresh_u64(&s.otherword[k])));
                 }
+                if (rank == 0 && tid < n_alive && sh.alive[tid] != root && sh.remainder[sh.alive[tid]] >= CORE_WHOLE) was_read(sh.row[sh.alive[tid]]);
+                flush(a.whole0, &ctl->read_count);
                 __syncthreads();
                 if (tid == 0) {
                     int n = 0;
                     for (int e = 0; e < n_alive; ++e) if (sh.alive[e] != root) sh.alive[n++] = sh.alive[e];
                     sh.n_alive = n;
-                    for (int e = 0; e < n; ++e) {
-                        const int j = sh.alive[e];
-                        if (sh.remainder[j] > CORE_FAR) sh.remainder[j] = fmax(sh.profit[j] + eps - sh.outside[j], (double)(long long)d_star);
-                    }
                 }
                 if (!barrier()) return MF_CORE_ABORT;
                 n_alive = sh.n_alive;
@@ -933,10 +969,34 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                                 const int i = wave_min(best == least ? who : 0x7fffffff);
                                 if (lane == 0) {
                                     const unsigned long long mine = ((unsigned long long)(long long)least << MF_ID_BITS) | (unsigned long long)i;
-                                    if (mine < load_fresh_u64(&a.label[k])) store_through(&a.label[k], mine);
+                                    atomicMin(&a.label[k], mine);
                                 }
-                                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                             }
+                        }
+                    }
+                    // ... and at the rows whose whole lines have been read: what is not on their lists they
+                    // would not offer the column again.  (Reading all those lines once more after every
+                    // path took 15 ms a path where 15,000 lines had been read.)
+                    const int n_read = load_fresh_i32(&ctl->read_count), stretches = (n_read + STRETCH - 1) / STRETCH;
+                    for (int it = gwave(); it < n_tree * stretches; it += gwaves()) {
+                        const int k = load_fresh_i32(&a.tree[it / stretches]), from = it % stretches * STRETCH;
+                        const double price = word_dual(load_fresh_u64(&s.otherword[k]));
+                        double best = CORE_FAR;
+                        int who = 0;
+#pragma unroll
+                        for (int q = 0; q < STRETCH / 64; ++q) {
+                            const int e = from + q * 64 + lane;
+                            if (e < n_read) {
+                                const int i = load_fresh_i32(&a.whole0[e]);
+                                const int32_t w = !s.line_len || k < s.line_len[i] ? s.A[(size_t)i * s.pitch + k] : MF_INFEASIBLE;
+                                const double cand = load_fresh(&a.base[i]) - fma(a.Kd, (double)w, -price);
+                                if (w != MF_INFEASIBLE && cand < best) { best = cand; who = i; }
+                            }
+                        }
+                        const double least = -wave_max(-best);
+                        if (least < CORE_FAR * 0.5) {
+                            const int i = wave_min(best == least ? who : 0x7fffffff);
+                            if (lane == 0) atomicMin(&a.label[k], ((unsigned long long)(long long)least << MF_ID_BITS) | (unsigned long long)i);
                         }
                     }
                     if (!barrier()) return MF_CORE_ABORT;
@@ -990,10 +1050,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 else reach(k, holder);
             }
         };
-        auto relax = [&](int i, double base, int k, int32_t w, unsigned long long word, unsigned long long seen) {
-            const double cand = candidate(base, w, word);
-            if (!(cand < CORE_FAR)) return;
-            const unsigned long long mine = label_of(cand, i);
+        auto relax = [&](int i, double cand, int k, unsigned long long word) {
+            const unsigned long long mine = label_of(cand, i), seen = load_fresh_u64(&a.label[k]);
             if (shorter(mine, seen)) settle(cand, k, word, mine, seen, atomicCAS(&a.label[k], seen, mine));
         };
         int *whole_list = (step & 1u) ? a.whole1 : a.whole0, *next_whole = (step & 1u) ? a.whole0 : a.whole1;
@@ -1078,7 +1136,9 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
             taken = end;
             first = wave; stride = CORE_WAVES;
             }
-            // whole lines, in slices: a wavefront each
+            // whole lines, in slices: a wavefront each.  What bounds it is latency: four entries' prices are in
+            // flight per lane, and a label is looked at only where it may be lowered (one entry at a
+            // time took 24 us a slice, 36 ms where 37,000 lines of 20,000 had to be read).
             const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
             for (int it = gwave(); it < nw * slices; it += gwaves()) {
                 const int e = it / slices, from = (it - e * slices) * CORE_SLICE;
@@ -1097,12 +1157,29 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
                 const int32_t *line = s.A + (size_t)i * s.pitch;
+                int4 ahead[CORE_SLICE / 256];
+                load_slice(line, from, to, ahead);
+                const double unlisted = base - (s.bound[i] + slack);
+                double left_out = CORE_FAR;                         // the nearest unlisted one beyond the nearest path end
+#pragma unroll
+                for (int q = 0; q < CORE_SLICE / 256; ++q) {
+                    const int j = from + q * 256 + lane * 4;
+                    if (j >= to) break;
+                    const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
+                    unsigned long long word[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
 #pragma unroll 1
-                for (int j = from + lane; j < to; j += 64) {
-                    const int32_t w = line[j];
-                    const unsigned long long word = load_fresh_u64(&s.otherword[j]), label = load_fresh_u64(&a.label[j]);
-                    relax(i, base, j, w, word, label);
+                    for (int e = 0; e < 4; ++e) {
+                        if (j + e >= to || w[e] == MF_INFEASIBLE) continue;
+                        const double x = base - fma(a.Kd, (double)w[e], -word_dual(word[e]));
+                        if (x < bound) relax(i, x, j + e, word[e]);
+                        else if (x >= unlisted) left_out = fmin(left_out, x);
+                    }
                 }
+                left_out = -wave_max(-left_out);
+                if (lane == 0 && left_out < CORE_FAR)
+                    atomicMin(entry < 0 ? &ctl->src_left[-1 - entry] : (unsigned long long *)&a.remainder[entry], (unsigned long long)__double_as_longlong(left_out));
                 if (from == 0) ++whole;
             }
             from_bidders = false;
@@ -1137,19 +1214,20 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
-                    else { read_whole(k); store_f64(&a.remainder[k], CORE_WHOLE); }
+                    else { read_whole(k); store_f64(&a.remainder[k], CORE_WHOLE); store_u32(&a.stamp[k], CORE_READ); }
                 }
             }
             if (rank == 0 && tid < n_alive) {
                 const int j = sh.alive[tid];
-                const double rem = sh.remainder[j], drop = __longlong_as_double((long long)load_fresh_u64(&ctl->src_dropped[j]));
+                const double rem = sh.remainder[j] < CORE_WHOLE ? sh.remainder[j] : __longlong_as_double((long long)load_fresh_u64(&ctl->src_left[j]));
+                const double drop = __longlong_as_double((long long)load_fresh_u64(&ctl->src_dropped[j]));
                 if (drop < bound) {
                     if (drop >= limit) atomicMin(&sh.low, (unsigned long long)(long long)drop);
                     else reach(-1 - j, sh.row[j]);
                 }
                 if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
-                    else { read_whole(-1 - j); sh.remainder[j] = CORE_WHOLE; }
+                    else { read_whole(-1 - j); sh.remainder[j] = CORE_WHOLE; store_through(&ctl->src_left[j], (unsigned long long)__double_as_longlong(CORE_WHOLE)); }
                 }
             }
         }
@@ -1286,17 +1364,25 @@ __device__ __forceinline__ int Core::refine(double lower_by)
             const double profit = col >= 0 ? fma(a.Kd, (double)load_fresh_i32(&a.held_weight[i]), -word_dual(load_fresh_u64(&s.otherword[max(col, 0)]))) : 0.0;
             const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
             const int32_t *line = s.A + (size_t)i * s.pitch;
-#pragma unroll 1
-            for (int j = from + lane; j < to; j += 64) {
-                const int32_t w = line[j];
-                const unsigned long long word = load_fresh_u64(&s.otherword[j]);
-                const double need = fma(a.Kd, (double)w, -profit);
-                if (w == MF_INFEASIBLE || !(word_dual(word) < need)) continue;
-                if (word_id(word) < 0) { atomicOr(&sh.failed, 1u); break; }
-                const unsigned long long mine = pack_word(need, (int)(word & MF_ID_MASK));
-                if (!(atomicMax(&s.otherword[j], mine) < mine)) continue;
-                if (few) { if (!keep(word_id(word))) atomicOr(&sh.failed, 1u); }
-                else if (atomicExch(&a.stamp[j], round) != round) push(word_id(word), next, counter);
+            int4 ahead[CORE_SLICE / 256];
+            load_slice(line, from, to, ahead);
+#pragma unroll
+            for (int q = 0; q < CORE_SLICE / 256; ++q) {
+                const int j = from + q * 256 + lane * 4;
+                if (j >= to) break;
+                const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
+                unsigned long long word[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
+                for (int e = 0; e < 4; ++e) {
+                    const double need = fma(a.Kd, (double)w[e], -profit);
+                    if (j + e >= to || w[e] == MF_INFEASIBLE || !(word_dual(word[e]) < need)) continue;
+                    if (word_id(word[e]) < 0) { atomicOr(&sh.failed, 1u); break; }
+                    const unsigned long long mine = pack_word(need, (int)(word[e] & MF_ID_MASK));
+                    if (!(atomicMax(&s.otherword[j + e], mine) < mine)) continue;
+                    if (few) { if (!keep(word_id(word[e]))) atomicOr(&sh.failed, 1u); }
+                    else if (atomicExch(&a.stamp[j + e], round) != round) push(word_id(word[e]), next, counter);
+                }
             }
             if (from == 0) ++whole;
         }
@@ -1562,8 +1648,13 @@ int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, do
 int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st)
 {
     CoreArgs a{};
-    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
-    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
+    // (a quarter of the matrix, at least eight million entries: about 3 ms on one die at 20,000 x 20,000)
+    auto read_limit = [](const SideArgs &side, int lines) {
+        const long long all = (long long)lines * side.len / 4, entries = all > (8ll << 20) ? all : (8ll << 20);
+        return entries / (side.typical_len > 1 ? side.typical_len : 1);
+    };
+    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, read_limit(fwd, rn), fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
+    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, read_limit(rev, rm), rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
     a.Kd = fwd.Kd;
     CorePhases phases{};
     for (int k = 0; k < plan.n_phases; ++k) { phases.eps[k] = (double)plan.eps[k]; phases.stop[k] = plan.stop[k]; phases.stop_grown[k] = plan.stop_grown[k]; }
