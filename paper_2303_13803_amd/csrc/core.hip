@@ -21,6 +21,7 @@
 // 20,000 x 40,000 36.3 -> 29.8 ms, 20,000 x 20,000 60 -> 57 ms; at 4096 rows and at 6001 it is a loss,
 // 9.0 -> 9.2 and 14.7 -> 16.5 ms, and the line is drawn at 8192).
 #include "scan.h"
+#include "search_words.h"
 
 namespace {
 
@@ -338,6 +339,11 @@ __device__ __forceinline__ int load_fresh_i32(const int *p) { return __hip_atomi
 __device__ __forceinline__ void store_i32(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_u32(unsigned *p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_f64(double *p, double v) { store_through((unsigned long long *)p, (unsigned long long)__double_as_longlong(v)); }
+
+struct SharedWords {                    // (the bits of doubles that are not negative are in the doubles' order)
+    __device__ __forceinline__ void lower(unsigned long long *p, unsigned long long v) const { atomicMin(p, v); }
+    __device__ __forceinline__ void lower(double *p, double v) const { atomicMin((unsigned long long *)p, (unsigned long long)__double_as_longlong(fmax(v, 0.0))); }
+};
 
 // Best and second-best value of a whole line against the current words (one wavefront).  Out of
 // line and with nothing but values passed: rare, and its registers would be the callers' otherwise.
@@ -1031,7 +1037,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         // One candidate: column k at weight w through row i.  `first` is what the compare-and-swap of
         // its label saw (so that a wavefront has those of both its entries in flight at once).  A
         // column lowered twice in a step is twice on the frontier: looking it up in a stamp would
-        // cost every first one another round trip.
+        // cost every first one another round trip, and what two scans of its holder publish goes
+        // together in any order (search_words.h).
         auto candidate = [&](double base, int32_t w, unsigned long long word) {
             const double cand = base - fma(a.Kd, (double)w, -word_dual(word));
             return w != MF_INFEASIBLE && cand < bound ? cand : CORE_FAR;
@@ -1092,7 +1099,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 double dist, profit;
                 if (mine_col < 0) { dist = 0.0; profit = sh.profit[-1 - mine_col]; }
                 else {
-                    if (lw == CORE_INF || (lw >> MF_ID_BITS) >= ex) continue;     // (scanned from that label already)
+                    if (lw == CORE_INF || scanned_from(lw >> MF_ID_BITS, ex)) continue;     // (from that label already)
                     dist = (double)(long long)(lw >> MF_ID_BITS);
                     profit = fma(a.Kd, (double)w_held, -word_dual(held_word));
                 }
@@ -1115,9 +1122,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 left_out = -wave_max(-left_out);
                 if (mine_col < 0 && lane == 0) store_through(&ctl->src_dropped[-1 - mine_col], (unsigned long long)__double_as_longlong(left_out));
                 if (mine_col >= 0 && lane == 0) {
-                    store_f64(&a.base[i], base);
-                    store_f64(&a.dropped[mine_col], left_out);
-                    store_through(&a.expanded[mine_col], lw >> MF_ID_BITS);
+                    publish_scan(SharedWords{}, ScanWords{&a.base[i], &a.dropped[mine_col], &a.expanded[mine_col]}, lw >> MF_ID_BITS, base, left_out);
                     // (what is not on the list is at least this far away: looked at when the window gets there)
                     store_f64(&a.remainder[mine_col], base - outside);
                     store_i32(&a.held[i], mine_col);
@@ -1197,7 +1202,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 const int holder = word_id(load_fresh_u64(&s.otherword[k]));
                 const unsigned long long d_int = lw >> MF_ID_BITS;
                 if (lw == CORE_INF) continue;
-                if (d_int < ex) {                       // not scanned from this label yet
+                if (!scanned_from(d_int, ex)) {         // not scanned from this label yet
                     const double d = (double)(long long)d_int;
                     if (!(d < bound)) continue;
                     if (holder < 0) atomicMin(&sh.sink, (d_int << 21) | (unsigned long long)k);
@@ -1210,7 +1215,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 if (rests < bound) atomicMin(&sh.sink, ((unsigned long long)(long long)rests << 21) | (1ull << 20) | (unsigned long long)holder);
                 if (drop < bound) {                     // candidates left out then may be of use now: scan it again
                     if (drop >= limit) atomicMin(&sh.low, (unsigned long long)(long long)drop);
-                    else { store_through(&a.expanded[k], CORE_INF); reach(k, holder); }
+                    else { store_through(&a.expanded[k], CORE_INF); store_f64(&a.dropped[k], CORE_FAR); reach(k, holder); }
                 }
                 if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
