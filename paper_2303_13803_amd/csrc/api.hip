@@ -198,6 +198,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
         TRY(dev_alloc(&ctx->core_depth, MF_CORE_PROBES));
         TRY(hipHostMalloc((void **)&ctx->h_core_depth, sizeof(double) * MF_CORE_PROBES));
         TRY(dev_alloc(&ctx->core_parent, nm));
+        TRY(dev_alloc(&ctx->core_read_from, nm));
         TRY(dev_alloc(&ctx->core_weight, nm));
         TRY(hipMalloc(&ctx->core_ctl, mf_core_ctl_bytes()));
         TRY(hipHostMalloc(&ctx->h_core_ctl, mf_core_ctl_bytes()));
@@ -238,7 +239,7 @@ int mf_destroy(mf_ctx *ctx)
                    ctx->profit, ctx->colword, ctx->roword, ctx->row2col, ctx->col2row, ctx->team_ctl, ctx->path_ctl, ctx->path_label, ctx->path_expanded, ctx->path_frontier[0], ctx->path_frontier[1], ctx->path_stamp, ctx->path_held, ctx->path_base, ctx->path_tree, ctx->path_parent, ctx->path_jump, ctx->edge_count, ctx->edge_start, ctx->list[0], ctx->list[1], ctx->colmark, ctx->stats,
                    ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
                    ctx->core_t_entries[0], ctx->core_t_entries[1], ctx->core_t_start[0], ctx->core_t_start[1], ctx->core_t_at[0], ctx->core_t_at[1],
-                   ctx->core_base, ctx->core_dropped, ctx->core_tree, ctx->core_depth, ctx->core_parent, ctx->core_weight, ctx->core_ctl, ctx->cert};
+                   ctx->core_base, ctx->core_dropped, ctx->core_tree, ctx->core_depth, ctx->core_parent, ctx->core_read_from, ctx->core_weight, ctx->core_ctl, ctx->cert};
     for (void *p : dev) if (p) (void)hipFree(p);
     if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     for (int i = 0; i < 2; ++i) {

@@ -42,7 +42,7 @@ constexpr int CORE_NO_LABEL = INT32_MIN;
 constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
 constexpr unsigned CORE_GAVE_UP = 0x80000000u;
 constexpr double CORE_FAR = 1.0e300;                  // no candidate
-constexpr double CORE_WHOLE = 2.0e300;                // in Core's remainder: the line has been read whole
+constexpr double CORE_WHOLE = 2.0e300;                // in CoreShared's remainder: the bidder's line has been read whole
 constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose list holds all of its entries
 
 // ---------------------------------------------------------------- the lists
@@ -315,7 +315,8 @@ struct CoreArgs {
     unsigned long long *parent;
     double *base;                       // [lines] of a line that has been scanned: length of its path + its profit + eps; else CORE_FAR
     double *dropped;                    // [columns] the shortest candidate the holder's scan left out because it lay beyond every path end
-    double *remainder;                  // [columns] how far off the nearest unlisted entry of the holder's line is at least
+    unsigned long long *read_from;      // [columns] label from which the holder's line has been read whole, else CORE_INF
+    double *left;                       // [columns] ... and the nearest entry that left out
     int *whole0, *whole1;               // lines to be read whole (by step parity)
     int32_t *held_weight;               // [max(rows, columns)] weight of each opposite line's pair with its holder
 };
@@ -341,6 +342,8 @@ __device__ __forceinline__ void store_u32(unsigned *p, unsigned v) { __hip_atomi
 __device__ __forceinline__ void store_f64(double *p, double v) { store_through((unsigned long long *)p, (unsigned long long)__double_as_longlong(v)); }
 
 struct SharedWords {                    // (the bits of doubles that are not negative are in the doubles' order)
+    __device__ __forceinline__ void set(unsigned long long *p, unsigned long long v) const { store_through(p, v); }
+    __device__ __forceinline__ void set(double *p, double v) const { store_f64(p, v); }
     __device__ __forceinline__ void lower(unsigned long long *p, unsigned long long v) const { atomicMin(p, v); }
     __device__ __forceinline__ void lower(double *p, double v) const { atomicMin((unsigned long long *)p, (unsigned long long)__double_as_longlong(fmax(v, 0.0))); }
 };
@@ -730,7 +733,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
     for (int k = gtid(); k < s.len; k += gsize()) {
         store_through(&a.label[k], CORE_INF);
         store_through(&a.expanded[k], CORE_INF);
-        store_f64(&a.remainder[k], CORE_FAR);
+        store_through(&a.read_from[k], CORE_INF);
+        store_f64(&a.left[k], CORE_FAR);
         store_f64(&a.dropped[k], CORE_FAR);
         store_u32(&a.stamp[k], 0u);
         const int h = word_id(load_fresh_u64(&s.otherword[k]));
@@ -931,7 +935,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                         store_through(&a.label[k], CORE_INF);
                         store_u32(&a.stamp[k], 0u);
                         store_through(&a.expanded[k], CORE_INF);
-                        store_f64(&a.remainder[k], CORE_FAR);
+                        store_through(&a.read_from[k], CORE_INF);
+                        store_f64(&a.left[k], CORE_FAR);
                         store_f64(&a.dropped[k], CORE_FAR);
                     } else if (state == CORE_READ) was_read(word_id(load_fresh_u64(&s.otherword[k])));
                 }
@@ -1085,7 +1090,6 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 const int2 *e = s.entries + (size_t)i * CORE_LIST;
                 const int2 e0 = e[lane], e1 = e[lane + 64];
-                const double outside = s.bound[i] + slack;
                 unsigned long long lw = 0ull, held_word = 0ull, ex = CORE_INF;
                 int32_t w_held = 0;
                 if (mine_col >= 0) {
@@ -1123,8 +1127,6 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 if (mine_col < 0 && lane == 0) store_through(&ctl->src_dropped[-1 - mine_col], (unsigned long long)__double_as_longlong(left_out));
                 if (mine_col >= 0 && lane == 0) {
                     publish_scan(SharedWords{}, ScanWords{&a.base[i], &a.dropped[mine_col], &a.expanded[mine_col]}, lw >> MF_ID_BITS, base, left_out);
-                    // (what is not on the list is at least this far away: looked at when the window gets there)
-                    store_f64(&a.remainder[mine_col], base - outside);
                     store_i32(&a.held[i], mine_col);
                     if (dist + profit < bound)
                         ends_at(((unsigned long long)(long long)(dist + profit) << 21) | (1ull << 20) | (unsigned long long)i);
@@ -1184,7 +1186,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 left_out = -wave_max(-left_out);
                 if (lane == 0 && left_out < CORE_FAR)
-                    atomicMin(entry < 0 ? &ctl->src_left[-1 - entry] : (unsigned long long *)&a.remainder[entry], (unsigned long long)__double_as_longlong(left_out));
+                    publish_slice(SharedWords{}, WholeLine{nullptr, entry < 0 ? (double *)&ctl->src_left[-1 - entry] : &a.left[entry]}, left_out);
                 if (from == 0) ++whole;
             }
             from_bidders = false;
@@ -1198,7 +1200,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
             for (int k = gtid(); k < s.len; k += gsize()) {
                 const unsigned long long lw = load_fresh_u64(&a.label[k]);
                 const unsigned long long ex = load_fresh_u64(&a.expanded[k]);
-                const double rem = load_fresh(&a.remainder[k]), drop = load_fresh(&a.dropped[k]);
+                const double left = load_fresh(&a.left[k]), drop = load_fresh(&a.dropped[k]);
+                const unsigned long long read_from = load_fresh_u64(&a.read_from[k]);
                 const int holder = word_id(load_fresh_u64(&s.otherword[k]));
                 const unsigned long long d_int = lw >> MF_ID_BITS;
                 if (lw == CORE_INF) continue;
@@ -1211,7 +1214,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                     continue;
                 }
                 // (a path may end in the row that holds it; found before, but ends found before one was served are forgotten)
-                const double rests = load_fresh(&a.base[holder]) - eps;
+                const double base = load_fresh(&a.base[holder]), rests = base - eps;
+                const double rem = unlisted_from(d_int, read_from, left, base - (s.bound[holder] + slack));
                 if (rests < bound) atomicMin(&sh.sink, ((unsigned long long)(long long)rests << 21) | (1ull << 20) | (unsigned long long)holder);
                 if (drop < bound) {                     // candidates left out then may be of use now: scan it again
                     if (drop >= limit) atomicMin(&sh.low, (unsigned long long)(long long)drop);
@@ -1219,7 +1223,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 }
                 if (rem < bound) {
                     if (rem >= limit) atomicMin(&sh.low, (unsigned long long)(long long)fmax(rem, 0.0));
-                    else { read_whole(k); store_f64(&a.remainder[k], CORE_WHOLE); store_u32(&a.stamp[k], CORE_READ); }
+                    else { read_whole(k); begin_whole_line(SharedWords{}, WholeLine{&a.read_from[k], &a.left[k]}, d_int, CORE_FAR); store_u32(&a.stamp[k], CORE_READ); }
                 }
             }
             if (rank == 0 && tid < n_alive) {
@@ -1698,7 +1702,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.label = ctx->path_label; a.expanded = ctx->path_expanded;
     a.frontier0 = ctx->path_frontier[0]; a.frontier1 = ctx->path_frontier[1];
     a.stamp = ctx->path_stamp; a.held = ctx->path_held; a.jump = ctx->path_jump;
-    a.parent = ctx->core_parent; a.remainder = ctx->path_base; a.whole0 = ctx->path_tree; a.whole1 = ctx->path_parent; a.held_weight = ctx->core_weight;
+    a.parent = ctx->core_parent; a.read_from = ctx->core_read_from; a.left = ctx->path_base; a.whole0 = ctx->path_tree; a.whole1 = ctx->path_parent; a.held_weight = ctx->core_weight;
     CoreCtl *ctl = (CoreCtl *)ctx->core_ctl;
     hipLaunchKernelGGL(core_begin_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl, st->phase, phases);
     // one workgroup per compute unit of the device: those of one die stay

@@ -155,7 +155,7 @@ struct mf_ctx {
     int *core_t_start[2], *core_t_at[2], *core_tree;    // the lists by opposite line (searches)
     int2 *core_t_entries[2];
     double *core_base, *core_dropped;
-    unsigned long long *core_parent;
+    unsigned long long *core_parent, *core_read_from;
     int32_t *core_weight;
     void *core_ctl, *h_core_ctl;
     int *list[2];

@@ -35,3 +35,35 @@ MF_SEARCH_FN void publish_scan(const Mem &mem, const ScanWords &at, unsigned lon
 
 // The pass over all columns: the row counts as scanned from the column's label as it is now.
 MF_SEARCH_FN bool scanned_from(unsigned long long length, unsigned long long expanded) { return length >= expanded; }
+
+// ---- lines read whole ----
+// What is not on a row's list is at least as far off as the list's bound says.  The pass over all
+// columns, during which no label changes, has the whole line read once that is near enough, and notes
+// the label the column has (`read_from`) and that nothing has been left out (`left`).  The slices of the
+// line read the label for themselves, that one or a shorter one, offer what they find and lower `left`
+// to the nearest entry that lay beyond every path end.  So the reading counts for as long as the label
+// is not below `read_from`; from a shorter label the list's bound holds again.  Scans of the row do not
+// touch either word: a scan in the step that reads the line, as the pass asks for when it also has
+// candidates to offer again, neither undoes the reading (the line was read twice) nor gets in its way.
+struct WholeLine {
+    unsigned long long *read_from;      // of the column: the label its holder's line has been read whole from
+    double *left;                       // the nearest entry that reading left out
+};
+
+// (by the pass over all columns, which looks at a column once)
+template <class Mem>
+MF_SEARCH_FN void begin_whole_line(const Mem &mem, const WholeLine &at, unsigned long long length, double nothing)
+{
+    mem.set(at.read_from, length);
+    mem.set(at.left, nothing);
+}
+
+template <class Mem>
+MF_SEARCH_FN void publish_slice(const Mem &mem, const WholeLine &at, double left_out) { mem.lower(at.left, left_out); }
+
+// How far off the nearest entry is at least that has neither been offered nor is in `dropped`, for a row
+// scanned from `length`; `by_bound`: base - the list's bound.
+MF_SEARCH_FN double unlisted_from(unsigned long long length, unsigned long long read_from, double left, double by_bound)
+{
+    return length >= read_from ? left : by_bound;
+}

@@ -3,8 +3,9 @@
 // Some wavefronts look at one row in the same step, each from the label its column had when that
 // wavefront read it.  Every access is one operation on shared memory; the orders of two or three
 // wavefronts' operations are all tried, and after each the pass over all columns must find nothing too
-// long and nothing hidden.  With "stores" the minima are plain stores, which has to fail: the orders
-// tried are those that matter.
+// long and nothing hidden.  With "stores" the minima are plain stores, and with "moved" a reading of a
+// whole line counts whatever label the column has by then: both have to fail, or the orders tried
+// would not be those that matter.
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
@@ -18,8 +19,8 @@ static const u64 NEVER = ~0ull;
 static const double PROFIT = 7.0, EPS = 1.0;
 
 struct Words {
-    double base, dropped;
-    u64 expanded;
+    double base, dropped, left;
+    u64 expanded, read_from;
 };
 
 struct Op {
@@ -32,6 +33,8 @@ struct Op {
 // notes the operations instead of making them
 struct Recorder {
     std::vector<Op> *ops;
+    void set(double *p, double v) const { *p = v; }     // (by the pass over all columns, alone)
+    void set(u64 *p, u64 v) const { *p = v; }
     void lower(double *p, double v) const { ops->push_back(Op{p, nullptr, v, 0}); }
     void lower(u64 *p, u64 v) const { ops->push_back(Op{nullptr, p, 0.0, v}); }
 };
@@ -66,7 +69,7 @@ static long orders, broken;
 // A row's scans in one step; `listed`: how far off its entries are when its path has length 0.
 static void scans(const std::vector<Scan> &all, const std::vector<double> &listed, bool stores)
 {
-    Words w{FAR, FAR, NEVER};
+    Words w{FAR, FAR, FAR, NEVER, NEVER};
     std::vector<std::vector<Op>> lists(all.size());
     std::vector<double> offered(listed.size(), FAR);
     u64 label = NEVER;
@@ -94,9 +97,56 @@ static void scans(const std::vector<Scan> &all, const std::vector<double> &liste
     });
 }
 
+// A pass over all columns has had the row, scanned from `length`, put on the list of whole lines and on the
+// frontier; in the next step one slice for each of `slices` reads half of the unlisted entries, and the
+// row is scanned from each of `again`.
+static void whole_line(u64 length, const std::vector<Scan> &slices, const std::vector<Scan> &again, const std::vector<double> &unlisted,
+                       bool stores, bool moved)
+{
+    double nearest = FAR;
+    for (double d : unlisted) nearest = d < nearest ? d : nearest;
+    Words w{(double)length + PROFIT + EPS, FAR, (double)length, NEVER, NEVER};
+    const ScanWords scan_at{&w.base, &w.dropped, &w.expanded};
+    const WholeLine line_at{&w.read_from, &w.left};
+    std::vector<std::vector<Op>> lists(slices.size() + again.size());
+    begin_whole_line(Recorder{nullptr}, line_at, length, FAR);
+    std::vector<double> offered(unlisted.size(), FAR);
+    u64 label = length;
+    double least_bound = FAR;
+    for (size_t k = 0; k < slices.size(); ++k) {
+        double left_out = FAR;
+        for (size_t e = k; e < unlisted.size(); e += slices.size()) {
+            const double x = (double)slices[k].length + unlisted[e];
+            if (x < slices[k].bound) offered[e] = x;
+            else left_out = x < left_out ? x : left_out;
+        }
+        if (left_out < FAR) publish_slice(Recorder{&lists[k]}, line_at, left_out);
+        label = slices[k].length < label ? slices[k].length : label;
+        least_bound = slices[k].bound < least_bound ? slices[k].bound : least_bound;
+    }
+    for (size_t k = 0; k < again.size(); ++k) {
+        publish_scan(Recorder{&lists[slices.size() + k]}, scan_at, again[k].length, (double)again[k].length + PROFIT + EPS, FAR);
+        label = again[k].length < label ? again[k].length : label;
+    }
+    std::vector<size_t> at(lists.size(), 0);
+    every_order(w, lists, at, stores, [&]() {
+        ++orders;
+        // (not scanned from its label yet: it is, before anything is concluded about what is not on its list)
+        const double by_bound = (double)label + nearest;
+        const double rem = unlisted_from(label, moved ? 0 : w.read_from, w.left, by_bound);
+        bool good = true;
+        for (size_t e = 0; e < unlisted.size(); ++e) {
+            const double x = (double)label + unlisted[e];
+            good = good && (offered[e] <= x || rem <= x);
+        }
+        if (label == length) good = good && rem >= least_bound;        // the line is not read again while no path end is farther
+        if (!good) ++broken;
+    });
+}
+
 int main(int argc, char **argv)
 {
-    const bool stores = argc > 1 && strcmp(argv[1], "stores") == 0;
+    const bool stores = argc > 1 && strcmp(argv[1], "stores") == 0, moved = argc > 1 && strcmp(argv[1], "moved") == 0;
     const std::vector<double> listed = {8.0, 9.0, 15.0, 40.0};
     const double bounds[] = {20.0, 30.0, 90.0};
     for (double b0 : bounds)
@@ -105,5 +155,19 @@ int main(int argc, char **argv)
             for (double b2 : bounds) scans({{20, b0}, {12, b1}, {5, b2}}, listed, stores);
         }
     printf("scans: %ld orders, %ld broken\n", orders, broken);
+    orders = broken = 0;
+    const std::vector<double> unlisted = {11.0, 25.0, 14.0, 70.0};
+    const u64 labels[] = {20, 12};
+    for (double b0 : bounds)
+        for (double b1 : bounds)
+            for (u64 l0 : labels)
+                for (u64 l1 : labels) {
+                    whole_line(20, {{l0, b0}, {l1, b1}}, {}, unlisted, stores, moved);
+                    for (u64 l2 : labels) {
+                        whole_line(20, {{l0, b0}, {l1, b1}}, {{l2, b0}}, unlisted, stores, moved);
+                        whole_line(20, {{l0, b0}, {l1, b1}}, {{20, b0}, {l2, b1}}, unlisted, stores, moved);
+                    }
+                }
+    printf("whole lines: %ld orders, %ld broken\n", orders, broken);
     return 0;
 }

@@ -30,3 +30,11 @@ def test_scans_of_one_row_in_any_order(orders):
     tried, broken = orders()["scans"]
     assert tried > 1000 and broken == 0
     assert orders("stores")["scans"][1] > 0
+
+
+def test_a_line_read_whole_while_its_row_is_scanned(orders):
+    """Nothing unlisted is hidden, whichever labels the slices of the line and the scans read, and a line whose
+    label has not moved is not asked for a second time."""
+    tried, broken = orders()["whole lines"]
+    assert tried > 1000 and broken == 0
+    assert orders("stores")["whole lines"][1] > 0 and orders("moved")["whole lines"][1] > 0
