@@ -22,6 +22,7 @@
 // 9.0 -> 9.2 and 14.7 -> 16.5 ms, and the line is drawn at 8192).
 #include "scan.h"
 #include "search_words.h"
+#include "team_join.h"
 
 namespace {
 
@@ -41,6 +42,9 @@ constexpr unsigned CORE_IN_TREE = 0xffffffffu, CORE_READ = 1u;     // of a colum
 constexpr int CORE_NO_LABEL = INT32_MIN;
 constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
 constexpr unsigned CORE_GAVE_UP = 0x80000000u;
+// Looks at the word that says how many have joined before a workgroup takes those that have (see
+// team_join.h): long enough for another context's longest kernel to make room.
+constexpr unsigned CORE_JOIN_LOOKS = 1u << 16;
 constexpr double CORE_FAR = 1.0e300;                  // no candidate
 constexpr double CORE_WHOLE = 2.0e300;                // in CoreShared's remainder: the bidder's line has been read whole
 constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose list holds all of its entries
@@ -238,7 +242,7 @@ __global__ void core_snapshot_kernel(const double *__restrict__ dual, int count,
 struct alignas(256) CoreCtl {
     // who takes part: the workgroups of the die the first one to arrive runs on
     int die;
-    unsigned joined, arrived;
+    unsigned joined, arrived, members;                   // (see team_join.h)
     // barriers each workgroup has reached (top bit: it gave up); one lane polls each
     alignas(256) unsigned reached[CORE_MAX_WORKGROUPS];
     // bidders handed on: epoch e reads cnt[e & 3], fills cnt[(e + 1) & 3] and clears cnt[(e + 2) & 3]
@@ -341,6 +345,15 @@ __device__ __forceinline__ void store_i32(int *p, int v) { __hip_atomic_store(p,
 __device__ __forceinline__ void store_u32(unsigned *p, unsigned v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_f64(double *p, double v) { store_through((unsigned long long *)p, (unsigned long long)__double_as_longlong(v)); }
 
+struct TeamMemory {
+    __device__ __forceinline__ unsigned load(const unsigned *p) const { return load_fresh_u32(p); }
+    __device__ __forceinline__ void store(unsigned *p, unsigned v) const { store_u32(p, v); }
+    __device__ __forceinline__ unsigned add(unsigned *p, unsigned v) const { return atomicAdd(p, v); }
+    __device__ __forceinline__ unsigned set_bits(unsigned *p, unsigned v) const { return atomicOr(p, v); }
+    __device__ __forceinline__ int swap_if(int *p, int from, int to) const { return atomicCAS(p, from, to); }
+    __device__ __forceinline__ void settle() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+};
+
 struct SharedWords {                    // (the bits of doubles that are not negative are in the doubles' order)
     __device__ __forceinline__ void set(unsigned long long *p, unsigned long long v) const { store_through(p, v); }
     __device__ __forceinline__ void set(double *p, double v) const { store_f64(p, v); }
@@ -432,21 +445,13 @@ struct Core {
     __device__ __forceinline__ int join()
     {
         if (tid == 0) {
-            const int mine = (int)die_number();
-            const int was = atomicCAS(&ctl->die, -1, mine);
-            int number = a.wide || was == -1 || was == mine ? (int)atomicAdd(&ctl->joined, 1u) : -1;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            atomicAdd(&ctl->arrived, 1u);
-            if (number >= a.workgroups) number = -1;
-            sh.n_alive = number;
-            sh.ok = number >= 0 ? 1 : 0;
-            if (number >= 0) {
-                unsigned spins = 0;
-                while (load_fresh_u32(&ctl->arrived) < gridDim.x)
-                    if (++spins > a.spin_limit) { sh.ok = -1; break; }
-                sh.base = min(load_fresh_u32(&ctl->joined), (unsigned)a.workgroups);
-                if (sh.ok < 0) store_u32(&ctl->reached[number], CORE_GAVE_UP);
-            }
+            unsigned number, members = 1u;
+            const int ok = join_team(TeamMemory{}, TeamWords{&ctl->die, &ctl->joined, &ctl->arrived, &ctl->members}, (int)die_number(),
+                                     a.wide != 0, gridDim.x, (unsigned)a.workgroups, CORE_JOIN_LOOKS, a.spin_limit, &number, &members);
+            if (ok == -2) store_u32(&ctl->reached[number], CORE_GAVE_UP);
+            sh.n_alive = (int)number;
+            sh.base = members;
+            sh.ok = ok >= 0 ? 1 : ok + 1;
         }
         __syncthreads();
         const int ok = sh.ok;
@@ -1602,7 +1607,7 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
     }
     if (threadIdx.x != 0) return;
     ctl->die = -1;
-    ctl->joined = 0u; ctl->arrived = 0u;
+    ctl->joined = 0u; ctl->arrived = 0u; ctl->members = 0u;
     ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
     ctl->columns_ready = 0u;
     ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_lines = 0ull; ctl->rested = 0ull;
