@@ -119,14 +119,14 @@ typedef struct {
     int64_t K;                  /* dual scale, K = min(n, m) + 1                        */
     int64_t min_reduced_cost;   /* min over feasible (i,j) of u_i + v_j - K*W_ij        */
     int64_t rounds;             /* bidding kernels run (forward + reverse)              */
-    int64_t bids;               /* bids evaluated: each scans one row or column         */
-    int64_t bytes_scanned;      /* weight-matrix bytes those scans read                 */
-    int64_t chain_bids;         /* bids evaluated by the chain-following kernels        */
+    int64_t bids;               /* bids evaluated: each scans a row, a column or its list */
+    int64_t bytes_scanned;      /* bytes of the matrix and of lists that bids and path_scans read */
+    int64_t chain_bids;         /* ... evaluated by the chain-following kernels and on lists */
     int64_t chain_depth;        /* longest per-workgroup bid sequence, summed over them */
     int64_t chain_retries;      /* chain bids that lost and were redone                 */
     int64_t team_bids;          /* chain bids evaluated by several workgroups together  */
     int64_t path_steps;         /* super-steps of the shortest-augmenting-path searches */
-    int64_t path_scans;         /* line scans those searches made                       */
+    int64_t path_scans;         /* line scans of the searches and of proofs on lists (not in bids) */
     int32_t matched;            /* rows with a partner                                  */
     int32_t phases;             /* epsilon-scaling phases                               */
     int32_t cert_ok;            /* 1: matching valid, duals feasible, 0 <= D - K*P < K  */

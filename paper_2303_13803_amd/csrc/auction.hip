@@ -1043,13 +1043,15 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     ctx->timings[T_DUALS] = ms_duals;
     ctx->timings[T_CERT] = ms_cert;
     h_res->rounds = (int64_t)ctx->h_stats->rounds;
-    h_res->bids = (int64_t)ctx->h_stats->bids + core.bids + core.scans;
+    // (the device's counts of bids include the searches' scans, which count against max_rounds)
+    const int64_t searched = (int64_t)ctx->h_stats->path_scans;
+    h_res->bids = (int64_t)ctx->h_stats->bids - searched + core.bids;
     h_res->bytes_scanned = (int64_t)(ctx->h_stats->bytes + ctx->h_stats->round_bytes) + core.bytes;
-    h_res->chain_bids = (int64_t)ctx->h_stats->chain_bids + core.bids + core.scans;
+    h_res->chain_bids = (int64_t)ctx->h_stats->chain_bids - searched + core.bids;
     h_res->chain_retries = (int64_t)ctx->h_stats->chain_retries;
     h_res->team_bids = (int64_t)ctx->h_stats->team_bids;
     h_res->path_steps = (int64_t)ctx->h_stats->path_steps + core.steps;
-    h_res->path_scans = (int64_t)ctx->h_stats->path_scans + core.scans;
+    h_res->path_scans = searched + core.scans;
     h_res->chain_depth = (int64_t)(ctx->h_stats->chain_depth + ctx->h_stats->launch_max) + core.depth + core.steps;
     h_res->phases = phases;
     h_res->fallbacks = ctx->fallbacks;

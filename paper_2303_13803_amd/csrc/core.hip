@@ -265,7 +265,7 @@ struct alignas(256) CoreCtl {
     // what the launch reports
     alignas(128) int reason, phase, stage, count, parity;
     unsigned columns_ready;
-    unsigned long long bids, depth, steps, scans, whole_lines, rested;
+    unsigned long long bids, depth, steps, scans, whole_groups, rested;      // (whole_groups: of four entries, of lines read whole)
 };
 
 struct CoreSide {
@@ -464,7 +464,9 @@ struct Core {
 
     __device__ __forceinline__ Top2 whole_line(const CoreSide &s, int b)
     {
-        return read_whole_line(s.A + (size_t)b * s.pitch, s.line_len ? min(s.line_len[b], s.len) : s.len, s.otherword, a.Kd, tie_salt(b));
+        const int to = s.line_len ? min(s.line_len[b], s.len) : s.len;
+        whole += (unsigned)(to + 3) / 4u;
+        return read_whole_line(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, tie_salt(b));
     }
 
     // a slice of a line, all of it in flight (lines are padded to a multiple of four)
@@ -509,7 +511,6 @@ struct Core {
         if (t.b1 < outside) {                            // the list no longer decides
             t = whole_line(s, b);
             outside = NEG_HUGE;
-            ++whole;
             if (lane == 0) atomicAdd(&sh.dense, 1);
         }
         if (t.b1 <= eps) {
@@ -1192,7 +1193,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 left_out = -wave_max(-left_out);
                 if (lane == 0 && left_out < CORE_FAR)
                     publish_slice(SharedWords{}, WholeLine{nullptr, entry < 0 ? (double *)&ctl->src_left[-1 - entry] : &a.left[entry]}, left_out);
-                if (from == 0) ++whole;
+                whole += (unsigned)max(to - from + 3, 0) / 4u;
             }
             from_bidders = false;
         } else {
@@ -1398,7 +1399,7 @@ __device__ __forceinline__ int Core::refine(double lower_by)
                     else if (atomicExch(&a.stamp[j + e], round) != round) push(word_id(word[e]), next, counter);
                 }
             }
-            if (from == 0) ++whole;
+            whole += (unsigned)max(to - from + 3, 0) / 4u;
         }
         if (few) hand_on(next, counter, taken, round);
         else flush(next, counter);
@@ -1427,7 +1428,7 @@ __device__ __forceinline__ int Core::leave(int reason, int phase, int stage, int
     if (lane == 0) {
         if (bids) atomicAdd(&ctl->bids, (unsigned long long)bids);
         if (scans) atomicAdd(&ctl->scans, (unsigned long long)scans);
-        if (whole) atomicAdd(&ctl->whole_lines, (unsigned long long)whole);
+        if (whole) atomicAdd(&ctl->whole_groups, (unsigned long long)whole);
         if (rests) atomicAdd(&ctl->rested, (unsigned long long)rests);
     }
     // a wait that runs out here still counts: the reason stays "a wait ran out"
@@ -1610,7 +1611,7 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
     ctl->joined = 0u; ctl->arrived = 0u; ctl->members = 0u;
     ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
     ctl->columns_ready = 0u;
-    ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_lines = 0ull; ctl->rested = 0ull;
+    ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_groups = 0ull; ctl->rested = 0ull;
 }
 
 }  // namespace
@@ -1721,8 +1722,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
-    st->bytes += (long long)(h.bids + h.scans) * CORE_LIST * 8 + (long long)h.whole_lines * rm * 4;
-    st->whole += (long long)h.whole_lines;
+    st->bytes += (long long)(h.bids + h.scans) * CORE_LIST * 8 + (long long)h.whole_groups * 16;
     return MF_OK;
 }
 

@@ -237,7 +237,7 @@ struct mf_core_state {
     int reason, phase, stage, count, parity;
     int wide, refined;
     unsigned columns_ready;             // the sides whose lists also exist by opposite line (bits)
-    long long bids, depth, steps, scans, rested, bytes, whole;      // summed over launches
+    long long bids, depth, steps, scans, rested, bytes;      // summed over launches
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep);

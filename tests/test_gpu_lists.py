@@ -41,3 +41,18 @@ def test_phases_on_lists_reach_the_optimum(orc, n, m, high, masked, options):
         assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0
         assert res.primal == P == expect
         ctx.close()
+
+
+@pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
+def test_counters_of_a_solve_on_lists(n, m):
+    """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
+    reads one list (128 entries of 8 bytes) and is counted once."""
+    import paper_2303_13803_amd as mm
+    ctx = mm.Context(n, m)
+    W = padded_matrix(synth.uniform_matrix(72, n, m, 2 ** 24, 0.2))
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(W, n, m, r2c, u, v)
+    ctx.close()
+    assert res.bids > 0 and res.path_scans > 0 and res.chain_bids == res.bids
+    assert res.bytes_scanned == 1024 * (res.bids + res.path_scans)
