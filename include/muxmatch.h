@@ -335,7 +335,9 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            "core_width" (8192): label window of those searches, in epsilons, "core_refine" (200):
  *            epsilon, in weight units, at or below which a complete phase is followed by an attempt
  *            to prove its assignment optimal at once, "core_wide" (8192; 0: never): rows from which on the
- *            launches begin on all dies, going on on one with at most "core_narrow" (1024) bidders
+ *            launches begin on all dies, going on on one with at most "core_narrow" (1024) bidders,
+ *            "core_read" (25 percent of the matrix) / "core_read_least" (2^23 entries, if they are more): what
+ *            one such search may read of whole lines before the whole device searches in its place
  */
 int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
 
@@ -350,7 +352,9 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
  * [5] dual extraction, [6] certificate, [7] the whole auction, [8] weight
  * bytes the rounds of [2] scanned, [9] the fraction of the n*m pairs the pair
  * kernel ran the MLP on (the rest could not fit in memory and were marked
- * infeasible without being scored).  Entries of stages that did not run are 0.
+ * infeasible without being scored), [10] launches of the phases on lists, [11] how often lists of a
+ * side were made for them, [12] sides of such phases that were finished on whole lines (a search read too
+ * much, or "max_rounds" came near).  Entries of stages that did not run are 0.
  */
 int mf_last_timings(mf_ctx *ctx, float what[16]);
 

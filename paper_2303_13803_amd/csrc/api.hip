@@ -137,6 +137,8 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     ctx->core_wide = 8192;
     ctx->core_narrow = 1024;
     ctx->core_width = 8192;
+    ctx->core_read = 25;
+    ctx->core_read_least = 8ll << 20;
     {
         hipDeviceProp_t prop;
         ctx->n_cus = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.multiProcessorCount : 0;
@@ -430,6 +432,8 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
     if (!strcmp(name, "core_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_width = (int)value; return MF_OK; }
     if (!strcmp(name, "core_wide")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_wide = (int)value; return MF_OK; }
     if (!strcmp(name, "core_narrow")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_narrow = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_read")) { if (value < 0 || value > 100) return MF_ERR_ARG; ctx->core_read = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_read_least")) { if (value < 0 || value > (1ll << 40)) return MF_ERR_ARG; ctx->core_read_least = value; return MF_OK; }
     if (!strcmp(name, "core_few")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_few = (int)value; return MF_OK; }
     if (!strcmp(name, "core_after")) { if (value < 0) return MF_ERR_ARG; ctx->core_after = value; return MF_OK; }
     if (!strcmp(name, "core_refine")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_refine = (int)value; return MF_OK; }

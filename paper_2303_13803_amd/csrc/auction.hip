@@ -773,6 +773,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
     plan.stale = 8.0;
     int rc = mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr);
     if (rc != MF_OK) return rc;
+    st.lists_made += 1;
     if (rm > rn) {                      // unused columns are certain: they will have to bid
         if (!have_transpose) make_transpose();
     }
@@ -797,6 +798,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
             rc = forward ? mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr)
                          : mf_core_lists(ctx, rev, rm, 1, ctx->price, ctx->col2row);
             if (rc != MF_OK) return rc;
+            st.lists_made += 1;
             st.columns_ready &= ~(forward ? 1u : 2u);
             if (!forward) plan.have_columns = true;
             continue;
@@ -812,6 +814,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
         int left_over = 0;
         rc = run_side(ctx, side, st.count, false, plan.stop[st.phase], 0, &left_over, st.reason == MF_CORE_DENSE ? 64 : 0);
         if (rc != MF_OK) return rc;
+        st.sides_left += 1;
         st.stage = forward ? MF_CORE_FORWARD_DONE : MF_CORE_REVERSE_DONE;
         st.count = left_over;
     }
@@ -1042,6 +1045,9 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     ctx->timings[T_SOLVE] = ms_solve;
     ctx->timings[T_DUALS] = ms_duals;
     ctx->timings[T_CERT] = ms_cert;
+    ctx->timings[T_LIST_LAUNCHES] = (float)core.launches;
+    ctx->timings[T_LISTS_MADE] = (float)core.lists_made;
+    ctx->timings[T_LIST_SIDES_LEFT] = (float)core.sides_left;
     h_res->rounds = (int64_t)ctx->h_stats->rounds;
     // (the device's counts of bids include the searches' scans, which count against max_rounds)
     const int64_t searched = (int64_t)ctx->h_stats->path_scans;

@@ -1663,9 +1663,9 @@ int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, do
 int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st)
 {
     CoreArgs a{};
-    // (a quarter of the matrix, at least eight million entries: about 3 ms on one die at 20,000 x 20,000)
-    auto read_limit = [](const SideArgs &side, int lines) {
-        const long long all = (long long)lines * side.len / 4, entries = all > (8ll << 20) ? all : (8ll << 20);
+    // (by default a quarter of the matrix, at least eight million entries: about 3 ms on one die at 20,000 x 20,000)
+    auto read_limit = [ctx](const SideArgs &side, int lines) {
+        const long long all = (long long)lines * side.len * ctx->core_read / 100, entries = all > ctx->core_read_least ? all : ctx->core_read_least;
         return entries / (side.typical_len > 1 ? side.typical_len : 1);
     };
     a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, read_limit(fwd, rn), fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
@@ -1722,6 +1722,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
+    st->launches += 1;
     st->bytes += (long long)(h.bids + h.scans) * CORE_LIST * 8 + (long long)h.whole_groups * 16;
     return MF_OK;
 }

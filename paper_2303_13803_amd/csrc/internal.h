@@ -23,7 +23,7 @@
 #define MF_MAX_TYPES 64
 
 enum { T_PROJ = 0, T_PAIR, T_BID_BULK, T_BID_BULK_LAUNCHES, T_TRANSPOSE, T_DUALS, T_CERT, T_SOLVE,
-       T_BID_BULK_BYTES, T_PAIR_EVALUATED, T_COUNT = 16 };
+       T_BID_BULK_BYTES, T_PAIR_EVALUATED, T_LIST_LAUNCHES, T_LISTS_MADE, T_LIST_SIDES_LEFT, T_COUNT = 16 };
 
 // The matching on short lists (core.hip): entries per list, most phases of a solve, lines a probe
 // looks at, why a launch ended and at which stage of a phase it (or the next one) starts.
@@ -148,6 +148,8 @@ struct mf_ctx {
     int core_many, core_few;        // chain steps between two looks at the list, with more / fewer bidders than wavefronts
     long long core_after;           // chain steps after which the last bidders are searched for
     int core_wide, core_narrow;     // lines from which the wide parts run on all dies; bidders at or below which one die takes over
+    int core_read;                  // percent of the matrix one search on lists may read whole, ...
+    long long core_read_least;      // ... or so many entries if they are more
     int core_refine;                // epsilon (weight units) at or below which a complete phase is followed by a refinement
     int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
     int core_width;                 // label window of a search on lists, in epsilons
@@ -238,6 +240,7 @@ struct mf_core_state {
     int wide, refined;
     unsigned columns_ready;             // the sides whose lists also exist by opposite line (bits)
     long long bids, depth, steps, scans, rested, bytes;      // summed over launches
+    int launches, lists_made, sides_left;       // sides_left: finished on whole lines
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep);

@@ -3,14 +3,15 @@
 The lists hold 128 entries: lines of fewer, of exactly as many, of one more, and of a multiple of
 the wavefront and of a slice of a whole line plus one; ties beyond what a list holds (a line is then
 read whole); lists that are made once and again; phases that start on
-the whole device and go on on one die.  The optimum is the exact CPU solver's, the duals
+the whole device and go on on one die; both sides of the problem, feasible prefixes, several GPU types;
+searches that read too much and sides that come near the limit on bids.  The optimum is the exact CPU solver's, the duals
 are re-checked on the host, and the solve with the lists off has to agree."""
 import numpy as np
 import pytest
 import torch
 
 import synth
-from gpu_util import padded_matrix
+from gpu_util import dev, dev_params, empty_matrix, padded_matrix
 
 pytestmark = pytest.mark.gpu
 INF = synth.INFEASIBLE
@@ -56,3 +57,80 @@ def test_counters_of_a_solve_on_lists(n, m):
     ctx.close()
     assert res.bids > 0 and res.path_scans > 0 and res.chain_bids == res.bids
     assert res.bytes_scanned == 1024 * (res.bids + res.path_scans)
+
+
+def _solve(orc, W, options):
+    """The solve of W with the host's checks made; returns what the phases on lists did."""
+    import paper_2303_13803_amd as mm
+    n, m = W.shape
+    expect = orc.max_weight_matching(W if n <= m else np.ascontiguousarray(W.T))[0]
+    ctx = mm.Context(n, m)
+    for k, val in options.items():
+        ctx.set_option(k, val)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    code, P, D = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P == expect
+    did = ctx.last_timings()
+    ctx.close()
+    return did
+
+
+@pytest.mark.parametrize("n,m,high,masked", [(5, 128, 2 ** 24, 0.1), (40, 129, 2 ** 24, 0.0), (512, 513, 255, 0.1), (100, 4097, 2 ** 24, 0.2),
+                                             (900, 350, 2 ** 24, 0.1), (1201, 1200, 2 ** 24, 0.2), (2051, 130, 2 ** 20, 0.5)])
+@pytest.mark.parametrize("wide", [0, 1])
+def test_what_runs_on_lists(orc, n, m, high, masked, wide):
+    W = synth.uniform_matrix(73, n, m, high, masked)
+    did = _solve(orc, W, {"core_depth": 0, "core_wide": wide, "core_narrow": 16})
+    assert did["list_launches"] > 0 and did["lists_made"] > 0 and did["list_sides_left"] == 0
+    assert _solve(orc, W, {"core": 0, "core_depth": 0})["list_launches"] == 0
+
+
+@pytest.mark.parametrize("n,m,high,masked", [(257, 1025, 2 ** 24, 0.5), (900, 350, 2 ** 24, 0.1), (640, 640, 3, 0.0)])
+def test_lists_that_no_longer_decide_are_made_again(orc, n, m, high, masked):
+    """Started on lists at a coarse epsilon, prices rise past what the lists hold: more than one list of each side is made."""
+    assert _solve(orc, synth.uniform_matrix(71, n, m, high, masked), {"core_depth": 0})["lists_made"] > 2
+
+
+@pytest.mark.parametrize("n,m,high,masked", [(300, 131, 2 ** 20, 0.3), (512, 513, 255, 0.1), (64, 8193, 2 ** 20, 0.6), (900, 350, 2 ** 24, 0.1),
+                                             (1201, 1200, 2 ** 24, 0.2)])
+def test_a_search_that_reads_too_much_leaves_the_rest_to_the_device(orc, n, m, high, masked):
+    """With no whole line to be read at all, the first search that wants one gives up half-way."""
+    did = _solve(orc, synth.uniform_matrix(71, n, m, high, masked), {"core_depth": 0, "core_after": 0, "core_read": 0, "core_read_least": 0})
+    assert did["list_sides_left"] > 0
+
+
+@pytest.mark.parametrize("n,m,high,masked", [(300, 131, 2 ** 20, 0.3), (200, 2051, 1, 0.0), (900, 350, 2 ** 24, 0.1), (1000, 1000, 2 ** 24, 0.95)])
+def test_a_side_near_the_limit_on_bids_is_finished_on_whole_lines(orc, n, m, high, masked):
+    """The bids a look at the list may lead to are counted before they are made: with 4096 of them a
+    bidder, two million are near at once, while the solve takes a hundredth of that."""
+    did = _solve(orc, synth.uniform_matrix(71, n, m, high, masked), {"core_depth": 0, "core_many": 4096, "core_few": 4096,
+                                                                     "max_rounds": 300_000 if n < 900 else 2_000_000})
+    assert did["list_sides_left"] > 0
+
+
+@pytest.mark.parametrize("cfg,n,m", [("C5", 700, 300), ("C5", 1500, 2100), ("C4", 900, 1100), ("C5", 60, 20500), ("C5", 3001, 97)])
+@pytest.mark.parametrize("hidden", [(128,), (128, 64, 128)])
+@pytest.mark.parametrize("options", [{"core_depth": 0}, {"core_depth": 0, "core_wide": 1, "core_narrow": 16, "core_after": 0}])
+def test_rounds_on_lists_of_feasible_prefixes(orc, cfg, n, m, hidden, options):
+    """The memory-ordered copy: every line ends where the pairs that can share do (rows by GPU type first)."""
+    import paper_2303_13803_amd as mm
+    r = synth.scheduling_round(cfg, 74, n=n, m=m)
+    S = r["cfg"].scale
+    ctx = mm.Context(n, m)
+    for k, val in dict(options, fit_prefix_below=101).items():
+        ctx.set_option(k, val)
+    preds = [ctx.predictor(dev_params(p), S) for p in synth.typed_predictors(74, r["cfg"].F, list(hidden))]
+    W = empty_matrix(n, m)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    plan = (dev(r["x_on"]), dev(r["x_off"]), W, r2c, u, v)
+    res = ctx.schedule_round(preds[0], *plan) if len(preds) == 1 else ctx.schedule_round_typed(preds, dev(synth.gpu_types(74, n, len(preds))), *plan)
+    did = ctx.last_timings()
+    ctx.close()
+    Wg = np.ascontiguousarray(W.cpu().numpy()[:, :m])
+    code, P, D = orc.check_certificate(Wg, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0
+    assert res.primal == P == orc.max_weight_matching(Wg if n <= m else np.ascontiguousarray(Wg.T))[0]
+    assert did["list_launches"] > 0
