@@ -595,9 +595,9 @@ void launch_round(mf_ctx *ctx, const SideArgs &s, int count, int ring)
 // Runs one side until at most `stop_at` bidders are left (0: until nobody is left to bid).
 // list[0] / cnt[0] hold the first bidders (`count` of them).  Returns MF_OK or an error;
 // *left_over is the number of bidders still unplaced.  search_now: at most so many bidders (0: none)
-// are searched for at once, without following their chains first.
+// are searched for at once, without following their chains first, with a label window of search_width.
 int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int stop_at, long long tail_budget, int *left_over,
-             int search_now = 0)
+             int search_now = 0, int search_width = 0)
 {
     int ring = 0;
     // Short chains are cheapest followed step by step; a chain that is still going after
@@ -672,7 +672,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         } else if (paths_ok && (count <= search_now || (count <= ctx->path_max && (team_steps >= ctx->path_after || !teams_ok)))) {
             // few enough bidders, and chains long enough, to place each bidder by a shortest-path
             // search over the whole device
-            const int rc = mf_launch_path_search(ctx, s, ring);
+            const int rc = mf_launch_path_search(ctx, s, ring, search_width > ctx->path_width ? search_width : ctx->path_width);
             if (rc != MF_OK) return rc;
             ++ring;
         } else if (!teams_ok || count > team_from) {
@@ -805,14 +805,19 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
         }
         if (st.stage == MF_CORE_PHASE_DONE) { plan.may_refine = false; continue; }       // (a refinement that lists do not help)
         // This side is finished on whole lines; where a search gave up, by one of the whole device's.  (At
-        // an epsilon this fine the chains of a few dozen bidders would go on for seconds.)
+        // an epsilon this fine the chains of a few dozen bidders would go on for seconds.)  Paths that made a
+        // search give up are thousands of epsilons long, and the whole device's takes a step of 8 us for every
+        // window of labels: it goes on with the window of searches on lists, not with path_width.  (The worst of a
+        // hundred 20,000 x 20,000 rounds, auction: 160 ms with 1,024 epsilons, 118 with 8,192, 130 without
+        // lists.  Wider windows help that round, 103 ms with 32,768, and scan more in others, 63 -> 70 ms.)
         if (st.parity == 1) { int *t = ctx->list[0]; ctx->list[0] = ctx->list[1]; ctx->list[1] = t; st.parity = 0; }
         hipLaunchKernelGGL(set_count_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->stats, st.count);
         if (!have_transpose) make_transpose();
         SideArgs side = forward ? fwd : rev;
         side.eps = (double)ladder[st.phase];
         int left_over = 0;
-        rc = run_side(ctx, side, st.count, false, plan.stop[st.phase], 0, &left_over, st.reason == MF_CORE_DENSE ? 64 : 0);
+        rc = run_side(ctx, side, st.count, false, plan.stop[st.phase], 0, &left_over, st.reason == MF_CORE_DENSE ? 64 : 0,
+                      st.reason == MF_CORE_DENSE ? ctx->core_width : 0);
         if (rc != MF_OK) return rc;
         st.sides_left += 1;
         st.stage = forward ? MF_CORE_FORWARD_DONE : MF_CORE_REVERSE_DONE;

@@ -224,7 +224,7 @@ inline size_t mf_edge_capacity(const mf_ctx *ctx)      // entries the lists may 
     return ((size_t)ctx->max_n * ((((size_t)ctx->max_m + 3) & ~(size_t)3)) / 2) & ~(size_t)3;
 }
 // paths.hip
-int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring);
+int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring, int width);     // width: label window, in epsilons
 // core.hip
 struct mf_core_plan {
     int n_phases;

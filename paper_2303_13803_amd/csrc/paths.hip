@@ -702,7 +702,7 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
 
 // Places the bidders listed in list[ring & 1] (stats->cnt[ring & 3] of them) by one search from
 // all of them; whoever is not served (a wait ran out) is handed on in list[(ring + 1) & 1].
-int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring)
+int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring, int width)
 {
     PathBuffers buf{ctx->path_label, ctx->path_expanded, ctx->path_stamp,
                     {ctx->path_frontier[0], ctx->path_frontier[1]}, ctx->path_held, ctx->path_base, ctx->path_tree,
@@ -714,7 +714,7 @@ int mf_launch_path_search(mf_ctx *ctx, const SideArgs &s, int ring)
     hipLaunchKernelGGL(path_kernel, dim3(path_wgs), dim3(PATH_THREADS), 0, ctx->stream, side,
                        ctx->list[ring & 1], ctx->list[(ring + 1) & 1], ctx->stats, (PathCtl *)ctx->path_ctl,
                        buf, ring, ctx->max_n > ctx->max_m ? ctx->max_n : ctx->max_m,
-                       (double)ctx->path_width * s.eps, ctx->path_spin_limit, ctx->path_frontier_rows);
+                       (double)width * s.eps, ctx->path_spin_limit, ctx->path_frontier_rows);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
