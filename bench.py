@@ -197,12 +197,15 @@ def main():
                               "traffic": MEASURED_TRAFFIC.get((cfg.name, "round_kernel")),
                               # every weight byte any scan of the solve read, over the whole auction's time
                               "whole_solve_gbps": res.bytes_scanned / (avg["auction_ms"] * 1e-3) / 1e9},
-        # the chain-following kernels take most of the auction's time but are bound by the latency of
-        # dependent steps, not by bandwidth: reported as steps and microseconds per step
-        "auction_tail": {"kernels": "chain_kernel + team_kernel (dependent bids), path_kernel (search super-steps)",
+        # the kernels for few bidders take most of the auction's time but are bound by the latency of
+        # dependent steps, not by bandwidth: reported as steps and scans
+        "auction_tail": {"kernels": "core_kernel (phases on lists: bids, searches, proofs), before them chain_kernel + "
+                                    "team_kernel (dependent bids), path_kernel (searches on whole lines)",
                          "bound": "latency", "sequential_steps": res.chain_depth, "bids": res.chain_bids,
                          "path_super_steps": res.path_steps, "path_row_scans": res.path_scans,
-                         "chain_steps": res.chain_depth - res.path_steps},
+                         "chain_steps": res.chain_depth - res.path_steps,
+                         "list_launches": avg["list_launches"], "lists_made": avg["lists_made"],
+                         "list_sides_left": avg["list_sides_left"]},
     }
     # measured ceilings of this device next to the published peaks
     ceil = ctx.measure_ceilings(W)
@@ -290,6 +293,7 @@ def main():
         # follow-up rounds: a share of the online and offline workloads is replaced by fresh draws,
         # only their rows/columns are re-scored, then the matching is solved again (from zero prices
         # unless the warm-start option is set)
+        ctx.schedule_round(pred, x_on, x_off, W, r2c, u, v)     # the previous round: W has held other seeds' since
         xo, xf = r["x_on"].copy(), r["x_off"].copy()
         times, last = [], None
         for k in range(args.update_rounds):
