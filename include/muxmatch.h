@@ -325,7 +325,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            chains are left
  *   searches "path_max" (16, at most 64; 0: none): bidders at or below which one device-wide
  *            shortest-augmenting-path search places them all, after "path_after" (256) chain
- *            steps; "path_grid" (0: one workgroup per compute unit), "path_width" (1024 epsilons),
+ *            steps; "path_grid" (0: one workgroup per compute unit), "path_width" (1024 epsilons; at least
+ *            "core_width" for a search that takes over from one on lists),
  *            "path_frontier_rows" (1024), "path_pull" (0), "path_spin_limit" (2^22 polls a workgroup
  *            waits for the others before all give up; see mf_result.fallbacks)
  *   lists    "core" (1; 0: never): the phases from the one on in which a list of every line's best entries

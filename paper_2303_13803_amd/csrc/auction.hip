@@ -767,7 +767,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
     plan.refine_below = (double)ctx->core_refine * fwd.Kd;
     st.phase = ph; st.stage = MF_CORE_RESET; st.count = 0; st.parity = 0;
     plan.may_refine = true;
-    // (launches over all dies pay from about 8000 rows on: see the top of core.hip)
+    // (launches over all dies pay from about 8000 rows on: figures at the top of core.hip)
     plan.use_wide = ctx->core_wide > 0 && rn >= ctx->core_wide;
     st.wide = plan.use_wide ? 1 : 0;
     plan.stale = 8.0;

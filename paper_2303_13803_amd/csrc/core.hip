@@ -17,9 +17,11 @@
 //
 // While thousands of lines bid at once throughput counts instead: the proof and the first bids of a
 // phase of a large problem run in launches over all dies, which hand over to one die once at most
-// core_narrow lines bid and get it back for the next phase (two launches a phase more, about 50 us:
-// 20,000 x 40,000 36.3 -> 29.8 ms, 20,000 x 20,000 60 -> 57 ms; at 4096 rows and at 6001 it is a loss,
-// 9.0 -> 9.2 and 14.7 -> 16.5 ms, and the line is drawn at 8192).
+// core_narrow lines bid and get it back for the next phase (two launches a phase more, about 50 us).
+// The auction with all phases on one die / with such launches, mean over seeds: 2048 x 4096 3.6 / 3.9 ms,
+// 4096 x 8192 5.7 / 5.9, 6001 x 9007 13.4 / 13.3, 8192 x 8192 12.8 / 10.9, 8192 x 12288 11.4 / 11.6,
+// 12,000 x 16,000 30.7 / 26.3, 20,000 x 20,000 30.0 / 25.8; 20,000 x 40,000 with prefixes of a tenth
+// 21.2 / 21.1.  The line is drawn at 8192 rows.
 #include "scan.h"
 #include "search_words.h"
 #include "team_join.h"
@@ -1624,7 +1626,10 @@ void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int whi
 #define MF_LIST(NT, NV)                                                                                                      \
     hipLaunchKernelGGL((core_list_kernel<NT, NV>), grid, dim3(NT), 0, ctx->stream, s.A, s.pitch, s.len, s.line_len, lines,   \
                        stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], depth, own_dual, partner)
-    // (the threads' best values stand for the line's best: there have to be well over CORE_LIST of them)
+    // The threads' best values stand for the line's best, so there have to be well over CORE_LIST of them, and
+    // a line that fits in registers is read once.  What is asked is how long lines are allocated, not how
+    // long their feasible prefixes are: 20,000 x 40,000 with prefixes of 4,000 entries on average is read
+    // three times, 0.55 ms for the rows' lists (40,000 columns' lists, of 2,000 entries on average and once: 0.37 ms).
     if (s.len <= 4096) MF_LIST(512, 2);
     else if (s.len <= 8192) MF_LIST(512, 4);
     else if (s.len <= 20480) MF_LIST(1024, 5);

@@ -29,9 +29,9 @@ namespace {
 // hidden unit k of the slab, and a wavefront does PROJECT_ROWS / 4 rows, so that one LDS read of a weight
 // (a row of 64, no conflicts) serves them all and a feature is a broadcast.  Weights and features are
 // staged PROJECT_FEATURES at a time; the sum runs over the features in order, starting from the bias.  A
-// thread per output, reading its weights 2F floats apart from its neighbour's, took 311 us each for
+// thread per output, reading its weights 2F floats apart from its neighbour's, took 155 us a side for
 // 20,000 workloads x 128 units where storing them takes 2, and the ranges another 40 us of reading it
-// all back.  The last PROJECT_EXTRA workgroups look at W2 and the SM term.
+// all back; both sides and the ranges now take 36 us.  The last PROJECT_EXTRA workgroups look at W2 and the SM term.
 constexpr int PROJECT_ROWS = 32, PROJECT_FEATURES = 32, PROJECT_EXTRA = 4;
 
 struct ProjectArgs {
@@ -402,7 +402,7 @@ template <int H, bool SPLIT> struct PairShape {
 // (largest relative error 3-4e-7 on every benchmark configuration).  fp16 ends at 65,504 and
 // thins out below 6e-5, so both operands are first scaled by powers of two (exact) that bring the
 // largest weight, and the largest value a layer-1 unit can take, to about 2^13: `range` holds the
-// largest magnitudes of the projections, of W2 and of the SM term, found by range_kernel; the
+// largest magnitudes of the projections, of W2 and of the SM term, found by project_kernel; the
 // accumulators then carry the product of the two scales, which b2 is given on the way in and W3
 // takes out again.  The result therefore does not depend on the size of the numbers.
 // For lane l, element t of its operand of k-block kb is hidden unit (l / 32) * H/2 + 8 kb + t, for
