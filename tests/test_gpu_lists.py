@@ -110,6 +110,16 @@ def test_a_side_near_the_limit_on_bids_is_finished_on_whole_lines(orc, n, m, hig
     assert did["list_sides_left"] > 0
 
 
+@pytest.mark.parametrize("n,m,masked", [(1300, 1300, 0.5), (1300, 1300, 0.0), (1290, 1500, 0.7), (1500, 1284, 0.2)])
+@pytest.mark.parametrize("options", [{"phase_stop": 1 << 20, "phase_keep": 1}, {"phase_stop": 1 << 20, "phase_keep": 2},
+                                     {"phase_stop": 2, "phase_keep": 3, "phase_growth": 4}])
+@pytest.mark.parametrize("wide", [0, 1])
+def test_columns_that_phases_leave_unused(orc, n, m, masked, options, wide):
+    """Phases that leave rows over leave columns unused at a price; in the last of them those bid."""
+    did = _solve(orc, synth.uniform_matrix(75, n, m, 2 ** 24, masked), dict(options, core_depth=0, core_wide=wide, core_narrow=64))
+    assert did["list_launches"] > 0
+
+
 @pytest.mark.parametrize("cfg,n,m", [("C5", 700, 300), ("C5", 1500, 2100), ("C4", 900, 1100), ("C5", 60, 20500), ("C5", 3001, 97)])
 @pytest.mark.parametrize("hidden", [(128,), (128, 64, 128)])
 @pytest.mark.parametrize("options", [{"core_depth": 0}, {"core_depth": 0, "core_wide": 1, "core_narrow": 16, "core_after": 0}])
