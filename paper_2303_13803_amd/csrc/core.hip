@@ -19,9 +19,9 @@
 // phase of a large problem run in launches over all dies, which hand over to one die once at most
 // core_narrow lines bid and get it back for the next phase (two launches a phase more, about 50 us).
 // The auction with all phases on one die / with such launches, mean over seeds: 2048 x 4096 3.6 / 3.9 ms,
-// 4096 x 8192 5.7 / 5.9, 6001 x 9007 13.4 / 13.3, 8192 x 8192 12.8 / 10.9, 8192 x 12288 11.4 / 11.6,
-// 12,000 x 16,000 30.7 / 26.3, 20,000 x 20,000 30.0 / 25.8; 20,000 x 40,000 with prefixes of a tenth
-// 21.2 / 21.1.  The line is drawn at 8192 rows.
+// 4096 x 8192 5.7 / 6.1, 6001 x 9007 13.5 / 13.3, 8192 x 8192 8.8 / 8.1, 8192 x 12288 11.7 / 11.7,
+// 12,000 x 16,000 29.8 / 26.6, 20,000 x 20,000 29.6 / 24.5; 20,000 x 40,000 with prefixes of a tenth
+// 21.6 / 20.8.  The line is drawn at 8192 rows.
 #include "scan.h"
 #include "search_words.h"
 #include "team_join.h"
