@@ -148,7 +148,7 @@ typedef struct {
  * scratch for problems up to max_n x max_m (each at most 2^20 - 2):
  * layer-1 projections, a transposed copy of the weight matrix and a copy with
  * rows and columns in order of memory fraction (4*max_n*max_m bytes each) and
- * O(max_n + max_m) solver state.
+ * O(max_n + max_m) solver state (about 2 KB for every row and column: the lists of best entries).
  * Fails with MF_ERR_HIP when no such device exists or memory runs out.
  */
 int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m);
