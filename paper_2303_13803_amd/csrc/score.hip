@@ -373,8 +373,8 @@ constexpr int PAIR_THREADS = 512;   // 8 wavefronts: two per SIMD share one LDS 
 constexpr int PAIR_WAVES = PAIR_THREADS / 64;
 constexpr int PAIR_COLS = PAIR_WAVES * 32;
 
-template <int H, bool SPLIT> struct PairShape {
-    static constexpr int ROWS = 64;                        // online rows per workgroup (128 with the fp16 pieces: measured slower)
+template <int H> struct PairShape {
+    static constexpr int ROWS = 64;                        // most online rows per workgroup (128 with the fp16 pieces: measured slower)
     static constexpr int KS = H / 2;                       // k-steps of the 32x32x2 tile
     static constexpr int MB = H / 32;                      // 32-row blocks of the hidden layer
     static constexpr size_t LDS_BYTES = sizeof(float) * ((size_t)H * H + (size_t)ROWS * H + 4 * H + 2 * ROWS);
@@ -418,9 +418,9 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     unsigned long long *__restrict__ evaluated, const int32_t *__restrict__ segment,
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
-    const unsigned *__restrict__ range)
+    const unsigned *__restrict__ range, int tile_rows)
 {
-    using S = PairShape<H, SPLIT>;
+    using S = PairShape<H>;
     constexpr int KS = S::KS, MB = S::MB, ROWS = S::ROWS, Q = KS / 4, KB = H / 16;
     extern __shared__ float4 lds4[];
     float4 *a_lds = lds4;                                  // [MB][Q][64] float4: MFMA A operand order
@@ -447,9 +447,9 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     // The row tile also shifts by one per column tile: in memory order the tiles with work
     // are the first so-many of each column tile, and without the shift the low XCDs would
     // collect the odd one out every time.
-    const int row0 = (int)((blockIdx.x + blockIdx.y) % gridDim.x) * ROWS;
+    const int row0 = (int)((blockIdx.x + blockIdx.y) % gridDim.x) * tile_rows;
     if (row0 >= n) return;                  // the grid's x extent is padded to a multiple of eight
-    const int nrows = min(ROWS, n - row0);
+    const int nrows = min(tile_rows, n - row0);
     const int j0 = (blockIdx.y * PAIR_WAVES + wave) * 32;
     // in memory order the tile's first row and first column are its smallest: if they do not
     // fit together, nothing in the tile does
@@ -530,17 +530,17 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
         constexpr int NR = decltype(nr_tag)::value;
         constexpr bool SPLIT_HERE = decltype(split_tag)::value;
         floatx16 acc[NR][MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        // b2, what the accumulators start from: the addend of a block's first matrix instructions, read by every
+        // row's from the same registers (copies of it were 64 instructions a row)
+        auto bias_of = [&](const int mb) {
+            floatx16 b;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                float4 bv = *(const float4 *)(b2_lds + mb * 32 + 8 * g + 4 * hh);
-#pragma unroll
-                for (int x = 0; x < NR; ++x) {
-                    acc[x][mb][4 * g] = bv.x; acc[x][mb][4 * g + 1] = bv.y;
-                    acc[x][mb][4 * g + 2] = bv.z; acc[x][mb][4 * g + 3] = bv.w;
-                }
+                const float4 bv = *(const float4 *)(b2_lds + mb * 32 + 8 * g + 4 * hh);
+                b[4 * g] = bv.x; b[4 * g + 1] = bv.y; b[4 * g + 2] = bv.z; b[4 * g + 3] = bv.w;
             }
+            return b;
+        };
         float share[NR];
 #pragma unroll
         for (int x = 0; x < NR; ++x) share[x] = PAIR_SM ? fminf(son_lds[r + x], soff) : 0.0f;
@@ -610,9 +610,11 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     // hi x hi, then the two cross terms; consecutive instructions alternate between the rows' accumulators
+                    floatx16 bias;
+                    if (kb == 0) bias = bias_of(mb);
 #pragma unroll
                     for (int x = 0; x < NR; ++x)
-                        acc[x][mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi[cur].v, bhi[x].v, acc[x][mb], 0, 0, 0);
+                        acc[x][mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi[cur].v, bhi[x].v, kb == 0 ? bias : acc[x][mb], 0, 0, 0);
 #pragma unroll
                     for (int x = 0; x < NR; ++x)
                         acc[x][mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi[cur].v, blo[x].v, acc[x][mb], 0, 0, 0);
@@ -623,6 +625,12 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
                 }
             }
         } else {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const floatx16 bias = bias_of(mb);
+#pragma unroll
+            for (int x = 0; x < NR; ++x) acc[x][mb] = bias;
+        }
         // operands of step q + 1 are fetched from LDS before the matrix instructions of step q are
         // issued, so that their latency hides behind those instead of in front of the next ones
         float4 av[2][MB], pv[2][NR];
@@ -688,54 +696,59 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
         float plus_inf = __builtin_inff();
         asm volatile("" : "+s"(plus_inf));
         auto relu = [plus_inf](const float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, plus_inf); };
+        // output layer on this lane's 16*MB hidden units
+        float zp[NR], sp[NR];
 #pragma unroll
-        for (int x = 0; x < NR; ++x) {
-            // output layer on this lane's 16*MB hidden units, then add the other half-wave's
-            float zp = 0.0f;
+        for (int x = 0; x < NR; ++x) zp[x] = sp[x] = 0.0f;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float4 wv = *(const float4 *)(w3_lds + mb * 32 + 8 * g + 4 * hh);
-                    zp = fmaf(wv.x, relu(acc[x][mb][4 * g]), zp);
-                    zp = fmaf(wv.y, relu(acc[x][mb][4 * g + 1]), zp);
-                    zp = fmaf(wv.z, relu(acc[x][mb][4 * g + 2]), zp);
-                    zp = fmaf(wv.w, relu(acc[x][mb][4 * g + 3]), zp);
-                }
-            const float z = zp + __shfl_xor(zp, 32) + bias3;
-            const float sg = 1.0f / (1.0f + expf(-z));
-            bool too_slow = false;
-            if (SLOWDOWN) {                 // the same output layer once more with the other unit's weights
-                float sp = 0.0f;
+            for (int g = 0; g < 4; ++g) {
+                const float4 wv = *(const float4 *)(w3_lds + mb * 32 + 8 * g + 4 * hh);
+                const float4 sv = SLOWDOWN ? *(const float4 *)(w3s_lds + mb * 32 + 8 * g + 4 * hh) : wv;
+                const float w[4] = {wv.x, wv.y, wv.z, wv.w}, ws[4] = {sv.x, sv.y, sv.z, sv.w};
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        float4 wv = *(const float4 *)(w3s_lds + mb * 32 + 8 * g + 4 * hh);
-                        sp = fmaf(wv.x, relu(acc[x][mb][4 * g]), sp);
-                        sp = fmaf(wv.y, relu(acc[x][mb][4 * g + 1]), sp);
-                        sp = fmaf(wv.z, relu(acc[x][mb][4 * g + 2]), sp);
-                        sp = fmaf(wv.w, relu(acc[x][mb][4 * g + 3]), sp);
+                    for (int x = 0; x < NR; ++x) {
+                        const float h2 = relu(acc[x][mb][4 * g + e]);
+                        zp[x] = fmaf(w[e], h2, zp[x]);
+                        if (SLOWDOWN) sp[x] = fmaf(ws[e], h2, sp[x]);
                     }
-                const float zs = sp + __shfl_xor(sp, 32) + bias3_slow;
-                too_slow = 1.0f / (1.0f + expf(-zs)) > slow_limit;
             }
-            if (hh == 0 && j < m) {
-                float qv = rintf(sg * scale);
-                qv = fminf(fmaxf(qv, 0.0f), scale);
-                int32_t w = (int32_t)qv;
-                const float memsum = mon_lds[r + x] + moff;
-                if (memsum > mem_limit || too_slow) w = MF_INFEASIBLE;
-                if (by_memory) {
-                    // the staged matrix: rows and columns both in memory order, one whole line per wave
-                    W[(size_t)(staged_row0 + row0 + r + x) * ldw + j] = w;
-                } else {
-                    // (looked up here, not above: a load still in flight at the end of a row makes
-                    // the next row wait for it and for every store issued after it)
-                    const int i = row_map ? row_map[row0 + r + x] : row0 + r + x;
-                    W[(size_t)i * ldw + jc] = w;
-                    if (sigma) sigma[(size_t)i * m + jc] = sg;
-                }
+        // ... plus the other half-wave's.  Of two rows the lower half-wave takes the first one's sum and the upper
+        // half-wave the second one's, and either goes on with its own row: one logistic for both rows
+        auto both_halves = [](const float *p) {
+            if constexpr (NR == 2) {
+                const auto swapped = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0]), __float_as_uint(p[1]), false, false);
+                return __uint_as_float(swapped[0]) + __uint_as_float(swapped[1]);
+            } else {
+                return p[0] + __shfl_xor(p[0], 32);
+            }
+        };
+        const int mine = NR == 2 ? r + hh : r;
+        const float z = both_halves(zp) + bias3;
+        const float sg = 1.0f / (1.0f + expf(-z));
+        bool too_slow = false;
+        if (SLOWDOWN) {
+            const float zs = both_halves(sp) + bias3_slow;
+            too_slow = 1.0f / (1.0f + expf(-zs)) > slow_limit;
+        }
+        if ((NR == 2 || hh == 0) && j < m) {
+            float qv = rintf(sg * scale);
+            qv = fminf(fmaxf(qv, 0.0f), scale);
+            int32_t w = (int32_t)qv;
+            const float memsum = mon_lds[mine] + moff;
+            if (memsum > mem_limit || too_slow) w = MF_INFEASIBLE;
+            if (by_memory) {
+                // the staged matrix: rows and columns both in memory order, a whole line per half-wave
+                W[(size_t)(staged_row0 + row0 + mine) * ldw + j] = w;
+            } else {
+                // (looked up here, not above: a load still in flight at the end of a row makes
+                // the next row wait for it and for every store issued after it)
+                const int i = row_map ? row_map[row0 + mine] : row0 + mine;
+                W[(size_t)i * ldw + jc] = w;
+                if (sigma) sigma[(size_t)i * m + jc] = sg;
             }
         }
     };
@@ -753,12 +766,31 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     if (evaluated && lane == 0 && r > 0) atomicAdd(evaluated, (unsigned long long)r * (unsigned)min(32, m - j0));
 }
 
+// Rows per workgroup.  A workgroup costs its set-up (W2's pieces, the columns' projections), about as long as
+// PAIR_SETUP_ROWS rows, and its rows; a compute unit holds one at a time (H = 128), so a launch lasts as long as
+// ceil(workgroups / units) of them.  The 64 rows that share one set-up best are halved while that gets
+// shorter: a 64 x 64 round is otherwise scored by one workgroup and a 1024 x 1024 one by 64.  With 64 rows
+// always / with this rule: 64 x 64 97 / 37 us for the whole pass, 1024 x 1024 123 / 76, 777 x 1501 290 / 175,
+// 3001 x 2003 726 / 622; 4096 x 8192 and larger keep 64.
+constexpr int PAIR_SETUP_ROWS = 8;
+int pair_tile_rows(int rows, int column_tiles, int units)
+{
+    int best = 64;
+    long long least = -1;
+    for (int t = 64; t >= 8; t >>= 1) {
+        const long long workgroups = (long long)((rows + t - 1) / t) * column_tiles;
+        const long long work = (workgroups + units - 1) / (units > 0 ? units : 1) * (t + PAIR_SETUP_ROWS);
+        if (least < 0 || work < least) { least = work; best = t; }
+    }
+    return best;
+}
+
 template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
 int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, int64_t ldw,
                         float *d_sigma, const int32_t *row_map, const int32_t *col_map, bool by_memory,
                         const int32_t *segment, int grid_rows)
 {
-    using S = PairShape<H, SPLIT>;
+    using S = PairShape<H>;
     // (the attribute belongs to the device, so what has been set is remembered per context)
     const unsigned flag = 1u << (5 + (H == 128 ? 8 : 0) + (PAIR_SM ? 4 : 0) + (SLOWDOWN ? 2 : 0) + (SPLIT ? 1 : 0));
     if (!(ctx->kernels_configured & flag)) {
@@ -768,12 +800,13 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
     }
     // x covers the rows this launch scores (a segment of the row map, or all n), padded to a
     // multiple of 8: every XCD then meets the same row tiles for each column tile
-    dim3 grid((((grid_rows + S::ROWS - 1) / S::ROWS) + 7) & ~7, (m + PAIR_COLS - 1) / PAIR_COLS);
+    const int column_tiles = (m + PAIR_COLS - 1) / PAIR_COLS, tile_rows = pair_tile_rows(grid_rows, column_tiles, ctx->n_cus);
+    dim3 grid((((grid_rows + tile_rows - 1) / tile_rows) + 7) & ~7, column_tiles);
     hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(PAIR_THREADS), S::LDS_BYTES, ctx->stream,
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
-                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr);
+                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, tile_rows);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }

@@ -58,6 +58,20 @@ def test_scores_match_checker(mm, orc, cfg, n, m):
         ctx.close()
 
 
+@pytest.mark.parametrize("n,m", [(7, 40), (8, 33), (9, 256), (15, 257), (17, 255), (31, 513), (65, 1), (127, 300),
+                                 (2049, 31), (2500, 1030), (1, 70000)])
+@pytest.mark.parametrize("cfg", ["C2", "C3"])
+def test_scores_at_the_edges_of_row_tiles(mm, orc, cfg, n, m):
+    """A workgroup scores 8 to 64 rows, chosen by the shape, two rows at a time: remainders of either."""
+    r = synth.scheduling_round(cfg, 3, n=n, m=m)
+    ctx = mm.Context(n, m)
+    Wg, sg = _score_on_gpu(mm, ctx, r)
+    _compare(orc, r, Wg, sg)
+    ordered, _ = _score_on_gpu(mm, ctx, r, want_sigma=False)
+    assert (ordered == Wg).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("case", ["huge projections", "tiny hidden weights", "huge hidden weights", "mixed magnitudes",
                                   "zero hidden layer"])
 def test_scores_do_not_depend_on_the_size_of_the_numbers(mm, orc, case):
