@@ -53,183 +53,231 @@ constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose lis
 
 // ---------------------------------------------------------------- the lists
 
-// One workgroup per line: the CORE_LIST entries with the largest K w - dual.  What bounds it is
-// reading the line, once, and a dozen barriers: a thread keeps the values of its up to NV groups of
-// four entries in registers, as floats relative to a good entry (the few listed entries' weights are
-// read again), so that two workgroups of 1024 threads fit a compute unit and one reads while the other
-// waits (20,000 lines of 20,000 entries: 1.18 ms with weights and doubles kept, 0.93 ms; reading the line
-// three times took 1.25 ms).  The bound allows for the rounding.
-// The cut is found from a histogram of the distances to the line's best value in
-// eighths of a power of two: all entries of the bins that fit are taken, the next bin fills the
-// list up in an order that starts somewhere else in every line (tied bidders would otherwise all
-// hold the same few of many tied entries).  Only entries at least as good as the CORE_LIST + 1st of the
-// threads' own best values go into the histogram, a few hundred: one LDS atomic for every entry
-// would take longer than reading the line.
-// NV == 0: lines of any length, read three times.
-constexpr int LIST_BINS = 2048;
-constexpr float LIST_NONE = -3.0e38f;                // an entry that cannot be chosen
+// The CORE_LIST entries with the largest K w - dual of every line, and what no other entry exceeds.
+//
+// What bounds it is reading the lines, once, four at a time so that a load of duals serves
+// them all (as in round_kernel; one at a time where there are too few lines to fill the device so).  Which entries are kept on the way is decided by a cut taken from a sample of
+// the line (LIST_SAMPLE_GROUPS groups, an eighth of a long line, in pieces of 128 bytes all along it): about LIST_AIM entries
+// lie above it, they go to LDS, and the best CORE_LIST of those make the list.  Everything is in doubles,
+// so the bound is exact; the cut only has to be near: with a few entries less than CORE_LIST above it the list is that
+// much shorter, with more than LDS holds the line is read again with a cut from those that were kept.
+// Entries tied with the cut fill the list up, whichever come first from a place that differs from group to group
+// of lines (tied bidders would otherwise all hold the same few of many tied entries).
+// A wavefront per line finds cut and list by bisection: counts come from ballots, no barrier in between.
+// (Lists of 20,000 lines of 20,000 entries: 926 us when a workgroup of 1024 threads kept a whole line in
+// registers and found the cut by histograms, a dozen barriers a line; 380 us now, 4.2 TB/s.  4096 lines of 8192:
+// 81 -> 46 us; 20,000 x 40,000 with prefixes of a tenth, rows 552 -> 150 us, columns 380 -> 141 us.  One line a workgroup up
+// to four a compute unit: 256 lines of 20,000 take 60 us by fours, 29 us so.)
+constexpr int LIST_THREADS = 256, LIST_CAP = 512, LIST_AIM = 300, LIST_SAMPLE_GROUPS = 512;
+constexpr double LIST_ALL = -1.0e300, LIST_NONE = 1.0e300;      // cuts
 
-__device__ __forceinline__ int distance_bin(float d)         // d >= 0; monotone
+// Of the integers in v (PER a lane; `low`: unused), a cut with at most `most` of them above it, and at
+// least `least` unless ties forbid it.  All lanes return the same.
+template <int PER>
+__device__ __forceinline__ double cut_above(const double (&v)[PER], int least, int most, double low)
 {
-    return min((int)(__float_as_uint(d) >> 20), LIST_BINS - 1);
+    double top = low, bottom = 1.0e300;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { top = fmax(top, v[q]); if (v[q] > low) bottom = fmin(bottom, v[q]); }
+    double hi = wave_max(top), lo = -wave_max(-bottom) - 1.0;
+    while (hi - lo > 1.0) {
+        const double mid = floor(0.5 * (lo + hi));
+        int above = 0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) above += __popcll(__ballot(v[q] > mid));
+        if (above > most) lo = mid;
+        else { hi = mid; if (above >= least) break; }
+    }
+    return hi;
 }
-// where a bin is counted: lane l of the wavefront that sums them up has bins 32 l .. 32 l + 31, a row apart
-__device__ __forceinline__ int bin_slot(int bin) { return (bin & 31) * 64 + (bin >> 5); }
-static_assert(LIST_BINS == 64 * 32, "32 bins per lane");
 
-template <int NT, int NV>
-__global__ __launch_bounds__(NT, NV > 0 ? 8 : 4) void core_list_kernel(
+template <int LINES>                                    // lines a workgroup makes lists of, at most one a wavefront
+__global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
     const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *depth,
     const double *__restrict__ own_dual, const int *__restrict__ partner)
 {
-    __shared__ unsigned hist[LIST_BINS];
-    __shared__ double s_red[NT / 64];
-    __shared__ int s_low, s_fill, s_cut, s_room, s_all, s_near;
-    const int b = blockIdx.x * stride;
-    if (b >= lines) return;
-    const int tid = threadIdx.x;
-    int2 *out = entries + (size_t)b * CORE_LIST;
-    // a column nobody holds and that has no price will not bid soon: an empty list that says so (should
-    // it bid before the lists are made again, it reads its whole line)
-    if (partner && partner[b] < 0 && !(own_dual[b] > 0.0)) {
-        for (int t = tid; t < CORE_LIST; t += NT) out[t] = make_int2(0, MF_INFEASIBLE);
-        if (tid == 0) { bound[b] = CORE_FAR; depth[blockIdx.x] = 0.0; }
-        return;
-    }
-    const int to = line_len ? min(line_len[b], len) : len;
-    const int32_t *line = A + (size_t)b * pitch;
-    const int groups = (to + 3) / 4;
-    const int turn = groups > 0 ? (int)(((unsigned)b * 2654435761u >> 8) % (unsigned)groups) : 0;
-    for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
-    constexpr int KEEP = NV > 0 ? NV : 1;
-    float kept_v[KEEP][4];
-    auto group_of = [&](int g0) { const int g = g0 + turn; return g >= groups ? g - groups : g; };
-    double ref = 0.0;
-    auto read = [&](int g, float *v) {
-        const int4 w4 = *(const int4 *)(line + g * 4);                  // lines are padded to a multiple of four
-        const double2 p01 = *(const double2 *)(dual + g * 4);
-        const double2 p23 = *(const double2 *)(dual + g * 4 + 2);
-        const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
-        const double p[4] = {p01.x, p01.y, p23.x, p23.y};
+    constexpr int PER = LIST_CAP / 64;
+    static_assert(LINES <= LIST_THREADS / 64, "a wavefront per line chooses");
+    __shared__ double s_value[LINES][LIST_CAP];
+    __shared__ int2 s_entry[LINES][LIST_CAP], s_tie[LINES][CORE_LIST];
+    __shared__ int s_count[LINES], s_ties[LINES], s_again[LINES];
+    __shared__ double s_cut[LINES];
+    static_assert(LIST_CAP >= LIST_THREADS, "a sample's largest values, one a thread");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int32_t *line[LINES];
+    int to[LINES], longest = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            v[e] = g * 4 + e < to && w[e] != MF_INFEASIBLE ? (float)(fma(Kd, (double)w[e], -p[e]) - ref) : LIST_NONE;
-    };
-    auto block_max = [&](double v) {
-        v = wave_max(v);
+    for (int r = 0; r < LINES; ++r) {
+        const long long b = ((long long)blockIdx.x * LINES + r) * stride;
+        const bool have = b < lines;
+        // a column nobody holds and that has no price will not bid soon: an empty list that says so (should
+        // it bid before the lists are made again, it reads its whole line)
+        const bool idle = have && partner && partner[b] < 0 && !(own_dual[b] > 0.0);
+        line[r] = A + (size_t)(have ? b : 0) * pitch;
+        to[r] = !have ? -1 : idle ? 0 : line_len ? min(line_len[b], len) : len;
+        longest = max(longest, to[r]);
+    }
+    const int groups = (longest + 3) / 4;
+    const int turn = groups > 0 ? (int)((blockIdx.x * 2654435761u >> 8) % (unsigned)groups) : 0;
+    auto value_of = [&](int r, int j, int32_t w, double p) { return j < to[r] && w != MF_INFEASIBLE ? fma(Kd, (double)w, -p) : LIST_ALL; };
+    // ---- the sample: each thread's best of up to two groups ----
+    const int pieces = min(groups / 8, LIST_SAMPLE_GROUPS / 8);         // of eight groups
+    const bool sampled = longest > LIST_CAP;
+    int looked = 0;                                                     // groups looked at, one or two a thread
+    if (sampled) {
+        double best[LINES];
+#pragma unroll
+        for (int r = 0; r < LINES; ++r) best[r] = LIST_ALL;
+#pragma unroll
+        for (int q = 0; q < LIST_SAMPLE_GROUPS / LIST_THREADS; ++q) {
+            const int piece = (q * LIST_THREADS + tid) >> 3;
+            if (piece < pieces) {
+                const int g = (int)((long long)piece * groups / pieces) + (tid & 7);
+                const double2 p01 = *(const double2 *)(dual + g * 4);
+                const double2 p23 = *(const double2 *)(dual + g * 4 + 2);
+#pragma unroll
+                for (int r = 0; r < LINES; ++r) {
+                    const int4 w = *(const int4 *)(line[r] + g * 4);
+                    best[r] = fmax(best[r], fmax(fmax(value_of(r, g * 4, w.x, p01.x), value_of(r, g * 4 + 1, w.y, p01.y)),
+                                                 fmax(value_of(r, g * 4 + 2, w.z, p23.x), value_of(r, g * 4 + 3, w.w, p23.y))));
+                }
+            }
+        }
+        looked = pieces * 8;
+#pragma unroll
+        for (int r = 0; r < LINES; ++r) s_value[r][tid] = best[r];
         __syncthreads();
-        if ((tid & 63) == 0) s_red[tid >> 6] = v;
-        __syncthreads();
-        v = s_red[0];
-        for (int k = 1; k < NT / 64; ++k) v = fmax(v, s_red[k]);
-        return v;
-    };
+    }
+    const bool choosing = wave < LINES;                                 // this wavefront has a line to choose for
     {
-        // values are kept as floats relative to the best of a first stretch of the line
-        double first = NEG_HUGE;
-        if (tid < groups) {
-            const int g = group_of(tid);
-            const int4 w4 = *(const int4 *)(line + g * 4);
-            const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+        double cut = LIST_NONE;
+        int mine = -1;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (g * 4 + e < to && w[e] != MF_INFEASIBLE) first = fmax(first, fma(Kd, (double)w[e], -dual[g * 4 + e]));
+        for (int r = 0; r < LINES; ++r) if (r == wave) mine = to[r];
+        if (mine > 0 && (!sampled || mine <= LIST_CAP)) cut = LIST_ALL;
+        else if (mine > 0) {
+            double v[LIST_THREADS / 64];
+            int feasible = 0;
+#pragma unroll
+            for (int q = 0; q < LIST_THREADS / 64; ++q) { v[q] = s_value[wave][q * 64 + lane]; feasible += __popcll(__ballot(v[q] > LIST_ALL)); }
+            // LIST_AIM of the line's entries are above the cut that so many of the sample's parts have an entry above
+            const int parts = min(min(looked, LIST_THREADS), max(1, (int)((long long)looked * mine / longest)));
+            const float each = 4.0f * (float)looked / (float)min(looked, LIST_THREADS), share = fminf(1.0f, (float)LIST_AIM / (float)mine);
+            const int want = max(1, (int)(parts * (1.0f - powf(1.0f - share, each))));
+            cut = feasible <= want ? LIST_ALL : cut_above(v, want - want / 16, want, LIST_ALL);
         }
-        first = block_max(first);
-        if (first > NEG_HUGE) ref = first;
+        __syncthreads();
+        if (choosing && lane == 0) { s_cut[wave] = cut; s_count[wave] = 0; s_ties[wave] = 0; }
+        __syncthreads();
     }
-    if constexpr (NV > 0) {
+    // ---- every line, once ----
+    double cut[LINES];
 #pragma unroll
-        for (int q = 0; q < KEEP; ++q) {
-            const int g0 = tid + q * NT;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) kept_v[q][e] = LIST_NONE;
-            if (g0 < groups) read(group_of(g0), kept_v[q]);
-            if (q % 2) __builtin_amdgcn_sched_barrier(0);       // two groups' loads in flight: more would not fit beside what is kept
-        }
-    }
-    // what(position, value) for the entries worth more than `above`
-    auto for_each = [&](float above, auto what) {
-        if constexpr (NV > 0) {
-#pragma unroll
-            for (int q = 0; q < KEEP; ++q) {
-                const int g0 = tid + q * NT, g = group_of(g0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (kept_v[q][e] > above) what(g * 4 + e, kept_v[q][e]);
+    for (int r = 0; r < LINES; ++r) cut[r] = s_cut[r];
+    for (int attempt = 0;; ++attempt) {
+        auto keep = [&](int r, int j, int32_t w, double v) {
+            if (j >= to[r] || w == MF_INFEASIBLE) return;
+            if (v > cut[r]) {
+                const int at = atomicAdd(&s_count[r], 1);
+                if (at < LIST_CAP) { s_value[r][at] = v; s_entry[r][at] = make_int2(j, w); }
+            } else if (s_ties[r] < CORE_LIST) {
+                const int at = atomicAdd(&s_ties[r], 1);
+                if (at < CORE_LIST) s_tie[r][at] = make_int2(j, w);
             }
-        } else {
-            for (int g0 = tid; g0 < groups; g0 += NT) {
-                const int g = group_of(g0);
-                float v[4];
-                read(g, v);
+        };
+#pragma unroll 2
+        for (int g0 = tid; g0 < groups; g0 += LIST_THREADS) {
+            const int g = g0 + turn >= groups ? g0 + turn - groups : g0 + turn, j = g * 4;
+            int4 w[LINES];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (v[e] > above) what(g * 4 + e, v[e]);
+            for (int r = 0; r < LINES; ++r) w[r] = *(const int4 *)(line[r] + j);      // (lines are padded to a multiple of four)
+            const double2 p01 = *(const double2 *)(dual + j);
+            const double2 p23 = *(const double2 *)(dual + j + 2);
+#pragma unroll
+            for (int r = 0; r < LINES; ++r) {
+                const double v[4] = {fma(Kd, (double)w[r].x, -p01.x), fma(Kd, (double)w[r].y, -p01.y),
+                                     fma(Kd, (double)w[r].z, -p23.x), fma(Kd, (double)w[r].w, -p23.y)};
+                if (fmax(fmax(v[0], v[1]), fmax(v[2], v[3])) >= cut[r]) {
+                    if (v[0] >= cut[r]) keep(r, j, w[r].x, v[0]);
+                    if (v[1] >= cut[r]) keep(r, j + 1, w[r].y, v[1]);
+                    if (v[2] >= cut[r]) keep(r, j + 2, w[r].z, v[2]);
+                    if (v[3] >= cut[r]) keep(r, j + 3, w[r].w, v[3]);
+                }
             }
         }
-    };
-    // the first bin at which the histogram's running count exceeds CORE_LIST (LIST_BINS if none does)
-    // and the count before it (all, if none); first wavefront
-    constexpr int PER = LIST_BINS / 64;
-    auto find_cut = [&](int &bin, int &room) {
-        unsigned mine = 0;
-        for (int t = 0; t < PER; ++t) mine += hist[t * 64 + tid];
-        unsigned run = mine;
-        for (int d = 1; d < 64; d <<= 1) { const unsigned o = __shfl_up(run, d); if (tid >= d) run += o; }
-        unsigned before = run - mine;
-        if (tid == 63 && run <= (unsigned)CORE_LIST) { bin = LIST_BINS; room = (int)run; }
-        if (before <= (unsigned)CORE_LIST && run > (unsigned)CORE_LIST) {
-            int t = 0;
-            while (before + hist[t * 64 + tid] <= (unsigned)CORE_LIST) { before += hist[t * 64 + tid]; ++t; }
-            bin = tid * PER + t;
-            room = (int)before;
+        __syncthreads();
+        // more than LDS holds: once more, for these lines only
+        const int found = choosing ? s_count[wave] : 0;
+        const bool again = found > LIST_CAP && attempt < 4;
+        double higher = LIST_NONE;
+        if (again) {
+            double v[PER];
+#pragma unroll
+            for (int q = 0; q < PER; ++q) v[q] = s_value[wave][q * 64 + lane];
+            const int want = max(1, (int)((long long)LIST_AIM * LIST_CAP / found));
+            higher = cut_above(v, want - want / 16, want, LIST_ALL);
         }
-    };
-    float best = LIST_NONE;
-    for_each(LIST_NONE, [&](int, float v) { best = fmaxf(best, v); });
-    const float own = best;
-    best = (float)block_max((double)best);
-    if (own > LIST_NONE) atomicAdd(&hist[bin_slot(distance_bin(best - own))], 1u);
-    __syncthreads();
-    if (tid < 64) find_cut(s_near, s_room);                  // the bin the CORE_LIST + 1st of the threads' best values is in
-    __syncthreads();
-    const int near = s_near;
-    for (int t = tid; t < LIST_BINS; t += NT) hist[t] = 0u;
-    __syncthreads();
-    // (everything in the bins up to that one is worth more than this: one comparison an entry from here on)
-    const float above = near < LIST_BINS - 1 ? fmaxf(best - __uint_as_float((unsigned)(near + 1) << 20), LIST_NONE) : LIST_NONE;
-    for_each(above, [&](int, float v) {
-        const int bin = distance_bin(best - v);
-        if (bin <= near) atomicAdd(&hist[bin_slot(bin)], 1u);
-    });
-    __syncthreads();
-    if (tid < 64) {
-        find_cut(s_cut, s_room);
-        if (tid == 0) { s_low = 0; s_fill = 0; s_all = 1; }
+        if (choosing && lane == 0) s_again[wave] = again;
+        __syncthreads();
+        if (again && lane == 0) { s_cut[wave] = higher; s_count[wave] = 0; s_ties[wave] = 0; }
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < LINES; ++r) any |= s_again[r] != 0;
+        __syncthreads();
+        if (!any) break;
+#pragma unroll
+        for (int r = 0; r < LINES; ++r) cut[r] = s_again[r] ? s_cut[r] : LIST_NONE;
     }
-    __syncthreads();
-    const int cut = s_cut, low = s_room;
-    float outside = above;                                   // what is worth less is not on the list
-    if (tid == 0 && above > LIST_NONE) s_all = 0;
-    for_each(above, [&](int j, float v) {
-        const int bin = distance_bin(best - v);
-        if (bin < cut) out[atomicAdd(&s_low, 1)] = make_int2(j, line[j]);
-        else {
-            const int at = bin == cut ? low + atomicAdd(&s_fill, 1) : CORE_LIST;
-            if (at < CORE_LIST) out[at] = make_int2(j, line[j]);
-            else { outside = fmaxf(outside, v); s_all = 0; }
-        }
-    });
-    // (no smaller than any unlisted value was before it was rounded)
-    const double past = block_max((double)outside + fabs((double)outside) * 0x1p-23);
-    __syncthreads();
-    const int used = min(low + s_fill, CORE_LIST);
-    for (int t = used + tid; t < CORE_LIST; t += NT) out[t] = make_int2(0, MF_INFEASIBLE);
-    if (tid == 0) {
-        bound[b] = s_all ? CORE_UNBOUNDED : ref + past;
-        depth[blockIdx.x] = s_all ? 1.0e13 : (double)best - past;
+    // ---- a wavefront per line ----
+    const long long b = ((long long)blockIdx.x * LINES + wave) * stride;
+    if (!choosing || b >= lines) return;
+    int2 *out = entries + (size_t)b * CORE_LIST;
+    int mine = 0;
+#pragma unroll
+    for (int r = 0; r < LINES; ++r) if (r == wave) mine = to[r];
+    const bool idle = partner && partner[b] < 0 && !(own_dual[b] > 0.0);
+    const int found = s_count[wave], have = min(found, LIST_CAP);
+    const double line_cut = s_cut[wave];
+    double v[PER], best = LIST_ALL;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { v[q] = q * 64 + lane < have ? s_value[wave][q * 64 + lane] : LIST_ALL; best = fmax(best, v[q]); }
+    const double chosen_above = have > CORE_LIST ? cut_above(v, CORE_LIST - 4, CORE_LIST, LIST_ALL) : LIST_ALL;
+    int used = 0;
+    double past = LIST_ALL;                                             // the best that is not on the list
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const unsigned long long in = __ballot(v[q] > chosen_above);
+        if (v[q] > chosen_above) out[used + __popcll(in & below)] = s_entry[wave][q * 64 + lane];
+        used += __popcll(in);
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {                                     // ... and of those at the cut as many as there is room for
+        const bool tied = v[q] > LIST_ALL && v[q] == chosen_above, rest = v[q] > LIST_ALL && v[q] < chosen_above;
+        const unsigned long long in = __ballot(tied);
+        const int at = used + __popcll(in & below);
+        if (tied && at < CORE_LIST) out[at] = s_entry[wave][q * 64 + lane];
+        if ((tied && at >= CORE_LIST) || rest) past = fmax(past, v[q]);
+        used = min(CORE_LIST, used + __popcll(in));
+    }
+    if (found <= CORE_LIST) {
+        const int ties = min(s_ties[wave], CORE_LIST);
+        for (int t = lane; t < ties; t += 64)
+            if (used + t < CORE_LIST) out[used + t] = s_tie[wave][t];
+        if (ties > 0) best = fmax(best, line_cut);
+        used = min(CORE_LIST, used + ties);
+    }
+    for (int t = used + lane; t < CORE_LIST; t += 64) out[t] = make_int2(0, MF_INFEASIBLE);
+    best = wave_max(best);
+    past = wave_max(past);
+    // (what did not reach the cut may be worth as much; what LDS had no room for after five readings, as much as the best)
+    if (mine > 0 && line_cut > LIST_ALL) past = fmax(past, line_cut);
+    if (found > LIST_CAP) past = CORE_FAR;
+    if (lane == 0) {
+        const bool all = past == LIST_ALL;
+        bound[b] = idle ? CORE_FAR : all ? CORE_UNBOUNDED : past;
+        depth[(long long)blockIdx.x * LINES + wave] = idle ? 0.0 : all ? 1.0e13 : fmax(best - past, 0.0);
     }
 }
 
@@ -1630,18 +1678,12 @@ namespace {
 
 void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int which, double *depth, const double *own_dual, const int *partner)
 {
-    const dim3 grid((lines + stride - 1) / stride);
-#define MF_LIST(NT, NV)                                                                                                      \
-    hipLaunchKernelGGL((core_list_kernel<NT, NV>), grid, dim3(NT), 0, ctx->stream, s.A, s.pitch, s.len, s.line_len, lines,   \
-                       stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], depth, own_dual, partner)
-    // The threads' best values stand for the line's best, so there have to be well over CORE_LIST of them, and
-    // a line that fits in registers is read once.  What is asked is how long lines are allocated, not how
-    // long their feasible prefixes are: 20,000 x 40,000 with prefixes of 4,000 entries on average is read
-    // three times, 0.55 ms for the rows' lists (40,000 columns' lists, of 2,000 entries on average and once: 0.37 ms).
-    if (s.len <= 4096) MF_LIST(512, 2);
-    else if (s.len <= 8192) MF_LIST(512, 4);
-    else if (s.len <= 20480) MF_LIST(1024, 5);
-    else MF_LIST(1024, 0);
+    const int made = (lines + stride - 1) / stride;
+#define MF_LIST(LINES)                                                                                                                     \
+    hipLaunchKernelGGL((core_list_kernel<LINES>), dim3((made + LINES - 1) / LINES), dim3(LIST_THREADS), 0, ctx->stream, s.A, s.pitch, s.len, \
+                       s.line_len, lines, stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], depth, own_dual, partner)
+    if (made > 4 * ctx->n_cus) MF_LIST(4);
+    else MF_LIST(1);
 #undef MF_LIST
 }
 

@@ -44,6 +44,49 @@ def test_phases_on_lists_reach_the_optimum(orc, n, m, high, masked, options):
         ctx.close()
 
 
+def _sampled_columns(m):
+    """The entries of a long line that the cut of its list is taken from (see core_list_kernel)."""
+    groups = (m + 3) // 4
+    pieces = min(groups // 8, 64)
+    return [4 * (p * groups // pieces + t) + e for p in range(pieces) for t in range(8) for e in range(4)]
+
+
+@pytest.mark.parametrize("kind", ["ties", "two levels", "nearly empty", "sample misses the best", "only the sample is good", "sorted"])
+@pytest.mark.parametrize("n,m", [(90, 2053), (1030, 1031), (1027, 4098)])
+def test_lists_of_lines_a_sample_says_little_about(orc, n, m, kind):
+    """The cut of a list comes from a sample: ties at it, more entries above it than fit, hardly any; a line or
+    four lines a workgroup, with lines left over."""
+    import paper_2303_13803_amd as mm
+    rng = np.random.default_rng(n + m)
+    if kind == "ties":
+        W = np.full((n, m), 1000, np.int32)
+        W[rng.random((n, m)) < 0.02] = 1001
+    elif kind == "two levels":
+        W = (rng.random((n, m)) < 0.4).astype(np.int32)
+    elif kind == "nearly empty":
+        W = np.where(rng.random((n, m)) < 0.002, rng.integers(0, 2 ** 20, (n, m)), INF).astype(np.int32)
+    else:
+        W = rng.integers(0, 2 ** 20, (n, m)).astype(np.int32)
+        seen = [c for c in _sampled_columns(m) if c < m]
+        if kind == "sample misses the best":
+            W[:, seen] //= 1024
+        elif kind == "only the sample is good":
+            W[:, [c for c in range(m) if c not in set(seen)]] //= 1024
+        else:
+            W = np.sort(W, axis=1)[:, ::-1].copy()
+    expect = orc.max_weight_matching(W)[0]
+    ctx = mm.Context(n, m)
+    ctx.set_option("core_depth", 0)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    lists = ctx.last_timings()["lists_made"]
+    ctx.close()
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and lists > 0
+    assert res.primal == P == expect
+
+
 @pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
 def test_counters_of_a_solve_on_lists(n, m):
     """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
