@@ -332,7 +332,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *   lists    "core" (1; 0: never): the phases from the one on in which a list of every line's best entries
  *            reaches "core_depth" (20) epsilons below the best run on such lists, in one launch;
  *            "core_many" (4) / "core_few" (32): chain steps between two looks at the list of bidders,
- *            "core_after" (256): chain steps after which the last bidders are searched for,
+ *            "core_after" (256): chain steps after which the last bidders are searched for
+ *            (fewer in proportion on problems of less than 1664 lines),
  *            "core_width" (8192): label window of those searches, in epsilons, "core_refine" (200):
  *            epsilon, in weight units, at or below which a complete phase is followed by an attempt
  *            to prove its assignment optimal at once, "core_wide" (8192; 0: never): rows from which on the

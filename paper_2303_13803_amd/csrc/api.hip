@@ -190,7 +190,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
         const size_t fewer = (size_t)(max_n < max_m ? max_n : max_m);
         TRY(dev_alloc(&ctx->core_entries[0], fewer * MF_CORE_LIST));
         TRY(dev_alloc(&ctx->core_entries[1], nm * MF_CORE_LIST));
-        for (int k = 0; k < 2; ++k) { TRY(dev_alloc(&ctx->core_bound[k], nm)); TRY(dev_alloc(&ctx->core_built[k], nm)); TRY(dev_alloc(&ctx->core_reach[k], nm)); }
+        for (int k = 0; k < 2; ++k) { TRY(dev_alloc(&ctx->core_bound[k], nm)); TRY(dev_alloc(&ctx->core_half_bound[k], nm)); TRY(dev_alloc(&ctx->core_built[k], nm)); TRY(dev_alloc(&ctx->core_reach[k], nm)); }
         TRY(dev_alloc(&ctx->core_t_entries[0], fewer * MF_CORE_LIST));
         TRY(dev_alloc(&ctx->core_t_entries[1], nm * MF_CORE_LIST));
         for (int k = 0; k < 2; ++k) { TRY(dev_alloc(&ctx->core_t_start[k], nm)); TRY(dev_alloc(&ctx->core_t_at[k], nm)); }
@@ -239,7 +239,7 @@ int mf_destroy(mf_ctx *ctx)
     (void)hipStreamSynchronize(ctx->stream);
     void *dev[] = {ctx->score_range, ctx->proj_on, ctx->proj_off, ctx->mem_on, ctx->mem_off, ctx->sm_on, ctx->sm_off, ctx->order_on, ctx->order_off, ctx->rank_off, ctx->rank_on, ctx->mem_on_sorted, ctx->mem_off_sorted, ctx->fit_len_on, ctx->fit_len_off, ctx->staged, ctx->type_segment, ctx->pairs_evaluated, ctx->feasible_pairs, ctx->largest_weight, ctx->wt, ctx->price,
                    ctx->profit, ctx->colword, ctx->roword, ctx->row2col, ctx->col2row, ctx->team_ctl, ctx->path_ctl, ctx->path_label, ctx->path_expanded, ctx->path_frontier[0], ctx->path_frontier[1], ctx->path_stamp, ctx->path_held, ctx->path_base, ctx->path_tree, ctx->path_parent, ctx->path_jump, ctx->edge_count, ctx->edge_start, ctx->list[0], ctx->list[1], ctx->colmark, ctx->stats,
-                   ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
+                   ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_half_bound[0], ctx->core_half_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
                    ctx->core_t_entries[0], ctx->core_t_entries[1], ctx->core_t_start[0], ctx->core_t_start[1], ctx->core_t_at[0], ctx->core_t_at[1],
                    ctx->core_base, ctx->core_dropped, ctx->core_tree, ctx->core_depth, ctx->core_parent, ctx->core_read_from, ctx->core_weight, ctx->core_ctl, ctx->cert};
     for (void *p : dev) if (p) (void)hipFree(p);

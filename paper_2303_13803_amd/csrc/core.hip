@@ -94,7 +94,7 @@ __device__ __forceinline__ double cut_above(const double (&v)[PER], int least, i
 template <int LINES>                                    // lines a workgroup makes lists of, at most one a wavefront
 __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
-    const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *depth,
+    const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *__restrict__ half_bound, double *depth,
     const double *__restrict__ own_dual, const int *__restrict__ partner)
 {
     constexpr int PER = LIST_CAP / 64;
@@ -243,40 +243,47 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
 #pragma unroll
     for (int q = 0; q < PER; ++q) { v[q] = q * 64 + lane < have ? s_value[wave][q * 64 + lane] : LIST_ALL; best = fmax(best, v[q]); }
     const double chosen_above = have > CORE_LIST ? cut_above(v, CORE_LIST - 4, CORE_LIST, LIST_ALL) : LIST_ALL;
+    // the best half of them comes first (a bid looks at the rest only if that does not decide it)
+    constexpr int HALF = CORE_LIST / 2;
+    const double half_above = have > HALF ? cut_above(v, HALF - 4, HALF, LIST_ALL) : LIST_ALL;
     int used = 0;
-    double past = LIST_ALL;                                             // the best that is not on the list
+    double past = LIST_ALL, past_half = LIST_ALL;                       // the best that is not on the list, not in its first half
     const unsigned long long below = (1ull << lane) - 1ull;
+    auto put = [&](bool mine, double worth, int2 entry) {               // what there is no room for is `past`
+        const unsigned long long in = __ballot(mine);
+        const int at = used + __popcll(in & below);
+        if (mine && at < CORE_LIST) out[at] = entry;
+        if (mine && at >= CORE_LIST) past = fmax(past, worth);
+        if (mine && at >= HALF) past_half = fmax(past_half, worth);
+        used = min(CORE_LIST, used + __popcll(in));
+    };
+#pragma unroll
+    for (int q = 0; q < PER; ++q) put(v[q] > half_above, v[q], s_entry[wave][q * 64 + lane]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) put(v[q] > chosen_above && v[q] <= half_above, v[q], s_entry[wave][q * 64 + lane]);
+    // ... and of those at the cut as many as there is room for
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const unsigned long long in = __ballot(v[q] > chosen_above);
-        if (v[q] > chosen_above) out[used + __popcll(in & below)] = s_entry[wave][q * 64 + lane];
-        used += __popcll(in);
-    }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {                                     // ... and of those at the cut as many as there is room for
-        const bool tied = v[q] > LIST_ALL && v[q] == chosen_above, rest = v[q] > LIST_ALL && v[q] < chosen_above;
-        const unsigned long long in = __ballot(tied);
-        const int at = used + __popcll(in & below);
-        if (tied && at < CORE_LIST) out[at] = s_entry[wave][q * 64 + lane];
-        if ((tied && at >= CORE_LIST) || rest) past = fmax(past, v[q]);
-        used = min(CORE_LIST, used + __popcll(in));
+        put(v[q] > LIST_ALL && v[q] == chosen_above, v[q], s_entry[wave][q * 64 + lane]);
+        if (v[q] < chosen_above) past = fmax(past, v[q]);
     }
     if (found <= CORE_LIST) {
         const int ties = min(s_ties[wave], CORE_LIST);
-        for (int t = lane; t < ties; t += 64)
-            if (used + t < CORE_LIST) out[used + t] = s_tie[wave][t];
+        for (int t = 0; t < ties; t += 64) put(t + lane < ties, line_cut, s_tie[wave][min(t + lane, CORE_LIST - 1)]);
         if (ties > 0) best = fmax(best, line_cut);
-        used = min(CORE_LIST, used + ties);
     }
     for (int t = used + lane; t < CORE_LIST; t += 64) out[t] = make_int2(0, MF_INFEASIBLE);
     best = wave_max(best);
     past = wave_max(past);
+    past_half = wave_max(past_half);
     // (what did not reach the cut may be worth as much; what LDS had no room for after five readings, as much as the best)
     if (mine > 0 && line_cut > LIST_ALL) past = fmax(past, line_cut);
     if (found > LIST_CAP) past = CORE_FAR;
+    past_half = fmax(past_half, past);
     if (lane == 0) {
         const bool all = past == LIST_ALL;
         bound[b] = idle ? CORE_FAR : all ? CORE_UNBOUNDED : past;
+        half_bound[b] = idle ? CORE_FAR : past_half == LIST_ALL ? CORE_UNBOUNDED : past_half;
         depth[(long long)blockIdx.x * LINES + wave] = idle ? 0.0 : all ? 1.0e13 : fmax(best - past, 0.0);
     }
 }
@@ -329,7 +336,7 @@ struct CoreSide {
     const int2 *entries;
     int *t_start, *t_at;                // the lists by opposite line: where each one's entries start (and, while they are made, end)
     int2 *t_entries;                    // (line, weight)
-    const double *bound, *built, *reach;    // built: the opposite duals when the lists were made; reach: from a line's best entry to its bound
+    const double *bound, *half_bound, *built, *reach;    // built: the opposite duals when the lists were made; reach: from a line's best entry to its bound
 };
 
 struct CoreArgs {
@@ -529,8 +536,15 @@ struct Core {
         }
     }
 
-    // the same from the line's list; *outside: what no unlisted entry exceeds
-    __device__ __forceinline__ Top2 listed(const CoreSide &s, int b, double slack, double *outside)
+    // The best half of a line's list, a lane an entry, and what nothing else is worth more than.
+    struct Half { int2 e; double bound; };
+    __device__ __forceinline__ Half half_of(const CoreSide &s, int b) const
+    {
+        return Half{s.entries[(size_t)b * CORE_LIST + lane], s.half_bound[b]};
+    }
+
+    // Best and second-best value of b's whole list; *outside: what no unlisted entry exceeds
+    __device__ __forceinline__ Top2 listed(const CoreSide &s, int b, double slack, double *outside) const
     {
         const int2 *e = s.entries + (size_t)b * CORE_LIST;
         const int2 e0 = e[lane], e1 = e[lane + 64];
@@ -552,16 +566,52 @@ struct Core {
         return t;
     }
 
-    // One bid of bidder b by this wavefront; returns who has to bid next because of it, or -1.
-    __device__ __forceinline__ int bid(const CoreSide &s, int b, double eps, double slack, bool count_rests)
+    // One bid of bidder b by this wavefront; returns who has to bid next because of it, or -1, with the first half of
+    // that one's list in h.  What bounds hundreds of chains is how many words a die's L2 hands out (every entry's
+    // is a request of its own: 256 wavefronts ask for 32,768 a step, 16 channels serve one each a cycle), what
+    // bounds a few is the chain of dependent trips: list 0.13 us, words 0.13, bid 0.37.  So the better half of the list
+    // is looked at alone first, and decides if its two best are both worth more than anything else can be
+    // (nine bids in ten); and who will be evicted is known from the words, before the bid is made, unless
+    // another wavefront gets in between: his list is on its way while the bid is.  The first bids of a 20,000 x
+    // 20,000 phase 236 -> 187 us, its last 570 bidders 820 -> 627 us; a matching 15.3 -> 14.5 ms, next round 24.2 -> 23.3.
+    // A maximum of doubles is a dozen dependent instructions of eight cycles and more, one of integers half a
+    // dozen of four: the two best are found from the distances above that bound as floats (their bits are in
+    // their order).  Where floats do not tell the best apart the doubles do; the second best may be taken
+    // for a little more than it is, up to the best (the bid is that much lower, and at least an epsilon up).
+    __device__ __forceinline__ int bid(const CoreSide &s, int b, Half &h, double eps, double slack, bool count_rests)
     {
-        double outside;
-        Top2 t = listed(s, b, slack, &outside);
+        double outside = fmax(h.bound + slack, 0.0);        // (what is worth nothing is not bid for and holds no bid down)
+        const unsigned long long word = load_fresh_u64(&s.otherword[h.e.x]);
         ++bids;
-        if (t.b1 < outside) {                            // the list no longer decides
-            t = whole_line(s, b);
-            outside = NEG_HUGE;
-            if (lane == 0) atomicAdd(&sh.dense, 1);
+        const double v = fma(a.Kd, (double)h.e.y, -word_dual(word));
+        const int key = (int)__float_as_uint((float)fmax(v - outside, 0.0)), top = wave_max(key);
+        unsigned long long hit = __ballot(key == top);
+        Top2 t;
+        if (hit & (hit - 1ull)) {                           // (or none is worth more than `outside`)
+            const double most = wave_max(key == top ? v : NEG_HUGE);
+            hit = __ballot(key == top && v == most);
+            // among tied lanes the first at or after a lane that depends on the bidder
+            const unsigned turn = (unsigned)tie_salt(b) & 63u;
+            const unsigned long long turned = hit & (~0ull << turn);
+            hit = turned ? turned : hit;
+        }
+        const int src = __ffsll((long long)hit) - 1;
+        int guess = __builtin_amdgcn_readlane(word_id(word), src);
+        Half ahead = h;
+        if (guess >= 0) ahead = half_of(s, guess);
+        t.b1 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
+        t.idx = __builtin_amdgcn_readlane(h.e.x, src);
+        t.w = __builtin_amdgcn_readlane(h.e.y, src);
+        const int second = wave_max(lane == src ? 0 : key);
+        t.b2 = fmin(t.b1, ceil(outside + (double)(__uint_as_float((unsigned)second) * (1.0f + 0x1p-22f))));
+        if ((top == 0 || second == 0) && outside > 0.0) {
+            guess = -1;
+            t = listed(s, b, slack, &outside);
+            if (t.b1 < outside) {                           // the list no longer decides
+                t = whole_line(s, b);
+                outside = NEG_HUGE;
+                if (lane == 0) atomicAdd(&sh.dense, 1);
+            }
         }
         if (t.b1 <= eps) {
             if (count_rests) ++rests;
@@ -574,7 +624,9 @@ struct Core {
             const unsigned long long old = atomicMax(&s.otherword[t.idx], mine);
             next = old < mine ? word_id(old) : b;
         }
-        return __builtin_amdgcn_readfirstlane(next);
+        next = __builtin_amdgcn_readfirstlane(next);
+        if (next >= 0 && next != b) h = next == guess ? ahead : half_of(s, next);
+        return next;
     }
 
     // hands a bidder on to the next epoch (called by one lane)
@@ -749,9 +801,10 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
             // (far more looks at the list than a side takes: finish it on whole lines)
             if (bid_budget < 0.0 || ++looks > 100000u) return MF_CORE_LIMIT;
             for (int item = c.gwave(); item < count; item += c.gwaves()) {
-                int b = load_fresh_i32(&list[item]);
+                int b = __builtin_amdgcn_readfirstlane(load_fresh_i32(&list[item]));
+                Core::Half h = c.half_of(s, b);
                 int done = 0;
-                for (; b >= 0 && done < most; ++done) b = c.bid(s, b, eps, slack, count_rests);
+                for (; b >= 0 && done < most; ++done) b = c.bid(s, b, h, eps, slack, count_rests);
                 if (b >= 0 && c.lane == 0) c.push(b, next, counter);
                 if (c.gwave() == 0) c.depth += (unsigned)done;
             }
@@ -1681,7 +1734,7 @@ void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int whi
     const int made = (lines + stride - 1) / stride;
 #define MF_LIST(LINES)                                                                                                                     \
     hipLaunchKernelGGL((core_list_kernel<LINES>), dim3((made + LINES - 1) / LINES), dim3(LIST_THREADS), 0, ctx->stream, s.A, s.pitch, s.len, \
-                       s.line_len, lines, stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], depth, own_dual, partner)
+                       s.line_len, lines, stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner)
     if (made > 4 * ctx->n_cus) MF_LIST(4);
     else MF_LIST(1);
 #undef MF_LIST
@@ -1723,8 +1776,8 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
         const long long all = (long long)lines * side.len * ctx->core_read / 100, entries = all > ctx->core_read_least ? all : ctx->core_read_least;
         return entries / (side.typical_len > 1 ? side.typical_len : 1);
     };
-    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, read_limit(fwd, rn), fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_built[0], ctx->core_reach[0]};
-    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, read_limit(rev, rm), rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_built[1], ctx->core_reach[1]};
+    a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, read_limit(fwd, rn), fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_half_bound[0], ctx->core_built[0], ctx->core_reach[0]};
+    a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, read_limit(rev, rm), rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_half_bound[1], ctx->core_built[1], ctx->core_reach[1]};
     a.Kd = fwd.Kd;
     CorePhases phases{};
     for (int k = 0; k < plan.n_phases; ++k) { phases.eps[k] = (double)plan.eps[k]; phases.stop[k] = plan.stop[k]; phases.stop_grown[k] = plan.stop_grown[k]; }
@@ -1741,7 +1794,12 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.refine_patience = 40;
     a.refine_lower = 256.0;
     a.path_max = ctx->path_max;
-    a.path_after = ctx->path_after < ctx->core_after ? ctx->path_after : ctx->core_after;
+    {
+        // (a search of a small problem costs less than long chains of its last bidders: with 256 steps for every size /
+        // with this rule rounds of 64 x 64 take 0.95 / 0.79 ms, 1024 x 1024 2.37 / 2.28, from 1664 rows on the same)
+        const long long share = 48 + rn / 8, after = ctx->core_after * (share < 256 ? share : 256) / 256;
+        a.path_after = ctx->path_after < after ? ctx->path_after : after;
+    }
     a.tail_steps = ctx->phase_tail_steps;
     a.steps_many = ctx->core_many; a.steps_few = ctx->core_few;
     a.path_width = (double)ctx->core_width;
@@ -1778,6 +1836,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
     st->launches += 1;
+    // (a bid counts as a whole list, also where the first half of it decided)
     st->bytes += (long long)(h.bids + h.scans) * CORE_LIST * 8 + (long long)h.whole_groups * 16;
     return MF_OK;
 }

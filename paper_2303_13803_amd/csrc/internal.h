@@ -153,7 +153,7 @@ struct mf_ctx {
     int core_refine;                // epsilon (weight units) at or below which a complete phase is followed by a refinement
     int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
     int core_width;                 // label window of a search on lists, in epsilons
-    double *core_bound[2], *core_built[2], *core_reach[2], *core_depth, *h_core_depth;
+    double *core_bound[2], *core_half_bound[2], *core_built[2], *core_reach[2], *core_depth, *h_core_depth;
     int *core_t_start[2], *core_t_at[2], *core_tree;    // the lists by opposite line (searches)
     int2 *core_t_entries[2];
     double *core_base, *core_dropped;

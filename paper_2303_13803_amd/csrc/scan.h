@@ -12,11 +12,17 @@ constexpr int BID_THREADS = 256;
 constexpr int MAX_GRID = 8192;
 constexpr double NEG_HUGE = -1.0e300;
 
+// (duals are integers below 2^44: added to 2^52 such an integer stands in the low bits of the sum, and the exponent
+// above them leaves at the top of the word; converting takes three times as many instructions)
 __device__ inline unsigned long long pack_word(double dual, int id_plus_one)
 {
-    return ((unsigned long long)(long long)dual << MF_ID_BITS) | (unsigned long long)id_plus_one;
+    static_assert(MF_ID_BITS == 20, "64 - 20 bits hold a dual");
+    return ((unsigned long long)__double_as_longlong(dual + 0x1p52) << MF_ID_BITS) | (unsigned long long)id_plus_one;
 }
-__device__ inline double word_dual(unsigned long long w) { return (double)(long long)(w >> MF_ID_BITS); }
+__device__ inline double word_dual(unsigned long long w)
+{
+    return __longlong_as_double((long long)((w >> MF_ID_BITS) | 0x4330000000000000ull)) - 0x1p52;
+}
 __device__ inline int word_id(unsigned long long w) { return (int)(w & MF_ID_MASK) - 1; }
 
 struct Top2 {
@@ -120,6 +126,23 @@ __device__ __forceinline__ double wave_max(double v)
     v = fmax(v, dpp_move<DPP_ROW_BCAST31>(v));
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
                             __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// (the lowest integer where a step has no source: moves and maxima are then one instruction a step)
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int v)
+{
+    return max(v, __builtin_amdgcn_update_dpp((int)0x80000000, v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ int wave_max(int v)
+{
+    v = dpp_max<DPP_ROW_SHR1>(v);
+    v = dpp_max<DPP_ROW_SHR2>(v);
+    v = dpp_max<DPP_ROW_SHR4>(v);
+    v = dpp_max<DPP_ROW_SHR8>(v);
+    v = dpp_max<DPP_ROW_BCAST15>(v);
+    v = dpp_max<DPP_ROW_BCAST31>(v);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ int wave_min(int v)

@@ -87,6 +87,24 @@ def test_lists_of_lines_a_sample_says_little_about(orc, n, m, kind):
     assert res.primal == P == expect
 
 
+@pytest.mark.parametrize("high", [2, 2 ** 20])
+@pytest.mark.parametrize("n,m", [(30, 63), (50, 64), (64, 65), (100, 66), (120, 127), (127, 128), (600, 700)])
+def test_bids_that_half_a_list_decides_or_does_not(orc, n, m, high):
+    """The first 64 entries of a list decide a bid if nothing else can be worth as much as its two best: lists of
+    about that length, with many ties (one of which always is) and with hardly any."""
+    import paper_2303_13803_amd as mm
+    W = synth.uniform_matrix(73, n, m, high, 0.1)
+    expect = orc.max_weight_matching(W if n <= m else np.ascontiguousarray(W.T))[0]
+    ctx = mm.Context(n, m)
+    ctx.set_option("core_depth", 0)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    ctx.close()
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P == expect
+
+
 @pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
 def test_counters_of_a_solve_on_lists(n, m):
     """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
