@@ -39,6 +39,7 @@ constexpr int CORE_SLICE = 1024;                    // entries of a whole line o
 // Rounds a workgroup goes on by itself within a step of a search or a refinement, and rows it does so
 // with at most (four for each of its wavefronts).  4 to 16 rounds measure the same within 3 %.
 constexpr int CORE_OWN_ROUNDS = 10, CORE_OWN_MOST = 32;
+constexpr int CORE_RESCANS = 4;                     // rows looked at once more for served trees, in lines of the side, before the lists are kept by column
 constexpr unsigned long long CORE_INF = ~0ull;
 constexpr unsigned CORE_IN_TREE = 0xffffffffu, CORE_READ = 1u;     // of a column, in a search: in the tree being served; its holder's line has been read whole
 constexpr int CORE_NO_LABEL = INT32_MIN;
@@ -308,6 +309,7 @@ struct alignas(256) CoreCtl {
     unsigned dense[4];                                   // whole lines read in an epoch (same ring)
     alignas(128) unsigned long long slack[3];            // see slack_of: bits of a non-negative double, two means
     int rev_count, tree_count, read_count;
+    unsigned long long rescans;                          // rows looked at once more for a served tree's columns, this search
     // searches
     // (read together, a lane each: [0..2] lowest label left per slot, [3..5] path ends found, [6..8] frontier lengths, [9] sink, [10..12] lines to be read whole)
     alignas(128) unsigned long long low[3];
@@ -832,7 +834,7 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
 // When a path is served only the columns of its root's tree change price, and only they lose their
 // labels: no label of another tree can become shorter, because a column of the tree is, at its raised
 // price, at least as far from any scanned row as the served path was long.  The tree's columns get
-// their new labels from the scanned rows whose lists they are on, through the lists kept by column, and
+// their new labels from the scanned rows whose lists they are on, and
 // candidates a scan left out because they lay beyond the path end of the time are remembered by
 // the shortest one.  (Scanning every labelled row again after each path was 600,000 scans, not 50,000, for
 // a 20,000 x 20,000 matching.)
@@ -871,7 +873,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
         store_through(&ctl->whole_front[gtid()], 0ull);
     }
     if (gtid() <= CORE_JUMP_PASSES) store_u32(&ctl->jump_pending[gtid()], 0u);
-    if (gtid() == 0) store_through(&ctl->sink, CORE_INF);
+    if (gtid() == 0) { store_through(&ctl->sink, CORE_INF); store_through(&ctl->rescans, 0ull); }
     if (!barrier()) return MF_CORE_ABORT;
     if (tid < count) {
         sh.profit[tid] = __longlong_as_double((long long)load_fresh_u64(&ctl->src_profit[tid]));
@@ -889,10 +891,6 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
     __syncthreads();
     int n_alive = sh.n_alive;
     const unsigned side_bit = s.otherword == a.side[0].otherword ? 1u : 2u;
-    if (n_alive > 1 && !(columns_ready & side_bit)) {
-        if (!by_column(s)) return MF_CORE_ABORT;
-        columns_ready |= side_bit;
-    }
     auto resting_bidders = [&]() {
         unsigned long long best = CORE_INF;
         for (int e = 0; e < n_alive; ++e) {
@@ -1002,14 +1000,16 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                             const int h = load_fresh_i32(&a.held[sink_id]);
                             k = h < 0 ? -1 : h;
                         }
+                        // (one dependent trip a hop here; the words are changed below, by as many threads as there are hops)
                         unsigned hops = 0;
                         while (k >= 0 && hops <= (unsigned)s.lines) {
                             const unsigned long long pr = load_fresh_u64(&a.parent[k]);
                             const int i = (int)(pr >> 32);
-                            const unsigned long long word = load_fresh_u64(&s.otherword[k]);
-                            store_through(&s.otherword[k], pack_word(word_dual(word) + eps, i + 1));
                             if (hops < (unsigned)CORE_PUSH_BUFFER) sh.list[hops] = ((unsigned long long)(unsigned)i << 32) | (unsigned long long)(unsigned)k;
-                            else store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                            else {
+                                store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
+                                store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                            }
                             ++hops;
                             k = (int)(unsigned)(pr & 0xffffffffull);
                         }
@@ -1024,6 +1024,7 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                     __syncthreads();
                     for (unsigned t = tid; t < min(sh.pushes, (unsigned)CORE_PUSH_BUFFER); t += CORE_THREADS) {
                         const int k = (int)(unsigned)(sh.list[t] & 0xffffffffull), i = (int)(sh.list[t] >> 32);
+                        store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
                         store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
                     }
                 }
@@ -1063,11 +1064,62 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
                 since_served = 0;
                 --step;
                 if (n_alive > 0) {
-                    // new labels for the tree's columns: a wavefront per column, or stretch of one's entries,
-                    // looks at the scanned rows whose lists it is on
+                    // New labels for the tree's columns, from the scanned rows whose lists they are on.  Either every
+                    // scanned row's list is looked through once more, or the lists are kept by column as well and
+                    // a wavefront takes a column, or a stretch of its entries.  Making those takes one die 0.1 ms for
+                    // 1024 lines, 0.65 ms for 20,000 (1 ms with 40,000 columns); looking through a thousand lists takes
+                    // 15 us, and a search has a dozen trees to serve.  So they are made once four times as many
+                    // rows have been looked at as there are, few searches.  (Made at the start of every
+                    // search: 20,000 x 20,000 next round 23.5 / 21.7 ms, 20,000 x 40,000 24.5 / 22.7, matching 14.3 /
+                    // 13.7, 4096 x 8192 7.65 / 7.44, smaller ones the same.)
                     const int n_tree = load_fresh_i32(&ctl->tree_count);
                     constexpr int STRETCH = 512;
-                    for (int it = gwave(); it < n_tree; it += gwaves()) {
+                    if (!(columns_ready & side_bit) && (s.len > CORE_PUSH_BUFFER * 32 || s.lines / (int)G + CORE_THREADS > CORE_PUSH_BUFFER || load_fresh_u64(&ctl->rescans) > (unsigned long long)s.lines * CORE_RESCANS)) {
+                        if (!by_column(s)) return MF_CORE_ABORT;
+                        columns_ready |= side_bit;
+                    }
+                    if (!(columns_ready & side_bit)) {
+                        unsigned *in_tree = (unsigned *)sh.list;             // a bit a column, and this workgroup's scanned rows
+                        int *rows = (int *)(sh.list + CORE_PUSH_BUFFER / 2);
+                        __syncthreads();
+                        if (tid == 0) sh.pushes = 0u;
+                        for (int t = tid; t * 32 < s.len; t += CORE_THREADS) in_tree[t] = 0u;
+                        __syncthreads();
+                        for (int t = tid; t < n_tree; t += CORE_THREADS) {
+                            const int k = load_fresh_i32(&a.tree[t]);
+                            atomicOr(&in_tree[k >> 5], 1u << (k & 31));
+                        }
+                        for (int i = gtid(); i < s.lines; i += gsize())
+                            if (load_fresh(&a.base[i]) < CORE_FAR * 0.5) rows[atomicAdd(&sh.pushes, 1u)] = i;
+                        __syncthreads();
+                        const int looked = (int)sh.pushes;
+                        int i = wave < looked ? rows[wave] : 0;
+                        const int2 *e = s.entries + (size_t)i * CORE_LIST;
+                        int2 e0 = e[lane], e1 = e[lane + 64];
+                        double base = load_fresh(&a.base[i]);
+                        for (int t = wave; t < looked; t += CORE_WAVES) {
+                            const int2 now0 = e0, now1 = e1;
+                            const int now = i;
+                            const double from = base;
+                            if (t + CORE_WAVES < looked) {                   // the next row's list, meanwhile
+                                i = rows[t + CORE_WAVES];
+                                e = s.entries + (size_t)i * CORE_LIST;
+                                e0 = e[lane]; e1 = e[lane + 64];
+                                base = load_fresh(&a.base[i]);
+                            }
+                            const bool in0 = now0.y != MF_INFEASIBLE && (in_tree[now0.x >> 5] >> (now0.x & 31) & 1u);
+                            const bool in1 = now1.y != MF_INFEASIBLE && (in_tree[now1.x >> 5] >> (now1.x & 31) & 1u);
+                            if (!__any(in0 || in1)) continue;
+                            unsigned long long w0 = 0ull, w1 = 0ull, l0 = 0ull, l1 = 0ull;
+                            if (in0) { w0 = load_fresh_u64(&s.otherword[now0.x]); l0 = load_fresh_u64(&a.label[now0.x]); }
+                            if (in1) { w1 = load_fresh_u64(&s.otherword[now1.x]); l1 = load_fresh_u64(&a.label[now1.x]); }
+                            const unsigned long long m0 = ((unsigned long long)(long long)(from - fma(a.Kd, (double)now0.y, -word_dual(w0))) << MF_ID_BITS) | (unsigned long long)now;
+                            const unsigned long long m1 = ((unsigned long long)(long long)(from - fma(a.Kd, (double)now1.y, -word_dual(w1))) << MF_ID_BITS) | (unsigned long long)now;
+                            if (in0 && m0 < l0) atomicMin(&a.label[now0.x], m0);
+                            if (in1 && m1 < l1) atomicMin(&a.label[now1.x], m1);
+                        }
+                        if (tid == 0 && looked) atomicAdd(&ctl->rescans, (unsigned long long)looked);
+                    } else for (int it = gwave(); it < n_tree; it += gwaves()) {
                         const int k = load_fresh_i32(&a.tree[it]);
                         const int from = load_fresh_i32(&s.t_start[k]), to = load_fresh_i32(&s.t_at[k]);
                         const double price = word_dual(load_fresh_u64(&s.otherword[k]));

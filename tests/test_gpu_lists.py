@@ -105,6 +105,24 @@ def test_bids_that_half_a_list_decides_or_does_not(orc, n, m, high):
     assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P == expect
 
 
+@pytest.mark.parametrize("n,m,high", [(60, 140001, 2), (60, 131073, 2 ** 20), (300, 301, 2), (700, 720, 2 ** 20), (1500, 1600, 40)])
+def test_trees_of_a_search_get_their_labels_back(orc, n, m, high):
+    """Searches with many bidders from the first step on: a served tree's columns are reached again from the scanned
+    rows' lists, or from lists kept by column where there are more columns than a workgroup has bits for."""
+    import paper_2303_13803_amd as mm
+    W = synth.uniform_matrix(74, n, m, high, 0.3)
+    expect = orc.max_weight_matching(W)[0]
+    ctx = mm.Context(n, m)
+    for k, val in {"core_depth": 0, "core_after": 0, "core_refine": 0, "phase_keep": 8}.items():
+        ctx.set_option(k, val)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    ctx.close()
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P == expect
+
+
 @pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
 def test_counters_of_a_solve_on_lists(n, m):
     """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
