@@ -9,7 +9,7 @@ namespace {
 // Duals handed to the caller: v_j = p_j and the tightest row dual the prices
 // allow, u_i = max(0, max_j (K W_ij - p_j)).
 // RB rows per workgroup share every load of the prices (8 bytes per entry against 4 for a
-// weight), as in the bulk bidding rounds.
+// weight), as in the bulk bidding rounds; rows of different lengths go one by one.
 template <int NT, int RB>
 __global__ __launch_bounds__(NT) void duals_kernel(
     const int32_t *__restrict__ W, int64_t ldw, int n, int m, const double *__restrict__ price,
@@ -19,14 +19,13 @@ __global__ __launch_bounds__(NT) void duals_kernel(
     __shared__ Top2 red[RB + RB * (NT / 64)];
     for (int i0 = blockIdx.x * RB; i0 < n; i0 += gridDim.x * RB) {
         const int32_t *rows[RB];
-        int salt[RB];
-        int len = 0;                                        // the group scans as far as its longest row
+        int salt[RB], len = m;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             const int i = min(i0 + r, n - 1);               // a short last group repeats its last row
             rows[r] = W + (size_t)i * ldw;
             salt[r] = 0;
-            len = max(len, line_len ? min(line_len[i], m) : m);
+            if (RB == 1 && line_len) len = min(line_len[i], m);
         }
         block_scan_rows<NT, RB>(rows, salt, price, len, Kd, red);
         if (threadIdx.x < RB && i0 + (int)threadIdx.x < n) {
@@ -216,13 +215,14 @@ int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ld
 int mf_extract_duals(mf_ctx *ctx, const int32_t *A, int64_t lda, int rn, int rm, double Kd, const int *line_len,
                      int n, bool flip, bool staged, int32_t *d_row2col, int64_t *d_u, int64_t *d_v)
 {
-    const int groups = (rn + 3) / 4, grid = groups < MAX_GRID ? groups : MAX_GRID;
+    const int groups = line_len ? rn : (rn + 3) / 4, grid = groups < MAX_GRID ? groups : MAX_GRID, threads = line_len ? 256 : 64;
+    const auto kernel = line_len ? duals_kernel<256, 1> : duals_kernel<64, 4>;
     if (!flip && !staged) {
-        hipLaunchKernelGGL((duals_kernel<64, 4>), dim3(grid), dim3(64), 0, ctx->stream, A, lda, rn, rm,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, ctx->stream, A, lda, rn, rm,
                            ctx->price, ctx->row2col, Kd, d_row2col, d_u, d_v, line_len);
     } else {
         int64_t *u_int = (int64_t *)ctx->path_label, *v_int = (int64_t *)ctx->path_expanded;
-        hipLaunchKernelGGL((duals_kernel<64, 4>), dim3(grid), dim3(64), 0, ctx->stream, A, lda, rn, rm,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, ctx->stream, A, lda, rn, rm,
                            ctx->price, ctx->row2col, Kd, ctx->list[0], u_int, v_int, line_len);
         hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_row2col, n, -1);
         const int32_t *row_ids = staged ? (flip ? ctx->order_off : ctx->order_on) : nullptr;

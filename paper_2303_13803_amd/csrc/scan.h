@@ -241,6 +241,7 @@ __device__ inline Top2 block_scan(const int32_t *__restrict__ A, const double *_
 // four entries and applied to all RB lines, which cuts the on-chip traffic per
 // entry (duals are 8 bytes, weights 4) and keeps RB + 2 loads in flight per
 // thread.  On return red[r] holds line r's result (a barrier has been passed).
+// All RB lines are len long.
 template <int NT, int RB>
 __device__ __forceinline__ void block_scan_rows(const int32_t *const (&rows)[RB], const int (&salt)[RB],
                                                 const double *__restrict__ dual, int len, double Kd,

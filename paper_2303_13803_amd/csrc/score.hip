@@ -127,6 +127,8 @@ struct SetupArgs {
     const int32_t *group;                                  // of the online side: order by group first (optional)
     float *sorted[2];                                      // null: not wanted
     int32_t *fit_len[2];
+    int32_t *staged;                                       // the matrix in memory order, 16-byte aligned,
+    int64_t pitch;                                         // a multiple of four
     float mem_limit;
     int slice[2];
     unsigned long long *pairs_evaluated, *feasible_pairs;
@@ -184,6 +186,18 @@ __device__ __forceinline__ void count_ranks(const float *__restrict__ key, const
         }
         __syncthreads();
         const int upto = (lim + 3) & ~3;
+        // a stretch of keys that all sit earlier than this workgroup's, or all later: one comparison decides
+        // also between equal ones (two instructions a key, not seven)
+        const int own = blockIdx.x * RANK_THREADS;
+        if (!GROUPED && (base + lim <= own || base >= own + RANK_THREADS)) {
+            const bool earlier = base < own;
+            for (int t = 0; t < upto; t += 4) {
+                const uint4 v = *(const uint4 *)(tile + t);
+                if (earlier) before += (v.x <= mine) + (v.y <= mine) + (v.z <= mine) + (v.w <= mine);
+                else before += (v.x < mine) + (v.y < mine) + (v.z < mine) + (v.w < mine);
+            }
+            continue;
+        }
         for (int t = 0; t < upto; t += 4) {
             const uint4 v = *(const uint4 *)(tile + t);
             const int at = base + t;
@@ -224,33 +238,15 @@ __global__ __launch_bounds__(256) void order_kernel(SetupArgs a)
     if (a.sorted[side]) a.sorted[side][at] = a.mem[side][i];
 }
 
-// The staged matrix: rows and columns of the weight matrix in order of memory fraction.  Before
-// the pair kernel runs it is filled, in whole lines, with MF_INFEASIBLE where the memory rule
-// (paper: Section "Implementation", the memory quota; one float32 addition) says the pair cannot
-// share and 0 elsewhere, so that what the kernel skips is already marked.
-__global__ __launch_bounds__(256) void stage_marks_kernel(const float *__restrict__ mem_on_sorted,
-                                                          const float *__restrict__ mem_off_sorted, int n, int m,
-                                                          float mem_limit, int32_t *__restrict__ S, int64_t lds,
-                                                          const int32_t *__restrict__ fit_len)
-{
-    const int i = blockIdx.x;
-    const float mon = mem_on_sorted[i];
-    int32_t *row = S + (size_t)i * lds;                    // lds is a multiple of four, S 16-byte aligned
-    // the pairs before fit_len[i] can share and are all written by the scoring kernel: only the
-    // rest of the line needs marks (from the group of four the boundary falls in)
-    const int first = fit_len[i] & ~3;
-    for (int j = first + (blockIdx.y * 256 + threadIdx.x) * 4; j < m; j += gridDim.y * 1024) {
-        int32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (j + e < m && mon + mem_off_sorted[j + e] > mem_limit) ? MF_INFEASIBLE : 0;
-        *(int4 *)(row + j) = make_int4(w[0], w[1], w[2], w[3]);
-    }
-}
-
 // In memory order the pairs that can share form, in every row, a prefix of the columns (and in
 // every column a prefix of the rows): len[k] = how many entries of `other` (ascending) fit next
 // to mine[k].  A binary search on the same float32 rule the marks were written with.
 // (columns with rows ordered by group first: count of all rows.)  Also how many pairs can share at all.
+//
+// The staged matrix has rows and columns in that order.  The scoring kernel writes the prefixes, and everything that
+// reads a row reads its prefix only, in groups of four: so all it needs besides are infeasible marks in the group
+// the prefix ends in (paper: Section "Implementation", the memory quota).  Marking the rest, as was done
+// before, wrote 2.9 GB for 20,000 x 40,000 pairs of which a tenth can share, 0.8 ms.
 __global__ __launch_bounds__(256) void fit_prefix_kernel(SetupArgs a)
 {
     const int side = blockIdx.y, k = blockIdx.x * 256 + threadIdx.x;
@@ -268,6 +264,13 @@ __global__ __launch_bounds__(256) void fit_prefix_kernel(SetupArgs a)
             len = lo;
         }
         a.fit_len[side][k] = len;
+        if (side == 0 && (len & 3)) {
+            const int first = len & ~3, m = a.rows[1];
+            int32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = first + e >= len && first + e < m ? MF_INFEASIBLE : 0;
+            *(int4 *)(a.staged + (size_t)k * a.pitch + first) = make_int4(w[0], w[1], w[2], w[3]);
+        }
     }
     if (side) return;
     unsigned long long t = (unsigned)len;
@@ -297,18 +300,23 @@ __device__ inline void note_largest(int mx, int *largest)
 // sits in the caches.
 __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ S, int64_t lds,
                                                     const int32_t *__restrict__ rank_on,
-                                                    const int32_t *__restrict__ rank_off, int n, int m,
+                                                    const int32_t *__restrict__ rank_off,
+                                                    const int32_t *__restrict__ fit_len, int n, int m,
                                                     int32_t *__restrict__ W, int64_t ldw, int wide_stores,
                                                     int *largest)
 {
-    const int i = blockIdx.x;
-    const int32_t *src = S + (size_t)rank_on[i] * lds;
+    const int i = blockIdx.x, from = rank_on[i], len = fit_len[from];       // entries at or beyond len cannot share
+    const int32_t *src = S + (size_t)from * lds;
     int32_t *row = W + (size_t)i * ldw;
     int mx = 0;                                             // "cannot share" is the smallest integer
     for (int j = (blockIdx.y * 256 + threadIdx.x) * 4; j < m; j += gridDim.y * 1024) {
         int32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { w[e] = j + e < m ? src[rank_off[j + e]] : 0; mx = max(mx, w[e]); }
+        for (int e = 0; e < 4; ++e) {
+            const int p = rank_off[min(j + e, m - 1)];
+            w[e] = j + e < m ? (p < len ? src[p] : MF_INFEASIBLE) : 0;
+            mx = max(mx, w[e]);
+        }
         if (wide_stores && j + 3 < m) {
             *(int4 *)(row + j) = make_int4(w[0], w[1], w[2], w[3]);
         } else {
@@ -323,16 +331,19 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
 // The same through LDS, for rows that fit there (measured faster than the kernel above): a
 // workgroup per row loads the staged row in whole lines - only as far as its pairs can share,
 // everything beyond is a mark anyway - picks each output's entry out of LDS, and stores the row
-// in whole lines: no scattered access reaches the caches.
-constexpr int PLACE_THREADS = 1024;
-constexpr size_t PLACE_LDS_BYTES = 159 * 1024;            // of the 160 KB a gfx950 workgroup can have
+// in whole lines: no scattered access reaches the caches.  LDS takes PLACE_LDS_ENTRIES of a row, so that a
+// compute unit has two workgroups, one storing while the other loads; what a longer prefix has beyond that is
+// picked out of the caches (20,000 x 40,000 with prefixes of 4000 entries on average: 1.16 ms with LDS for whole rows
+// and one workgroup a compute unit, 1.06 so).
+constexpr int PLACE_THREADS = 1024, PLACE_LDS_ENTRIES = 79 * 256;
+constexpr int64_t PLACE_LONGEST = 40704;                  // columns up to which this is used (beyond, the kernel above)
 
 __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
     const int32_t *__restrict__ S, int64_t lds, const int32_t *__restrict__ rank_on,
     const int32_t *__restrict__ rank_off, const int32_t *__restrict__ fit_len, int n, int m,
     int32_t *__restrict__ W, int64_t ldw, int wide_stores, int *largest)
 {
-    extern __shared__ int32_t staged[];
+    __shared__ int32_t staged[PLACE_LDS_ENTRIES];
     const int i = blockIdx.x, tid = threadIdx.x;
     const int from = rank_on[i];
     const int32_t *src = S + (size_t)from * lds;
@@ -341,7 +352,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
     int mx = 0;                                             // "cannot share" is the smallest integer
     for (int t = tid * 4; t < len; t += PLACE_THREADS * 4) {
         const int4 v = *(const int4 *)(src + t);            // the last group may reach into the marks
-        *(int4 *)(staged + t) = v;
+        if (t < PLACE_LDS_ENTRIES) *(int4 *)(staged + t) = v;
         mx = max(max(mx, max(v.x, v.y)), max(v.z, v.w));
     }
     note_largest<PLACE_THREADS>(mx, largest);               // passes a barrier: the staged row is complete
@@ -350,7 +361,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int p = rank_off[min(j + e, m - 1)];
-            w[e] = j + e < m ? (p < len ? staged[p] : MF_INFEASIBLE) : 0;
+            w[e] = j + e < m ? (p < len ? (p < PLACE_LDS_ENTRIES ? staged[p] : src[p]) : MF_INFEASIBLE) : 0;
         }
         if (wide_stores && j + 3 < m) {
             *(int4 *)(row + j) = make_int4(w[0], w[1], w[2], w[3]);
@@ -918,6 +929,7 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     // score, walk rows and columns in memory order: the pairs that cannot fit then form one
     // corner of the tile grid and the kernel leaves them out.  Results land at the same places.
     const bool by_memory = ctx->fit_order && !d_sigma;
+    const int64_t lds = ((int64_t)m + 3) & ~3ll;
     // (each of these is a few microseconds of work: as eight launches, not twenty-two, the set-up of a
     // 64 x 64 round takes 31 us, not 310)
     SetupArgs a = setup_args(ctx, p0, d_on, n, d_off, m);
@@ -930,6 +942,8 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
         a.sorted[0] = ctx->mem_on_sorted; a.sorted[1] = ctx->mem_off_sorted;
         a.fit_len[0] = ctx->fit_len_on; a.fit_len[1] = ctx->fit_len_off;
         a.feasible_pairs = ctx->feasible_pairs;
+        a.staged = ctx->staged;
+        a.pitch = lds;
     }
     const int most = n > m ? n : m, blocks = (most + 255) / 256;
     hipLaunchKernelGGL(setup_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
@@ -947,16 +961,12 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
                            ctx->stream, a);
         hipLaunchKernelGGL(order_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
     }
-    const int64_t lds = ((int64_t)m + 3) & ~3ll;
     ctx->staged_n = ctx->staged_m = 0;
     if (by_memory) {
-        const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
         // feasibility is a prefix of every staged row (columns are in memory order) and, when the
         // rows are in memory order too - one predictor - of every staged column; with several
         // predictors the rows are ordered by type first and columns are read whole
         hipLaunchKernelGGL(fit_prefix_kernel, dim3(blocks, 2), dim3(256), 0, ctx->stream, a);
-        hipLaunchKernelGGL(stage_marks_kernel, dim3(n, chunks), dim3(256), 0, ctx->stream, ctx->mem_on_sorted,
-                           ctx->mem_off_sorted, n, m, p0->mem_limit, ctx->staged, lds, ctx->fit_len_on);
         ctx->staged_n = n;
         ctx->staged_m = m;
     }
@@ -984,18 +994,13 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     if (by_memory) {
         const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
         const int wide = ((uintptr_t)d_W & 15u) == 0 && (ldw & 3) == 0;
-        if ((size_t)lds * sizeof(int32_t) <= PLACE_LDS_BYTES) {
-            if (!(ctx->kernels_configured & 16u)) {
-                MF_HIP(hipFuncSetAttribute((const void *)place_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)PLACE_LDS_BYTES));
-                ctx->kernels_configured |= 16u;
-            }
-            hipLaunchKernelGGL(place_lds_kernel, dim3(n), dim3(PLACE_THREADS), sizeof(int32_t) * (size_t)lds, ctx->stream,
+        if (lds <= PLACE_LONGEST) {
+            hipLaunchKernelGGL(place_lds_kernel, dim3(n), dim3(PLACE_THREADS), 0, ctx->stream,
                                ctx->staged, lds, ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide,
                                ctx->largest_weight);
         } else {
             hipLaunchKernelGGL(place_kernel, dim3(n, chunks), dim3(256), 0, ctx->stream, ctx->staged, lds,
-                               ctx->rank_on, ctx->rank_off, n, m, d_W, ldw, wide, ctx->largest_weight);
+                               ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide, ctx->largest_weight);
         }
         MF_HIP(hipGetLastError());
         ctx->largest_weight_known = true;
