@@ -759,6 +759,9 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     return MF_OK;
 }
 
+// Lists made for one side of one phase before it is finished on whole lines.
+constexpr int CORE_MOST_LISTS = 64;
+
 // The rest of a solve, from phase `ph`, on lists of every line's best entries (core.hip): one launch
 // unless lists have to be made (again) or a side has to be finished on whole lines.  *after: n_phases
 // when the solve is done, else the phase to go on from without this.
@@ -783,6 +786,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
         if (!have_transpose) make_transpose();
     }
     int lists_made = 0, at_phase = -1, at_stage = -1;
+    bool some_newer = false;
     for (;;) {
         plan.bid_limit = (double)ctx->max_rounds - (double)ctx->h_stats->bids - (double)st.bids;
         plan.rested_before = (unsigned long long)ctx->h_stats->rested + (unsigned long long)st.rested;
@@ -795,11 +799,34 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
             after = st.phase;
             return MF_OK;
         }
-        if (st.reason == MF_CORE_HANDOVER) { st.wide = !st.wide; continue; }
         const bool forward = st.stage != MF_CORE_REVERSE;
+        if (st.reason == MF_CORE_HANDOVER) {
+            if (st.wide && some_newer && (st.stage == MF_CORE_FORWARD || st.stage == MF_CORE_REVERSE)) {
+                rc = forward ? mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr) : mf_core_lists(ctx, rev, rm, 1, nullptr, nullptr);
+                if (rc != MF_OK) return rc;
+                st.lists_made += 1;
+                st.columns_ready &= ~(forward ? 1u : 2u);
+            }
+            some_newer = false;
+            st.wide = !st.wide;
+            continue;
+        }
         if (st.phase != at_phase || st.stage != at_stage) { at_phase = st.phase; at_stage = st.stage; lists_made = 0; }
-        if (st.reason == MF_CORE_COLUMNS || (st.reason == MF_CORE_RELIST && ++lists_made <= 4)) {
+        if (st.reason == MF_CORE_COLUMNS || (st.reason == MF_CORE_RELIST && ++lists_made <= CORE_MOST_LISTS)) {
             if (!forward && !have_transpose) make_transpose();
+            const int lines = forward ? rn : rm;
+            if (st.reason == MF_CORE_RELIST && st.stage != MF_CORE_PHASE_DONE && st.wide && st.count < lines / 2) {
+                // thousands of bidders wait for better lists: theirs alone (the others' still hold, and the lot is
+                // made before one die takes over: a few hundred bidders would set off one row with an old list
+                // after the other, and wait 0.1 ms each time)
+                rc = forward ? mf_core_lists_of(ctx, fwd, ctx->list[st.parity], st.count, 0)
+                             : mf_core_lists_of(ctx, rev, ctx->list[st.parity], st.count, 1);
+                if (rc != MF_OK) return rc;
+                st.lists_made += 1;
+                some_newer = true;
+                st.columns_ready &= ~(forward ? 1u : 2u);
+                continue;
+            }
             rc = forward ? mf_core_lists(ctx, fwd, rn, 0, nullptr, nullptr)
                          : mf_core_lists(ctx, rev, rm, 1, ctx->price, ctx->col2row);
             if (rc != MF_OK) return rc;
@@ -979,11 +1006,17 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     bool core_ok = ctx->core && ctx->n_cus > 0 && !ctx->path_off;
     for (int ph = 0; ph < n_phases; ++ph) {
         // From the phase on in which a list of each row's best columns reaches far enough below the
-        // best (core_depth epsilons), the rest of the solve runs on such lists.
+        // best (core_depth epsilons), the rest of the solve runs on such lists.  On problems whose first bids
+        // run on all dies bidders whose lists have sunk wait there for better ones, a thousand and more at
+        // once, and lists pay from a twentieth of that depth on: 20,000 x 20,000 next rounds 21.4 / 19.7 ms, one pair
+        // in two of 15,000 x 15,000 19.4 / 13.8, others of 10,000 and more 0 to 4 % less.  Not with feasible
+        // prefixes, whose lines cost little (20,000 x 40,000 20.3 / 22.3), and not where one die does it all (6001 x
+        // 9007 13.2 / 14.2).
         if (core_ok && (ph > 0 || warm || rm <= MF_CORE_LIST)) {
             double deep = 1.0;
             if (rm > MF_CORE_LIST) {
-                const int rc = mf_core_probe(ctx, fwd, rn, (double)ctx->core_depth_eps * (double)ladder[ph], &deep);
+                const bool all_dies = ctx->core_wide > 0 && rn >= ctx->core_wide && !fwd.line_len;
+                const int rc = mf_core_probe(ctx, fwd, rn, (double)ctx->core_depth_eps * (double)ladder[ph] / (all_dies ? 20.0 : 1.0), &deep);
                 if (rc != MF_OK) return rc;
             }
             if (deep >= 0.75) {

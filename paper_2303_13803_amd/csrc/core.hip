@@ -44,6 +44,7 @@ constexpr unsigned long long CORE_INF = ~0ull;
 constexpr unsigned CORE_IN_TREE = 0xffffffffu, CORE_READ = 1u;     // of a column, in a search: in the tree being served; its holder's line has been read whole
 constexpr int CORE_NO_LABEL = INT32_MIN;
 constexpr int CORE_JUMP_HOPS = 4, CORE_JUMP_PASSES = 48;
+constexpr unsigned CORE_WAITING = 32;               // bidders waiting for better lists above which these are made
 constexpr unsigned CORE_GAVE_UP = 0x80000000u;
 // Looks at the word that says how many have joined before a workgroup takes those that have (see
 // team_join.h): long enough for another context's longest kernel to make room.
@@ -95,9 +96,12 @@ __device__ __forceinline__ double cut_above(const double (&v)[PER], int least, i
 template <int LINES>                                    // lines a workgroup makes lists of, at most one a wavefront
 __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
-    const double *__restrict__ dual, double Kd, int2 *__restrict__ entries, double *__restrict__ bound, double *__restrict__ half_bound, double *depth,
-    const double *__restrict__ own_dual, const int *__restrict__ partner)
+    const int *__restrict__ which, const double *__restrict__ dual, double Kd, int2 *__restrict__ entries,
+    double *__restrict__ bound, double *__restrict__ half_bound, double *depth, const double *__restrict__ own_dual,
+    const int *__restrict__ partner)
 {
+    // line number q of this launch's `lines`: every stride-th, or the q-th listed in `which`
+    auto line_number = [&](int q) { return which ? (long long)which[q] : (long long)q * stride; };
     constexpr int PER = LIST_CAP / 64;
     static_assert(LINES <= LIST_THREADS / 64, "a wavefront per line chooses");
     __shared__ double s_value[LINES][LIST_CAP];
@@ -110,12 +114,13 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     int to[LINES], longest = 0;
 #pragma unroll
     for (int r = 0; r < LINES; ++r) {
-        const long long b = ((long long)blockIdx.x * LINES + r) * stride;
-        const bool have = b < lines;
+        const int q = blockIdx.x * LINES + r;
+        const bool have = q < lines;
+        const long long b = have ? line_number(q) : 0;
         // a column nobody holds and that has no price will not bid soon: an empty list that says so (should
         // it bid before the lists are made again, it reads its whole line)
         const bool idle = have && partner && partner[b] < 0 && !(own_dual[b] > 0.0);
-        line[r] = A + (size_t)(have ? b : 0) * pitch;
+        line[r] = A + (size_t)b * pitch;
         to[r] = !have ? -1 : idle ? 0 : line_len ? min(line_len[b], len) : len;
         longest = max(longest, to[r]);
     }
@@ -231,8 +236,9 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
         for (int r = 0; r < LINES; ++r) cut[r] = s_again[r] ? s_cut[r] : LIST_NONE;
     }
     // ---- a wavefront per line ----
-    const long long b = ((long long)blockIdx.x * LINES + wave) * stride;
-    if (!choosing || b >= lines) return;
+    const int number = blockIdx.x * LINES + wave;
+    if (!choosing || number >= lines) return;
+    const long long b = line_number(number);
     int2 *out = entries + (size_t)b * CORE_LIST;
     int mine = 0;
 #pragma unroll
@@ -285,14 +291,16 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
         const bool all = past == LIST_ALL;
         bound[b] = idle ? CORE_FAR : all ? CORE_UNBOUNDED : past;
         half_bound[b] = idle ? CORE_FAR : past_half == LIST_ALL ? CORE_UNBOUNDED : past_half;
-        depth[(long long)blockIdx.x * LINES + wave] = idle ? 0.0 : all ? 1.0e13 : fmax(best - past, 0.0);
+        depth[which ? b : (long long)number] = idle ? 0.0 : all ? 1.0e13 : fmax(best - past, 0.0);
     }
 }
 
-__global__ void core_snapshot_kernel(const double *__restrict__ dual, int count, double *__restrict__ built)
+// built: the duals all lists of a side were made for; where some lines' lists are newer than others', the larger
+// ones (a bound holds as long as no dual is lower than when the list was made).
+__global__ void core_snapshot_kernel(const double *__restrict__ dual, int count, double *__restrict__ built, int some)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) built[k] = dual[k];
+    if (k < count) built[k] = some ? fmax(built[k], dual[k]) : dual[k];
 }
 
 // ---------------------------------------------------------------- the engine
@@ -443,7 +451,32 @@ __device__ __noinline__ Top2 read_whole_line(const int32_t *line, int to, const 
     return t;
 }
 
-// Everything a workgroup carries through the launch.
+// The same of a whole list (out of line for the same reason: nine bids in ten are decided by its first half).
+__device__ __noinline__ Top2 read_list(const int2 *e, const unsigned long long *words, double Kd, int salt)
+{
+    const int lane = threadIdx.x & 63;
+    const int2 e0 = e[lane], e1 = e[lane + 64];
+    const unsigned long long w0 = load_fresh_u64(&words[e0.x]), w1 = load_fresh_u64(&words[e1.x]);
+    const double v0 = fma(Kd, (double)e0.y, -word_dual(w0)), v1 = fma(Kd, (double)e1.y, -word_dual(w1));
+    const bool first = v0 >= v1;
+    const double hi = fmax(v0, v1), lo = fmin(v0, v1);
+    Top2 t;
+    t.b1 = wave_max(hi);
+    const unsigned long long hit = __ballot(hi == t.b1);
+    // among tied lanes the first at or after a lane that depends on the bidder
+    const unsigned turn = (unsigned)salt & 63u;
+    const unsigned long long turned = hit & (~0ull << turn);
+    const int src = __ffsll((long long)(turned ? turned : hit)) - 1;
+    t.b2 = wave_max(lane == src ? lo : hi);
+    t.idx = __builtin_amdgcn_readlane(first ? e0.x : e1.x, src);
+    t.w = __builtin_amdgcn_readlane(first ? e0.y : e1.y, src);
+    return t;
+}
+
+// Everything a workgroup carries through the launch.  LARGE: for problems whose first bids run on all dies, where
+// bidders may wait for better lists and counts are summed up by workgroup.  (Those few instructions cost a
+// chain's step 3 % where one die does it all.)
+template <bool LARGE>
 struct Core {
     const CoreArgs &a;
     CoreCtl *ctl;
@@ -548,24 +581,8 @@ struct Core {
     // Best and second-best value of b's whole list; *outside: what no unlisted entry exceeds
     __device__ __forceinline__ Top2 listed(const CoreSide &s, int b, double slack, double *outside) const
     {
-        const int2 *e = s.entries + (size_t)b * CORE_LIST;
-        const int2 e0 = e[lane], e1 = e[lane + 64];
         *outside = s.bound[b] + slack;
-        const unsigned long long w0 = load_fresh_u64(&s.otherword[e0.x]), w1 = load_fresh_u64(&s.otherword[e1.x]);
-        const double v0 = fma(a.Kd, (double)e0.y, -word_dual(w0)), v1 = fma(a.Kd, (double)e1.y, -word_dual(w1));
-        const bool first = v0 >= v1;
-        const double hi = fmax(v0, v1), lo = fmin(v0, v1);
-        Top2 t;
-        t.b1 = wave_max(hi);
-        const unsigned long long hit = __ballot(hi == t.b1);
-        // among tied lanes the first at or after a lane that depends on the bidder
-        const unsigned turn = (unsigned)tie_salt(b) & 63u;
-        const unsigned long long turned = (hit >> turn) | (turn ? hit << (64u - turn) : 0ull);
-        const int src = (int)((((unsigned)__ffsll((long long)turned) - 1u) + turn) & 63u);
-        t.b2 = wave_max(lane == src ? lo : hi);
-        t.idx = __builtin_amdgcn_readlane(first ? e0.x : e1.x, src);
-        t.w = __builtin_amdgcn_readlane(first ? e0.y : e1.y, src);
-        return t;
+        return read_list(s.entries + (size_t)b * CORE_LIST, s.otherword, a.Kd, tie_salt(b));
     }
 
     // One bid of bidder b by this wavefront; returns who has to bid next because of it, or -1, with the first half of
@@ -580,7 +597,8 @@ struct Core {
     // dozen of four: the two best are found from the distances above that bound as floats (their bits are in
     // their order).  Where floats do not tell the best apart the doubles do; the second best may be taken
     // for a little more than it is, up to the best (the bid is that much lower, and at least an epsilon up).
-    __device__ __forceinline__ int bid(const CoreSide &s, int b, Half &h, double eps, double slack, bool count_rests)
+    // waiting: if it is -1 a bidder whose whole list no longer decides does not have his line read but goes there.
+    __device__ __forceinline__ int bid(const CoreSide &s, int b, Half &h, double eps, double slack, bool count_rests, int &waiting)
     {
         double outside = fmax(h.bound + slack, 0.0);        // (what is worth nothing is not bid for and holds no bid down)
         const unsigned long long word = load_fresh_u64(&s.otherword[h.e.x]);
@@ -610,6 +628,12 @@ struct Core {
             guess = -1;
             t = listed(s, b, slack, &outside);
             if (t.b1 < outside) {                           // the list no longer decides
+                if (LARGE && waiting == -1) {
+                    if (lane == 0) atomicAdd(&sh.dense, 1);
+                    --bids;
+                    waiting = b;
+                    return -1;
+                }
                 t = whole_line(s, b);
                 outside = NEG_HUGE;
                 if (lane == 0) atomicAdd(&sh.dense, 1);
@@ -689,7 +713,16 @@ struct Core {
         for (int i = gtid(); i < s.lines; i += gsize()) reach += s.reach[i];
         most = wave_max(most);
         for (int off = 32; off >= 1; off >>= 1) { rise += __shfl_xor(rise, off); reach += __shfl_xor(reach, off); }
-        if (lane == 0) {
+        // (one workgroup's share at a time: atomics on one address complete at one per 10 ns, and 2048 wavefronts' took 25 us)
+        if (LARGE) {
+            double *part = (double *)sh.list;
+            __syncthreads();
+            if (lane == 0) { part[wave] = most; part[CORE_WAVES + wave] = rise; part[2 * CORE_WAVES + wave] = reach; }
+            __syncthreads();
+            if (tid == 0)
+                for (int w = 1; w < CORE_WAVES; ++w) { most = fmax(most, part[w]); rise += part[CORE_WAVES + w]; reach += part[2 * CORE_WAVES + w]; }
+        }
+        if (LARGE ? tid == 0 : lane == 0) {
             if (most > 0.0) atomicMax(&ctl->slack[0], (unsigned long long)__double_as_longlong(most));
             if (rise > 0.0) atomicAdd(&ctl->slack[1], (unsigned long long)(rise / s.len));
             atomicAdd(&ctl->slack[2], (unsigned long long)(reach / s.lines));
@@ -768,7 +801,8 @@ struct Core {
 
 // Runs one side until at most stop_at bidders are left.  epoch: position in the rings of lists and
 // counters.  Returns 0 (done), or a reason to leave the launch.
-__device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, double slack, int stop_at, bool count_rests, unsigned &epoch,
+template <bool LARGE>
+__device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, double eps, double slack, int stop_at, bool count_rests, unsigned &epoch,
                         int &count, double &bid_budget)
 {
     const CoreArgs &a = c.a;
@@ -776,6 +810,10 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
     long long few_steps = 0, stuck_steps = 0;
     int fewest = count;
     unsigned dense_lines = 0, looks = 0;
+    // Bidders whose lists no longer decide wait for better ones while there are many of them: a wavefront takes 0.1 to
+    // 0.3 ms to read a line of 20,000 past the caches, the lists of 9000 such lines are made in 0.2 ms.  (First bids of
+    // the second phase of a 20,000 x 20,000 round on lists: 2.1 ms with lines read, 0.12 ms and 0.4 ms of lists so.)
+    bool put_off = LARGE;
     while (count > stop_at) {
         const int *list = ((epoch & 1u) ? a.list1 : a.list0);
         int *next = ((epoch & 1u) ? a.list0 : a.list1);
@@ -804,9 +842,10 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
             if (bid_budget < 0.0 || ++looks > 100000u) return MF_CORE_LIMIT;
             for (int item = c.gwave(); item < count; item += c.gwaves()) {
                 int b = __builtin_amdgcn_readfirstlane(load_fresh_i32(&list[item]));
-                Core::Half h = c.half_of(s, b);
-                int done = 0;
-                for (; b >= 0 && done < most; ++done) b = c.bid(s, b, h, eps, slack, count_rests);
+                typename Core<LARGE>::Half h = c.half_of(s, b);
+                int done = 0, waiting = put_off ? -1 : -2;
+                for (; b >= 0 && done < most; ++done) b = c.bid(s, b, h, eps, slack, count_rests, waiting);
+                if (LARGE && waiting >= 0) b = waiting;
                 if (b >= 0 && c.lane == 0) c.push(b, next, counter);
                 if (c.gwave() == 0) c.depth += (unsigned)done;
             }
@@ -819,8 +858,15 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
         ++epoch;
         count = load_fresh_i32(&ctl->cnt[epoch & 3u]);
         if (count <= fewest - fewest / 8) { fewest = count; stuck_steps = 0; }
-        dense_lines += load_fresh_u32(&ctl->dense[epoch & 3u]);
-        if (count > stop_at && dense_lines > (unsigned)a.dense_limit) return MF_CORE_RELIST;
+        const unsigned dense = load_fresh_u32(&ctl->dense[epoch & 3u]);
+        if (LARGE && put_off) {
+            if (count > stop_at && dense > CORE_WAITING && 4u * dense >= (unsigned)count) return MF_CORE_RELIST;
+            put_off = dense == 0u || dense > CORE_WAITING;      // (few enough to read their lines)
+        } else {
+            dense_lines += dense;
+            if (count > stop_at && dense_lines > (unsigned)a.dense_limit) return MF_CORE_RELIST;
+            put_off = LARGE;
+        }
     }
     return 0;
 }
@@ -838,7 +884,8 @@ __device__ __forceinline__ int run_bids(Core &c, const CoreSide &s, double eps, 
 // candidates a scan left out because they lay beyond the path end of the time are remembered by
 // the shortest one.  (Scanning every labelled row again after each path was 600,000 scans, not 50,000, for
 // a 20,000 x 20,000 matching.)
-__device__ __forceinline__ int Core::search(const CoreSide &s, double eps, double slack, int listed_count, const int *list, int *next, int *counter)
+template <bool LARGE>
+__device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps, double slack, int listed_count, const int *list, int *next, int *counter)
 {
     const int count = min(listed_count, CORE_MAX_SOURCES);
     for (int k = gtid(); k < s.len; k += gsize()) {
@@ -1435,7 +1482,8 @@ __device__ __forceinline__ int Core::search(const CoreSide &s, double eps, doubl
 // phases at finer epsilons, which would re-assign everybody several times over only to arrive at the
 // same assignment, are then left out.  Returns 1 (prices proved exact), 0 (not optimal yet),
 // 2 (better lists are wanted; it goes on from the prices reached), or -1.
-__device__ __forceinline__ int Core::refine(double lower_by)
+template <bool LARGE>
+__device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
 {
     const CoreSide &s = a.side[0];
     for (int k = gtid(); k < s.len; k += gsize()) {
@@ -1578,13 +1626,28 @@ __device__ __forceinline__ int Core::refine(double lower_by)
 }
 
 // Ends the launch with everything the host, or the next launch, needs in memory.
-__device__ __forceinline__ int Core::leave(int reason, int phase, int stage, int count, int parity)
+template <bool LARGE>
+__device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int stage, int count, int parity)
 {
+    if (LARGE) {
+        __syncthreads();
+        if (tid < 4) sh.list[tid] = 0ull;
+        __syncthreads();
+    }
+    unsigned long long *sums[4] = {&ctl->bids, &ctl->scans, &ctl->whole_groups, &ctl->rested};
+    const unsigned mine[4] = {bids, scans, whole, rests};
     if (lane == 0) {
-        if (bids) atomicAdd(&ctl->bids, (unsigned long long)bids);
-        if (scans) atomicAdd(&ctl->scans, (unsigned long long)scans);
-        if (whole) atomicAdd(&ctl->whole_groups, (unsigned long long)whole);
-        if (rests) atomicAdd(&ctl->rested, (unsigned long long)rests);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (mine[q]) atomicAdd(LARGE ? &sh.list[q] : sums[q], (unsigned long long)mine[q]);
+    }
+    if (LARGE) {
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (sh.list[q]) atomicAdd(sums[q], sh.list[q]);
+        }
     }
     // a wait that runs out here still counts: the reason stays "a wait ran out"
     if (reason == MF_CORE_ABORT || !barrier()) return MF_CORE_ABORT;
@@ -1601,7 +1664,8 @@ __device__ __forceinline__ int Core::leave(int reason, int phase, int stage, int
     return reason;
 }
 
-__device__ __forceinline__ int Core::run()
+template <bool LARGE>
+__device__ __forceinline__ int Core<LARGE>::run()
 {
     const CoreSide &fwd = a.side[0], &rev = a.side[1];
     int ph = a.first_phase, stage = a.first_stage, count = a.first_count;
@@ -1750,10 +1814,11 @@ __device__ __forceinline__ int Core::run()
     }
 }
 
+template <bool LARGE>
 __global__ __launch_bounds__(CORE_THREADS) void core_kernel(CoreArgs a, CoreCtl *ctl)
 {
     __shared__ CoreShared sh;
-    Core core(a, ctl, sh);
+    Core<LARGE> core(a, ctl, sh);
     const int joined = core.join();
     if (joined != 1) return;                            // (not of that die, or a wait ran out: the reason stays as it was)
     (void)core.run();
@@ -1781,12 +1846,11 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
 
 namespace {
 
-void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int which, double *depth, const double *own_dual, const int *partner)
+void launch_lists(mf_ctx *ctx, const SideArgs &s, int made, int stride, const int *list, int which, double *depth, const double *own_dual, const int *partner)
 {
-    const int made = (lines + stride - 1) / stride;
 #define MF_LIST(LINES)                                                                                                                     \
     hipLaunchKernelGGL((core_list_kernel<LINES>), dim3((made + LINES - 1) / LINES), dim3(LIST_THREADS), 0, ctx->stream, s.A, s.pitch, s.len, \
-                       s.line_len, lines, stride, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner)
+                       s.line_len, made, stride, list, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner)
     if (made > 4 * ctx->n_cus) MF_LIST(4);
     else MF_LIST(1);
 #undef MF_LIST
@@ -1798,9 +1862,20 @@ void launch_lists(mf_ctx *ctx, const SideArgs &s, int lines, int stride, int whi
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner)
 {
     if (s.len <= CORE_LIST) partner = nullptr;          // whole lines: they never have to be made again
-    launch_lists(ctx, s, lines, 1, which, ctx->core_reach[which], own_dual, partner);
+    launch_lists(ctx, s, lines, 1, nullptr, which, ctx->core_reach[which], own_dual, partner);
     hipLaunchKernelGGL(core_snapshot_kernel, dim3((s.len + 255) / 256), dim3(256), 0, ctx->stream, s.other_dual, s.len,
-                       ctx->core_built[which]);
+                       ctx->core_built[which], 0);
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
+// The same for `count` lines only, those in `list` (device); the others' lists stay as they are.
+int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count, int which)
+{
+    if (count <= 0) return MF_OK;
+    launch_lists(ctx, s, count, 1, list, which, ctx->core_reach[which], nullptr, nullptr);
+    hipLaunchKernelGGL(core_snapshot_kernel, dim3((s.len + 255) / 256), dim3(256), 0, ctx->stream, s.other_dual, s.len,
+                       ctx->core_built[which], 1);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
@@ -1810,7 +1885,7 @@ int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const do
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep)
 {
     const int stride = (lines + MF_CORE_PROBES - 1) / MF_CORE_PROBES, probes = (lines + stride - 1) / stride;
-    launch_lists(ctx, s, lines, stride, 0, ctx->core_depth, nullptr, nullptr);
+    launch_lists(ctx, s, probes, stride, nullptr, 0, ctx->core_depth, nullptr, nullptr);
     MF_HIP(hipGetLastError());
     MF_HIP(hipMemcpyAsync(ctx->h_core_depth, ctx->core_depth, sizeof(double) * probes, hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
@@ -1877,7 +1952,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     CoreCtl *ctl = (CoreCtl *)ctx->core_ctl;
     hipLaunchKernelGGL(core_begin_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl, st->phase, phases);
     // one workgroup per compute unit of the device: those of one die stay
-    hipLaunchKernelGGL(core_kernel, dim3(ctx->n_cus), dim3(CORE_THREADS), 0, ctx->stream, a, ctl);
+    hipLaunchKernelGGL(plan.use_wide ? core_kernel<true> : core_kernel<false>, dim3(ctx->n_cus), dim3(CORE_THREADS), 0, ctx->stream, a, ctl);
     MF_HIP(hipGetLastError());
     MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));

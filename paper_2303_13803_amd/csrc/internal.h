@@ -243,6 +243,7 @@ struct mf_core_state {
     int launches, lists_made, sides_left;       // sides_left: finished on whole lines
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
+int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count, int which);
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep);
 int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st);
 size_t mf_core_ctl_bytes();

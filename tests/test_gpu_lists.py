@@ -123,6 +123,17 @@ def test_trees_of_a_search_get_their_labels_back(orc, n, m, high):
     assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P == expect
 
 
+@pytest.mark.parametrize("n,m,masked", [(1500, 1500, 0.0), (1300, 1400, 0.5), (1200, 1700, 0.2), (1601, 1205, 0.1)])
+def test_bidders_that_wait_for_better_lists(orc, n, m, masked):
+    """On all dies bidders whose lists have sunk wait until theirs alone are made again: every row ranks the columns
+    nearly alike, so that lists of several ages are in use on both sides and most of them sink."""
+    rng = np.random.default_rng(n + m)
+    W = (2 ** 20 - 400 * np.arange(m)[None, :] + rng.integers(0, 2000, (n, m))).astype(np.int32)
+    W[rng.random((n, m)) < masked] = INF
+    t = _solve(orc, W, {"core_depth": 0, "core_wide": 1, "core_narrow": 16, "core_many": 2})
+    assert t["lists_made"] > 4
+
+
 @pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
 def test_counters_of_a_solve_on_lists(n, m):
     """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
