@@ -128,7 +128,7 @@ typedef struct {
     int64_t path_steps;         /* super-steps of the shortest-augmenting-path searches */
     int64_t path_scans;         /* line scans of the searches and of proofs on lists (not in bids) */
     int32_t matched;            /* rows with a partner                                  */
-    int32_t phases;             /* epsilon-scaling phases                               */
+    int32_t phases;             /* epsilon-scaling phases (1 where there is no epsilon) */
     int32_t cert_ok;            /* 1: matching valid, duals feasible, 0 <= D - K*P < K  */
     int32_t status;             /* same code the call returned                          */
     float   ms_solve;           /* device time of the auction (HIP events)              */
@@ -305,7 +305,9 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *   "warm_reset_cols"  1 (default): such a start takes replaced columns at price 0
  *
  * TUNING (defaults were measured on the benchmark rounds; names and meanings may change with
- * the kernels they steer; every setting leaves the result exactly optimal):
+ * the kernels they steer; every setting leaves the result exactly optimal).  A context on which one of them, or of the
+ * options above other than "max_rounds", "score_split" and "fit_order", has been set matches with the kernels they
+ * steer at every size; any other matches up to about a hundred rows in one compute unit, which none of them concerns:
  *   phases   "phase_stop" (16) / "phase_keep" (4) / "phase_growth" (2): either side of a phase that
  *            only prepares prices ends once at most phase_stop bidders are unplaced (times
  *            phase_growth per phase before, while fewer than "phase_growth_rest" (32) bidders have

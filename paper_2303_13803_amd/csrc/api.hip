@@ -75,6 +75,57 @@ int finish_score_timing(mf_ctx *ctx)
     return MF_OK;
 }
 
+int set_option(mf_ctx *ctx, const char *name, int64_t value)
+{
+    if (!strcmp(name, "theta")) { if (value < 2 || value > 1024) return MF_ERR_ARG; ctx->theta = value; return MF_OK; }
+    if (!strcmp(name, "phase_keep")) { if (value < 1 || value > 64) return MF_ERR_ARG; ctx->phase_keep = (int)value; return MF_OK; }
+    if (!strcmp(name, "phase_tail_steps")) { if (value < 0) return MF_ERR_ARG; ctx->phase_tail_steps = value; return MF_OK; }
+    if (!strcmp(name, "phase_tail_from")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_tail_from = (int)value; return MF_OK; }
+    if (!strcmp(name, "phase_tail_sides")) { if (value < 0 || value > 3) return MF_ERR_ARG; ctx->phase_tail_sides = (int)value; return MF_OK; }
+    if (!strcmp(name, "final_jump")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->final_jump = value; return MF_OK; }
+    if (!strcmp(name, "phase_growth_rest")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_growth_rest = (int)value; return MF_OK; }
+    if (!strcmp(name, "phase_growth")) { if (value < 1 || value > 64) return MF_ERR_ARG; ctx->phase_growth = (int)value; return MF_OK; }
+    if (!strcmp(name, "phase_stop")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_stop = (int)value; return MF_OK; }
+    if (!strcmp(name, "score_split")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->score_split = (int)value; return MF_OK; }
+    if (!strcmp(name, "round_lag")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->round_lag = (int)value; return MF_OK; }
+    if (!strcmp(name, "tail_max")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->tail_max = (int)value; return MF_OK; }
+    if (!strcmp(name, "bulk_grid")) { if (value < 0 || value > 8192) return MF_ERR_ARG; ctx->bulk_grid = (int)value; return MF_OK; }
+    if (!strcmp(name, "bulk_share")) { if (value < 0 || value > 100) return MF_ERR_ARG; ctx->bulk_share = (int)value; return MF_OK; }
+    if (!strcmp(name, "bulk_shape")) { if (value < 0 || value > 4) return MF_ERR_ARG; ctx->bulk_shape = (int)value; return MF_OK; }
+    if (!strcmp(name, "warm_reset_cols")) { ctx->warm_reset_cols = value != 0; return MF_OK; }
+    if (!strcmp(name, "warm_eps_units")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->warm_eps_units = value; return MF_OK; }
+    if (!strcmp(name, "team_max")) { if (value < 0 || value > 16) return MF_ERR_ARG; ctx->team_max = (int)value; return MF_OK; }
+    if (!strcmp(name, "team_wide")) { if (value < 0 || value > 64) return MF_ERR_ARG; ctx->team_wide = (int)value; return MF_OK; }
+    if (!strcmp(name, "team_regroup")) { if (value < 1) return MF_ERR_ARG; ctx->team_regroup = value; return MF_OK; }
+    if (!strcmp(name, "team_size")) { if (value < 2 || value > 32) return MF_ERR_ARG; ctx->team_size = (int)value; return MF_OK; }
+    if (!strcmp(name, "team_threads")) { if (value != 64 && value != 128 && value != 256 && value != 512 && value != 1024) return MF_ERR_ARG; ctx->team_threads = (int)value; return MF_OK; }
+    if (!strcmp(name, "chain_grid")) { if (value < 1 || value > 4096) return MF_ERR_ARG; ctx->chain_grid = (int)value; return MF_OK; }
+    if (!strcmp(name, "path_max")) { if (value < 0 || value > 64) return MF_ERR_ARG; ctx->path_max = (int)value; return MF_OK; }
+    if (!strcmp(name, "path_spin_limit")) { if (value < 0 || value > (1ll << 30)) return MF_ERR_ARG; ctx->path_spin_limit = (unsigned)value; return MF_OK; }
+    if (!strcmp(name, "path_after")) { if (value < 0) return MF_ERR_ARG; ctx->path_after = value; return MF_OK; }
+    if (!strcmp(name, "path_grid")) { if (value < 0 || value > 1024) return MF_ERR_ARG; ctx->path_grid = (int)value; return MF_OK; }
+    if (!strcmp(name, "path_pull")) { ctx->path_pull = value != 0; return MF_OK; }
+    if (!strcmp(name, "path_frontier_rows")) { if (value < 8 || value > (1 << 20)) return MF_ERR_ARG; ctx->path_frontier_rows = (int)value; return MF_OK; }
+    if (!strcmp(name, "path_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->path_width = (int)value; return MF_OK; }
+    if (!strcmp(name, "core")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->core = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_depth")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_depth_eps = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_many")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_many = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_width = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_wide")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_wide = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_narrow")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_narrow = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_read")) { if (value < 0 || value > 100) return MF_ERR_ARG; ctx->core_read = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_read_least")) { if (value < 0 || value > (1ll << 40)) return MF_ERR_ARG; ctx->core_read_least = value; return MF_OK; }
+    if (!strcmp(name, "core_few")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_few = (int)value; return MF_OK; }
+    if (!strcmp(name, "core_after")) { if (value < 0) return MF_ERR_ARG; ctx->core_after = value; return MF_OK; }
+    if (!strcmp(name, "core_refine")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_refine = (int)value; return MF_OK; }
+    if (!strcmp(name, "edge_lists_from")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->edge_lists_from = (int)value; return MF_OK; }
+    if (!strcmp(name, "fit_prefix_below")) { if (value < 0 || value > 101) return MF_ERR_ARG; ctx->fit_prefix_below = (int)value; return MF_OK; }
+    if (!strcmp(name, "fit_prefix")) { ctx->fit_prefix = value != 0; return MF_OK; }
+    if (!strcmp(name, "fit_order")) { ctx->fit_order = value != 0; return MF_OK; }
+    if (!strcmp(name, "max_rounds")) { if (value < 1) return MF_ERR_ARG; ctx->max_rounds = value; return MF_OK; }
+    return MF_ERR_ARG;
+}
+
 }  // namespace
 
 extern "C" {
@@ -295,7 +346,7 @@ int mf_check_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t 
     clear_timings(ctx);
     memset(h_res, 0, sizeof(*h_res));
     MF_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
-    rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res);
+    rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
     if (rc == MF_OK) {
         MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
         MF_HIP(hipStreamSynchronize(ctx->stream));
@@ -396,53 +447,9 @@ int mf_schedule_round_update(mf_ctx *ctx, const mf_predictor *pred, const float 
 int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
 {
     if (!ctx || !name) return MF_ERR_ARG;
-    if (!strcmp(name, "theta")) { if (value < 2 || value > 1024) return MF_ERR_ARG; ctx->theta = value; return MF_OK; }
-    if (!strcmp(name, "phase_keep")) { if (value < 1 || value > 64) return MF_ERR_ARG; ctx->phase_keep = (int)value; return MF_OK; }
-    if (!strcmp(name, "phase_tail_steps")) { if (value < 0) return MF_ERR_ARG; ctx->phase_tail_steps = value; return MF_OK; }
-    if (!strcmp(name, "phase_tail_from")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_tail_from = (int)value; return MF_OK; }
-    if (!strcmp(name, "phase_tail_sides")) { if (value < 0 || value > 3) return MF_ERR_ARG; ctx->phase_tail_sides = (int)value; return MF_OK; }
-    if (!strcmp(name, "final_jump")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->final_jump = value; return MF_OK; }
-    if (!strcmp(name, "phase_growth_rest")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_growth_rest = (int)value; return MF_OK; }
-    if (!strcmp(name, "phase_growth")) { if (value < 1 || value > 64) return MF_ERR_ARG; ctx->phase_growth = (int)value; return MF_OK; }
-    if (!strcmp(name, "phase_stop")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->phase_stop = (int)value; return MF_OK; }
-    if (!strcmp(name, "score_split")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->score_split = (int)value; return MF_OK; }
-    if (!strcmp(name, "round_lag")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->round_lag = (int)value; return MF_OK; }
-    if (!strcmp(name, "tail_max")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->tail_max = (int)value; return MF_OK; }
-    if (!strcmp(name, "bulk_grid")) { if (value < 0 || value > 8192) return MF_ERR_ARG; ctx->bulk_grid = (int)value; return MF_OK; }
-    if (!strcmp(name, "bulk_share")) { if (value < 0 || value > 100) return MF_ERR_ARG; ctx->bulk_share = (int)value; return MF_OK; }
-    if (!strcmp(name, "bulk_shape")) { if (value < 0 || value > 4) return MF_ERR_ARG; ctx->bulk_shape = (int)value; return MF_OK; }
-    if (!strcmp(name, "warm_reset_cols")) { ctx->warm_reset_cols = value != 0; return MF_OK; }
-    if (!strcmp(name, "warm_eps_units")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->warm_eps_units = value; return MF_OK; }
-    if (!strcmp(name, "team_max")) { if (value < 0 || value > 16) return MF_ERR_ARG; ctx->team_max = (int)value; return MF_OK; }
-    if (!strcmp(name, "team_wide")) { if (value < 0 || value > 64) return MF_ERR_ARG; ctx->team_wide = (int)value; return MF_OK; }
-    if (!strcmp(name, "team_regroup")) { if (value < 1) return MF_ERR_ARG; ctx->team_regroup = value; return MF_OK; }
-    if (!strcmp(name, "team_size")) { if (value < 2 || value > 32) return MF_ERR_ARG; ctx->team_size = (int)value; return MF_OK; }
-    if (!strcmp(name, "team_threads")) { if (value != 64 && value != 128 && value != 256 && value != 512 && value != 1024) return MF_ERR_ARG; ctx->team_threads = (int)value; return MF_OK; }
-    if (!strcmp(name, "chain_grid")) { if (value < 1 || value > 4096) return MF_ERR_ARG; ctx->chain_grid = (int)value; return MF_OK; }
-    if (!strcmp(name, "path_max")) { if (value < 0 || value > 64) return MF_ERR_ARG; ctx->path_max = (int)value; return MF_OK; }
-    if (!strcmp(name, "path_spin_limit")) { if (value < 0 || value > (1ll << 30)) return MF_ERR_ARG; ctx->path_spin_limit = (unsigned)value; return MF_OK; }
-    if (!strcmp(name, "path_after")) { if (value < 0) return MF_ERR_ARG; ctx->path_after = value; return MF_OK; }
-    if (!strcmp(name, "path_grid")) { if (value < 0 || value > 1024) return MF_ERR_ARG; ctx->path_grid = (int)value; return MF_OK; }
-    if (!strcmp(name, "path_pull")) { ctx->path_pull = value != 0; return MF_OK; }
-    if (!strcmp(name, "path_frontier_rows")) { if (value < 8 || value > (1 << 20)) return MF_ERR_ARG; ctx->path_frontier_rows = (int)value; return MF_OK; }
-    if (!strcmp(name, "path_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->path_width = (int)value; return MF_OK; }
-    if (!strcmp(name, "core")) { if (value < 0 || value > 1) return MF_ERR_ARG; ctx->core = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_depth")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_depth_eps = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_many")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_many = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_width")) { if (value < 1 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_width = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_wide")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_wide = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_narrow")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_narrow = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_read")) { if (value < 0 || value > 100) return MF_ERR_ARG; ctx->core_read = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_read_least")) { if (value < 0 || value > (1ll << 40)) return MF_ERR_ARG; ctx->core_read_least = value; return MF_OK; }
-    if (!strcmp(name, "core_few")) { if (value < 1 || value > (1 << 20)) return MF_ERR_ARG; ctx->core_few = (int)value; return MF_OK; }
-    if (!strcmp(name, "core_after")) { if (value < 0) return MF_ERR_ARG; ctx->core_after = value; return MF_OK; }
-    if (!strcmp(name, "core_refine")) { if (value < 0 || value > (1 << 30)) return MF_ERR_ARG; ctx->core_refine = (int)value; return MF_OK; }
-    if (!strcmp(name, "edge_lists_from")) { if (value < 0 || value > (1 << 20)) return MF_ERR_ARG; ctx->edge_lists_from = (int)value; return MF_OK; }
-    if (!strcmp(name, "fit_prefix_below")) { if (value < 0 || value > 101) return MF_ERR_ARG; ctx->fit_prefix_below = (int)value; return MF_OK; }
-    if (!strcmp(name, "fit_prefix")) { ctx->fit_prefix = value != 0; return MF_OK; }
-    if (!strcmp(name, "fit_order")) { ctx->fit_order = value != 0; return MF_OK; }
-    if (!strcmp(name, "max_rounds")) { if (value < 1) return MF_ERR_ARG; ctx->max_rounds = value; return MF_OK; }
-    return MF_ERR_ARG;
+    const int rc = set_option(ctx, name, value);
+    if (rc == MF_OK && strcmp(name, "max_rounds") && strcmp(name, "score_split") && strcmp(name, "fit_order")) ctx->as_told = true;
+    return rc;
 }
 
 int mf_last_timings(mf_ctx *ctx, float what[16])

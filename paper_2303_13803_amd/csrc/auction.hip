@@ -857,6 +857,33 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
     }
 }
 
+// A problem that one compute unit holds (small.hip), from the caller's matrix.  *general: its weights are too large for that.
+int run_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_t *d_row2col, int64_t *d_u, int64_t *d_v, mf_result *h_res,
+              bool *general)
+{
+    MF_HIP(hipEventRecord(ctx->ev[3], ctx->stream));
+    int rc = mf_launch_small(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v);
+    if (rc != MF_OK) return rc;
+    MF_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
+    rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, (int64_t)n + 1, h_res, true);
+    if (rc != MF_OK) return rc;
+    const mf_cert_out &c = *ctx->h_cert;
+    *general = c.status == MF_SMALL_GENERAL;
+    if (c.status != MF_OK) return c.status;
+    MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
+    MF_HIP(hipStreamSynchronize(ctx->stream));
+    MF_HIP(hipEventElapsedTime(&ctx->timings[T_SOLVE], ctx->ev[3], ctx->ev[4]));
+    MF_HIP(hipEventElapsedTime(&ctx->timings[T_CERT], ctx->ev[4], ctx->ev[6]));
+    h_res->bids = h_res->chain_bids = c.bids;
+    h_res->path_steps = h_res->path_scans = c.scans;
+    h_res->chain_depth = (int64_t)c.bids + c.scans;
+    h_res->bytes_scanned = 4ll * n * m;               // read once, into LDS
+    h_res->phases = 1;
+    h_res->ms_solve = ctx->timings[T_SOLVE];
+    h_res->ms_certify = ctx->timings[T_CERT];
+    return h_res->cert_ok ? MF_OK : MF_ERR_CERT;
+}
+
 }  // namespace
 
 // `warm`: start from the prices the previous solve of the same shape left in
@@ -878,6 +905,12 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     const bool flip = n > m;
     warm = warm && !flip && !candidate && ctx->warm_n == n && ctx->warm_m == m;
     ctx->warm_n = ctx->warm_m = 0;
+    if (!ctx->as_told && mf_small_fits(n, m)) {
+        bool general = false;
+        const int rc = run_small(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, &general);
+        if (!general) return rc;
+        *h_res = mf_result{};
+    }
     const int64_t ldt = ((int64_t)n + 3) & ~3ll;
     const int rn = flip ? m : n, rm = flip ? n : m;
     const long long K = (long long)rn + 1;
@@ -1077,7 +1110,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     }
     MF_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
     MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
-    int rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res);
+    int rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
     if (rc != MF_OK) return rc;
     MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));

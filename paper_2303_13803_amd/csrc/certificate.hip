@@ -186,10 +186,12 @@ __global__ void init_cert_kernel(mf_cert_out *out)
 
 int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
                        const int32_t *d_row2col, const int64_t *d_u, const int64_t *d_v,
-                       int64_t K, mf_result *h_res)
+                       int64_t K, mf_result *h_res, bool begun)
 {
-    hipLaunchKernelGGL(init_cert_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->cert);
-    hipLaunchKernelGGL(fill_int_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->colmark, m, 0);
+    if (!begun) {
+        hipLaunchKernelGGL(init_cert_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->cert);
+        hipLaunchKernelGGL(fill_int_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->colmark, m, 0);
+    }
     const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
     hipLaunchKernelGGL(K >= INT32_MIN && K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>,
                        dim3(grid), dim3(BID_THREADS), 0, ctx->stream, d_W, ldw, n, m,

@@ -67,6 +67,7 @@ struct mf_cert_out {                // lives in device memory, cleared per check
     long long min_rc;
     int matched;
     int flags;                      // bit0 bad index/duplicate, bit1 infeasible pair, bit2 negative dual
+    int bids, scans, status;        // of a matching by small_kernel, which begins the check in the same launch
 };
 
 struct mf_ctx {
@@ -174,6 +175,7 @@ struct mf_ctx {
     mf_cert_out *h_cert;
     // options
     int64_t theta, max_rounds;
+    bool as_told;                   // an option says how to match: small problems are then matched that way too
     // timing
     hipEvent_t ev[10];              // 0..2 and 8: scoring stages; 3..7: solver stages
     float timings[T_COUNT];
@@ -252,4 +254,8 @@ int mf_extract_duals(mf_ctx *ctx, const int32_t *A, int64_t lda, int rn, int rm,
                      int n, bool flip, bool staged, int32_t *d_row2col, int64_t *d_u, int64_t *d_v);
 int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
                        const int32_t *d_row2col, const int64_t *d_u, const int64_t *d_v,
-                       int64_t K, mf_result *h_res);
+                       int64_t K, mf_result *h_res, bool begun);        // begun: ctx->cert and ctx->colmark are cleared
+// small.hip
+enum { MF_SMALL_GENERAL = 1 };           // status: left to the auction
+bool mf_small_fits(int n, int m);
+int mf_launch_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_t *d_row2col, int64_t *d_u, int64_t *d_v);

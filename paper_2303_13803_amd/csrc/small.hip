@@ -1,0 +1,296 @@
+// The matching of problems of up to about a hundred rows, whose whole matrix fits into one compute unit's LDS (the
+// paper's GetMatching on a handful of GPUs: Section "Matching-based scheduling").
+//
+// The auction's phases are made for matrices that many workgroups read at once; on 64 x 64 they are two dozen
+// launches and 1 us for every bid of a chain, which goes through the L2 four times.  Here one workgroup puts the
+// matrix into LDS and one wavefront of it solves: prices, holders and labels sit in registers, a lane having C
+// neighbouring columns; a bid or a scanned row of a search is one read of LDS and a reduction or two over the
+// wavefront.  All of it is exact in whole weight units, so there is no epsilon and no ladder:
+//   bids      a row takes its best column and raises its price by what it prefers it to its second best (or to
+//             none at all); whoever held it goes on.  A row whose best column is held and not preferred waits.
+//   searches  each row that waits is placed by one shortest augmenting path (Dijkstra over columns, a label per
+//             column), which may end at a free column or leave the row on it with the least to lose unmatched.
+// Throughout, held pairs are tight, no pair of a placed or given-up row is worth more than its duals, and a
+// column that nobody holds has price 0: in the end the duals prove the matching, with no gap.
+#include "scan.h"
+
+namespace {
+
+constexpr int SMALL_THREADS = 1024;         // one of the 16 wavefronts solves, all of them fetch the matrix
+constexpr int SMALL_FETCH = 8;                  // rows a wavefront has on their way at once
+constexpr int SMALL_COLS = 512;                 // eight columns a lane
+constexpr int SMALL_LDS = 152 * 1024;           // (of 160 KB)
+// Rows: the searches scan up to half as many rows as there are, one after the other, where the auction's bidders go on side
+// by side.  Rounds of scored pairs, whose rows prefer nearly the same columns, auction / this, ms: 64 x 64 0.51..0.78 /
+// 0.27, 72 x 72 0.62 / 0.51, 80 x 80 0.67 / 0.61, 96 x 96 0.71 / 0.77, 128 x 128 0.87 / 1.25; with more columns
+// than rows there is less to search: 64 x 150 0.76 / 0.37, 96 x 130 1.15 / 0.82, 104 x 160 0.92 / 0.82, 112 x 200 0.94 /
+// 0.85, 112 x 300 0.87 / 0.96.  Other matrices gain at any of these sizes (uniform weights, 100 x 100 0.36 / 0.19; products of
+// a row and a column, the longest searches there are, 64 x 64 1.6 / 0.59, 100 x 300 3.6 / 2.7).
+// More rows than columns are left to the auction: such a solve is promised to run on lists, one read and counted for every bid.
+constexpr int SMALL_ROWS = 80, SMALL_ROWS_WIDE = 104;       // ... the latter with a third more columns than rows
+constexpr int SMALL_BIDS = 4;                   // bids in the first part, per row
+constexpr int SMALL_WEIGHTS = 1 << 28;          // weights below it: twice every sum below then stays within 32 bits
+
+struct SmallShape {
+    int n, m, pitch;                            // rows n <= columns m; entries from a row to the next in LDS
+    long long ldw;
+};
+
+// A lane holds the columns lane * C ... lane * C + C - 1.
+template <int C>
+__device__ __forceinline__ void set_column(int (&x)[C], int k, int value, int lane)
+{
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (k == lane * C + c) x[c] = value;
+}
+
+// The largest of x over the wavefront, where it is, and what y is there.  (One ballot and two moves from a lane to a
+// scalar, whatever C: each lane first picks among its own.)
+struct Pick { int value, column, other; };
+template <int C>
+__device__ __forceinline__ Pick pick(const int (&x)[C], const int (&y)[C], int lane)
+{
+    int best = x[0], which = lane * C, mine = y[0];
+#pragma unroll
+    for (int c = 1; c < C; ++c) {
+        const int take = x[c] > best ? -1 : 0, there = y[c];       // (selected by bits: a choice between entries of an array ends up in memory)
+        best = max(best, x[c]);
+        which = ((lane * C + c) & take) | (which & ~take);
+        mine = (there & take) | (mine & ~take);
+    }
+    Pick p;
+    p.value = wave_max(best);
+    const int src = __builtin_ctzll(__ballot(best == p.value));
+    p.column = C == 1 ? src : __builtin_amdgcn_readlane(which, src);
+    p.other = __builtin_amdgcn_readlane(mine, src);
+    return p;
+}
+
+template <int C>
+__device__ __forceinline__ int largest_of(const int (&x)[C])
+{
+    int b = x[0];
+#pragma unroll
+    for (int c = 1; c < C; ++c) b = max(b, x[c]);
+    return wave_max(b);
+}
+
+// What bounds it: one chain of dependent bids and scans (0.20 us a scan with one column a lane, 0.31 with four, 0.43 with
+// eight: a third of it the reduction, a quarter LDS) and 6 us for the launch and the matrix's way into one compute
+// unit.  64 x 64 of scored pairs: about 290 bids and 860 scans, 230 us, of which the auction's launches took 565.
+// Weights, prices, profits and labels are held doubled, and the price of a column that somebody holds is odd: of
+// equally good columns the maximum then is one that nobody holds.
+// Prices and profits are at most the largest weight (a price never exceeds the weight of the pair that holds it), which
+// is below 2^28; a path is never longer than what its start would get; an infeasible pair's weight is taken as -2^28,
+// farther than any path, and the doubled sums stay within 32 bits.
+template <int C>
+__global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__restrict__ W, SmallShape s, long long K, int limit,
+                                                              int32_t *__restrict__ out_row2col, int64_t *__restrict__ out_u,
+                                                              int64_t *__restrict__ out_v, int *__restrict__ colmark,
+                                                              mf_cert_out *__restrict__ out)
+{
+    extern __shared__ __align__(32) int lds[];
+    // Rows of LDS: the weights of row r (negative: infeasible), its profit and the column it holds, from r * pitch on, which is
+    // what names a row below; then zeros for the last lanes to read on into, the rows that wait, the prices.
+    int *const weight = lds, *const profit = lds + s.pitch - 2, *const held = lds + s.pitch - 1;
+    int *const waits = lds + s.n * s.pitch + 64 * C, *const price_out = waits + s.n;
+    __shared__ int largest;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0) largest = 0;
+    __syncthreads();
+    {
+        int most = 0;
+        for (int j = lane; j < s.m; j += 64)
+            for (int i0 = wave; i0 < s.n; i0 += SMALL_FETCH * (SMALL_THREADS / 64)) {
+                int w[SMALL_FETCH];
+#pragma unroll
+                for (int q = 0; q < SMALL_FETCH; ++q)
+                    w[q] = W[(size_t)min(i0 + q * (SMALL_THREADS / 64), s.n - 1) * s.ldw + j];
+#pragma unroll
+                for (int q = 0; q < SMALL_FETCH; ++q) {
+                    const int i = i0 + q * (SMALL_THREADS / 64);
+                    if (i >= s.n) break;
+                    most = max(most, w[q]);
+                    weight[i * s.pitch + j] = 2 * (w[q] < 0 || w[q] >= SMALL_WEIGHTS ? -SMALL_WEIGHTS : w[q]);
+                }
+            }
+        most = wave_max(most);
+        if (lane == 0) atomicMax(&largest, most);
+        for (int j = threadIdx.x; j < s.m; j += SMALL_THREADS) colmark[j] = 0;
+        for (int k = threadIdx.x; k < 64 * C; k += SMALL_THREADS) weight[s.n * s.pitch + k] = 0;
+        for (int i = threadIdx.x; i < s.n; i += SMALL_THREADS) {
+            for (int j = s.m; j < s.pitch - 2; ++j) weight[i * s.pitch + j] = 0;
+            held[i * s.pitch] = -1;
+            profit[i * s.pitch] = 0;
+        }
+        for (int j = threadIdx.x; j < s.m; j += SMALL_THREADS) price_out[j] = 0;
+        if (threadIdx.x == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
+    }
+    __syncthreads();
+    const bool general = largest >= SMALL_WEIGHTS || K * (long long)largest >= MF_MAX_DUAL;
+    if (wave == 0) {
+        int bids = 0, scans = 0;
+        bool over = false;
+        if (!general) {
+            // (lanes without a column read on into the next row, at a price that nobody pays)
+            int price[C], holder[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) { price[c] = lane * C + c < s.m ? 0 : 2 * SMALL_WEIGHTS; holder[c] = -1; }
+            // what row r would have left of each column's weight at the prices
+            int left[C];
+            auto look = [&](int r) {
+                typedef int Columns __attribute__((ext_vector_type(C)));
+                const Columns w = *(const Columns *)(weight + r + lane * C);
+#pragma unroll
+                for (int c = 0; c < C; ++c) left[c] = w[c] - price[c];
+            };
+            auto even = [](int x) { return (x + 1) & ~1; };
+
+            int waiting = 0;
+            for (int row = 0; row < s.n; ++row) {
+                if (bids >= limit) { over = true; break; }
+                int r = row * s.pitch;
+                for (;;) {
+                    bids += 1;
+                    look(r);
+                    const Pick p = pick<C>(left, holder, lane);
+                    const int best = even(p.value), before = p.other;
+                    if (best <= 0) { held[r] = -1; profit[r] = 0; break; }         // for good: prices only rise
+                    set_column<C>(left, p.column, -2 * SMALL_WEIGHTS, lane);
+                    const int second = even(max(largest_of<C>(left), 0));
+                    if (before >= 0 && (second == best || bids >= SMALL_BIDS * s.n)) { waits[waiting++] = r; break; }
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (p.column == lane * C + c) { price[c] = (price[c] + best - second) | 1; holder[c] = r; }
+                    held[r] = p.column;
+                    profit[r] = second;
+                    if (before < 0) break;
+                    held[before] = -1;
+                    r = before;
+                }
+            }
+
+            for (int q = 0; q < waiting && !over; ++q) {
+                const int start = __builtin_amdgcn_readfirstlane(waits[q]);
+                // minus the length of the shortest path known, the row it comes from, and what it is worth to go there
+                // (the lowest integer once it has been)
+                int label[C], from[C], cap[C], open[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) { label[c] = INT32_MIN; from[c] = -1; cap[c] = lane * C + c < s.m ? INT32_MAX : INT32_MIN; }
+                look(start);
+                const int all = even(max(largest_of<C>(left), 0));
+                int end = all, end_row = start, end_col = -1;      // the path that ends first: leave end_row unmatched
+                int r = start, base = all;
+                Pick p;
+                for (;;) {                                         // (a column more is scanned each time)
+                    scans += 1;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const int by_r = left[c] - base;            // (never above the label of a scanned column)
+                        from[c] = by_r > label[c] ? r : from[c];
+                        label[c] = max(label[c], by_r);
+                        open[c] = min(label[c], cap[c]);
+                    }
+                    p = pick<C>(open, holder, lane);
+                    if (min(p.value + (end - 1), p.other) < 0) break;       // the path known ends first, or a column that nobody holds
+                    r = p.other;
+                    look(r);
+                    const int worth = __builtin_amdgcn_readfirstlane(profit[r]);
+                    set_column<C>(cap, p.column, INT32_MIN, lane);
+                    base = worth - even(p.value);
+                    end_row = base < end ? r : end_row;
+                    end = min(base, end);
+                }
+                if (p.value > -end) { end = -p.value; end_col = p.column; }
+                over = bids + scans >= limit;
+                // the new duals: what was nearer than the path's end gives up the difference
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (cap[c] == INT32_MIN && lane * C + c < s.m) {
+                        const int give = end + even(label[c]);
+                        if (give > 0) { price[c] += give; profit[holder[c]] -= give; }
+                    }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                profit[start] = all - end;
+                // and the path: columns change hands back to the start
+                int k = end_col;
+                if (k < 0) {
+                    k = __builtin_amdgcn_readfirstlane(held[end_row]);
+                    held[end_row] = -1;
+                }
+                for (int hop = 0; k >= 0 && hop < s.n; ++hop) {       // (the start holds nothing)
+                    int mine = 0;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) mine |= from[c] & (k % C == c ? -1 : 0);
+                    const int to = __builtin_amdgcn_readlane(mine, k / C);
+                    const int next = __builtin_amdgcn_readfirstlane(held[to]);
+                    held[to] = k;
+                    set_column<C>(holder, k, to, lane);
+                    k = next;
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (lane * C + c < s.m) price_out[lane * C + c] = price[c];
+        }
+        if (lane == 0) {
+            out->bids = bids; out->scans = scans;
+            out->status = general ? MF_SMALL_GENERAL : (over ? MF_ERR_NOT_CONVERGED : MF_OK);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < s.n; i += SMALL_THREADS) {
+        out_u[i] = K * (long long)(profit[i * s.pitch] >> 1);
+        out_row2col[i] = held[i * s.pitch];
+    }
+    for (int j = threadIdx.x; j < s.m; j += SMALL_THREADS) out_v[j] = K * (long long)(price_out[j] >> 1);
+}
+
+SmallShape small_shape(int n, int m, int64_t ldw, int *columns)
+{
+    *columns = m <= 64 ? 1 : (m <= 128 ? 2 : (m <= 256 ? 4 : 8));
+    return SmallShape{n, m, (m + 2 + *columns - 1) / *columns * *columns, (long long)ldw};       // (whole loads)
+}
+
+size_t small_bytes(const SmallShape &s, int columns)
+{
+    return sizeof(int) * ((size_t)s.n * (size_t)s.pitch + 64 * (size_t)columns + (size_t)s.n + (size_t)s.m);
+}
+
+template <int C>
+int launch_small(mf_ctx *ctx, const SmallShape &s, const int32_t *d_W, long long K, int32_t *d_row2col, int64_t *d_u, int64_t *d_v)
+{
+    static_assert(SMALL_COLS == 64 * 8, "the widest instance");
+    const unsigned flag = 1u << (C == 1 ? 21 : (C == 2 ? 22 : (C == 4 ? 23 : 24)));
+    if (!(ctx->kernels_configured & flag)) {
+        MF_HIP(hipFuncSetAttribute((const void *)small_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, SMALL_LDS));
+        ctx->kernels_configured |= flag;
+    }
+    hipLaunchKernelGGL((small_kernel<C>), dim3(1), dim3(SMALL_THREADS), small_bytes(s, C), ctx->stream, d_W, s, K,
+                       (int)(ctx->max_rounds < INT32_MAX ? ctx->max_rounds : INT32_MAX), d_row2col, d_u, d_v, ctx->colmark, ctx->cert);
+    MF_HIP(hipGetLastError());
+    return MF_OK;
+}
+
+}  // namespace
+
+bool mf_small_fits(int n, int m)
+{
+    int columns = 0;
+    const SmallShape s = small_shape(n, m, 0, &columns);
+    const bool few = s.n <= SMALL_ROWS || (s.n <= SMALL_ROWS_WIDE && 3 * s.m >= 4 * s.n);
+    return n <= m && few && s.m <= SMALL_COLS && small_bytes(s, columns) <= (size_t)SMALL_LDS;
+}
+
+// Leaves row2col, u, v with the caller and ctx->cert and ctx->colmark ready for the certificate.
+int mf_launch_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_t *d_row2col, int64_t *d_u, int64_t *d_v)
+{
+    int columns = 0;
+    const SmallShape s = small_shape(n, m, ldw, &columns);
+    const long long K = (long long)n + 1;
+    if (columns == 1) return launch_small<1>(ctx, s, d_W, K, d_row2col, d_u, d_v);
+    if (columns == 2) return launch_small<2>(ctx, s, d_W, K, d_row2col, d_u, d_v);
+    if (columns == 4) return launch_small<4>(ctx, s, d_W, K, d_row2col, d_u, d_v);
+    return launch_small<8>(ctx, s, d_W, K, d_row2col, d_u, d_v);
+}

@@ -1,0 +1,76 @@
+"""Problems matched in one compute unit (GPU): against the oracle and against the auction, which a context with a
+tuning option set (to its default here) uses at every size."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import padded_matrix
+
+pytestmark = pytest.mark.gpu
+
+INF = np.iinfo(np.int32).min
+
+
+def _solve(orc, W, options):
+    import paper_2303_13803_amd as mm
+    n, m = W.shape
+    ctx = mm.Context(n, m)
+    for name, value in options.items():
+        ctx.set_option(name, value)
+    r2c = torch.full((n,), 7, dtype=torch.int32, device="cuda")
+    u, v = torch.full((n,), -7, dtype=torch.int64, device="cuda"), torch.full((m,), -7, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    did = ctx.last_timings()
+    ctx.close()
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.primal == P
+    return res, did
+
+
+def _kinds(n, m):
+    yield "uniform", synth.uniform_matrix(81, n, m, 2 ** 24, 0.1)
+    yield "ties", synth.uniform_matrix(82, n, m, 3, 0.3)
+    yield "few pairs", synth.uniform_matrix(83, n, m, 1000, 0.95)
+    yield "product", (np.arange(1, n + 1)[:, None] * np.arange(1, m + 1)[None]).astype(np.int32)
+    yield "one value", np.full((n, m), 77, np.int32)
+    yield "nothing feasible", np.full((n, m), INF, np.int32)
+    W = synth.uniform_matrix(84, n, m, 2 ** 20, 0.2)
+    W[::3] = np.where(W[::3] == INF, INF, 0)                # worth nothing, and below that
+    W[:, ::5] = np.where(W[:, ::5] == INF, INF, -W[:, ::5])
+    yield "zero and negative", W
+
+
+# one column a lane and its last lane, two, four and eight; pitches that are and are not whole loads; the most rows, and
+# the first sizes that are left to the auction (more rows than columns always are)
+@pytest.mark.parametrize("n,m", [(1, 1), (1, 512), (2, 513), (3, 2), (30, 30), (63, 64), (64, 65), (80, 80), (81, 82), (97, 127), (96, 128),
+                                 (104, 139), (104, 256), (105, 141), (60, 257), (70, 512), (75, 512)])
+def test_one_compute_unit_finds_the_optimum(orc, n, m):
+    for name, W in _kinds(n, m):
+        res, did = _solve(orc, W, {})
+        other, _ = _solve(orc, W, {"theta": 24})
+        assert res.primal == other.primal, name
+        here = n <= m <= 512 and n <= 104 and (n <= 80 or 3 * m >= 4 * n) and n * m < 38000         # 152 KB of LDS
+        assert (res.rounds == 0 and did["list_launches"] == 0) == here, name
+        assert not here or res.bytes_scanned == 4 * n * m and res.phases == 1, name
+
+
+@pytest.mark.parametrize("largest", [2 ** 28 - 1, 2 ** 28, 2 ** 31 - 1])
+def test_weights_at_the_edge_of_its_integers(orc, largest):
+    W = (largest - synth.uniform_matrix(85, 50, 60, 1000, 0.0)).astype(np.int32)
+    W[0, 0], W[3] = largest, INF
+    res, _ = _solve(orc, W, {})
+    assert res.primal == orc.max_weight_matching(W)[0]
+    assert (res.bytes_scanned == 4 * W.size) == (largest < 2 ** 28)     # larger ones are left to the auction
+
+
+def test_it_stops_at_the_limit_on_bids(orc):
+    import paper_2303_13803_amd as mm
+    W = (np.arange(1, 61)[:, None] * np.arange(1, 61)[None]).astype(np.int32)
+    res, _ = _solve(orc, W, {})
+    steps = res.bids + res.path_scans
+    assert _solve(orc, W, {"max_rounds": steps + 1})[0].primal == res.primal
+    for limit in (1, res.bids + 1, steps // 2):
+        with pytest.raises(mm.MuxmatchError) as e:
+            _solve(orc, W, {"max_rounds": limit})
+        assert e.value.code == mm.ERR_NOT_CONVERGED
