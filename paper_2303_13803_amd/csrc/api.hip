@@ -58,11 +58,14 @@ void clear_timings(mf_ctx *ctx)
     ctx->score_pending = false;
 }
 
-int finish_score_timing(mf_ctx *ctx)
+// (after a certificate the count of pairs has come along with it)
+int finish_score_timing(mf_ctx *ctx, bool counted)
 {
-    MF_HIP(hipMemcpyAsync(ctx->h_pairs_evaluated, ctx->pairs_evaluated, sizeof(unsigned long long),
-                          hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
+    if (!counted) {
+        MF_HIP(hipMemcpyAsync(ctx->h_pairs_evaluated, ctx->pairs_evaluated, sizeof(unsigned long long),
+                              hipMemcpyDeviceToHost, ctx->stream));
+        MF_HIP(hipStreamSynchronize(ctx->stream));
+    }
     float a = 0.0f, b = 0.0f;
     float c = 0.0f;
     MF_HIP(hipEventElapsedTime(&a, ctx->ev[0], ctx->ev[1]));
@@ -348,8 +351,6 @@ int mf_check_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t 
     MF_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
     rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
     if (rc == MF_OK) {
-        MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
-        MF_HIP(hipStreamSynchronize(ctx->stream));
         MF_HIP(hipEventElapsedTime(&ctx->timings[T_CERT], ctx->ev[5], ctx->ev[6]));
         h_res->ms_certify = ctx->timings[T_CERT];
     }
@@ -372,7 +373,7 @@ int mf_schedule_round(mf_ctx *ctx, const mf_predictor *pred, const float *d_on, 
     rc = mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, nullptr);
     if (rc == MF_OK) rc = mf_run_solver(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, false, nullptr, 0, true);
     if (rc == MF_OK || rc == MF_ERR_CERT) {
-        int rt = finish_score_timing(ctx);
+        int rt = finish_score_timing(ctx, true);
         if (rt != MF_OK) rc = rt;
     }
     h_res->status = rc;
@@ -407,7 +408,7 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
     rc = mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, nullptr);
     if (rc == MF_OK) rc = mf_run_solver(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, false, nullptr, 0, true);
     if (rc == MF_OK || rc == MF_ERR_CERT) {
-        int rt = finish_score_timing(ctx);
+        int rt = finish_score_timing(ctx, true);
         if (rt != MF_OK) rc = rt;
     }
     h_res->status = rc;
@@ -437,7 +438,7 @@ int mf_schedule_round_update(mf_ctx *ctx, const mf_predictor *pred, const float 
         rc = mf_run_solver(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, ctx->warm_eps_units > 0, d_changed_off,
                            ctx->warm_reset_cols ? n_changed_off : 0, false);
     if (rc == MF_OK || rc == MF_ERR_CERT) {
-        int rt = finish_score_timing(ctx);
+        int rt = finish_score_timing(ctx, true);
         if (rt != MF_OK) rc = rt;
     }
     h_res->status = rc;
@@ -456,7 +457,7 @@ int mf_last_timings(mf_ctx *ctx, float what[16])
 {
     if (!ctx || !what) return MF_ERR_ARG;
     if (ctx->score_pending) {           // a bare mf_score_pairs does not wait for its events
-        int rc = finish_score_timing(ctx);
+        int rc = finish_score_timing(ctx, false);
         if (rc != MF_OK) return rc;
     }
     memcpy(what, ctx->timings, sizeof(float) * 16);

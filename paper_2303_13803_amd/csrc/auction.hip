@@ -522,7 +522,6 @@ __global__ void set_count_kernel(mf_device_stats *stats, int count)
 {
     stats->cnt[0] = count; stats->cnt[1] = 0; stats->cnt[2] = 0; stats->cnt[3] = 0;
 }
-__global__ void known_weight_kernel(const int *largest, mf_device_stats *stats) { stats->max_weight = *largest; }
 __global__ void fill_counter_kernel(unsigned long long *counter) { *counter = 0ull; }
 
 // The largest weight alone (it sets the first epsilon), for solves that may never need W^T.
@@ -550,15 +549,17 @@ __global__ void zero_listed_kernel(double *price, const int32_t *__restrict__ wh
     if (i < count && which[i] >= 0 && which[i] < m) price[which[i]] = 0.0;
 }
 
+// known, known_pairs (or null): largest weight and feasible pairs of the matrix, noted while it was scored
 __global__ void init_solver_kernel(int n, int m, double *price, double *profit, mf_device_stats *stats,
-                                   int keep_prices)
+                                   int keep_prices, const int *known, const unsigned long long *known_pairs)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n + 4) profit[i] = 0.0;
     if (i < m + 4 && (!keep_prices || i >= m)) price[i] = 0.0;
     if (i == 0) {
         stats->rounds = 0; stats->bids = 0; stats->bytes = 0; stats->round_bytes = 0; stats->head = 0;
-        stats->chain_bids = 0; stats->chain_depth = 0; stats->launch_max = 0; stats->chain_retries = 0; stats->team_bids = 0; stats->path_steps = 0; stats->path_scans = 0; stats->team_abort = 0; stats->rested = 0; stats->active = 0; stats->max_weight = 0;
+        stats->chain_bids = 0; stats->chain_depth = 0; stats->launch_max = 0; stats->chain_retries = 0; stats->team_bids = 0; stats->path_steps = 0; stats->path_scans = 0; stats->team_abort = 0; stats->rested = 0; stats->active = 0; stats->max_weight = known ? *known : 0;
+        stats->feasible_pairs = known_pairs ? *known_pairs : ~0ull;
         stats->cnt[0] = 0; stats->cnt[1] = 0; stats->cnt[2] = 0; stats->cnt[3] = 0;
     }
 }
@@ -870,8 +871,6 @@ int run_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_
     const mf_cert_out &c = *ctx->h_cert;
     *general = c.status == MF_SMALL_GENERAL;
     if (c.status != MF_OK) return c.status;
-    MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
     MF_HIP(hipEventElapsedTime(&ctx->timings[T_SOLVE], ctx->ev[3], ctx->ev[4]));
     MF_HIP(hipEventElapsedTime(&ctx->timings[T_CERT], ctx->ev[4], ctx->ev[6]));
     h_res->bids = h_res->chain_bids = c.bids;
@@ -924,28 +923,27 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     MF_HIP(hipEventRecord(ctx->ev[3], ctx->stream));
     {
         // the largest weight sets the first epsilon
+        const bool known = candidate && ctx->largest_weight_known;
         const int chunks = (m + 4095) / 4096 < 4 ? (m + 4095) / 4096 : 4;
         hipLaunchKernelGGL(init_solver_kernel, dim3((nm + 4 + 255) / 256), dim3(256), 0, ctx->stream, rn, rm,
-                           ctx->price, ctx->profit, ctx->stats, warm ? 1 : 0);
-        // (when the matrix was scored here a moment ago its largest weight was noted on the way)
-        if (candidate && ctx->largest_weight_known)
-            hipLaunchKernelGGL(known_weight_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->largest_weight, ctx->stats);
-        else if (lists_possible) {
+                           ctx->price, ctx->profit, ctx->stats, warm ? 1 : 0,
+                           known ? ctx->largest_weight : nullptr, candidate ? ctx->feasible_pairs : nullptr);
+        if (lists_possible) {
             // the same pass also counts the feasible pairs of every row: with few of them the rounds read lists
             hipLaunchKernelGGL(fill_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->feasible_pairs);
             const int rc = mf_count_edges(ctx, d_W, n, m, ldw);
             if (rc != MF_OK) return rc;
-        } else
+        } else if (!known)
             hipLaunchKernelGGL(max_weight_kernel, dim3(chunks, n < 1024 ? n : 1024), dim3(256), 0, ctx->stream, d_W, n,
                                m, ldw, ctx->stats);
         MF_HIP(hipGetLastError());
     }
-    *ctx->h_feasible_pairs = ~0ull;
-    if (candidate || lists_possible)
+    if (lists_possible)
         MF_HIP(hipMemcpyAsync(ctx->h_feasible_pairs, ctx->feasible_pairs, sizeof(unsigned long long),
                               hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
+    if (!lists_possible) *ctx->h_feasible_pairs = ctx->h_stats->feasible_pairs;
     const long long cmax = K * (long long)ctx->h_stats->max_weight;
     if (cmax >= MF_MAX_DUAL) return MF_ERR_RANGE;
     // ... worth it when most of the matrix can be left unread
@@ -971,13 +969,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     };
     if (flip) make_transpose();
     MF_HIP(hipGetLastError());
-    MF_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
-    {
-        float ms = 0.0f;
-        MF_HIP(hipEventElapsedTime(&ms, ctx->ev[3], ctx->ev[4]));
-        ctx->timings[T_TRANSPOSE] = ms;
-    }
+    MF_HIP(hipEventRecord(ctx->ev[9], ctx->stream));
 
     // with per-line lengths a scan reads, on average, the pairs that can share divided by the lines
     const double feasible = staged ? (double)*ctx->h_feasible_pairs : (double)n * (double)m;
@@ -1112,9 +1104,8 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
     int rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
     if (rc != MF_OK) return rc;
-    MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
     float ms_solve = 0.0f, ms_duals = 0.0f, ms_cert = 0.0f;
+    MF_HIP(hipEventElapsedTime(&ctx->timings[T_TRANSPOSE], ctx->ev[3], ctx->ev[9]));
     MF_HIP(hipEventElapsedTime(&ms_solve, ctx->ev[3], ctx->ev[4]));
     MF_HIP(hipEventElapsedTime(&ms_duals, ctx->ev[4], ctx->ev[5]));
     MF_HIP(hipEventElapsedTime(&ms_cert, ctx->ev[5], ctx->ev[6]));

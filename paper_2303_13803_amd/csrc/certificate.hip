@@ -177,9 +177,11 @@ __global__ void map_back_kernel(int rn, int rm, const int32_t *__restrict__ r2c,
     }
 }
 
-__global__ void init_cert_kernel(mf_cert_out *out)
+__global__ void cert_begin_kernel(mf_cert_out *out, int *colmark, int m)
 {
-    out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < m) colmark[j] = 0;
+    if (j == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
 }
 
 }  // namespace
@@ -188,16 +190,17 @@ int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ld
                        const int32_t *d_row2col, const int64_t *d_u, const int64_t *d_v,
                        int64_t K, mf_result *h_res, bool begun)
 {
-    if (!begun) {
-        hipLaunchKernelGGL(init_cert_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->cert);
-        hipLaunchKernelGGL(fill_int_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->colmark, m, 0);
-    }
+    if (!begun) hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->cert, ctx->colmark, m);
     const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
     hipLaunchKernelGGL(K >= INT32_MIN && K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>,
                        dim3(grid), dim3(BID_THREADS), 0, ctx->stream, d_W, ldw, n, m,
                        d_row2col, d_u, d_v, (long long)K, ctx->colmark, ctx->cert);
     MF_HIP(hipGetLastError());
+    MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
+    // the last wait of a call: what else the host wants to know comes along with it
     MF_HIP(hipMemcpyAsync(ctx->h_cert, ctx->cert, sizeof(mf_cert_out), hipMemcpyDeviceToHost, ctx->stream));
+    if (ctx->score_pending)
+        MF_HIP(hipMemcpyAsync(ctx->h_pairs_evaluated, ctx->pairs_evaluated, sizeof(unsigned long long), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
     const mf_cert_out &c = *ctx->h_cert;
     h_res->primal = c.primal;
@@ -251,13 +254,6 @@ constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex noalloc_lock;
 unsigned char *noalloc_ptr[NOALLOC_MAX_DEVICES];    // scratch's address on each device (null: not looked up yet)
 
-__global__ void noalloc_begin_kernel(mf_cert_out *out, int *colmark, int m)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < m) colmark[j] = 0;
-    if (j == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
-}
-
 __global__ void noalloc_finish_kernel(const mf_cert_out *in, long long K, mf_certificate *d_out)
 {
     const long long min_rc = in->min_rc == INT64_MAX ? 0 : in->min_rc;
@@ -299,7 +295,7 @@ extern "C" int mf_check_certificate_noalloc(void *hip_stream, const int32_t *d_W
     hipStream_t stream = (hipStream_t)hip_stream;
     // the array keeps what the previous call left: both parts are cleared by a kernel (no
     // memset node, so the sequence can be captured into a graph)
-    hipLaunchKernelGGL(noalloc_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, out, colmark, m);
+    hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, out, colmark, m);
     const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
     hipLaunchKernelGGL(K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>, dim3(grid),
                        dim3(BID_THREADS), 0, stream, d_W, ldw, n, m, d_row2col, d_u, d_v, (long long)K, colmark, out);

@@ -50,6 +50,7 @@ struct mf_device_stats {            // lives in device memory, cleared per solve
     unsigned long long path_steps;  // super-steps of the shortest-path searches
     unsigned long long path_scans;  // line scans those searches made
     unsigned long long launch_max;  // scratch: that maximum for the chain kernel in flight
+    unsigned long long feasible_pairs;      // of the matrix, where the scoring pass counted them (else ~0)
     int max_weight;
     int cnt[4];                     // ring of bidder-list lengths: round r reads cnt[r & 3]
     int head;                       // next unclaimed entry of the list a chain kernel works through
@@ -177,7 +178,7 @@ struct mf_ctx {
     int64_t theta, max_rounds;
     bool as_told;                   // an option says how to match: small problems are then matched that way too
     // timing
-    hipEvent_t ev[10];              // 0..2 and 8: scoring stages; 3..7: solver stages
+    hipEvent_t ev[10];              // 0..2 and 8: scoring stages; 3..7 and 9: solver stages
     float timings[T_COUNT];
     bool score_pending;             // score events recorded but not yet read
 };
