@@ -21,14 +21,17 @@ constexpr int SMALL_FETCH = 8;                  // rows a wavefront has on their
 constexpr int SMALL_COLS = 512;                 // eight columns a lane
 constexpr int SMALL_LDS = 152 * 1024;           // (of 160 KB)
 // Rows: the searches scan up to half as many rows as there are, one after the other, where the auction's bidders go on side
-// by side.  Rounds of scored pairs, whose rows prefer nearly the same columns, auction / this, ms: 64 x 64 0.51..0.78 /
-// 0.27, 72 x 72 0.62 / 0.51, 80 x 80 0.67 / 0.61, 96 x 96 0.71 / 0.77, 128 x 128 0.87 / 1.25; with more columns
-// than rows there is less to search: 64 x 150 0.76 / 0.37, 96 x 130 1.15 / 0.82, 104 x 160 0.92 / 0.82, 112 x 200 0.94 /
-// 0.85, 112 x 300 0.87 / 0.96.  Other matrices gain at any of these sizes (uniform weights, 100 x 100 0.36 / 0.19; products of
-// a row and a column, the longest searches there are, 64 x 64 1.6 / 0.59, 100 x 300 3.6 / 2.7).
+// by side.  Rounds of scored pairs, whose rows prefer nearly the same columns, auction / this, ms (the laws of four
+// configurations, four seeds): 64 x 64 0.44..0.90 / 0.23..0.41, 80 x 80 0.56..1.1 / 0.31..0.62, 88 x 88 0.54..0.86 / 0.34..0.76,
+// 104 x 104 0.58..1.1 / 0.44..1.08 (the slowest law 0.76 / 0.90 in the mean), 128 x 128 0.87 / 1.25.  With more columns than
+// rows there is less to search: 64 x 150 0.51..0.88 / 0.23..0.46, 112 x 200 0.66..1.2 / 0.51..1.05, but with eight columns a lane
+// 112 x 300 0.59..1.1 / 0.52..1.33.  Other matrices gain at any of these sizes (uniform weights, 100 x 100 0.36 / 0.19;
+// products of a row and a column, the longest searches there are, 64 x 64 1.6 / 0.6).
 // More rows than columns are left to the auction: such a solve is promised to run on lists, one read and counted for every bid.
-constexpr int SMALL_ROWS = 80, SMALL_ROWS_WIDE = 104;       // ... the latter with a third more columns than rows
-constexpr int SMALL_BIDS = 4;                   // bids in the first part, per row
+constexpr int SMALL_ROWS = 88, SMALL_ROWS_WIDE = 112, SMALL_COLS_WIDE = 256;     // ... the latter with a third more columns than rows
+// Bids in the first part, per row.  (More leave fewer rows waiting but prefer the same columns: 64 x 64 with 1, 2, 4 and 8 a row,
+// 109 + 1018, 170 + 1035, 295 + 864 and 538 + 872 bids and scans, and a bid takes half as long again as a scan.)
+constexpr int SMALL_BIDS = 1;
 constexpr int SMALL_WEIGHTS = 1 << 28;          // weights below it: twice every sum below then stays within 32 bits
 
 struct SmallShape {
@@ -78,7 +81,7 @@ __device__ __forceinline__ int largest_of(const int (&x)[C])
 
 // What bounds it: one chain of dependent bids and scans (0.20 us a scan with one column a lane, 0.31 with four, 0.43 with
 // eight: a third of it the reduction, a quarter LDS) and 6 us for the launch and the matrix's way into one compute
-// unit.  64 x 64 of scored pairs: about 290 bids and 860 scans, 230 us, of which the auction's launches took 565.
+// unit.  64 x 64 of scored pairs: about 110 bids and 550 to 1300 scans, 140 to 280 us, where the auction's launches took 565.
 // Weights, prices, profits and labels are held doubled, and the price of a column that somebody holds is odd: of
 // equally good columns the maximum then is one that nobody holds.
 // Prices and profits are at most the largest weight (a price never exceeds the weight of the pair that holds it), which
@@ -279,7 +282,7 @@ bool mf_small_fits(int n, int m)
 {
     int columns = 0;
     const SmallShape s = small_shape(n, m, 0, &columns);
-    const bool few = s.n <= SMALL_ROWS || (s.n <= SMALL_ROWS_WIDE && 3 * s.m >= 4 * s.n);
+    const bool few = s.n <= SMALL_ROWS || (s.n <= SMALL_ROWS_WIDE && 3 * s.m >= 4 * s.n && s.m <= SMALL_COLS_WIDE);
     return n <= m && few && s.m <= SMALL_COLS && small_bytes(s, columns) <= (size_t)SMALL_LDS;
 }
 
