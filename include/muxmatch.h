@@ -332,7 +332,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            "path_frontier_rows" (1024), "path_pull" (0), "path_spin_limit" (2^22 polls a workgroup
  *            waits for the others before all give up; see mf_result.fallbacks)
  *   lists    "core" (1; 0: never): the phases from the one on in which a list of every line's best entries
- *            reaches "core_depth" (20) epsilons below the best run on such lists, in one launch;
+ *            reaches "core_depth" (20) epsilons below the best (a twentieth of that on problems of "core_wide"
+ *            lines without feasible prefixes) run on such lists, in one launch;
  *            "core_many" (4) / "core_few" (32): chain steps between two looks at the list of bidders,
  *            "core_after" (256): chain steps after which the last bidders are searched for
  *            (fewer in proportion on problems of less than 1664 lines),
