@@ -293,7 +293,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *                      stay as close to an fp64 evaluation as with fp32 products, about 3e-7
  *                      relative, at a third of the time); 0: fp32 products
  *   "fit_order"        1 (default): scoring walks workloads in order of memory fraction and runs no
- *                      MLP for pairs that cannot fit; 0: every pair goes through the MLP
+ *                      MLP for pairs that cannot fit (but in rounds of up to about a hundred rows,
+ *                      where finding the order takes longer); 0: every pair goes through the MLP
  *   "fit_prefix"       1 (default) / 0: allow mf_schedule_round to match on the context's
  *                      memory-ordered copy of the matrix, reading only each line's feasible prefix
  *   "fit_prefix_below" percent (default 50): ... when fewer of the pairs just scored can share; 0: never

@@ -321,7 +321,7 @@ int mf_score_pairs(mf_ctx *ctx, const mf_predictor *pred, const float *d_on, int
     if (n > ctx->max_n || m > ctx->max_m) return MF_ERR_SHAPE;
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
-    return mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, d_sigma);
+    return mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
 }
 
 int mf_solve_assignment(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
@@ -370,7 +370,7 @@ int mf_schedule_round(mf_ctx *ctx, const mf_predictor *pred, const float *d_on, 
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
     memset(h_res, 0, sizeof(*h_res));
-    rc = mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, nullptr);
+    rc = mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, nullptr, mf_small_fits(ctx, n, m));
     if (rc == MF_OK) rc = mf_run_solver(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, false, nullptr, 0, true);
     if (rc == MF_OK || rc == MF_ERR_CERT) {
         int rt = finish_score_timing(ctx, true);
@@ -390,7 +390,7 @@ int mf_score_pairs_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types, co
     if (n > ctx->max_n || m > ctx->max_m) return MF_ERR_SHAPE;
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
-    return mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, d_sigma);
+    return mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
 }
 
 int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types, const int32_t *d_type_on,
@@ -405,7 +405,7 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
     memset(h_res, 0, sizeof(*h_res));
-    rc = mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, nullptr);
+    rc = mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, nullptr, mf_small_fits(ctx, n, m));
     if (rc == MF_OK) rc = mf_run_solver(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, false, nullptr, 0, true);
     if (rc == MF_OK || rc == MF_ERR_CERT) {
         int rt = finish_score_timing(ctx, true);

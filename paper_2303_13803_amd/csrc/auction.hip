@@ -904,7 +904,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     const bool flip = n > m;
     warm = warm && !flip && !candidate && ctx->warm_n == n && ctx->warm_m == m;
     ctx->warm_n = ctx->warm_m = 0;
-    if (!ctx->as_told && mf_small_fits(n, m)) {
+    if (mf_small_fits(ctx, n, m)) {
         bool general = false;
         const int rc = run_small(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, &general);
         if (!general) return rc;

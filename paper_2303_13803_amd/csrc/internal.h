@@ -210,7 +210,7 @@ struct SideArgs {
 // score.hip
 int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const int32_t *d_type,
                     const float *d_on, int n, const float *d_off, int m, int32_t *d_W, int64_t ldw,
-                    float *d_sigma);
+                    float *d_sigma, bool as_it_comes);
 int mf_launch_rescore(mf_ctx *ctx, const mf_predictor *pred, const float *d_on, int n, const float *d_off,
                       int m, int32_t *d_W, int64_t ldw, const int32_t *d_rows, int n_rows,
                       const int32_t *d_cols, int n_cols);
@@ -258,5 +258,5 @@ int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ld
                        int64_t K, mf_result *h_res, bool begun);        // begun: ctx->cert and ctx->colmark are cleared
 // small.hip
 enum { MF_SMALL_GENERAL = 1 };           // status: left to the auction
-bool mf_small_fits(int n, int m);
+bool mf_small_fits(const mf_ctx *ctx, int n, int m);
 int mf_launch_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_t *d_row2col, int64_t *d_u, int64_t *d_v);

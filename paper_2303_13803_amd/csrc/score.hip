@@ -773,7 +773,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
         if (pair_of_rows) { score_rows(std::integral_constant<int, 2>{}, std::integral_constant<bool, SPLIT>{}, r); r += 2; }
         else { score_rows(std::integral_constant<int, 1>{}, std::integral_constant<bool, SPLIT>{}, r); r += 1; }
     }
-    // rows the loop left early keep the "cannot fit" marks the staged matrix was filled with
+    // (what rows the loop left early have here lies beyond their feasible prefixes and is never read)
     if (evaluated && lane == 0 && r > 0) atomicAdd(evaluated, (unsigned long long)r * (unsigned)min(32, m - j0));
 }
 
@@ -906,7 +906,7 @@ __global__ __launch_bounds__(1024) void type_segments_kernel(const int32_t *__re
 // segment of the row map, which lists the online workloads by (type, memory fraction).
 int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const int32_t *d_type,
                     const float *d_on, int n, const float *d_off, int m, int32_t *d_W, int64_t ldw,
-                    float *d_sigma)
+                    float *d_sigma, bool as_it_comes)
 {
     const mf_predictor *p0 = &preds[0];
     const bool typed = d_type != nullptr;
@@ -928,7 +928,9 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     // Pairs whose memory fractions do not fit get no score, so unless the caller wants every
     // score, walk rows and columns in memory order: the pairs that cannot fit then form one
     // corner of the tile grid and the kernel leaves them out.  Results land at the same places.
-    const bool by_memory = ctx->fit_order && !d_sigma;
+    // (as_it_comes: a problem so small that the four launches which find the order and undo it take longer than
+    // the pairs: a 64 x 64 round 241 / 218 us)
+    const bool by_memory = ctx->fit_order && !d_sigma && !as_it_comes;
     const int64_t lds = ((int64_t)m + 3) & ~3ll;
     // (each of these is a few microseconds of work: as eight launches, not twenty-two, the set-up of a
     // 64 x 64 round takes 31 us, not 310)

@@ -74,3 +74,26 @@ def test_it_stops_at_the_limit_on_bids(orc):
         with pytest.raises(mm.MuxmatchError) as e:
             _solve(orc, W, {"max_rounds": limit})
         assert e.value.code == mm.ERR_NOT_CONVERGED
+
+
+@pytest.mark.parametrize("law,n,m", [("C1", 64, 64), ("C4", 33, 257), ("C5", 88, 201)])
+def test_its_rounds_score_pairs_as_they_come(orc, law, n, m):
+    """No memory order is found for them: the weights are those of the pass that walks in it, bit for bit."""
+    import paper_2303_13803_amd as mm
+    r = synth.scheduling_round(law, 86, n=n, m=m)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = mm.Context(n, m)
+    pred = ctx.predictor({k: dev(v) for k, v in r["params"].items()}, r["cfg"].scale)
+    x_on, x_off, pad = dev(r["x_on"]), dev(r["x_off"]), (m + 3) // 4 * 4
+    W, again = (torch.full((n, pad), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.schedule_round(pred, x_on, x_off, W, r2c, u, v)
+    fraction = ctx.last_timings()["pairs_evaluated_fraction"]
+    ctx.score_pairs(pred, x_on, x_off, again)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert fraction == 1.0 and res.rounds == 0 and torch.equal(W, again)
+    Wh = W.cpu().numpy()[:, :m]
+    code, P, _ = orc.check_certificate(np.ascontiguousarray(Wh), r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.primal == P
