@@ -25,6 +25,7 @@
 #include "scan.h"
 #include "search_words.h"
 #include "team_join.h"
+#include "team_steps.h"
 
 namespace {
 
@@ -746,6 +747,11 @@ struct Core {
         }
     }
 
+    // (see team_steps.h)
+    __device__ __forceinline__ unsigned long long rows_looked_at() const { return load_fresh_u64(&ctl->rescans); }
+    __device__ __forceinline__ void add_rows_looked_at(int looked) { if (tid == 0 && looked) atomicAdd(&ctl->rescans, (unsigned long long)looked); }
+    __device__ __forceinline__ bool bidders_left() const { return sh.n_alive > 0; }
+
     // The side's lists once more by opposite line (columns, in a search): made when a search first
     // needs them and good as long as the lists are.
     __device__ __forceinline__ bool by_column(const CoreSide &s)
@@ -1040,77 +1046,74 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                 }
                 flush(a.tree, &ctl->tree_count);
                 if (!barrier()) return MF_CORE_ABORT;
-                if (rank == 0) {
-                    if (tid == 0) {
-                        int k = sink_id;
-                        if (gives_up) {
-                            const int h = load_fresh_i32(&a.held[sink_id]);
-                            k = h < 0 ? -1 : h;
-                        }
-                        // (one dependent trip a hop here; the words are changed below, by as many threads as there are hops)
-                        unsigned hops = 0;
-                        while (k >= 0 && hops <= (unsigned)s.lines) {
-                            const unsigned long long pr = load_fresh_u64(&a.parent[k]);
-                            const int i = (int)(pr >> 32);
-                            if (hops < (unsigned)CORE_PUSH_BUFFER) sh.list[hops] = ((unsigned long long)(unsigned)i << 32) | (unsigned long long)(unsigned)k;
-                            else {
-                                store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
-                                store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                auto clear_tree = [&]() {
+                    if (rank == 0) {
+                        if (tid == 0) {
+                            int k = sink_id;
+                            if (gives_up) {
+                                const int h = load_fresh_i32(&a.held[sink_id]);
+                                k = h < 0 ? -1 : h;
                             }
-                            ++hops;
-                            k = (int)(unsigned)(pr & 0xffffffffull);
+                            // (one dependent trip a hop here; the words are changed below, by as many threads as there are hops)
+                            unsigned hops = 0;
+                            while (k >= 0 && hops <= (unsigned)s.lines) {
+                                const unsigned long long pr = load_fresh_u64(&a.parent[k]);
+                                const int i = (int)(pr >> 32);
+                                if (hops < (unsigned)CORE_PUSH_BUFFER) sh.list[hops] = ((unsigned long long)(unsigned)i << 32) | (unsigned long long)(unsigned)k;
+                                else {
+                                    store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
+                                    store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                                }
+                                ++hops;
+                                k = (int)(unsigned)(pr & 0xffffffffull);
+                            }
+                            sh.pushes = hops;
+                            for (int q = 0; q <= CORE_JUMP_PASSES; ++q) store_u32(&ctl->jump_pending[q], 0u);
+                            store_through(&ctl->sink, CORE_INF);
+                            for (int q = 0; q < 3; ++q) {
+                                store_through(&ctl->sink_found[q], CORE_INF); store_through(&ctl->low[q], CORE_INF);
+                                store_through(&ctl->frontier[q], 0ull); store_through(&ctl->whole_front[q], 0ull);
+                            }
                         }
-                        sh.pushes = hops;
-                        for (int q = 0; q <= CORE_JUMP_PASSES; ++q) store_u32(&ctl->jump_pending[q], 0u);
-                        store_through(&ctl->sink, CORE_INF);
-                        for (int q = 0; q < 3; ++q) {
-                            store_through(&ctl->sink_found[q], CORE_INF); store_through(&ctl->low[q], CORE_INF);
-                            store_through(&ctl->frontier[q], 0ull); store_through(&ctl->whole_front[q], 0ull);
+                        __syncthreads();
+                        for (unsigned t = tid; t < min(sh.pushes, (unsigned)CORE_PUSH_BUFFER); t += CORE_THREADS) {
+                            const int k = (int)(unsigned)(sh.list[t] & 0xffffffffull), i = (int)(sh.list[t] >> 32);
+                            store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
+                            store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
                         }
                     }
+                    // The tree's columns lose their labels.  What the others have reached stays as it is: a
+                    // column of the tree, at its raised price, is at least as far from any of them as the
+                    // path just served was long.
                     __syncthreads();
-                    for (unsigned t = tid; t < min(sh.pushes, (unsigned)CORE_PUSH_BUFFER); t += CORE_THREADS) {
-                        const int k = (int)(unsigned)(sh.list[t] & 0xffffffffull), i = (int)(sh.list[t] >> 32);
-                        store_through(&s.otherword[k], pack_word(word_dual(load_fresh_u64(&s.otherword[k])) + eps, i + 1));
-                        store_i32(&a.held_weight[k], s.A[(size_t)i * s.pitch + k]);
+                    if (tid == 0) sh.pushes = 0u;
+                    __syncthreads();
+                    auto was_read = [&](int i) {
+                        const unsigned slot = atomicAdd(&sh.pushes, 1u);
+                        if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)i;
+                        else store_i32(&a.whole0[atomicAdd(&ctl->read_count, 1)], i);
+                    };
+                    for (int k = gtid(); k < s.len; k += gsize()) {
+                        const unsigned state = load_fresh_u32(&a.stamp[k]);
+                        if (state == CORE_IN_TREE) {
+                            store_through(&a.label[k], CORE_INF);
+                            store_u32(&a.stamp[k], 0u);
+                            store_through(&a.expanded[k], CORE_INF);
+                            store_through(&a.read_from[k], CORE_INF);
+                            store_f64(&a.left[k], CORE_FAR);
+                            store_f64(&a.dropped[k], CORE_FAR);
+                        } else if (state == CORE_READ) was_read(word_id(load_fresh_u64(&s.otherword[k])));
                     }
-                }
-                // The tree's columns lose their labels.  What the others have reached stays as it is: a
-                // column of the tree, at its raised price, is at least as far from any of them as the
-                // path just served was long.
-                __syncthreads();
-                if (tid == 0) sh.pushes = 0u;
-                __syncthreads();
-                auto was_read = [&](int i) {
-                    const unsigned slot = atomicAdd(&sh.pushes, 1u);
-                    if (slot < (unsigned)CORE_PUSH_BUFFER) sh.list[slot] = (unsigned long long)(unsigned)i;
-                    else store_i32(&a.whole0[atomicAdd(&ctl->read_count, 1)], i);
+                    if (rank == 0 && tid < n_alive && sh.alive[tid] != root && sh.remainder[sh.alive[tid]] >= CORE_WHOLE) was_read(sh.row[sh.alive[tid]]);
+                    flush(a.whole0, &ctl->read_count);
+                    __syncthreads();
+                    if (tid == 0) {
+                        int n = 0;
+                        for (int e = 0; e < n_alive; ++e) if (sh.alive[e] != root) sh.alive[n++] = sh.alive[e];
+                        sh.n_alive = n;
+                    }
                 };
-                for (int k = gtid(); k < s.len; k += gsize()) {
-                    const unsigned state = load_fresh_u32(&a.stamp[k]);
-                    if (state == CORE_IN_TREE) {
-                        store_through(&a.label[k], CORE_INF);
-                        store_u32(&a.stamp[k], 0u);
-                        store_through(&a.expanded[k], CORE_INF);
-                        store_through(&a.read_from[k], CORE_INF);
-                        store_f64(&a.left[k], CORE_FAR);
-                        store_f64(&a.dropped[k], CORE_FAR);
-                    } else if (state == CORE_READ) was_read(word_id(load_fresh_u64(&s.otherword[k])));
-                }
-                if (rank == 0 && tid < n_alive && sh.alive[tid] != root && sh.remainder[sh.alive[tid]] >= CORE_WHOLE) was_read(sh.row[sh.alive[tid]]);
-                flush(a.whole0, &ctl->read_count);
-                __syncthreads();
-                if (tid == 0) {
-                    int n = 0;
-                    for (int e = 0; e < n_alive; ++e) if (sh.alive[e] != root) sh.alive[n++] = sh.alive[e];
-                    sh.n_alive = n;
-                }
-                if (!barrier()) return MF_CORE_ABORT;
-                n_alive = sh.n_alive;
-                agreed_sink = resting_bidders();
-                since_served = 0;
-                --step;
-                if (n_alive > 0) {
+                auto offer_again = [&](bool from_columns) {
                     // New labels for the tree's columns, from the scanned rows whose lists they are on.  Either every
                     // scanned row's list is looked through once more, or the lists are kept by column as well and
                     // a wavefront takes a column, or a stretch of its entries.  Making those takes one die 0.1 ms for
@@ -1121,11 +1124,8 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                     // 13.7, 4096 x 8192 7.65 / 7.44, smaller ones the same.)
                     const int n_tree = load_fresh_i32(&ctl->tree_count);
                     constexpr int STRETCH = 512;
-                    if (!(columns_ready & side_bit) && (s.len > CORE_PUSH_BUFFER * 32 || s.lines / (int)G + CORE_THREADS > CORE_PUSH_BUFFER || load_fresh_u64(&ctl->rescans) > (unsigned long long)s.lines * CORE_RESCANS)) {
-                        if (!by_column(s)) return MF_CORE_ABORT;
-                        columns_ready |= side_bit;
-                    }
-                    if (!(columns_ready & side_bit)) {
+                    int looked = 0;
+                    if (!from_columns) {
                         unsigned *in_tree = (unsigned *)sh.list;             // a bit a column, and this workgroup's scanned rows
                         int *rows = (int *)(sh.list + CORE_PUSH_BUFFER / 2);
                         __syncthreads();
@@ -1139,7 +1139,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                         for (int i = gtid(); i < s.lines; i += gsize())
                             if (load_fresh(&a.base[i]) < CORE_FAR * 0.5) rows[atomicAdd(&sh.pushes, 1u)] = i;
                         __syncthreads();
-                        const int looked = (int)sh.pushes;
+                        looked = (int)sh.pushes;
                         int i = wave < looked ? rows[wave] : 0;
                         const int2 *e = s.entries + (size_t)i * CORE_LIST;
                         int2 e0 = e[lane], e1 = e[lane + 64];
@@ -1165,7 +1165,6 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                             if (in0 && m0 < l0) atomicMin(&a.label[now0.x], m0);
                             if (in1 && m1 < l1) atomicMin(&a.label[now1.x], m1);
                         }
-                        if (tid == 0 && looked) atomicAdd(&ctl->rescans, (unsigned long long)looked);
                     } else for (int it = gwave(); it < n_tree; it += gwaves()) {
                         const int k = load_fresh_i32(&a.tree[it]);
                         const int from = load_fresh_i32(&s.t_start[k]), to = load_fresh_i32(&s.t_at[k]);
@@ -1218,8 +1217,18 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                             if (lane == 0) atomicMin(&a.label[k], ((unsigned long long)(long long)least << MF_ID_BITS) | (unsigned long long)i);
                         }
                     }
-                    if (!barrier()) return MF_CORE_ABORT;
-                }
+                    return looked;
+                };
+                bool by_columns = (columns_ready & side_bit) != 0u;
+                const bool must = s.len > CORE_PUSH_BUFFER * 32 || s.lines / (int)G + CORE_THREADS > CORE_PUSH_BUFFER;      // (no room in LDS)
+                if (!labels_of_served_tree(*this, by_columns, must, (unsigned long long)s.lines * CORE_RESCANS, clear_tree,
+                                           [&]() { return by_column(s); }, offer_again))
+                    return MF_CORE_ABORT;
+                if (by_columns) columns_ready |= side_bit;
+                n_alive = sh.n_alive;
+                agreed_sink = resting_bidders();
+                since_served = 0;
+                --step;
                 from_bidders = false; sweep_next = true; swept = false;
                 continue;
             }

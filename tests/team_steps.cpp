@@ -1,0 +1,128 @@
+// Runs csrc/team_steps.h on threads (test_team_steps.py): a thread stands for a workgroup, and one of them is held up
+// after every barrier until all others have come to the next one.  At each barrier all have to say that they
+// are in the same place.
+//
+//   team_steps RULE     "labels": as the header has it; "labels read late": the count of rows read behind the barrier
+#include <stdio.h>
+#include <string.h>
+#include <condition_variable>
+#include <mutex>
+#include <thread>
+#include <vector>
+#include "team_steps.h"
+
+// The barrier.  `apart`: two members came to it from different places; everybody leaves then.
+struct Meeting {
+    std::mutex guard;
+    std::condition_variable turned;
+    int members, late;                  // late: the member that is held up
+    int waiting = 0, number = 0, place = 0;
+    bool apart = false;
+
+    Meeting(int m, int l) : members(m), late(l) {}
+
+    bool barrier(int who, int where)
+    {
+        std::unique_lock<std::mutex> hold(guard);
+        if (waiting == 0) place = where;
+        else if (place != where) apart = true;
+        const int mine = number;
+        if (++waiting == members) { waiting = 0; ++number; }
+        turned.notify_all();
+        turned.wait(hold, [&]() { return apart || number != mine; });
+        if (who == late) turned.wait(hold, [&]() { return apart || waiting == members - 1; });
+        return !apart;
+    }
+    void leave()
+    {
+        std::lock_guard<std::mutex> hold(guard);
+        if (--members == waiting && waiting > 0) { waiting = 0; ++number; }
+        turned.notify_all();
+    }
+};
+
+struct Shared {
+    unsigned long long rows = 0;
+};
+
+// places a barrier can be at
+enum { SERVED = 1, MAKING = 100, OFFERED = 1000 };
+
+struct Member {
+    Meeting &meeting;
+    Shared &shared;
+    int number, place = 0, tree = 0, trees;
+
+    unsigned long long rows_looked_at() { return __atomic_load_n(&shared.rows, __ATOMIC_SEQ_CST); }
+    void add_rows_looked_at(int n) { place = OFFERED; __atomic_fetch_add(&shared.rows, (unsigned long long)n, __ATOMIC_SEQ_CST); }
+    bool bidders_left() const { return tree < trees; }
+    bool barrier() { return meeting.barrier(number, place); }
+};
+
+template <class Team, class Clear, class Make, class Offer>
+static bool labels_read_late(Team &team, bool &by_column, bool must, unsigned long long most, const Clear &clear, const Make &make, const Offer &offer)
+{
+    clear();
+    if (!team.barrier()) return false;
+    if (!team.bidders_left()) return true;
+    if (!by_column && (must || team.rows_looked_at() > most)) {
+        if (!make()) return false;
+        by_column = true;
+    }
+    team.add_rows_looked_at(offer(by_column));
+    return team.barrier();
+}
+
+static bool serve_trees(Member &m, bool read_late, unsigned long long most, int *made_for)
+{
+    bool by_column = false;
+    const auto clear = [&]() { m.place = SERVED; };
+    const auto make = [&]() {
+        for (int k = 0; k < 4; ++k) {
+            m.place = MAKING + k;
+            if (!m.barrier()) return false;
+        }
+        *made_for = m.tree;
+        return true;
+    };
+    const auto offer = [&](bool columns) { return columns ? 0 : 2 + m.number; };
+    while (m.tree < m.trees) {
+        ++m.tree;
+        if (!(read_late ? labels_read_late(m, by_column, false, most, clear, make, offer)
+                        : labels_of_served_tree(m, by_column, false, most, clear, make, offer)))
+            return false;
+    }
+    return true;
+}
+
+int main(int argc, char **argv)
+{
+    if (argc != 2) return 2;
+    const bool read_late = !strcmp(argv[1], "labels read late");
+    if (!read_late && strcmp(argv[1], "labels")) return 2;
+    const int members = 4, trees = 6;
+    int together = 0, apart = 0, wrong = 0;
+    for (int late = 0; late < members; ++late)
+        for (unsigned long long most = 0; most < 80; ++most) {
+            Meeting meeting(members, late);
+            Shared shared;
+            std::vector<int> made_for(members, 0);
+            std::vector<std::thread> team;
+            for (int k = 0; k < members; ++k)
+                team.emplace_back([&, k]() {
+                    Member m{meeting, shared, k};
+                    m.trees = trees;
+                    (void)serve_trees(m, read_late, most, &made_for[k]);
+                    meeting.leave();
+                });
+            for (std::thread &t : team) t.join();
+            if (meeting.apart) { ++apart; continue; }
+            ++together;
+            // a tree adds 2 + 3 + 4 + 5 rows; the last one places the last bidder, and nobody asks for labels
+            int expect = (int)(most / 14) + 2;
+            if (expect >= trees) expect = 0;
+            for (int k = 0; k < members; ++k) wrong += made_for[k] != expect;
+        }
+    printf("%d together, %d apart, %d wrong\n", together, apart, wrong);
+    return apart == 0 && wrong == 0 ? 0 : 1;
+}
