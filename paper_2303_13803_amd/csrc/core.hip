@@ -312,10 +312,10 @@ struct alignas(256) CoreCtl {
     unsigned joined, arrived, members;                   // (see team_join.h)
     // barriers each workgroup has reached (top bit: it gave up); one lane polls each
     alignas(256) unsigned reached[CORE_MAX_WORKGROUPS];
-    // bidders handed on: epoch e reads cnt[e & 3], fills cnt[(e + 1) & 3] and clears cnt[(e + 2) & 3]
-    alignas(128) int cnt[4];
-    int whole_count[4];                                  // rows whose whole lines a refinement looks at next (same ring)
-    unsigned dense[4];                                   // whole lines read in an epoch (same ring)
+    // rings by step (team_steps.h), clear when the launch begins
+    alignas(128) int cnt[STEP_RING];                     // bidders handed on
+    int whole_count[STEP_RING];                          // rows whose whole lines a refinement looks at next
+    unsigned dense[STEP_RING];                           // whole lines read in a step
     alignas(128) unsigned long long slack[3];            // see slack_of: bits of a non-negative double, two means
     int rev_count, tree_count, read_count;
     unsigned long long rescans;                          // rows looked at once more for a served tree's columns, this search
@@ -484,11 +484,12 @@ struct Core {
     CoreShared &sh;
     unsigned G, rank;
     unsigned generation, columns_ready;     // columns_ready: the sides whose lists exist by column (bits)
+    unsigned epoch;                         // the step the launch is at: never set back (team_steps.h)
     int tid, lane, wave;
     unsigned bids, depth, steps, scans, whole, rests;          // this wavefront's counts
 
     __device__ Core(const CoreArgs &args, CoreCtl *c, CoreShared &s)
-        : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), columns_ready(args.columns_ready), tid(threadIdx.x), lane(threadIdx.x & 63),
+        : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), columns_ready(args.columns_ready), epoch((unsigned)args.first_parity), tid(threadIdx.x), lane(threadIdx.x & 63),
           wave(threadIdx.x >> 6), bids(0), depth(0), steps(0), scans(0), whole(0), rests(0) {}
 
     __device__ int gtid() const { return (int)rank * CORE_THREADS + tid; }
@@ -702,7 +703,7 @@ struct Core {
     // that many of them are about to stop deciding bids.
     __device__ __forceinline__ double slack_of(const CoreSide &s, bool &ok, bool *stale)
     {
-        if (gtid() < 3) store_through(&ctl->slack[gtid()], 0ull);
+        if (gtid() < 3) store_through(&ctl->slack[gtid()], 0ull);      // (every stage has a barrier after its last reading of these)
         ok = barrier();
         if (!ok) return 0.0;
         double most = 0.0, rise = 0.0, reach = 0.0;
@@ -738,13 +739,15 @@ struct Core {
     {
         for (int k = gtid(); k < s.len; k += gsize()) store_f64(&s.other_dual[k], word_dual(load_fresh_u64(&s.otherword[k])));
     }
-    __device__ __forceinline__ void begin_lists(int parity, int count)
+    // A step's list of bidders and the next one's; the rings of counts, cleared two steps ahead (see team_steps.h)
+    __device__ __forceinline__ int *bidders(unsigned step) const { return (step & 1u) ? a.list1 : a.list0; }
+    __device__ __forceinline__ void clear_ahead()
     {
-        if (gtid() < 4) {
-            store_i32(&ctl->cnt[gtid()], gtid() == parity ? count : 0);
-            store_u32(&ctl->dense[gtid()], 0u);
-            store_i32(&ctl->whole_count[gtid()], 0);
-        }
+        if (gtid() != 0) return;
+        const unsigned z = step_clears(epoch);
+        store_i32(&ctl->cnt[z], 0);
+        store_i32(&ctl->whole_count[z], 0);
+        store_u32(&ctl->dense[z], 0u);
     }
 
     // (see team_steps.h)
@@ -805,10 +808,9 @@ struct Core {
     __device__ __forceinline__ int leave(int reason, int phase, int stage, int count, int parity);
 };
 
-// Runs one side until at most stop_at bidders are left.  epoch: position in the rings of lists and
-// counters.  Returns 0 (done), or a reason to leave the launch.
+// Runs one side until at most stop_at bidders are left.  Returns 0 (done), or a reason to leave the launch.
 template <bool LARGE>
-__device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, double eps, double slack, int stop_at, bool count_rests, unsigned &epoch,
+__device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, double eps, double slack, int stop_at, bool count_rests,
                         int &count, double &bid_budget)
 {
     const CoreArgs &a = c.a;
@@ -821,10 +823,10 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
     // the second phase of a 20,000 x 20,000 round on lists: 2.1 ms with lines read, 0.12 ms and 0.4 ms of lists so.)
     bool put_off = LARGE;
     while (count > stop_at) {
-        const int *list = ((epoch & 1u) ? a.list1 : a.list0);
-        int *next = ((epoch & 1u) ? a.list0 : a.list1);
-        int *counter = &ctl->cnt[(epoch + 1u) & 3u];
-        if (c.gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); }
+        const int *list = c.bidders(c.epoch);
+        int *next = c.bidders(c.epoch + 1u);
+        int *counter = &ctl->cnt[step_fills(c.epoch)];
+        c.clear_ahead();
         if (c.tid == 0) { c.sh.pushes = 0u; c.sh.dense = 0; }
         __syncthreads();
         // few enough for one die: its chain steps and barriers are shorter
@@ -837,7 +839,7 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
         const bool stuck = stuck_steps >= 16 * a.path_after + 512;
         if (a.path_max > 0 && ((few && few_steps >= a.path_after) || stuck)) {
             const int rc = c.search(s, eps, slack, count, list, next, counter);
-            if (rc == MF_CORE_DENSE || rc == MF_CORE_RELIST) { ++epoch; count = load_fresh_i32(&ctl->cnt[epoch & 3u]); }
+            if (rc == MF_CORE_DENSE || rc == MF_CORE_RELIST) { ++c.epoch; count = load_fresh_i32(&ctl->cnt[step_reads(c.epoch)]); }
             if (rc) return rc;
             few_steps = stuck_steps = 0;
         } else {
@@ -858,13 +860,13 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
             if (count <= CORE_MAX_SOURCES) few_steps += most;
             stuck_steps += most;
             c.flush(next, counter);
-            if (c.tid == 0 && c.sh.dense) atomicAdd(&ctl->dense[(epoch + 1u) & 3u], (unsigned)c.sh.dense);
+            if (c.tid == 0 && c.sh.dense) atomicAdd(&ctl->dense[step_fills(c.epoch)], (unsigned)c.sh.dense);
         }
         if (!c.barrier()) return MF_CORE_ABORT;
-        ++epoch;
-        count = load_fresh_i32(&ctl->cnt[epoch & 3u]);
+        ++c.epoch;
+        count = load_fresh_i32(&ctl->cnt[step_reads(c.epoch)]);
         if (count <= fewest - fewest / 8) { fewest = count; stuck_steps = 0; }
-        const unsigned dense = load_fresh_u32(&ctl->dense[epoch & 3u]);
+        const unsigned dense = load_fresh_u32(&ctl->dense[step_reads(c.epoch)]);
         if (LARGE && put_off) {
             if (count > stop_at && dense > CORE_WAITING && 4u * dense >= (unsigned)count) return MF_CORE_RELIST;
             put_off = dense == 0u || dense > CORE_WAITING;      // (few enough to read their lines)
@@ -966,6 +968,8 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
         const unsigned c = step % 3u, p = (step + 1u) % 3u, z = (step + 2u) % 3u;
         if (tid == 0) { sh.pushes = 0u; sh.sink = CORE_INF; sh.low = CORE_INF; sh.dense = 0; }
         __syncthreads();
+        // (the last step's barrier ended all writing to slot c: this step writes p and z, and a served tree clears them behind
+        // the next barrier.  The nearest sink, [9], moves meanwhile: it only prunes, and decides nothing)
         const unsigned long long words = load_fresh_u64(&ctl->low[min(lane, 12)]);
         auto word_at = [&](unsigned q) {
             return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(words & 0xffffffffull), (int)q) |
@@ -1015,7 +1019,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                     }
                     if (__syncthreads_or(short_of_it) && tid == 0) atomicOr(&ctl->jump_pending[passes], 1u);
                     if (!barrier()) return MF_CORE_ABORT;
-                    if (load_fresh_u32(&ctl->jump_pending[passes]) == 0u) break;
+                    if (load_fresh_u32(&ctl->jump_pending[passes]) == 0u) break;      // (cleared two barriers from here)
                     if (++passes >= CORE_JUMP_PASSES) { lost = true; break; }
                 }
                 int root = -1;
@@ -1122,7 +1126,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                     // rows have been looked at as there are, few searches.  (Made at the start of every
                     // search: 20,000 x 20,000 next round 23.5 / 21.7 ms, 20,000 x 40,000 24.5 / 22.7, matching 14.3 /
                     // 13.7, 4096 x 8192 7.65 / 7.44, smaller ones the same.)
-                    const int n_tree = load_fresh_i32(&ctl->tree_count);
+                    const int n_tree = load_fresh_i32(&ctl->tree_count);       // (this and read_count: complete, and cleared by the next tree)
                     constexpr int STRETCH = 512;
                     int looked = 0;
                     if (!from_columns) {
@@ -1501,25 +1505,25 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
         store_u32(&a.stamp[k], 0u);
     }
     for (int i = gtid(); i < s.lines; i += gsize()) {
-        store_i32(&a.list0[i], i);
+        store_i32(&bidders(epoch)[i], i);
         const int col = load_fresh_i32(&a.row2col[i]);
         store_i32(&a.held_weight[i], col >= 0 ? s.A[(size_t)i * s.pitch + col] : 0);
     }
-    if (gtid() < 3) store_u32(&ctl->failed[gtid()], 0u);
-    begin_lists(0, 0);
+    if (gtid() < 3) store_u32(&ctl->failed[gtid()], 0u);    // (read last before the barriers of the stages since)
     bool ok;
     bool risen;
     const double slack = slack_of(s, ok, &risen);               // (its barriers also end the set-up above)
     if (!ok) return -1;
     int count = s.lines;
     int done = -2;
-    unsigned epoch = 0, whole_lines = 0;
+    unsigned whole_lines = 0;
     int whole_rows = 0, fewest = count, unimproved = 0;
-    for (unsigned round = 1;; ++round, ++epoch) {
-        const int *list = ((epoch & 1u) ? a.list1 : a.list0);
-        int *next = ((epoch & 1u) ? a.list0 : a.list1);
-        int *counter = &ctl->cnt[(epoch + 1u) & 3u];
-        if (gtid() == 0) { store_i32(&ctl->cnt[(epoch + 2u) & 3u], 0); store_u32(&ctl->dense[(epoch + 2u) & 3u], 0u); store_i32(&ctl->whole_count[(epoch + 2u) & 3u], 0); store_u32(&ctl->failed[(round + 1u) % 3u], 0u); }
+    for (unsigned round = 1;; ++round) {
+        const int *list = bidders(epoch);
+        int *next = bidders(epoch + 1u);
+        int *counter = &ctl->cnt[step_fills(epoch)];
+        clear_ahead();
+        if (gtid() == 0) store_u32(&ctl->failed[(round + 1u) % 3u], 0u);
         if (tid == 0) { sh.pushes = 0u; sh.failed = 0u; sh.dense = 0; }
         __syncthreads();
         // (few rows left: a workgroup looks at the rows it has set off itself for some rounds, as in a
@@ -1564,7 +1568,7 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
                     }
                 }
                 if (lane == 0 && profit < outside) {    // the list does not show everything this row might want: all of it, next round
-                    const int at = atomicAdd(&ctl->whole_count[(epoch + 1u) & 3u], 1);
+                    const int at = atomicAdd(&ctl->whole_count[step_fills(epoch)], 1);
                     if (at < s.len) store_i32(&((epoch & 1u) ? a.whole0 : a.whole1)[at], i);
                     else failed = true;
                     atomicAdd(&sh.dense, 1);
@@ -1616,13 +1620,14 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
         if (few) hand_on(next, counter, taken, round);
         else flush(next, counter);
         if (tid == 0 && sh.failed) atomicOr(&ctl->failed[round % 3u], 1u);
-        if (tid == 0 && sh.dense) atomicAdd(&ctl->dense[(epoch + 1u) & 3u], (unsigned)sh.dense);
+        if (tid == 0 && sh.dense) atomicAdd(&ctl->dense[step_fills(epoch)], (unsigned)sh.dense);
         if (!barrier()) return -1;
-        if (load_fresh_u32(&ctl->failed[round % 3u]) != 0u) { done = 0; break; }
-        count = load_fresh_i32(&ctl->cnt[(epoch + 1u) & 3u]);
-        whole_rows = min(load_fresh_i32(&ctl->whole_count[(epoch + 1u) & 3u]), s.len);
+        ++epoch;
+        if (load_fresh_u32(&ctl->failed[round % 3u]) != 0u) { done = 0; break; }        // (the next round writes the other two)
+        count = load_fresh_i32(&ctl->cnt[step_reads(epoch)]);
+        whole_rows = min(load_fresh_i32(&ctl->whole_count[step_reads(epoch)]), s.len);
         if (count + whole_rows == 0) { done = 1; break; }
-        whole_lines += load_fresh_u32(&ctl->dense[(epoch + 1u) & 3u]);
+        whole_lines += load_fresh_u32(&ctl->dense[step_reads(epoch)]);
         if (whole_lines > (unsigned)a.dense_limit) { done = 2; break; }
         // (on the way to a proof fewer and fewer rows are left; once more and more of them are, prices
         // are going round and round)
@@ -1678,18 +1683,14 @@ __device__ __forceinline__ int Core<LARGE>::run()
 {
     const CoreSide &fwd = a.side[0], &rev = a.side[1];
     int ph = a.first_phase, stage = a.first_stage, count = a.first_count;
-    unsigned epoch = (unsigned)a.first_parity;
     int left_rows = 0, left_cols = 0;
     double bid_budget = a.bid_limit;
     bool ok, fresh_lists = stage != MF_CORE_RESET;    // (the launch before this one asked for them)
-    if (stage == MF_CORE_FORWARD || stage == MF_CORE_REVERSE) {
-        begin_lists((int)epoch, count);
-        if (!barrier()) return MF_CORE_ABORT;
-    }
     if (stage == MF_CORE_FORWARD_DONE) left_rows = count;
     if (stage == MF_CORE_REVERSE_DONE) left_cols = count;
     for (;;) {
         const double eps = ctl->eps[ph];
+        // (added to at the end of a forward side: barriers of that side before it, of the next stage after it)
         const int stop = a.rested_before + load_fresh_u64(&ctl->rested) < (unsigned long long)a.growth_rest ? ctl->stop_grown[ph] : ctl->stop[ph];
         if (stage == MF_CORE_RESET && a.use_wide && !a.wide) return leave(MF_CORE_HANDOVER, ph, stage, 0, 0);
         if (stage == MF_CORE_RESET) {
@@ -1698,10 +1699,8 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 store_through(&fwd.otherword[k], pack_word(load_fresh(&fwd.other_dual[k]), 0));
                 store_i32(&a.col2row[k], -1);
             }
-            for (int i = gtid(); i < fwd.lines; i += gsize()) { store_i32(&a.row2col[i], -1); store_i32(&a.list0[i], i); }
-            begin_lists(0, fwd.lines);
+            for (int i = gtid(); i < fwd.lines; i += gsize()) { store_i32(&a.row2col[i], -1); store_i32(&bidders(epoch)[i], i); }
             count = fwd.lines;
-            epoch = 0;
             stage = MF_CORE_FORWARD;                    // (slack_of's barriers end this)
         }
         if (stage == MF_CORE_FORWARD || stage == MF_CORE_REVERSE) {
@@ -1716,7 +1715,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 return leave(MF_CORE_RELIST, ph, stage, count, (int)(epoch & 1u));
             }
             fresh_lists = false;
-            const int rc = run_bids(*this, side, eps, slack, stop, forward, epoch, count, bid_budget);
+            const int rc = run_bids(*this, side, eps, slack, stop, forward, count, bid_budget);
             if (rc) {
                 if (rc != MF_CORE_ABORT) write_duals(side);
                 return leave(rc, ph, stage, count, (int)(epoch & 1u));
@@ -1732,7 +1731,8 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 store_f64(&rev.other_dual[i], 0.0);
                 store_through(&a.rowword[i], 0ull);
             }
-            begin_lists(0, 0);
+            int *next = bidders(epoch + 1u), *counter = &ctl->cnt[step_fills(epoch)];
+            clear_ahead();
             if (tid == 0) sh.pushes = 0u;
             if (!barrier()) return MF_CORE_ABORT;
             for (int k = gtid(); k < fwd.len; k += gsize()) {
@@ -1746,11 +1746,12 @@ __device__ __forceinline__ int Core<LARGE>::run()
                     store_i32(&a.row2col[r], k);
                     store_f64(&rev.other_dual[r], pi);
                     store_through(&a.rowword[r], pack_word(pi, k + 1));
-                } else if (p > 0.0) push(k, a.list0, &ctl->cnt[0]);      // an unassigned column that still carries a price must bid
+                } else if (p > 0.0) push(k, next, counter);      // an unassigned column that still carries a price must bid
             }
-            flush(a.list0, &ctl->cnt[0]);
+            flush(next, counter);
             if (!barrier()) return MF_CORE_ABORT;
-            count = load_fresh_i32(&ctl->cnt[0]);
+            ++epoch;
+            count = load_fresh_i32(&ctl->cnt[step_reads(epoch)]);
             // Every row left over leaves a column unused, too, and columns are as a rule not asked to bid for that:
             // their lists (and, the first time, the transposed matrix) take a millisecond or two.  But an unused column
             // keeps the price a coarser phase drove it to, and with no better way out the first phase that runs to the end
@@ -1778,10 +1779,9 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 }
                 if (!barrier()) return MF_CORE_ABORT;
             }
-            epoch = 0;
             left_cols = count;
             if (count > most_unused) {
-                if (!a.have_columns) return leave(MF_CORE_COLUMNS, ph, MF_CORE_REVERSE, count, 0);
+                if (!a.have_columns) return leave(MF_CORE_COLUMNS, ph, MF_CORE_REVERSE, count, (int)(epoch & 1u));
                 stage = MF_CORE_REVERSE;
                 continue;
             }
@@ -1847,6 +1847,7 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
     ctl->die = -1;
     ctl->joined = 0u; ctl->arrived = 0u; ctl->members = 0u;
     ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
+    for (unsigned q = 0; q < STEP_RING; ++q) { ctl->cnt[q] = 0; ctl->whole_count[q] = 0; ctl->dense[q] = 0u; }
     ctl->columns_ready = 0u;
     ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_groups = 0ull; ctl->rested = 0ull;
 }

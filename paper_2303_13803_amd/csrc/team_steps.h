@@ -15,6 +15,17 @@
 #define MF_STEPS_FN inline
 #endif
 
+// ---- counts kept from one step to the next: a ring of four ----
+// Step e begins with reading its own count, adds to that of e + 1 and clears that of e + 2.  Whoever is late reading
+// meets others in step e, none in e + 1: a barrier is in between.  Every stage of a launch is a step of the same
+// ring, also those that do not bid, and steps are never counted from the start again; the rings are clear when the
+// launch begins.  (Stages used to begin by clearing the whole ring, which could come before somebody's
+// reading of what the stage before had left: bidders left over read as none, or as all of the next phase's.)
+constexpr unsigned STEP_RING = 4;
+MF_STEPS_FN unsigned step_reads(unsigned step) { return step % STEP_RING; }
+MF_STEPS_FN unsigned step_fills(unsigned step) { return (step + 1u) % STEP_RING; }
+MF_STEPS_FN unsigned step_clears(unsigned step) { return (step + 2u) % STEP_RING; }
+
 // ---- new labels for the columns of a served tree ----
 // The scanned rows offer them again: either every scanned row's list is looked through once more, or the lists are kept
 // by column from here on (`make`, which has barriers of its own).  Which, is decided by how many rows all workgroups have

@@ -2,7 +2,8 @@
 // after every barrier until all others have come to the next one.  At each barrier all have to say that they
 // are in the same place.
 //
-//   team_steps RULE     "labels": as the header has it; "labels read late": the count of rows read behind the barrier
+//   team_steps RULE     "labels", "stages": as the header has them; "labels read late": the count of rows read behind the
+//                       barrier; "stages begin anew": every stage clears the whole ring
 #include <stdio.h>
 #include <string.h>
 #include <condition_variable>
@@ -43,10 +44,11 @@ struct Meeting {
 
 struct Shared {
     unsigned long long rows = 0;
+    int ring[STEP_RING] = {0, 0, 0, 0};
 };
 
 // places a barrier can be at
-enum { SERVED = 1, MAKING = 100, OFFERED = 1000 };
+enum { SERVED = 1, MAKING = 100, OFFERED = 1000, BIDDING = 2000, SIDE_DONE = 3000, SETTLED, PHASE, PROVING };
 
 struct Member {
     Meeting &meeting;
@@ -95,33 +97,111 @@ static bool serve_trees(Member &m, bool read_late, unsigned long long most, int 
     return true;
 }
 
+// The stages of a launch as core.hip goes through them, with nothing but their counts: what each step hands on, of how
+// many are left, decides which barriers come next.  Member 0 is the one that clears.
+struct Stages {
+    Member &m;
+    bool anew;
+    unsigned step = 0;
+    std::vector<int> &seen;
+
+    int *ring() { return m.shared.ring; }
+    void add(int n) { __atomic_fetch_add(&ring()[step_fills(step)], n, __ATOMIC_SEQ_CST); }
+    void set(unsigned at, int n) { if (m.number == 0) __atomic_store_n(&ring()[at], n, __ATOMIC_SEQ_CST); }
+    int read()
+    {
+        ++step;
+        seen.push_back(__atomic_load_n(&ring()[step_reads(step)], __ATOMIC_SEQ_CST));
+        return seen.back();
+    }
+    void clear_ahead() { set(step_clears(step), 0); }
+    void begin(int lines)
+    {
+        if (!anew) return;
+        step = 0;
+        for (unsigned q = 0; q < STEP_RING; ++q) set(q, q == 0 ? lines : 0);
+    }
+    bool at(int where) { m.place = where; return m.barrier(); }
+
+    // a side: a quarter of the bidders is handed on by every step
+    bool side(int &count, int stop)
+    {
+        if (!at(PHASE) || !at(PHASE + 1)) return false;
+        for (int k = 0; count > stop; ++k) {
+            clear_ahead();
+            add(count / 16);
+            if (!at(BIDDING + k)) return false;
+            count = read();
+        }
+        return true;
+    }
+    bool run(int lines, int phases)
+    {
+        for (int ph = 0; ph < phases; ++ph) {
+            const int stop = ph == phases - 1 ? 0 : 24 >> ph;
+            int count = lines;
+            begin(lines);
+            if (!side(count, stop)) return false;
+            const int left = count;
+            begin(0);
+            clear_ahead();
+            if (!at(SIDE_DONE)) return false;
+            if (anew) __atomic_fetch_add(&ring()[0], 2 + 4 * ph, __ATOMIC_SEQ_CST);
+            else add(2 + 4 * ph);
+            if (!at(SIDE_DONE + 10)) return false;
+            if (anew) { step = STEP_RING - 1; count = read(); step = 0; }
+            else count = read();
+            if (left > 0 && count > stop && !at(SETTLED)) return false;
+            if (count > stop && !side(count, stop)) return false;
+            if (left == 0 && count == 0) {              // a proof: rounds with fewer and fewer rows
+                begin(0);
+                count = lines;
+                if (!at(PHASE)) return false;
+                for (int round = 0; count > 0 && round < 2 + ph; ++round) {
+                    clear_ahead();
+                    add(count / 16);
+                    if (!at(PROVING + round)) return false;
+                    count = read();
+                }
+            }
+        }
+        return true;
+    }
+};
+
 int main(int argc, char **argv)
 {
     if (argc != 2) return 2;
-    const bool read_late = !strcmp(argv[1], "labels read late");
-    if (!read_late && strcmp(argv[1], "labels")) return 2;
+    const bool read_late = !strcmp(argv[1], "labels read late"), labels = read_late || !strcmp(argv[1], "labels");
+    const bool anew = !strcmp(argv[1], "stages begin anew"), stages = anew || !strcmp(argv[1], "stages");
+    if (!labels && !stages) return 2;
     const int members = 4, trees = 6;
     int together = 0, apart = 0, wrong = 0;
     for (int late = 0; late < members; ++late)
-        for (unsigned long long most = 0; most < 80; ++most) {
+        for (int most = 0; most < 80; ++most) {
             Meeting meeting(members, late);
             Shared shared;
             std::vector<int> made_for(members, 0);
+            std::vector<std::vector<int>> seen(members);
             std::vector<std::thread> team;
             for (int k = 0; k < members; ++k)
                 team.emplace_back([&, k]() {
                     Member m{meeting, shared, k};
                     m.trees = trees;
-                    (void)serve_trees(m, read_late, most, &made_for[k]);
+                    if (labels) (void)serve_trees(m, read_late, (unsigned long long)most, &made_for[k]);
+                    else {
+                        Stages launch{m, anew, 0, seen[k]};
+                        (void)launch.run(64 + 16 * most, 4);
+                    }
                     meeting.leave();
                 });
             for (std::thread &t : team) t.join();
             if (meeting.apart) { ++apart; continue; }
             ++together;
             // a tree adds 2 + 3 + 4 + 5 rows; the last one places the last bidder, and nobody asks for labels
-            int expect = (int)(most / 14) + 2;
+            int expect = labels ? most / 14 + 2 : 0;
             if (expect >= trees) expect = 0;
-            for (int k = 0; k < members; ++k) wrong += made_for[k] != expect;
+            for (int k = 0; k < members; ++k) wrong += made_for[k] != expect || seen[k] != seen[0];
         }
     printf("%d together, %d apart, %d wrong\n", together, apart, wrong);
     return apart == 0 && wrong == 0 ? 0 : 1;

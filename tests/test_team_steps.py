@@ -27,3 +27,13 @@ def test_served_trees_get_their_labels_the_same_way_everywhere(steps):
 def test_a_count_read_behind_the_barrier_sends_members_to_different_barriers(steps):
     done = steps("labels read late")
     assert done.returncode == 1 and int(done.stdout.split(" together, ")[1].split()[0]) > 0, done.stdout
+
+
+def test_stages_go_on_from_the_same_counts_everywhere(steps):
+    done = steps("stages")
+    assert done.returncode == 0, done.stdout
+
+
+def test_stages_that_clear_the_whole_ring_go_on_from_different_counts(steps):
+    done = steps("stages begin anew")
+    assert done.returncode == 1 and int(done.stdout.split(" together, ")[1].split()[0]) > 0, done.stdout
