@@ -3,6 +3,7 @@
 // searches are the successive-shortest-path step of the Hungarian method the paper uses,
 // applied to the few bidders whose chains of bids would otherwise go on for thousands of steps).
 #include "scan.h"
+#include "team_steps.h"
 #include <limits.h>
 
 namespace {
@@ -68,7 +69,7 @@ struct alignas(128) PathCtl {
     struct alignas(128) { unsigned int number; } open;        // barriers completed so far | PATH_GAVE_UP
     alignas(128) unsigned long long steps;
     unsigned long long scans, entries;
-    alignas(128) unsigned int tree_count;                     // columns of the tree being served (list in PathBuffers::tree)
+    alignas(128) unsigned int tree_count[STEP_RING];          // columns of the tree being served (list in PathBuffers::tree), a ring by tree
     // pass q of finding every column's root left some column short of it (zero between uses)
     alignas(128) unsigned int jump_pending[PATH_JUMP_PASSES + 1];
     struct alignas(128) { unsigned int arrive; } group[PATH_MAX_GROUPS];
@@ -138,7 +139,8 @@ __device__ inline bool grid_barrier(PathCtl *ctl, unsigned workgroups, unsigned 
 
 __global__ void path_begin_kernel(mf_device_stats *stats, PathCtl *ctl, int ring)
 {
-    ctl->arrive.count = 0u; ctl->open.number = 0u; ctl->steps = 0ull; ctl->scans = 0ull; ctl->entries = 0ull; ctl->tree_count = 0u;
+    ctl->arrive.count = 0u; ctl->open.number = 0u; ctl->steps = 0ull; ctl->scans = 0ull; ctl->entries = 0ull;
+    for (unsigned q = 0; q < STEP_RING; ++q) ctl->tree_count[q] = 0u;
     for (int q = 0; q <= PATH_JUMP_PASSES; ++q) ctl->jump_pending[q] = 0u;
     for (int g = 0; g < PATH_MAX_GROUPS; ++g) ctl->group[g].arrive = 0u;
     stats->cnt[(ring + 1) & 3] = 0;
@@ -276,6 +278,7 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
     double width = 4.0 * s.eps;
     const int segment = wg / PATH_GROUP % PATH_SEGMENTS;
     unsigned step = 0, since_served = 0;
+    unsigned tree = 0;                       // trees served (steps of a ring of their own, see team_steps.h)
     bool swept = false;                      // the previous step was a pass over all columns
     bool from_bidders = true;                // this step scans the bidders themselves (the first, and the one after a re-assignment)
     bool sweep_next = false;                 // ... and the step after that looks at every column
@@ -371,19 +374,21 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
                                 store_through((unsigned long long *)&buf.base[holder], (unsigned long long)__double_as_longlong(PATH_FAR));
                             const unsigned slot = atomicAdd(&s_pushes, 1u);
                             if (slot < (unsigned)PATH_PUSH_BUFFER) s_list[slot] = (unsigned long long)k;
-                            else __hip_atomic_store(&buf.tree[atomicAdd(&ctl->tree_count, 1u)], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            else __hip_atomic_store(&buf.tree[atomicAdd(&ctl->tree_count[step_fills(tree)], 1u)], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
                     }
                 }
                 __syncthreads();
                 if (pull) {
                     const unsigned mine = min(s_pushes, (unsigned)PATH_PUSH_BUFFER);
-                    if (tid == 0) s_base = mine ? atomicAdd(&ctl->tree_count, mine) : 0u;
+                    if (tid == 0) s_base = mine ? atomicAdd(&ctl->tree_count[step_fills(tree)], mine) : 0u;
                     __syncthreads();
                     for (unsigned t = tid; t < mine; t += PATH_THREADS)
                         __hip_atomic_store(&buf.tree[s_base + t], (int)s_list[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (gtid == 0)          // the bidder itself is no root any more
+                    if (gtid == 0) {        // the bidder itself is no root any more
+                        __hip_atomic_store(&ctl->tree_count[step_clears(tree)], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         store_through((unsigned long long *)&buf.base[s_row[root]], (unsigned long long)__double_as_longlong(PATH_FAR));
+                    }
                 }
                 if (!grid_barrier(ctl, G, generation, spin_limit)) { ok = false; break; }
                 if (wg == 0) {
@@ -455,11 +460,12 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
                 far_bound = farthest_rest();
                 since_served = 0;
                 --step;                                                // this was no step: the slots keep their turn
+                ++tree;
                 if (!pull) { from_bidders = true; sweep_next = false; swept = false; continue; }
                 if (n_alive > 0) {
                     // ---- new labels for the served tree's columns: one wavefront per column looks at
                     // every row that has been scanned (and at the bidders) in the other copy of the matrix ----
-                    const unsigned n_tree = load_fresh_u32(&ctl->tree_count);
+                    const unsigned n_tree = load_fresh_u32(&ctl->tree_count[step_reads(tree)]);
                     constexpr int WAVES = PATH_THREADS / 64;
                     const int lane = tid & 63;
                     for (unsigned it = (unsigned)(wg * WAVES + (tid >> 6)); it < n_tree; it += G * WAVES) {
@@ -489,7 +495,6 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
                         }
                     }
                 }
-                if (gtid == 0) __hip_atomic_store(&ctl->tree_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (!grid_barrier(ctl, G, generation, spin_limit)) { ok = false; break; }
                 from_bidders = false; sweep_next = true; swept = false;    // next: a pass over all columns picks them up
                 continue;

@@ -3,7 +3,8 @@
 // are in the same place.
 //
 //   team_steps RULE     "labels", "stages": as the header has them; "labels read late": the count of rows read behind the
-//                       barrier; "stages begin anew": every stage clears the whole ring
+//                       barrier; "stages begin anew": every stage clears the whole ring; "cleared when read":
+//                       the member that clears does so with a count it has just read
 #include <stdio.h>
 #include <string.h>
 #include <condition_variable>
@@ -101,7 +102,7 @@ static bool serve_trees(Member &m, bool read_late, unsigned long long most, int 
 // many are left, decides which barriers come next.  Member 0 is the one that clears.
 struct Stages {
     Member &m;
-    bool anew;
+    bool anew, when_read;
     unsigned step = 0;
     std::vector<int> &seen;
 
@@ -112,6 +113,7 @@ struct Stages {
     {
         ++step;
         seen.push_back(__atomic_load_n(&ring()[step_reads(step)], __ATOMIC_SEQ_CST));
+        if (when_read) set(step_reads(step), 0);
         return seen.back();
     }
     void clear_ahead() { set(step_clears(step), 0); }
@@ -173,7 +175,8 @@ int main(int argc, char **argv)
 {
     if (argc != 2) return 2;
     const bool read_late = !strcmp(argv[1], "labels read late"), labels = read_late || !strcmp(argv[1], "labels");
-    const bool anew = !strcmp(argv[1], "stages begin anew"), stages = anew || !strcmp(argv[1], "stages");
+    const bool anew = !strcmp(argv[1], "stages begin anew"), when_read = !strcmp(argv[1], "cleared when read");
+    const bool stages = anew || when_read || !strcmp(argv[1], "stages");
     if (!labels && !stages) return 2;
     const int members = 4, trees = 6;
     int together = 0, apart = 0, wrong = 0;
@@ -190,7 +193,7 @@ int main(int argc, char **argv)
                     m.trees = trees;
                     if (labels) (void)serve_trees(m, read_late, (unsigned long long)most, &made_for[k]);
                     else {
-                        Stages launch{m, anew, 0, seen[k]};
+                        Stages launch{m, anew, when_read, 0, seen[k]};
                         (void)launch.run(64 + 16 * most, 4);
                     }
                     meeting.leave();

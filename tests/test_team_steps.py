@@ -34,6 +34,7 @@ def test_stages_go_on_from_the_same_counts_everywhere(steps):
     assert done.returncode == 0, done.stdout
 
 
-def test_stages_that_clear_the_whole_ring_go_on_from_different_counts(steps):
-    done = steps("stages begin anew")
+@pytest.mark.parametrize("rule", ["stages begin anew", "cleared when read"])
+def test_counts_cleared_before_everybody_has_read_them(steps, rule):
+    done = steps(rule)
     assert done.returncode == 1 and int(done.stdout.split(" together, ")[1].split()[0]) > 0, done.stdout
