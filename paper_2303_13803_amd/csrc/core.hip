@@ -23,6 +23,7 @@
 // 12,000 x 16,000 29.8 / 26.6, 20,000 x 20,000 29.6 / 24.5; 20,000 x 40,000 with prefixes of a tenth
 // 21.6 / 20.8.  The line is drawn at 8192 rows.
 #include "scan.h"
+#include "half_list.h"
 #include "search_words.h"
 #include "team_join.h"
 #include "team_steps.h"
@@ -422,6 +423,23 @@ struct TeamMemory {
     __device__ __forceinline__ void settle() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 };
 
+struct WaveLanes {                      // for half_list.h: a value a lane
+    typedef double Values;
+    typedef int Keys;
+    __device__ __forceinline__ int keys(double v, double outside) const { return __float_as_int((float)fmax(v - outside, 0.0)); }
+    __device__ __forceinline__ double distance(int key) const { return (double)__int_as_float(key); }
+    __device__ __forceinline__ int largest(int key) const { return wave_max(key); }
+    __device__ __forceinline__ unsigned long long equal(int key, int to) const { return __ballot(key == to); }
+    __device__ __forceinline__ bool in(unsigned long long lanes) const { return (lanes >> (threadIdx.x & 63u)) & 1ull; }
+    __device__ __forceinline__ double largest_among(double v, unsigned long long lanes) const { return wave_max(in(lanes) ? v : NEG_HUGE); }
+    __device__ __forceinline__ unsigned long long equal_among(double v, double to, unsigned long long lanes) const { return __ballot(v == to) & lanes; }
+    __device__ __forceinline__ int without(int key, int lane) const { return (int)(threadIdx.x & 63u) == lane ? 0 : key; }
+    __device__ __forceinline__ double at(double v, int lane) const
+    {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+    }
+};
+
 struct SharedWords {                    // (the bits of doubles that are not negative are in the doubles' order)
     __device__ __forceinline__ void set(unsigned long long *p, unsigned long long v) const { store_through(p, v); }
     __device__ __forceinline__ void set(double *p, double v) const { store_f64(p, v); }
@@ -595,10 +613,7 @@ struct Core {
     // (nine bids in ten); and who will be evicted is known from the words, before the bid is made, unless
     // another wavefront gets in between: his list is on its way while the bid is.  The first bids of a 20,000 x
     // 20,000 phase 236 -> 187 us, its last 570 bidders 820 -> 627 us; a matching 15.3 -> 14.5 ms, next round 24.2 -> 23.3.
-    // A maximum of doubles is a dozen dependent instructions of eight cycles and more, one of integers half a
-    // dozen of four: the two best are found from the distances above that bound as floats (their bits are in
-    // their order).  Where floats do not tell the best apart the doubles do; the second best may be taken
-    // for a little more than it is, up to the best (the bid is that much lower, and at least an epsilon up).
+    // The two best are found as half_list.h says.
     // waiting: if it is -1 a bidder whose whole list no longer decides does not have his line read but goes there.
     __device__ __forceinline__ int bid(const CoreSide &s, int b, Half &h, double eps, double slack, bool count_rests, int &waiting)
     {
@@ -606,26 +621,18 @@ struct Core {
         const unsigned long long word = load_fresh_u64(&s.otherword[h.e.x]);
         ++bids;
         const double v = fma(a.Kd, (double)h.e.y, -word_dual(word));
-        const int key = (int)__float_as_uint((float)fmax(v - outside, 0.0)), top = wave_max(key);
-        unsigned long long hit = __ballot(key == top);
-        Top2 t;
-        if (hit & (hit - 1ull)) {                           // (or none is worth more than `outside`)
-            const double most = wave_max(key == top ? v : NEG_HUGE);
-            hit = __ballot(key == top && v == most);
-            // among tied lanes the first at or after a lane that depends on the bidder
-            const unsigned turn = (unsigned)tie_salt(b) & 63u;
-            const unsigned long long turned = hit & (~0ull << turn);
-            hit = turned ? turned : hit;
-        }
-        const int src = __ffsll((long long)hit) - 1;
+        const WaveLanes lanes;
+        const int key = lanes.keys(v, outside);
+        int top, second;
+        const int src = best_lane(lanes, v, key, (unsigned)tie_salt(b) & 63u, &top);
         int guess = __builtin_amdgcn_readlane(word_id(word), src);
         Half ahead = h;
         if (guess >= 0) ahead = half_of(s, guess);
-        t.b1 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
+        Top2 t;
+        t.b1 = lanes.at(v, src);
         t.idx = __builtin_amdgcn_readlane(h.e.x, src);
         t.w = __builtin_amdgcn_readlane(h.e.y, src);
-        const int second = wave_max(lane == src ? 0 : key);
-        t.b2 = fmin(t.b1, ceil(outside + (double)(__uint_as_float((unsigned)second) * (1.0f + 0x1p-22f))));
+        t.b2 = next_value(lanes, v, key, src, outside, &second);
         if ((top == 0 || second == 0) && outside > 0.0) {
             guess = -1;
             t = listed(s, b, slack, &outside);
