@@ -306,9 +306,9 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *   "warm_reset_cols"  1 (default): such a start takes replaced columns at price 0
  *
  * TUNING (defaults were measured on the benchmark rounds; names and meanings may change with
- * the kernels they steer; every setting leaves the result exactly optimal).  A context on which one of them, or of the
- * options above other than "max_rounds", "score_split" and "fit_order", has been set matches with the kernels they
- * steer at every size; any other matches up to about a hundred rows in one compute unit, which none of them concerns:
+ * the kernels they steer; every setting leaves the result exactly optimal).  While one of them, or of the options
+ * above other than "max_rounds", "score_split" and "fit_order", differs from its default, a context matches with the
+ * kernels they steer at every size; else up to about a hundred rows in one compute unit, which none of them concerns:
  *   phases   "phase_stop" (16) / "phase_keep" (4) / "phase_growth" (2): either side of a phase that
  *            only prepares prices ends once at most phase_stop bidders are unplaced (times
  *            phase_growth per phase before, while fewer than "phase_growth_rest" (32) bidders have

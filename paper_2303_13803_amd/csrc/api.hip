@@ -140,59 +140,12 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) return MF_ERR_HIP;
     if (hipSetDevice(device) != hipSuccess) return MF_ERR_HIP;
-    mf_ctx *ctx = new (std::nothrow) mf_ctx();
+    mf_ctx *ctx = new (std::nothrow) mf_ctx();         // (options at their defaults, the rest cleared)
     if (!ctx) return MF_ERR_HIP;
-    memset(ctx, 0, sizeof(*ctx));
     ctx->device = device;
     ctx->stream = (hipStream_t)hip_stream;
     ctx->max_n = max_n;
     ctx->max_m = max_m;
-    ctx->theta = 24;
-    ctx->max_rounds = 4000000000ll;
-    ctx->tail_max = 1024;
-    ctx->round_lag = 1;
-    ctx->score_split = 1;
-    ctx->phase_stop = 16;
-    ctx->phase_keep = 4;
-    ctx->phase_growth = 2;
-    ctx->phase_growth_rest = 32;
-    ctx->final_jump = 0;
-    ctx->phase_tail_steps = 64;
-    ctx->phase_tail_sides = 1;
-    ctx->phase_tail_from = 8192;
-    ctx->warm_eps_units = 0;
-    ctx->warm_reset_cols = true;
-    ctx->chain_grid = 256;
-    ctx->bulk_shape = 1;
-    ctx->bulk_grid = 0;
-    ctx->bulk_share = 95;
-    ctx->team_max = 8;
-    ctx->team_size = 16;
-    ctx->team_wide = 64;
-    ctx->team_regroup = 128;
-    ctx->team_threads = 1024;
-    ctx->fit_order = true;
-    ctx->fit_prefix = true;
-    ctx->fit_prefix_below = 50;
-    ctx->edge_lists_from = 4096;
-    ctx->path_max = 16;
-    ctx->path_width = 1024;
-    ctx->path_frontier_rows = 1024;
-    ctx->path_pull = false;
-    ctx->path_grid = 0;
-    ctx->path_after = 256;
-    ctx->path_spin_limit = 1u << 22;
-    ctx->core = 1;
-    ctx->core_depth_eps = 20;
-    ctx->core_many = 4;
-    ctx->core_few = 32;
-    ctx->core_after = 256;
-    ctx->core_refine = 200;
-    ctx->core_wide = 8192;
-    ctx->core_narrow = 1024;
-    ctx->core_width = 8192;
-    ctx->core_read = 25;
-    ctx->core_read_least = 8ll << 20;
     {
         hipDeviceProp_t prop;
         ctx->n_cus = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.multiProcessorCount : 0;
@@ -448,9 +401,7 @@ int mf_schedule_round_update(mf_ctx *ctx, const mf_predictor *pred, const float 
 int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
 {
     if (!ctx || !name) return MF_ERR_ARG;
-    const int rc = set_option(ctx, name, value);
-    if (rc == MF_OK && strcmp(name, "max_rounds") && strcmp(name, "score_split") && strcmp(name, "fit_order")) ctx->as_told = true;
-    return rc;
+    return set_option(ctx, name, value);
 }
 
 int mf_last_timings(mf_ctx *ctx, float what[16])

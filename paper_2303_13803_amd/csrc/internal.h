@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <tuple>
 #include "muxmatch.h"
 
 #define MF_HIP(call)                                                            \
@@ -71,7 +72,71 @@ struct mf_cert_out {                // lives in device memory, cleared per check
     int bids, scans, status;        // of a matching by small_kernel, which begins the check in the same launch
 };
 
-struct mf_ctx {
+// What mf_set_option sets, with the defaults.
+struct mf_options {
+    int64_t theta = 24;                         // epsilon divisor per phase
+    int64_t max_rounds = 4000000000ll;          // limit on evaluated bids per solve
+    int fit_prefix_below = 50;                  // percent of pairs that can share below which the solve uses the staged matrix
+    int edge_lists_from = 4096;                 // rows from which a matrix the caller brought is turned into lists when few pairs are feasible (0: never)
+    bool fit_prefix = true;                     // solve on the staged matrix, reading only the prefixes that can share
+    bool fit_order = true;                      // score in memory order and skip pairs that cannot fit
+    bool warm_reset_cols = true;                // start replaced columns at price 0 instead of their predecessor's price
+    int64_t warm_eps_units = 0;                 // first epsilon of a warm-started solve, in weight units
+    int phase_stop = 16;                        // unplaced bidders at or below which a phase that only prepares prices ends
+    int phase_growth = 2;                       // ... times this for every phase further from the ones that run to the end
+    int phase_growth_rest = 32;                 // bidders that may have given up before coarse phases stop leaving more
+    int phase_keep = 4;                         // the last so many phases always run to the end
+    long long phase_tail_steps = 64;            // dependent chain steps after which a side that only prepares prices ends (0: no limit)
+    int phase_tail_from = 8192;                 // ... for problems with at least this many bidding lines
+    int phase_tail_sides = 1;                   // ... on which sides: bit 0 the first (rows bid), bit 1 the second
+    long long final_jump = 0;                   // epsilon (weight units) at or below which the next phase is the last (0: never)
+    int tail_max = 1024;                        // bidder count at or below which chains are followed in one kernel
+    int bulk_grid = 0;                          // most workgroups of a round with many bidders (0: one per group of lines, up to 8192)
+    int bulk_shape = 1;                         // workgroup shape of rounds with many bidders (see launch_round)
+    int bulk_share = 95;                        // ... "many": at least 2048 and this share (percent) of the side's lines
+    int team_max = 8;                           // chains at or below which several workgroups share each chain (0: never)
+    int team_size = 16, team_threads = 1024;    // most workgroups per chain, threads per such workgroup
+    int team_wide = 64;                         // chains at or below which smaller teams already take over from chain_kernel
+    long long team_regroup = 128;               // steps after which such teams stop so that the chains left can be regrouped
+    int path_max = 16;                          // bidders at or below which shortest-path searches place them (0: never)
+    long long path_after = 256;                 // chain steps per run after which the searches take over
+    int path_grid = 0;                          // workgroups of a search (0: one per compute unit)
+    int path_width = 1024;                      // label window of one super-step, in epsilons
+    bool path_pull = false;                     // re-label a served tree's columns from the other copy of the matrix
+    int path_frontier_rows = 1024;              // frontier above which the window is halved (doubled below an eighth of it)
+    unsigned path_spin_limit = 1u << 22;        // polls a workgroup waits at a barrier of the search before it gives up
+    int chain_grid = 256;                       // workgroups of chain_kernel
+    int core = 1;                               // 0: no phases on short lists (core.hip)
+    int core_depth_eps = 20;                    // how many epsilons the lists have to reach below a line's best value
+    int core_many = 4, core_few = 32;           // chain steps between two looks at the list, with more / fewer bidders than wavefronts
+    long long core_after = 256;                 // chain steps after which the last bidders are searched for
+    int core_wide = 8192, core_narrow = 1024;   // lines from which the wide parts run on all dies; bidders at or below which one die takes over
+    int core_read = 25;                         // percent of the matrix one search on lists may read whole, ...
+    long long core_read_least = 8ll << 20;      // ... or so many entries if they are more
+    int core_refine = 200;                      // epsilon (weight units) at or below which a complete phase is followed by a refinement
+    int core_width = 8192;                      // label window of a search on lists, in epsilons
+    int score_split = 1;                        // 1: the scorer's hidden layer multiplies fp16 pieces of its fp32 operands
+    int round_lag = 1;                          // 1: bulk rounds are launched one ahead of the host's reads
+
+    auto how_to_match() const
+    {
+        return std::tie(theta, fit_prefix_below, edge_lists_from, fit_prefix, warm_reset_cols, warm_eps_units, phase_stop, phase_growth,
+                        phase_growth_rest, phase_keep, phase_tail_steps, phase_tail_from, phase_tail_sides,
+                        final_jump, tail_max, bulk_grid, bulk_shape, bulk_share, team_max, team_size, team_threads,
+                        team_wide, team_regroup, path_max, path_after, path_grid, path_width, path_pull,
+                        path_frontier_rows, path_spin_limit, chain_grid, core, core_depth_eps, core_many, core_few,
+                        core_after, core_wide, core_narrow, core_read, core_read_least, core_refine, core_width,
+                        round_lag);
+    }
+    // Whether one that says how to match differs from its default: small problems are then matched that way, too.
+    bool as_told() const
+    {
+        const mf_options defaults;
+        return how_to_match() != defaults.how_to_match();
+    }
+};
+
+struct mf_ctx : mf_options {
     int device;
     hipStream_t stream;
     int max_n, max_m;
@@ -87,42 +152,20 @@ struct mf_ctx {
     int32_t *staged;                // [max_n][pad4(max_m)] the last scored matrix with rows and columns in memory order
     int32_t *fit_len_on, *fit_len_off;   // per staged row / column: how many entries from the start can share
     unsigned long long *feasible_pairs, *h_feasible_pairs;    // how many pairs of the staged matrix can share (device, pinned)
-    int fit_prefix_below;           // percent of pairs that can share below which the solve uses the staged matrix
     int *edge_count;                // [max(max_n, max_m)] feasible pairs per row of a matrix the caller brought, padded to 4
     long long *edge_start;          // [max(max_n, max_m) + 1] where each row's list starts
-    int edge_lists_from;            // rows from which such a matrix is turned into lists when few pairs are feasible (0: never)
     int staged_n, staged_m;         // shape of the staged matrix the solver may use (0: none)
     int *largest_weight;            // largest weight of the matrix just scored (device), noted while it was put in place
     bool largest_weight_known;      // ... and whether it is that of the matrix the staged copy belongs to
     int32_t *type_segment;          // [MF_MAX_TYPES + 1] first position of each type in order_on
     unsigned long long *pairs_evaluated, *h_pairs_evaluated;   // pairs the last scoring pass ran the MLP on (device, pinned)
     double pairs_total;             // ... out of this many
-    bool fit_prefix;                // solve on the staged matrix, reading only the prefixes that can share
-    bool fit_order;                 // score in memory order and skip pairs that cannot fit
     // solver scratch
     int32_t *wt;                    // transposed weights [max_m][ldt]
     double *price, *profit;         // [max_m+4], [max_n+4]: exact integers held in doubles
     unsigned long long *colword, *roword;
     int *row2col, *col2row;
     int warm_n, warm_m;             // shape of the solve whose prices the context still holds (0: none)
-    bool warm_reset_cols;           // start replaced columns at price 0 instead of their predecessor's price
-    int64_t warm_eps_units;         // first epsilon of a warm-started solve, in weight units
-    int phase_stop;                 // unplaced bidders at or below which a phase that only prepares prices ends
-    int phase_growth;               // ... times this for every phase further from the ones that run to the end
-    int phase_growth_rest;               // bidders that may have given up before coarse phases stop leaving more
-    int phase_keep;                 // the last so many phases always run to the end
-    long long phase_tail_steps;     // dependent chain steps after which a side that only prepares prices ends (0: no limit)
-    int phase_tail_from;            // ... for problems with at least this many bidding lines
-    int phase_tail_sides;           // ... on which sides: bit 0 the first (rows bid), bit 1 the second
-    long long final_jump;           // epsilon (weight units) at or below which the next phase is the last (0: never)
-    int tail_max;                   // bidder count at or below which chains are followed in one kernel
-    int bulk_grid;                  // most workgroups of such a round (0: one per group of lines, up to 8192)
-    int bulk_shape;                 // workgroup shape of rounds with many bidders (see launch_round)
-    int bulk_share;                 // ... "many": at least 2048 and this share (percent) of the side's lines
-    int team_max;                   // chains at or below which several workgroups share each chain (0: never)
-    int team_size, team_threads;    // most workgroups per chain, threads per such workgroup
-    int team_wide;                  // chains at or below which smaller teams already take over from chain_kernel
-    long long team_regroup;         // steps after which such teams stop so that the chains left can be regrouped
     bool team_off;                  // set after a team wait ran out, for the rest of the solve
     int fallbacks;                  // MF_FALLBACK_* bits of the running solve
     void *team_ctl;                 // control blocks of the cooperating workgroups
@@ -134,27 +177,10 @@ struct mf_ctx {
     double *path_base;              // per bidding line: length of the shortest path to it plus what it would pay, or +inf
     int *path_tree;                 // columns of the tree being served
     int *path_parent, *path_jump;   // [max(max_n, max_m)] each: predecessor columns while a tree is served
-    int path_max;                   // bidders at or below which shortest-path searches place them (0: never)
-    long long path_after;           // chain steps per run after which the searches take over
-    int path_grid;                  // workgroups of a search (0: one per compute unit)
-    int path_width;                 // label window of one super-step, in epsilons
-    bool path_pull;                 // re-label a served tree's columns from the other copy of the matrix
-    int path_frontier_rows;         // frontier above which the window is halved (doubled below an eighth of it)
-    unsigned path_spin_limit;       // polls a workgroup waits at a barrier of the search before it gives up
     bool path_off;                  // set after a wait of the search ran out, for the rest of the solve
     int n_cus;                      // compute units of the device
-    int chain_grid;                 // workgroups of that kernel
     // phases on short lists (core.hip)
-    int core;                       // 0: never
-    int core_depth_eps;             // how many epsilons the lists have to reach below a line's best value
-    int core_many, core_few;        // chain steps between two looks at the list, with more / fewer bidders than wavefronts
-    long long core_after;           // chain steps after which the last bidders are searched for
-    int core_wide, core_narrow;     // lines from which the wide parts run on all dies; bidders at or below which one die takes over
-    int core_read;                  // percent of the matrix one search on lists may read whole, ...
-    long long core_read_least;      // ... or so many entries if they are more
-    int core_refine;                // epsilon (weight units) at or below which a complete phase is followed by a refinement
     int2 *core_entries[2];          // lists of the rows (of the side with fewer lines), of the columns
-    int core_width;                 // label window of a search on lists, in epsilons
     double *core_bound[2], *core_half_bound[2], *core_built[2], *core_reach[2], *core_depth, *h_core_depth;
     int *core_t_start[2], *core_t_at[2], *core_tree;    // the lists by opposite line (searches)
     int2 *core_t_entries[2];
@@ -171,12 +197,7 @@ struct mf_ctx {
     mf_device_stats *h_stats_slot[2];   // pinned: where the counts of bulk rounds land while the next round runs
     hipEvent_t ev_stats[2];
     unsigned *score_range;              // device: largest magnitudes the scorer's fp16 pieces are scaled by (project_kernel)
-    int score_split;                    // 1: the scorer's hidden layer multiplies fp16 pieces of its fp32 operands
-    int round_lag;                      // 1: bulk rounds are launched one ahead of the host's reads
     mf_cert_out *h_cert;
-    // options
-    int64_t theta, max_rounds;
-    bool as_told;                   // an option says how to match: small problems are then matched that way too
     // timing
     hipEvent_t ev[10];              // 0..2 and 8: scoring stages; 3..7 and 9: solver stages
     float timings[T_COUNT];

@@ -283,7 +283,7 @@ bool mf_small_fits(const mf_ctx *ctx, int n, int m)
     int columns = 0;
     const SmallShape s = small_shape(n, m, 0, &columns);
     const bool few = s.n <= SMALL_ROWS || (s.n <= SMALL_ROWS_WIDE && 3 * s.m >= 4 * s.n && s.m <= SMALL_COLS_WIDE);
-    return !ctx->as_told && n <= m && few && s.m <= SMALL_COLS && small_bytes(s, columns) <= (size_t)SMALL_LDS;
+    return !ctx->as_told() && n <= m && few && s.m <= SMALL_COLS && small_bytes(s, columns) <= (size_t)SMALL_LDS;
 }
 
 // Leaves row2col, u, v with the caller and ctx->cert and ctx->colmark ready for the certificate.

@@ -21,7 +21,7 @@ INF = synth.INFEASIBLE
                                              (300, 131, 2 ** 20, 0.3), (257, 1025, 2 ** 24, 0.5), (512, 513, 255, 0.1),
                                              (640, 640, 3, 0.0), (200, 2051, 1, 0.0), (1000, 1000, 2 ** 24, 0.95),
                                              (100, 4097, 2 ** 24, 0.2), (64, 8193, 2 ** 20, 0.6), (30, 20483, 2 ** 24, 0.2)])
-@pytest.mark.parametrize("options", [{}, {"core_depth": 0}, {"core_depth": 0, "core_after": 0, "core_width": 1}, {"core_refine": 0},
+@pytest.mark.parametrize("options", [{"core_many": 5}, {"core_depth": 0}, {"core_depth": 0, "core_after": 0, "core_width": 1}, {"core_refine": 0},
                                      {"core_depth": 0, "core_wide": 1, "core_narrow": 16}])
 def test_phases_on_lists_reach_the_optimum(orc, n, m, high, masked, options):
     import paper_2303_13803_amd as mm

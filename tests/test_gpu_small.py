@@ -1,5 +1,5 @@
 """Problems matched in one compute unit (GPU): against the oracle and against the auction, which a context with a
-tuning option set (to its default here) uses at every size."""
+tuning option that differs from its default uses at every size."""
 import numpy as np
 import pytest
 import torch
@@ -48,11 +48,27 @@ def _kinds(n, m):
 def test_one_compute_unit_finds_the_optimum(orc, n, m):
     for name, W in _kinds(n, m):
         res, did = _solve(orc, W, {})
-        other, _ = _solve(orc, W, {"theta": 24})
+        other, _ = _solve(orc, W, {"theta": 25})
         assert res.primal == other.primal, name
         here = n <= m <= 512 and (n <= 88 or (n <= 112 and 4 * n <= 3 * m <= 768)) and n * m < 38000         # 152 KB of LDS
         assert (res.rounds == 0 and did["list_launches"] == 0) == here, name
         assert not here or res.bytes_scanned == 4 * n * m and res.phases == 1, name
+
+
+def test_an_option_counts_while_it_differs_from_its_default(orc):
+    import paper_2303_13803_amd as mm
+    W = synth.uniform_matrix(87, 64, 64, 2 ** 20, 0.1)
+    expect, device = orc.max_weight_matching(W)[0], padded_matrix(W)
+    r2c = torch.empty(64, dtype=torch.int32, device="cuda")
+    u, v = (torch.empty(64, dtype=torch.int64, device="cuda") for _ in range(2))
+    ctx = mm.Context(64, 64)
+    for name, value, here in [("theta", 24, True), ("warm_reset_cols", 1, True), ("theta", 25, False), ("core_few", 33, False),
+                              ("theta", 24, False), ("core_few", 32, True), ("fit_prefix", 0, False), ("fit_prefix", 1, True)]:
+        ctx.set_option(name, value)
+        res = ctx.solve_assignment(device, 64, 64, r2c, u, v)
+        assert res.primal == expect and res.cert_ok == 1
+        assert (ctx.last_timings()["list_launches"] == 0) == here, (name, value)
+    ctx.close()
 
 
 @pytest.mark.parametrize("largest", [2 ** 28 - 1, 2 ** 28, 2 ** 31 - 1])
