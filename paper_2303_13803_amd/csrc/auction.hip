@@ -760,8 +760,13 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     return MF_OK;
 }
 
-// Lists made for one side of one phase before it is finished on whole lines.
-constexpr int CORE_MOST_LISTS = 64;
+// Lists made for one side of one phase before it is finished on whole lines.  Where launches run on all dies most are made of
+// the waiting lines alone, and a side of a round needs 10 to 20: with 4, 8, 12, 16, 24, 64 of them auctions of
+// thirteen 20,000 x 20,000 rounds take 20.2, 19.8, 19.3, 17.9, 17.3, 17.5 ms.  Where one die does it all they are made of
+// every line, and a side that wants a fifth wants dozens: 6000 rows that rank 6000 columns nearly alike take 42, 44, 51,
+// 64, 139 ms with 2, 4, 8, 16, 64 (1500 of them 19, 22, 26, 39, 20), rounds and masked matrices of 100 to 6000 rows, which
+// make fewer, the same with any.
+constexpr int CORE_MOST_LISTS = 4, CORE_MOST_LISTS_WIDE = 24;
 
 // The rest of a solve, from phase `ph`, on lists of every line's best entries (core.hip): one launch
 // unless lists have to be made (again) or a side has to be finished on whole lines.  *after: n_phases
@@ -813,7 +818,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
             continue;
         }
         if (st.phase != at_phase || st.stage != at_stage) { at_phase = st.phase; at_stage = st.stage; lists_made = 0; }
-        if (st.reason == MF_CORE_COLUMNS || (st.reason == MF_CORE_RELIST && ++lists_made <= CORE_MOST_LISTS)) {
+        if (st.reason == MF_CORE_COLUMNS || (st.reason == MF_CORE_RELIST && ++lists_made <= (plan.use_wide ? CORE_MOST_LISTS_WIDE : CORE_MOST_LISTS))) {
             if (!forward && !have_transpose) make_transpose();
             const int lines = forward ? rn : rm;
             if (st.reason == MF_CORE_RELIST && st.stage != MF_CORE_PHASE_DONE && st.wide && st.count < lines / 2) {

@@ -134,6 +134,23 @@ def test_bidders_that_wait_for_better_lists(orc, n, m, masked):
     assert t["lists_made"] > 4
 
 
+def test_lists_of_every_line_are_not_made_for_ever(orc):
+    """Rows that rank the columns nearly alike: lists sink as soon as they are made, and the side goes on on whole lines
+    (where one die does it all 66 lists were made of a phase's two sides, and the solve took three times as long)."""
+    import paper_2303_13803_amd as mm
+    n = 6000
+    W = (2 ** 20 - 7 * np.arange(n)[None, :] + np.random.default_rng(76).integers(0, 3000, (n, n))).astype(np.int32)
+    ctx = mm.Context(n, n)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = (torch.empty(n, dtype=torch.int64, device="cuda") for _ in range(2))
+    res = ctx.solve_assignment(padded_matrix(W), n, n, r2c, u, v)
+    did = ctx.last_timings()
+    ctx.close()
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.fallbacks == 0 and res.primal == P
+    assert did["list_launches"] > 0 and did["lists_made"] <= 8 * res.phases
+
+
 @pytest.mark.parametrize("n,m", [(100, 128), (128, 128), (90, 64)])
 def test_counters_of_a_solve_on_lists(n, m):
     """Lines no longer than a list: the whole solve runs on lists, every bid and every scan of a search or a proof
