@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import synth
-from gpu_util import padded_matrix
+from gpu_util import assert_weights_close, padded_matrix
 
 pytestmark = pytest.mark.gpu
 
@@ -90,6 +90,34 @@ def test_it_stops_at_the_limit_on_bids(orc):
         with pytest.raises(mm.MuxmatchError) as e:
             _solve(orc, W, {"max_rounds": limit})
         assert e.value.code == mm.ERR_NOT_CONVERGED
+
+
+@pytest.mark.parametrize("law,n,m,hidden", [("C4", 40, 61, (128, 64, 128)), ("C3", 88, 130, (64, 128)), ("C5", 7, 500, (128, 128, 64, 64)), ("C1", 64, 64, (64,))])
+def test_its_typed_rounds_score_pairs_as_they_come(orc, law, n, m, hidden):
+    """Rows in order of their type, not of memory as well, and no scores asked for: the weights are those of the pass
+    that walks in memory order, bit for bit, and the oracle's optimum is found."""
+    r = synth.scheduling_round(law, 88, n=n, m=m)
+    import paper_2303_13803_amd as mm
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = mm.Context(n, m)
+    params = synth.typed_predictors(88, r["cfg"].F, list(hidden))
+    types = synth.gpu_types(88, n, len(hidden))
+    preds = [ctx.predictor({k: dev(v) for k, v in p.items()}, r["cfg"].scale) for p in params]
+    x_on, x_off, pad = dev(r["x_on"]), dev(r["x_off"]), (m + 3) // 4 * 4
+    W, again = (torch.full((n, pad), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.schedule_round_typed(preds, dev(types), x_on, x_off, W, r2c, u, v)
+    ctx.score_pairs_typed(preds, dev(types), x_on, x_off, again)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert res.rounds == 0 and res.bytes_scanned == 4 * n * m and torch.equal(W, again)
+    Wh = np.ascontiguousarray(W.cpu().numpy()[:, :m])
+    _, Wc = orc.score_pairs_typed(r["x_on"], r["x_off"], params, types, r["cfg"].scale)
+    assert_weights_close(Wh, Wc, r["cfg"].scale, Wc != INF)
+    assert ((Wh == INF) == (Wc == INF)).all()
+    code, P, _ = orc.check_certificate(Wh, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and res.primal == P == orc.max_weight_matching(Wh)[0]
 
 
 @pytest.mark.parametrize("law,n,m", [("C1", 64, 64), ("C4", 33, 257), ("C5", 88, 201)])
