@@ -27,7 +27,8 @@ constexpr int SMALL_LDS = 152 * 1024;           // (of 160 KB)
 // rows there is less to search: 64 x 150 0.51..0.88 / 0.23..0.46, 112 x 200 0.66..1.2 / 0.51..1.05, but with eight columns a lane
 // 112 x 300 0.59..1.1 / 0.52..1.33.  Other matrices gain at any of these sizes (uniform weights, 100 x 100 0.36 / 0.19;
 // products of a row and a column, the longest searches there are, 64 x 64 1.6 / 0.6).
-// More rows than columns are left to the auction: such a solve is promised to run on lists, one read and counted for every bid.
+// More rows than columns are left to the auction: they would have to be transposed on their way into LDS, and partners and
+// duals on their way out, which is not written (it should gain as much).
 constexpr int SMALL_ROWS = 88, SMALL_ROWS_WIDE = 112, SMALL_COLS_WIDE = 256;     // ... the latter with a third more columns than rows
 // Bids in the first part, per row.  (More leave fewer rows waiting but prefer the same columns: 64 x 64 with 1, 2, 4 and 8 a row,
 // 109 + 1018, 170 + 1035, 295 + 864 and 538 + 872 bids and scans, and a bid takes half as long again as a scan.)

@@ -157,6 +157,7 @@ def test_counters_of_a_solve_on_lists(n, m):
     reads one list (128 entries of 8 bytes) and is counted once."""
     import paper_2303_13803_amd as mm
     ctx = mm.Context(n, m)
+    ctx.set_option("core_few", 33)                       # (matched on lists, however small)
     W = padded_matrix(synth.uniform_matrix(72, n, m, 2 ** 24, 0.2))
     r2c = torch.empty(n, dtype=torch.int32, device="cuda")
     u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
