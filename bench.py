@@ -195,8 +195,11 @@ def main():
                               "unit": "GB/s", "frac": bulk_bytes / (bulk_ms * 1e-3) / HBM_PEAK,
                               "bytes_per_launch": bulk_bytes, "ms_per_launch": bulk_ms,
                               "traffic": MEASURED_TRAFFIC.get((cfg.name, "round_kernel")),
-                              # every weight byte any scan of the solve read, over the whole auction's time
-                              "whole_solve_gbps": res.bytes_scanned / (avg["auction_ms"] * 1e-3) / 1e9},
+                              # every weight byte any scan of the solve read, over the whole auction's time; a bid on a list
+                              # counts as all of it (1 KB), though half of one decides nine in ten
+                              "whole_solve_gbps": res.bytes_scanned / (avg["auction_ms"] * 1e-3) / 1e9,
+                              "whole_solve_gbps_note": "an upper bound: bids on lists are counted as whole lists of 1 KB, and nine in "
+                                                       "ten read half of one"},
         # the kernels for few bidders take most of the auction's time but are bound by the latency of
         # dependent steps, not by bandwidth: reported as steps and scans
         "auction_tail": {"kernels": "core_kernel (phases on lists: bids, searches, proofs), before them chain_kernel + "

@@ -120,7 +120,8 @@ typedef struct {
     int64_t min_reduced_cost;   /* min over feasible (i,j) of u_i + v_j - K*W_ij        */
     int64_t rounds;             /* bidding kernels run (forward + reverse)              */
     int64_t bids;               /* bids evaluated: each scans a row, a column or its list */
-    int64_t bytes_scanned;      /* bytes of the matrix and of lists that bids and path_scans read */
+    int64_t bytes_scanned;      /* bytes of the matrix and of lists that bids and path_scans read (a bid on a list counts as all of
+                                 * it, 1 KB, also where its first half decided) */
     int64_t chain_bids;         /* ... evaluated by the chain-following kernels and on lists */
     int64_t chain_depth;        /* longest per-workgroup bid sequence, summed over them */
     int64_t chain_retries;      /* chain bids that lost and were redone                 */
