@@ -4,8 +4,8 @@
 // a dozen of four.  So the two best are looked for by their distances above what nothing else is worth more than, as
 // floats, whose bits are in their order.  Values are whole numbers: up to 2^24 floats tell them all apart, and above that
 // rounding keeps their order, so the best is among those with the largest float.  Where several share that, the doubles
-// decide; both values are exact.  (The second one from its float, rounded up, took 0 to 2 % less time over seven measured
-// calls and made bids that rise by a little less than they may.)
+// decide; both values are exact.  (The second one from its float, rounded up, made bids that rise by a
+// little less than they may; seven measured calls took 0.98 to 1.02 of the time.)
 //
 // No dependence on the device: tests/half_list.cpp runs it with arrays in the lanes' place.
 #pragma once

@@ -556,8 +556,8 @@ __global__ __launch_bounds__(PATH_THREADS) void path_kernel(SideArgs s, const in
                 const int32_t *row = s.A + (size_t)i * s.pitch;
                 const int from = sl * span, reach = min(s.len, from + span);
                 // requested together: the column's label, what its holder pays for it, the line's
-                // length and the first entries of the slice (a line is allocated to its full
-                // length; what lies beyond its feasible part is marked infeasible)
+                // length and the first entries of the slice (a line is allocated to its full length; what
+                // lies beyond its feasible part may never have been written and is left out by `to` below)
                 unsigned long long lw = 0ull;
                 int32_t w_held = 0;
                 double p_held = 0.0;
