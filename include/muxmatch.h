@@ -361,7 +361,8 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
  * kernel ran the MLP on (the rest could not fit in memory and were marked
  * infeasible without being scored), [10] launches of the phases on lists, [11] how often lists of a
  * side were made for them, [12] sides of such phases that were finished on whole lines (a search read too
- * much, or "max_rounds" came near).  Entries of stages that did not run are 0.
+ * much, or "max_rounds" came near), [13] how often searches on lists had a side's lists put together by
+ * opposite line as well.  Entries of stages that did not run are 0.
  */
 int mf_last_timings(mf_ctx *ctx, float what[16]);
 

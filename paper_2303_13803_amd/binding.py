@@ -24,7 +24,7 @@ EXPORTS = ["mf_create", "mf_destroy", "mf_score_pairs", "mf_solve_assignment",
 
 TIMING_NAMES = ["projections_ms", "pair_scoring_ms", "bulk_bid_ms", "bulk_bid_launches",
                 "prepare_ms", "duals_ms", "certificate_ms", "auction_ms", "bulk_bid_bytes",
-                "pairs_evaluated_fraction", "list_launches", "lists_made", "list_sides_left"]
+                "pairs_evaluated_fraction", "list_launches", "lists_made", "list_sides_left", "lists_by_column"]
 
 
 class Predictor(C.Structure):

@@ -1120,6 +1120,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     ctx->timings[T_LIST_LAUNCHES] = (float)core.launches;
     ctx->timings[T_LISTS_MADE] = (float)core.lists_made;
     ctx->timings[T_LIST_SIDES_LEFT] = (float)core.sides_left;
+    ctx->timings[T_LISTS_BY_COLUMN] = (float)core.by_column;
     h_res->rounds = (int64_t)ctx->h_stats->rounds;
     // (the device's counts of bids include the searches' scans, which count against max_rounds)
     const int64_t searched = (int64_t)ctx->h_stats->path_scans;

@@ -1974,6 +1974,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
     const CoreCtl &h = *(const CoreCtl *)ctx->h_core_ctl;
+    st->by_column += __builtin_popcount(h.columns_ready & ~st->columns_ready);
     st->columns_ready = h.columns_ready;
     st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
     st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;

@@ -24,7 +24,7 @@
 #define MF_MAX_TYPES 64
 
 enum { T_PROJ = 0, T_PAIR, T_BID_BULK, T_BID_BULK_LAUNCHES, T_TRANSPOSE, T_DUALS, T_CERT, T_SOLVE,
-       T_BID_BULK_BYTES, T_PAIR_EVALUATED, T_LIST_LAUNCHES, T_LISTS_MADE, T_LIST_SIDES_LEFT, T_COUNT = 16 };
+       T_BID_BULK_BYTES, T_PAIR_EVALUATED, T_LIST_LAUNCHES, T_LISTS_MADE, T_LIST_SIDES_LEFT, T_LISTS_BY_COLUMN, T_COUNT = 16 };
 
 // The matching on short lists (core.hip): entries per list, most phases of a solve, lines a probe
 // looks at, why a launch ended and at which stage of a phase it (or the next one) starts.
@@ -264,7 +264,7 @@ struct mf_core_state {
     int wide, refined;
     unsigned columns_ready;             // the sides whose lists also exist by opposite line (bits)
     long long bids, depth, steps, scans, rested, bytes;      // summed over launches
-    int launches, lists_made, sides_left;       // sides_left: finished on whole lines
+    int launches, lists_made, sides_left, by_column;     // sides_left: finished on whole lines; by_column: lists that launches kept by opposite line, too
 };
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner);
 int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count, int which);
