@@ -12,6 +12,8 @@
 //             column), which may end at a free column or leave the row on it with the least to lose unmatched.
 // Throughout, held pairs are tight, no pair of a placed or given-up row is worth more than its duals, and a
 // column that nobody holds has price 0: in the end the duals prove the matching, with no gap.
+// (The order of the two parts is that of Jonker and Volgenant 1987, "A shortest augmenting path algorithm for dense and
+// sparse linear assignment problems".)
 #include "scan.h"
 
 namespace {
