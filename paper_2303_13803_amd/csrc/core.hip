@@ -100,8 +100,15 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
     const int *__restrict__ which, const double *__restrict__ dual, double Kd, int2 *__restrict__ entries,
     double *__restrict__ bound, double *__restrict__ half_bound, double *depth, const double *__restrict__ own_dual,
-    const int *__restrict__ partner)
+    const int *__restrict__ partner, double *__restrict__ built, int some)
 {
+    // The duals the side's lists were made for; where some lines' lists are newer than others', the larger ones (a
+    // bound holds as long as no dual is lower than when the list was made).  (A launch of its own took 5 us and its gap.)
+    if (built)
+        for (int k = blockIdx.x * LIST_THREADS + threadIdx.x; k < len; k += gridDim.x * LIST_THREADS) {
+            const double d = dual[k];
+            built[k] = some ? fmax(built[k], d) : d;
+        }
     // line number q of this launch's `lines`: every stride-th, or the q-th listed in `which`
     auto line_number = [&](int q) { return which ? (long long)which[q] : (long long)q * stride; };
     constexpr int PER = LIST_CAP / 64;
@@ -297,14 +304,6 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     }
 }
 
-// built: the duals all lists of a side were made for; where some lines' lists are newer than others', the larger
-// ones (a bound holds as long as no dual is lower than when the list was made).
-__global__ void core_snapshot_kernel(const double *__restrict__ dual, int count, double *__restrict__ built, int some)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) built[k] = some ? fmax(built[k], dual[k]) : dual[k];
-}
-
 // ---------------------------------------------------------------- the engine
 
 struct alignas(256) CoreCtl {
@@ -493,8 +492,7 @@ __device__ __noinline__ Top2 read_list(const int2 *e, const unsigned long long *
 }
 
 // Everything a workgroup carries through the launch.  LARGE: for problems whose first bids run on all dies, where
-// bidders may wait for better lists and counts are summed up by workgroup.  (Those few instructions cost a
-// chain's step 3 % where one die does it all.)
+// bidders may wait for better lists.  (Those few instructions cost a chain's step 3 % where one die does it all.)
 template <bool LARGE>
 struct Core {
     const CoreArgs &a;
@@ -722,16 +720,14 @@ struct Core {
         for (int i = gtid(); i < s.lines; i += gsize()) reach += s.reach[i];
         most = wave_max(most);
         for (int off = 32; off >= 1; off >>= 1) { rise += __shfl_xor(rise, off); reach += __shfl_xor(reach, off); }
-        // (one workgroup's share at a time: atomics on one address complete at one per 10 ns, and 2048 wavefronts' took 25 us)
-        if (LARGE) {
-            double *part = (double *)sh.list;
-            __syncthreads();
-            if (lane == 0) { part[wave] = most; part[CORE_WAVES + wave] = rise; part[2 * CORE_WAVES + wave] = reach; }
-            __syncthreads();
-            if (tid == 0)
-                for (int w = 1; w < CORE_WAVES; ++w) { most = fmax(most, part[w]); rise += part[CORE_WAVES + w]; reach += part[2 * CORE_WAVES + w]; }
-        }
-        if (LARGE ? tid == 0 : lane == 0) {
+        // (one workgroup's share at a time: atomics on one address complete at one per 10 ns, and 2048 wavefronts' took 25 us,
+        // 256 wavefronts' 8 us)
+        double *part = (double *)sh.list;
+        __syncthreads();
+        if (lane == 0) { part[wave] = most; part[CORE_WAVES + wave] = rise; part[2 * CORE_WAVES + wave] = reach; }
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < CORE_WAVES; ++w) { most = fmax(most, part[w]); rise += part[CORE_WAVES + w]; reach += part[2 * CORE_WAVES + w]; }
             if (most > 0.0) atomicMax(&ctl->slack[0], (unsigned long long)__double_as_longlong(most));
             if (rise > 0.0) atomicAdd(&ctl->slack[1], (unsigned long long)(rise / s.len));
             atomicAdd(&ctl->slack[2], (unsigned long long)(reach / s.lines));
@@ -1650,25 +1646,22 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
 template <bool LARGE>
 __device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int stage, int count, int parity)
 {
-    if (LARGE) {
-        __syncthreads();
-        if (tid < 4) sh.list[tid] = 0ull;
-        __syncthreads();
-    }
+    // (summed up by workgroup first: four atomics from each of 256 wavefronts, on four addresses, took a launch 15 to 30 us)
+    __syncthreads();
+    if (tid < 4) sh.list[tid] = 0ull;
+    __syncthreads();
     unsigned long long *sums[4] = {&ctl->bids, &ctl->scans, &ctl->whole_groups, &ctl->rested};
     const unsigned mine[4] = {bids, scans, whole, rests};
     if (lane == 0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (mine[q]) atomicAdd(LARGE ? &sh.list[q] : sums[q], (unsigned long long)mine[q]);
+            if (mine[q]) atomicAdd(&sh.list[q], (unsigned long long)mine[q]);
     }
-    if (LARGE) {
-        __syncthreads();
-        if (tid == 0) {
+    __syncthreads();
+    if (tid == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (sh.list[q]) atomicAdd(sums[q], sh.list[q]);
-        }
+        for (int q = 0; q < 4; ++q)
+            if (sh.list[q]) atomicAdd(sums[q], sh.list[q]);
     }
     // a wait that runs out here still counts: the reason stays "a wait ran out"
     if (reason == MF_CORE_ABORT || !barrier()) return MF_CORE_ABORT;
@@ -1863,11 +1856,12 @@ __global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
 
 namespace {
 
-void launch_lists(mf_ctx *ctx, const SideArgs &s, int made, int stride, const int *list, int which, double *depth, const double *own_dual, const int *partner)
+void launch_lists(mf_ctx *ctx, const SideArgs &s, int made, int stride, const int *list, int which, double *depth, const double *own_dual, const int *partner,
+                  double *built)
 {
 #define MF_LIST(LINES)                                                                                                                     \
     hipLaunchKernelGGL((core_list_kernel<LINES>), dim3((made + LINES - 1) / LINES), dim3(LIST_THREADS), 0, ctx->stream, s.A, s.pitch, s.len, \
-                       s.line_len, made, stride, list, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner)
+                       s.line_len, made, stride, list, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner, built, list ? 1 : 0)
     if (made > 4 * ctx->n_cus) MF_LIST(4);
     else MF_LIST(1);
 #undef MF_LIST
@@ -1879,9 +1873,7 @@ void launch_lists(mf_ctx *ctx, const SideArgs &s, int made, int stride, const in
 int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const double *own_dual, const int *partner)
 {
     if (s.len <= CORE_LIST) partner = nullptr;          // whole lines: they never have to be made again
-    launch_lists(ctx, s, lines, 1, nullptr, which, ctx->core_reach[which], own_dual, partner);
-    hipLaunchKernelGGL(core_snapshot_kernel, dim3((s.len + 255) / 256), dim3(256), 0, ctx->stream, s.other_dual, s.len,
-                       ctx->core_built[which], 0);
+    launch_lists(ctx, s, lines, 1, nullptr, which, ctx->core_reach[which], own_dual, partner, ctx->core_built[which]);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
@@ -1890,9 +1882,7 @@ int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const do
 int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count, int which)
 {
     if (count <= 0) return MF_OK;
-    launch_lists(ctx, s, count, 1, list, which, ctx->core_reach[which], nullptr, nullptr);
-    hipLaunchKernelGGL(core_snapshot_kernel, dim3((s.len + 255) / 256), dim3(256), 0, ctx->stream, s.other_dual, s.len,
-                       ctx->core_built[which], 1);
+    launch_lists(ctx, s, count, 1, list, which, ctx->core_reach[which], nullptr, nullptr, ctx->core_built[which]);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
@@ -1902,7 +1892,7 @@ int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count,
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep)
 {
     const int stride = (lines + MF_CORE_PROBES - 1) / MF_CORE_PROBES, probes = (lines + stride - 1) / stride;
-    launch_lists(ctx, s, probes, stride, nullptr, 0, ctx->core_depth, nullptr, nullptr);
+    launch_lists(ctx, s, probes, stride, nullptr, 0, ctx->core_depth, nullptr, nullptr, nullptr);
     MF_HIP(hipGetLastError());
     MF_HIP(hipMemcpyAsync(ctx->h_core_depth, ctx->core_depth, sizeof(double) * probes, hipMemcpyDeviceToHost, ctx->stream));
     MF_HIP(hipStreamSynchronize(ctx->stream));
