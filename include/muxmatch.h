@@ -132,7 +132,7 @@ typedef struct {
     int32_t phases;             /* epsilon-scaling phases (1 where there is no epsilon) */
     int32_t cert_ok;            /* 1: matching valid, duals feasible, 0 <= D - K*P < K  */
     int32_t status;             /* same code the call returned                          */
-    float   ms_solve;           /* device time of the auction (HIP events)              */
+    float   ms_solve;           /* device time of the auction                           */
     float   ms_certify;         /* device time of dual extraction + certificate         */
     int32_t fallbacks;          /* MF_FALLBACK_* bits: kernels this solve had to do without */
 } mf_result;
@@ -350,7 +350,7 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value);
 
 /*
  * Device time, in milliseconds, of the kernels the last call on this context
- * launched, by stage, measured with HIP events on the context's stream:
+ * launched, by stage, measured with the device's clock:
  * what[0] layer-1 projections (and the memory ordering), [1] pair scoring,
  * [2] the bidding rounds in which every line of the bidding side scans (the
  * first of each phase), [3] how many of those ran, [4] preparation of the solve (largest

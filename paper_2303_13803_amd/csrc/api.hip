@@ -62,17 +62,12 @@ void clear_timings(mf_ctx *ctx)
 int finish_score_timing(mf_ctx *ctx, bool counted)
 {
     if (!counted) {
-        MF_HIP(hipMemcpyAsync(ctx->h_pairs_evaluated, ctx->pairs_evaluated, sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, ctx->stream));
-        MF_HIP(hipStreamSynchronize(ctx->stream));
+        const int rc = mf_send_and_await(ctx, mf_report{{{ctx->pairs_evaluated, ctx->h_pairs_evaluated, 2}, {ctx->times, ctx->h_times, 2 * AT_COUNT}}});
+        if (rc != MF_OK) return rc;
     }
-    float a = 0.0f, b = 0.0f;
-    float c = 0.0f;
-    MF_HIP(hipEventElapsedTime(&a, ctx->ev[0], ctx->ev[1]));
-    MF_HIP(hipEventElapsedTime(&b, ctx->ev[1], ctx->ev[2]));
-    MF_HIP(hipEventElapsedTime(&c, ctx->ev[2], ctx->ev[8]));      // putting the columns back in place
-    ctx->timings[T_PROJ] = a + c;
-    ctx->timings[T_PAIR] = b;
+    const unsigned long long *t = ctx->h_times, paired = ctx->score_placed ? t[AT_PLACE] : t[AT_SCORED];
+    ctx->timings[T_PROJ] = mf_ms(ctx, t[AT_SCORE], t[AT_PAIRS]) + mf_ms(ctx, paired, t[AT_SCORED]);      // (the second: putting the columns back in place)
+    ctx->timings[T_PAIR] = mf_ms(ctx, t[AT_PAIRS], paired);
     ctx->timings[T_PAIR_EVALUATED] = ctx->pairs_total > 0 ? (float)((double)*ctx->h_pairs_evaluated / ctx->pairs_total) : 0.0f;
     ctx->score_pending = false;
     return MF_OK;
@@ -149,6 +144,8 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     {
         hipDeviceProp_t prop;
         ctx->n_cus = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.multiProcessorCount : 0;
+        int khz = 0;
+        ctx->clock_khz = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0 ? (double)khz : 100000.0;
     }
     const size_t nm = (size_t)(max_n > max_m ? max_n : max_m);   // either side may be the one that bids first
     const size_t ldt = ((size_t)max_n + 3) & ~(size_t)3;
@@ -210,7 +207,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
         TRY(dev_alloc(&ctx->core_read_from, nm));
         TRY(dev_alloc(&ctx->core_weight, nm));
         TRY(hipMalloc(&ctx->core_ctl, mf_core_ctl_bytes()));
-        TRY(hipHostMalloc(&ctx->h_core_ctl, mf_core_ctl_bytes()));
+        TRY(hipHostMalloc(&ctx->h_core_report, mf_core_report_bytes()));
     }
     TRY(dev_alloc(&ctx->path_tree, nm + 64));
     TRY(dev_alloc(&ctx->path_parent, nm + 64));
@@ -225,10 +222,15 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(hipHostMalloc((void **)&ctx->h_stats, sizeof(mf_device_stats)));
     for (int i = 0; i < 2; ++i) {
         TRY(hipHostMalloc((void **)&ctx->h_stats_slot[i], sizeof(mf_device_stats)));
-        TRY(hipEventCreate(&ctx->ev_stats[i]));
     }
+    TRY(hipHostMalloc((void **)&ctx->h_type_first, sizeof(int32_t) * (MF_MAX_TYPES + 1)));
+    TRY(hipHostMalloc((void **)&ctx->h_bad, sizeof(int)));
+    TRY(dev_alloc(&ctx->times, AT_COUNT));
+    TRY(hipHostMalloc((void **)&ctx->h_times, sizeof(unsigned long long) * AT_COUNT));
+    TRY(hipHostMalloc((void **)&ctx->h_told, sizeof(mf_told)));
+    if (e == hipSuccess) memset(ctx->h_told, 0, sizeof(mf_told));
     TRY(hipHostMalloc((void **)&ctx->h_cert, sizeof(mf_cert_out)));
-    for (int i = 0; i < 10; ++i) TRY(hipEventCreate(&ctx->ev[i]));
+    for (int i = 0; i < 2; ++i) TRY(hipEventCreate(&ctx->ev[i]));
 #undef TRY
     if (e != hipSuccess) {
         ctx->hip_error = e;
@@ -248,19 +250,22 @@ int mf_destroy(mf_ctx *ctx)
                    ctx->profit, ctx->colword, ctx->roword, ctx->row2col, ctx->col2row, ctx->team_ctl, ctx->path_ctl, ctx->path_label, ctx->path_expanded, ctx->path_frontier[0], ctx->path_frontier[1], ctx->path_stamp, ctx->path_held, ctx->path_base, ctx->path_tree, ctx->path_parent, ctx->path_jump, ctx->edge_count, ctx->edge_start, ctx->list[0], ctx->list[1], ctx->colmark, ctx->stats,
                    ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_half_bound[0], ctx->core_half_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
                    ctx->core_t_entries[0], ctx->core_t_entries[1], ctx->core_t_start[0], ctx->core_t_start[1], ctx->core_t_at[0], ctx->core_t_at[1],
-                   ctx->core_base, ctx->core_dropped, ctx->core_tree, ctx->core_depth, ctx->core_parent, ctx->core_read_from, ctx->core_weight, ctx->core_ctl, ctx->cert};
+                   ctx->core_base, ctx->core_dropped, ctx->core_tree, ctx->core_depth, ctx->core_parent, ctx->core_read_from, ctx->core_weight, ctx->core_ctl, ctx->cert, ctx->times};
     for (void *p : dev) if (p) (void)hipFree(p);
     if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
     for (int i = 0; i < 2; ++i) {
         if (ctx->h_stats_slot[i]) (void)hipHostFree(ctx->h_stats_slot[i]);
-        if (ctx->ev_stats[i]) (void)hipEventDestroy(ctx->ev_stats[i]);
     }
+    if (ctx->h_type_first) (void)hipHostFree(ctx->h_type_first);
+    if (ctx->h_bad) (void)hipHostFree(ctx->h_bad);
+    if (ctx->h_times) (void)hipHostFree(ctx->h_times);
+    if (ctx->h_told) (void)hipHostFree(ctx->h_told);
     if (ctx->h_cert) (void)hipHostFree(ctx->h_cert);
     if (ctx->h_core_depth) (void)hipHostFree(ctx->h_core_depth);
-    if (ctx->h_core_ctl) (void)hipHostFree(ctx->h_core_ctl);
+    if (ctx->h_core_report) (void)hipHostFree(ctx->h_core_report);
     if (ctx->h_pairs_evaluated) (void)hipHostFree(ctx->h_pairs_evaluated);
     if (ctx->h_feasible_pairs) (void)hipHostFree(ctx->h_feasible_pairs);
-    for (int i = 0; i < 10; ++i) if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
+    for (int i = 0; i < 2; ++i) if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
     delete ctx;
     return MF_OK;
 }
@@ -274,7 +279,9 @@ int mf_score_pairs(mf_ctx *ctx, const mf_predictor *pred, const float *d_on, int
     if (n > ctx->max_n || m > ctx->max_m) return MF_ERR_SHAPE;
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
-    return mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
+    const int launched = mf_launch_score(ctx, pred, 1, nullptr, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
+    if (launched == MF_OK) mf_note_time(ctx, AT_SCORED);
+    return launched;
 }
 
 int mf_solve_assignment(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
@@ -301,12 +308,8 @@ int mf_check_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t 
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
     memset(h_res, 0, sizeof(*h_res));
-    MF_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
     rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
-    if (rc == MF_OK) {
-        MF_HIP(hipEventElapsedTime(&ctx->timings[T_CERT], ctx->ev[5], ctx->ev[6]));
-        h_res->ms_certify = ctx->timings[T_CERT];
-    }
+    if (rc == MF_OK) h_res->ms_certify = ctx->timings[T_CERT];
     h_res->status = rc;
     return rc;
 }
@@ -343,7 +346,9 @@ int mf_score_pairs_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types, co
     if (n > ctx->max_n || m > ctx->max_m) return MF_ERR_SHAPE;
     MF_HIP(hipSetDevice(ctx->device));
     clear_timings(ctx);
-    return mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
+    const int launched = mf_launch_score(ctx, preds, n_types, d_type_on, d_on, n, d_off, m, d_W, ldw, d_sigma, false);
+    if (launched == MF_OK) mf_note_time(ctx, AT_SCORED);
+    return launched;
 }
 
 int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types, const int32_t *d_type_on,
@@ -407,7 +412,7 @@ int mf_set_option(mf_ctx *ctx, const char *name, int64_t value)
 int mf_last_timings(mf_ctx *ctx, float what[16])
 {
     if (!ctx || !what) return MF_ERR_ARG;
-    if (ctx->score_pending) {           // a bare mf_score_pairs does not wait for its events
+    if (ctx->score_pending) {           // a bare mf_score_pairs does not wait for its times
         int rc = finish_score_timing(ctx, false);
         if (rc != MF_OK) return rc;
     }

@@ -27,6 +27,7 @@
 // double precision, where such integers and their differences are exact, so
 // that they run at the full rate of the FP64 vector units.
 #include "scan.h"
+#include "report.h"
 
 namespace {
 
@@ -54,6 +55,7 @@ __global__ __launch_bounds__(NT, 3) void round_kernel(SideArgs s, const int *__r
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         stats->cnt[(ring + 2) & 3] = 0;
         stats->head = 0;
+        stats->round_at = device_time();
         if (count > 0) {
             stats->rounds += 1ull;
             stats->bids += (unsigned long long)count;
@@ -378,9 +380,10 @@ __global__ __launch_bounds__(NT) void team_kernel(SideArgs s, const int *__restr
 // Start of an epsilon phase: drop the assignment, keep the duals, all rows bid.
 __global__ void reset_kernel(int n, int m, const double *__restrict__ price,
                              unsigned long long *colword, int *row2col, int *col2row, int *list,
-                             mf_device_stats *stats)
+                             mf_device_stats *stats, unsigned long long *times)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0 && times[AT_PREPARED] == 0ull) times[AT_PREPARED] = device_time();
     if (i < n) { row2col[i] = -1; list[i] = i; }
     if (i < m) { col2row[i] = -1; colword[i] = pack_word(price[i], 0); }
     if (i == 0) { stats->cnt[0] = n; stats->cnt[1] = 0; stats->cnt[2] = 0; stats->cnt[3] = 0; }
@@ -389,9 +392,10 @@ __global__ void reset_kernel(int n, int m, const double *__restrict__ price,
 // After the forward rounds the price words name every column's holder, and a
 // row's profit is whatever its column leaves it (0 for a row that rests).
 __global__ void forward_done_rows_kernel(int n, double *__restrict__ profit,
-                                         unsigned long long *roword, int *row2col)
+                                         unsigned long long *roword, int *row2col, mf_device_stats *stats)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) { stats->cnt[0] = 0; stats->cnt[1] = 0; stats->cnt[2] = 0; stats->cnt[3] = 0; }
     if (i < n) { row2col[i] = -1; profit[i] = 0.0; roword[i] = 0ull; }
 }
 
@@ -460,11 +464,6 @@ __global__ void reverse_done_rows_kernel(int n, const int32_t *__restrict__ W, i
         col2row[c] = i;
         price[c] = Kd * (double)W[(size_t)i * ldw + c] - word_dual(word);
     }
-}
-
-__global__ void clear_counts_kernel(mf_device_stats *stats)
-{
-    stats->cnt[0] = 0; stats->cnt[1] = 0; stats->cnt[2] = 0; stats->cnt[3] = 0;
 }
 
 // W^T (for the reverse rounds' coalesced column scans) and the largest weight.
@@ -549,11 +548,18 @@ __global__ void zero_listed_kernel(double *price, const int32_t *__restrict__ wh
     if (i < count && which[i] >= 0 && which[i] < m) price[which[i]] = 0.0;
 }
 
-// known, known_pairs (or null): largest weight and feasible pairs of the matrix, noted while it was scored
+// known, known_pairs (or null): largest weight and feasible pairs of the matrix, noted while it was scored.  scored: this
+// launch is the first after the scoring pass.
 __global__ void init_solver_kernel(int n, int m, double *price, double *profit, mf_device_stats *stats,
-                                   int keep_prices, const int *known, const unsigned long long *known_pairs)
+                                   int keep_prices, const int *known, const unsigned long long *known_pairs,
+                                   unsigned long long *times, int scored)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) {
+        times[AT_SOLVE] = device_time();
+        if (scored) times[AT_SCORED] = times[AT_SOLVE];
+        times[AT_PREPARED] = 0ull;
+    }
     if (i < n + 4) profit[i] = 0.0;
     if (i < m + 4 && (!keep_prices || i >= m)) price[i] = 0.0;
     if (i == 0) {
@@ -619,6 +625,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     // that such a round is in flight; every other kind of launch waits for the exact count first.
     bool unread = false;
     int unread_ring = 0, unread_slot = 0, slot = 0;
+    unsigned unread_report = 0;
     bool counted_teams = false, chained = false;
     unsigned long long bids_before = ctx->h_stats->bids;
     // takes in the statistics copied after the launch that left the lists at position `at`
@@ -638,7 +645,8 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         return MF_OK;
     };
     auto read_unread = [&]() -> int {
-        MF_HIP(hipEventSynchronize(ctx->ev_stats[unread_slot]));
+        const int rc = mf_await(ctx, unread_report);
+        if (rc != MF_OK) return rc;
         *ctx->h_stats = *ctx->h_stats_slot[unread_slot];
         unread = false;
         return absorb(unread_ring);
@@ -670,9 +678,8 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         if (bulk) {
             const int batch = (count > 4096 || time_first) ? 1 : 3;     // the timed round stands alone
             for (int r = 0; r < batch; ++r) {
-                if (time_first && r == 0) { MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream)); timed = true; }
+                timed = time_first;
                 launch_round(ctx, s, count, ring);
-                if (time_first && r == 0) MF_HIP(hipEventRecord(ctx->ev[7], ctx->stream));
                 ++ring;
             }
         } else if (paths_ok && (count <= search_now || (count <= ctx->path_max && (team_steps >= ctx->path_after || !teams_ok)))) {
@@ -727,30 +734,27 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         }
         MF_HIP(hipGetLastError());
         if (bulk && !timed && ctx->round_lag && count > 4096) {     // (smaller rounds go three to a read, above)
-            MF_HIP(hipMemcpyAsync(ctx->h_stats_slot[slot], ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
-            MF_HIP(hipEventRecord(ctx->ev_stats[slot], ctx->stream));
-            if (unread) {
-                const int rc = read_unread();           // the round before this one, while this one runs
-                if (rc != MF_OK) return rc;
-            }
+            unsigned report = 0;
+            int rc = mf_send(ctx, mf_report_stats(ctx, ctx->h_stats_slot[slot]), &report);
+            if (rc == MF_OK && unread) rc = read_unread();      // the round before this one, while this one runs
+            if (rc != MF_OK) return rc;
             unread = true;
+            unread_report = report;
             unread_ring = ring;
             unread_slot = slot;
             slot ^= 1;
             continue;
         }
-        MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
-        MF_HIP(hipStreamSynchronize(ctx->stream));
-        unread = false;                                  // (a later copy on the same stream: it covers the round in flight too)
+        int rc = mf_send_and_await(ctx, mf_report_stats(ctx, ctx->h_stats));
+        if (rc != MF_OK) return rc;
+        unread = false;                                  // (a later report on the same stream: it covers the round in flight too)
         if (timed) {
-            float ms = 0.0f;
-            MF_HIP(hipEventElapsedTime(&ms, ctx->ev[6], ctx->ev[7]));
-            ctx->timings[T_BID_BULK] += ms;
+            ctx->timings[T_BID_BULK] += mf_ms(ctx, ctx->h_stats->round_at, ctx->h_told->at);
             ctx->timings[T_BID_BULK_LAUNCHES] += 1.0f;
             ctx->timings[T_BID_BULK_BYTES] += (float)((double)(ctx->h_stats->bytes + ctx->h_stats->round_bytes - bytes_before));
         }
         time_first = false;
-        const int rc = absorb(ring);
+        rc = absorb(ring);
         if (rc != MF_OK) return rc;
     }
     if (unread) {
@@ -867,17 +871,14 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
 int run_small(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, int32_t *d_row2col, int64_t *d_u, int64_t *d_v, mf_result *h_res,
               bool *general)
 {
-    MF_HIP(hipEventRecord(ctx->ev[3], ctx->stream));
     int rc = mf_launch_small(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v);
     if (rc != MF_OK) return rc;
-    MF_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
     rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, (int64_t)n + 1, h_res, true);
     if (rc != MF_OK) return rc;
     const mf_cert_out &c = *ctx->h_cert;
     *general = c.status == MF_SMALL_GENERAL;
     if (c.status != MF_OK) return c.status;
-    MF_HIP(hipEventElapsedTime(&ctx->timings[T_SOLVE], ctx->ev[3], ctx->ev[4]));
-    MF_HIP(hipEventElapsedTime(&ctx->timings[T_CERT], ctx->ev[4], ctx->ev[6]));
+    ctx->timings[T_SOLVE] = mf_ms(ctx, ctx->h_times[AT_SOLVE], ctx->h_times[AT_CERT]);
     h_res->bids = h_res->chain_bids = c.bids;
     h_res->path_steps = h_res->path_scans = c.scans;
     h_res->chain_depth = (int64_t)c.bids + c.scans;
@@ -909,10 +910,12 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     const bool flip = n > m;
     warm = warm && !flip && !candidate && ctx->warm_n == n && ctx->warm_m == m;
     ctx->warm_n = ctx->warm_m = 0;
+    bool scored = true;                         // nothing has come between the scoring pass and the launches below
     if (mf_small_fits(ctx, n, m)) {
         bool general = false;
         const int rc = run_small(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, h_res, &general);
         if (!general) return rc;
+        scored = false;
         *h_res = mf_result{};
     }
     const int64_t ldt = ((int64_t)n + 3) & ~3ll;
@@ -925,14 +928,13 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     // infeasible pairs, in any pattern: its rows are then also kept as lists of feasible pairs.
     const bool lists_possible = !candidate && !flip && !warm && ctx->edge_lists_from > 0 && n >= ctx->edge_lists_from &&
                                 ctx->fit_prefix_below > 0;
-    MF_HIP(hipEventRecord(ctx->ev[3], ctx->stream));
     {
         // the largest weight sets the first epsilon
         const bool known = candidate && ctx->largest_weight_known;
         const int chunks = (m + 4095) / 4096 < 4 ? (m + 4095) / 4096 : 4;
         hipLaunchKernelGGL(init_solver_kernel, dim3((nm + 4 + 255) / 256), dim3(256), 0, ctx->stream, rn, rm,
                            ctx->price, ctx->profit, ctx->stats, warm ? 1 : 0,
-                           known ? ctx->largest_weight : nullptr, candidate ? ctx->feasible_pairs : nullptr);
+                           known ? ctx->largest_weight : nullptr, candidate ? ctx->feasible_pairs : nullptr, ctx->times, scored ? 1 : 0);
         if (lists_possible) {
             // the same pass also counts the feasible pairs of every row: with few of them the rounds read lists
             hipLaunchKernelGGL(fill_counter_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->feasible_pairs);
@@ -943,11 +945,12 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
                                m, ldw, ctx->stats);
         MF_HIP(hipGetLastError());
     }
-    if (lists_possible)
-        MF_HIP(hipMemcpyAsync(ctx->h_feasible_pairs, ctx->feasible_pairs, sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
+    {
+        mf_report r = mf_report_stats(ctx, ctx->h_stats);
+        r.piece[1] = {ctx->feasible_pairs, ctx->h_feasible_pairs, 2};
+        const int rc = mf_send_and_await(ctx, r);
+        if (rc != MF_OK) return rc;
+    }
     if (!lists_possible) *ctx->h_feasible_pairs = ctx->h_stats->feasible_pairs;
     const long long cmax = K * (long long)ctx->h_stats->max_weight;
     if (cmax >= MF_MAX_DUAL) return MF_ERR_RANGE;
@@ -974,7 +977,6 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     };
     if (flip) make_transpose();
     MF_HIP(hipGetLastError());
-    MF_HIP(hipEventRecord(ctx->ev[9], ctx->stream));
 
     // with per-line lengths a scan reads, on average, the pairs that can share divided by the lines
     const double feasible = staged ? (double)*ctx->h_feasible_pairs : (double)n * (double)m;
@@ -1043,6 +1045,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         // prefixes, whose lines cost little (20,000 x 40,000 20.3 / 22.3), and not where one die does it all (6001 x
         // 9007 13.2 / 14.2).
         if (core_ok && (ph > 0 || warm || rm <= MF_CORE_LIST)) {
+            if (ph == 0) mf_note_time(ctx, AT_PREPARED);
             double deep = 1.0;
             if (rm > MF_CORE_LIST) {
                 const bool all_dies = ctx->core_wide > 0 && rn >= ctx->core_wide && !fwd.line_len;
@@ -1062,7 +1065,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         phases = ph + 1;
         fwd.eps = rev.eps = (double)eps;
         hipLaunchKernelGGL(reset_kernel, dim3((nm + 255) / 256), dim3(256), 0, ctx->stream, rn, rm, ctx->price,
-                           ctx->colword, ctx->row2col, ctx->col2row, ctx->list[0], ctx->stats);
+                           ctx->colword, ctx->row2col, ctx->col2row, ctx->list[0], ctx->stats, ctx->times);
         int left_over = 0;
         // ... unless bidders have been giving up (best value at most epsilon) in this solve: then
         // workloads stay unmatched at the optimum, the bidders left over would be the ones that
@@ -1075,9 +1078,8 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         int rc = run_side(ctx, fwd, rn, true, stop_at, (ctx->phase_tail_sides & 1) && rn >= ctx->phase_tail_from ? ctx->phase_tail_steps : 0, &left_over);
         if (rc != MF_OK) return rc;
         // who holds what after the forward rounds; unassigned priced columns go to list[0]
-        hipLaunchKernelGGL(clear_counts_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->stats);
         hipLaunchKernelGGL(forward_done_rows_kernel, dim3((rn + 255) / 256), dim3(256), 0, ctx->stream, rn,
-                           ctx->profit, ctx->roword, ctx->row2col);
+                           ctx->profit, ctx->roword, ctx->row2col, ctx->stats);
         hipLaunchKernelGGL(forward_done_cols_kernel, dim3((rm + 255) / 256), dim3(256), 0, ctx->stream, rm,
                            A, lda, Kd, ctx->colword, ctx->price, ctx->profit, ctx->roword, ctx->row2col,
                            ctx->col2row, ctx->list[0], ctx->stats);
@@ -1086,8 +1088,8 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
                                ctx->stream, A, lda, rn, rm, ctx->price, ctx->row2col, Kd, ctx->profit, ctx->roword,
                                fwd.line_len);
         MF_HIP(hipGetLastError());
-        MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
-        MF_HIP(hipStreamSynchronize(ctx->stream));
+        rc = mf_send_and_await(ctx, mf_report_stats(ctx, ctx->h_stats));
+        if (rc != MF_OK) return rc;
         const int rev_count = ctx->h_stats->cnt[0];
         if (rev_count > stop_at) {
             if (!have_transpose) make_transpose();
@@ -1100,23 +1102,17 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
             MF_HIP(hipGetLastError());
         }
     }
-    MF_HIP(hipEventRecord(ctx->ev[4], ctx->stream));
     {
         const int rc = mf_extract_duals(ctx, A, lda, rn, rm, Kd, fwd.line_len, n, flip, staged, d_row2col, d_u, d_v);
         if (rc != MF_OK) return rc;
     }
-    MF_HIP(hipEventRecord(ctx->ev[5], ctx->stream));
-    MF_HIP(hipMemcpyAsync(ctx->h_stats, ctx->stats, sizeof(mf_device_stats), hipMemcpyDeviceToHost, ctx->stream));
     int rc = mf_run_certificate(ctx, d_W, n, m, ldw, d_row2col, d_u, d_v, K, h_res, false);
     if (rc != MF_OK) return rc;
-    float ms_solve = 0.0f, ms_duals = 0.0f, ms_cert = 0.0f;
-    MF_HIP(hipEventElapsedTime(&ctx->timings[T_TRANSPOSE], ctx->ev[3], ctx->ev[9]));
-    MF_HIP(hipEventElapsedTime(&ms_solve, ctx->ev[3], ctx->ev[4]));
-    MF_HIP(hipEventElapsedTime(&ms_duals, ctx->ev[4], ctx->ev[5]));
-    MF_HIP(hipEventElapsedTime(&ms_cert, ctx->ev[5], ctx->ev[6]));
+    const unsigned long long *at = ctx->h_times;
+    const float ms_solve = mf_ms(ctx, at[AT_SOLVE], at[AT_DUALS]), ms_duals = mf_ms(ctx, at[AT_DUALS], at[AT_CERT]), ms_cert = ctx->timings[T_CERT];
+    ctx->timings[T_TRANSPOSE] = mf_ms(ctx, at[AT_SOLVE], at[AT_PREPARED]);
     ctx->timings[T_SOLVE] = ms_solve;
     ctx->timings[T_DUALS] = ms_duals;
-    ctx->timings[T_CERT] = ms_cert;
     ctx->timings[T_LIST_LAUNCHES] = (float)core.launches;
     ctx->timings[T_LISTS_MADE] = (float)core.lists_made;
     ctx->timings[T_LIST_SIDES_LEFT] = (float)core.sides_left;

@@ -2,6 +2,7 @@
 // problem (paper: Section "Matching-based scheduling" states the problem whose optimum is asked
 // for) and the certificate that matching and duals are optimal together.
 #include "scan.h"
+#include "report.h"
 #include <mutex>
 
 namespace {
@@ -14,8 +15,9 @@ template <int NT, int RB>
 __global__ __launch_bounds__(NT) void duals_kernel(
     const int32_t *__restrict__ W, int64_t ldw, int n, int m, const double *__restrict__ price,
     const int *__restrict__ row2col, double Kd, int32_t *__restrict__ out_row2col,
-    int64_t *__restrict__ u, int64_t *__restrict__ v, const int *__restrict__ line_len)
+    int64_t *__restrict__ u, int64_t *__restrict__ v, const int *__restrict__ line_len, unsigned long long *times)
 {
+    note_time(times, AT_DUALS);
     __shared__ Top2 red[RB + RB * (NT / 64)];
     for (int i0 = blockIdx.x * RB; i0 < n; i0 += gridDim.x * RB) {
         const int32_t *rows[RB];
@@ -54,8 +56,9 @@ template <bool K32>
 __global__ __launch_bounds__(BID_THREADS) void certificate_kernel(
     const int32_t *__restrict__ W, int64_t ldw, int n, int m, const int32_t *__restrict__ row2col,
     const int64_t *__restrict__ u, const int64_t *__restrict__ v, long long K, int *colmark,
-    mf_cert_out *out)
+    mf_cert_out *out, unsigned long long *times)
 {
+    note_time(times, AT_CERT);
     __shared__ long long red[BID_THREADS / 64];
     constexpr int UN = 1;               // column groups of four in flight per thread
     long long dual_part = 0, primal_part = 0;
@@ -177,8 +180,9 @@ __global__ void map_back_kernel(int rn, int rm, const int32_t *__restrict__ r2c,
     }
 }
 
-__global__ void cert_begin_kernel(mf_cert_out *out, int *colmark, int m)
+__global__ void cert_begin_kernel(mf_cert_out *out, int *colmark, int m, unsigned long long *times)
 {
+    note_time(times, AT_CERT);
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j < m) colmark[j] = 0;
     if (j == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
@@ -190,18 +194,19 @@ int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ld
                        const int32_t *d_row2col, const int64_t *d_u, const int64_t *d_v,
                        int64_t K, mf_result *h_res, bool begun)
 {
-    if (!begun) hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->cert, ctx->colmark, m);
+    if (!begun) hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->cert, ctx->colmark, m, ctx->times);
     const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
     hipLaunchKernelGGL(K >= INT32_MIN && K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>,
                        dim3(grid), dim3(BID_THREADS), 0, ctx->stream, d_W, ldw, n, m,
-                       d_row2col, d_u, d_v, (long long)K, ctx->colmark, ctx->cert);
+                       d_row2col, d_u, d_v, (long long)K, ctx->colmark, ctx->cert, begun ? ctx->times : nullptr);
     MF_HIP(hipGetLastError());
-    MF_HIP(hipEventRecord(ctx->ev[6], ctx->stream));
     // the last wait of a call: what else the host wants to know comes along with it
-    MF_HIP(hipMemcpyAsync(ctx->h_cert, ctx->cert, sizeof(mf_cert_out), hipMemcpyDeviceToHost, ctx->stream));
-    if (ctx->score_pending)
-        MF_HIP(hipMemcpyAsync(ctx->h_pairs_evaluated, ctx->pairs_evaluated, sizeof(unsigned long long), hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
+    const int rc = mf_send_and_await(ctx, mf_report{{{ctx->cert, ctx->h_cert, (int)(sizeof(mf_cert_out) / 4)},
+                                                     {ctx->times, ctx->h_times, 2 * AT_COUNT},
+                                                     {ctx->pairs_evaluated, ctx->h_pairs_evaluated, 2},
+                                                     {ctx->stats, ctx->h_stats, (int)(sizeof(mf_device_stats) / 4)}}});
+    if (rc != MF_OK) return rc;
+    ctx->timings[T_CERT] = mf_ms(ctx, ctx->h_times[AT_CERT], ctx->h_told->at);
     const mf_cert_out &c = *ctx->h_cert;
     h_res->primal = c.primal;
     h_res->dual = c.dual;
@@ -224,11 +229,11 @@ int mf_extract_duals(mf_ctx *ctx, const int32_t *A, int64_t lda, int rn, int rm,
     const auto kernel = line_len ? duals_kernel<256, 1> : duals_kernel<64, 4>;
     if (!flip && !staged) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, ctx->stream, A, lda, rn, rm,
-                           ctx->price, ctx->row2col, Kd, d_row2col, d_u, d_v, line_len);
+                           ctx->price, ctx->row2col, Kd, d_row2col, d_u, d_v, line_len, ctx->times);
     } else {
         int64_t *u_int = (int64_t *)ctx->path_label, *v_int = (int64_t *)ctx->path_expanded;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, ctx->stream, A, lda, rn, rm,
-                           ctx->price, ctx->row2col, Kd, ctx->list[0], u_int, v_int, line_len);
+                           ctx->price, ctx->row2col, Kd, ctx->list[0], u_int, v_int, line_len, ctx->times);
         hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, d_row2col, n, -1);
         const int32_t *row_ids = staged ? (flip ? ctx->order_off : ctx->order_on) : nullptr;
         const int32_t *col_ids = staged ? (flip ? ctx->order_on : ctx->order_off) : nullptr;
@@ -295,10 +300,10 @@ extern "C" int mf_check_certificate_noalloc(void *hip_stream, const int32_t *d_W
     hipStream_t stream = (hipStream_t)hip_stream;
     // the array keeps what the previous call left: both parts are cleared by a kernel (no
     // memset node, so the sequence can be captured into a graph)
-    hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, out, colmark, m);
+    hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, out, colmark, m, (unsigned long long *)nullptr);
     const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
     hipLaunchKernelGGL(K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>, dim3(grid),
-                       dim3(BID_THREADS), 0, stream, d_W, ldw, n, m, d_row2col, d_u, d_v, (long long)K, colmark, out);
+                       dim3(BID_THREADS), 0, stream, d_W, ldw, n, m, d_row2col, d_u, d_v, (long long)K, colmark, out, (unsigned long long *)nullptr);
     hipLaunchKernelGGL(noalloc_finish_kernel, dim3(1), dim3(1), 0, stream, out, (long long)K, d_out);
     return hipGetLastError() == hipSuccess ? MF_OK : MF_ERR_HIP;
 }

@@ -23,6 +23,7 @@
 // 12,000 x 16,000 29.8 / 26.6, 20,000 x 20,000 29.6 / 24.5; 20,000 x 40,000 with prefixes of a tenth
 // 21.6 / 20.8.  The line is drawn at 8192 rows.
 #include "scan.h"
+#include "report.h"
 #include "half_list.h"
 #include "search_words.h"
 #include "team_join.h"
@@ -306,6 +307,13 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
 
 // ---------------------------------------------------------------- the engine
 
+struct CoreReport {
+    int reason, phase, stage, count, parity;
+    unsigned columns_ready;
+    unsigned long long bids, depth, steps, scans, whole_groups, rested;      // (whole_groups: of four entries, of lines read whole)
+};
+static_assert(sizeof(CoreReport) % 8 == 0, "told in words");
+
 struct alignas(256) CoreCtl {
     // who takes part: the workgroups of the die the first one to arrive runs on
     int die;
@@ -327,13 +335,8 @@ struct alignas(256) CoreCtl {
     alignas(128) unsigned jump_pending[CORE_JUMP_PASSES + 1];
     // refinement
     alignas(128) unsigned failed[3];
-    // the phases
-    alignas(128) double eps[MF_CORE_PHASES];
-    int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];   // bidders that may be left over (second: while few have given up)
-    // what the launch reports
-    alignas(128) int reason, phase, stage, count, parity;
-    unsigned columns_ready;
-    unsigned long long bids, depth, steps, scans, whole_groups, rested;      // (whole_groups: of four entries, of lines read whole)
+    // what the launch reports (phase -1: it did not get to one)
+    alignas(128) CoreReport out;
 };
 
 struct CoreSide {
@@ -354,6 +357,8 @@ struct CoreArgs {
     CoreSide side[2];                   // 0: rows bid, 1: columns bid
     double Kd;
     int n_phases, first_phase, first_stage, first_count, first_parity;
+    double eps[MF_CORE_PHASES];
+    int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES];   // bidders that may be left over (second: while few have given up)
     int growth_rest;
     unsigned long long rested_before;
     int have_columns;                   // the lists of side 1 exist
@@ -1650,7 +1655,8 @@ __device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int sta
     __syncthreads();
     if (tid < 4) sh.list[tid] = 0ull;
     __syncthreads();
-    unsigned long long *sums[4] = {&ctl->bids, &ctl->scans, &ctl->whole_groups, &ctl->rested};
+    CoreReport &out = ctl->out;
+    unsigned long long *sums[4] = {&out.bids, &out.scans, &out.whole_groups, &out.rested};
     const unsigned mine[4] = {bids, scans, whole, rests};
     if (lane == 0) {
 #pragma unroll
@@ -1666,14 +1672,14 @@ __device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int sta
     // a wait that runs out here still counts: the reason stays "a wait ran out"
     if (reason == MF_CORE_ABORT || !barrier()) return MF_CORE_ABORT;
     if (gtid() == 0) {
-        ctl->reason = reason;
-        ctl->phase = phase;
-        ctl->stage = stage;
-        ctl->count = count;
-        ctl->parity = parity;
-        ctl->steps = steps;
-        ctl->columns_ready = columns_ready;
-        ctl->depth = depth;
+        out.reason = reason;
+        out.phase = phase;
+        out.stage = stage;
+        out.count = count;
+        out.parity = parity;
+        out.steps = steps;
+        out.columns_ready = columns_ready;
+        out.depth = depth;
     }
     return reason;
 }
@@ -1689,12 +1695,12 @@ __device__ __forceinline__ int Core<LARGE>::run()
     if (stage == MF_CORE_FORWARD_DONE) left_rows = count;
     if (stage == MF_CORE_REVERSE_DONE) left_cols = count;
     for (;;) {
-        const double eps = ctl->eps[ph];
+        const double eps = a.eps[ph];
         // (added to at the end of a forward side: barriers of that side before it, of the next stage after it)
-        const int stop = a.rested_before + load_fresh_u64(&ctl->rested) < (unsigned long long)a.growth_rest ? ctl->stop_grown[ph] : ctl->stop[ph];
+        const int stop = a.rested_before + load_fresh_u64(&ctl->out.rested) < (unsigned long long)a.growth_rest ? a.stop_grown[ph] : a.stop[ph];
         if (stage == MF_CORE_RESET && a.use_wide && !a.wide) return leave(MF_CORE_HANDOVER, ph, stage, 0, 0);
         if (stage == MF_CORE_RESET) {
-            if (gtid() == 0) store_i32(&ctl->phase, ph);
+            if (gtid() == 0) store_i32(&ctl->out.phase, ph);
             for (int k = gtid(); k < fwd.len; k += gsize()) {
                 store_through(&fwd.otherword[k], pack_word(load_fresh(&fwd.other_dual[k]), 0));
                 store_i32(&a.col2row[k], -1);
@@ -1724,7 +1730,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
             else { left_cols = count; stage = MF_CORE_REVERSE_DONE; }
         }
         if (stage == MF_CORE_FORWARD_DONE) {
-            if (lane == 0 && rests) atomicAdd(&ctl->rested, (unsigned long long)rests);
+            if (lane == 0 && rests) atomicAdd(&ctl->out.rested, (unsigned long long)rests);
             rests = 0;
             for (int i = gtid(); i < fwd.lines; i += gsize()) {
                 store_i32(&a.row2col[i], -1);
@@ -1760,7 +1766,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
             // in 2, 3, 4, 6, 10 feasible 104 / 26, 72 / 21, 50 / 23, 50 / 33, 20 / 17 ms; sixteen 20,000 x 20,000 rounds
             // 28.2 / 24.8 (median), nine rounds after those 31.0 / 27.7.  In every phase: 28.1; also in the first on
             // lists: 28.6.
-            const bool next_complete = ph + 1 >= a.n_phases || ctl->stop[ph + 1] == 0;
+            const bool next_complete = ph + 1 >= a.n_phases || a.stop[ph + 1] == 0;
             const int most_unused = stop > 0 && !next_complete ? stop + left_rows : stop;
             if (left_rows > 0 && count > most_unused) {
                 // rows that still wanted to bid get the profit that covers all of their pairs (see settle_unplaced_kernel)
@@ -1833,23 +1839,25 @@ __global__ __launch_bounds__(CORE_THREADS) void core_kernel(CoreArgs a, CoreCtl 
     (void)core.run();
 }
 
-struct CorePhases { double eps[MF_CORE_PHASES]; int stop[MF_CORE_PHASES], stop_grown[MF_CORE_PHASES]; };
-
-__global__ void core_begin_kernel(CoreCtl *ctl, int phase, CorePhases phases)
+// The control block as a launch wants to find it (one wavefront).
+__device__ __forceinline__ void clear_control(CoreCtl *ctl, int lane)
 {
-    for (int k = threadIdx.x; k < CORE_MAX_WORKGROUPS; k += blockDim.x) ctl->reached[k] = 0u;
-    if (threadIdx.x < MF_CORE_PHASES) {
-        ctl->eps[threadIdx.x] = phases.eps[threadIdx.x];
-        ctl->stop[threadIdx.x] = phases.stop[threadIdx.x];
-        ctl->stop_grown[threadIdx.x] = phases.stop_grown[threadIdx.x];
-    }
-    if (threadIdx.x != 0) return;
+    for (int k = lane; k < CORE_MAX_WORKGROUPS; k += 64) ctl->reached[k] = 0u;
+    if (lane != 0) return;
     ctl->die = -1;
     ctl->joined = 0u; ctl->arrived = 0u; ctl->members = 0u;
-    ctl->reason = MF_CORE_ABORT; ctl->phase = phase; ctl->stage = MF_CORE_RESET; ctl->count = 0; ctl->parity = 0;
     for (unsigned q = 0; q < STEP_RING; ++q) { ctl->cnt[q] = 0; ctl->whole_count[q] = 0; ctl->dense[q] = 0u; }
-    ctl->columns_ready = 0u;
-    ctl->bids = 0ull; ctl->depth = 0ull; ctl->steps = 0ull; ctl->scans = 0ull; ctl->whole_groups = 0ull; ctl->rested = 0ull;
+    ctl->out = CoreReport{MF_CORE_ABORT, -1, MF_CORE_RESET, 0, 0, 0u, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
+}
+
+__global__ __launch_bounds__(64) void core_clear_kernel(CoreCtl *ctl) { clear_control(ctl, threadIdx.x); }
+
+// Tells the host how a launch ended, and leaves the control block clear for the next one.
+__global__ __launch_bounds__(64) void core_report_kernel(CoreCtl *ctl, void *to, unsigned *told, unsigned number)
+{
+    tell(&ctl->out, to, (int)(sizeof(CoreReport) / 4), threadIdx.x);
+    tell_number(told, number, threadIdx.x);
+    clear_control(ctl, threadIdx.x);
 }
 
 }  // namespace
@@ -1894,8 +1902,8 @@ int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, do
     const int stride = (lines + MF_CORE_PROBES - 1) / MF_CORE_PROBES, probes = (lines + stride - 1) / stride;
     launch_lists(ctx, s, probes, stride, nullptr, 0, ctx->core_depth, nullptr, nullptr, nullptr);
     MF_HIP(hipGetLastError());
-    MF_HIP(hipMemcpyAsync(ctx->h_core_depth, ctx->core_depth, sizeof(double) * probes, hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
+    const int rc = mf_send_and_await(ctx, mf_report{{{ctx->core_depth, ctx->h_core_depth, 2 * probes}}});
+    if (rc != MF_OK) return rc;
     int n = 0;
     for (int k = 0; k < probes; ++k) n += ctx->h_core_depth[k] >= distance;
     *deep = (double)n / probes;
@@ -1913,8 +1921,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.side[0] = CoreSide{fwd.A, fwd.pitch, rn, rm, read_limit(fwd, rn), fwd.line_len, ctx->colword, ctx->price, ctx->core_entries[0], ctx->core_t_start[0], ctx->core_t_at[0], ctx->core_t_entries[0], ctx->core_bound[0], ctx->core_half_bound[0], ctx->core_built[0], ctx->core_reach[0]};
     a.side[1] = CoreSide{rev.A, rev.pitch, rm, rn, read_limit(rev, rm), rev.line_len, ctx->roword, ctx->profit, ctx->core_entries[1], ctx->core_t_start[1], ctx->core_t_at[1], ctx->core_t_entries[1], ctx->core_bound[1], ctx->core_half_bound[1], ctx->core_built[1], ctx->core_reach[1]};
     a.Kd = fwd.Kd;
-    CorePhases phases{};
-    for (int k = 0; k < plan.n_phases; ++k) { phases.eps[k] = (double)plan.eps[k]; phases.stop[k] = plan.stop[k]; phases.stop_grown[k] = plan.stop_grown[k]; }
+    for (int k = 0; k < plan.n_phases; ++k) { a.eps[k] = (double)plan.eps[k]; a.stop[k] = plan.stop[k]; a.stop_grown[k] = plan.stop_grown[k]; }
     a.n_phases = plan.n_phases;
     a.first_phase = st->phase; a.first_stage = st->stage; a.first_count = st->count; a.first_parity = st->parity;
     a.growth_rest = ctx->phase_growth_rest;
@@ -1957,17 +1964,22 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     a.stamp = ctx->path_stamp; a.held = ctx->path_held; a.jump = ctx->path_jump;
     a.parent = ctx->core_parent; a.read_from = ctx->core_read_from; a.left = ctx->path_base; a.whole0 = ctx->path_tree; a.whole1 = ctx->path_parent; a.held_weight = ctx->core_weight;
     CoreCtl *ctl = (CoreCtl *)ctx->core_ctl;
-    hipLaunchKernelGGL(core_begin_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl, st->phase, phases);
+    if (!ctx->core_clear) hipLaunchKernelGGL(core_clear_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl);
+    ctx->core_clear = false;
     // one workgroup per compute unit of the device: those of one die stay
     hipLaunchKernelGGL(plan.use_wide ? core_kernel<true> : core_kernel<false>, dim3(ctx->n_cus), dim3(CORE_THREADS), 0, ctx->stream, a, ctl);
     MF_HIP(hipGetLastError());
-    MF_HIP(hipMemcpyAsync(ctx->h_core_ctl, ctl, sizeof(CoreCtl), hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
-    const CoreCtl &h = *(const CoreCtl *)ctx->h_core_ctl;
+    const unsigned report = ++ctx->reports;
+    hipLaunchKernelGGL(core_report_kernel, dim3(1), dim3(64), 0, ctx->stream, ctl, ctx->h_core_report, &ctx->h_told->number, report);
+    MF_HIP(hipGetLastError());
+    const int rc = mf_await(ctx, report);
+    if (rc != MF_OK) return rc;
+    ctx->core_clear = true;                             // (behind the report, and before anything else on the stream)
+    const CoreReport &h = *(const CoreReport *)ctx->h_core_report;
     st->by_column += __builtin_popcount(h.columns_ready & ~st->columns_ready);
     st->columns_ready = h.columns_ready;
     st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
-    st->reason = h.reason; st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
+    st->reason = h.reason; if (h.phase >= 0) st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
     st->launches += 1;
@@ -1977,4 +1989,5 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
 }
 
 size_t mf_core_ctl_bytes() { return sizeof(CoreCtl); }
+size_t mf_core_report_bytes() { return sizeof(CoreReport); }
 

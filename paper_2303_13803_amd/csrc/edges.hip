@@ -9,6 +9,7 @@
 // run, whose steps are bound by latency, and the final passes (duals, certificate) keep reading
 // the matrix itself.
 #include "scan.h"
+#include "report.h"
 
 namespace {
 
@@ -51,8 +52,10 @@ __global__ __launch_bounds__(256) void edge_count_kernel(const int32_t *__restri
 }
 
 // Where each row's list starts: running sums of the padded counts (one workgroup).
-__global__ __launch_bounds__(1024) void edge_offsets_kernel(const int *__restrict__ padded_count, int n, long long *__restrict__ start)
+__global__ __launch_bounds__(1024) void edge_offsets_kernel(const int *__restrict__ padded_count, int n, long long *__restrict__ start,
+                                                            unsigned long long *times)
 {
+    note_time(times, AT_PREPARED);
     __shared__ long long s_sum[1024];
     const int per = (n + 1023) / 1024, first = threadIdx.x * per;
     long long mine = 0;
@@ -134,6 +137,7 @@ __global__ __launch_bounds__(64) void round_lists_kernel(SideArgs s, const int *
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         stats->cnt[(ring + 2) & 3] = 0;
         stats->head = 0;
+        stats->round_at = device_time();
         if (count > 0) {
             stats->rounds += 1ull;
             stats->bids += (unsigned long long)count;
@@ -195,7 +199,7 @@ int mf_build_edge_lists(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t l
     int *col = (int *)ctx->staged;
     int32_t *weight = ctx->staged + capacity;
     ctx->staged_n = ctx->staged_m = 0;                          // whatever was staged there is gone
-    hipLaunchKernelGGL(edge_offsets_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->edge_count, n, ctx->edge_start);
+    hipLaunchKernelGGL(edge_offsets_kernel, dim3(1), dim3(1024), 0, ctx->stream, ctx->edge_count, n, ctx->edge_start, ctx->times);
     hipLaunchKernelGGL(edge_fill_kernel, dim3(n < 8192 ? n : 8192), dim3(256), 0, ctx->stream, d_W, n, m, ldw,
                        ctx->edge_start, col, weight);
     MF_HIP(hipGetLastError());

@@ -40,6 +40,19 @@ enum { MF_CORE_DONE = 1,        // the matching is complete and its prices are g
        MF_CORE_HANDOVER };      // on from here on all dies, or on one
 enum { MF_CORE_RESET = 0, MF_CORE_FORWARD, MF_CORE_FORWARD_DONE, MF_CORE_REVERSE, MF_CORE_REVERSE_DONE, MF_CORE_PHASE_DONE };
 
+// When a call's stages began (mf_ctx::times, ticks of the device's constant clock): noted by the first kernel of each.
+enum { AT_SCORE = 0, AT_PAIRS, AT_PLACE, AT_SCORED, AT_SOLVE, AT_PREPARED, AT_DUALS, AT_CERT, AT_COUNT };
+
+// Up to so many stretches of device memory stored into pinned memory (report.hip).
+constexpr int MF_REPORT_PIECES = 4;
+struct mf_report {
+    struct { const void *from; void *to; int words; } piece[MF_REPORT_PIECES];      // of four bytes
+};
+struct mf_told {                    // pinned
+    alignas(64) unsigned number;    // of the last report that is there
+    alignas(64) unsigned long long at;      // when it was made
+};
+
 struct mf_device_stats {            // lives in device memory, cleared per solve
     unsigned long long rounds;      // bidding rounds
     unsigned long long bids;        // bids evaluated (one line scan each)
@@ -52,6 +65,7 @@ struct mf_device_stats {            // lives in device memory, cleared per solve
     unsigned long long path_scans;  // line scans those searches made
     unsigned long long launch_max;  // scratch: that maximum for the chain kernel in flight
     unsigned long long feasible_pairs;      // of the matrix, where the scoring pass counted them (else ~0)
+    unsigned long long round_at;    // when the last bidding round began
     int max_weight;
     int cnt[4];                     // ring of bidder-list lengths: round r reads cnt[r & 3]
     int head;                       // next unclaimed entry of the list a chain kernel works through
@@ -187,7 +201,8 @@ struct mf_ctx : mf_options {
     double *core_base, *core_dropped;
     unsigned long long *core_parent, *core_read_from;
     int32_t *core_weight;
-    void *core_ctl, *h_core_ctl;
+    void *core_ctl, *h_core_report;
+    bool core_clear;                // the control block is as a launch wants to find it
     int *list[2];
     int *colmark;                   // [max_m]
     mf_device_stats *stats;
@@ -195,13 +210,18 @@ struct mf_ctx : mf_options {
     // pinned host mirrors
     mf_device_stats *h_stats;
     mf_device_stats *h_stats_slot[2];   // pinned: where the counts of bulk rounds land while the next round runs
-    hipEvent_t ev_stats[2];
+    int32_t *h_type_first;              // pinned: where each type's rows start
+    int *h_bad;                         // pinned: an index or a type was out of range
+    mf_told *h_told;
+    unsigned reports;                   // sent so far
     unsigned *score_range;              // device: largest magnitudes the scorer's fp16 pieces are scaled by (project_kernel)
     mf_cert_out *h_cert;
     // timing
-    hipEvent_t ev[10];              // 0..2 and 8: scoring stages; 3..7 and 9: solver stages
+    unsigned long long *times, *h_times;        // [AT_COUNT] device, pinned
+    double clock_khz;               // of the clock they are in
+    hipEvent_t ev[2];               // (mf_measure_ceilings)
     float timings[T_COUNT];
-    bool score_pending;             // score events recorded but not yet read
+    bool score_pending, score_placed;       // times of a scoring pass noted but not yet read; it put the scores in place
 };
 
 // One side of the auction as its kernels see it (rows bidding for columns, or the reverse).
@@ -228,6 +248,13 @@ struct SideArgs {
     int *rested;                        // optional: counts the bidders that rest (best value at most eps)
 };
 
+// report.hip
+int mf_send(mf_ctx *ctx, const mf_report &r, unsigned *number);         // on the stream; *number says which it is
+int mf_await(mf_ctx *ctx, unsigned number);                             // until that one is there
+int mf_send_and_await(mf_ctx *ctx, const mf_report &r);
+void mf_note_time(mf_ctx *ctx, int stage);                              // by a launch of its own
+inline mf_report mf_report_stats(const mf_ctx *ctx, mf_device_stats *to) { return mf_report{{{ctx->stats, to, (int)(sizeof(mf_device_stats) / 4)}}}; }
+inline float mf_ms(const mf_ctx *ctx, unsigned long long from, unsigned long long to) { return to > from ? (float)((double)(to - from) / ctx->clock_khz) : 0.0f; }
 // score.hip
 int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const int32_t *d_type,
                     const float *d_on, int n, const float *d_off, int m, int32_t *d_W, int64_t ldw,
@@ -270,7 +297,7 @@ int mf_core_lists(mf_ctx *ctx, const SideArgs &s, int lines, int which, const do
 int mf_core_lists_of(mf_ctx *ctx, const SideArgs &s, const int *list, int count, int which);
 int mf_core_probe(mf_ctx *ctx, const SideArgs &s, int lines, double distance, double *deep);
 int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn, int rm, const mf_core_plan &plan, mf_core_state *st);
-size_t mf_core_ctl_bytes();
+size_t mf_core_ctl_bytes(), mf_core_report_bytes();
 // certificate.hip
 int mf_extract_duals(mf_ctx *ctx, const int32_t *A, int64_t lda, int rn, int rm, double Kd, const int *line_len,
                      int n, bool flip, bool staged, int32_t *d_row2col, int64_t *d_u, int64_t *d_v);

@@ -11,7 +11,7 @@
 // the MFMA tile, so each lane ends up owning whole pairs and the output layer,
 // logistic, quantisation and memory-fit mask run in registers before one
 // coalesced int32 store.
-#include "internal.h"
+#include "report.h"
 #include <math.h>
 #include <type_traits>
 
@@ -134,10 +134,12 @@ struct SetupArgs {
     unsigned long long *pairs_evaluated, *feasible_pairs;
     int *largest;
     unsigned *range;
+    unsigned long long *times;
 };
 
 __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
 {
+    note_time(a.times, AT_SCORE);
     const int side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
     if (side == 0 && r < 8) {
         a.range[r] = 0u;
@@ -303,8 +305,9 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
                                                     const int32_t *__restrict__ rank_off,
                                                     const int32_t *__restrict__ fit_len, int n, int m,
                                                     int32_t *__restrict__ W, int64_t ldw, int wide_stores,
-                                                    int *largest)
+                                                    int *largest, unsigned long long *times)
 {
+    note_time(times, AT_PLACE);
     const int i = blockIdx.x, from = rank_on[i], len = fit_len[from];       // entries at or beyond len cannot share
     const int32_t *src = S + (size_t)from * lds;
     int32_t *row = W + (size_t)i * ldw;
@@ -341,8 +344,9 @@ constexpr int64_t PLACE_LONGEST = 40704;                  // columns up to which
 __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
     const int32_t *__restrict__ S, int64_t lds, const int32_t *__restrict__ rank_on,
     const int32_t *__restrict__ rank_off, const int32_t *__restrict__ fit_len, int n, int m,
-    int32_t *__restrict__ W, int64_t ldw, int wide_stores, int *largest)
+    int32_t *__restrict__ W, int64_t ldw, int wide_stores, int *largest, unsigned long long *times)
 {
+    note_time(times, AT_PLACE);
     __shared__ int32_t staged[PLACE_LDS_ENTRIES];
     const int i = blockIdx.x, tid = threadIdx.x;
     const int from = rank_on[i];
@@ -429,8 +433,9 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     unsigned long long *__restrict__ evaluated, const int32_t *__restrict__ segment,
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
-    const unsigned *__restrict__ range, int tile_rows)
+    const unsigned *__restrict__ range, int tile_rows, unsigned long long *times)
 {
+    note_time(times, AT_PAIRS);
     using S = PairShape<H>;
     constexpr int KS = S::KS, MB = S::MB, ROWS = S::ROWS, Q = KS / 4, KB = H / 16;
     extern __shared__ float4 lds4[];
@@ -799,7 +804,7 @@ int pair_tile_rows(int rows, int column_tiles, int units)
 template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
 int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, int64_t ldw,
                         float *d_sigma, const int32_t *row_map, const int32_t *col_map, bool by_memory,
-                        const int32_t *segment, int grid_rows)
+                        const int32_t *segment, int grid_rows, unsigned long long *times)
 {
     using S = PairShape<H>;
     // (the attribute belongs to the device, so what has been set is remembered per context)
@@ -817,7 +822,7 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
-                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, tile_rows);
+                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, tile_rows, times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
@@ -825,12 +830,12 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
 template <int H>
 int launch_pair(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, int64_t ldw,
                 float *d_sigma, const int32_t *row_map, const int32_t *col_map, bool by_memory,
-                const int32_t *segment = nullptr, int segment_rows = -1)
+                unsigned long long *times, const int32_t *segment = nullptr, int segment_rows = -1)
 {
     const int grid_rows = segment_rows >= 0 ? segment_rows : n;
     const int which = (p->d_W1sm ? 4 : 0) + (p->d_W3_slow ? 2 : 0) + (ctx->score_split ? 1 : 0);
 #define MF_PAIR_CASE(SM, SLOW, SPL) \
-    return launch_pair_variant<H, SM, SLOW, SPL>(ctx, p, n, m, d_W, ldw, d_sigma, row_map, col_map, by_memory, segment, grid_rows)
+    return launch_pair_variant<H, SM, SLOW, SPL>(ctx, p, n, m, d_W, ldw, d_sigma, row_map, col_map, by_memory, segment, grid_rows, times)
     switch (which) {
     case 0: MF_PAIR_CASE(false, false, false);
     case 1: MF_PAIR_CASE(false, false, true);
@@ -874,6 +879,7 @@ SetupArgs setup_args(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int 
     a.mem_limit = p->mem_limit;
     a.pairs_evaluated = ctx->pairs_evaluated;
     a.range = ctx->score_range;
+    a.times = ctx->times;
     return a;
 }
 
@@ -910,21 +916,17 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
 {
     const mf_predictor *p0 = &preds[0];
     const bool typed = d_type != nullptr;
-    int32_t type_first[MF_MAX_TYPES + 1] = {0};
     if (typed) {
         hipLaunchKernelGGL(fill_flag_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->colmark);
         hipLaunchKernelGGL(type_segments_kernel, dim3(1), dim3(1024), 0, ctx->stream, d_type, n, n_types,
                            ctx->type_segment, ctx->colmark);
         MF_HIP(hipGetLastError());
-        int bad = 0;
-        MF_HIP(hipMemcpyAsync(&bad, ctx->colmark, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
         // the host sizes each type's launch by its number of rows
-        MF_HIP(hipMemcpyAsync(type_first, ctx->type_segment, sizeof(int32_t) * (size_t)(n_types + 1),
-                              hipMemcpyDeviceToHost, ctx->stream));
-        MF_HIP(hipStreamSynchronize(ctx->stream));
-        if (bad) return MF_ERR_ARG;
+        const int rc = mf_send_and_await(ctx, mf_report{{{ctx->colmark, ctx->h_bad, 1}, {ctx->type_segment, ctx->h_type_first, n_types + 1}}});
+        if (rc != MF_OK) return rc;
+        if (*ctx->h_bad) return MF_ERR_ARG;
     }
-    MF_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
+    const int32_t *type_first = ctx->h_type_first;
     // Pairs whose memory fractions do not fit get no score, so unless the caller wants every
     // score, walk rows and columns in memory order: the pairs that cannot fit then form one
     // corner of the tile grid and the kernel leaves them out.  Results land at the same places.
@@ -978,36 +980,36 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     // in memory order the scores go to the staged matrix
     int32_t *out = by_memory ? ctx->staged : d_W;
     const int64_t ldo = by_memory ? lds : ldw;
+    unsigned long long *times = ctx->times;
     for (int t = 0; t < n_types; ++t) {
         const mf_predictor *p = &preds[t];
         const int H = p->H;
         if (t > 0) hipLaunchKernelGGL(range_clear_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->score_range);
         launch_projections(ctx, p, d_on, n, d_off, m);
         MF_HIP(hipGetLastError());
-        if (t == 0) MF_HIP(hipEventRecord(ctx->ev[1], ctx->stream));      // later types' projections count as scoring
         const int32_t *segment = typed ? ctx->type_segment + t : nullptr;
         const int segment_rows = typed ? type_first[t + 1] - type_first[t] : -1;
         if (segment_rows == 0) continue;                                   // no workload of this type
-        int rc = (H == 64) ? launch_pair<64>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, segment, segment_rows)
-                           : launch_pair<128>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, segment, segment_rows);
+        int rc = (H == 64) ? launch_pair<64>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, segment, segment_rows)
+                           : launch_pair<128>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, segment, segment_rows);
+        times = nullptr;                                                   // (later types' projections count as scoring)
         if (rc != MF_OK) return rc;
     }
-    MF_HIP(hipEventRecord(ctx->ev[2], ctx->stream));
     if (by_memory) {
         const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
         const int wide = ((uintptr_t)d_W & 15u) == 0 && (ldw & 3) == 0;
         if (lds <= PLACE_LONGEST) {
             hipLaunchKernelGGL(place_lds_kernel, dim3(n), dim3(PLACE_THREADS), 0, ctx->stream,
                                ctx->staged, lds, ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide,
-                               ctx->largest_weight);
+                               ctx->largest_weight, ctx->times);
         } else {
             hipLaunchKernelGGL(place_kernel, dim3(n, chunks), dim3(256), 0, ctx->stream, ctx->staged, lds,
-                               ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide, ctx->largest_weight);
+                               ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide, ctx->largest_weight, ctx->times);
         }
         MF_HIP(hipGetLastError());
         ctx->largest_weight_known = true;
     }
-    MF_HIP(hipEventRecord(ctx->ev[8], ctx->stream));
+    ctx->score_placed = by_memory;
     ctx->score_pending = true;
     return MF_OK;
 }
@@ -1042,27 +1044,23 @@ int mf_launch_rescore(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int
         hipLaunchKernelGGL(check_indices_kernel, dim3((n_cols + 255) / 256), dim3(256), 0, ctx->stream, d_cols,
                            n_cols, m, ctx->colmark);
     MF_HIP(hipGetLastError());
-    int bad = 0;
-    MF_HIP(hipMemcpyAsync(&bad, ctx->colmark, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    MF_HIP(hipStreamSynchronize(ctx->stream));
-    if (bad) return MF_ERR_ARG;
-    MF_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
+    int rc = mf_send_and_await(ctx, mf_report{{{ctx->colmark, ctx->h_bad, 1}}});
+    if (rc != MF_OK) return rc;
+    if (*ctx->h_bad) return MF_ERR_ARG;
     const SetupArgs a = setup_args(ctx, p, d_on, n, d_off, m);
     hipLaunchKernelGGL(setup_kernel, dim3(((n > m ? n : m) + 255) / 256, 2), dim3(256), 0, ctx->stream, a);
     launch_projections(ctx, p, d_on, n, d_off, m);          // of everybody, and so the range, as in a full scoring pass
     MF_HIP(hipGetLastError());
     ctx->pairs_total = (double)n_rows * (double)m + (double)n * (double)n_cols;
-    MF_HIP(hipEventRecord(ctx->ev[1], ctx->stream));
-    int rc = MF_OK;
+    if (n_rows == 0 && n_cols == 0) mf_note_time(ctx, AT_PAIRS);
     if (n_rows > 0)
-        rc = (H == 64) ? launch_pair<64>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false)
-                       : launch_pair<128>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false);
+        rc = (H == 64) ? launch_pair<64>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times)
+                       : launch_pair<128>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times);
     if (rc == MF_OK && n_cols > 0)
-        rc = (H == 64) ? launch_pair<64>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false)
-                       : launch_pair<128>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false);
+        rc = (H == 64) ? launch_pair<64>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times)
+                       : launch_pair<128>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times);
     if (rc != MF_OK) return rc;
-    MF_HIP(hipEventRecord(ctx->ev[2], ctx->stream));
-    MF_HIP(hipEventRecord(ctx->ev[8], ctx->stream));
+    ctx->score_placed = false;
     ctx->score_pending = true;
     return MF_OK;
 }

@@ -15,6 +15,7 @@
 // (The order of the two parts is that of Jonker and Volgenant 1987, "A shortest augmenting path algorithm for dense and
 // sparse linear assignment problems".)
 #include "scan.h"
+#include "report.h"
 
 namespace {
 
@@ -94,8 +95,10 @@ template <int C>
 __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__restrict__ W, SmallShape s, long long K, int limit,
                                                               int32_t *__restrict__ out_row2col, int64_t *__restrict__ out_u,
                                                               int64_t *__restrict__ out_v, int *__restrict__ colmark,
-                                                              mf_cert_out *__restrict__ out)
+                                                              mf_cert_out *__restrict__ out, unsigned long long *times)
 {
+    note_time(times, AT_SCORED);
+    note_time(times, AT_SOLVE);
     extern __shared__ __align__(32) int lds[];
     // Rows of LDS: the weights of row r (negative: infeasible), its profit and the column it holds, from r * pitch on, which is
     // what names a row below; then zeros for the last lanes to read on into, the rows that wait, the prices.
@@ -274,7 +277,7 @@ int launch_small(mf_ctx *ctx, const SmallShape &s, const int32_t *d_W, long long
         ctx->kernels_configured |= flag;
     }
     hipLaunchKernelGGL((small_kernel<C>), dim3(1), dim3(SMALL_THREADS), small_bytes(s, C), ctx->stream, d_W, s, K,
-                       (int)(ctx->max_rounds < INT32_MAX ? ctx->max_rounds : INT32_MAX), d_row2col, d_u, d_v, ctx->colmark, ctx->cert);
+                       (int)(ctx->max_rounds < INT32_MAX ? ctx->max_rounds : INT32_MAX), d_row2col, d_u, d_v, ctx->colmark, ctx->cert, ctx->times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
