@@ -35,69 +35,95 @@ namespace {
 // once.  Later bidders of the same round may already see them (or a slightly
 // older dual): the auction tolerates both because duals only move one way and a
 // bid computed from an outdated dual simply fails to win.  The counters form a
-// ring: round r reads cnt[r], fills cnt[r+1] and clears cnt[r+2].
-constexpr int ROUND_GROUPS_PER_WORKGROUP = 128;
+// ring: launch r reads cnt[r], fills cnt[r+1] and clears cnt[r+2].
+//
+// A bid sets off at most one bidder (the holder it displaced, or itself), who takes its place in the next round's list: no
+// counter is touched.  Places where nobody has to go on hold -1, and compact_kernel takes them out before the
+// host, or any other kernel, looks at the list; what a place has cost since it was last full (its bids, its words read) adds up
+// in `work` until then.  (Handing bidders over by atomics on one counter, one a workgroup, bounded these rounds: 10 ns each, and
+// the workgroups that started meanwhile waited 7 us to read the count on the same line.  Rounds of 3000, 2000 and 1200 bidders
+// on lines of 6001 to 9007 entries 45 -> 26, 36 -> 24 and 26 -> 15 us; compact_kernel takes 5 us, once for three of them.)
+__device__ __forceinline__ unsigned long long work_of(unsigned long long words) { return (1ull << MF_WORK_WORDS) + words; }
 
 template <int NT, int RB>
 __global__ __launch_bounds__(NT, 3) void round_kernel(SideArgs s, const int *__restrict__ list,
                                                    int *__restrict__ next, mf_device_stats *stats,
-                                                   int ring)
+                                                   int ring, unsigned long long *__restrict__ work, int full)
 {
-    // Bidders this workgroup has to pass on are collected here and handed over together: the
-    // list counter is a single address, every atomic on it takes its turn, and thousands of
-    // workgroups that finish at the same moment would queue up behind it (measured: one such
-    // atomic per group of four lines costs a full-matrix round a fifth of its time).
-    // The launch gives every workgroup at most ROUND_GROUPS_PER_WORKGROUP groups of lines.
     __shared__ Top2 red[RB + RB * (NT / 64)];
-    __shared__ int s_hold[RB * ROUND_GROUPS_PER_WORKGROUP];
     const int count = stats->cnt[ring & 3];
-    int *ncnt = &stats->cnt[(ring + 1) & 3];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        stats->cnt[(ring + 1) & 3] = count;
         stats->cnt[(ring + 2) & 3] = 0;
         stats->head = 0;
         stats->round_at = device_time();
-        if (count > 0) {
-            stats->rounds += 1ull;
-            stats->bids += (unsigned long long)count;
-        }
+        if (count > 0) stats->rounds += 1ull;
     }
-    int held = 0;                                           // entries of s_hold in use (first wavefront, same in every lane)
-    unsigned long long entries = 0;                         // scanned by this workgroup (thread 0 keeps count)
     for (int item = blockIdx.x * RB; item < count; item += gridDim.x * RB) {
         int salt[RB], len = s.len;                          // (lines of different lengths go one by one)
         const int32_t *rows[RB];
+        bool any = false;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             const int b = list[min(item + r, count - 1)];   // a short last group repeats its last line
-            rows[r] = s.A + (size_t)b * s.pitch;
-            salt[r] = tie_salt(b);
-            if (RB == 1) len = line_length(s, b);
-            if (item + r < count) entries += (unsigned long long)len;
+            any |= b >= 0;
+            rows[r] = s.A + (size_t)max(b, 0) * s.pitch;
+            salt[r] = tie_salt(max(b, 0));
+            if (RB == 1) len = line_length(s, max(b, 0));
+        }
+        if (!any) {                                         // (the same in the whole workgroup)
+            if (threadIdx.x < RB && item + (int)threadIdx.x < count) next[item + threadIdx.x] = -1;
+            continue;
         }
         block_scan_rows<NT, RB>(rows, salt, s.other_dual, len, s.Kd, red);
-        if (threadIdx.x < 64) {                                      // first wavefront: one lane bids per line
+        if (threadIdx.x < RB && item + (int)threadIdx.x < count) {      // one lane bids per line
+            const int place = item + threadIdx.x, b = list[place];
             int again = -1;
-            if (threadIdx.x < RB && item + (int)threadIdx.x < count) {
-                const int b = list[item + threadIdx.x];
+            if (b >= 0) {
                 Top2 t = red[threadIdx.x];
                 t.idx ^= tie_salt(b);
                 again = decide_and_bid<true>(s, b, t);
+                work[place] = (full ? 0ull : work[place]) + work_of((unsigned long long)len);
             }
-            const unsigned long long pushing = __ballot(again >= 0);
-            if (pushing) {
-                if (again >= 0) s_hold[held + __popcll(pushing & ((1ull << threadIdx.x) - 1ull))] = again;
-                held += __popcll(pushing);
-            }
+            next[place] = again;
         }
     }
-    if (threadIdx.x < 64 && held > 0) {
-        int base = 0;
-        if (threadIdx.x == 0) base = atomicAdd(ncnt, held);
-        base = __shfl(base, 0);
-        for (int k = threadIdx.x; k < held; k += 64) next[base + k] = s_hold[k];
+}
+
+// The bidders left by the rounds since the list was last full, one behind the other, and what those rounds have cost.
+constexpr int COMPACT_THREADS = 1024;
+
+__global__ __launch_bounds__(COMPACT_THREADS) void compact_kernel(const int *__restrict__ list, int *__restrict__ next,
+                                                                  mf_device_stats *stats, int ring, const unsigned long long *__restrict__ work)
+{
+    constexpr int WAVES = COMPACT_THREADS / 64;
+    __shared__ int s_count[WAVES], s_base;
+    __shared__ unsigned long long s_bids[WAVES], s_words[WAVES];
+    const int count = stats->cnt[ring & 3], lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        stats->cnt[(ring + 2) & 3] = 0;
+        stats->round_end = device_time();
     }
-    // (a word with a cache line to itself: not behind the list counter)
-    if (threadIdx.x == 0 && entries) atomicAdd(&stats->round_bytes, entries * 4ull);
+    for (int first = blockIdx.x * COMPACT_THREADS; first < count; first += gridDim.x * COMPACT_THREADS) {
+        const int item = first + threadIdx.x;
+        const int b = item < count ? list[item] : -1;
+        const unsigned long long done = item < count ? work[item] : 0ull, going = __ballot(b >= 0);
+        unsigned long long bids = done >> MF_WORK_WORDS, words = done & ((1ull << MF_WORK_WORDS) - 1ull);
+        for (int off = 32; off >= 1; off >>= 1) { bids += __shfl_xor(bids, off); words += __shfl_xor(words, off); }
+        if (lane == 0) { s_count[wave] = __popcll(going); s_bids[wave] = bids; s_words[wave] = words; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int total = 0;
+            for (int w = 0; w < WAVES; ++w) { const int c = s_count[w]; s_count[w] = total; total += c; }
+            for (int w = 1; w < WAVES; ++w) { bids += s_bids[w]; words += s_words[w]; }
+            s_base = total ? atomicAdd(&stats->cnt[(ring + 1) & 3], total) : 0;
+            atomicAdd(&stats->bids, bids);
+            atomicAdd(&stats->round_bytes, words * 4ull);
+        }
+        __syncthreads();
+        if (b >= 0) next[s_base + s_count[wave] + __popcll(going & ((1ull << lane) - 1ull))] = b;
+        __syncthreads();                                    // before the next stretch overwrites the counts
+    }
 }
 
 // The tail of a run.  When few bidders are left, rounds are bound by launch
@@ -571,23 +597,22 @@ __global__ void init_solver_kernel(int n, int m, double *price, double *profit, 
 }
 
 template <int NT, int RB>
-void launch_round_shape(mf_ctx *ctx, const SideArgs &s, int count, int ring)
+void launch_round_shape(mf_ctx *ctx, const SideArgs &s, int count, int ring, bool full)
 {
     int grid = (count + RB - 1) / RB;
     if (grid > MAX_GRID) grid = MAX_GRID;
     // ten workgroups per compute unit read a matrix faster than one per group of lines: those that
-    // finish early take another group, and fewer of them queue for the list counter at the end
+    // finish early take another group
     const int cap = ctx->bulk_grid > 0 ? ctx->bulk_grid : 10 * (ctx->n_cus > 0 ? ctx->n_cus : 256);
     if (grid > cap) grid = cap;
-    const int groups = (count + RB - 1) / RB;               // (a workgroup's list of bidders to pass on holds so many groups)
-    if ((long long)grid * ROUND_GROUPS_PER_WORKGROUP < groups) grid = (groups + ROUND_GROUPS_PER_WORKGROUP - 1) / ROUND_GROUPS_PER_WORKGROUP;
     hipLaunchKernelGGL((round_kernel<NT, RB>), dim3(grid), dim3(NT), 0, ctx->stream, s, ctx->list[ring & 1],
-                       ctx->list[(ring + 1) & 1], ctx->stats, ring);
+                       ctx->list[(ring + 1) & 1], ctx->stats, ring, ctx->path_label, full ? 1 : 0);
 }
 
-void launch_round(mf_ctx *ctx, const SideArgs &s, int count, int ring)
+// full: nobody is missing from the list
+void launch_round(mf_ctx *ctx, const SideArgs &s, int count, int ring, bool full)
 {
-    if (s.edge_start && count >= 2048) { mf_launch_list_round(ctx, s, count, ring); return; }
+    if (s.edge_start && count >= 2048) { mf_launch_list_round(ctx, s, count, ring, ctx->path_label, full); return; }
     // Lines in groups per wavefront read the matrix fastest, and that is what counts when (nearly)
     // every line bids: the first round of a phase.  In the rounds after it, one line per workgroup
     // does better although it reads more slowly: bids land sooner, later bidders of the same round
@@ -596,11 +621,11 @@ void launch_round(mf_ctx *ctx, const SideArgs &s, int count, int ring)
     // is what a grouped round then waits for (20,000 x 40,000, a tenth feasible: 207 us, 130 to 174 one by one).
     const bool grouped = !s.line_len && count >= 2048 && (long long)count * 100 >= (long long)ctx->bulk_share * (long long)s.len_t;
     switch (grouped ? ctx->bulk_shape : 0) {
-    case 1: launch_round_shape<64, 4>(ctx, s, count, ring); break;
-    case 2: launch_round_shape<64, 2>(ctx, s, count, ring); break;
-    case 3: launch_round_shape<128, 4>(ctx, s, count, ring); break;
-    case 4: launch_round_shape<256, 4>(ctx, s, count, ring); break;
-    default: launch_round_shape<256, 1>(ctx, s, count, ring); break;
+    case 1: launch_round_shape<64, 4>(ctx, s, count, ring, full); break;
+    case 2: launch_round_shape<64, 2>(ctx, s, count, ring, full); break;
+    case 3: launch_round_shape<128, 4>(ctx, s, count, ring, full); break;
+    case 4: launch_round_shape<256, 4>(ctx, s, count, ring, full); break;
+    default: launch_round_shape<256, 1>(ctx, s, count, ring, full); break;
     }
 }
 
@@ -679,9 +704,12 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             const int batch = (count > 4096 || time_first) ? 1 : 3;     // the timed round stands alone
             for (int r = 0; r < batch; ++r) {
                 timed = time_first;
-                launch_round(ctx, s, count, ring);
+                launch_round(ctx, s, count, ring, r == 0);
                 ++ring;
             }
+            hipLaunchKernelGGL(compact_kernel, dim3((count + COMPACT_THREADS - 1) / COMPACT_THREADS), dim3(COMPACT_THREADS), 0, ctx->stream,
+                               ctx->list[ring & 1], ctx->list[(ring + 1) & 1], ctx->stats, ring, ctx->path_label);
+            ++ring;
         } else if (paths_ok && (count <= search_now || (count <= ctx->path_max && (team_steps >= ctx->path_after || !teams_ok)))) {
             // few enough bidders, and chains long enough, to place each bidder by a shortest-path
             // search over the whole device
@@ -749,7 +777,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         if (rc != MF_OK) return rc;
         unread = false;                                  // (a later report on the same stream: it covers the round in flight too)
         if (timed) {
-            ctx->timings[T_BID_BULK] += mf_ms(ctx, ctx->h_stats->round_at, ctx->h_told->at);
+            ctx->timings[T_BID_BULK] += mf_ms(ctx, ctx->h_stats->round_at, ctx->h_stats->round_end);
             ctx->timings[T_BID_BULK_LAUNCHES] += 1.0f;
             ctx->timings[T_BID_BULK_BYTES] += (float)((double)(ctx->h_stats->bytes + ctx->h_stats->round_bytes - bytes_before));
         }

@@ -13,8 +13,6 @@
 
 namespace {
 
-constexpr int LIST_LINES_PER_WORKGROUP = 128;
-
 // Per row: how many pairs are feasible (rounded up to a multiple of four: lists are read 16 bytes
 // at a time); the total, and the largest weight (which sets the first epsilon).
 __global__ __launch_bounds__(256) void edge_count_kernel(const int32_t *__restrict__ W, int n, int m, int64_t ldw,
@@ -127,30 +125,28 @@ __device__ __forceinline__ void top2_push4_at(double &b1, double &b2, int &idx, 
 }
 
 // One round for many bidders, each reading its list: one wavefront per bidder.  Otherwise as
-// round_kernel (same bids, same lists of bidders to pass on, same ring of counters).
+// round_kernel (same bids, bidders to pass on in the same places, same ring of counters).
 __global__ __launch_bounds__(64) void round_lists_kernel(SideArgs s, const int *__restrict__ list,
-                                                         int *__restrict__ next, mf_device_stats *stats, int ring)
+                                                         int *__restrict__ next, mf_device_stats *stats, int ring,
+                                                         unsigned long long *__restrict__ work, int full)
 {
-    __shared__ int s_hold[LIST_LINES_PER_WORKGROUP];
     const int count = stats->cnt[ring & 3];
-    int *ncnt = &stats->cnt[(ring + 1) & 3];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        stats->cnt[(ring + 1) & 3] = count;
         stats->cnt[(ring + 2) & 3] = 0;
         stats->head = 0;
         stats->round_at = device_time();
-        if (count > 0) {
-            stats->rounds += 1ull;
-            stats->bids += (unsigned long long)count;
-        }
+        if (count > 0) stats->rounds += 1ull;
     }
-    int held = 0;
-    unsigned long long entries = 0;
     const int lane = threadIdx.x;
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
         const int b = list[item];
+        if (b < 0) {
+            if (lane == 0) next[item] = -1;
+            continue;
+        }
         const int salt = tie_salt(b);
         const long long from = s.edge_start[b], to = s.edge_start[b + 1];
-        entries += (unsigned long long)(to - from);
         Top2 t{NEG_HUGE, NEG_HUGE, 0x7fffffff, 0};
 #pragma unroll 2
         for (long long e = from + lane * 4; e < to; e += 256) {
@@ -161,21 +157,12 @@ __global__ __launch_bounds__(64) void round_lists_kernel(SideArgs s, const int *
                           fma(s.Kd, (double)w.z, -p2), fma(s.Kd, (double)w.w, -p3), c, w, salt);
         }
         t = wave_top2(t);
-        int again = -1;
         if (lane == 0) {
             t.idx ^= salt;
-            again = decide_and_bid<true>(s, b, t);
-            if (again >= 0) s_hold[held] = again;
+            next[item] = decide_and_bid<true>(s, b, t);
+            work[item] = (full ? 0ull : work[item]) + (1ull << MF_WORK_WORDS) + 2ull * (unsigned long long)(to - from);
         }
-        held += __shfl(again >= 0 ? 1 : 0, 0);
     }
-    if (held > 0) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(ncnt, held);
-        base = __shfl(base, 0);
-        for (int k = lane; k < held; k += 64) next[base + k] = s_hold[k];
-    }
-    if (lane == 0 && entries) atomicAdd(&stats->round_bytes, entries * 8ull);
 }
 
 }  // namespace
@@ -209,10 +196,9 @@ int mf_build_edge_lists(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t l
     return MF_OK;
 }
 
-void mf_launch_list_round(mf_ctx *ctx, const SideArgs &s, int count, int ring)
+void mf_launch_list_round(mf_ctx *ctx, const SideArgs &s, int count, int ring, unsigned long long *work, bool full)
 {
-    int grid = count < MAX_GRID ? count : MAX_GRID;
-    if ((long long)grid * LIST_LINES_PER_WORKGROUP < count) grid = (count + LIST_LINES_PER_WORKGROUP - 1) / LIST_LINES_PER_WORKGROUP;
+    const int grid = count < MAX_GRID ? count : MAX_GRID;
     hipLaunchKernelGGL(round_lists_kernel, dim3(grid), dim3(64), 0, ctx->stream, s, ctx->list[ring & 1],
-                       ctx->list[(ring + 1) & 1], ctx->stats, ring);
+                       ctx->list[(ring + 1) & 1], ctx->stats, ring, work, full ? 1 : 0);
 }

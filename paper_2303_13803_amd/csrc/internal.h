@@ -65,17 +65,18 @@ struct mf_device_stats {            // lives in device memory, cleared per solve
     unsigned long long path_scans;  // line scans those searches made
     unsigned long long launch_max;  // scratch: that maximum for the chain kernel in flight
     unsigned long long feasible_pairs;      // of the matrix, where the scoring pass counted them (else ~0)
-    unsigned long long round_at;    // when the last bidding round began
+    unsigned long long round_at, round_end;     // when the last bidding round began, and when it was over
     int max_weight;
     int cnt[4];                     // ring of bidder-list lengths: round r reads cnt[r & 3]
     int head;                       // next unclaimed entry of the list a chain kernel works through
     int active;                     // workgroups of the running chain kernel still following a chain
     int team_abort;                 // a bounded wait between cooperating workgroups ran out (1: chain teams, 2: path search)
     int rested;                     // bidders of the side on which rows bid that gave up with best value <= eps, this solve
-    // weight bytes the rounds with many bidders read: every workgroup of such a round adds to it as
-    // it leaves, so it sits on a cache line of its own, away from the list counters above
-    alignas(128) unsigned long long round_bytes;
+    unsigned long long round_bytes; // weight bytes the rounds with many bidders read
 };
+
+// What a place of a bidding round's list has cost: 4-byte words read, from this bit on bids (see round_kernel).
+#define MF_WORK_WORDS 40
 
 struct mf_cert_out {                // lives in device memory, cleared per check
     long long primal;
@@ -269,7 +270,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
 // edges.hip
 int mf_count_edges(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw);
 int mf_build_edge_lists(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw, SideArgs *side);
-void mf_launch_list_round(mf_ctx *ctx, const SideArgs &s, int count, int ring);
+void mf_launch_list_round(mf_ctx *ctx, const SideArgs &s, int count, int ring, unsigned long long *work, bool full);
 inline size_t mf_edge_capacity(const mf_ctx *ctx)      // entries the lists may hold: half the staged copy's words each for columns and weights
 {
     return ((size_t)ctx->max_n * ((((size_t)ctx->max_m + 3) & ~(size_t)3)) / 2) & ~(size_t)3;

@@ -175,3 +175,27 @@ def test_workgroup_shapes_of_the_bidding_rounds(mm, orc, options):
             ctx.set_option(k, val)
         _solve_and_verify(ctx, orc, W, expect)
         ctx.close()
+
+
+@pytest.mark.parametrize("n, m", [(89, 120), (120, 89), (1023, 1100), (1025, 1025), (2050, 2047), (4097, 4200)])
+def test_bidding_rounds_down_to_the_last_bidder(mm, orc, n, m):
+    """With no chains, searches or lists every bid is one of a bidding round, from all bidders down to one, with places
+    that go empty in between: each bid reads its line once, so the counts of bids and of bytes have to agree."""
+    W = synth.threshold_matrix(71, n, m, 4096, 0.7) if n < 4000 else synth.uniform_matrix(72, n, m, 2 ** 20, 0.2)
+    ctx = mm.Context(n, m)
+    for k, v in {"core": 0, "tail_max": 0, "path_max": 0, "team_max": 0, "edge_lists_from": 0, "phase_stop": 0}.items():
+        ctx.set_option(k, v)
+    Wd = padded_matrix(W)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u = torch.empty(n, dtype=torch.int64, device="cuda")
+    v = torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(Wd, n, m, r2c, u, v)
+    assert res.cert_ok == 1 and res.chain_bids == 0 and res.fallbacks == 0
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and P == res.primal
+    assert res.bids >= min(n, m) and res.rounds > 0
+    # (lines of the side that bids first are as long as the other side has lines; columns bid as well, on lines as long as that)
+    assert 4 * min(n, m) * res.bids <= res.bytes_scanned <= 4 * max(n, m) * res.bids
+    if n == m:
+        assert res.bytes_scanned == 4 * n * res.bids
+    ctx.close()
