@@ -202,7 +202,7 @@ int mf_check_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t 
  * tight serving loops, harnesses that forbid hipMalloc.  It needs no context
  * and calls no allocating routine: the partial sums and the per-column marks
  * live in an array that is part of the library's image on every device
- * (256 bytes + 4 bytes per column, 256 KiB in all, held until the process
+ * (2 KiB + 4 bytes per column, 258 KiB in all, held until the process
  * ends), so m is limited to MF_NOALLOC_MAX_COLS (MF_ERR_SHAPE beyond it, and
  * for n above 2^20 - 2); arguments are otherwise as above (MF_ERR_ARG for a
  * null pointer, a pitch that is not a multiple of 4, a d_W that is not

@@ -217,7 +217,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(dev_alloc(&ctx->list[1], nm));
     TRY(dev_alloc(&ctx->colmark, (size_t)max_m));
     TRY(dev_alloc(&ctx->stats, 1));
-    TRY(dev_alloc(&ctx->cert, 1));
+    TRY(dev_alloc(&ctx->cert, MF_CERT_PARTS));
     TRY(hipMalloc((void **)&ctx->score_range, 8 * sizeof(unsigned)));
     TRY(hipHostMalloc((void **)&ctx->h_stats, sizeof(mf_device_stats)));
     for (int i = 0; i < 2; ++i) {
@@ -229,7 +229,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(hipHostMalloc((void **)&ctx->h_times, sizeof(unsigned long long) * AT_COUNT));
     TRY(hipHostMalloc((void **)&ctx->h_told, sizeof(mf_told)));
     if (e == hipSuccess) memset(ctx->h_told, 0, sizeof(mf_told));
-    TRY(hipHostMalloc((void **)&ctx->h_cert, sizeof(mf_cert_out)));
+    TRY(hipHostMalloc((void **)&ctx->h_cert, sizeof(mf_cert_out) * MF_CERT_PARTS));
     for (int i = 0; i < 2; ++i) TRY(hipEventCreate(&ctx->ev[i]));
 #undef TRY
     if (e != hipSuccess) {

@@ -45,27 +45,33 @@ __global__ __launch_bounds__(NT) void duals_kernel(
 // (min reduced cost), primal and dual totals.
 // K32: K fits a signed 32-bit integer, so K*w is one 32 x 32 -> 64-bit multiply-add.
 // A workgroup takes CERT_ROWS rows at a time: each column dual (8 bytes, against 4 for a weight)
-// is loaded once for all of them.  The grid is capped at what the chip holds at once (8 workgroups
-// on each of 256 compute units) and every workgroup walks over its share of the rows: measured on
-// a 20,000 x 20,000 matrix the scan then runs at 0.70-0.73 of the HBM peak, against 0.60 with one
-// workgroup per group of rows.
+// is loaded once for all of them.  What bounds it is reading the matrix.  The grid is capped, and every workgroup walks over its share
+// of the pieces, a piece being some of the columns of a group of rows: as many as it takes for the shares to be equal
+// (cert_pieces), and for small matrices to fill the device.  Before, a workgroup took whole rows, 2048 of them one or two
+// groups of a 20,000-row matrix each, and all added up in one place (four atomics each, 10 ns one after the other):
+// the whole check of 20,000 x 40,000 553 -> 526 us (6.2 TB/s, as a plain read), 20,000 x 20,000 290 -> 274, 12,345 x 30,001 286 -> 255,
+// 4096 x 8192 52 -> 31, 2003 x 3001 23 -> 16.  Grids of 2048 and 8192 536 and 543 us; 4, 6 and 12 rows at a time 606, 553, 539; four
+// wavefronts a SIMD (97 registers) 533.
 constexpr int CERT_ROWS = 8;
-constexpr int CERT_GRID = 2048;
+constexpr int CERT_GRID = 4096;
 
 template <bool K32>
-__global__ __launch_bounds__(BID_THREADS) void certificate_kernel(
+__global__ __launch_bounds__(BID_THREADS, 5) void certificate_kernel(
     const int32_t *__restrict__ W, int64_t ldw, int n, int m, const int32_t *__restrict__ row2col,
     const int64_t *__restrict__ u, const int64_t *__restrict__ v, long long K, int *colmark,
-    mf_cert_out *out, unsigned long long *times)
+    mf_cert_out *out, unsigned long long *times, int pieces, int piece_cols)
 {
     note_time(times, AT_CERT);
-    __shared__ long long red[BID_THREADS / 64];
+    __shared__ long long red[3][BID_THREADS / 64];
+    __shared__ int red_matched[BID_THREADS / 64], red_flags[BID_THREADS / 64];
     constexpr int UN = 1;               // column groups of four in flight per thread
     long long dual_part = 0, primal_part = 0;
     int flags = 0, matched = 0;
     long long min_rc = INT64_MAX;
     const int k32 = (int)K;
-    for (int i0 = blockIdx.x * CERT_ROWS; i0 < n; i0 += gridDim.x * CERT_ROWS) {
+    const int groups = (n + CERT_ROWS - 1) / CERT_ROWS;
+    for (int item = blockIdx.x; item < groups * pieces; item += gridDim.x) {
+        const int i0 = item / pieces * CERT_ROWS, from = item % pieces * piece_cols, to = min(from + piece_cols, m);
         long long ui[CERT_ROWS];
         const int32_t *rows[CERT_ROWS];
 #pragma unroll
@@ -74,7 +80,7 @@ __global__ __launch_bounds__(BID_THREADS) void certificate_kernel(
             ui[r] = u[i];
             rows[r] = W + (size_t)i * ldw;
         }
-        for (int j0 = threadIdx.x * 4; j0 < m; j0 += BID_THREADS * 4 * UN) {
+        for (int j0 = from + threadIdx.x * 4; j0 < to; j0 += BID_THREADS * 4 * UN) {
             // every load is issued before any comparison: the column duals whatever the weights
             // turn out to be (index clamped into the array), the weights of all the rows
             long long vj[UN][4];
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(BID_THREADS) void certificate_kernel(
                 }
             }
         }
-        if (threadIdx.x < CERT_ROWS && i0 + (int)threadIdx.x < n) {          // one thread per row of the group
+        if (from == 0 && threadIdx.x < CERT_ROWS && i0 + (int)threadIdx.x < n) {         // one thread per row of the group
             const int i = i0 + threadIdx.x;
             const long long mine = u[i];
             if (mine < 0) flags |= 4;
@@ -137,17 +143,35 @@ __global__ __launch_bounds__(BID_THREADS) void certificate_kernel(
         flags |= __shfl_xor(flags, off);
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) red[wave] = min_rc;
+    if (lane == 0) { red[0][wave] = min_rc; red[1][wave] = dual_part; red[2][wave] = primal_part; red_matched[wave] = matched; red_flags[wave] = flags; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int wv = 1; wv < BID_THREADS / 64; ++wv) min_rc = red[wv] < min_rc ? red[wv] : min_rc;
-        atomicMin(&out->min_rc, min_rc);
-        if (primal_part) atomicAdd((unsigned long long *)&out->primal, (unsigned long long)primal_part);
-        if (matched) atomicAdd(&out->matched, matched);
+        for (int wv = 1; wv < BID_THREADS / 64; ++wv) {
+            min_rc = red[0][wv] < min_rc ? red[0][wv] : min_rc;
+            dual_part += red[1][wv]; primal_part += red[2][wv]; matched += red_matched[wv]; flags |= red_flags[wv];
+        }
+        mf_cert_out *mine = out + blockIdx.x % MF_CERT_PARTS;
+        atomicMin(&mine->min_rc, min_rc);
+        if (primal_part) atomicAdd((unsigned long long *)&mine->primal, (unsigned long long)primal_part);
+        if (matched) atomicAdd(&mine->matched, matched);
+        if (dual_part) atomicAdd((unsigned long long *)&mine->dual, (unsigned long long)dual_part);
+        if (flags) atomicOr(&mine->flags, flags);
     }
-    if (lane == 0) {
-        if (dual_part) atomicAdd((unsigned long long *)&out->dual, (unsigned long long)dual_part);
-        if (flags) atomicOr(&out->flags, flags);
+}
+
+// Columns of a piece and how many there are of a group of rows: the fewest that give the workgroups equal shares
+// within 5 percent (20,000 rows are 2500 groups for 2048 workgroups: one or two each), or one for each step of a workgroup.
+struct CertPieces { int pieces, cols, grid; };
+CertPieces cert_pieces(int n, int m)
+{
+    constexpr int STEP = BID_THREADS * 4;
+    const long long groups = (n + CERT_ROWS - 1) / CERT_ROWS;
+    const int steps = (m + STEP - 1) / STEP;
+    for (int want = 1;; ++want) {
+        const int each = (steps + want - 1) / want, pieces = (steps + each - 1) / each;
+        const long long items = groups * pieces, share = (items + CERT_GRID - 1) / CERT_GRID;
+        if (want >= steps || (items >= CERT_GRID && share * CERT_GRID * 20 <= items * 21))
+            return CertPieces{pieces, each * STEP, (int)(items < CERT_GRID ? items : CERT_GRID)};
     }
 }
 
@@ -185,7 +209,7 @@ __global__ void cert_begin_kernel(mf_cert_out *out, int *colmark, int m, unsigne
     note_time(times, AT_CERT);
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j < m) colmark[j] = 0;
-    if (j == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
+    if (j < MF_CERT_PARTS) mf_clear_part(out + j);
 }
 
 }  // namespace
@@ -195,19 +219,19 @@ int mf_run_certificate(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ld
                        int64_t K, mf_result *h_res, bool begun)
 {
     if (!begun) hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, ctx->stream, ctx->cert, ctx->colmark, m, ctx->times);
-    const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
+    const CertPieces p = cert_pieces(n, m);
     hipLaunchKernelGGL(K >= INT32_MIN && K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>,
-                       dim3(grid), dim3(BID_THREADS), 0, ctx->stream, d_W, ldw, n, m,
-                       d_row2col, d_u, d_v, (long long)K, ctx->colmark, ctx->cert, begun ? ctx->times : nullptr);
+                       dim3(p.grid), dim3(BID_THREADS), 0, ctx->stream, d_W, ldw, n, m,
+                       d_row2col, d_u, d_v, (long long)K, ctx->colmark, ctx->cert, begun ? ctx->times : nullptr, p.pieces, p.cols);
     MF_HIP(hipGetLastError());
     // the last wait of a call: what else the host wants to know comes along with it
-    const int rc = mf_send_and_await(ctx, mf_report{{{ctx->cert, ctx->h_cert, (int)(sizeof(mf_cert_out) / 4)},
+    const int rc = mf_send_and_await(ctx, mf_report{{{ctx->cert, ctx->h_cert, (int)(sizeof(mf_cert_out) / 4) * MF_CERT_PARTS},
                                                      {ctx->times, ctx->h_times, 2 * AT_COUNT},
                                                      {ctx->pairs_evaluated, ctx->h_pairs_evaluated, 2},
                                                      {ctx->stats, ctx->h_stats, (int)(sizeof(mf_device_stats) / 4)}}});
     if (rc != MF_OK) return rc;
     ctx->timings[T_CERT] = mf_ms(ctx, ctx->h_times[AT_CERT], ctx->h_told->at);
-    const mf_cert_out &c = *ctx->h_cert;
+    const mf_cert_out c = mf_sum_parts(ctx->h_cert);
     h_res->primal = c.primal;
     h_res->dual = c.dual;
     h_res->K = K;
@@ -252,15 +276,16 @@ namespace {
 // use marks) lives here in one array that is part of the library's image on every device.
 // In host code the array's name is only a handle: what kernels, copies and fills get is the
 // device address looked up once per device.
-constexpr int NOALLOC_HEADER_BYTES = 256;           // an mf_cert_out, padded
+constexpr int NOALLOC_HEADER_BYTES = sizeof(mf_cert_out) * MF_CERT_PARTS;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_HEADER_BYTES + 4 * MF_NOALLOC_MAX_COLS];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
 std::mutex noalloc_lock;
 unsigned char *noalloc_ptr[NOALLOC_MAX_DEVICES];    // scratch's address on each device (null: not looked up yet)
 
-__global__ void noalloc_finish_kernel(const mf_cert_out *in, long long K, mf_certificate *d_out)
+__global__ void noalloc_finish_kernel(const mf_cert_out *parts, long long K, mf_certificate *d_out)
 {
+    const mf_cert_out sum = mf_sum_parts(parts), *in = &sum;
     const long long min_rc = in->min_rc == INT64_MAX ? 0 : in->min_rc;
     const long long gap = in->dual - K * in->primal;
     d_out->primal = in->primal;
@@ -301,9 +326,9 @@ extern "C" int mf_check_certificate_noalloc(void *hip_stream, const int32_t *d_W
     // the array keeps what the previous call left: both parts are cleared by a kernel (no
     // memset node, so the sequence can be captured into a graph)
     hipLaunchKernelGGL(cert_begin_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, out, colmark, m, (unsigned long long *)nullptr);
-    const int groups = (n + CERT_ROWS - 1) / CERT_ROWS, grid = groups < CERT_GRID ? groups : CERT_GRID;
-    hipLaunchKernelGGL(K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>, dim3(grid),
-                       dim3(BID_THREADS), 0, stream, d_W, ldw, n, m, d_row2col, d_u, d_v, (long long)K, colmark, out, (unsigned long long *)nullptr);
+    const CertPieces p = cert_pieces(n, m);
+    hipLaunchKernelGGL(K <= INT32_MAX ? certificate_kernel<true> : certificate_kernel<false>, dim3(p.grid),
+                       dim3(BID_THREADS), 0, stream, d_W, ldw, n, m, d_row2col, d_u, d_v, (long long)K, colmark, out, (unsigned long long *)nullptr, p.pieces, p.cols);
     hipLaunchKernelGGL(noalloc_finish_kernel, dim3(1), dim3(1), 0, stream, out, (long long)K, d_out);
     return hipGetLastError() == hipSuccess ? MF_OK : MF_ERR_HIP;
 }

@@ -78,14 +78,28 @@ struct mf_device_stats {            // lives in device memory, cleared per solve
 // What a place of a bidding round's list has cost: 4-byte words read, from this bit on bids (see round_kernel).
 #define MF_WORK_WORDS 40
 
-struct mf_cert_out {                // lives in device memory, cleared per check
+struct alignas(128) mf_cert_out {   // lives in device memory, cleared per check
     long long primal;
     long long dual;
     long long min_rc;
     int matched;
     int flags;                      // bit0 bad index/duplicate, bit1 infeasible pair, bit2 negative dual
-    int bids, scans, status;        // of a matching by small_kernel, which begins the check in the same launch
+    int bids, scans, status;        // of a matching by small_kernel, which begins the check in the same launch (in the first part)
 };
+
+// A check adds up in so many parts: workgroups that finish together would queue up behind atomics on one line.
+constexpr int MF_CERT_PARTS = 16;
+// (one thread clears a part)
+__host__ __device__ inline void mf_clear_part(mf_cert_out *o) { o->primal = 0; o->dual = 0; o->min_rc = INT64_MAX; o->matched = 0; o->flags = 0; }
+__host__ __device__ inline mf_cert_out mf_sum_parts(const mf_cert_out *o)
+{
+    mf_cert_out s = o[0];
+    for (int p = 1; p < MF_CERT_PARTS; ++p) {
+        s.primal += o[p].primal; s.dual += o[p].dual; s.matched += o[p].matched; s.flags |= o[p].flags;
+        s.min_rc = o[p].min_rc < s.min_rc ? o[p].min_rc : s.min_rc;
+    }
+    return s;
+}
 
 // What mf_set_option sets, with the defaults.
 struct mf_options {

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
             profit[i * s.pitch] = 0;
         }
         for (int j = threadIdx.x; j < s.m; j += SMALL_THREADS) price_out[j] = 0;
-        if (threadIdx.x == 0) { out->primal = 0; out->dual = 0; out->min_rc = INT64_MAX; out->matched = 0; out->flags = 0; }
+        if (threadIdx.x < MF_CERT_PARTS) mf_clear_part(out + threadIdx.x);
     }
     __syncthreads();
     const bool general = largest >= SMALL_WEIGHTS || K * (long long)largest >= MF_MAX_DUAL;

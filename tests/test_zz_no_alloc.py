@@ -72,3 +72,39 @@ def test_sizes_beyond_the_static_array_are_refused():
     torch.cuda.synchronize()
     got = binding.read_certificate(out)
     assert got.cert_ok == 1 and got.primal == 0 and got.dual == 0 and got.matched == 0
+
+
+@pytest.mark.parametrize("n, m", [(1, 1), (7, 1023), (8, 1024), (9, 1025), (257, 2049), (8193, 1030), (33000, 40), (2500, 5003)])
+def test_every_pair_is_looked_at_once(n, m):
+    """Sizes at the edges of a workgroup's rows and columns and of its share of the matrix: the least reduced cost, wherever it
+    is, and the sums are those of the definition."""
+    import ctypes
+    import paper_2303_13803_amd as mm
+    from paper_2303_13803_amd import binding
+    rng = np.random.default_rng(n * 10007 + m)
+    ctx = mm.Context(n, m)
+    out = torch.empty(ctypes.sizeof(binding.Certificate), dtype=torch.uint8, device="cuda")
+    K = min(n, m) + 1
+    a, b = rng.integers(1000, 2000, n), rng.integers(1000, 2000, m)
+    W = (a[:, None] + b[None, :] - rng.integers(1, 900, (n, m))).astype(np.int32)
+    W[rng.random((n, m)) < 0.2] = mm.INFEASIBLE
+    k = min(n, m)
+    r2c = np.full(n, -1, dtype=np.int32)
+    r2c[rng.permutation(n)[:k]] = rng.permutation(m)[:k]
+    rows = np.flatnonzero(r2c >= 0)
+    W[rows, r2c[rows]] = (a[rows] + b[r2c[rows]] - 1).astype(np.int32)
+    u, v = a.astype(np.int64) * K, b.astype(np.int64) * K
+    step = 1024
+    for i, j in {(0, 0), (n - 1, m - 1), (n - 1, 0), (0, m - 1), (n // 2, min(m - 1, step)), (n // 2, max(0, m // step * step - 1))}:
+        for lift in (0, 5000):                              # as it is, and with this pair not covered
+            V = W.copy()
+            if lift:
+                V[i, j] = a[i] + b[j] + lift
+            cost = np.where(V == mm.INFEASIBLE, np.iinfo(np.int64).max, u[:, None] + v[None, :] - K * V.astype(np.int64))
+            Wd = padded_matrix(V)
+            args = [torch.from_numpy(x).cuda() for x in (r2c, u, v)]
+            ref, got = _both(mm, binding, ctx, Wd, n, m, *args, K, out)
+            assert ref.min_reduced_cost == cost.min()
+            assert ref.dual == int(u.sum() + v.sum()) and ref.matched == k
+            assert ref.primal == int(V[rows, r2c[rows]].astype(np.int64).sum())
+    ctx.close()
