@@ -25,6 +25,7 @@
 #include "scan.h"
 #include "report.h"
 #include "half_list.h"
+#include "list_cut.h"
 #include "search_words.h"
 #include "team_join.h"
 #include "team_steps.h"
@@ -69,12 +70,17 @@ constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose lis
 // Entries tied with the cut fill the list up, whichever come first from a place that differs from group to group
 // of lines (tied bidders would otherwise all hold the same few of many tied entries).
 // A wavefront per line finds cut and list by bisection: counts come from ballots, no barrier in between.
+//
+// In the pass nearly every wavefront has a few entries to keep in every step, and looking at sixteen entries a lane exactly, and
+// keeping each behind a branch and an atomic of its own, took 1.5 us a step where the loads take half of that.  So floats decide which
+// entries are looked at exactly, a lane goes through its own few one after the other, and the next step's loads are on
+// their way meanwhile (one step a time: unrolled, the registers leave a wavefront less a SIMD).
 // (Lists of 20,000 lines of 20,000 entries: 926 us when a workgroup of 1024 threads kept a whole line in
-// registers and found the cut by histograms, a dozen barriers a line; 380 us now, 4.2 TB/s.  4096 lines of 8192:
-// 81 -> 46 us; 20,000 x 40,000 with prefixes of a tenth, rows 552 -> 150 us, columns 380 -> 141 us.  One line a workgroup up
-// to four a compute unit: 256 lines of 20,000 take 60 us by fours, 29 us so.)
-constexpr int LIST_THREADS = 256, LIST_CAP = 512, LIST_AIM = 300, LIST_SAMPLE_GROUPS = 512;
-constexpr double LIST_ALL = -1.0e300, LIST_NONE = 1.0e300;      // cuts
+// registers and found the cut by histograms, a dozen barriers a line; 400 us with every entry looked at exactly; 346 us now, 4.6 TB/s.  6500,
+// 2500 and 1200 of them 155 -> 132, 78 -> 61 and 68 -> 42 us; 4096 lines of 8192 52 -> 45, 2003 of 3001 26 -> 24.
+// One line a workgroup up to four a compute unit, two up to eight: 256 lines of 20,000 take 60 us by fours, 24 us so;
+// 1200 46 by fours, 41 by twos; 4096 of 8192 entries 45 by fours, 54 by twos.)
+constexpr int LIST_THREADS = 256, LIST_CAP = 512, LIST_AIM = 240, LIST_SAMPLE_GROUPS = 512;
 
 // Of the integers in v (PER a lane; `low`: unused), a cut with at most `most` of them above it, and at
 // least `least` unless ties forbid it.  All lanes return the same.
@@ -97,11 +103,11 @@ __device__ __forceinline__ double cut_above(const double (&v)[PER], int least, i
 }
 
 template <int LINES>                                    // lines a workgroup makes lists of, at most one a wavefront
-__global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
+__global__ __launch_bounds__(LIST_THREADS, 5) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
     const int *__restrict__ which, const double *__restrict__ dual, double Kd, int2 *__restrict__ entries,
     double *__restrict__ bound, double *__restrict__ half_bound, double *depth, const double *__restrict__ own_dual,
-    const int *__restrict__ partner, double *__restrict__ built, int some)
+    const int *__restrict__ partner, double *__restrict__ built, int some, double most)
 {
     // The duals the side's lists were made for; where some lines' lists are newer than others', the larger ones (a
     // bound holds as long as no dual is lower than when the list was made).  (A launch of its own took 5 us and its gap.)
@@ -116,7 +122,7 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     static_assert(LINES <= LIST_THREADS / 64, "a wavefront per line chooses");
     __shared__ double s_value[LINES][LIST_CAP];
     __shared__ int2 s_entry[LINES][LIST_CAP], s_tie[LINES][CORE_LIST];
-    __shared__ int s_count[LINES], s_ties[LINES], s_again[LINES];
+    __shared__ int s_count[LINES], s_ties[LINES], s_again[LINES], s_to[LINES];
     __shared__ double s_cut[LINES];
     static_assert(LIST_CAP >= LIST_THREADS, "a sample's largest values, one a thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -184,41 +190,59 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
             cut = feasible <= want ? LIST_ALL : cut_above(v, want - want / 16, want, LIST_ALL);
         }
         __syncthreads();
-        if (choosing && lane == 0) { s_cut[wave] = cut; s_count[wave] = 0; s_ties[wave] = 0; }
+        if (choosing && lane == 0) { s_cut[wave] = cut; s_count[wave] = 0; s_ties[wave] = 0; s_to[wave] = mine; }
         __syncthreads();
     }
     // ---- every line, once ----
-    double cut[LINES];
+    // (floats tell what has to be looked at exactly: list_cut.h)
+    float cut_f[LINES];
 #pragma unroll
-    for (int r = 0; r < LINES; ++r) cut[r] = s_cut[r];
+    for (int r = 0; r < LINES; ++r) cut_f[r] = cut_in_floats(s_cut[r], most);
+    const float kf = (float)Kd;                                         // (exact: K is at most 2^20)
     for (int attempt = 0;; ++attempt) {
-        auto keep = [&](int r, int j, int32_t w, double v) {
-            if (j >= to[r] || w == MF_INFEASIBLE) return;
-            if (v > cut[r]) {
-                const int at = atomicAdd(&s_count[r], 1);
-                if (at < LIST_CAP) { s_value[r][at] = v; s_entry[r][at] = make_int2(j, w); }
-            } else if (s_ties[r] < CORE_LIST) {
-                const int at = atomicAdd(&s_ties[r], 1);
-                if (at < CORE_LIST) s_tie[r][at] = make_int2(j, w);
-            }
-        };
-#pragma unroll 2
-        for (int g0 = tid; g0 < groups; g0 += LIST_THREADS) {
+        // (the next groups are on their way while these are looked at: the compiler moves no load past a branch that may keep an entry)
+        int4 w[LINES], w_next[LINES];
+        double2 p01, p23, p01_next, p23_next;
+        auto fetch = [&](int g0, int4 (&w)[LINES], double2 &p01, double2 &p23) {
             const int g = g0 + turn >= groups ? g0 + turn - groups : g0 + turn, j = g * 4;
-            int4 w[LINES];
 #pragma unroll
             for (int r = 0; r < LINES; ++r) w[r] = *(const int4 *)(line[r] + j);      // (lines are padded to a multiple of four)
-            const double2 p01 = *(const double2 *)(dual + j);
-            const double2 p23 = *(const double2 *)(dual + j + 2);
+            p01 = *(const double2 *)(dual + j);
+            p23 = *(const double2 *)(dual + j + 2);
+        };
+        if (tid < groups) fetch(tid, w_next, p01_next, p23_next);
+#pragma unroll 1
+        for (int g0 = tid; g0 < groups; g0 += LIST_THREADS) {
+            const int g = g0 + turn >= groups ? g0 + turn - groups : g0 + turn, j = g * 4;
+#pragma unroll
+            for (int r = 0; r < LINES; ++r) w[r] = w_next[r];
+            p01 = p01_next; p23 = p23_next;
+            if (g0 + LIST_THREADS < groups) fetch(g0 + LIST_THREADS, w_next, p01_next, p23_next);
+            // Floats tell what may be above the cut, or at it; only that is looked at exactly.
+            const float p[4] = {(float)p01.x, (float)p01.y, (float)p23.x, (float)p23.y};
+            unsigned hits = 0u;
 #pragma unroll
             for (int r = 0; r < LINES; ++r) {
-                const double v[4] = {fma(Kd, (double)w[r].x, -p01.x), fma(Kd, (double)w[r].y, -p01.y),
-                                     fma(Kd, (double)w[r].z, -p23.x), fma(Kd, (double)w[r].w, -p23.y)};
-                if (fmax(fmax(v[0], v[1]), fmax(v[2], v[3])) >= cut[r]) {
-                    if (v[0] >= cut[r]) keep(r, j, w[r].x, v[0]);
-                    if (v[1] >= cut[r]) keep(r, j + 1, w[r].y, v[1]);
-                    if (v[2] >= cut[r]) keep(r, j + 2, w[r].z, v[2]);
-                    if (v[3] >= cut[r]) keep(r, j + 3, w[r].w, v[3]);
+                const int32_t we[4] = {w[r].x, w[r].y, w[r].z, w[r].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hits |= may_reach(kf, we[e], p[e], cut_f[r]) ? 1u << (4 * r + e) : 0u;
+            }
+            while (hits) {
+                const int bit = __ffs((int)hits) - 1, r = bit >> 2, e = bit & 3;
+                hits &= hits - 1u;
+                int4 of = w[0];
+#pragma unroll
+                for (int q = 1; q < LINES; ++q)
+                    if (r == q) of = w[q];
+                const int32_t we = e == 0 ? of.x : e == 1 ? of.y : e == 2 ? of.z : of.w;
+                const double v = fma(Kd, (double)we, -(e == 0 ? p01.x : e == 1 ? p01.y : e == 2 ? p23.x : p23.y)), line_cut = s_cut[r];
+                if (we == MF_INFEASIBLE || j + e >= s_to[r] || v < line_cut) continue;
+                if (v > line_cut) {
+                    const int at = atomicAdd(&s_count[r], 1);
+                    if (at < LIST_CAP) { s_value[r][at] = v; s_entry[r][at] = make_int2(j + e, we); }
+                } else if (s_ties[r] < CORE_LIST) {
+                    const int at = atomicAdd(&s_ties[r], 1);
+                    if (at < CORE_LIST) s_tie[r][at] = make_int2(j + e, we);
                 }
             }
         }
@@ -243,7 +267,7 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
         __syncthreads();
         if (!any) break;
 #pragma unroll
-        for (int r = 0; r < LINES; ++r) cut[r] = s_again[r] ? s_cut[r] : LIST_NONE;
+        for (int r = 0; r < LINES; ++r) cut_f[r] = cut_in_floats(s_again[r] ? s_cut[r] : LIST_NONE, most);
     }
     // ---- a wavefront per line ----
     const int number = blockIdx.x * LINES + wave;
@@ -1869,8 +1893,9 @@ void launch_lists(mf_ctx *ctx, const SideArgs &s, int made, int stride, const in
 {
 #define MF_LIST(LINES)                                                                                                                     \
     hipLaunchKernelGGL((core_list_kernel<LINES>), dim3((made + LINES - 1) / LINES), dim3(LIST_THREADS), 0, ctx->stream, s.A, s.pitch, s.len, \
-                       s.line_len, made, stride, list, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner, built, list ? 1 : 0)
-    if (made > 4 * ctx->n_cus) MF_LIST(4);
+                       s.line_len, made, stride, list, s.other_dual, s.Kd, ctx->core_entries[which], ctx->core_bound[which], ctx->core_half_bound[which], depth, own_dual, partner, built, list ? 1 : 0, \
+                       s.Kd * (double)ctx->h_stats->max_weight)
+    if (made > 8 * ctx->n_cus) MF_LIST(4); else if (made > 4 * ctx->n_cus) MF_LIST(2);
     else MF_LIST(1);
 #undef MF_LIST
 }
