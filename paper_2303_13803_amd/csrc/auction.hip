@@ -616,7 +616,10 @@ void launch_round(mf_ctx *ctx, const SideArgs &s, int count, int ring, bool full
     // Lines in groups per wavefront read the matrix fastest, and that is what counts when (nearly)
     // every line bids: the first round of a phase.  In the rounds after it, one line per workgroup
     // does better although it reads more slowly: bids land sooner, later bidders of the same round
-    // see them, and fewer bids are wasted (measured on cluster-scale rounds: a fifth fewer bids).
+    // see them, and fewer bids are wasted (measured on cluster-scale rounds: a fifth fewer bids).  Two lines
+    // a group, not four, for the same reason, since rounds hand bidders over without atomics, which the more workgroups the
+    // longer queued up: six seeds of 20,000 x 20,000 rounds 40.5 / 39.9 ms, of the rounds after them 17.9 / 17.3, one pair in two of
+    // 15,000 x 15,000 15.1 / 11.2, 4096 x 8192 6.69 / 6.59 (one line and 256 threads there, too: 39.4, 17.4, 13.3, 6.53).
     // Feasible prefixes differ in length from nothing to the whole line, and one wavefront on the four longest
     // is what a grouped round then waits for (20,000 x 40,000, a tenth feasible: 207 us, 130 to 174 one by one).
     const bool grouped = !s.line_len && count >= 2048 && (long long)count * 100 >= (long long)ctx->bulk_share * (long long)s.len_t;

@@ -121,7 +121,7 @@ struct mf_options {
     long long final_jump = 0;                   // epsilon (weight units) at or below which the next phase is the last (0: never)
     int tail_max = 1024;                        // bidder count at or below which chains are followed in one kernel
     int bulk_grid = 0;                          // most workgroups of a round with many bidders (0: one per group of lines, up to 8192)
-    int bulk_shape = 1;                         // workgroup shape of rounds with many bidders (see launch_round)
+    int bulk_shape = 2;                         // workgroup shape of rounds with many bidders (see launch_round)
     int bulk_share = 95;                        // ... "many": at least 2048 and this share (percent) of the side's lines
     int team_max = 8;                           // chains at or below which several workgroups share each chain (0: never)
     int team_size = 16, team_threads = 1024;    // most workgroups per chain, threads per such workgroup

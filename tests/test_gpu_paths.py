@@ -157,7 +157,7 @@ def test_phases_that_end_early_leave_the_optimum_alone(mm, orc, options):
 _BULK = {}
 
 
-@pytest.mark.parametrize("options", [{}, {"bulk_shape": 0}, {"bulk_shape": 2, "bulk_share": 0},
+@pytest.mark.parametrize("options", [{}, {"bulk_shape": 0}, {"bulk_shape": 1}, {"bulk_shape": 2, "bulk_share": 0},
                                      {"bulk_shape": 3, "bulk_share": 50}, {"bulk_shape": 4, "bulk_grid": 64},
                                      {"bulk_share": 100, "round_lag": 0}, {"bulk_share": 0, "bulk_grid": 8192}])
 def test_workgroup_shapes_of_the_bidding_rounds(mm, orc, options):
