@@ -618,6 +618,14 @@ struct Core {
         }
     }
 
+    // Wavefronts that read a line together, each every so many-th slice of it: one, unless there are fewer lines than
+    // wavefronts.  (A wavefront for every slice that the longest line might have looked 40 times at each of 27,000 feasible prefixes
+    // of 4000 entries, 1.6 us each time: 6.7 ms of a 20,000 x 40,000 round.)
+    __device__ __forceinline__ int parts_of_line(const CoreSide &s, int lines) const
+    {
+        return max(1, min((s.len + CORE_SLICE - 1) / CORE_SLICE, gwaves() / lines));
+    }
+
     // The best half of a line's list, a lane an entry, and what nothing else is worth more than.
     struct Half { int2 e; double bound; };
     __device__ __forceinline__ Half half_of(const CoreSide &s, int b) const
@@ -1399,9 +1407,9 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
             // whole lines, in slices: a wavefront each.  What bounds it is latency: four entries' prices are in
             // flight per lane, and a label is looked at only where it may be lowered (one entry at a
             // time took 24 us a slice, 36 ms where 37,000 lines of 20,000 had to be read).
-            const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
-            for (int it = gwave(); it < nw * slices; it += gwaves()) {
-                const int e = it / slices, from = (it - e * slices) * CORE_SLICE;
+            const int parts = nw > 0 ? parts_of_line(s, nw) : 1;
+            for (int it = gwave(); it < nw * parts; it += gwaves()) {
+                const int e = it / parts, part = it - e * parts;
                 const int entry = load_fresh_i32(&whole_list[e]);
                 int i;
                 double base;
@@ -1415,32 +1423,35 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                     base = (double)(long long)(lw >> MF_ID_BITS) + fma(a.Kd, (double)load_fresh_i32(&a.held_weight[entry]), -word_dual(word)) + eps;
                     if (lw == CORE_INF || i < 0) continue;          // (cannot be)
                 }
-                const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
+                const int length = s.line_len ? min(s.line_len[i], s.len) : s.len;
                 const int32_t *line = s.A + (size_t)i * s.pitch;
-                int4 ahead[CORE_SLICE / 256];
-                load_slice(line, from, to, ahead);
                 const double unlisted = base - (s.bound[i] + slack);
                 double left_out = CORE_FAR;                         // the nearest unlisted one beyond the nearest path end
+                for (int from = part * CORE_SLICE; from < length; from += parts * CORE_SLICE) {
+                    const int to = min(length, from + CORE_SLICE);
+                    int4 ahead[CORE_SLICE / 256];
+                    load_slice(line, from, to, ahead);
 #pragma unroll
-                for (int q = 0; q < CORE_SLICE / 256; ++q) {
-                    const int j = from + q * 256 + lane * 4;
-                    if (j >= to) break;
-                    const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
-                    unsigned long long word[4];
+                    for (int q = 0; q < CORE_SLICE / 256; ++q) {
+                        const int j = from + q * 256 + lane * 4;
+                        if (j >= to) break;
+                        const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
+                        unsigned long long word[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
+                        for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
 #pragma unroll 1
-                    for (int e = 0; e < 4; ++e) {
-                        if (j + e >= to || w[e] == MF_INFEASIBLE) continue;
-                        const double x = base - fma(a.Kd, (double)w[e], -word_dual(word[e]));
-                        if (x < bound) relax(i, x, j + e, word[e]);
-                        else if (x >= unlisted) left_out = fmin(left_out, x);
+                        for (int e = 0; e < 4; ++e) {
+                            if (j + e >= to || w[e] == MF_INFEASIBLE) continue;
+                            const double x = base - fma(a.Kd, (double)w[e], -word_dual(word[e]));
+                            if (x < bound) relax(i, x, j + e, word[e]);
+                            else if (x >= unlisted) left_out = fmin(left_out, x);
+                        }
                     }
+                    whole += (unsigned)(to - from + 3) / 4u;
                 }
                 left_out = -wave_max(-left_out);
                 if (lane == 0 && left_out < CORE_FAR)
                     publish_slice(SharedWords{}, WholeLine{nullptr, entry < 0 ? (double *)&ctl->src_left[-1 - entry] : &a.left[entry]}, left_out);
-                whole += (unsigned)max(to - from + 3, 0) / 4u;
             }
             from_bidders = false;
         } else {
@@ -1620,34 +1631,37 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
         taken = end;
         first = wave; stride = CORE_WAVES;
         }
-        const int slices = (s.len + CORE_SLICE - 1) / CORE_SLICE;
-        for (int it = gwave(); it < whole_rows * slices; it += gwaves()) {
-            const int i = load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[it / slices]), from = it % slices * CORE_SLICE;
+        const int parts = whole_rows > 0 ? parts_of_line(s, whole_rows) : 1;
+        for (int it = gwave(); it < whole_rows * parts; it += gwaves()) {
+            const int i = load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[it / parts]);
             const int col = load_fresh_i32(&a.row2col[i]);
             const double profit = col >= 0 ? fma(a.Kd, (double)load_fresh_i32(&a.held_weight[i]), -word_dual(load_fresh_u64(&s.otherword[max(col, 0)]))) : 0.0;
-            const int to = min(s.line_len ? min(s.line_len[i], s.len) : s.len, from + CORE_SLICE);
+            const int length = s.line_len ? min(s.line_len[i], s.len) : s.len;
             const int32_t *line = s.A + (size_t)i * s.pitch;
-            int4 ahead[CORE_SLICE / 256];
-            load_slice(line, from, to, ahead);
+            for (int from = it % parts * CORE_SLICE; from < length; from += parts * CORE_SLICE) {
+                const int to = min(length, from + CORE_SLICE);
+                int4 ahead[CORE_SLICE / 256];
+                load_slice(line, from, to, ahead);
 #pragma unroll
-            for (int q = 0; q < CORE_SLICE / 256; ++q) {
-                const int j = from + q * 256 + lane * 4;
-                if (j >= to) break;
-                const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
-                unsigned long long word[4];
+                for (int q = 0; q < CORE_SLICE / 256; ++q) {
+                    const int j = from + q * 256 + lane * 4;
+                    if (j >= to) break;
+                    const int32_t w[4] = {ahead[q].x, ahead[q].y, ahead[q].z, ahead[q].w};
+                    unsigned long long word[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
-                for (int e = 0; e < 4; ++e) {
-                    const double need = fma(a.Kd, (double)w[e], -profit);
-                    if (j + e >= to || w[e] == MF_INFEASIBLE || !(word_dual(word[e]) < need)) continue;
-                    if (word_id(word[e]) < 0) { atomicOr(&sh.failed, 1u); break; }
-                    const unsigned long long mine = pack_word(need, (int)(word[e] & MF_ID_MASK));
-                    if (!(atomicMax(&s.otherword[j + e], mine) < mine)) continue;
-                    if (few) { if (!keep(word_id(word[e]))) atomicOr(&sh.failed, 1u); }
-                    else if (atomicExch(&a.stamp[j + e], round) != round) push(word_id(word[e]), next, counter);
+                    for (int e = 0; e < 4; ++e) word[e] = load_fresh_u64(&s.otherword[min(j + e, to - 1)]);
+                    for (int e = 0; e < 4; ++e) {
+                        const double need = fma(a.Kd, (double)w[e], -profit);
+                        if (j + e >= to || w[e] == MF_INFEASIBLE || !(word_dual(word[e]) < need)) continue;
+                        if (word_id(word[e]) < 0) { atomicOr(&sh.failed, 1u); break; }
+                        const unsigned long long mine = pack_word(need, (int)(word[e] & MF_ID_MASK));
+                        if (!(atomicMax(&s.otherword[j + e], mine) < mine)) continue;
+                        if (few) { if (!keep(word_id(word[e]))) atomicOr(&sh.failed, 1u); }
+                        else if (atomicExch(&a.stamp[j + e], round) != round) push(word_id(word[e]), next, counter);
+                    }
                 }
+                whole += (unsigned)(to - from + 3) / 4u;
             }
-            whole += (unsigned)max(to - from + 3, 0) / 4u;
         }
         if (few) hand_on(next, counter, taken, round);
         else flush(next, counter);
