@@ -426,6 +426,7 @@ struct CoreShared {
     unsigned long long list[CORE_PUSH_BUFFER];
     double profit[CORE_MAX_SOURCES], remainder[CORE_MAX_SOURCES], outside[CORE_MAX_SOURCES];
     int row[CORE_MAX_SOURCES], alive[CORE_MAX_SOURCES];
+    Top2 part[CORE_WAVES];
     unsigned pushes, base;
     unsigned long long sink, low;
     int n_alive, ok, dense;
@@ -477,12 +478,13 @@ struct SharedWords {                    // (the bits of doubles that are not neg
 
 // Best and second-best value of a whole line against the current words (one wavefront).  Out of
 // line and with nothing but values passed: rare, and its registers would be the callers' otherwise.
-__device__ __noinline__ Top2 read_whole_line(const int32_t *line, int to, const unsigned long long *words, double Kd, int salt)
+// share, shares: every so many-th stretch of 256 entries only, where several wavefronts read a line together
+__device__ __noinline__ Top2 read_whole_line(const int32_t *line, int to, const unsigned long long *words, double Kd, int salt, int share, int shares)
 {
     const int lane = threadIdx.x & 63;
     Top2 t{NEG_HUGE, NEG_HUGE, 0x7fffffff, 0};
 #pragma unroll 2
-    for (int j = lane * 4; j < to; j += 256) {
+    for (int j = share * 256 + lane * 4; j < to; j += shares * 256) {
         const int4 w4 = *(const int4 *)(line + j);
         const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
         double v[4];
@@ -605,7 +607,7 @@ struct Core {
     {
         const int to = s.line_len ? min(s.line_len[b], s.len) : s.len;
         whole += (unsigned)(to + 3) / 4u;
-        return read_whole_line(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, tie_salt(b));
+        return read_whole_line(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, tie_salt(b), 0, 1);
     }
 
     // a slice of a line, all of it in flight (lines are padded to a multiple of four)
@@ -649,7 +651,7 @@ struct Core {
     // another wavefront gets in between: his list is on its way while the bid is.  The first bids of a 20,000 x
     // 20,000 phase 236 -> 187 us, its last 570 bidders 820 -> 627 us; a matching 15.3 -> 14.5 ms, next round 24.2 -> 23.3.
     // The two best are found as half_list.h says.
-    // waiting: if it is -1 a bidder whose whole list no longer decides does not have his line read but goes there.
+    // waiting: if it is -1 a bidder whose whole list no longer decides does not have his line read here but goes there.
     __device__ __forceinline__ int bid(const CoreSide &s, int b, Half &h, double eps, double slack, bool count_rests, int &waiting)
     {
         double outside = fmax(h.bound + slack, 0.0);        // (what is worth nothing is not bid for and holds no bid down)
@@ -696,6 +698,31 @@ struct Core {
         }
         next = __builtin_amdgcn_readfirstlane(next);
         if (next >= 0 && next != b) h = next == guess ? ahead : half_of(s, next);
+        return next;
+    }
+
+    // The same for a bidder whose line has to be read whole, by all of the workgroup: a wavefront alone takes 0.15 ms for a line of
+    // 20,000, and the step lasts as long as the slowest.  Returns, in the first wavefront, who has to bid next.
+    __device__ __forceinline__ int bid_on_whole_line(const CoreSide &s, int b, double eps, bool count_rests)
+    {
+        const int to = s.line_len ? min(s.line_len[b], s.len) : s.len;
+        Top2 t = read_whole_line(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, tie_salt(b), wave, CORE_WAVES);
+        if (lane == 0) sh.part[wave] = t;
+        __syncthreads();
+        int next = -1;
+        if (wave == 0) {
+            for (int w = 1; w < CORE_WAVES; ++w) top2_merge(t, sh.part[w]);
+            ++bids;
+            whole += (unsigned)(to + 3) / 4u;
+            if (t.b1 <= eps) {
+                if (count_rests) ++rests;
+            } else if (lane == 0) {
+                const unsigned long long mine = pack_word(a.Kd * (double)t.w - fmax(t.b2 - eps, 0.0), b + 1);
+                const unsigned long long old = atomicMax(&s.otherword[t.idx], mine);
+                next = old < mine ? word_id(old) : b;
+            }
+        }
+        __syncthreads();
         return next;
     }
 
@@ -867,7 +894,7 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
         int *next = c.bidders(c.epoch + 1u);
         int *counter = &ctl->cnt[step_fills(c.epoch)];
         c.clear_ahead();
-        if (c.tid == 0) { c.sh.pushes = 0u; c.sh.dense = 0; }
+        if (c.tid == 0) { c.sh.pushes = 0u; c.sh.dense = 0; if (LARGE) c.sh.n_alive = 0; }
         __syncthreads();
         // few enough for one die: its chain steps and barriers are shorter
         if (a.wide && count <= a.narrow_at) return MF_CORE_HANDOVER;
@@ -891,11 +918,30 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
             for (int item = c.gwave(); item < count; item += c.gwaves()) {
                 int b = __builtin_amdgcn_readfirstlane(load_fresh_i32(&list[item]));
                 typename Core<LARGE>::Half h = c.half_of(s, b);
-                int done = 0, waiting = put_off ? -1 : -2;
+                int done = 0, waiting = -1;
                 for (; b >= 0 && done < most; ++done) b = c.bid(s, b, h, eps, slack, count_rests, waiting);
-                if (LARGE && waiting >= 0) b = waiting;
+                if (LARGE && waiting >= 0) {
+                    b = waiting;
+                    if (!put_off) {                         // (read below; should there be no room, in a step to come)
+                        int at = 0;
+                        if (c.lane == 0) at = atomicAdd(&c.sh.n_alive, 1);
+                        at = __builtin_amdgcn_readfirstlane(at);
+                        if (at < CORE_MAX_SOURCES) {
+                            if (c.lane == 0) c.sh.alive[at] = b;
+                            b = -1;
+                        }
+                    }
+                }
                 if (b >= 0 && c.lane == 0) c.push(b, next, counter);
                 if (c.gwave() == 0) c.depth += (unsigned)done;
+            }
+            if (LARGE && !put_off) {
+                __syncthreads();
+                const int reading = min(c.sh.n_alive, CORE_MAX_SOURCES);
+                for (int q = 0; q < reading; ++q) {
+                    const int set_off = c.bid_on_whole_line(s, c.sh.alive[q], eps, count_rests);
+                    if (c.tid == 0 && set_off >= 0) c.push(set_off, next, counter);
+                }
             }
             if (count <= CORE_MAX_SOURCES) few_steps += most;
             stuck_steps += most;
