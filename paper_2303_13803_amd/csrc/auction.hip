@@ -1049,14 +1049,20 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     // them settles what was left open, the last one is what makes the result exact.  The
     // second side runs whenever more columns than that are unused and still priced - skipping
     // it would carry their prices into ever finer phases, where taking them off costs far more.
+    // Of a ladder of at most five phases (weights of a few hundred levels) the last three: where the first complete one
+    // would be the first or second, most of its work is done again by the next, and lists do not reach far enough for it yet.  Last
+    // four / three, six seeds: 8-bit rounds of 20,000 x 40,000 21.5 / 19.6 ms, 9000 x 20,000 9.23 / 8.32, 4000 x 9000 5.73 / 5.17,
+    // 600 x 1500 1.29 / 1.02, 300 x 700 0.71 / 0.74; uniform 8-bit matrices 12,000 x 12,000 24.6 / 15.8, 3000 x 3000 7.6 / 5.0,
+    // 3000 x 5000 1.70 / 1.73.  Longer ladders lose (4096 x 8192 of 2^24 levels 7.3 / 8.0).
+    const int keep = !warm && n_phases <= 5 && ctx->phase_keep == mf_options{}.phase_keep ? 3 : ctx->phase_keep;
     auto stop_of = [&](int ph, int growth) -> int {
         const int phases_after = n_phases - 1 - ph;
         // The coarser the phase, the more may be left (phase_growth times more per phase), but
         // never more than one bidder in 64: small problems complete every phase.
         long long stop_ll = 0;
-        if (phases_after >= ctx->phase_keep) {
+        if (phases_after >= keep) {
             stop_ll = ctx->phase_stop;
-            for (int k = ctx->phase_keep; k < phases_after && stop_ll < rn; ++k) stop_ll *= growth;
+            for (int k = keep; k < phases_after && stop_ll < rn; ++k) stop_ll *= growth;
             // the searches are for the phases that have to finish: a coarse one ends at the latest
             // where they would take over
             if (ctx->path_max > 0 && !ctx->path_off && stop_ll > 0 && stop_ll < ctx->path_max) stop_ll = ctx->path_max;
