@@ -52,25 +52,27 @@ __device__ __forceinline__ void set_column(int (&x)[C], int k, int value, int la
         if (k == lane * C + c) x[c] = value;
 }
 
-// The largest of x over the wavefront, where it is, and what y is there.  (One ballot and two moves from a lane to a
+// The largest of x over the wavefront, where it is, and what y and, with THIRD, z are there.  (One ballot and two or three moves from a lane to a
 // scalar, whatever C: each lane first picks among its own.)
-struct Pick { int value, column, other; };
-template <int C>
-__device__ __forceinline__ Pick pick(const int (&x)[C], const int (&y)[C], int lane)
+struct Pick { int value, column, other, third; };
+template <int C, bool THIRD>
+__device__ __forceinline__ Pick pick(const int (&x)[C], const int (&y)[C], const int (&z)[C], int lane)
 {
-    int best = x[0], which = lane * C, mine = y[0];
+    int best = x[0], which = lane * C, mine = y[0], also = z[0];
 #pragma unroll
     for (int c = 1; c < C; ++c) {
         const int take = x[c] > best ? -1 : 0, there = y[c];       // (selected by bits: a choice between entries of an array ends up in memory)
         best = max(best, x[c]);
         which = ((lane * C + c) & take) | (which & ~take);
         mine = (there & take) | (mine & ~take);
+        if constexpr (THIRD) { const int third = z[c]; also = (third & take) | (also & ~take); }
     }
     Pick p;
     p.value = wave_max(best);
     const int src = __builtin_ctzll(__ballot(best == p.value));
     p.column = C == 1 ? src : __builtin_amdgcn_readlane(which, src);
     p.other = __builtin_amdgcn_readlane(mine, src);
+    p.third = THIRD ? __builtin_amdgcn_readlane(also, src) : 0;
     return p;
 }
 
@@ -83,9 +85,13 @@ __device__ __forceinline__ int largest_of(const int (&x)[C])
     return wave_max(b);
 }
 
-// What bounds it: one chain of dependent bids and scans (0.20 us a scan with one column a lane, 0.31 with four, 0.43 with
+// What bounds it: one chain of dependent bids and scans (0.19 us a scan with one column a lane, 0.28 with four, 0.43 with
 // eight: a third of it the reduction, a quarter LDS) and 6 us for the launch and the matrix's way into one compute
 // unit.  64 x 64 of scored pairs: about 110 bids and 550 to 1300 scans, 140 to 280 us, where the auction's launches took 565.
+// The profit of a column's holder is kept beside the holder, so that all that a scan takes off the next row's weights is there before
+// they are: read from LDS with them it came another trip to a scalar and an addition later.  Rounds of 64 x 64 186..338 / 180..324 us
+// (two laws, three seeds each), 88 x 88 288..697 / 277..662, 64 x 150 212..416 / 200..382, 100 x 250 350..848 / 327..770.  With eight columns
+// a lane picking one more value among them costs more than it saves (64 x 400 170..397 / 173..401): read from LDS there.
 // Weights, prices, profits and labels are held doubled, and the price of a column that somebody holds is odd: of
 // equally good columns the maximum then is one that nobody holds.
 // Prices and profits are at most the largest weight (a price never exceeds the weight of the pair that holds it), which
@@ -143,14 +149,17 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
         bool over = false;
         if (!general) {
             // (lanes without a column read on into the next row, at a price that nobody pays)
-            int price[C], holder[C];
+            // (worth: the profit of a column's holder, where it is kept)
+            constexpr bool KEPT = C <= 4;
+            int price[C], holder[C], worth[C];
 #pragma unroll
-            for (int c = 0; c < C; ++c) { price[c] = lane * C + c < s.m ? 0 : 2 * SMALL_WEIGHTS; holder[c] = -1; }
+            for (int c = 0; c < C; ++c) { price[c] = lane * C + c < s.m ? 0 : 2 * SMALL_WEIGHTS; holder[c] = -1; worth[c] = 0; }
+            typedef int Columns __attribute__((ext_vector_type(C)));
+            auto weights_of = [&](int r) { return *(const Columns *)(weight + r + lane * C); };
             // what row r would have left of each column's weight at the prices
             int left[C];
             auto look = [&](int r) {
-                typedef int Columns __attribute__((ext_vector_type(C)));
-                const Columns w = *(const Columns *)(weight + r + lane * C);
+                const Columns w = weights_of(r);
 #pragma unroll
                 for (int c = 0; c < C; ++c) left[c] = w[c] - price[c];
             };
@@ -163,7 +172,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
                 for (;;) {
                     bids += 1;
                     look(r);
-                    const Pick p = pick<C>(left, holder, lane);
+                    const Pick p = pick<C, false>(left, holder, worth, lane);
                     const int best = even(p.value), before = p.other;
                     if (best <= 0) { held[r] = -1; profit[r] = 0; break; }         // for good: prices only rise
                     set_column<C>(left, p.column, -2 * SMALL_WEIGHTS, lane);
@@ -171,7 +180,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
                     if (before >= 0 && (second == best || bids >= SMALL_BIDS * s.n)) { waits[waiting++] = r; break; }
 #pragma unroll
                     for (int c = 0; c < C; ++c)
-                        if (p.column == lane * C + c) { price[c] = (price[c] + best - second) | 1; holder[c] = r; }
+                        if (p.column == lane * C + c) { price[c] = (price[c] + best - second) | 1; holder[c] = r; if constexpr (KEPT) worth[c] = second; }
                     held[r] = p.column;
                     profit[r] = second;
                     if (before < 0) break;
@@ -191,23 +200,36 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
                 const int all = even(max(largest_of<C>(left), 0));
                 int end = all, end_row = start, end_col = -1;      // the path that ends first: leave end_row unmatched
                 int r = start, base = all;
+                // (what a scan takes off the row's weights, and its base, are there before the weights are)
+                Columns w = weights_of(start);
+                int off[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) off[c] = price[c] + base;
                 Pick p;
                 for (;;) {                                         // (a column more is scanned each time)
                     scans += 1;
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        const int by_r = left[c] - base;            // (never above the label of a scanned column)
+                        const int by_r = KEPT ? w[c] - off[c] : left[c] - base;     // (never above the label of a scanned column)
                         from[c] = by_r > label[c] ? r : from[c];
                         label[c] = max(label[c], by_r);
                         open[c] = min(label[c], cap[c]);
                     }
-                    p = pick<C>(open, holder, lane);
+                    p = pick<C, KEPT>(open, holder, worth, lane);
                     if (min(p.value + (end - 1), p.other) < 0) break;       // the path known ends first, or a column that nobody holds
                     r = p.other;
-                    look(r);
-                    const int worth = __builtin_amdgcn_readfirstlane(profit[r]);
-                    set_column<C>(cap, p.column, INT32_MIN, lane);
-                    base = worth - even(p.value);
+                    if constexpr (KEPT) {
+                        w = weights_of(r);
+                        set_column<C>(cap, p.column, INT32_MIN, lane);
+                        base = p.third - even(p.value);
+#pragma unroll
+                        for (int c = 0; c < C; ++c) off[c] = price[c] + base;
+                    } else {
+                        look(r);
+                        const int has = __builtin_amdgcn_readfirstlane(profit[r]);
+                        set_column<C>(cap, p.column, INT32_MIN, lane);
+                        base = has - even(p.value);
+                    }
                     end_row = base < end ? r : end_row;
                     end = min(base, end);
                 }
@@ -218,7 +240,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
                 for (int c = 0; c < C; ++c)
                     if (cap[c] == INT32_MIN && lane * C + c < s.m) {
                         const int give = end + even(label[c]);
-                        if (give > 0) { price[c] += give; profit[holder[c]] -= give; }
+                        if (give > 0) {
+                            price[c] += give;
+                            if constexpr (KEPT) { worth[c] -= give; profit[holder[c]] = worth[c]; }
+                            else profit[holder[c]] -= give;
+                        }
                     }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 profit[start] = all - end;
@@ -236,6 +262,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const int32_t *__r
                     const int next = __builtin_amdgcn_readfirstlane(held[to]);
                     held[to] = k;
                     set_column<C>(holder, k, to, lane);
+                    if constexpr (KEPT) set_column<C>(worth, k, profit[to], lane);
                     k = next;
                 }
             }
