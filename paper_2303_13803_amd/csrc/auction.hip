@@ -679,9 +679,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         unread = false;
         return absorb(unread_ring);
     };
-    while (count > stop_at) {
-        // a side that only prepares prices (stop_at > 0) does not follow chains for ever
-        if (stop_at > 0 && tail_budget > 0 && tail_steps >= tail_budget) break;
+    while (!side_ends(count, stop_at, tail_budget, tail_steps)) {
         const bool bulk = count > ctx->tail_max;
         if (unread && !bulk) {
             // chains, teams and searches are laid out for the exact number of bidders
@@ -1056,19 +1054,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     // 3000 x 5000 1.70 / 1.73.  Longer ladders lose (4096 x 8192 of 2^24 levels 7.3 / 8.0).
     const int keep = !warm && n_phases <= 5 && ctx->phase_keep == mf_options{}.phase_keep ? 3 : ctx->phase_keep;
     auto stop_of = [&](int ph, int growth) -> int {
-        const int phases_after = n_phases - 1 - ph;
-        // The coarser the phase, the more may be left (phase_growth times more per phase), but
-        // never more than one bidder in 64: small problems complete every phase.
-        long long stop_ll = 0;
-        if (phases_after >= keep) {
-            stop_ll = ctx->phase_stop;
-            for (int k = keep; k < phases_after && stop_ll < rn; ++k) stop_ll *= growth;
-            // the searches are for the phases that have to finish: a coarse one ends at the latest
-            // where they would take over
-            if (ctx->path_max > 0 && !ctx->path_off && stop_ll > 0 && stop_ll < ctx->path_max) stop_ll = ctx->path_max;
-            if (stop_ll > rn / 64) stop_ll = rn / 64;
-        }
-        return (int)stop_ll;
+        return bidders_left_over(n_phases - 1 - ph, keep, ctx->phase_stop, growth, ctx->path_off ? 0 : ctx->path_max, rn);
     };
     int phases = 0;
     mf_core_state core{};
@@ -1112,7 +1098,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         // columns of a served tree from the other copy of the matrix
         if (!have_transpose && stop_at == 0 && ctx->path_max > 1 && rn > 1) make_transpose();
         if (have_transpose) fwd.T = At;
-        int rc = run_side(ctx, fwd, rn, true, stop_at, (ctx->phase_tail_sides & 1) && rn >= ctx->phase_tail_from ? ctx->phase_tail_steps : 0, &left_over);
+        int rc = run_side(ctx, fwd, rn, true, stop_at, mf_tail_steps(ctx, 0, rn), &left_over);
         if (rc != MF_OK) return rc;
         // who holds what after the forward rounds; unassigned priced columns go to list[0]
         hipLaunchKernelGGL(forward_done_rows_kernel, dim3((rn + 255) / 256), dim3(256), 0, ctx->stream, rn,
@@ -1130,7 +1116,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         const int rev_count = ctx->h_stats->cnt[0];
         if (rev_count > stop_at) {
             if (!have_transpose) make_transpose();
-            rc = run_side(ctx, rev, rev_count, false, stop_at, (ctx->phase_tail_sides & 2) && rn >= ctx->phase_tail_from ? ctx->phase_tail_steps : 0, &left_over);
+            rc = run_side(ctx, rev, rev_count, false, stop_at, mf_tail_steps(ctx, 1, rn), &left_over);
             if (rc != MF_OK) return rc;
             hipLaunchKernelGGL(reverse_done_cols_kernel, dim3((rm + 255) / 256), dim3(256), 0, ctx->stream, rm,
                                ctx->price, ctx->col2row);

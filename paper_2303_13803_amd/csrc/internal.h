@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <tuple>
 #include "muxmatch.h"
+#include "side_end.h"
 
 #define MF_HIP(call)                                                            \
     do {                                                                        \
@@ -262,6 +263,8 @@ struct SideArgs {
     const int32_t *edge_weight;
     int *rested;                        // optional: counts the bidders that rest (best value at most eps)
 };
+
+inline long long mf_tail_steps(const mf_ctx *ctx, int side, int lines) { return steps_of_side(side, ctx->phase_tail_sides, ctx->phase_tail_steps, ctx->phase_tail_from, lines); }
 
 // report.hip
 int mf_send(mf_ctx *ctx, const mf_report &r, unsigned *number);         // on the stream; *number says which it is

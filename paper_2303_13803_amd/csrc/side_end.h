@@ -1,0 +1,33 @@
+// When a side of a phase that only prepares prices ends with bidders left over (run_side in auction.hip, run_bids in core.hip).
+//
+// What such a side leaves undone the next phase finds: columns that nobody holds and that have to come down to price 0, all others
+// with them, one of the next phase's smaller epsilons at a time.  A few of those a search places at once, however far they have to come;
+// fifty of them bid.  With 900 rows, 950 columns and weights of 2^29 to 2^29 + 3 the phases on lists ended both sides
+// after 64 dependent steps: the fifty columns too many were left over every time, prices stayed where the
+// first phase had driven them, and the first phase that runs to the end, at 2531, was to bring them down from
+// 1.8e10: billions of bids.  Where columns bid until at most `stop` are left, every side takes some 25 bids a line.
+//
+// No dependence on the device: tests/side_end.cpp counts the bids of such ladders on the CPU.
+#pragma once
+
+#if defined(__HIPCC__)
+#define MF_END_FN __host__ __device__ __forceinline__
+#else
+#define MF_END_FN inline
+#endif
+
+// Bidders that may be left over, with `after` phases to come of which the last `keep` run to the end: `stop`, times `growth` for every
+// phase further from those, at least `search` (so many are placed by a search: for the phases that have to finish), at most one line in 64.
+MF_END_FN int bidders_left_over(int after, int keep, long long stop, int growth, int search, int lines)
+{
+    if (after < keep) return 0;
+    for (int k = keep; k < after && stop < lines; ++k) stop *= growth;
+    if (stop > 0 && stop < search) stop = search;
+    return (int)(stop < lines / 64 ? stop : lines / 64);
+}
+
+// Dependent steps after which the side (0: rows bid, 1: columns) ends all the same (0: no limit).  sides: a bit each.
+MF_END_FN long long steps_of_side(int side, int sides, long long steps, int from, int lines) { return (sides >> side & 1) && lines >= from ? steps : 0; }
+
+// Whether a side with `left` bidders ends, of which `stop` may be left over, after `followed` dependent steps.
+MF_END_FN bool side_ends(int left, int stop, long long steps, long long followed) { return left <= stop || (stop > 0 && steps > 0 && followed >= steps); }
