@@ -317,7 +317,8 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            the last phase_keep phases (of at most five, the last three while it has its default) run until nobody is
  *            left to bid.  "phase_tail_steps" (64) /
  *            "phase_tail_sides" (1: rows bidding; 2: columns; 3: both) / "phase_tail_from" (8192
- *            lines): such a side also ends after that many dependent chain steps.  "final_jump" (0:
+ *            lines): such a side also ends after that many dependent chain steps (in phases on lists, either
+ *            side unless phase_tail_sides is 0).  "final_jump" (0:
  *            off): epsilon in weight units at or below which the next phase is the last.
  *   rounds   "tail_max" (1024 bidders: below, one kernel follows the eviction chains), "bulk_shape"
  *            (0..4: threads x lines per workgroup with many bidders: 256x1, 64x4, 64x2 (default),
@@ -330,7 +331,7 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            chains are left
  *   searches "path_max" (16, at most 64; 0: none): bidders at or below which one device-wide
  *            shortest-augmenting-path search places them all, after "path_after" (256) chain
- *            steps; "path_grid" (0: one workgroup per compute unit), "path_width" (1024 epsilons; at least
+ *            steps, and as many as it takes of any number after 16 times as many and 512 without an eighth fewer; "path_grid" (0: one workgroup per compute unit), "path_width" (1024 epsilons; at least
  *            "core_width" for a search that takes over from one on lists),
  *            "path_frontier_rows" (1024), "path_pull" (0), "path_spin_limit" (2^22 polls a workgroup
  *            waits for the others before all give up; see mf_result.fallbacks)

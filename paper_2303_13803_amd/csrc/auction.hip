@@ -643,6 +643,8 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     // Short chains are cheapest followed step by step; a chain that is still going after
     // `path_after` steps is ended by shortest-path searches instead.
     long long team_steps = 0;
+    long long stuck_steps = 0;              // chain steps, and rounds, since there were an eighth more bidders
+    int fewest = count;
     int idle_launches = 0;
     long long tail_steps = 0;               // dependent steps of the chain kernels of this run, longest workgroup of each
     *left_over = count;
@@ -665,7 +667,11 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         bids_before = ctx->h_stats->bids;
         count = ctx->h_stats->cnt[at & 3];
         if (counted_teams) team_steps += (long long)ctx->h_stats->launch_max;     // the longest any leader went
-        if (chained) tail_steps += (long long)ctx->h_stats->launch_max;
+        if (chained) {
+            tail_steps += (long long)ctx->h_stats->launch_max;
+            stuck_steps += (long long)ctx->h_stats->launch_max;
+        }
+        if (count < fewest - fewest / 8) { fewest = count; stuck_steps = 0; }
         // a bounded wait ran out: one workgroup per chain, or no more searches, for the rest of this solve
         if (ctx->h_stats->team_abort == 1) { ctx->team_off = true; ctx->fallbacks |= MF_FALLBACK_TEAMS; }
         if (ctx->h_stats->team_abort == 2) { ctx->path_off = true; ctx->fallbacks |= MF_FALLBACK_SEARCHES; }
@@ -680,7 +686,9 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         return absorb(unread_ring);
     };
     while (!side_ends(count, stop_at, tail_budget, tail_steps)) {
-        const bool bulk = count > ctx->tail_max;
+        const bool paths_ok = ctx->path_max > 0 && !ctx->path_off && ctx->n_cus > 0;
+        const long long until_stuck = paths_ok ? stuck_after(ctx->path_after) - stuck_steps : ctx->max_rounds;
+        const bool stuck = until_stuck <= 0, bulk = count > ctx->tail_max && !stuck;
         if (unread && !bulk) {
             // chains, teams and searches are laid out for the exact number of bidders
             const int rc = read_unread();
@@ -690,7 +698,6 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         bool timed = false;
         counted_teams = false; chained = false;
         const unsigned long long bytes_before = ctx->h_stats->bytes + ctx->h_stats->round_bytes;
-        const bool paths_ok = ctx->path_max > 0 && !ctx->path_off && ctx->n_cus > 0;
         const bool teams_ok = ctx->team_max > 0 && !ctx->team_off;
         const int cus = ctx->n_cus > 0 ? ctx->n_cus : 256;
         // chains at or below which teams take over from one workgroup per chain
@@ -703,6 +710,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         if (left <= 0) return MF_ERR_NOT_CONVERGED;
         if (bulk) {
             const int batch = (count > 4096 || time_first) ? 1 : 3;     // the timed round stands alone
+            stuck_steps += batch;
             for (int r = 0; r < batch; ++r) {
                 timed = time_first;
                 launch_round(ctx, s, count, ring, r == 0);
@@ -711,11 +719,14 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             hipLaunchKernelGGL(compact_kernel, dim3((count + COMPACT_THREADS - 1) / COMPACT_THREADS), dim3(COMPACT_THREADS), 0, ctx->stream,
                                ctx->list[ring & 1], ctx->list[(ring + 1) & 1], ctx->stats, ring, ctx->path_label);
             ++ring;
-        } else if (paths_ok && (count <= search_now || (count <= ctx->path_max && (team_steps >= ctx->path_after || !teams_ok)))) {
-            // few enough bidders, and chains long enough, to place each bidder by a shortest-path
+        } else if (paths_ok && (count <= search_now || stuck || (count <= ctx->path_max && (team_steps >= ctx->path_after || !teams_ok)))) {
+            // few enough bidders, or chains long enough, to place each bidder by a shortest-path
             // search over the whole device
-            const int rc = mf_launch_path_search(ctx, s, ring, search_width > ctx->path_width ? search_width : ctx->path_width);
+            int width = search_width > ctx->path_width ? search_width : ctx->path_width;
+            if (stuck && width < ctx->core_width) width = ctx->core_width;
+            const int rc = mf_launch_path_search(ctx, s, ring, width);
             if (rc != MF_OK) return rc;
+            stuck_steps = 0;
             ++ring;
         } else if (!teams_ok || count > team_from) {
             const int grid = count < ctx->chain_grid ? count : ctx->chain_grid;
@@ -732,7 +743,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             // then take seconds - measured)
             hipLaunchKernelGGL(chain_kernel, dim3(grid), dim3(CHAIN_THREADS), 0, ctx->stream, s,
                                ctx->list[ring & 1], ctx->list[(ring + 1) & 1], ctx->stats, ring,
-                               left / grid + 1, hand_back);
+                               left / grid + 1 < until_stuck ? left / grid + 1 : until_stuck, hand_back);
             ++ring;
         } else {
             // every remaining chain gets a team: the fewer chains, the more workgroups on each
@@ -746,6 +757,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             const long long stop_after = before_paths ? ctx->path_after - team_steps
                                                       : (count > ctx->team_max ? ctx->team_regroup : team_cap);
             if (stop_after < team_cap) team_cap = stop_after;
+            if (until_stuck < team_cap) team_cap = until_stuck;
             counted_teams = before_paths;
             chained = true;
             hipLaunchKernelGGL(team_begin_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->stats,

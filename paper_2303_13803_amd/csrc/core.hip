@@ -395,7 +395,7 @@ struct CoreArgs {
     double refine_lower;
     double refine_below;                // epsilon at or below which a complete phase is followed by a refinement
     int path_max;
-    long long path_after, tail_steps[2];      // (by side)
+    long long path_after, tail_steps;
     int steps_many, steps_few;
     double path_width;
     int frontier_high;
@@ -882,7 +882,6 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
 {
     const CoreArgs &a = c.a;
     CoreCtl *ctl = c.ctl;
-    const long long tail_steps = a.tail_steps[count_rests ? 0 : 1];         // (rows bid where rests count)
     long long few_steps = 0, stuck_steps = 0;
     int fewest = count;
     unsigned dense_lines = 0, looks = 0;
@@ -899,11 +898,11 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
         __syncthreads();
         // few enough for one die: its chain steps and barriers are shorter
         if (a.wide && count <= a.narrow_at) return MF_CORE_HANDOVER;
-        if (side_ends(count, stop_at, tail_steps, few_steps)) break;            // (does not follow its last chains for ever)
+        if (side_ends(count, stop_at, a.tail_steps, few_steps)) break;            // (does not follow its last chains for ever)
         const bool few = count <= a.path_max || (count <= CORE_MAX_SOURCES && few_steps >= 4 * a.path_after);
         // (hundreds of bidders that outbid each other by an epsilon at a time, as on rank-one weights: a
         // search for as many of them as it takes)
-        const bool stuck = stuck_steps >= 16 * a.path_after + 512;
+        const bool stuck = stuck_steps >= stuck_after(a.path_after);
         if (a.path_max > 0 && ((few && few_steps >= a.path_after) || stuck)) {
             const int rc = c.search(s, eps, slack, count, list, next, counter);
             if (rc == MF_CORE_DENSE || rc == MF_CORE_RELIST) { ++c.epoch; count = load_fresh_i32(&ctl->cnt[step_reads(c.epoch)]); }
@@ -2026,7 +2025,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
         const long long share = 48 + rn / 8, after = ctx->core_after * (share < 256 ? share : 256) / 256;
         a.path_after = ctx->path_after < after ? ctx->path_after : after;
     }
-    for (int side = 0; side < 2; ++side) a.tail_steps[side] = mf_tail_steps(ctx, side, rn);
+    a.tail_steps = steps_of_side(0, ctx->phase_tail_sides ? 1 : 0, ctx->phase_tail_steps, ctx->phase_tail_from, rn);
     a.steps_many = ctx->core_many; a.steps_few = ctx->core_few;
     a.path_width = (double)ctx->core_width;
         a.frontier_high = ctx->path_frontier_rows;

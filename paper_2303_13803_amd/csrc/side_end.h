@@ -6,6 +6,9 @@
 // after 64 dependent steps: the fifty columns too many were left over every time, prices stayed where the
 // first phase had driven them, and the first phase that runs to the end, at 2531, was to bring them down from
 // 1.8e10: billions of bids.  Where columns bid until at most `stop` are left, every side takes some 25 bids a line.
+// From phase_tail_from lines on sides do end so (on lists, both), for what it saves: C4's 20,000 x 20,000, seeds 63, 83 and 97, auctions of 49, 49 and 63 ms
+// that take 73, 79 and 83 where columns bid on (seed 81 116 / 37 ms, sixteen ordinary ones 15.4 / 14.6).  Prices that are far off are then left to searches
+// (stuck_after): 8200 x 8240 such weights 0.9 s, 8200 x 8300, where more columns are too many than may be left over, 0.08 s.
 //
 // No dependence on the device: tests/side_end.cpp counts the bids of such ladders on the CPU.
 #pragma once
@@ -31,3 +34,8 @@ MF_END_FN long long steps_of_side(int side, int sides, long long steps, int from
 
 // Whether a side with `left` bidders ends, of which `stop` may be left over, after `followed` dependent steps.
 MF_END_FN bool side_ends(int left, int stop, long long steps, long long followed) { return left <= stop || (stop > 0 && steps > 0 && followed >= steps); }
+
+// Dependent steps without an eighth fewer bidders after which a search takes as many of them as it can, however many there are:
+// they outbid each other by an epsilon at a time, and may have as far to go as prices reach.  (Twenty columns too many where the phases before
+// might leave 23 over, 1500 x 1520 weights of 2^29 to 2^29 + 3: 2e10 at an epsilon of 1e5.)
+MF_END_FN long long stuck_after(long long path_after) { return 512 + 16 * (path_after < 1ll << 40 ? path_after : 1ll << 40); }

@@ -279,17 +279,18 @@ def test_lists_one_two_and_four_lines_a_workgroup(orc, n, m, base, spread):
     assert did["lists_made"] > 0
 
 
-@pytest.mark.parametrize("n,m", [(900, 950), (950, 900), (900, 1800)])
+@pytest.mark.parametrize("n,m", [(900, 950), (950, 900), (900, 1800), (1500, 1520), (2100, 2120), (8200, 8240)])
 @pytest.mark.parametrize("options", [{}, {"core_refine": 0}, {"core": 0}])
 def test_weights_that_are_nearly_the_same(orc, n, m, options):
     """A few units on top of 2^29: every column too many has to come all the way down from what the first phase, at
-    2^29 (n + 1) / 24, drove the prices to.  Some 30 bids a line and phase and what the searches scan; a bid for each epsilon would be billions."""
+    2^29 (n + 1) / 24, drove the prices to.  Some 30 bids a line and phase and what the searches scan (from 8192 rows on more: phases
+    on lists end sides early there); a bid for each epsilon would be billions."""
     import paper_2303_13803_amd as mm
     rng = np.random.default_rng(n + m)
     W = (2 ** 29 + rng.integers(0, 4, (n, m))).astype(np.int32)
     W[rng.random((n, m)) < 0.3] = INF
     ctx = mm.Context(n, m)
-    for k, val in dict(options, max_rounds=20_000_000).items():
+    for k, val in dict(options, max_rounds=20_000_000 if n < 8192 else 400_000_000).items():
         ctx.set_option(k, val)
     r2c = torch.empty(n, dtype=torch.int32, device="cuda")
     u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
