@@ -1059,12 +1059,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     // them settles what was left open, the last one is what makes the result exact.  The
     // second side runs whenever more columns than that are unused and still priced - skipping
     // it would carry their prices into ever finer phases, where taking them off costs far more.
-    // Of a ladder of at most five phases (weights of a few hundred levels) the last three: where the first complete one
-    // would be the first or second, most of its work is done again by the next, and lists do not reach far enough for it yet.  Last
-    // four / three, six seeds: 8-bit rounds of 20,000 x 40,000 21.5 / 19.6 ms, 9000 x 20,000 9.23 / 8.32, 4000 x 9000 5.73 / 5.17,
-    // 600 x 1500 1.29 / 1.02, 300 x 700 0.71 / 0.74; uniform 8-bit matrices 12,000 x 12,000 24.6 / 15.8, 3000 x 3000 7.6 / 5.0,
-    // 3000 x 5000 1.70 / 1.73.  Longer ladders lose (4096 x 8192 of 2^24 levels 7.3 / 8.0).
-    const int keep = !warm && n_phases <= 5 && ctx->phase_keep == mf_options{}.phase_keep ? 3 : ctx->phase_keep;
+    const int keep = phases_to_the_end(ctx->phase_keep, warm, n_phases, rn, rm);
     auto stop_of = [&](int ph, int growth) -> int {
         return bidders_left_over(n_phases - 1 - ph, keep, ctx->phase_stop, growth, ctx->path_off ? 0 : ctx->path_max, rn);
     };

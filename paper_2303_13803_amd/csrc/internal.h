@@ -115,7 +115,7 @@ struct mf_options {
     int phase_stop = 16;                        // unplaced bidders at or below which a phase that only prepares prices ends
     int phase_growth = 2;                       // ... times this for every phase further from the ones that run to the end
     int phase_growth_rest = 32;                 // bidders that may have given up before coarse phases stop leaving more
-    int phase_keep = 4;                         // the last so many phases always run to the end
+    int phase_keep = 0;                         // the last so many phases always run to the end (0: nobody has said how many, see side_end.h)
     long long phase_tail_steps = 64;            // dependent chain steps after which a side that only prepares prices ends (0: no limit)
     int phase_tail_from = 8192;                 // ... for problems with at least this many bidding lines
     int phase_tail_sides = 1;                   // ... on which sides: bit 0 the first (rows bid), bit 1 the second
@@ -150,13 +150,13 @@ struct mf_options {
 
     auto how_to_match() const
     {
-        return std::tie(theta, fit_prefix_below, edge_lists_from, fit_prefix, warm_reset_cols, warm_eps_units, phase_stop, phase_growth,
-                        phase_growth_rest, phase_keep, phase_tail_steps, phase_tail_from, phase_tail_sides,
+        return std::tuple_cat(std::make_tuple(phase_keep ? phase_keep : PHASES_TO_THE_END), std::tie(theta, fit_prefix_below, edge_lists_from, fit_prefix, warm_reset_cols, warm_eps_units, phase_stop, phase_growth,
+                        phase_growth_rest, phase_tail_steps, phase_tail_from, phase_tail_sides,
                         final_jump, tail_max, bulk_grid, bulk_shape, bulk_share, team_max, team_size, team_threads,
                         team_wide, team_regroup, path_max, path_after, path_grid, path_width, path_pull,
                         path_frontier_rows, path_spin_limit, chain_grid, core, core_depth_eps, core_many, core_few,
                         core_after, core_wide, core_narrow, core_read, core_read_least, core_refine, core_width,
-                        round_lag);
+                        round_lag));
     }
     // Whether one that says how to match differs from its default: small problems are then matched that way, too.
     bool as_told() const

@@ -19,6 +19,20 @@
 #define MF_END_FN inline
 #endif
 
+// How many of a solve's last phases run until nobody is left to bid.  asked: so many, whatever the number (0: nobody has).
+// While nobody has said how many: of a ladder of at most five phases (weights of a few hundred levels) the last three, where there are
+// many lines or half as many columns again as rows; there the first complete one would be the first or second, most of its work is
+// done again by the next, and lists do not reach far enough for it yet.  Four / three, ms, four or six seeds: 8-bit rounds of 20,000 x 40,000 14.8 / 11.6, 9000 x
+// 20,000 8.6 / 7.1, 4000 x 9000 5.0 / 4.7, 1200 x 2500 2.16 / 1.98, 600 x 1500 1.39 / 1.11, 300 x 700 0.69 / 0.69; uniform 8-bit matrices 12,000 x 12,000 21.5 /
+// 7.7, 6000 x 6000 9.7 / 8.8, 9000 x 12,000 5.6 / 5.6, 3000 x 5000 2.68 / 2.69, 1000 x 1700 0.75 / 0.75.  Smaller ones nearer the square lose: 3000 x 3000 3.46 / 3.96,
+// 1000 x 1000 3.57 / 4.07, 600 x 600 2.28 / 2.59, a round of 3000 x 3300 3.29 / 3.44.  So do longer ladders (4096 x 8192 of 2^24 levels 7.3 / 8.0).
+constexpr int PHASES_TO_THE_END = 4;
+MF_END_FN int phases_to_the_end(int asked, bool warm, int phases, int rows, int columns)
+{
+    if (asked) return asked;
+    return !warm && phases <= 5 && (rows >= 4096 || 2ll * columns >= 3ll * rows) ? 3 : PHASES_TO_THE_END;
+}
+
 // Bidders that may be left over, with `after` phases to come of which the last `keep` run to the end: `stop`, times `growth` for every
 // phase further from those, at least `search` (so many are placed by a search: for the phases that have to finish), at most one line in 64.
 MF_END_FN int bidders_left_over(int after, int keep, long long stop, int growth, int search, int lines)

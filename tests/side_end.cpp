@@ -67,6 +67,10 @@ long long run(const Side &s, double K, std::vector<int> bidders, double eps, int
 
 int main(int argc, char **argv)
 {
+    if (argc == 6 && !strcmp(argv[1], "asked")) {               // asked phases rows columns: what is asked for is what is done
+        printf("%d\n", phases_to_the_end(atoi(argv[2]), false, atoi(argv[3]), atoi(argv[4]), atoi(argv[5])));
+        return 0;
+    }
     if (argc < 6) return 2;
     const int n = atoi(argv[1]), m = atoi(argv[2]), base = atoi(argv[3]), spread = atoi(argv[4]), theta = 24, keep = 4;
     const bool every_side = !strcmp(argv[5], "every side");

@@ -154,6 +154,20 @@ def test_phases_that_end_early_leave_the_optimum_alone(mm, orc, options):
         ctx.close()
 
 
+@pytest.mark.parametrize("n,m", [(150, 240), (700, 720), (1500, 2300)])
+def test_phases_that_run_to_the_end_of_a_short_ladder(mm, orc, n, m):
+    """8-bit weights have at most five phases.  The last three of them run to the end, or four, or as many as are asked for."""
+    W = synth.threshold_matrix(50, n, m, 256, 0.7)
+    expect = _optimum(orc, W)
+    for keep in (None, 3, 4, 5):
+        ctx = mm.Context(n, m)
+        if keep:
+            ctx.set_option("phase_keep", keep)
+        res = _solve_and_verify(ctx, orc, W, expect)
+        assert 2 <= res.phases <= 5
+        ctx.close()
+
+
 _BULK = {}
 
 
