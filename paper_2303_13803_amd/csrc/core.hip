@@ -25,6 +25,7 @@
 #include "scan.h"
 #include "report.h"
 #include "half_list.h"
+#include "line_parts.h"
 #include "list_cut.h"
 #include "search_words.h"
 #include "team_join.h"
@@ -620,12 +621,10 @@ struct Core {
         }
     }
 
-    // Wavefronts that read a line together, each every so many-th slice of it: one, unless there are fewer lines than
-    // wavefronts.  (A wavefront for every slice that the longest line might have looked 40 times at each of 27,000 feasible prefixes
-    // of 4000 entries, 1.6 us each time: 6.7 ms of a 20,000 x 40,000 round.)
-    __device__ __forceinline__ int parts_of_line(const CoreSide &s, int lines) const
+    // Wavefronts that read a line together, each every so many-th slice of it
+    __device__ __forceinline__ int parts_of(const CoreSide &s, int lines) const
     {
-        return max(1, min((s.len + CORE_SLICE - 1) / CORE_SLICE, gwaves() / lines));
+        return parts_of_line((s.len + CORE_SLICE - 1) / CORE_SLICE, lines, gwaves(), s.line_len != nullptr);
     }
 
     // The best half of a line's list, a lane an entry, and what nothing else is worth more than.
@@ -1452,7 +1451,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
             // whole lines, in slices: a wavefront each.  What bounds it is latency: four entries' prices are in
             // flight per lane, and a label is looked at only where it may be lowered (one entry at a
             // time took 24 us a slice, 36 ms where 37,000 lines of 20,000 had to be read).
-            const int parts = nw > 0 ? parts_of_line(s, nw) : 1;
+            const int parts = nw > 0 ? parts_of(s, nw) : 1;
             for (int it = gwave(); it < nw * parts; it += gwaves()) {
                 const int e = it / parts, part = it - e * parts;
                 const int entry = load_fresh_i32(&whole_list[e]);
@@ -1676,7 +1675,7 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
         taken = end;
         first = wave; stride = CORE_WAVES;
         }
-        const int parts = whole_rows > 0 ? parts_of_line(s, whole_rows) : 1;
+        const int parts = whole_rows > 0 ? parts_of(s, whole_rows) : 1;
         for (int it = gwave(); it < whole_rows * parts; it += gwaves()) {
             const int i = load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[it / parts]);
             const int col = load_fresh_i32(&a.row2col[i]);
