@@ -523,6 +523,32 @@ __device__ __noinline__ Top2 read_list(const int2 *e, const unsigned long long *
     return t;
 }
 
+// A bid on a whole line that all of a workgroup reads; returns, in its first lane, who has to bid next, -1 or (in all of the first wavefront)
+// RESTS.  Out of line like read_whole_line.
+constexpr int RESTS = -2;
+__device__ __noinline__ int bid_by_workgroup(const int32_t *line, int to, unsigned long long *words, double Kd, int b, double eps, Top2 *part)
+{
+    const int wave = (int)threadIdx.x >> 6;
+    Top2 t = read_whole_line(line, to, words, Kd, tie_salt(b), wave, CORE_WAVES);
+    if ((threadIdx.x & 63) == 0) part[wave] = t;
+    __syncthreads();
+    int next = -1;
+    if (wave == 0) {
+        for (int w = 1; w < CORE_WAVES; ++w) top2_merge(t, part[w]);
+        if (t.b1 <= eps) next = RESTS;
+        else if (threadIdx.x == 0) {
+            const unsigned long long mine = pack_word(Kd * (double)t.w - fmax(t.b2 - eps, 0.0), b + 1);
+            const unsigned long long old = atomicMax(&words[t.idx], mine);
+            next = old < mine ? word_id(old) : b;
+        }
+    }
+    __syncthreads();
+    return next;
+}
+
+// (out of line: rare, and a dozen divisions)
+__device__ __noinline__ int parts_out_of_line(int slices, int lines, int waves, bool prefixes) { return parts_of_line(slices, lines, waves, prefixes); }
+
 // Everything a workgroup carries through the launch.  LARGE: for problems whose first bids run on all dies, where
 // bidders may wait for better lists.  (Those few instructions cost a chain's step 3 % where one die does it all.)
 template <bool LARGE>
@@ -538,7 +564,7 @@ struct Core {
 
     __device__ Core(const CoreArgs &args, CoreCtl *c, CoreShared &s)
         : a(args), ctl(c), sh(s), G(1), rank(0), generation(0), columns_ready(args.columns_ready), epoch((unsigned)args.first_parity), tid(threadIdx.x), lane(threadIdx.x & 63),
-          wave(threadIdx.x >> 6), bids(0), depth(0), steps(0), scans(0), whole(0), rests(0) {}
+          wave(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)), bids(0), depth(0), steps(0), scans(0), whole(0), rests(0) {}
 
     __device__ int gtid() const { return (int)rank * CORE_THREADS + tid; }
     __device__ int gsize() const { return (int)G * CORE_THREADS; }
@@ -624,7 +650,7 @@ struct Core {
     // Wavefronts that read a line together, each every so many-th slice of it
     __device__ __forceinline__ int parts_of(const CoreSide &s, int lines) const
     {
-        return parts_of_line((s.len + CORE_SLICE - 1) / CORE_SLICE, lines, gwaves(), s.line_len != nullptr);
+        return parts_out_of_line((s.len + CORE_SLICE - 1) / CORE_SLICE, lines, gwaves(), s.line_len != nullptr);
     }
 
     // The best half of a line's list, a lane an entry, and what nothing else is worth more than.
@@ -701,27 +727,16 @@ struct Core {
     }
 
     // The same for a bidder whose line has to be read whole, by all of the workgroup: a wavefront alone takes 0.15 ms for a line of
-    // 20,000, and the step lasts as long as the slowest.  Returns, in the first wavefront, who has to bid next.
+    // 20,000, and the step lasts as long as the slowest.  Returns, in the first lane, who has to bid next.
     __device__ __forceinline__ int bid_on_whole_line(const CoreSide &s, int b, double eps, bool count_rests)
     {
         const int to = s.line_len ? min(s.line_len[b], s.len) : s.len;
-        Top2 t = read_whole_line(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, tie_salt(b), wave, CORE_WAVES);
-        if (lane == 0) sh.part[wave] = t;
-        __syncthreads();
-        int next = -1;
+        const int next = bid_by_workgroup(s.A + (size_t)b * s.pitch, to, s.otherword, a.Kd, b, eps, sh.part);
         if (wave == 0) {
-            for (int w = 1; w < CORE_WAVES; ++w) top2_merge(t, sh.part[w]);
             ++bids;
             whole += (unsigned)(to + 3) / 4u;
-            if (t.b1 <= eps) {
-                if (count_rests) ++rests;
-            } else if (lane == 0) {
-                const unsigned long long mine = pack_word(a.Kd * (double)t.w - fmax(t.b2 - eps, 0.0), b + 1);
-                const unsigned long long old = atomicMax(&s.otherword[t.idx], mine);
-                next = old < mine ? word_id(old) : b;
-            }
+            if (next == RESTS && count_rests) ++rests;
         }
-        __syncthreads();
         return next;
     }
 
@@ -1452,29 +1467,29 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
             // flight per lane, and a label is looked at only where it may be lowered (one entry at a
             // time took 24 us a slice, 36 ms where 37,000 lines of 20,000 had to be read).
             const int parts = nw > 0 ? parts_of(s, nw) : 1;
-            for (int it = gwave(); it < nw * parts; it += gwaves()) {
-                const int e = it / parts, part = it - e * parts;
-                const int entry = load_fresh_i32(&whole_list[e]);
+            int slice = 0;                                          // (a slice a turn: what a line needs is loaded again, a loop around the slices keeps it in registers)
+            for (int it = gwave(); it < nw * parts;) {
+                const int e = it / parts, from = (it - e * parts + slice * parts) * CORE_SLICE;
+                const int entry = __builtin_amdgcn_readfirstlane(load_fresh_i32(&whole_list[e]));
                 int i;
                 double base;
+                bool sound = true;
                 if (entry < 0) {                                    // a bidder
                     const int j = -1 - entry;
-                    i = sh.row[j];
+                    i = __builtin_amdgcn_readfirstlane(sh.row[j]);
                     base = sh.profit[j] + eps;
                 } else {
                     const unsigned long long lw = load_fresh_u64(&a.label[entry]), word = load_fresh_u64(&s.otherword[entry]);
-                    i = word_id(word);
+                    i = __builtin_amdgcn_readfirstlane(word_id(word));
                     base = (double)(long long)(lw >> MF_ID_BITS) + fma(a.Kd, (double)load_fresh_i32(&a.held_weight[entry]), -word_dual(word)) + eps;
-                    if (lw == CORE_INF || i < 0) continue;          // (cannot be)
+                    sound = lw != CORE_INF && i >= 0;               // (cannot be otherwise)
                 }
-                const int length = s.line_len ? min(s.line_len[i], s.len) : s.len;
-                const int32_t *line = s.A + (size_t)i * s.pitch;
-                const double unlisted = base - (s.bound[i] + slack);
-                double left_out = CORE_FAR;                         // the nearest unlisted one beyond the nearest path end
-                for (int from = part * CORE_SLICE; from < length; from += parts * CORE_SLICE) {
-                    const int to = min(length, from + CORE_SLICE);
+                const int length = !sound ? 0 : s.line_len ? min(s.line_len[i], s.len) : s.len, to = min(length, from + CORE_SLICE);
+                if (from < to) {
                     int4 ahead[CORE_SLICE / 256];
-                    load_slice(line, from, to, ahead);
+                    load_slice(s.A + (size_t)i * s.pitch, from, to, ahead);
+                    const double unlisted = base - (s.bound[i] + slack);
+                    double left_out = CORE_FAR;                     // the nearest unlisted one beyond the nearest path end
 #pragma unroll
                     for (int q = 0; q < CORE_SLICE / 256; ++q) {
                         const int j = from + q * 256 + lane * 4;
@@ -1492,10 +1507,12 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                         }
                     }
                     whole += (unsigned)(to - from + 3) / 4u;
+                    left_out = -wave_max(-left_out);
+                    if (lane == 0 && left_out < CORE_FAR)
+                        publish_slice(SharedWords{}, WholeLine{nullptr, entry < 0 ? (double *)&ctl->src_left[-1 - entry] : &a.left[entry]}, left_out);
                 }
-                left_out = -wave_max(-left_out);
-                if (lane == 0 && left_out < CORE_FAR)
-                    publish_slice(SharedWords{}, WholeLine{nullptr, entry < 0 ? (double *)&ctl->src_left[-1 - entry] : &a.left[entry]}, left_out);
+                if (from + parts * CORE_SLICE < length) ++slice;
+                else { it += gwaves(); slice = 0; }
             }
             from_bidders = false;
         } else {
@@ -1676,16 +1693,16 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
         first = wave; stride = CORE_WAVES;
         }
         const int parts = whole_rows > 0 ? parts_of(s, whole_rows) : 1;
-        for (int it = gwave(); it < whole_rows * parts; it += gwaves()) {
-            const int i = load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[it / parts]);
+        int slice = 0;
+        for (int it = gwave(); it < whole_rows * parts;) {
+            const int row = it / parts, from = (it - row * parts + slice * parts) * CORE_SLICE;
+            const int i = __builtin_amdgcn_readfirstlane(load_fresh_i32(&((epoch & 1u) ? a.whole1 : a.whole0)[row]));
             const int col = load_fresh_i32(&a.row2col[i]);
             const double profit = col >= 0 ? fma(a.Kd, (double)load_fresh_i32(&a.held_weight[i]), -word_dual(load_fresh_u64(&s.otherword[max(col, 0)]))) : 0.0;
-            const int length = s.line_len ? min(s.line_len[i], s.len) : s.len;
-            const int32_t *line = s.A + (size_t)i * s.pitch;
-            for (int from = it % parts * CORE_SLICE; from < length; from += parts * CORE_SLICE) {
-                const int to = min(length, from + CORE_SLICE);
+            const int length = s.line_len ? min(s.line_len[i], s.len) : s.len, to = min(length, from + CORE_SLICE);
+            if (from < to) {
                 int4 ahead[CORE_SLICE / 256];
-                load_slice(line, from, to, ahead);
+                load_slice(s.A + (size_t)i * s.pitch, from, to, ahead);
 #pragma unroll
                 for (int q = 0; q < CORE_SLICE / 256; ++q) {
                     const int j = from + q * 256 + lane * 4;
@@ -1706,6 +1723,8 @@ __device__ __forceinline__ int Core<LARGE>::refine(double lower_by)
                 }
                 whole += (unsigned)(to - from + 3) / 4u;
             }
+            if (from + parts * CORE_SLICE < length) ++slice;
+            else { it += gwaves(); slice = 0; }
         }
         if (few) hand_on(next, counter, taken, round);
         else flush(next, counter);
