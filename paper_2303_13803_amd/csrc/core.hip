@@ -75,12 +75,16 @@ constexpr double CORE_UNBOUNDED = -1.0e300;         // bound of a line whose lis
 // In the pass nearly every wavefront has a few entries to keep in every step, and looking at sixteen entries a lane exactly, and
 // keeping each behind a branch and an atomic of its own, took 1.5 us a step where the loads take half of that.  So floats decide which
 // entries are looked at exactly, a lane goes through its own few one after the other, and the next step's loads are on
-// their way meanwhile (one step a time: unrolled, the registers leave a wavefront less a SIMD).
+// their way meanwhile.  One step a time: by twos four lines need more registers than four wavefronts a SIMD leave each (334 / 366 us for 20,000
+// lines of 20,000).  Four are as many as LDS lets in with four lines; held to five, one line and two spill eight and twelve
+// registers and take 1 to 3 % longer (1000 lines of 20,000 30.0 / 29.4 us, 2003 of 3001 23.6 / 22.9).
 // (Lists of 20,000 lines of 20,000 entries: 926 us when a workgroup of 1024 threads kept a whole line in
 // registers and found the cut by histograms, a dozen barriers a line; 400 us with every entry looked at exactly; 346 us now, 4.6 TB/s.  6500,
 // 2500 and 1200 of them 155 -> 132, 78 -> 61 and 68 -> 42 us; 4096 lines of 8192 52 -> 45, 2003 of 3001 26 -> 24.
 // One line a workgroup up to four a compute unit, two up to eight: 256 lines of 20,000 take 60 us by fours, 24 us so;
-// 1200 46 by fours, 41 by twos; 4096 of 8192 entries 45 by fours, 54 by twos.)
+// 1200 46 by fours, 41 by twos; 4096 of 8192 entries 45 by fours, 54 by twos.  Aiming at 300 entries above the first cut, not 240: fewer
+// lists fall short of CORE_LIST, more are looked at, 1 to 3 % longer: 1000 lines of 20,000 30.8 / 30.0, 1900
+// 45.8 / 44.7, 4096 of 8192 45.4 / 44.6, 20,000 of 20,000 335 / 333.)
 constexpr int LIST_THREADS = 256, LIST_CAP = 512, LIST_AIM = 240, LIST_SAMPLE_GROUPS = 512;
 
 // Of the integers in v (PER a lane; `low`: unused), a cut with at most `most` of them above it, and at
@@ -104,7 +108,7 @@ __device__ __forceinline__ double cut_above(const double (&v)[PER], int least, i
 }
 
 template <int LINES>                                    // lines a workgroup makes lists of, at most one a wavefront
-__global__ __launch_bounds__(LIST_THREADS, 5) void core_list_kernel(
+__global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
     const int32_t *__restrict__ A, long long pitch, int len, const int *__restrict__ line_len, int lines, int stride,
     const int *__restrict__ which, const double *__restrict__ dual, double Kd, int2 *__restrict__ entries,
     double *__restrict__ bound, double *__restrict__ half_bound, double *depth, const double *__restrict__ own_dual,

@@ -22,3 +22,5 @@ def test_registers_of_the_kernels_on_lists(tmp_path):
         spilled[name] = int(re.search(r"VGPRs Spill: (\d+)", rest).group(1))
     engine = [n for k, n in spilled.items() if "core_kernel" in k]
     assert len(engine) == 2 and max(engine) <= 51, spilled
+    lists = [n for k, n in spilled.items() if "core_list_kernel" in k]
+    assert len(lists) == 3 and max(lists) == 0, spilled
