@@ -213,3 +213,55 @@ def test_bidding_rounds_down_to_the_last_bidder(mm, orc, n, m):
     if n == m:
         assert res.bytes_scanned == 4 * n * res.bids
     ctx.close()
+
+
+def _sought_after(seed, n, m, feasible=1.0):
+    """Weights of which half is the column's own: most rows want the same few columns, so that thousands lose the first rounds.
+    feasible: the share of each row's pairs that may be used, the same number in every row."""
+    rng = np.random.default_rng(seed)
+    W = (2 ** 19 * (rng.random((1, m)) + rng.random((n, m)))).astype(np.int32)
+    if feasible < 1.0:
+        keep = int(feasible * m) // 4 * 4
+        drop = np.argsort(rng.random((n, m)), axis=1)[:, keep:]
+        np.put_along_axis(W, drop, INF, axis=1)
+    return W
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("n, m", [(4001, 4001), (3900, 4897)])
+def test_groups_of_lines_with_places_that_are_empty(mm, orc, shape, n, m):
+    """Rounds of two and four lines a workgroup, three to a look at the counts, of which the second and the third have empty places
+    among them: whatever is missing or there twice, in bids or in bytes, does not add up."""
+    W = _sought_after(73, n, m)
+    assert n - len(np.unique(W.argmax(axis=1))) > 2048              # bidders of the second round: groups all the same
+    ctx = mm.Context(n, m)
+    for k, v in {"core": 0, "tail_max": 0, "path_max": 0, "team_max": 0, "edge_lists_from": 0, "phase_stop": 0, "bulk_shape": shape, "bulk_share": 0}.items():
+        ctx.set_option(k, v)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(m, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, m, r2c, u, v)
+    ctx.close()
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and P == res.primal and res.chain_bids == 0 and res.fallbacks == 0
+    # rows read m entries a bid and columns n, which leaves one count of each; a bid or a line more or less is off by a
+    # share of m - n (997)
+    by_rows = res.bids if n == m else (res.bytes_scanned // 4 - n * res.bids) // (m - n)
+    assert res.bytes_scanned == 4 * (m * by_rows + n * (res.bids - by_rows)) and n <= by_rows <= res.bids
+
+
+@pytest.mark.parametrize("n, feasible", [(4100, 0.25), (6001, 0.1)])
+def test_rounds_on_lists_of_feasible_pairs_with_places_that_are_empty(mm, orc, n, feasible):
+    """As many feasible pairs in every row, on lists of which at least 2048 bidders read eight bytes a pair; the rest of them reads whole lines."""
+    W = _sought_after(74, n, n, feasible)
+    d = int(feasible * n) // 4 * 4
+    assert ((W != mm.INFEASIBLE).sum(axis=1) == d).all()
+    ctx = mm.Context(n, n)
+    for k, v in {"core": 0, "tail_max": 2047, "path_max": 0, "edge_lists_from": 4096, "phase_stop": 0}.items():
+        ctx.set_option(k, v)
+    r2c = torch.empty(n, dtype=torch.int32, device="cuda")
+    u, v = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(n, dtype=torch.int64, device="cuda")
+    res = ctx.solve_assignment(padded_matrix(W), n, n, r2c, u, v)
+    ctx.close()
+    code, P, _ = orc.check_certificate(W, r2c.cpu().numpy(), u.cpu().numpy(), v.cpu().numpy(), res.K)
+    assert code == 0 and res.cert_ok == 1 and P == res.primal and res.fallbacks == 0 and res.matched == n
+    assert res.bids > res.chain_bids and res.bytes_scanned == 8 * d * (res.bids - res.chain_bids) + 4 * n * res.chain_bids
