@@ -903,6 +903,7 @@ int run_core(mf_ctx *ctx, SideArgs &fwd, SideArgs &rev, int rn, int rm, const lo
                       st.reason == MF_CORE_DENSE ? ctx->core_width : 0);
         if (rc != MF_OK) return rc;
         st.sides_left += 1;
+        if (ctx->path_off) { after = st.phase; return MF_OK; }      // (what a search left half-done may hold nobody to his epsilon: the phase once more)
         st.stage = forward ? MF_CORE_FORWARD_DONE : MF_CORE_REVERSE_DONE;
         st.count = left_over;
     }
@@ -1092,6 +1093,9 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
             }
         }
         const long long eps = ladder[ph];
+        const bool searching = !ctx->path_off;
+        // (a wait ran out in a search: what it left half-done may hold nobody to his epsilon, so the phase begins once more, without searches)
+        const auto once_more = [&]() { return searching && ctx->path_off; };
         phases = ph + 1;
         fwd.eps = rev.eps = (double)eps;
         hipLaunchKernelGGL(reset_kernel, dim3((nm + 255) / 256), dim3(256), 0, ctx->stream, rn, rm, ctx->price,
@@ -1107,6 +1111,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
         if (have_transpose) fwd.T = At;
         int rc = run_side(ctx, fwd, rn, true, stop_at, mf_tail_steps(ctx, 0, rn), &left_over);
         if (rc != MF_OK) return rc;
+        if (once_more()) { core_ok = false; --ph; continue; }
         // who holds what after the forward rounds; unassigned priced columns go to list[0]
         hipLaunchKernelGGL(forward_done_rows_kernel, dim3((rn + 255) / 256), dim3(256), 0, ctx->stream, rn,
                            ctx->profit, ctx->roword, ctx->row2col, ctx->stats);
@@ -1125,6 +1130,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
             if (!have_transpose) make_transpose();
             rc = run_side(ctx, rev, rev_count, false, stop_at, mf_tail_steps(ctx, 1, rn), &left_over);
             if (rc != MF_OK) return rc;
+            if (once_more()) { core_ok = false; --ph; continue; }
             hipLaunchKernelGGL(reverse_done_cols_kernel, dim3((rm + 255) / 256), dim3(256), 0, ctx->stream, rm,
                                ctx->price, ctx->col2row);
             hipLaunchKernelGGL(reverse_done_rows_kernel, dim3((rn + 255) / 256), dim3(256), 0, ctx->stream, rn,

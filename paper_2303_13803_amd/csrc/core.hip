@@ -433,7 +433,7 @@ struct CoreShared {
     int row[CORE_MAX_SOURCES], alive[CORE_MAX_SOURCES];
     Top2 part[CORE_WAVES];
     unsigned pushes, base;
-    unsigned long long sink, low;
+    unsigned long long sink, low, served;      // served: length of the search's last path
     int n_alive, ok, dense;
     unsigned failed;
 };
@@ -1045,6 +1045,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
         for (int j = 0; j < count; ++j)
             if (sh.profit[j] > 0.0) sh.alive[n++] = j;      // a bidder whose best value is at most eps rests
         sh.n_alive = n;
+        sh.served = 0ull;
     }
     __syncthreads();
     int n_alive = sh.n_alive;
@@ -1332,6 +1333,7 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
                                            [&]() { return by_column(s); }, offer_again))
                     return MF_CORE_ABORT;
                 if (by_columns) columns_ready |= side_bit;
+                if (tid == 0) sh.served = d_star;
                 n_alive = sh.n_alive;
                 agreed_sink = resting_bidders();
                 since_served = 0;
@@ -1582,6 +1584,16 @@ __device__ __forceinline__ int Core<LARGE>::search(const CoreSide &s, double eps
         ++my_steps;
         if (!barrier()) return MF_CORE_ABORT;
     }
+    // What the other trees' columns have still to rise for the paths served so far: a row of a tree that has been served
+    // would rather have them at these prices.  (See pending_rise in search_words.h; the last step's barrier ended all writing of labels.)
+    if (status)
+        for (int k = gtid(); k < s.len; k += gsize()) {
+            const unsigned long long rise = pending_rise(load_fresh_u64(&a.label[k]), CORE_INF, MF_ID_BITS, sh.served);
+            if (rise) {
+                const unsigned long long word = load_fresh_u64(&s.otherword[k]);
+                store_through(&s.otherword[k], pack_word(word_dual(word) + (double)(long long)rise, (int)(word & MF_ID_MASK)));
+            }
+        }
     if (gtid() == 0) {
         steps += (unsigned)my_steps;
         for (int e = 0; e < n_alive; ++e) store_i32(&next[atomicAdd(counter, 1)], sh.row[sh.alive[e]]);

@@ -67,3 +67,16 @@ MF_SEARCH_FN double unlisted_from(unsigned long long length, unsigned long long 
 {
     return length >= read_from ? left : by_bound;
 }
+
+// ---- searches that end before all their bidders are placed ----
+// Serving a path of length d raises its own tree's columns by d less their labels.  The columns of other trees with labels below d are
+// left as they are until their own tree is served, by a path at least as long: until then a row of the served tree may like one of
+// them better than what it holds, by up to d less that column's label, which is more than the epsilon that bids and searches rest on.
+// So a search that ends early raises them by that: as far as if their trees had been served at the length of the last
+// path.  (Labels below that length are final; those of the served tree's columns are not below it.  Left out, later searches met cycles of
+// negative length, found no root and gave up: one in twelve solves of rank-one weights, 848 x 924.)
+MF_SEARCH_FN unsigned long long pending_rise(unsigned long long label, unsigned long long none, int id_bits, unsigned long long served)
+{
+    const unsigned long long length = label >> id_bits;
+    return label != none && length < served ? served - length : 0ull;
+}
