@@ -644,6 +644,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     // `path_after` steps is ended by shortest-path searches instead.
     long long team_steps = 0;
     long long stuck_steps = 0;              // chain steps, and rounds, since there were an eighth more bidders
+    long long until_stuck = 0;              // ... of which so many may come
     int fewest = count;
     int idle_launches = 0;
     long long tail_steps = 0;               // dependent steps of the chain kernels of this run, longest workgroup of each
@@ -656,7 +657,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     bool unread = false;
     int unread_ring = 0, unread_slot = 0, slot = 0;
     unsigned unread_report = 0;
-    bool counted_teams = false, chained = false;
+    bool counted_teams = false, chained = false, unstuck = false;
     unsigned long long bids_before = ctx->h_stats->bids;
     // takes in the statistics copied after the launch that left the lists at position `at`
     auto absorb = [&](int at) -> int {
@@ -668,10 +669,13 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
         count = ctx->h_stats->cnt[at & 3];
         if (counted_teams) team_steps += (long long)ctx->h_stats->launch_max;     // the longest any leader went
         if (chained) {
-            tail_steps += (long long)ctx->h_stats->launch_max;
+            // (a launch that ended because its chains are stuck leaves hundreds of bidders: a search first, and chains again)
+            if ((long long)ctx->h_stats->launch_max < until_stuck) tail_steps += (long long)ctx->h_stats->launch_max;
             stuck_steps += (long long)ctx->h_stats->launch_max;
         }
         if (count < fewest - fewest / 8) { fewest = count; stuck_steps = 0; }
+        // (a step of a search takes as long as four of a chain: no more time goes into such searches than into chains)
+        if (unstuck) stuck_steps = -4 * (long long)ctx->h_stats->launch_max;
         // a bounded wait ran out: one workgroup per chain, or no more searches, for the rest of this solve
         if (ctx->h_stats->team_abort == 1) { ctx->team_off = true; ctx->fallbacks |= MF_FALLBACK_TEAMS; }
         if (ctx->h_stats->team_abort == 2) { ctx->path_off = true; ctx->fallbacks |= MF_FALLBACK_SEARCHES; }
@@ -687,7 +691,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
     };
     while (!side_ends(count, stop_at, tail_budget, tail_steps)) {
         const bool paths_ok = ctx->path_max > 0 && !ctx->path_off && ctx->n_cus > 0;
-        const long long until_stuck = paths_ok ? stuck_after(ctx->path_after) - stuck_steps : ctx->max_rounds;
+        until_stuck = paths_ok ? stuck_after(ctx->path_after) - stuck_steps : ctx->max_rounds;
         const bool stuck = until_stuck <= 0, bulk = count > ctx->tail_max && !stuck;
         if (unread && !bulk) {
             // chains, teams and searches are laid out for the exact number of bidders
@@ -696,7 +700,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             continue;
         }
         bool timed = false;
-        counted_teams = false; chained = false;
+        counted_teams = false; chained = false; unstuck = false;
         const unsigned long long bytes_before = ctx->h_stats->bytes + ctx->h_stats->round_bytes;
         const bool teams_ok = ctx->team_max > 0 && !ctx->team_off;
         const int cus = ctx->n_cus > 0 ? ctx->n_cus : 256;
@@ -726,7 +730,7 @@ int run_side(mf_ctx *ctx, const SideArgs &s, int count, bool time_first, int sto
             if (stuck && width < ctx->core_width) width = ctx->core_width;
             const int rc = mf_launch_path_search(ctx, s, ring, width);
             if (rc != MF_OK) return rc;
-            stuck_steps = 0;
+            unstuck = stuck;
             ++ring;
         } else if (!teams_ok || count > team_from) {
             const int grid = count < ctx->chain_grid ? count : ctx->chain_grid;
@@ -1060,7 +1064,7 @@ int mf_run_solver(mf_ctx *ctx, const int32_t *d_W, int n, int m, int64_t ldw,
     // them settles what was left open, the last one is what makes the result exact.  The
     // second side runs whenever more columns than that are unused and still priced - skipping
     // it would carry their prices into ever finer phases, where taking them off costs far more.
-    const int keep = phases_to_the_end(ctx->phase_keep, warm, n_phases, rn, rm);
+    const int keep = phases_to_the_end(ctx->phase_keep, warm, n_phases);
     auto stop_of = [&](int ph, int growth) -> int {
         return bidders_left_over(n_phases - 1 - ph, keep, ctx->phase_stop, growth, ctx->path_off ? 0 : ctx->path_max, rn);
     };

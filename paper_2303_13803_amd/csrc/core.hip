@@ -337,7 +337,7 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
 // ---------------------------------------------------------------- the engine
 
 struct CoreReport {
-    int reason, phase, stage, count, parity;
+    int reason, phase, stage, count, parity, columns_fit;
     unsigned columns_ready;
     unsigned long long bids, depth, steps, scans, whole_groups, rested;      // (whole_groups: of four entries, of lines read whole)
 };
@@ -393,6 +393,7 @@ struct CoreArgs {
     int have_columns;                   // the lists of side 1 exist
     int may_refine;
     unsigned columns_ready;
+    int columns_fit;                    // where the launch begins with columns that bid: they find rows that have none
     double stale_rise;
     double stale;                       // epsilons a dual may have come down since the lists were made before they are made again
     int refine_rounds, refine_patience; // rounds in all; rounds without a new least number of rows left
@@ -401,6 +402,7 @@ struct CoreArgs {
     double refine_below;                // epsilon at or below which a complete phase is followed by a refinement
     int path_max;
     long long path_after, tail_steps;
+    int tail_always;                    // of a side on which columns have to come down, too (side_end.h)
     int steps_many, steps_few;
     double path_width;
     int frontier_high;
@@ -434,7 +436,7 @@ struct CoreShared {
     Top2 part[CORE_WAVES];
     unsigned pushes, base;
     unsigned long long sink, low, served;      // served: length of the search's last path
-    int n_alive, ok, dense;
+    int n_alive, ok, dense, columns_fit;
     unsigned failed;
 };
 
@@ -916,7 +918,7 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
         __syncthreads();
         // few enough for one die: its chain steps and barriers are shorter
         if (a.wide && count <= a.narrow_at) return MF_CORE_HANDOVER;
-        if (side_ends(count, stop_at, a.tail_steps, few_steps)) break;            // (does not follow its last chains for ever)
+        if (side_ends(count, stop_at, count_rests || a.tail_always || __builtin_amdgcn_readfirstlane(c.sh.columns_fit) ? a.tail_steps : 0, few_steps)) break;      // (see side_end.h)
         const bool few = count <= a.path_max || (count <= CORE_MAX_SOURCES && few_steps >= 4 * a.path_after);
         // (hundreds of bidders that outbid each other by an epsilon at a time, as on rank-one weights: a
         // search for as many of them as it takes)
@@ -1794,6 +1796,7 @@ __device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int sta
         out.stage = stage;
         out.count = count;
         out.parity = parity;
+        out.columns_fit = sh.columns_fit;
         out.steps = steps;
         out.columns_ready = columns_ready;
         out.depth = depth;
@@ -1807,6 +1810,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
     const CoreSide &fwd = a.side[0], &rev = a.side[1];
     int ph = a.first_phase, stage = a.first_stage, count = a.first_count;
     int left_rows = 0, left_cols = 0;
+    if (tid == 0) sh.columns_fit = a.columns_fit;      // (barriers before anybody asks)
     double bid_budget = a.bid_limit;
     bool ok, fresh_lists = stage != MF_CORE_RESET;    // (the launch before this one asked for them)
     if (stage == MF_CORE_FORWARD_DONE) left_rows = count;
@@ -1903,6 +1907,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 if (!barrier()) return MF_CORE_ABORT;
             }
             left_cols = count;
+            if (tid == 0) sh.columns_fit = columns_find_room(count, left_rows, stop) ? 1 : 0;
             if (count > most_unused) {
                 if (!a.have_columns) return leave(MF_CORE_COLUMNS, ph, MF_CORE_REVERSE, count, (int)(epoch & 1u));
                 stage = MF_CORE_REVERSE;
@@ -1964,7 +1969,7 @@ __device__ __forceinline__ void clear_control(CoreCtl *ctl, int lane)
     ctl->die = -1;
     ctl->joined = 0u; ctl->arrived = 0u; ctl->members = 0u;
     for (unsigned q = 0; q < STEP_RING; ++q) { ctl->cnt[q] = 0; ctl->whole_count[q] = 0; ctl->dense[q] = 0u; }
-    ctl->out = CoreReport{MF_CORE_ABORT, -1, MF_CORE_RESET, 0, 0, 0u, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
+    ctl->out = CoreReport{MF_CORE_ABORT, -1, MF_CORE_RESET, 0, 0, 0, 0u, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
 }
 
 __global__ __launch_bounds__(64) void core_clear_kernel(CoreCtl *ctl) { clear_control(ctl, threadIdx.x); }
@@ -2042,6 +2047,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     for (int k = 0; k < plan.n_phases; ++k) { a.eps[k] = (double)plan.eps[k]; a.stop[k] = plan.stop[k]; a.stop_grown[k] = plan.stop_grown[k]; }
     a.n_phases = plan.n_phases;
     a.first_phase = st->phase; a.first_stage = st->stage; a.first_count = st->count; a.first_parity = st->parity;
+    a.columns_fit = st->columns_fit;
     a.growth_rest = ctx->phase_growth_rest;
     a.rested_before = plan.rested_before;
     a.have_columns = plan.have_columns ? 1 : 0;
@@ -2059,7 +2065,8 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
         const long long share = 48 + rn / 8, after = ctx->core_after * (share < 256 ? share : 256) / 256;
         a.path_after = ctx->path_after < after ? ctx->path_after : after;
     }
-    a.tail_steps = steps_of_side(0, ctx->phase_tail_sides ? 1 : 0, ctx->phase_tail_steps, ctx->phase_tail_from, rn);
+    a.tail_steps = ctx->phase_tail_sides ? ctx->phase_tail_steps : 0;
+    a.tail_always = rn >= ctx->phase_tail_from ? 1 : 0;
     a.steps_many = ctx->core_many; a.steps_few = ctx->core_few;
     a.path_width = (double)ctx->core_width;
         a.frontier_high = ctx->path_frontier_rows;
@@ -2097,7 +2104,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     st->by_column += __builtin_popcount(h.columns_ready & ~st->columns_ready);
     st->columns_ready = h.columns_ready;
     st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
-    st->reason = h.reason; if (h.phase >= 0) st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity;
+    st->reason = h.reason; if (h.phase >= 0) st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity; st->columns_fit = h.columns_fit;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
     st->launches += 1;

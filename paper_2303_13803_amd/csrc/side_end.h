@@ -5,8 +5,9 @@
 // fifty of them bid.  With 900 rows, 950 columns and weights of 2^29 to 2^29 + 3 the phases on lists ended both sides
 // after 64 dependent steps: the fifty columns too many were left over every time, prices stayed where the
 // first phase had driven them, and the first phase that runs to the end, at 2531, was to bring them down from
-// 1.8e10: billions of bids.  Where columns bid until at most `stop` are left, every side takes some 25 bids a line.
-// From phase_tail_from lines on sides do end so (on lists, both), for what it saves: C4's 20,000 x 20,000, seeds 63, 83 and 97, auctions of 49, 49 and 63 ms
+// 1.8e10: billions of bids.  So columns that do not all find rows without one bid until at most `stop` are left: every such side takes some 25
+// bids a line.  Other sides on lists end early, at every size: 2946 x 2946 such weights, where no column is too many, 11 ms, 24 where sides go on.
+// From phase_tail_from lines on all sides on lists do, for what it saves: C4's 20,000 x 20,000, seeds 63, 83 and 97, auctions of 49, 49 and 63 ms
 // that take 73, 79 and 83 where columns bid on (seed 81 116 / 37 ms, sixteen ordinary ones 15.4 / 14.6).  Prices that are far off are then left to searches
 // (stuck_after): 8200 x 8240 such weights 0.9 s, 8200 x 8300, where more columns are too many than may be left over, 0.08 s.
 //
@@ -20,18 +21,14 @@
 #endif
 
 // How many of a solve's last phases run until nobody is left to bid.  asked: so many, whatever the number (0: nobody has).
-// While nobody has said how many: of a ladder of at most five phases (weights of a few hundred levels) the last three, where there are
-// many lines or half as many columns again as rows; there the first complete one would be the first or second, most of its work is
-// done again by the next, and lists do not reach far enough for it yet.  Four / three, ms, four or six seeds: 8-bit rounds of 20,000 x 40,000 14.8 / 11.6, 9000 x
-// 20,000 8.6 / 7.1, 4000 x 9000 5.0 / 4.7, 1200 x 2500 2.16 / 1.98, 600 x 1500 1.39 / 1.11, 300 x 700 0.69 / 0.69; uniform 8-bit matrices 12,000 x 12,000 21.5 /
-// 7.7, 6000 x 6000 9.7 / 8.8, 9000 x 12,000 5.6 / 5.6, 3000 x 5000 2.68 / 2.69, 1000 x 1700 0.75 / 0.75.  Smaller ones nearer the square lose: 3000 x 3000 3.46 / 3.96,
-// 1000 x 1000 3.57 / 4.07, 600 x 600 2.28 / 2.59, a round of 3000 x 3300 3.29 / 3.44.  So do longer ladders (4096 x 8192 of 2^24 levels 7.3 / 8.0).
+// While nobody has: of a ladder of at most five phases (weights of a few hundred levels) the last three; the first complete one would be the
+// first or second, most of its work is done again by the next, and lists do not reach far enough for it yet.  Four / three, ms, four or
+// six seeds: 8-bit rounds of 20,000 x 40,000 14.8 / 11.6, 9000 x 20,000 8.6 / 7.1, 4000 x 9000 5.0 / 4.7, 600 x 1500 1.39 / 1.11, 300 x 700 0.69 / 0.69; uniform 8-bit
+// matrices 12,000 x 12,000 21.5 / 7.7, 6000 x 6000 9.7 / 8.8, 3000 x 5000 2.68 / 2.69; with prefixes of a half 3613 x 3613 33 / 6.7; thresholds of 2612 x 2653
+// 6.6 / 2.4, four levels of 750 x 750 9.5 / 3.8.  Some lose a little (uniform 3000 x 3000 3.46 / 3.96, 600 x 600 2.28 / 2.59), longer ladders more
+// (4096 x 8192 of 2^24 levels 7.3 / 8.0).
 constexpr int PHASES_TO_THE_END = 4;
-MF_END_FN int phases_to_the_end(int asked, bool warm, int phases, int rows, int columns)
-{
-    if (asked) return asked;
-    return !warm && phases <= 5 && (rows >= 4096 || 2ll * columns >= 3ll * rows) ? 3 : PHASES_TO_THE_END;
-}
+MF_END_FN int phases_to_the_end(int asked, bool warm, int phases) { return asked ? asked : !warm && phases <= 5 ? 3 : PHASES_TO_THE_END; }
 
 // Bidders that may be left over, with `after` phases to come of which the last `keep` run to the end: `stop`, times `growth` for every
 // phase further from those, at least `search` (so many are placed by a search: for the phases that have to finish), at most one line in 64.
@@ -45,6 +42,9 @@ MF_END_FN int bidders_left_over(int after, int keep, long long stop, int growth,
 
 // Dependent steps after which the side (0: rows bid, 1: columns) ends all the same (0: no limit).  sides: a bit each.
 MF_END_FN long long steps_of_side(int side, int sides, long long steps, int from, int lines) { return (sides >> side & 1) && lines >= from ? steps : 0; }
+
+// Whether the columns that bid, of which `stop` may be left over, find rows that have none: then nobody has to come down to 0.
+MF_END_FN bool columns_find_room(int columns, int rows, int stop) { return columns - rows <= stop; }
 
 // Whether a side with `left` bidders ends, of which `stop` may be left over, after `followed` dependent steps.
 MF_END_FN bool side_ends(int left, int stop, long long steps, long long followed) { return left <= stop || (stop > 0 && steps > 0 && followed >= steps); }

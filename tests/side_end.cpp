@@ -67,8 +67,8 @@ long long run(const Side &s, double K, std::vector<int> bidders, double eps, int
 
 int main(int argc, char **argv)
 {
-    if (argc == 6 && !strcmp(argv[1], "asked")) {               // asked phases rows columns: what is asked for is what is done
-        printf("%d\n", phases_to_the_end(atoi(argv[2]), false, atoi(argv[3]), atoi(argv[4]), atoi(argv[5])));
+    if (argc == 4 && !strcmp(argv[1], "asked")) {               // so many asked for of so many phases
+        printf("%d\n", phases_to_the_end(atoi(argv[2]), false, atoi(argv[3])));
         return 0;
     }
     if (argc < 6) return 2;
@@ -93,12 +93,10 @@ int main(int argc, char **argv)
     for (int ph = 0; ph < preparing; ++ph) {
         const double eps = (double)ladder[ph];
         const int stop = bidders_left_over(phases - 1 - ph, keep, 16, 2, 16, n);
-        // (the first phase is on whole lines)
-        const long long steps[2] = {ph == 0 ? 0 : every_side ? 64 : steps_of_side(0, 1, 64, 8192, n), ph == 0 ? 0 : every_side ? 64 : steps_of_side(1, 1, 64, 8192, n)};
         std::vector<int> all(n), holder(m, -1), row_holder(n, -1), unused;
         for (int i = 0; i < n; ++i) all[i] = i;
         int rows_left = 0, columns_left = 0;
-        bids += run(Side{W, n, m, price, holder}, K, all, eps, stop, steps[0], most, rows_left);
+        bids += run(Side{W, n, m, price, holder}, K, all, eps, stop, ph == 0 ? 0 : 64, most, rows_left);      // (the first phase is on whole lines)
         std::fill(profit.begin(), profit.end(), -1.0);
         for (int k = 0; k < m; ++k) {
             if (holder[k] >= 0) { row_holder[holder[k]] = k; profit[holder[k]] = K * W[(size_t)holder[k] * m + k] - price[k]; }
@@ -110,7 +108,8 @@ int main(int argc, char **argv)
                     if (W[(size_t)i * m + k] >= 0) profit[i] = std::max(profit[i], K * W[(size_t)i * m + k] - price[k]);
         const bool next_runs_to_the_end = ph + 1 >= preparing;
         if ((int)unused.size() > (stop > 0 && !next_runs_to_the_end ? stop + rows_left : stop)) {
-            bids += run(Side{T, m, n, profit, row_holder}, K, unused, eps, stop, steps[1], most, columns_left);
+            const bool early = ph > 0 && (every_side || columns_find_room((int)unused.size(), rows_left, stop));
+            bids += run(Side{T, m, n, profit, row_holder}, K, unused, eps, stop, early ? 64 : 0, most, columns_left);
             std::fill(price.begin(), price.end(), 0.0);
             for (int i = 0; i < n; ++i) if (row_holder[i] >= 0) price[row_holder[i]] = K * W[(size_t)i * m + row_holder[i]] - profit[i];
         }

@@ -31,7 +31,7 @@ def test_a_limit_on_the_steps_of_every_side_is_not(ladder, n, m):
     assert done.returncode == 1, done.stdout
 
 
-@pytest.mark.parametrize("phases,n,m,unasked", [(4, 150, 240, 3), (5, 700, 720, 4), (5, 1000, 1499, 4), (5, 1000, 1500, 3), (5, 4095, 4095, 4), (5, 4096, 4096, 3), (6, 20000, 40000, 4)])
-def test_as_many_phases_run_to_the_end_as_are_asked_for(ladder, phases, n, m, unasked):
-    """Also where that is as many as without being asked on longer ladders."""
-    assert [int(ladder("asked", asked, phases, n, m).stdout) for asked in (0, 1, 3, 4, 5, 64)] == [unasked, 1, 3, 4, 5, 64]
+@pytest.mark.parametrize("phases,unasked", [(1, 3), (5, 3), (6, 4), (36, 4)])
+def test_as_many_phases_run_to_the_end_as_are_asked_for(ladder, phases, unasked):
+    """Also where that is as many as on longer ladders without being asked."""
+    assert [int(ladder("asked", asked, phases).stdout) for asked in (0, 1, 3, 4, 5, 64)] == [unasked, 1, 3, 4, 5, 64]
