@@ -318,7 +318,7 @@ int mf_schedule_round_typed(mf_ctx *ctx, const mf_predictor *preds, int n_types,
  *            unless it has been set: to 4, too).  "phase_tail_steps" (64) /
  *            "phase_tail_sides" (1: rows bidding; 2: columns; 3: both) / "phase_tail_from" (8192
  *            lines): such a side also ends after that many dependent chain steps (in phases on lists, unless phase_tail_sides
- *            is 0, either side at any size, but below that many lines not one with columns too many).  "final_jump" (0:
+ *            is 0, either side at any size, but below that many lines not one with 17 to 64 columns too many).  "final_jump" (0:
  *            off): epsilon in weight units at or below which the next phase is the last.
  *   rounds   "tail_max" (1024 bidders: below, one kernel follows the eviction chains), "bulk_shape"
  *            (0..4: threads x lines per workgroup with many bidders: 256x1, 64x4, 64x2 (default),

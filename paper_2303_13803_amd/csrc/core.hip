@@ -337,7 +337,7 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void core_list_kernel(
 // ---------------------------------------------------------------- the engine
 
 struct CoreReport {
-    int reason, phase, stage, count, parity, columns_fit;
+    int reason, phase, stage, count, parity, columns_wait;
     unsigned columns_ready;
     unsigned long long bids, depth, steps, scans, whole_groups, rested;      // (whole_groups: of four entries, of lines read whole)
 };
@@ -393,7 +393,7 @@ struct CoreArgs {
     int have_columns;                   // the lists of side 1 exist
     int may_refine;
     unsigned columns_ready;
-    int columns_fit;                    // where the launch begins with columns that bid: they find rows that have none
+    int columns_wait;                    // where the launch begins with columns that bid: they may be left to the next phase (side_end.h)
     double stale_rise;
     double stale;                       // epsilons a dual may have come down since the lists were made before they are made again
     int refine_rounds, refine_patience; // rounds in all; rounds without a new least number of rows left
@@ -436,7 +436,7 @@ struct CoreShared {
     Top2 part[CORE_WAVES];
     unsigned pushes, base;
     unsigned long long sink, low, served;      // served: length of the search's last path
-    int n_alive, ok, dense, columns_fit;
+    int n_alive, ok, dense, columns_wait;
     unsigned failed;
 };
 
@@ -918,7 +918,7 @@ __device__ __forceinline__ int run_bids(Core<LARGE> &c, const CoreSide &s, doubl
         __syncthreads();
         // few enough for one die: its chain steps and barriers are shorter
         if (a.wide && count <= a.narrow_at) return MF_CORE_HANDOVER;
-        if (side_ends(count, stop_at, count_rests || a.tail_always || __builtin_amdgcn_readfirstlane(c.sh.columns_fit) ? a.tail_steps : 0, few_steps)) break;      // (see side_end.h)
+        if (side_ends(count, stop_at, count_rests || a.tail_always || __builtin_amdgcn_readfirstlane(c.sh.columns_wait) ? a.tail_steps : 0, few_steps)) break;      // (see side_end.h)
         const bool few = count <= a.path_max || (count <= CORE_MAX_SOURCES && few_steps >= 4 * a.path_after);
         // (hundreds of bidders that outbid each other by an epsilon at a time, as on rank-one weights: a
         // search for as many of them as it takes)
@@ -1796,7 +1796,7 @@ __device__ __forceinline__ int Core<LARGE>::leave(int reason, int phase, int sta
         out.stage = stage;
         out.count = count;
         out.parity = parity;
-        out.columns_fit = sh.columns_fit;
+        out.columns_wait = sh.columns_wait;
         out.steps = steps;
         out.columns_ready = columns_ready;
         out.depth = depth;
@@ -1810,7 +1810,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
     const CoreSide &fwd = a.side[0], &rev = a.side[1];
     int ph = a.first_phase, stage = a.first_stage, count = a.first_count;
     int left_rows = 0, left_cols = 0;
-    if (tid == 0) sh.columns_fit = a.columns_fit;      // (barriers before anybody asks)
+    if (tid == 0) sh.columns_wait = a.columns_wait;      // (barriers before anybody asks)
     double bid_budget = a.bid_limit;
     bool ok, fresh_lists = stage != MF_CORE_RESET;    // (the launch before this one asked for them)
     if (stage == MF_CORE_FORWARD_DONE) left_rows = count;
@@ -1907,7 +1907,7 @@ __device__ __forceinline__ int Core<LARGE>::run()
                 if (!barrier()) return MF_CORE_ABORT;
             }
             left_cols = count;
-            if (tid == 0) sh.columns_fit = columns_find_room(count, left_rows, stop) ? 1 : 0;
+            if (tid == 0) sh.columns_wait = columns_may_wait(count, left_rows, stop, a.path_max, CORE_MAX_SOURCES) ? 1 : 0;
             if (count > most_unused) {
                 if (!a.have_columns) return leave(MF_CORE_COLUMNS, ph, MF_CORE_REVERSE, count, (int)(epoch & 1u));
                 stage = MF_CORE_REVERSE;
@@ -2047,7 +2047,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     for (int k = 0; k < plan.n_phases; ++k) { a.eps[k] = (double)plan.eps[k]; a.stop[k] = plan.stop[k]; a.stop_grown[k] = plan.stop_grown[k]; }
     a.n_phases = plan.n_phases;
     a.first_phase = st->phase; a.first_stage = st->stage; a.first_count = st->count; a.first_parity = st->parity;
-    a.columns_fit = st->columns_fit;
+    a.columns_wait = st->columns_wait;
     a.growth_rest = ctx->phase_growth_rest;
     a.rested_before = plan.rested_before;
     a.have_columns = plan.have_columns ? 1 : 0;
@@ -2104,7 +2104,7 @@ int mf_core_launch(mf_ctx *ctx, const SideArgs &fwd, const SideArgs &rev, int rn
     st->by_column += __builtin_popcount(h.columns_ready & ~st->columns_ready);
     st->columns_ready = h.columns_ready;
     st->refined = h.reason == MF_CORE_RELIST && h.stage == MF_CORE_PHASE_DONE;
-    st->reason = h.reason; if (h.phase >= 0) st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity; st->columns_fit = h.columns_fit;
+    st->reason = h.reason; if (h.phase >= 0) st->phase = h.phase; st->stage = h.stage; st->count = h.count; st->parity = h.parity; st->columns_wait = h.columns_wait;
     st->bids += (long long)h.bids; st->depth += (long long)h.depth; st->steps += (long long)h.steps; st->scans += (long long)h.scans;
     st->rested += (long long)h.rested;
     st->launches += 1;

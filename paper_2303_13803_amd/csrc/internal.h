@@ -307,7 +307,7 @@ struct mf_core_plan {
 struct mf_core_state {
     int reason, phase, stage, count, parity;
     int wide, refined;
-    int columns_fit;                    // the columns that bid find rows that have none (side_end.h)
+    int columns_wait;                   // the columns that bid may be left to the next phase (side_end.h)
     unsigned columns_ready;             // the sides whose lists also exist by opposite line (bits)
     long long bids, depth, steps, scans, rested, bytes;      // summed over launches
     int launches, lists_made, sides_left, by_column;     // sides_left: finished on whole lines; by_column: lists that launches kept by opposite line, too

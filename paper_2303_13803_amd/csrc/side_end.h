@@ -5,7 +5,7 @@
 // fifty of them bid.  With 900 rows, 950 columns and weights of 2^29 to 2^29 + 3 the phases on lists ended both sides
 // after 64 dependent steps: the fifty columns too many were left over every time, prices stayed where the
 // first phase had driven them, and the first phase that runs to the end, at 2531, was to bring them down from
-// 1.8e10: billions of bids.  So columns that do not all find rows without one bid until at most `stop` are left: every such side takes some 25
+// 1.8e10: billions of bids.  So such columns bid until at most `stop` are left (columns_may_wait): every such side takes some 25
 // bids a line.  Other sides on lists end early, at every size: 2946 x 2946 such weights, where no column is too many, 11 ms, 24 where sides go on.
 // From phase_tail_from lines on all sides on lists do, for what it saves: C4's 20,000 x 20,000, seeds 63, 83 and 97, auctions of 49, 49 and 63 ms
 // that take 73, 79 and 83 where columns bid on (seed 81 116 / 37 ms, sixteen ordinary ones 15.4 / 14.6).  Prices that are far off are then left to searches
@@ -43,8 +43,14 @@ MF_END_FN int bidders_left_over(int after, int keep, long long stop, int growth,
 // Dependent steps after which the side (0: rows bid, 1: columns) ends all the same (0: no limit).  sides: a bit each.
 MF_END_FN long long steps_of_side(int side, int sides, long long steps, int from, int lines) { return (sides >> side & 1) && lines >= from ? steps : 0; }
 
-// Whether the columns that bid, of which `stop` may be left over, find rows that have none: then nobody has to come down to 0.
-MF_END_FN bool columns_find_room(int columns, int rows, int stop) { return columns - rows <= stop; }
+// Whether columns that bid may be left to the next phase after that many steps, which on lists count while at most `few` (64) of them are left.  With no more too
+// many (than rows without one, and `stop`) than a search places, a search brings them down; with more than `few`, some have come down to 0 by
+// then, and all others with them.  (Rounds of 1015 x 1420 2.6 ms so, 3.0 where all sides with columns too many go on, 106 x 109 1.2 and 1.5.)
+MF_END_FN bool columns_may_wait(int columns, int rows, int stop, int search, int few)
+{
+    const int too_many = columns - rows;
+    return too_many <= (stop > search ? stop : search) || too_many > few;
+}
 
 // Whether a side with `left` bidders ends, of which `stop` may be left over, after `followed` dependent steps.
 MF_END_FN bool side_ends(int left, int stop, long long steps, long long followed) { return left <= stop || (stop > 0 && steps > 0 && followed >= steps); }

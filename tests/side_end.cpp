@@ -108,7 +108,7 @@ int main(int argc, char **argv)
                     if (W[(size_t)i * m + k] >= 0) profit[i] = std::max(profit[i], K * W[(size_t)i * m + k] - price[k]);
         const bool next_runs_to_the_end = ph + 1 >= preparing;
         if ((int)unused.size() > (stop > 0 && !next_runs_to_the_end ? stop + rows_left : stop)) {
-            const bool early = ph > 0 && (every_side || columns_find_room((int)unused.size(), rows_left, stop));
+            const bool early = ph > 0 && (every_side || columns_may_wait((int)unused.size(), rows_left, stop, 16, FEW));
             bids += run(Side{T, m, n, profit, row_holder}, K, unused, eps, stop, early ? 64 : 0, most, columns_left);
             std::fill(price.begin(), price.end(), 0.0);
             for (int i = 0; i < n; ++i) if (row_holder[i] >= 0) price[row_holder[i]] = K * W[(size_t)i * m + row_holder[i]] - profit[i];

@@ -19,7 +19,7 @@ def ladder(tmp_path_factory):
     return lambda *a: subprocess.run([program, *map(str, a)], capture_output=True, text=True, timeout=120)
 
 
-@pytest.mark.parametrize("n,m,base,spread", [(300, 330, 2 ** 29, 3), (900, 950, 2 ** 29, 3), (300, 600, 2 ** 29, 3), (300, 330, 2 ** 30, 0)])
+@pytest.mark.parametrize("n,m,base,spread", [(300, 330, 2 ** 29, 3), (900, 950, 2 ** 29, 3), (300, 600, 2 ** 29, 3), (300, 330, 2 ** 30, 0), (900, 965, 2 ** 29, 3), (300, 317, 2 ** 29, 3)])
 def test_what_a_phase_leaves_to_the_next_is_bounded(ladder, n, m, base, spread):
     done = ladder(n, m, base, spread, "as it is")
     assert done.returncode == 0, done.stdout
