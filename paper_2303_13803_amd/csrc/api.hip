@@ -219,6 +219,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(dev_alloc(&ctx->stats, 1));
     TRY(dev_alloc(&ctx->cert, MF_CERT_PARTS));
     TRY(hipMalloc((void **)&ctx->score_range, 8 * sizeof(unsigned)));
+    TRY(hipMalloc((void **)&ctx->score_queue, MF_MAX_TYPES * 256 * sizeof(int)));
     TRY(hipHostMalloc((void **)&ctx->h_stats, sizeof(mf_device_stats)));
     for (int i = 0; i < 2; ++i) {
         TRY(hipHostMalloc((void **)&ctx->h_stats_slot[i], sizeof(mf_device_stats)));
@@ -246,7 +247,7 @@ int mf_destroy(mf_ctx *ctx)
     if (!ctx) return MF_ERR_ARG;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    void *dev[] = {ctx->score_range, ctx->proj_on, ctx->proj_off, ctx->mem_on, ctx->mem_off, ctx->sm_on, ctx->sm_off, ctx->order_on, ctx->order_off, ctx->rank_off, ctx->rank_on, ctx->mem_on_sorted, ctx->mem_off_sorted, ctx->fit_len_on, ctx->fit_len_off, ctx->staged, ctx->type_segment, ctx->pairs_evaluated, ctx->feasible_pairs, ctx->largest_weight, ctx->wt, ctx->price,
+    void *dev[] = {ctx->score_range, ctx->score_queue, ctx->proj_on, ctx->proj_off, ctx->mem_on, ctx->mem_off, ctx->sm_on, ctx->sm_off, ctx->order_on, ctx->order_off, ctx->rank_off, ctx->rank_on, ctx->mem_on_sorted, ctx->mem_off_sorted, ctx->fit_len_on, ctx->fit_len_off, ctx->staged, ctx->type_segment, ctx->pairs_evaluated, ctx->feasible_pairs, ctx->largest_weight, ctx->wt, ctx->price,
                    ctx->profit, ctx->colword, ctx->roword, ctx->row2col, ctx->col2row, ctx->team_ctl, ctx->path_ctl, ctx->path_label, ctx->path_expanded, ctx->path_frontier[0], ctx->path_frontier[1], ctx->path_stamp, ctx->path_held, ctx->path_base, ctx->path_tree, ctx->path_parent, ctx->path_jump, ctx->edge_count, ctx->edge_start, ctx->list[0], ctx->list[1], ctx->colmark, ctx->stats,
                    ctx->core_entries[0], ctx->core_entries[1], ctx->core_bound[0], ctx->core_bound[1], ctx->core_half_bound[0], ctx->core_half_bound[1], ctx->core_built[0], ctx->core_built[1], ctx->core_reach[0], ctx->core_reach[1],
                    ctx->core_t_entries[0], ctx->core_t_entries[1], ctx->core_t_start[0], ctx->core_t_start[1], ctx->core_t_at[0], ctx->core_t_at[1],

@@ -230,6 +230,7 @@ struct mf_ctx : mf_options {
     int *h_bad;                         // pinned: an index or a type was out of range
     mf_told *h_told;
     unsigned reports;                   // sent so far
+    int *score_queue;                   // device: next tasks of the pair kernel's launches, 16 counters each, a cache line apart
     unsigned *score_range;              // device: largest magnitudes the scorer's fp16 pieces are scaled by (project_kernel)
     mf_cert_out *h_cert;
     // timing

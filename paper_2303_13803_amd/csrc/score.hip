@@ -116,6 +116,8 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
     if (a.range) note_range(mx, &a.range[side], wave_mx);
 }
 
+constexpr int PAIR_QUEUES = 16, PAIR_QUEUE_STEP = 16;      // counters of a launch, one a cache line
+
 // What is prepared per workload before anything is ordered: its memory fraction and SM share, its rank
 // (zero), and the words later kernels of the call count or take maxima in.
 struct SetupArgs {
@@ -134,6 +136,7 @@ struct SetupArgs {
     unsigned long long *pairs_evaluated, *feasible_pairs;
     int *largest;
     unsigned *range;
+    int *queue, launches;                                  // counters of the next task, for so many launches of the pair kernel
     unsigned long long *times;
 };
 
@@ -141,6 +144,8 @@ __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
 {
     note_time(a.times, AT_SCORE);
     const int side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
+    if (side == 0 && blockIdx.x == 0)
+        for (int q = r; q < a.launches * PAIR_QUEUES; q += 256) a.queue[q * PAIR_QUEUE_STEP] = 0;
     if (side == 0 && r < 8) {
         a.range[r] = 0u;
         if (r == 0) { *a.pairs_evaluated = 0ull; if (a.feasible_pairs) *a.feasible_pairs = 0ull; if (a.largest) *a.largest = 0; }
@@ -384,22 +389,33 @@ __global__ void range_clear_kernel(unsigned *slots)
     if (threadIdx.x < 8) slots[threadIdx.x] = 0u;
 }
 
-constexpr int PAIR_THREADS = 512;   // 8 wavefronts: two per SIMD share one LDS copy of W2
-constexpr int PAIR_WAVES = PAIR_THREADS / 64;
-constexpr int PAIR_COLS = PAIR_WAVES * 32;
-
 template <int H> struct PairShape {
-    static constexpr int ROWS = 64;                        // most online rows per workgroup (128 with the fp16 pieces: measured slower)
+    static constexpr int WAVES = H == 128 ? 8 : 4;         // wavefronts that share an LDS copy of W2 and its pieces,
+    static constexpr int THREADS = WAVES * 64;
+    static constexpr int PER_UNIT = H == 128 ? 1 : 3;      // such workgroups a compute unit: two wavefronts a SIMD, or three
+    static constexpr int ROWS = 16;                        // online rows a wavefront has in LDS at a time
     static constexpr int KS = H / 2;                       // k-steps of the 32x32x2 tile
     static constexpr int MB = H / 32;                      // 32-row blocks of the hidden layer
-    static constexpr size_t LDS_BYTES = sizeof(float) * ((size_t)H * H + (size_t)ROWS * H + 4 * H + 2 * ROWS);
+    static constexpr int WAVE_FLOATS = ROWS * H + 2 * ROWS;
+    static constexpr size_t LDS_BYTES = sizeof(float) * ((size_t)H * H + 4 * H + 4 + (size_t)WAVES * WAVE_FLOATS);
 };
 
 // One wavefront owns 32 offline columns (lane & 31) and walks down the online
-// rows of the tile.  n and m count the rows and columns to score; with
+// rows of a task: those columns beside task_rows rows.  n and m count the rows and columns to score; with
 // row_map / col_map (either may be null) entry t of the map names the online
-// row / offline column that tile position t stands for, so a scattered subset
-// of rows or columns can be re-scored in place.  v_mfma_f32_32x32x2_f32 computes D[32x32] += A[32x2] B[2x32]
+// row / offline column that position t stands for, so a scattered subset
+// of rows or columns can be re-scored in place.
+//
+// Workgroups stay: each makes W2's pieces once, then its wavefronts take one task after the other, each on its own, the
+// rows' projections in LDS of their own, with no barrier.  What bounds the kernel is the matrix pipe at the clock that
+// power allows: the matrix instructions alone, on operands as they occur here, take 17.9 ns each and 21.4 with four
+// vector instructions and the reads of W2 beside them (constants, which toggle nothing: 13.5), so the 9.6e8 of
+// 20,000 x 20,000 pairs take 16.8 and 20.1 ms.  A workgroup per tile of 64 x 256 pairs set itself up
+// for each (7 percent of its time, and nothing else fits into the compute unit meanwhile), waited for its slowest
+// wavefront, and was launched for every tile that cannot fit as well.  Before / now: 20,000 x 20,000 24.6 / 23.1 ms,
+// 20,000 x 40,000 with a tenth of the pairs 7.4 / 6.2, 4096 x 8192 2.14 / 1.91, 777 x 1501 0.137 / 0.091.
+//
+// v_mfma_f32_32x32x2_f32 computes D[32x32] += A[32x2] B[2x32]
 // with lane l supplying A[l%32][l/32] and B[l/32][l%32]; we let the two k
 // slots of step s be hidden features s and H/2 + s, so each half-wave streams
 // a contiguous half of the projections.  Accumulator register r of lane l is
@@ -423,7 +439,7 @@ template <int H> struct PairShape {
 // For lane l, element t of its operand of k-block kb is hidden unit (l / 32) * H/2 + 8 kb + t, for
 // A (rows of W2) and B (pairs) alike.
 template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
-__global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
+__global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * PairShape<H>::WAVES / 4) void pair_mlp_kernel(
     const float *__restrict__ P_on, const float *__restrict__ P_off,
     const float *__restrict__ W2, const float *__restrict__ b2, const float *__restrict__ W3,
     const float *__restrict__ b3, const float *__restrict__ mem_on,
@@ -433,7 +449,8 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     unsigned long long *__restrict__ evaluated, const int32_t *__restrict__ segment,
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
-    const unsigned *__restrict__ range, int tile_rows, unsigned long long *times)
+    const unsigned *__restrict__ range, int task_rows, const int32_t *__restrict__ fit_len, int *__restrict__ next_task,
+    unsigned long long *times)
 {
     note_time(times, AT_PAIRS);
     using S = PairShape<H>;
@@ -441,36 +458,24 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     extern __shared__ float4 lds4[];
     float4 *a_lds = lds4;                                  // [MB][Q][64] float4: MFMA A operand order
     uint4 *a16_lds = (uint4 *)lds4;                        // SPLIT: [2 pieces][MB][KB][64] eight fp16 each (the same bytes)
-    float *pon_lds = (float *)(lds4) + H * H;              // [ROWS][H]
-    float *b2_lds = pon_lds + ROWS * H;
-    float *w3_lds = b2_lds + H;
-    float *mon_lds = w3_lds + H;                           // [ROWS] memory fraction of the tile's rows
-    float *wsm_lds = mon_lds + ROWS;                       // [H] layer-1 weights of the SM share
-    float *son_lds = wsm_lds + H;                          // [ROWS] 1 - SM activity of the tile's rows
-    float *w3s_lds = son_lds + ROWS;                       // [H] output weights of the slowdown unit
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hh = lane >> 5, nn = lane & 31;
+    float *b2_lds = (float *)(lds4) + H * H;
+    float *w3_lds = b2_lds + H;
+    float *wsm_lds = w3_lds + H;                           // [H] layer-1 weights of the SM share
+    float *w3s_lds = wsm_lds + H;                          // [H] output weights of the slowdown unit
+    unsigned long long *scored_lds = (unsigned long long *)(w3s_lds + H);  // pairs the workgroup has scored
+    int *ended_lds = (int *)(scored_lds + 1);              // its wavefronts that are done
+    float *pon_lds = w3s_lds + H + 4 + wave * S::WAVE_FLOATS;  // this wavefront's own: [ROWS][H] projections,
+    float *mon_lds = pon_lds + ROWS * H;                   // [ROWS] memory fractions and
+    float *son_lds = mon_lds + ROWS;                       // [ROWS] 1 - SM activities of its rows
+
     int staged_row0 = 0;                    // where the row map's entry 0 sits in the staged matrix
     if (segment) {                          // only entries [segment[0], segment[1]) of the row map
         row_map += segment[0];
         staged_row0 = segment[0];
         n = segment[1] - segment[0];
     }
-    // consecutive workgroups (which the hardware deals out to the eight XCDs in turn) share one
-    // tile of offline columns and walk down the online rows, so that tile stays in every L2
-    // and each XCD keeps re-reading the same eighth of the online projections
-    // The row tile also shifts by one per column tile: in memory order the tiles with work
-    // are the first so-many of each column tile, and without the shift the low XCDs would
-    // collect the odd one out every time.
-    const int row0 = (int)((blockIdx.x + blockIdx.y) % gridDim.x) * tile_rows;
-    if (row0 >= n) return;                  // the grid's x extent is padded to a multiple of eight
-    const int nrows = min(tile_rows, n - row0);
-    const int j0 = (blockIdx.y * PAIR_WAVES + wave) * 32;
-    // in memory order the tile's first row and first column are its smallest: if they do not
-    // fit together, nothing in the tile does
-    if (by_memory && mem_on[row_map[row0]] + mem_off[col_map[blockIdx.y * PAIR_COLS]] > mem_limit) return;
-
     // SPLIT: the powers of two that scale layer-1 values and W2 into fp16's comfortable range
     float scale_p = 1.0f, scale_w = 1.0f;
     if (SPLIT) {
@@ -484,7 +489,7 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
     }
     const float scale_acc = scale_p * scale_w, unscale_acc = 1.0f / scale_acc;
     if (SPLIT) {
-        for (int idx = tid; idx < MB * KB * 64; idx += PAIR_THREADS) {
+        for (int idx = tid; idx < MB * KB * 64; idx += S::THREADS) {
             const int ln = idx & 63, kb = (idx >> 6) % KB, mb = idx / (64 * KB);
             const float *src = W2 + (size_t)(mb * 32 + (ln & 31)) * H + (ln >> 5) * KS + kb * 8;
             const float4 w0 = *(const float4 *)src, w1 = *(const float4 *)(src + 4);
@@ -501,46 +506,23 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
             a16_lds[((MB + mb) * KB + kb) * 64 + ln] = lo.q;
         }
     } else {
-        for (int idx = tid; idx < MB * Q * 64; idx += PAIR_THREADS) {
+        for (int idx = tid; idx < MB * Q * 64; idx += S::THREADS) {
             int ln = idx & 63, s4 = (idx >> 6) % Q, mb = idx / (64 * Q);
             a_lds[idx] = *(const float4 *)(W2 + (size_t)(mb * 32 + (ln & 31)) * H + (ln >> 5) * KS + s4 * 4);
         }
     }
-    for (int idx = tid; idx < nrows * (H / 4); idx += PAIR_THREADS) {
-        const int r = idx / (H / 4), q = idx % (H / 4);
-        const int gi = row_map ? row_map[row0 + r] : row0 + r;
-        float4 v = ((const float4 *)(P_on + (size_t)gi * H))[q];
-        if (SPLIT) { v.x *= scale_p; v.y *= scale_p; v.z *= scale_p; v.w *= scale_p; }
-        ((float4 *)pon_lds)[idx] = v;
-    }
     if (tid < H) { b2_lds[tid] = b2[tid] * scale_acc; w3_lds[tid] = W3[tid] * unscale_acc; }
-    if (tid < nrows) mon_lds[tid] = mem_on[row_map ? row_map[row0 + tid] : row0 + tid];
-    if (PAIR_SM) {
-        if (tid < H) wsm_lds[tid] = w_sm[tid] * scale_p;
-        if (tid < nrows) son_lds[tid] = 1.0f - sm_on[row_map ? row_map[row0 + tid] : row0 + tid];
-    }
+    if (tid == 0) { *scored_lds = 0ull; *ended_lds = 0; }
+    if (PAIR_SM && tid < H) wsm_lds[tid] = w_sm[tid] * scale_p;
     if (SLOWDOWN && tid < H) w3s_lds[tid] = w3_slow[tid] * unscale_acc;
     __syncthreads();
-    if (j0 >= m) return;
 
-    const int j = j0 + nn;
-    const int jc = col_map ? col_map[min(j, m - 1)] : min(j, m - 1);     // the column this lane scores
-    float poff[KS];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        float4 t = *(const float4 *)(P_off + (size_t)jc * H + hh * KS + q * 4);
-        poff[4 * q] = t.x * scale_p; poff[4 * q + 1] = t.y * scale_p; poff[4 * q + 2] = t.z * scale_p; poff[4 * q + 3] = t.w * scale_p;
-    }
-    const float moff = mem_off[jc];
-    const float soff = PAIR_SM ? sm_off[jc] : 0.0f;
+    // what the wavefront's lanes keep of their column while they walk down a task's rows
+    float poff[KS], moff = 0.0f, soff = 0.0f;
+    int j = 0, jc = 0, row0 = 0;
     const float bias3 = b3[0];
     const float bias3_slow = SLOWDOWN ? b3_slow[0] : 0.0f;
-    // by_memory: the maps list rows and columns by ascending memory fraction, so this
-    // wavefront's first column has its smallest one, and once a row does not fit next to
-    // that column (float addition is monotone) no later row of the tile fits any of its columns
-    const float moff_least = by_memory ? __shfl(moff, 0) : 0.0f;
-
-    // NR rows of the tile at once against this wavefront's 32 columns.  Two rows share every
+    // NR of the wavefront's rows at once against this wavefront's 32 columns.  Two rows share every
     // W2 operand fetched from LDS and give the matrix pipe two independent accumulator sets.
     auto score_rows = [&](auto nr_tag, auto split_tag, const int r) {
         constexpr int NR = decltype(nr_tag)::value;
@@ -769,33 +751,112 @@ __global__ __launch_bounds__(PAIR_THREADS) void pair_mlp_kernel(
         }
     };
 
-    int r = 0;
-    while (r < nrows) {
-        // W2 does not fit in registers next to the accumulators: keep its loads inside the row loop
-        asm volatile("" ::: "memory");
-        if (by_memory && mon_lds[r] + moff_least > mem_limit) break;
-        const bool pair_of_rows = r + 1 < nrows && !(by_memory && mon_lds[r + 1] + moff_least > mem_limit);
-        if (pair_of_rows) { score_rows(std::integral_constant<int, 2>{}, std::integral_constant<bool, SPLIT>{}, r); r += 2; }
-        else { score_rows(std::integral_constant<int, 1>{}, std::integral_constant<bool, SPLIT>{}, r); r += 1; }
+    const int chunks = (n + task_rows - 1) / task_rows, blocks = (m + 31) / 32;
+    // Tasks are dealt out in turn to `queues` groups of workgroups, each with a counter of its own: the first ones by
+    // the wavefront's place, then whoever is done takes the group's next.  (Two thousand wavefronts that end together at
+    // one counter waited 20 us for it: 1024 x 1024 54 / 44 us.)  By rows first, so that the two thousand
+    // tasks under way share a few rows' projections and every row of the matrix is written within a short time.
+    const int queues = (int)gridDim.x < PAIR_QUEUES ? 1 : PAIR_QUEUES, queue = blockIdx.x % queues;
+    const int team = ((int)gridDim.x - queue + queues - 1) / queues;       // workgroups of this one's group
+    int task = queue + queues * (int)(blockIdx.x / queues + team * wave), chunk = 0, before = 0;   // (before: tasks of earlier chunks)
+    unsigned long long scored = 0;
+    while (true) {
+        int block;
+        if (by_memory) {
+            // a chunk of rows has as many tasks as blocks of columns fit its first row: a prefix of them
+            int had = 0;
+            unsigned long long beyond = 0;
+            for (; chunk < chunks; chunk += 64, before += had) {
+                const int c = chunk + lane;
+                const int mine = c < chunks ? (fit_len[staged_row0 + c * task_rows] + 31) >> 5 : 0;
+                int upto = mine;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) { const int o = __shfl_up(upto, off); if (lane >= off) upto += o; }
+                beyond = __ballot(before + upto > task);
+                if (beyond) {
+                    const int at = __builtin_ctzll(beyond);
+                    before += __builtin_amdgcn_readfirstlane(__shfl(upto - mine, at));
+                    chunk += at;
+                    break;
+                }
+                had = __builtin_amdgcn_readfirstlane(__shfl(upto, 63));
+            }
+            if (!beyond) break;
+            block = task - before;
+        } else {
+            if (task >= chunks * blocks) break;
+            chunk = task / blocks;
+            block = task % blocks;
+        }
+        row0 = chunk * task_rows;
+        const int j0 = block * 32, rows = min(task_rows, n - row0);
+        j = j0 + nn;
+        jc = col_map ? col_map[min(j, m - 1)] : min(j, m - 1);             // the column this lane scores
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            float4 t = *(const float4 *)(P_off + (size_t)jc * H + hh * KS + q * 4);
+            poff[4 * q] = t.x * scale_p; poff[4 * q + 1] = t.y * scale_p; poff[4 * q + 2] = t.z * scale_p; poff[4 * q + 3] = t.w * scale_p;
+        }
+        moff = mem_off[jc];
+        soff = PAIR_SM ? sm_off[jc] : 0.0f;
+        // by_memory: the maps list rows and columns by ascending memory fraction, so this
+        // wavefront's first column has its smallest one, and once a row does not fit next to
+        // that column (float addition is monotone) no later row of the chunk fits any of its columns
+        const float moff_least = by_memory ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(moff))) : 0.0f;
+        int done = 0;
+        while (done < rows) {
+            const int here = min(ROWS, rows - done);
+            // LDS instructions of one wavefront are carried out in order; the compiler has to keep them so
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int idx = lane; idx < here * (H / 4); idx += 64) {
+                const int at = row0 + idx / (H / 4), gi = row_map ? row_map[at] : at;
+                float4 v = ((const float4 *)(P_on + (size_t)gi * H))[idx % (H / 4)];
+                if (SPLIT) { v.x *= scale_p; v.y *= scale_p; v.z *= scale_p; v.w *= scale_p; }
+                ((float4 *)pon_lds)[idx] = v;
+            }
+            bool out = true;
+            if (lane < here) {
+                const int gi = row_map ? row_map[row0 + lane] : row0 + lane;
+                const float mon = mem_on[gi];
+                mon_lds[lane] = mon;
+                if (PAIR_SM) son_lds[lane] = 1.0f - sm_on[gi];
+                out = by_memory && mon + moff_least > mem_limit;
+            }
+            const int fit = __builtin_ctzll(__ballot(out));                // (lanes from ROWS on are out)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int r = 0; r < fit;) {
+                // W2 does not fit in registers next to the accumulators: keep its loads inside the row loop
+                asm volatile("" ::: "memory");
+                if (r + 1 < fit) { score_rows(std::integral_constant<int, 2>{}, std::integral_constant<bool, SPLIT>{}, r); r += 2; }
+                else { score_rows(std::integral_constant<int, 1>{}, std::integral_constant<bool, SPLIT>{}, r); r += 1; }
+            }
+            done += fit;
+            row0 += fit;
+            if (fit < here) break;          // (what rows left out have here lies beyond their feasible prefixes and is never read)
+        }
+        scored += (unsigned long long)done * (unsigned)min(32, m - j0);
+        int taken = 0;
+        if (lane == 0) taken = atomicAdd(next_task + queue * PAIR_QUEUE_STEP, 1);
+        task = queue + queues * (team * S::WAVES + __builtin_amdgcn_readfirstlane(taken));
     }
-    // (what rows the loop left early have here lies beyond their feasible prefixes and is never read)
-    if (evaluated && lane == 0 && r > 0) atomicAdd(evaluated, (unsigned long long)r * (unsigned)min(32, m - j0));
+    if (lane == 0) {                        // the workgroup's last wavefront adds for all
+        atomicAdd(scored_lds, scored);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        if (atomicAdd(ended_lds, 1) == S::WAVES - 1) atomicAdd(evaluated, atomicAdd(scored_lds, 0ull));
+    }
 }
 
-// Rows per workgroup.  A workgroup costs its set-up (W2's pieces, the columns' projections), about as long as
-// PAIR_SETUP_ROWS rows, and its rows; a compute unit holds one at a time (H = 128), so a launch lasts as long as
-// ceil(workgroups / units) of them.  The 64 rows that share one set-up best are halved while that gets
-// shorter: a 64 x 64 round is otherwise scored by one workgroup and a 1024 x 1024 one by 64.  With 64 rows
-// always / with this rule: 64 x 64 97 / 37 us for the whole pass, 1024 x 1024 123 / 76, 777 x 1501 290 / 175,
-// 3001 x 2003 726 / 622; 4096 x 8192 and larger keep 64.
-constexpr int PAIR_SETUP_ROWS = 8;
-int pair_tile_rows(int rows, int column_tiles, int units)
+// Rows of a task.  A task costs its columns' projections and a few dependent reads, about as long as PAIR_SETUP_ROWS
+// rows, so it has 64 rows where there are enough tasks, and half as many while the wavefronts that take the most of
+// them are done earlier so: 2 rows for 64 x 64 pairs, 8 for 777 x 1501, 64 from 4096 x 8192 on.
+constexpr int PAIR_SETUP_ROWS = 2;
+int pair_task_rows(int rows, int blocks, int waves)
 {
     int best = 64;
     long long least = -1;
-    for (int t = 64; t >= 8; t >>= 1) {
-        const long long workgroups = (long long)((rows + t - 1) / t) * column_tiles;
-        const long long work = (workgroups + units - 1) / (units > 0 ? units : 1) * (t + PAIR_SETUP_ROWS);
+    for (int t = 64; t >= 2; t >>= 1) {
+        const long long tasks = (long long)((rows + t - 1) / t) * blocks;
+        const long long work = (tasks + waves - 1) / waves * (t + PAIR_SETUP_ROWS);
         if (least < 0 || work < least) { least = work; best = t; }
     }
     return best;
@@ -804,7 +865,7 @@ int pair_tile_rows(int rows, int column_tiles, int units)
 template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
 int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, int64_t ldw,
                         float *d_sigma, const int32_t *row_map, const int32_t *col_map, bool by_memory,
-                        const int32_t *segment, int grid_rows, unsigned long long *times)
+                        const int32_t *segment, int grid_rows, int launch, unsigned long long *times)
 {
     using S = PairShape<H>;
     // (the attribute belongs to the device, so what has been set is remembered per context)
@@ -814,15 +875,16 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES));
         ctx->kernels_configured |= flag;
     }
-    // x covers the rows this launch scores (a segment of the row map, or all n), padded to a
-    // multiple of 8: every XCD then meets the same row tiles for each column tile
-    const int column_tiles = (m + PAIR_COLS - 1) / PAIR_COLS, tile_rows = pair_tile_rows(grid_rows, column_tiles, ctx->n_cus);
-    dim3 grid((((grid_rows + tile_rows - 1) / tile_rows) + 7) & ~7, column_tiles);
-    hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(PAIR_THREADS), S::LDS_BYTES, ctx->stream,
+    const int blocks = (m + 31) / 32, units = ctx->n_cus > 0 ? ctx->n_cus : 1;
+    const int task_rows = pair_task_rows(grid_rows, blocks, units * S::PER_UNIT * S::WAVES);
+    const long long tasks = (long long)((grid_rows + task_rows - 1) / task_rows) * blocks;
+    const dim3 grid((unsigned)(tasks < units * S::PER_UNIT ? tasks : units * S::PER_UNIT));
+    hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(S::THREADS), S::LDS_BYTES, ctx->stream,
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
-                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, tile_rows, times);
+                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, task_rows, by_memory ? ctx->fit_len_on : nullptr,
+                       ctx->score_queue + launch * PAIR_QUEUES * PAIR_QUEUE_STEP, times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
@@ -830,12 +892,12 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
 template <int H>
 int launch_pair(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_t *d_W, int64_t ldw,
                 float *d_sigma, const int32_t *row_map, const int32_t *col_map, bool by_memory,
-                unsigned long long *times, const int32_t *segment = nullptr, int segment_rows = -1)
+                unsigned long long *times, int launch, const int32_t *segment = nullptr, int segment_rows = -1)
 {
     const int grid_rows = segment_rows >= 0 ? segment_rows : n;
     const int which = (p->d_W1sm ? 4 : 0) + (p->d_W3_slow ? 2 : 0) + (ctx->score_split ? 1 : 0);
 #define MF_PAIR_CASE(SM, SLOW, SPL) \
-    return launch_pair_variant<H, SM, SLOW, SPL>(ctx, p, n, m, d_W, ldw, d_sigma, row_map, col_map, by_memory, segment, grid_rows, times)
+    return launch_pair_variant<H, SM, SLOW, SPL>(ctx, p, n, m, d_W, ldw, d_sigma, row_map, col_map, by_memory, segment, grid_rows, launch, times)
     switch (which) {
     case 0: MF_PAIR_CASE(false, false, false);
     case 1: MF_PAIR_CASE(false, false, true);
@@ -866,7 +928,7 @@ void launch_projections(mf_ctx *ctx, const mf_predictor *p, const float *d_on, i
     hipLaunchKernelGGL(project_kernel, dim3(tiles + PROJECT_EXTRA, p->H / 64), dim3(256), 0, ctx->stream, a);
 }
 
-SetupArgs setup_args(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int n, const float *d_off, int m)
+SetupArgs setup_args(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int n, const float *d_off, int m, int launches)
 {
     SetupArgs a{};
     a.X[0] = d_on; a.X[1] = d_off;
@@ -879,6 +941,7 @@ SetupArgs setup_args(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int 
     a.mem_limit = p->mem_limit;
     a.pairs_evaluated = ctx->pairs_evaluated;
     a.range = ctx->score_range;
+    a.queue = ctx->score_queue; a.launches = launches;
     a.times = ctx->times;
     return a;
 }
@@ -936,7 +999,7 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     const int64_t lds = ((int64_t)m + 3) & ~3ll;
     // (each of these is a few microseconds of work: as eight launches, not twenty-two, the set-up of a
     // 64 x 64 round takes 31 us, not 310)
-    SetupArgs a = setup_args(ctx, p0, d_on, n, d_off, m);
+    SetupArgs a = setup_args(ctx, p0, d_on, n, d_off, m, n_types);
     a.largest = ctx->largest_weight;
     ctx->largest_weight_known = false;
     a.group = d_type;
@@ -990,8 +1053,8 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
         const int32_t *segment = typed ? ctx->type_segment + t : nullptr;
         const int segment_rows = typed ? type_first[t + 1] - type_first[t] : -1;
         if (segment_rows == 0) continue;                                   // no workload of this type
-        int rc = (H == 64) ? launch_pair<64>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, segment, segment_rows)
-                           : launch_pair<128>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, segment, segment_rows);
+        int rc = (H == 64) ? launch_pair<64>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, t, segment, segment_rows)
+                           : launch_pair<128>(ctx, p, n, m, out, ldo, d_sigma, rmap, cmap, by_memory, times, t, segment, segment_rows);
         times = nullptr;                                                   // (later types' projections count as scoring)
         if (rc != MF_OK) return rc;
     }
@@ -1047,18 +1110,18 @@ int mf_launch_rescore(mf_ctx *ctx, const mf_predictor *p, const float *d_on, int
     int rc = mf_send_and_await(ctx, mf_report{{{ctx->colmark, ctx->h_bad, 1}}});
     if (rc != MF_OK) return rc;
     if (*ctx->h_bad) return MF_ERR_ARG;
-    const SetupArgs a = setup_args(ctx, p, d_on, n, d_off, m);
+    const SetupArgs a = setup_args(ctx, p, d_on, n, d_off, m, 2);
     hipLaunchKernelGGL(setup_kernel, dim3(((n > m ? n : m) + 255) / 256, 2), dim3(256), 0, ctx->stream, a);
     launch_projections(ctx, p, d_on, n, d_off, m);          // of everybody, and so the range, as in a full scoring pass
     MF_HIP(hipGetLastError());
     ctx->pairs_total = (double)n_rows * (double)m + (double)n * (double)n_cols;
     if (n_rows == 0 && n_cols == 0) mf_note_time(ctx, AT_PAIRS);
     if (n_rows > 0)
-        rc = (H == 64) ? launch_pair<64>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times)
-                       : launch_pair<128>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times);
+        rc = (H == 64) ? launch_pair<64>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times, 0)
+                       : launch_pair<128>(ctx, p, n_rows, m, d_W, ldw, nullptr, d_rows, nullptr, false, ctx->times, 0);
     if (rc == MF_OK && n_cols > 0)
-        rc = (H == 64) ? launch_pair<64>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times)
-                       : launch_pair<128>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times);
+        rc = (H == 64) ? launch_pair<64>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times, 1)
+                       : launch_pair<128>(ctx, p, n, n_cols, d_W, ldw, nullptr, nullptr, d_cols, false, n_rows > 0 ? nullptr : ctx->times, 1);
     if (rc != MF_OK) return rc;
     ctx->score_placed = false;
     ctx->score_pending = true;

@@ -62,13 +62,31 @@ def test_scores_match_checker(mm, orc, cfg, n, m):
                                  (2049, 31), (2500, 1030), (1, 70000)])
 @pytest.mark.parametrize("cfg", ["C2", "C3"])
 def test_scores_at_the_edges_of_row_tiles(mm, orc, cfg, n, m):
-    """A workgroup scores 8 to 64 rows, chosen by the shape, two rows at a time: remainders of either."""
+    """A task has 2 to 64 rows, chosen by the shape, scored two at a time: remainders of either."""
     r = synth.scheduling_round(cfg, 3, n=n, m=m)
     ctx = mm.Context(n, m)
     Wg, sg = _score_on_gpu(mm, ctx, r)
     _compare(orc, r, Wg, sg)
     ordered, _ = _score_on_gpu(mm, ctx, r, want_sigma=False)
     assert (ordered == Wg).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("cfg", ["C2", "C5"])
+@pytest.mark.parametrize("n,m", [(2, 33), (30, 31), (33, 480), (130, 9000), (4200, 65), (9000, 36), (5000, 1100)])
+def test_scores_of_tasks(mm, orc, cfg, n, m):
+    """Wavefronts take tasks of 2 to 64 rows beside 32 columns: fewer tasks than groups that share a counter, fewer
+    and more than wavefronts, one column block, more chunks of rows than lanes look at in one step, and chunks
+    that have no task because nothing fits their first row; passes on one context are the same to the bit."""
+    r = synth.scheduling_round(cfg, 5, n=n, m=m)
+    ctx = mm.Context(n, m)
+    Wg, sg = _score_on_gpu(mm, ctx, r)
+    _compare(orc, r, Wg, sg)
+    for _ in range(2):
+        ordered, _ = _score_on_gpu(mm, ctx, r, want_sigma=False)
+        assert (ordered == Wg).all()
+        fits = float((Wg != INF).mean())                # whole blocks of columns are scored beside their rows: at least what fits
+        assert fits <= ctx.last_timings()["pairs_evaluated_fraction"] + 1e-6 <= 1.0 + 2e-6
     ctx.close()
 
 
