@@ -16,6 +16,7 @@
 #include <type_traits>
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 union Half8Words { half8 v; unsigned int u[4]; uint4 q; };
 
@@ -317,22 +318,15 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
     const int32_t *src = S + (size_t)from * lds;
     int32_t *row = W + (size_t)i * ldw;
     int mx = 0;                                             // "cannot share" is the smallest integer
-    for (int j = (blockIdx.y * 256 + threadIdx.x) * 4; j < m; j += gridDim.y * 1024) {
-        int32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int p = rank_off[min(j + e, m - 1)];
-            w[e] = j + e < m ? (p < len ? src[p] : MF_INFEASIBLE) : 0;
-            mx = max(mx, w[e]);
-        }
-        if (wide_stores && j + 3 < m) {
-            *(int4 *)(row + j) = make_int4(w[0], w[1], w[2], w[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (j + e < m) row[j + e] = w[e];
-        }
+    auto entry = [&](int p) { const int32_t w = p < len ? src[p] : MF_INFEASIBLE; mx = max(mx, w); return w; };
+    const int whole = m & ~3;
+    for (int j = (blockIdx.y * 256 + threadIdx.x) * 4; j < whole; j += gridDim.y * 1024) {
+        const int4 p = *(const int4 *)(rank_off + j);
+        const int4 w = make_int4(entry(p.x), entry(p.y), entry(p.z), entry(p.w));
+        if (wide_stores) *(int4 *)(row + j) = w;
+        else { row[j] = w.x; row[j + 1] = w.y; row[j + 2] = w.z; row[j + 3] = w.w; }
     }
+    if (blockIdx.y == 0 && whole + (int)threadIdx.x < m) row[whole + threadIdx.x] = entry(rank_off[whole + threadIdx.x]);
     note_largest<256>(mx, largest);
 }
 
@@ -342,7 +336,9 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
 // in whole lines: no scattered access reaches the caches.  LDS takes PLACE_LDS_ENTRIES of a row, so that a
 // compute unit has two workgroups, one storing while the other loads; what a longer prefix has beyond that is
 // picked out of the caches (20,000 x 40,000 with prefixes of 4000 entries on average: 1.16 ms with LDS for whole rows
-// and one workgroup a compute unit, 1.06 so).
+// and one workgroup a compute unit, 1.06 so).  What bounds it is storing the row (3.2 GB there), if the entries' places are
+// read by fours and the reads of four steps are on their way together: 1.06 -> 0.67 ms, 20,000 x 20,000 0.66 -> 0.55, when they were read
+// one by one and waited for in every step.
 constexpr int PLACE_THREADS = 1024, PLACE_LDS_ENTRIES = 79 * 256;
 constexpr int64_t PLACE_LONGEST = 40704;                  // columns up to which this is used (beyond, the kernel above)
 
@@ -365,21 +361,17 @@ __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
         mx = max(max(mx, max(v.x, v.y)), max(v.z, v.w));
     }
     note_largest<PLACE_THREADS>(mx, largest);               // passes a barrier: the staged row is complete
-    for (int j = tid * 4; j < m; j += PLACE_THREADS * 4) {
-        int32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int p = rank_off[min(j + e, m - 1)];
-            w[e] = j + e < m ? (p < len ? (p < PLACE_LDS_ENTRIES ? staged[p] : src[p]) : MF_INFEASIBLE) : 0;
-        }
-        if (wide_stores && j + 3 < m) {
-            *(int4 *)(row + j) = make_int4(w[0], w[1], w[2], w[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (j + e < m) row[j + e] = w[e];
-        }
+    auto entry = [&](int p) { return p < len ? (p < PLACE_LDS_ENTRIES ? staged[p] : src[p]) : MF_INFEASIBLE; };
+    const int whole = m & ~3;
+#pragma unroll 4
+    for (int j = tid * 4; j < whole; j += PLACE_THREADS * 4) {
+        const int4 p = *(const int4 *)(rank_off + j);
+        const intx4 w = {entry(p.x), entry(p.y), entry(p.z), entry(p.w)};
+        if (wide_stores == 2) __builtin_nontemporal_store(w, (intx4 *)(row + j));
+        else if (wide_stores) *(intx4 *)(row + j) = w;
+        else { row[j] = w.x; row[j + 1] = w.y; row[j + 2] = w.z; row[j + 3] = w.w; }
     }
+    if (whole + tid < m) row[whole + tid] = entry(rank_off[whole + tid]);
 }
 
 __global__ void fill_flag_kernel(int *flag) { *flag = 0; }
@@ -1060,7 +1052,10 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     }
     if (by_memory) {
         const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
-        const int wide = ((uintptr_t)d_W & 15u) == 0 && (ldw & 3) == 0;
+        // 0: entry by entry; 1: by fours; 2: by fours and past the caches, for a matrix that does not stay in the last one until
+        // it is read (256 MB): 20,000 x 40,000 0.72 / 0.67 ms, 20,000 x 20,000 0.57 / 0.55
+        int wide = ((uintptr_t)d_W & 15u) == 0 && (ldw & 3) == 0;
+        if (wide && (int64_t)n * ldw * 4 > (256ll << 20)) wide = 2;
         if (lds <= PLACE_LONGEST) {
             hipLaunchKernelGGL(place_lds_kernel, dim3(n), dim3(PLACE_THREADS), 0, ctx->stream,
                                ctx->staged, lds, ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide,

@@ -90,6 +90,29 @@ def test_scores_of_tasks(mm, orc, cfg, n, m):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,m,pad,shift", [(130, 517, 4, 0), (130, 517, 1, 0), (130, 518, 4, 1), (40, 20227, 4, 0), (40, 40703, 4, 0), (40, 40707, 4, 0),
+                                           (40, 40707, 1, 3), (1700, 40703, 4, 0), (70000, 1001, 4, 0)])
+def test_entries_come_to_their_places(mm, n, m, pad, shift):
+    """Scored in memory order and put in place, or scored as they come: the same matrix.  Rows that end in a part of a
+    group, pitches and starts that are not whole groups, rows longer than what LDS takes of them and than the
+    kernel with LDS takes, and matrices beyond the last-level cache, which are stored past it."""
+    r = synth.scheduling_round("C2", 9, n=n, m=m)
+    pitch = (m + pad - 1) // pad * pad
+    ctx = mm.Context(n, m)
+    pred = ctx.predictor(dev_params(r["params"]), r["cfg"].scale)
+    x_on, x_off, got = dev(r["x_on"]), dev(r["x_off"]), []
+    for order in (0, 1):
+        ctx.set_option("fit_order", order)
+        buffer = torch.full((n * pitch + 8,), -7, dtype=torch.int32, device="cuda")
+        W = buffer[shift:shift + n * pitch].view(n, pitch)
+        ctx.score_pairs(pred, x_on, x_off, W)
+        torch.cuda.synchronize()
+        got.append(buffer)
+    assert torch.equal(got[0], got[1])
+    assert bool((got[1][shift:shift + n * pitch].view(n, pitch)[:, m:] == -7).all()) and bool((got[1][shift + n * pitch:] == -7).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("case", ["huge projections", "tiny hidden weights", "huge hidden weights", "mixed magnitudes",
                                   "zero hidden layer"])
 def test_scores_do_not_depend_on_the_size_of_the_numbers(mm, orc, case):
