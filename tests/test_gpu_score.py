@@ -113,6 +113,33 @@ def test_entries_come_to_their_places(mm, n, m, pad, shift):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,m,types", [(12288, 100, 1), (300, 14337, 1), (13000, 12500, 3), (16385, 65, 64), (12287, 70, 2)])
+def test_many_workloads_in_memory_order(mm, n, m, types):
+    """From 12,288 workloads on a side they are sorted in stretches of 2048, not counted: stretches that end early, many
+    equal memory fractions, and types to order by first.  The matrix is that scored as it comes, and little
+    beyond the pairs that fit (a tenth) went through the predictor, as in order of memory."""
+    r = synth.scheduling_round("C5", 11, n=n, m=m)
+    for x in (r["x_on"], r["x_off"]):
+        x[:, 0] = np.round(x[:, 0] * 64) / 64
+    ctx = mm.Context(n, m)
+    pred = ctx.predictor(dev_params(r["params"]), 2.0 ** 24)
+    x_on, x_off, got = dev(r["x_on"]), dev(r["x_off"]), []
+    kind = dev(synth.gpu_types(11, n, types))
+    for order in (0, 1):
+        ctx.set_option("fit_order", order)
+        W = empty_matrix(n, m)
+        if types > 1:
+            ctx.score_pairs_typed([pred] * types, kind, x_on, x_off, W)
+        else:
+            ctx.score_pairs(pred, x_on, x_off, W)
+        torch.cuda.synchronize()
+        got.append(W)
+    assert torch.equal(got[0], got[1])
+    fits = float((got[0][:, :m] != int(INF)).float().mean())
+    assert fits <= ctx.last_timings()["pairs_evaluated_fraction"] + 1e-6 <= 2 * fits + 0.1
+    ctx.close()
+
+
 @pytest.mark.parametrize("case", ["huge projections", "tiny hidden weights", "huge hidden weights", "mixed magnitudes",
                                   "zero hidden layer"])
 def test_scores_do_not_depend_on_the_size_of_the_numbers(mm, orc, case):
