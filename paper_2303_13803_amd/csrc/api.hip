@@ -219,7 +219,7 @@ int mf_create(mf_ctx **out, int device, void *hip_stream, int max_n, int max_m)
     TRY(dev_alloc(&ctx->stats, 1));
     TRY(dev_alloc(&ctx->cert, MF_CERT_PARTS));
     TRY(hipMalloc((void **)&ctx->score_range, 8 * sizeof(unsigned)));
-    TRY(hipMalloc((void **)&ctx->score_queue, MF_MAX_TYPES * 256 * sizeof(int)));
+    TRY(hipMalloc((void **)&ctx->score_queue, MF_MAX_TYPES * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP * sizeof(int)));
     TRY(hipHostMalloc((void **)&ctx->h_stats, sizeof(mf_device_stats)));
     for (int i = 0; i < 2; ++i) {
         TRY(hipHostMalloc((void **)&ctx->h_stats_slot[i], sizeof(mf_device_stats)));

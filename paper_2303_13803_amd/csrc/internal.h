@@ -90,6 +90,8 @@ struct alignas(128) mf_cert_out {   // lives in device memory, cleared per check
 
 // A check adds up in so many parts: workgroups that finish together would queue up behind atomics on one line.
 constexpr int MF_CERT_PARTS = 16;
+// Counters of a launch of the pair kernel (score.hip), and words from one to the next: a line of 128 bytes each.
+constexpr int MF_PAIR_QUEUES = 16, MF_PAIR_QUEUE_STEP = 32;
 // (one thread clears a part)
 __host__ __device__ inline void mf_clear_part(mf_cert_out *o) { o->primal = 0; o->dual = 0; o->min_rc = INT64_MAX; o->matched = 0; o->flags = 0; }
 __host__ __device__ inline mf_cert_out mf_sum_parts(const mf_cert_out *o)
@@ -230,7 +232,7 @@ struct mf_ctx : mf_options {
     int *h_bad;                         // pinned: an index or a type was out of range
     mf_told *h_told;
     unsigned reports;                   // sent so far
-    int *score_queue;                   // device: next tasks of the pair kernel's launches, 16 counters each, a cache line apart
+    int *score_queue;                   // device: next tasks of the pair kernel's launches, one a type, MF_PAIR_QUEUES counters each
     unsigned *score_range;              // device: largest magnitudes the scorer's fp16 pieces are scaled by (project_kernel)
     mf_cert_out *h_cert;
     // timing

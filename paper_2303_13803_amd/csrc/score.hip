@@ -117,8 +117,6 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
     if (a.range) note_range(mx, &a.range[side], wave_mx);
 }
 
-constexpr int PAIR_QUEUES = 16, PAIR_QUEUE_STEP = 16;      // counters of a launch, one a cache line
-
 // What is prepared per workload before anything is ordered: its memory fraction and SM share, its rank
 // (zero), and the words later kernels of the call count or take maxima in.
 struct SetupArgs {
@@ -147,7 +145,7 @@ __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
     note_time(a.times, AT_SCORE);
     const int side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
     if (side == 0 && blockIdx.x == 0)
-        for (int q = r; q < a.launches * PAIR_QUEUES; q += 256) a.queue[q * PAIR_QUEUE_STEP] = 0;
+        for (int q = r; q < a.launches * MF_PAIR_QUEUES; q += 256) a.queue[q * MF_PAIR_QUEUE_STEP] = 0;
     if (side == 0 && r < 8) {
         a.range[r] = 0u;
         if (r == 0) { *a.pairs_evaluated = 0ull; if (a.feasible_pairs) *a.feasible_pairs = 0ull; if (a.largest) *a.largest = 0; }
@@ -801,7 +799,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     // the wavefront's place, then whoever is done takes the group's next.  (Two thousand wavefronts that end together at
     // one counter waited 20 us for it: 1024 x 1024 54 / 44 us.)  By rows first, so that the two thousand
     // tasks under way share a few rows' projections and every row of the matrix is written within a short time.
-    const int queues = (int)gridDim.x < PAIR_QUEUES ? 1 : PAIR_QUEUES, queue = blockIdx.x % queues;
+    const int queues = (int)gridDim.x < MF_PAIR_QUEUES ? 1 : MF_PAIR_QUEUES, queue = blockIdx.x % queues;
     const int team = ((int)gridDim.x - queue + queues - 1) / queues;       // workgroups of this one's group
     int task = queue + queues * (int)(blockIdx.x / queues + team * wave), chunk = 0, before = 0;   // (before: tasks of earlier chunks)
     unsigned long long scored = 0;
@@ -881,7 +879,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         }
         scored += (unsigned long long)done * (unsigned)min(32, m - j0);
         int taken = 0;
-        if (lane == 0) taken = atomicAdd(next_task + queue * PAIR_QUEUE_STEP, 1);
+        if (lane == 0) taken = atomicAdd(next_task + queue * MF_PAIR_QUEUE_STEP, 1);
         task = queue + queues * (team * S::WAVES + __builtin_amdgcn_readfirstlane(taken));
     }
     if (lane == 0) {                        // the workgroup's last wavefront adds for all
@@ -929,7 +927,7 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
                        p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, task_rows, by_memory ? ctx->fit_len_on : nullptr,
-                       ctx->score_queue + launch * PAIR_QUEUES * PAIR_QUEUE_STEP, times);
+                       ctx->score_queue + launch * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP, times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
