@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <tuple>
 #include "muxmatch.h"
+#include "pair_tasks.h"
 #include "side_end.h"
 
 #define MF_HIP(call)                                                            \
@@ -90,8 +91,6 @@ struct alignas(128) mf_cert_out {   // lives in device memory, cleared per check
 
 // A check adds up in so many parts: workgroups that finish together would queue up behind atomics on one line.
 constexpr int MF_CERT_PARTS = 16;
-// Counters of a launch of the pair kernel (score.hip), and words from one to the next: a line of 128 bytes each.
-constexpr int MF_PAIR_QUEUES = 16, MF_PAIR_QUEUE_STEP = 32;
 // (one thread clears a part)
 __host__ __device__ inline void mf_clear_part(mf_cert_out *o) { o->primal = 0; o->dual = 0; o->min_rc = INT64_MAX; o->matched = 0; o->flags = 0; }
 __host__ __device__ inline mf_cert_out mf_sum_parts(const mf_cert_out *o)

@@ -492,8 +492,8 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     unsigned long long *__restrict__ evaluated, const int32_t *__restrict__ segment,
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
-    const unsigned *__restrict__ range, int task_rows, const int32_t *__restrict__ fit_len, int *__restrict__ next_task,
-    unsigned long long *times)
+    const unsigned *__restrict__ range, float units, const unsigned long long *__restrict__ feasible, const int32_t *__restrict__ fit_len,
+    int *__restrict__ next_task, unsigned long long *times)
 {
     note_time(times, AT_PAIRS);
     using S = PairShape<H>;
@@ -513,6 +513,9 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     float *mon_lds = pon_lds + ROWS * H;                   // [ROWS] memory fractions and
     float *son_lds = mon_lds + ROWS;                       // [ROWS] 1 - SM activities of its rows
 
+    const int blocks = (m + 31) / 32;
+    // blocks of columns that a row has: in memory order as many as fit, on average, and the last one in part
+    const float row_blocks = by_memory ? (float)*feasible / (32.0f * (float)n) + 0.5f : (float)blocks;
     int staged_row0 = 0;                    // where the row map's entry 0 sits in the staged matrix
     if (segment) {                          // only entries [segment[0], segment[1]) of the row map
         row_map += segment[0];
@@ -794,14 +797,10 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         }
     };
 
-    const int chunks = (n + task_rows - 1) / task_rows, blocks = (m + 31) / 32;
-    // Tasks are dealt out in turn to `queues` groups of workgroups, each with a counter of its own: the first ones by
-    // the wavefront's place, then whoever is done takes the group's next.  (Two thousand wavefronts that end together at
-    // one counter waited 20 us for it: 1024 x 1024 54 / 44 us.)  By rows first, so that the two thousand
-    // tasks under way share a few rows' projections and every row of the matrix is written within a short time.
-    const int queues = (int)gridDim.x < MF_PAIR_QUEUES ? 1 : MF_PAIR_QUEUES, queue = blockIdx.x % queues;
-    const int team = ((int)gridDim.x - queue + queues - 1) / queues;       // workgroups of this one's group
-    int task = queue + queues * (int)(blockIdx.x / queues + team * wave), chunk = 0, before = 0;   // (before: tasks of earlier chunks)
+    const int task_rows = __builtin_amdgcn_readfirstlane(pair_task_rows(H, (float)n * row_blocks, units));
+    const int chunks = (n + task_rows - 1) / task_rows;
+    const int queue = blockIdx.x % pair_queues(gridDim.x);
+    int task = pair_task_by_place(blockIdx.x, wave, gridDim.x), chunk = 0, before = 0;   // (before: tasks of earlier chunks)
     unsigned long long scored = 0;
     while (true) {
         int block;
@@ -880,29 +879,13 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         scored += (unsigned long long)done * (unsigned)min(32, m - j0);
         int taken = 0;
         if (lane == 0) taken = atomicAdd(next_task + queue * MF_PAIR_QUEUE_STEP, 1);
-        task = queue + queues * (team * S::WAVES + __builtin_amdgcn_readfirstlane(taken));
+        task = pair_task_taken(queue, __builtin_amdgcn_readfirstlane(taken), gridDim.x, S::WAVES);
     }
     if (lane == 0) {                        // the workgroup's last wavefront adds for all
         atomicAdd(scored_lds, scored);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         if (atomicAdd(ended_lds, 1) == S::WAVES - 1) atomicAdd(evaluated, atomicAdd(scored_lds, 0ull));
     }
-}
-
-// Rows of a task.  A task costs its columns' projections and a few dependent reads, about as long as PAIR_SETUP_ROWS
-// rows, so it has 64 rows where there are enough tasks, and half as many while the wavefronts that take the most of
-// them are done earlier so: 2 rows for 64 x 64 pairs, 8 for 777 x 1501, 64 from 4096 x 8192 on.
-constexpr int PAIR_SETUP_ROWS = 2;
-int pair_task_rows(int rows, int blocks, int waves)
-{
-    int best = 64;
-    long long least = -1;
-    for (int t = 64; t >= 2; t >>= 1) {
-        const long long tasks = (long long)((rows + t - 1) / t) * blocks;
-        const long long work = (tasks + waves - 1) / waves * (t + PAIR_SETUP_ROWS);
-        if (least < 0 || work < least) { least = work; best = t; }
-    }
-    return best;
 }
 
 template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
@@ -919,15 +902,19 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
         ctx->kernels_configured |= flag;
     }
     const int blocks = (m + 31) / 32, units = ctx->n_cus > 0 ? ctx->n_cus : 1;
-    const int task_rows = pair_task_rows(grid_rows, blocks, units * S::PER_UNIT * S::WAVES);
-    const long long tasks = (long long)((grid_rows + task_rows - 1) / task_rows) * blocks;
-    const dim3 grid((unsigned)(tasks < units * S::PER_UNIT ? tasks : units * S::PER_UNIT));
+    // No more workgroups a compute unit than its wavefronts have tasks: each sets itself up, and three in one unit at once take
+    // longer (H = 64: 200 x 400 three to a unit 20 us, one 15; 500 x 1000 30 / 27 with two).
+    // (In memory order the kernel finds that there is less to do than this, and takes fewer rows a task.)
+    const int task_rows = pair_task_rows(H, (float)grid_rows * (float)blocks, (float)units);
+    const long long tasks = (long long)((grid_rows + task_rows - 1) / task_rows) * blocks, waves = (long long)units * S::WAVES;
+    const long long most = units * (tasks > waves * S::PER_UNIT ? S::PER_UNIT : (tasks + waves - 1) / waves);
+    const dim3 grid((unsigned)(tasks < most ? tasks : most));
     hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(S::THREADS), S::LDS_BYTES, ctx->stream,
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
-                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, task_rows, by_memory ? ctx->fit_len_on : nullptr,
-                       ctx->score_queue + launch * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP, times);
+                       p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, (float)units,
+                       by_memory ? ctx->feasible_pairs : nullptr, by_memory ? ctx->fit_len_on : nullptr, ctx->score_queue + launch * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP, times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }
