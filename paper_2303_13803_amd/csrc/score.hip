@@ -12,6 +12,7 @@
 // logistic, quantisation and memory-fit mask run in registers before one
 // coalesced int32 store.
 #include "report.h"
+#include <limits.h>
 #include <math.h>
 #include <type_traits>
 
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(256) void setup_kernel(SetupArgs a)
     note_time(a.times, AT_SCORE);
     const int side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
     if (side == 0 && blockIdx.x == 0)
-        for (int q = r; q < a.launches * MF_PAIR_QUEUES; q += 256) a.queue[q * MF_PAIR_QUEUE_STEP] = 0;
+        for (int q = r; q < a.launches * MF_PAIR_QUEUES; q += 256) *(int4 *)(a.queue + q * MF_PAIR_QUEUE_STEP) = make_int4(0, 0, 0, 0);
     if (side == 0 && r < 8) {
         a.range[r] = 0u;
         if (r == 0) { *a.pairs_evaluated = 0ull; if (a.feasible_pairs) *a.feasible_pairs = 0ull; if (a.largest) *a.largest = 0; }
@@ -449,8 +450,8 @@ template <int H> struct PairShape {
 // row / offline column that position t stands for, so a scattered subset
 // of rows or columns can be re-scored in place.
 //
-// Workgroups stay: each makes W2's pieces once, then its wavefronts take one task after the other, each on its own, the
-// rows' projections in LDS of their own, with no barrier.  What bounds the kernel is the matrix pipe at the clock that
+// Workgroups stay (but see pair_tasks.h): each makes W2's pieces once, then its wavefronts take one task after the other, each on its
+// own, the rows' projections in LDS of their own, with no barrier.  What bounds the kernel is the matrix pipe at the clock that
 // power allows: the matrix instructions alone, on operands as they occur here, take 17.9 ns each and 21.4 with four
 // vector instructions and the reads of W2 beside them (constants, which toggle nothing: 13.5), so the 9.6e8 of
 // 20,000 x 20,000 pairs take 16.8 and 20.1 ms.  A workgroup per tile of 64 x 256 pairs set itself up
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
     const unsigned *__restrict__ range, float units, const unsigned long long *__restrict__ feasible, const int32_t *__restrict__ fit_len,
-    int *__restrict__ next_task, unsigned long long *times)
+    int *__restrict__ next_task, int first, unsigned long long *times)
 {
     note_time(times, AT_PAIRS);
     using S = PairShape<H>;
@@ -509,6 +510,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     float *w3s_lds = wsm_lds + H;                          // [H] output weights of the slowdown unit
     unsigned long long *scored_lds = (unsigned long long *)(w3s_lds + H);  // pairs the workgroup has scored
     int *ended_lds = (int *)(scored_lds + 1);              // its wavefronts that are done
+    int *leave_lds = ended_lds + 1;                        // it leaves (before its set-up: nothing is left to do)
     float *pon_lds = w3s_lds + H + 4 + wave * S::WAVE_FLOATS;  // this wavefront's own: [ROWS][H] projections,
     float *mon_lds = pon_lds + ROWS * H;                   // [ROWS] memory fractions and
     float *son_lds = mon_lds + ROWS;                       // [ROWS] 1 - SM activities of its rows
@@ -522,6 +524,17 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         staged_row0 = segment[0];
         n = segment[1] - segment[0];
     }
+    const int task_rows = __builtin_amdgcn_readfirstlane(pair_task_rows(H, (float)n * row_blocks, units));
+    const int later = (int)gridDim.x - first, queue = blockIdx.x % pair_queues(first);
+    int *const next = next_task + queue * MF_PAIR_QUEUE_STEP;
+    if ((int)blockIdx.x >= first) {
+        if (tid == 0) *leave_lds = __hip_atomic_load(next + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (*leave_lds) return;
+        if (tid == 0) atomicAdd(next + 2, 1);
+    }
+    if (tid == 0 && ((int)blockIdx.x >= first || (int)blockIdx.x < pair_queues(first)))
+        __hip_atomic_store(next + 3, (int)device_time(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // SPLIT: the powers of two that scale layer-1 values and W2 into fp16's comfortable range
     float scale_p = 1.0f, scale_w = 1.0f;
     if (SPLIT) {
@@ -558,7 +571,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         }
     }
     if (tid < H) { b2_lds[tid] = b2[tid] * scale_acc; w3_lds[tid] = W3[tid] * unscale_acc; }
-    if (tid == 0) { *scored_lds = 0ull; *ended_lds = 0; }
+    if (tid == 0) { *scored_lds = 0ull; *ended_lds = 0; *leave_lds = 0; }
     if (PAIR_SM && tid < H) wsm_lds[tid] = w_sm[tid] * scale_p;
     if (SLOWDOWN && tid < H) w3s_lds[tid] = w3_slow[tid] * unscale_acc;
     __syncthreads();
@@ -797,12 +810,20 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         }
     };
 
-    const int task_rows = __builtin_amdgcn_readfirstlane(pair_task_rows(H, (float)n * row_blocks, units));
     const int chunks = (n + task_rows - 1) / task_rows;
-    const int queue = blockIdx.x % pair_queues(gridDim.x);
-    int task = pair_task_by_place(blockIdx.x, wave, gridDim.x), chunk = 0, before = 0;   // (before: tasks of earlier chunks)
+    const auto take = [&]() {
+        int taken = 0;
+        if (lane == 0) taken = atomicAdd(next, 1);
+        return pair_task_taken(queue, __builtin_amdgcn_readfirstlane(taken), first, S::WAVES);
+    };
+    int task = (int)blockIdx.x < first ? pair_task_by_place(blockIdx.x, wave, first) : take();
+    int chunk = 0, before = 0;              // (before: tasks of earlier chunks)
     unsigned long long scored = 0;
-    while (true) {
+    const bool turns = pair_takes_turns(blockIdx.x, first, later);
+    int left = turns ? max(PAIR_STAY_ROWS / task_rows, 1) : INT_MAX;       // tasks until it leaves
+    unsigned begun = (unsigned)device_time(), longest = 0;                 // of its tasks, in ticks
+    bool none = false;
+    for (;; task = take()) {
         int block;
         if (by_memory) {
             // a chunk of rows has as many tasks as blocks of columns fit its first row: a prefix of them
@@ -823,10 +844,10 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
                 }
                 had = __builtin_amdgcn_readfirstlane(__shfl(upto, 63));
             }
-            if (!beyond) break;
+            if (!beyond) { none = true; break; }
             block = task - before;
         } else {
-            if (task >= chunks * blocks) break;
+            if (task >= chunks * blocks) { none = true; break; }
             chunk = task / blocks;
             block = task % blocks;
         }
@@ -877,11 +898,21 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
             if (fit < here) break;          // (what rows left out have here lies beyond their feasible prefixes and is never read)
         }
         scored += (unsigned long long)done * (unsigned)min(32, m - j0);
-        int taken = 0;
-        if (lane == 0) taken = atomicAdd(next_task + queue * MF_PAIR_QUEUE_STEP, 1);
-        task = pair_task_taken(queue, __builtin_amdgcn_readfirstlane(taken), gridDim.x, S::WAVES);
+        if (--left == 0 || __builtin_amdgcn_readfirstlane(*(volatile int *)leave_lds)) break;
+        if (!turns && (int)blockIdx.x < first && later > 0) {
+            const int later_begun = __builtin_amdgcn_readfirstlane(__hip_atomic_load(next + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            const unsigned last = (unsigned)__builtin_amdgcn_readfirstlane(__hip_atomic_load(next + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            const unsigned now = (unsigned)device_time();
+            longest = max(longest, now - begun);
+            begun = now;
+            if (pair_may_leave(blockIdx.x, first, later, later_begun) && (int)(now - last) > 0 && now - last > PAIR_PATIENCE * longest) {
+                *(volatile int *)leave_lds = 1;
+                break;
+            }
+        }
     }
     if (lane == 0) {                        // the workgroup's last wavefront adds for all
+        if (none) __hip_atomic_store(next + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         atomicAdd(scored_lds, scored);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         if (atomicAdd(ended_lds, 1) == S::WAVES - 1) atomicAdd(evaluated, atomicAdd(scored_lds, 0ull));
@@ -908,13 +939,14 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
     const int task_rows = pair_task_rows(H, (float)grid_rows * (float)blocks, (float)units);
     const long long tasks = (long long)((grid_rows + task_rows - 1) / task_rows) * blocks, waves = (long long)units * S::WAVES;
     const long long most = units * (tasks > waves * S::PER_UNIT ? S::PER_UNIT : (tasks + waves - 1) / waves);
-    const dim3 grid((unsigned)(tasks < most ? tasks : most));
+    const int first = (int)(tasks < most ? tasks : most);
+    const dim3 grid((unsigned)(first + pair_later(tasks, waves * S::PER_UNIT, S::WAVES, grid_rows, blocks, first)));
     hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(S::THREADS), S::LDS_BYTES, ctx->stream,
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,
                        p->d_W3_slow, p->d_b3_slow, p->slow_limit, SPLIT ? ctx->score_range : nullptr, (float)units,
-                       by_memory ? ctx->feasible_pairs : nullptr, by_memory ? ctx->fit_len_on : nullptr, ctx->score_queue + launch * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP, times);
+                       by_memory ? ctx->feasible_pairs : nullptr, by_memory ? ctx->fit_len_on : nullptr, ctx->score_queue + launch * MF_PAIR_QUEUES * MF_PAIR_QUEUE_STEP, first, times);
     MF_HIP(hipGetLastError());
     return MF_OK;
 }

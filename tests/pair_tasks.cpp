@@ -1,5 +1,5 @@
 // Deals tasks of csrc/pair_tasks.h out on the CPU (test_pair_tasks.py): wavefronts take turns at random, and every task has
-// to be done once, whoever is slow.  And there are enough tasks, also where few pairs fit.
+// to be done once, whoever is slow and whoever leaves.  And there are enough tasks, also where few pairs fit.
 //
 //   pair_tasks CASES SEED     prints the first case in which a task was not done once, and ends with 1
 #include <stdio.h>
@@ -16,21 +16,46 @@ int main(int argc, char **argv)
     for (int c = 0; c < cases; ++c) {
         const int waves = upto(1) ? 8 : 4, first = 1 + upto(upto(1) ? 20 : 300), tasks = upto(upto(1) ? 50 : 6 * first * waves);
         std::vector<int> done(tasks, 0), counter(MF_PAIR_QUEUES, 0);
-        struct Wave { int workgroup, task; };
+        // places for `first` workgroups or fewer; later ones take turns with others or not, and how readily the first ones leave differs
+        const int later = upto(2) ? first + upto(upto(1) ? 10 : 300) : 0, places = 1 + upto(first - 1), each = 1 + upto(3), ready = upto(3);
+        std::vector<int> none(MF_PAIR_QUEUES, 0), begun(MF_PAIR_QUEUES, 0), leaves(first + later, 0), waves_of(first + later, 0);
+        struct Wave { int workgroup, task, left; };
         std::vector<Wave> busy;
-        for (int w = 0; w < first; ++w)
-            for (int v = 0; v < waves; ++v) busy.push_back({w, pair_task_by_place(w, v, first)});
-        while (!busy.empty()) {
+        int launched = 0, here = 0;
+        const auto taken = [&](int queue) { return pair_task_taken(queue, counter[queue]++, first, waves); };
+        while (true) {
+            while (here < places && launched < first + later) {
+                const int w = launched++, queue = w % pair_queues(first);
+                if (w >= first && none[queue]) continue;
+                if (w >= first) ++begun[queue];
+                for (int v = 0; v < waves; ++v)
+                    busy.push_back({w, w < first ? pair_task_by_place(w, v, first) : taken(queue), pair_takes_turns(w, first, later) ? each : 1 << 30});
+                waves_of[w] = waves;
+                ++here;
+            }
+            if (busy.empty()) break;
             const size_t k = rng() % busy.size();
-            Wave &wave = busy[k];
-            if (wave.task >= tasks) { wave = busy.back(); busy.pop_back(); continue; }
-            ++done[wave.task];
+            Wave wave = busy[k];
             const int queue = wave.workgroup % pair_queues(first);
-            wave.task = pair_task_taken(queue, counter[queue]++, first, waves);
+            bool ends = wave.task >= tasks;
+            if (ends) none[queue] = 1;
+            else {
+                ++done[wave.task];
+                ends = --wave.left == 0 || leaves[wave.workgroup];
+                if (!ends && wave.left > 1 << 20 && later > 0 && pair_may_leave(wave.workgroup, first, later, begun[queue]) && upto(3) < ready)
+                    ends = leaves[wave.workgroup] = 1;
+                if (!ends) wave.task = taken(queue);
+            }
+            if (!ends) busy[k] = wave;
+            else {
+                busy[k] = busy.back();
+                busy.pop_back();
+                if (--waves_of[wave.workgroup] == 0) --here;
+            }
         }
         for (int t = 0; t < tasks; ++t)
             if (done[t] != 1) {
-                printf("case %d: %d workgroups of %d, task %d of %d done %d times\n", c, first, waves, t, tasks, done[t]);
+                printf("case %d: %d and %d workgroups of %d, task %d of %d done %d times\n", c, first, later, waves, t, tasks, done[t]);
                 return 1;
             }
     }

@@ -45,6 +45,19 @@ def _compare(orc, r, Wg, sg, scale=None):
     return rel.max()
 
 
+def _pairs_in_tasks(r):
+    """Pairs that go through the predictor in order of memory: whole blocks of 32 columns beside every row that fits
+    their first one, whatever the rows of a task."""
+    on, off = r["x_on"][:, 0], np.sort(r["x_off"][:, 0])
+    return sum(int((on + off[j] <= np.float32(1.0)).sum()) * min(32, len(off) - j) for j in range(0, len(off), 32))
+
+
+def _some_rows(n):
+    """Rows at the edges of tasks and of the stretches of 16 rows in LDS, and every 97th."""
+    rows = {t + d for t in range(0, n, max(64, n // 16 // 64 * 64)) for d in (0, 1, 15, 16, 17, 31, 32, 63)} | set(range(0, n, 97)) | {n - 2, n - 1}
+    return np.array(sorted(i for i in rows if i < n))
+
+
 @pytest.mark.parametrize("cfg,n,m", [("C1", None, None), ("C2", None, None), ("C1", 1, 1), ("C1", 3, 5),
                                      ("C2", 130, 517), ("C3", 150, 700), ("C4", 97, 1031),
                                      ("C5", 64, 300), ("C3", 65, 257)])
@@ -87,6 +100,33 @@ def test_scores_of_tasks(mm, orc, cfg, n, m):
         assert (ordered == Wg).all()
         fits = float((Wg != INF).mean())                # whole blocks of columns are scored beside their rows: at least what fits
         assert fits <= ctx.last_timings()["pairs_evaluated_fraction"] + 1e-6 <= 1.0 + 2e-6
+    ctx.close()
+
+
+@pytest.mark.parametrize("cfg,n,m", [("C2", 8200, 8300), ("C4", 6100, 6300), ("C5", 9000, 20000)])
+def test_scores_of_long_passes(mm, orc, cfg, n, m):
+    """From eight tasks a wavefront on some workgroups leave and later ones take their place, most of those with
+    nothing left to do in the last case: nothing is missing, and nothing is done twice."""
+    r = synth.scheduling_round(cfg, 7, n=n, m=m)
+    ctx = mm.Context(n, m)
+    pred = ctx.predictor(dev_params(r["params"]), r["cfg"].scale)
+    x_on, x_off, got = dev(r["x_on"]), dev(r["x_off"]), []
+    for order, split in ((0, 1), (1, 1), (0, 0), (1, 0)):
+        ctx.set_option("fit_order", order)
+        ctx.set_option("score_split", split)
+        W = empty_matrix(n, m)
+        ctx.score_pairs(pred, x_on, x_off, W)
+        torch.cuda.synchronize()
+        expect = _pairs_in_tasks(r) if order else n * m
+        assert abs(ctx.last_timings()["pairs_evaluated_fraction"] - expect / (n * m)) <= 6e-8      # (a float; the smallest task is 3.6e-7 here)
+        got.append(W)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[2], got[3])
+    rows = _some_rows(n)
+    _, expect = orc.score_pairs(np.ascontiguousarray(r["x_on"][rows]), r["x_off"], r["params"], r["cfg"].scale)
+    for W in (got[1], got[3]):
+        Wg = W[torch.from_numpy(rows).cuda()].cpu().numpy()[:, :m]
+        assert ((Wg == INF) == (expect == INF)).all()
+        assert_weights_close(Wg, expect, r["cfg"].scale, expect != INF)
     ctx.close()
 
 
