@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
     note_largest<256>(mx, largest);
 }
 
-// The same through LDS, for rows that fit there (measured faster than the kernel above): a
+// The same through LDS: a
 // workgroup per row loads the staged row in whole lines - only as far as its pairs can share,
 // everything beyond is a mark anyway - picks each output's entry out of LDS, and stores the row
 // in whole lines: no scattered access reaches the caches.  LDS takes PLACE_LDS_ENTRIES of a row, so that a
@@ -392,7 +392,15 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t *__restrict__ 
 // read by fours and the reads of four steps are on their way together: 1.06 -> 0.73 ms, 20,000 x 20,000 0.66 -> 0.53, when they were read
 // one by one and waited for in every step.
 constexpr int PLACE_THREADS = 1024, PLACE_LDS_ENTRIES = 79 * 256;
-constexpr int64_t PLACE_LONGEST = 40704;                  // columns up to which this is used (beyond, the kernel above)
+
+// Which of the two.  A workgroup has a whole row with LDS, and a part of one without, which is faster where long rows do not give every compute unit its
+// two, and beyond 200,000 columns, most of whose prefixes do not fit in LDS.  A whole pass without / with, ms: 2000 x 45,000 3.28 / 2.37, 2000 x
+// 200,000 16.0 / 13.6, with a tenth of the pairs 4.09 / 3.72, and 16,000 x 48,900 7.98 / 7.12; 64 x 100,000 0.30 / 0.33, 30 x 60,000
+// 0.140 / 0.155, 192 x 200,000 with a tenth 0.69 / 0.74, 300 x 300,000 1.49 / 1.53.  Up to 40,704 columns they differ by 2 %, from 40,000 and for 30
+// rows and fewer by 5 to 11 %.
+constexpr int64_t PLACE_LONGEST = 200000, PLACE_SHORT = 40704;
+constexpr int PLACE_MANY = 512;
+bool place_by_lds(int n, int64_t columns) { return columns <= PLACE_SHORT || (n >= PLACE_MANY && columns <= PLACE_LONGEST); }
 
 __global__ __launch_bounds__(PLACE_THREADS) void place_lds_kernel(
     const int32_t *__restrict__ S, int64_t lds, const int32_t *__restrict__ rank_on,
@@ -1128,11 +1136,11 @@ int mf_launch_score(mf_ctx *ctx, const mf_predictor *preds, int n_types, const i
     }
     if (by_memory) {
         const int chunks = (m + 4095) / 4096 < 16 ? (m + 4095) / 4096 : 16;
-        // 0: entry by entry; 1: by fours; 2: by fours and past the caches, for a matrix that does not stay in the last one until
+        // 0: entry by entry; 1: by fours; 2: by fours and, with LDS, past the caches, for a matrix that does not stay in the last one until
         // it is read (256 MB): 20,000 x 40,000 0.05 ms less, 20,000 x 20,000 0.02
         int wide = ((uintptr_t)d_W & 15u) == 0 && (ldw & 3) == 0;
         if (wide && (int64_t)n * ldw * 4 > (256ll << 20)) wide = 2;
-        if (lds <= PLACE_LONGEST) {
+        if (place_by_lds(n, lds)) {
             hipLaunchKernelGGL(place_lds_kernel, dim3(n), dim3(PLACE_THREADS), 0, ctx->stream,
                                ctx->staged, lds, ctx->rank_on, ctx->rank_off, ctx->fit_len_on, n, m, d_W, ldw, wide,
                                ctx->largest_weight, ctx->times);

@@ -131,11 +131,11 @@ def test_scores_of_long_passes(mm, orc, cfg, n, m):
 
 
 @pytest.mark.parametrize("n,m,pad,shift", [(130, 517, 4, 0), (130, 517, 1, 0), (130, 518, 4, 1), (40, 20227, 4, 0), (40, 40703, 4, 0), (40, 40707, 4, 0),
-                                           (40, 40707, 1, 3), (1700, 40703, 4, 0), (70000, 1001, 4, 0)])
+                                           (40, 40707, 1, 3), (511, 40707, 1, 0), (512, 40706, 4, 0), (513, 45001, 1, 1), (1700, 40703, 4, 0), (1400, 60003, 4, 0), (512, 199998, 4, 0), (512, 200003, 4, 0), (70000, 1001, 4, 0)])
 def test_entries_come_to_their_places(mm, n, m, pad, shift):
     """Scored in memory order and put in place, or scored as they come: the same matrix.  Rows that end in a part of a
-    group, pitches and starts that are not whole groups, rows longer than what LDS takes of them and than the
-    kernel with LDS takes, and matrices beyond the last-level cache, which are stored past it."""
+    group, pitches and starts that are not whole groups, rows longer than what LDS takes of them, few and many
+    rows around the widths that the kernel with LDS takes of either, and matrices beyond the last-level cache, which are stored past it."""
     r = synth.scheduling_round("C2", 9, n=n, m=m)
     pitch = (m + pad - 1) // pad * pad
     ctx = mm.Context(n, m)
