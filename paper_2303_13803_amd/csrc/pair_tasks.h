@@ -22,6 +22,7 @@
 //
 // No dependence on the device: tests/pair_tasks.cpp deals tasks out on the CPU.
 #pragma once
+#include <math.h>
 
 #if defined(__HIPCC__)
 #define MF_PAIR_FN __host__ __device__ __forceinline__
@@ -45,24 +46,27 @@ constexpr int MF_PAIR_QUEUES = 16, MF_PAIR_QUEUE_STEP = 32;
 MF_PAIR_FN int pair_task_rows(int hidden, float row_blocks, float units)
 {
     const float share = row_blocks / (4.0f * units) * (hidden == 128 ? 2.7f : 4.0f);
-    int t = 2;
-    while (t < 64 && share > (float)(2 * t * t)) t *= 2;
-    return t;
+    int bits;
+    frexpf(share, &bits);               // share < 2^bits
+    bits >>= 1;
+    return bits < 1 ? 2 : bits > 6 ? 64 : 1 << bits;
 }
 
 // first: workgroups that begin with the launch.
-MF_PAIR_FN int pair_queues(int first) { return first < MF_PAIR_QUEUES ? 1 : MF_PAIR_QUEUES; }
+MF_PAIR_FN int pair_queue_bits(int first) { return first < MF_PAIR_QUEUES ? 0 : 4; }
+MF_PAIR_FN int pair_queues(int first) { return 1 << pair_queue_bits(first); }
+MF_PAIR_FN int pair_queue(int workgroup, int first) { return workgroup & (pair_queues(first) - 1); }
 
 // The task that a wavefront of such a workgroup begins with, and the one that the taken-th to take from the counter goes on with.
 MF_PAIR_FN int pair_task_by_place(int workgroup, int wave, int first)
 {
-    const int queues = pair_queues(first), queue = workgroup % queues, team = (first - queue + queues - 1) / queues;
-    return queue + queues * (workgroup / queues + team * wave);
+    const int bits = pair_queue_bits(first), queue = pair_queue(workgroup, first), team = (first - queue + pair_queues(first) - 1) >> bits;
+    return queue + (((workgroup >> bits) + team * wave) << bits);
 }
 MF_PAIR_FN int pair_task_taken(int queue, int taken, int first, int waves)
 {
-    const int queues = pair_queues(first), team = (first - queue + queues - 1) / queues;
-    return queue + queues * (team * waves + taken);
+    const int bits = pair_queue_bits(first), team = (first - queue + pair_queues(first) - 1) >> bits;
+    return queue + ((team * waves + taken) << bits);
 }
 
 // One workgroup in PAIR_TURN, 32 neighbours at a time: they are dispatched to the eight dies in turn and on a die to its four

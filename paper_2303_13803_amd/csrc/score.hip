@@ -490,7 +490,7 @@ template <int H> struct PairShape {
 // takes out again.  The result therefore does not depend on the size of the numbers.
 // For lane l, element t of its operand of k-block kb is hidden unit (l / 32) * H/2 + 8 kb + t, for
 // A (rows of W2) and B (pairs) alike.
-template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT>
+template <int H, bool PAIR_SM, bool SLOWDOWN, bool SPLIT, bool LONG>
 __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * PairShape<H>::WAVES / 4) void pair_mlp_kernel(
     const float *__restrict__ P_on, const float *__restrict__ P_off,
     const float *__restrict__ W2, const float *__restrict__ b2, const float *__restrict__ W3,
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
     const float *__restrict__ w_sm, const float *__restrict__ sm_on, const float *__restrict__ sm_off,
     const float *__restrict__ w3_slow, const float *__restrict__ b3_slow, float slow_limit,
     const unsigned *__restrict__ range, float units, const unsigned long long *__restrict__ feasible, const int32_t *__restrict__ fit_len,
-    int *__restrict__ next_task, int first, unsigned long long *times)
+    int *__restrict__ next_task, int begin, unsigned long long *times)
 {
     note_time(times, AT_PAIRS);
     using S = PairShape<H>;
@@ -533,15 +533,15 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         n = segment[1] - segment[0];
     }
     const int task_rows = __builtin_amdgcn_readfirstlane(pair_task_rows(H, (float)n * row_blocks, units));
-    const int later = (int)gridDim.x - first, queue = blockIdx.x % pair_queues(first);
+    const int first = LONG ? begin : (int)gridDim.x, later = (int)gridDim.x - first, queue = pair_queue(blockIdx.x, first);
     int *const next = next_task + queue * MF_PAIR_QUEUE_STEP;
-    if ((int)blockIdx.x >= first) {
+    if (LONG && (int)blockIdx.x >= first) {
         if (tid == 0) *leave_lds = __hip_atomic_load(next + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (*leave_lds) return;
         if (tid == 0) atomicAdd(next + 2, 1);
     }
-    if (tid == 0 && ((int)blockIdx.x >= first || (int)blockIdx.x < pair_queues(first)))
+    if (LONG && tid == 0 && ((int)blockIdx.x >= first || (int)blockIdx.x < pair_queues(first)))
         __hip_atomic_store(next + 3, (int)device_time(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // SPLIT: the powers of two that scale layer-1 values and W2 into fp16's comfortable range
     float scale_p = 1.0f, scale_w = 1.0f;
@@ -824,12 +824,12 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         if (lane == 0) taken = atomicAdd(next, 1);
         return pair_task_taken(queue, __builtin_amdgcn_readfirstlane(taken), first, S::WAVES);
     };
-    int task = (int)blockIdx.x < first ? pair_task_by_place(blockIdx.x, wave, first) : take();
+    int task = !LONG || (int)blockIdx.x < first ? pair_task_by_place(blockIdx.x, wave, first) : take();
     int chunk = 0, before = 0;              // (before: tasks of earlier chunks)
     unsigned long long scored = 0;
-    const bool turns = pair_takes_turns(blockIdx.x, first, later);
+    const bool turns = LONG && pair_takes_turns(blockIdx.x, first, later);
     int left = turns ? max(PAIR_STAY_ROWS / task_rows, 1) : INT_MAX;       // tasks until it leaves
-    unsigned begun = (unsigned)device_time(), longest = 0;                 // of its tasks, in ticks
+    unsigned begun = LONG ? (unsigned)device_time() : 0u, longest = 0;     // of its tasks, in ticks
     bool none = false;
     for (;; task = take()) {
         int block;
@@ -906,8 +906,8 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
             if (fit < here) break;          // (what rows left out have here lies beyond their feasible prefixes and is never read)
         }
         scored += (unsigned long long)done * (unsigned)min(32, m - j0);
-        if (--left == 0 || __builtin_amdgcn_readfirstlane(*(volatile int *)leave_lds)) break;
-        if (!turns && (int)blockIdx.x < first && later > 0) {
+        if (LONG && (--left == 0 || __builtin_amdgcn_readfirstlane(*(volatile int *)leave_lds))) break;
+        if (LONG && !turns && (int)blockIdx.x < first) {
             const int later_begun = __builtin_amdgcn_readfirstlane(__hip_atomic_load(next + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             const unsigned last = (unsigned)__builtin_amdgcn_readfirstlane(__hip_atomic_load(next + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             const unsigned now = (unsigned)device_time();
@@ -920,7 +920,7 @@ __global__ __launch_bounds__(PairShape<H>::THREADS, PairShape<H>::PER_UNIT * Pai
         }
     }
     if (lane == 0) {                        // the workgroup's last wavefront adds for all
-        if (none) __hip_atomic_store(next + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (LONG && none) __hip_atomic_store(next + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         atomicAdd(scored_lds, scored);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         if (atomicAdd(ended_lds, 1) == S::WAVES - 1) atomicAdd(evaluated, atomicAdd(scored_lds, 0ull));
@@ -936,8 +936,8 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
     // (the attribute belongs to the device, so what has been set is remembered per context)
     const unsigned flag = 1u << (5 + (H == 128 ? 8 : 0) + (PAIR_SM ? 4 : 0) + (SLOWDOWN ? 2 : 0) + (SPLIT ? 1 : 0));
     if (!(ctx->kernels_configured & flag)) {
-        MF_HIP(hipFuncSetAttribute((const void *)pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES));
+        for (const auto kernel : {pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT, false>, pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT, true>})
+            MF_HIP(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES));
         ctx->kernels_configured |= flag;
     }
     const int blocks = (m + 31) / 32, units = ctx->n_cus > 0 ? ctx->n_cus : 1;
@@ -948,8 +948,10 @@ int launch_pair_variant(mf_ctx *ctx, const mf_predictor *p, int n, int m, int32_
     const long long tasks = (long long)((grid_rows + task_rows - 1) / task_rows) * blocks, waves = (long long)units * S::WAVES;
     const long long most = units * (tasks > waves * S::PER_UNIT ? S::PER_UNIT : (tasks + waves - 1) / waves);
     const int first = (int)(tasks < most ? tasks : most);
-    const dim3 grid((unsigned)(first + pair_later(tasks, waves * S::PER_UNIT, S::WAVES, grid_rows, blocks, first)));
-    hipLaunchKernelGGL((pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT>), grid, dim3(S::THREADS), S::LDS_BYTES, ctx->stream,
+    // What turns cost, in code and registers, short passes do not pay: 1 us of 23 to 33 for 64 x 64 to 200 x 400 pairs with every option.
+    const long long later = pair_later(tasks, waves * S::PER_UNIT, S::WAVES, grid_rows, blocks, first);
+    hipLaunchKernelGGL((later ? pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT, true> : pair_mlp_kernel<H, PAIR_SM, SLOWDOWN, SPLIT, false>),
+                       dim3((unsigned)(first + later)), dim3(S::THREADS), S::LDS_BYTES, ctx->stream,
                        ctx->proj_on, ctx->proj_off, p->d_W2, p->d_b2, p->d_W3, p->d_b3,
                        ctx->mem_on, ctx->mem_off, n, m, p->scale, p->mem_limit, d_W, ldw, d_sigma, row_map, col_map,
                        by_memory ? 1 : 0, ctx->pairs_evaluated, segment, p->d_W1sm, ctx->sm_on, ctx->sm_off,

@@ -25,7 +25,7 @@ int main(int argc, char **argv)
         const auto taken = [&](int queue) { return pair_task_taken(queue, counter[queue]++, first, waves); };
         while (true) {
             while (here < places && launched < first + later) {
-                const int w = launched++, queue = w % pair_queues(first);
+                const int w = launched++, queue = pair_queue(w, first);
                 if (w >= first && none[queue]) continue;
                 if (w >= first) ++begun[queue];
                 for (int v = 0; v < waves; ++v)
@@ -36,7 +36,7 @@ int main(int argc, char **argv)
             if (busy.empty()) break;
             const size_t k = rng() % busy.size();
             Wave wave = busy[k];
-            const int queue = wave.workgroup % pair_queues(first);
+            const int queue = pair_queue(wave.workgroup, first);
             bool ends = wave.task >= tasks;
             if (ends) none[queue] = 1;
             else {
