@@ -364,7 +364,7 @@ struct alignas(256) CoreCtl {
     alignas(128) unsigned jump_pending[CORE_JUMP_PASSES + 1];
     // refinement
     alignas(128) unsigned failed[3];
-    unsigned told;                                       // ... and whether it has told the host itself
+    unsigned told;                                       // the launch has told the host itself how it ended
     // what the launch reports (phase -1: it did not get to one)
     alignas(128) CoreReport out;
 };
@@ -557,8 +557,6 @@ __device__ __noinline__ int bid_by_workgroup(const int32_t *line, int to, unsign
 // (out of line: rare, and a dozen divisions)
 __device__ __noinline__ int parts_out_of_line(int slices, int lines, int waves, bool prefixes) { return parts_of_line(slices, lines, waves, prefixes); }
 
-// Everything a workgroup carries through the launch.  LARGE: for problems whose first bids run on all dies, where
-// bidders may wait for better lists.  (Those few instructions cost a chain's step 3 % where one die does it all.)
 // One wavefront.  The host is told by the launch itself, not by the one behind it, and decides while this one ends and that one
 // clears the control block.  Being a function of its own it also ends the kernel's vector spills (51 in either instance before).  Rounds of
 // 777 x 1501 1.67 -> 1.64 ms, 1024 x 1024 2.07 -> 2.00, 3001 x 2003 4.05 -> 3.97, 4096 x 8192 6.37 -> 6.25, 20,000 x 20,000 39.6 -> 38.8.
@@ -574,6 +572,8 @@ __device__ __noinline__ void tell_host(CoreCtl *ctl, void *to, unsigned *told, u
     if (lane == 0) __hip_atomic_store(told, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Everything a workgroup carries through the launch.  LARGE: for problems whose first bids run on all dies, where
+// bidders may wait for better lists.  (Those few instructions cost a chain's step 3 % where one die does it all.)
 template <bool LARGE>
 struct Core {
     const CoreArgs &a;
