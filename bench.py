@@ -23,8 +23,8 @@ HBM_PEAK = 8.0e12              # byte/s
 # what the same counters read for a 1 GiB copy), valid for the named kernel at the named workload
 # only.  Set an entry to None when its kernel changes after the counters were taken.
 MEASURED_TRAFFIC = {
-    ("C4", "pair_mlp_kernel"): 2.255e9,
-    ("C4", "pair_mlp_kernel, fp32 products"): 2.058e9,
+    ("C4", "pair_mlp_kernel"): 4.095e9,
+    ("C4", "pair_mlp_kernel, fp32 products"): 3.846e9,
     ("C4", "round_kernel"): 1.612e9,
 }
 
@@ -189,7 +189,7 @@ def main():
                      "traffic": MEASURED_TRAFFIC.get((cfg.name, "pair_mlp_kernel")),
                      "note": "frac counts one product per pair of fp32 operands against the fp16 matrix peak; the kernel "
                              "issues three fp16 products for it (issued_frac).  The same layer with fp32 products "
-                             "(fp32_products.roofline) runs at 0.85 of the fp32 matrix peak and takes three times as long"},
+                             "(fp32_products.roofline) runs at 0.89 of the fp32 matrix peak and takes three times as long"},
         "roofline_bid_scan": {"bound": "hbm", "kernel": "round_kernel (first round of each phase: every row bids)",
                               "achieved": bulk_bytes / (bulk_ms * 1e-3) / 1e9, "peak": HBM_PEAK / 1e9,
                               "unit": "GB/s", "frac": bulk_bytes / (bulk_ms * 1e-3) / HBM_PEAK,

@@ -464,8 +464,8 @@ template <int H> struct PairShape {
 // vector instructions and the reads of W2 beside them (constants, which toggle nothing: 13.5), so the 9.6e8 of
 // 20,000 x 20,000 pairs take 16.8 and 20.1 ms.  A workgroup per tile of 64 x 256 pairs set itself up
 // for each (7 percent of its time, and nothing else fits into the compute unit meanwhile), waited for its slowest
-// wavefront, and was launched for every tile that cannot fit as well.  Before / now: 20,000 x 20,000 24.6 / 23.1 ms,
-// 20,000 x 40,000 with a tenth of the pairs 7.4 / 6.2, 4096 x 8192 2.14 / 1.91, 777 x 1501 0.137 / 0.091.
+// wavefront, and was launched for every tile that cannot fit as well.  Before / now: 20,000 x 20,000 23.0 / 22.2 ms,
+// 20,000 x 40,000 with a tenth of the pairs 6.85 / 5.9, 4096 x 8192 2.10 / 1.93, 777 x 1501 0.134 / 0.090.
 //
 // v_mfma_f32_32x32x2_f32 computes D[32x32] += A[32x2] B[2x32]
 // with lane l supplying A[l%32][l/32] and B[l/32][l%32]; we let the two k
