@@ -353,3 +353,27 @@ def test_argument_errors(mm):
         ctx.score_pairs(ctx.predictor(params, 2.0 ** 20), dev(big["x_on"]), dev(big["x_off"]), empty_matrix(9, 9))
     assert e.value.code == mm.ERR_SHAPE
     ctx.close()
+
+
+@pytest.mark.parametrize("cfg,n,m", [("C2", 300, 200), ("C4", 6100, 6300), ("C5", 13000, 900)])
+def test_a_captured_pass_is_the_same_every_time(mm, cfg, n, m):
+    """The counters of tasks, of turns and of ranks are cleared by kernels of the pass itself: replays, with other passes of the
+    context between them, find them so.  A short pass, a long one, and one whose workloads are sorted."""
+    r = synth.scheduling_round(cfg, 19, n=n, m=m)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = mm.Context(n, m)
+        pred, x_on, x_off, W, other = ctx.predictor(dev_params(r["params"]), r["cfg"].scale), dev(r["x_on"]), dev(r["x_off"]), empty_matrix(n, m), empty_matrix(n, m)
+        ctx.score_pairs(pred, x_on, x_off, W)
+        stream.synchronize()
+        expect = W.clone()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            ctx.score_pairs(pred, x_on, x_off, W)
+        for _ in range(4):
+            W.fill_(-7)
+            graph.replay()
+            ctx.score_pairs(pred, x_on, x_off, other)
+            stream.synchronize()
+            assert torch.equal(W, expect) and torch.equal(other, expect)
+        ctx.close()
