@@ -108,7 +108,7 @@ def test_scores_of_tasks(mm, orc, cfg, n, m):
 @pytest.mark.parametrize("with_limit", [False, True])
 def test_every_kind_of_predictor_in_many_tasks(mm, orc, cfg, n, m, split, with_sm, with_limit):
     """Wavefronts that take several tasks, of 16, 32 and 64 rows (one, two and four stretches of rows in LDS), with either kind of products,
-    SM share and slowdown unit.  The limit on the slowdown is the median of the checker's predictions, so half of the pairs are
+    SM share and slowdown unit.  The limit on the slowdown is the median of the oracle's predictions, so half of the pairs are
     above it; a float decides, so where it hides a pair is compared 1e-5 away from it, the tolerance of a score."""
     r = synth.scheduling_round(cfg, 17, n=n, m=m)
     full, sm = (synth.with_sm_input(r["params"], 12), (2, 3)) if with_sm else (r["params"], None)
